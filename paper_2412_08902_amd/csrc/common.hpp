@@ -32,6 +32,9 @@ constexpr int kSliceCols = 4096;       // condensed columns per workgroup; wider
 // ---- scalar path -------------------------------------------------------------------------------
 constexpr int kRowsPerGroup = 8;       // most consecutive rows one lane group may walk (short rows); also the narrowest group
 constexpr int kMidRow = 128;           // rows with more non-zeros than this get a whole wave
+// On a matrix of few rows the longest chain of dependent loads is what a call takes, so a wave takes rows over earlier
+// (30,000 rows, fp32, 64 columns: 16.4 -> 14.9 us; 16,000 rows, bf16, 128 columns: 11.1 -> 8.0 us); large ones lose 3-7 %.
+constexpr int kMidRowSmall = 64, kMidRowFewRows = 65536;
 constexpr int kFusedMidRow = 256;      // with the update stage fused in, rows up to this length stay in the workgroup's tile
 constexpr int kLongRow = 1024;         // rows with more non-zeros than this are cut into workgroup-sized segments
 constexpr int kSegLen = 2048;          // non-zeros per segment of a long row
@@ -143,6 +146,7 @@ hipError_t launch_build_segments(int32_t n_rows, const int32_t* rowptr, const in
 // ---- compute launchers -------------------------------------------------------------------------
 struct SpmmArgs {
     int32_t n_rows;
+    int32_t n_cols;       // rows of X
     const int32_t* rowptr;
     const int32_t* colind;
     const float* vals;
@@ -223,9 +227,15 @@ template <int VEC> __device__ inline void out_store(float* __restrict__ Y, int y
 // row goes to a.Y, which then is the aggregation workspace Z, and launch_update_rest finishes it.
 bool update_fusable(const SpmmArgs& a);
 bool mfma_update_fusable(const SpmmArgs& a);
+// what the scalar path's launch knows about its rows beyond the launch tables
+struct CsrHints {
+    int64_t nnz;          // non-zeros of the scalar-path windows
+    int64_t rows;
+    bool scattered;       // neighbouring rows are known to share few columns
+};
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
-                      int32_t mid_row, hipStream_t s, const UpdateArgs* upd = nullptr);
+                      int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd = nullptr);
 hipError_t launch_update_rest(const SpmmArgs& a, int32_t n_rest, const int32_t* rest_rows, const UpdateArgs& upd,
                               hipStream_t s);
 // dense product through the 16-row update kernel (narrow W), see spmm_csr_kernels.hip

@@ -936,13 +936,17 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         HC_HIP(launch_mfma_small(a, p->n_mfma_small, p->mfma_small_desc, p->wcols, p->erc, s_small, upd));
         if (ev) HC_HIP(hipEventRecord(ev[2], stream));
     }
+    // (the windows' distinct columns against their non-zeros say how much neighbouring rows share; a scalar-only plan does
+    // not count them)
+    const bool scattered = p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * p->total_ncols > 6 * p->nnz;
+    const CsrHints hints{p->nnz - p->nnz_mfma, (int64_t)p->n_csr * kH, scattered};
     if (upd)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, p->n_csr > 0 ? p->n_rows : 0, nullptr,
-                          p->route, p->fused_mid_row, stream, upd));
+                          p->route, p->fused_mid_row, hints, stream, upd));
     else
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows,
                           p->short_rows ? p->n_short : (p->n_short > 0 ? p->n_rows : 0), p->short_rows, p->route,
-                          p->mid_row, stream));
+                          p->mid_row, hints, stream));
     if (ev) HC_HIP(hipEventRecord(ev[3], stream));
     HC_HIP(launch_reduce_partials(a, p->n_multi, p->multi, partial, stream));
     if (ev) HC_HIP(hipEventRecord(ev[4], stream));
@@ -1000,7 +1004,7 @@ static hcspmm_status init_plan_header(hcspmm_plan* p, int32_t n_rows, int32_t n_
     p->W = (int32_t)(((int64_t)n_rows + kH - 1) / kH);
     p->rowptr = d_rowptr; p->colind = d_colind; p->vals = d_vals;
     p->opt = o;
-    p->mid_row = kMidRow;
+    p->mid_row = n_rows <= kMidRowFewRows ? kMidRowSmall : kMidRow;
     p->long_row = kLongRow;
     // tuning knobs for experiments (not part of the ABI): override the row-tier thresholds
     if (tune().mid_row >= 1) p->mid_row = tune().mid_row;
@@ -1292,7 +1296,7 @@ static hcspmm_status spmm_impl(const hcspmm_plan* plan, const void* d_X, int64_t
     if ((st = check_dense("X", d_X, ldx, d)) != HCSPMM_OK) return st;
     if ((st = check_dense("Y", d_Y, ldy, d)) != HCSPMM_OK) return st;
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d; a.x_dtype = x_dtype; a.Y = static_cast<float*>(d_Y); a.ldy = ldy; a.relu = 0;
     a.y_dtype = y_dtype;
     if (plan->n_mfma > 0 && !mfma_shape_supported(a)) {
@@ -1366,7 +1370,7 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
     if (((uintptr_t)d_workspace & 255) != 0) { set_error("workspace must be 256-byte aligned"); return HCSPMM_EINVAL; }
     hipStream_t s = static_cast<hipStream_t>(stream);
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_workspace; a.ldx = d_out; a.d = d_out; a.x_dtype = t_dtype; a.Y = static_cast<float*>(d_Y); a.ldy = ldy;
     a.relu = apply_relu ? 1 : 0;
     a.y_dtype = y_dtype;
@@ -1416,7 +1420,7 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* Z = static_cast<float*>(d_workspace);
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d_in; a.x_dtype = x_dtype; a.Y = Z; a.ldy = d_in; a.relu = 0;
     // The fused update pays where most rows can keep their tile on chip; rows that go through the
     // workspace anyway (wide matrix-path windows, mid and long rows) are finished 16 at a time, which
@@ -1492,7 +1496,7 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
     }
     if (plan->n_rows > 0) {
         SpmmArgs a{};
-        a.n_rows = plan->n_rows; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+        a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
         a.X = G; a.ldx = g_ld; a.d = d_out; a.x_dtype = HCSPMM_F32; a.Y = S; a.ldy = d_out; a.relu = 0;
         if (d_dX) {
             HC_HIP(launch_transpose(d_in, d_out, static_cast<const float*>(d_W), ldw, Wt, s));

@@ -2,27 +2,33 @@
 // (Alg. 1 gives the arithmetic, Alg. 3 the mapping idea: a group of lanes owns one output row and
 // each lane one slice of the dense width, so X rows are read as whole contiguous segments).
 //
-// wave64 mapping: a group of LPR lanes owns a row, every lane holds VEC consecutive output
-// columns; a 64-lane wave therefore works on 64/LPR rows (short rows) or on 64/LPR non-zeros of
-// the same row (mid and long rows) per load instruction.  Column indices and values are fetched
-// LPR at a time with one coalesced load per group and handed round with cross-lane reads; X is
-// read directly from global memory / L2 (the paper found staging X in shared memory a loss on
-// this path).  Three tiers by row length balance power-law degree distributions:
+// wave64 mapping: a group of 16 lanes -- one DPP row -- owns an output row, every lane holds NV
+// vectors of VEC consecutive columns; a wave works on four rows (short rows) or on four non-zeros
+// of the same row (mid and long rows) per load instruction.  Column indices and values are fetched
+// 16 at a time with one coalesced load per group and handed round by DPP row broadcasts, which are
+// operands of the address add and of the multiply-adds themselves: per non-zero and group one add,
+// NV loads and NV*VEC multiply-adds, nothing else.  (Handing them round through LDS, 64-bit row
+// addresses and 8-lane groups used to cost ~30 issue slots per load and 86 registers: a pass over
+// 115 M non-zeros took 0.76 ms with rows of 16 BYTES, i.e. with next to nothing to gather.)  Row
+// addresses are a uniform base plus a 32-bit byte offset; matrices X of 4 GiB and more take the
+// WIDE form with 64-bit row offsets.  X is read directly from global memory / L2 (the paper found
+// staging X in shared memory a loss on this path).  Three tiers by row length balance power-law
+// degree distributions:
 //   short rows  a lane group walks one to four consecutive rows in one flattened loop, and the
 //               workgroups reach the XCDs in runs so that neighbouring rows share an L2;
 //   mid rows    one wave per row, the groups stride over the row and combine with cross-lane adds;
 //   long rows   one workgroup per segment of kSegLen non-zeros, combined through LDS in a fixed
 //               order (and, for rows of several segments, through partial rows in memory).
+// Wide X may be cut into column slices that different XCDs own (see k_csr).
 #include <cstdlib>
+#include <utility>
 
 #include "common.hpp"
 #include "update_tile.hpp"
 
 namespace hcspmm {
 
-// XK: element kind of X -- 0 fp32, 1 bf16, 2 fp16.  16-bit elements are widened to fp32 on load;
-// all arithmetic of this path is fp32.
-template <int XK> struct XElem { static constexpr int size = XK == 0 ? 4 : 2; };
+constexpr int kGroup = 16;                                     // lanes per group: one DPP row
 
 template <int VEC> __device__ inline void vzero(float (&a)[VEC])
 {
@@ -30,327 +36,200 @@ template <int VEC> __device__ inline void vzero(float (&a)[VEC])
     for (int i = 0; i < VEC; ++i) a[i] = 0.f;
 }
 
-__device__ inline float widen16(uint32_t bits, int xk)
+template <int N, class F, int... I> __device__ __forceinline__ void unrolled_impl(F&& f, std::integer_sequence<int, I...>)
 {
-    if (xk == 1) return __uint_as_float(bits << 16);
-    const _Float16 h = __builtin_bit_cast(_Float16, (unsigned short)bits);
-    return (float)h;
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void unrolled(F&& f) { unrolled_impl<N>(f, std::make_integer_sequence<int, N>{}); }
+
+// lane I of the 16-lane row, in every lane of the row (a DPP operand: no instruction of its own where the user allows one)
+template <int I> __device__ __forceinline__ uint32_t row_bcast(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + I, 0xf, 0xf, true);
+}
+template <int I> __device__ __forceinline__ float row_bcast(float x) { return __uint_as_float(row_bcast<I>(__float_as_uint(x))); }
+
+// One gathered vector as it sits in registers (16-bit elements stay packed until they are multiplied).  Loads are
+// aligned to 4 bytes at least (2 for single 16-bit elements), which is all the hardware asks for.
+typedef uint32_t raw4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t raw2 __attribute__((ext_vector_type(2), aligned(4)));
+template <int BYTES> struct Raw { uint32_t w[BYTES / 4]; };
+template <> struct Raw<2> { uint32_t w[1]; };
+template <int BYTES> __device__ __forceinline__ void raw_load(const char* __restrict__ p, Raw<BYTES>& r)
+{
+    static_assert(BYTES == 2 || BYTES == 4 || BYTES == 8 || BYTES == 16, "vector sizes");
+    if constexpr (BYTES == 16) { const raw4 v = *reinterpret_cast<const raw4*>(p); r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w; }
+    else if constexpr (BYTES == 8) { const raw2 v = *reinterpret_cast<const raw2*>(p); r.w[0] = v.x; r.w[1] = v.y; }
+    else if constexpr (BYTES == 4) { r.w[0] = *reinterpret_cast<const uint32_t*>(p); }
+    else { r.w[0] = *reinterpret_cast<const unsigned short*>(p); }
 }
 
-// reads VEC consecutive elements starting at byte address p (aligned to the vector size)
-template <int VEC, int XK> __device__ inline void vload(const char* __restrict__ p, float (&x)[VEC])
+// XK: element kind of X -- 0 fp32, 1 bf16, 2 fp16.  16-bit elements are widened to fp32; all arithmetic is fp32.
+template <int XK> __device__ __forceinline__ float widened(const uint32_t* w, int i)
 {
-    if constexpr (XK == 0) {
-        static_assert(VEC == 4 || VEC == 2 || VEC == 1, "fp32 vectors are 1, 2 or 4 wide");
-        if constexpr (VEC == 4) { const float4 v = *reinterpret_cast<const float4*>(p); x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w; }
-        else if constexpr (VEC == 2) { const float2 v = *reinterpret_cast<const float2*>(p); x[0] = v.x; x[1] = v.y; }
-        else { x[0] = *reinterpret_cast<const float*>(p); }
-    } else {
-        static_assert(VEC == 8 || VEC == 4 || VEC == 1, "16-bit vectors are 1, 4 or 8 wide");
-        if constexpr (VEC == 8) {
-            const uint4 v = *reinterpret_cast<const uint4*>(p);
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    if constexpr (XK == 0) return __uint_as_float(w[i]);
+    else if constexpr (XK == 1) return __uint_as_float((i & 1) ? (w[i >> 1] & 0xffff0000u) : (w[i >> 1] << 16));
+    else return (float)__builtin_bit_cast(_Float16, (unsigned short)((i & 1) ? (w[i >> 1] >> 16) : (w[i >> 1] & 0xffffu)));
+}
+
+// The gather of one lane group: the 16 lanes hold NV vectors of VEC elements each, COLS columns of an X row in all.
+// SPLIT = 2: the two halves of the group work on two non-zeros at a time (slots 2t and 2t+1), 8 lanes covering the row, and
+// are added when the row is done.  A vector-memory instruction takes the CU's load path 16 clocks whether its lanes ask for
+// 8 or 16 bytes (measured on cache hits: 140 G rows of 128 bytes per second with 16 lanes x 8 bytes, 206 G with 8 x 16), so
+// rows of up to 128 bytes are read by 8 lanes; the second broadcast that this takes is free, the VALU has slack.
+template <int XK, int VEC, int NV, int SPLIT, bool WIDE> struct Gather {
+    static constexpr int ES = XK == 0 ? 4 : 2;
+    static constexpr int BYTES = VEC * ES;
+    static constexpr int LANES = kGroup / SPLIT;                // lanes per X row
+    static constexpr int COLS = LANES * VEC * NV;
+    static constexpr int N = VEC * NV;                          // columns per lane
+    static constexpr int WORDS = (BYTES < 4 ? 1 : BYTES / 4) * NV;
+    static constexpr int U = SPLIT == 2 ? 4 : WORDS <= 4 ? 8 : (WORDS <= 8 ? 4 : 2);   // rows requested before the first is used
+    static constexpr int RAW = BYTES;
+    // Waves per SIMD the registers are held to.  Short rows are bound by their chain of dependent loads, so 16-byte
+    // vectors with one accumulator set are squeezed into 64 registers for all 8 waves (community graph, bf16, 64 columns:
+    // 37.0 -> 32.2 us; power law, fp32, 32 columns: 36.7 -> 35.1 us); wider rows are bound by the traffic behind L2 and
+    // lose more to the squeeze (fp32, 128 columns: 120.8 -> 137 us).
+    static constexpr int WAVES = SPLIT == 2 ? 8 : (XK != 0 && VEC == 8 && NV == 1) ? 6 : 1;
+
+    const char* X;              // uniform: first column of the slice
+    uint64_t ldxb;              // bytes between rows (uniform)
+    uint32_t lane_off[NV];      // byte offset of this lane's vectors inside the slice
+    int shift[NV];              // leading elements of a vector that belong to the lane to the left
+    bool ok[NV];                // the vector has columns of the slice
+
+    // columns [c0, c0 + w) of X, w <= COLS; a vector that would stick out of the row is moved left so that it ends at the
+    // row's last column of the slice (the elements it then shares with its left neighbour are not stored)
+    __device__ __forceinline__ void init(const SpmmArgs& a, int c0, int w, int lig_)
+    {
+        const int lig = lig_ % LANES;
+        X = static_cast<const char*>(a.X);
+        ldxb = (uint64_t)a.ldx * ES;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { x[2 * i] = widen16(w[i] & 0xffffu, XK); x[2 * i + 1] = widen16(w[i] >> 16, XK); }
-        } else if constexpr (VEC == 4) {
-            const uint2 v = *reinterpret_cast<const uint2*>(p);
-            x[0] = widen16(v.x & 0xffffu, XK); x[1] = widen16(v.x >> 16, XK);
-            x[2] = widen16(v.y & 0xffffu, XK); x[3] = widen16(v.y >> 16, XK);
-        } else {
-            x[0] = widen16(*reinterpret_cast<const unsigned short*>(p), XK);
+        for (int v = 0; v < NV; ++v) {
+            const int col = (v * LANES + lig) * VEC;
+            ok[v] = col < w;
+            const int at = ok[v] ? min(col, w - VEC) : 0;       // (may reach left of c0, never left of column 0: d >= VEC)
+            shift[v] = ok[v] ? col - at : 0;
+            ok[v] = ok[v] && lig_ < LANES;                      // only the first half stores
+            lane_off[v] = (uint32_t)(max(c0 + at, 0) * ES);
         }
     }
-}
+    // what a lane keeps of a non-zero: byte offset of its X row (the column itself in the WIDE form)
+    __device__ __forceinline__ uint32_t key(int32_t c) const { return WIDE ? (uint32_t)c : (uint32_t)c * (uint32_t)ldxb; }
 
-template <int VEC> __device__ inline void vstore(float* __restrict__ p, const float (&x)[VEC], int relu)
-{
-    float y[VEC];
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) y[i] = relu ? fmaxf(x[i], 0.f) : x[i];
-    if constexpr (VEC == 8) {
-        *reinterpret_cast<float4*>(p) = make_float4(y[0], y[1], y[2], y[3]);
-        *reinterpret_cast<float4*>(p + 4) = make_float4(y[4], y[5], y[6], y[7]);
-    } else if constexpr (VEC == 4) {
-        *reinterpret_cast<float4*>(p) = make_float4(y[0], y[1], y[2], y[3]);
-    } else if constexpr (VEC == 2) {
-        *reinterpret_cast<float2*>(p) = make_float2(y[0], y[1]);
-    } else {
-        *p = y[0];
+    // step T's entry: slot T of the group, or slots 2T and 2T+1 for its two halves
+    template <int T> static __device__ __forceinline__ uint32_t slot(uint32_t x)
+    {
+        if constexpr (SPLIT == 1) return row_bcast<T>(x);
+        else return (uint32_t)__builtin_amdgcn_update_dpp((int)row_bcast<2 * T>(x), (int)x, 0x150 + 2 * T + 1, 0xf, 0xc, false);
     }
-}
-
-// One batch: the group's lanes hold up to LPR (column, value) pairs; every lane accumulates
-// val * X[col, c .. c+VEC) over the batch.  Slots past the end of the row carry the row's last
-// column with value 0, so the loads carry no branches and all of them are in flight together.
-// Xc already points at a valid column for every lane (lanes past the matrix width read column 0
-// and never store).
-template <int LPR, int VEC, int XK>
-__device__ inline void batch_accumulate(int32_t mc, float mv, int cnt, const char* __restrict__ Xc,
-                                        int64_t ldx /* bytes */, float (&acc)[VEC])
-{
-    constexpr int U = LPR < 8 ? LPR : 8;
-#pragma unroll 1
-    for (int t0 = 0; t0 < cnt; t0 += U) {
-        float x[U][VEC];
-        float v[U];
+    template <int T> __device__ __forceinline__ void load(uint32_t key_, Raw<RAW> (&x)[NV]) const
+    {
+        const uint32_t b = slot<T>(key_);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t c = __shfl(mc, t0 + u, LPR);
-            v[u] = __shfl(mv, t0 + u, LPR);
-            vload<VEC, XK>(Xc + (int64_t)c * ldx, x[u]);
+        for (int v = 0; v < NV; ++v) {
+            if constexpr (WIDE) raw_load<BYTES>(X + ((uint64_t)b * ldxb + lane_off[v]), x[v]);
+            else raw_load<BYTES>(X + (size_t)(b + lane_off[v]), x[v]);
         }
+    }
+    template <int T> __device__ __forceinline__ void add(float val, const Raw<RAW> (&x)[NV], float (&acc)[N]) const
+    {
+        const float w = __uint_as_float(slot<T>(__float_as_uint(val)));
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int v = 0; v < NV; ++v)
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) acc[i] = fmaf(v[u], x[u][i], acc[i]);
+            for (int i = 0; i < VEC; ++i) acc[v * VEC + i] = fmaf(w, widened<XK>(x[v].w, i), acc[v * VEC + i]);
     }
-}
-
-// (column, value) of non-zero k of a row ending at e (k may run past the end: value 0, last column)
-__device__ inline void fetch_entry(const int32_t* __restrict__ colind, const float* __restrict__ vals, int k, int e,
-                                   int32_t& c, float& v)
-{
-    const int kc = min(k, e - 1);
-    c = colind[kc];
-    const float t = vals[kc];
-    v = k < e ? t : 0.f;
-}
-
-// Accumulate a span [kb, ke) of one row taken LPR non-zeros at a time with stride `stride`
-// (stride = LPR when one group owns the span, larger when several groups share it).
-template <int LPR, int VEC, int XK>
-__device__ inline void span_accumulate(int kb, int ke, int stride, int lig,
-                                       const int32_t* __restrict__ colind, const float* __restrict__ vals,
-                                       const char* __restrict__ Xc, int64_t ldx, float (&acc)[VEC])
-{
-    if (kb >= ke) return;
-    int32_t mc, nc;
-    float mv, nv;
-    fetch_entry(colind, vals, kb + lig, ke, mc, mv);
-    for (int k0 = kb; k0 < ke; k0 += stride) {
-        // fetch the next batch's indices before this batch's X rows
-        fetch_entry(colind, vals, k0 + stride + lig, ke, nc, nv);
-        batch_accumulate<LPR, VEC, XK>(mc, mv, min(LPR, ke - k0), Xc, ldx, acc);
-        mc = nc;
-        mv = nv;
+    // steps T0 .. T0+COUNT-1: the rows requested together, then multiplied
+    template <int T0, int COUNT> __device__ __forceinline__ void steps(uint32_t key_, float val, float (&acc)[N]) const
+    {
+        Raw<RAW> x[COUNT][NV];
+        unrolled<COUNT>([&](auto u) { this->template load<T0 + decltype(u)::value>(key_, x[decltype(u)::value]); });
+        unrolled<COUNT>([&](auto u) { this->template add<T0 + decltype(u)::value>(val, x[decltype(u)::value], acc); });
     }
-}
-
-// ---- short rows -----------------------------------------------------------------------------
-// A group of LPR lanes walks rows_per_group (<= kRowsPerGroup) consecutive items (rows, or entries of row_list) in a
-// single flattened loop: each trip either moves to the next row (storing the finished one) or
-// consumes one batch of the current row, so groups of one wave stay busy on rows of unequal
-// length.  The rows' extents are fetched up front, one per lane.
-template <int LPR, int VEC, int XK>
-__device__ inline void csr_short_body(int64_t block, int32_t n_items, const int32_t* __restrict__ row_list,
-                                      const uint8_t* __restrict__ route, int rows_per_group, int mid_row,
-                                      const SpmmArgs& a)
-{
-    static_assert(LPR >= kRowsPerGroup, "a group must be able to hold one row extent per lane");
-    constexpr int GPB = 256 / LPR;
-    const int64_t blk = block * GPB + threadIdx.x / LPR;
-    const int lig = threadIdx.x % LPR;
-    const int64_t i0 = blk * rows_per_group;
-    if (i0 >= n_items) return;
-    const int nr = (int)min((int64_t)rows_per_group, (int64_t)n_items - i0);
-    int32_t my_row = -1, my_s = 0, my_e = 0;
-    if (lig < nr) {
-        my_row = row_list ? row_list[i0 + lig] : (int32_t)(i0 + lig);
-        my_s = a.rowptr[my_row];
-        my_e = a.rowptr[my_row + 1];
-        // walking every row: skip rows owned by the matrix path or by the mid/long-row kernels
-        if (!row_list && (route[my_row / kH] != 0 || my_e - my_s > mid_row)) my_row = -1;
+    // Up to 16 non-zeros (cnt of them, uniform within the group), U steps at a time.  Slots past the row's end carry the
+    // row's last column with value 0, so the loads carry no branches.
+    __device__ __forceinline__ void batch(uint32_t key_, float val, int cnt, float (&acc)[N]) const
+    {
+        if constexpr (SPLIT == 2 && XK == 0) {
+            // a wave whose groups all have more than half a batch left keeps the whole batch in flight (16-bit rows have twice
+            // the accumulators and would spill)
+            if (__all(cnt > kGroup / 2)) { steps<0, LANES>(key_, val, acc); return; }
+        }
+        unrolled<LANES / U>([&](auto blk) {
+            constexpr int T0 = decltype(blk)::value * U;
+            if (T0 == 0 || cnt > T0 * SPLIT) this->template steps<T0, U>(key_, val, acc);
+        });
     }
-    const char* __restrict__ X = static_cast<const char*>(a.X);
-    constexpr int ES = XElem<XK>::size;
-    const int64_t ldxb = a.ldx * ES;
-    for (int c0 = 0; c0 < a.d; c0 += LPR * VEC) {
-        const int c = c0 + lig * VEC;
-        const bool col_ok = c < a.d;
-        float acc[VEC];
-        vzero<VEC>(acc);
-        int j = 0, k = 0, e = 0;
-        int32_t row = -1;
-        int32_t mc = 0;
-        float mv = 0.f;
-        for (;;) {
-            if (k >= e) {
-                if (row >= 0 && col_ok) out_store<VEC>(a.Y, a.y_dtype, (int64_t)row * a.ldy + c, acc, a.relu);
-                row = -1;
-                while (j < nr && row < 0) {
-                    row = __shfl(my_row, j, LPR);
-                    k = __shfl(my_s, j, LPR);
-                    e = __shfl(my_e, j, LPR);
-                    ++j;
-                }
-                if (row < 0) break;
-                vzero<VEC>(acc);
-                if (k < e) fetch_entry(a.colind, a.vals, k + lig, e, mc, mv);
-                continue;                       // an empty row is stored (as zeros) on the next trip
-            }
-            int32_t nc;
-            float nv;
-            fetch_entry(a.colind, a.vals, k + LPR + lig, e, nc, nv);
-            batch_accumulate<LPR, VEC, XK>(mc, mv, min(LPR, e - k), X + (col_ok ? c : 0) * ES, ldxb, acc);
-            mc = nc;
+    // (key, value) of non-zero k of a row ending at e (k may run past the end: value 0, last column)
+    __device__ __forceinline__ void fetch(const SpmmArgs& a, int k, int e, uint32_t& key_, float& v) const
+    {
+        const int kc = min(k, e - 1);
+        const int32_t c = a.colind[kc];
+        const float t = a.vals[kc];
+        key_ = key(c);
+        v = k < e ? t : 0.f;
+    }
+    // a span [kb, ke) of one row taken 16 non-zeros at a time with stride `stride` (16 when one group owns the span)
+    __device__ __forceinline__ void span(const SpmmArgs& a, int kb, int ke, int stride, int lig, float (&acc)[N]) const
+    {
+        if (kb >= ke) return;
+        uint32_t mk, nk;
+        float mv, nv;
+        fetch(a, kb + lig, ke, mk, mv);
+        for (int k0 = kb; k0 < ke; k0 += stride) {
+            fetch(a, k0 + stride + lig, ke, nk, nv);            // the next batch's indices before this batch's X rows
+            batch(mk, mv, min(kGroup, ke - k0), acc);
+            mk = nk;
             mv = nv;
-            k += LPR;
         }
     }
-}
-
-// ---- short rows with the update stage fused in ------------------------------------------------
-// Same walk as csr_short_body, but a workgroup covers exactly 16 (or, with 8-lane groups, 32) list
-// entries and a finished row goes to a 16 x d tile in LDS instead of memory; after a barrier the
-// four waves share the tile(s), each multiplying it by an interleaved quarter (half) of W's
-// 16-column blocks on the matrix cores, and write act(Z W) for the rows the workgroup owns
-// (Section V-A: the aggregation result of a window stays on chip for the update).
-// The width d must fit one pass of the group (d <= LPR*VEC) and be a multiple of 16.
-template <int LPR, int VEC> struct FusedShape {
-    static constexpr int G = 64 / LPR;                          // lane groups per wave
-    static constexpr int RPG = LPR / 16 > 1 ? LPR / 16 : 1;     // consecutive rows per group
-    static constexpr int ROWS = 4 * G * RPG;                    // list entries per workgroup
-    static constexpr int T = ROWS / 16;                         // 16-row tiles per workgroup
-    static constexpr int LDZ = LPR * VEC + 4;
-    static_assert(ROWS % 16 == 0 && (T == 1 || T == 2), "one or two tiles per workgroup");
+    // a row is done: the two halves' sums are added (the first half's lanes hold the result)
+    static __device__ __forceinline__ void finish(float (&acc)[N])
+    {
+        if constexpr (SPLIT == 2) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                acc[i] += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(acc[i]), 0x128 /* row_ror:8 */, 0xf, 0xf, true));
+        }
+    }
+    // stores the lane's columns of output row `row` (element type a.y_dtype); c0: first column of the slice
+    __device__ __forceinline__ void store(const SpmmArgs& a, int y_vec, int64_t row, int c0, int lig, const float (&acc)[N]) const
+    {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if (!ok[v]) continue;
+            const int64_t off = row * a.ldy + c0 + (v * LANES + lig) * VEC - shift[v];
+            float y[VEC];
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) y[i] = acc[v * VEC + i];
+            if (y_vec && shift[v] == 0) {
+                out_store<VEC>(a.Y, a.y_dtype, off, y, a.relu);
+            } else {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    const float one[1] = {y[i]};
+                    if (i >= shift[v]) out_store<1>(a.Y, a.y_dtype, off + i, one, a.relu);
+                }
+            }
+        }
+    }
+    // the same into a row of fp32 partial sums (or an LDS tile) starting at p
+    __device__ __forceinline__ void store_f32(float* p, int lig, const float (&acc)[N]) const
+    {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if (!ok[v]) continue;
+            float* q = p + (v * LANES + lig) * VEC - shift[v];
+#pragma unroll
+            for (int i = 0; i < VEC; ++i)
+                if (i >= shift[v]) q[i] = acc[v * VEC + i];
+        }
+    }
 };
 
-template <int LPR, int VEC, int XK>
-__device__ inline void csr_short_fused_body(int64_t block, int32_t n_items, const int32_t* __restrict__ row_list,
-                                            const uint8_t* __restrict__ route, int mid_row, const SpmmArgs& a,
-                                            const UpdateArgs& u, float* __restrict__ zt, int32_t* __restrict__ rows_s)
-{
-    using S = FusedShape<LPR, VEC>;
-    constexpr int RPG = S::RPG, LDZ = S::LDZ;
-    static_assert(LPR >= RPG, "a group must be able to hold one row extent per lane");
-    const int64_t b0 = (int64_t)block * S::ROWS;                // first list entry of the workgroup
-    if (b0 >= n_items) return;                                  // whole workgroup past the end
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int gw = threadIdx.x / LPR, lig = threadIdx.x % LPR;  // group within the workgroup
-    const int64_t i0 = b0 + gw * RPG;
-    const int nr = (int)max((int64_t)0, min((int64_t)RPG, (int64_t)n_items - i0));
-    int32_t my_row = -1, my_s = 0, my_e = 0;
-    if (lig < nr) {
-        my_row = row_list ? row_list[i0 + lig] : (int32_t)(i0 + lig);
-        my_s = a.rowptr[my_row];
-        my_e = a.rowptr[my_row + 1];
-        if (!row_list && (route[my_row / kH] != 0 || my_e - my_s > mid_row)) my_row = -1;
-    }
-    if (lig < RPG) rows_s[gw * RPG + lig] = my_row;
-    const char* __restrict__ X = static_cast<const char*>(a.X);
-    constexpr int ES = XElem<XK>::size;
-    const int64_t ldxb = a.ldx * ES;
-    const int c = lig * VEC;
-    const bool col_ok = c < a.d;
-    float acc[VEC];
-    vzero<VEC>(acc);
-    int j = 0, k = 0, e = 0, slot = 0;
-    int32_t row = -1;
-    int32_t mc = 0;
-    float mv = 0.f;
-    for (;;) {
-        if (k >= e) {
-            if (row >= 0 && col_ok) vstore<VEC>(zt + (gw * RPG + slot) * LDZ + c, acc, 0);
-            row = -1;
-            while (j < nr && row < 0) {
-                row = __shfl(my_row, j, LPR);
-                k = __shfl(my_s, j, LPR);
-                e = __shfl(my_e, j, LPR);
-                slot = j;
-                ++j;
-            }
-            if (row < 0) break;
-            vzero<VEC>(acc);
-            if (k < e) fetch_entry(a.colind, a.vals, k + lig, e, mc, mv);
-            continue;
-        }
-        int32_t nc;
-        float nv;
-        fetch_entry(a.colind, a.vals, k + LPR + lig, e, nc, nv);
-        batch_accumulate<LPR, VEC, XK>(mc, mv, min(LPR, e - k), X + (col_ok ? c : 0) * ES, ldxb, acc);
-        mc = nc;
-        mv = nv;
-        k += LPR;
-    }
-    __syncthreads();
-    if (u.keep_z) store_tile_rows(zt, LDZ, rows_s, S::ROWS, a.d, a.Y, a.ldy, threadIdx.x, 256);
-    constexpr int WPT = 4 / S::T;                               // waves sharing one tile
-    const int tile = wave / WPT;
-    update_tile16(zt + tile * 16 * LDZ, LDZ, rows_s + tile * 16, a.d, u, lane, wave % WPT, WPT);
-}
-
-// ---- mid rows: one wave per row -------------------------------------------------------------
-template <int LPR, int VEC, int XK>
-__device__ inline void csr_mid_body(int64_t block, int32_t n_mid, const int32_t* __restrict__ mid_rows,
-                                    const SpmmArgs& a, int min_len = 0 /* rows this short belong to another tier */)
-{
-    constexpr int G = 64 / LPR;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t item = block * 4 + wave;
-    if (item >= n_mid) return;
-    const int32_t row = mid_rows[item];
-    const int32_t s = a.rowptr[row], e = a.rowptr[row + 1];
-    if (e - s <= min_len) return;
-    const int g = lane / LPR, lig = lane % LPR;
-    const char* __restrict__ X = static_cast<const char*>(a.X);
-    constexpr int ES = XElem<XK>::size;
-    const int64_t ldxb = a.ldx * ES;
-    for (int c0 = 0; c0 < a.d; c0 += LPR * VEC) {
-        const int c = c0 + lig * VEC;
-        const bool col_ok = c < a.d;
-        float acc[VEC];
-        vzero<VEC>(acc);
-        span_accumulate<LPR, VEC, XK>(s + g * LPR, e, G * LPR, lig, a.colind, a.vals, X + (col_ok ? c : 0) * ES, ldxb, acc);
-        // butterfly over the G groups: same operation order on every run
-#pragma unroll
-        for (int off = LPR; off < 64; off <<= 1)
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
-        if (g == 0 && col_ok) out_store<VEC>(a.Y, a.y_dtype, (int64_t)row * a.ldy + c, acc, a.relu);
-    }
-}
-
-// ---- long rows: one workgroup per segment of a row ------------------------------------------
-template <int LPR, int VEC, int XK>
-__device__ inline void csr_long_body(int64_t block, const Segment* __restrict__ segs, float* __restrict__ partial,
-                                     float* __restrict__ red /* LDS, 256*VEC floats */, const SpmmArgs& a)
-{
-    constexpr int G = 256 / LPR;
-    const Segment sg = segs[block];
-    const int g = threadIdx.x / LPR, lig = threadIdx.x % LPR;
-    const char* __restrict__ X = static_cast<const char*>(a.X);
-    constexpr int ES = XElem<XK>::size;
-    const int64_t ldxb = a.ldx * ES;
-    for (int c0 = 0; c0 < a.d; c0 += LPR * VEC) {
-        const int c = c0 + lig * VEC;
-        const bool col_ok = c < a.d;
-        float acc[VEC];
-        vzero<VEC>(acc);
-        span_accumulate<LPR, VEC, XK>(sg.k_begin + g * LPR, sg.k_end, G * LPR, lig, a.colind, a.vals,
-                                      X + (col_ok ? c : 0) * ES, ldxb, acc);
-        // fixed-order tree over the G groups: the result does not depend on scheduling
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) red[(g * LPR + lig) * VEC + i] = acc[i];
-        __syncthreads();
-        for (int st = G / 2; st > 0; st >>= 1) {
-            if (g < st) {
-#pragma unroll
-                for (int i = 0; i < VEC; ++i)
-                    red[(g * LPR + lig) * VEC + i] += red[((g + st) * LPR + lig) * VEC + i];
-            }
-            __syncthreads();
-        }
-        if (g == 0 && col_ok) {
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) acc[i] = red[lig * VEC + i];
-            if (sg.slot < 0) out_store<VEC>(a.Y, a.y_dtype, (int64_t)sg.row * a.ldy + c, acc, a.relu);
-            else vstore<VEC>(partial + (int64_t)sg.slot * a.d + c, acc, 0);
-        }
-        __syncthreads();
-    }
-}
-
-// ---- one launch for all three tiers ---------------------------------------------------------
+// ---- launch description ---------------------------------------------------------------------
 // Workgroups are numbered heaviest first: long-row segments, then mid rows (four per workgroup),
 // then the blocks of short rows, so the short rows fill the machine while the last long rows
 // drain instead of each tier waiting for the previous one's tail.
@@ -364,70 +243,273 @@ struct CsrWork {
     const int32_t* row_list;
     const uint8_t* route;
     int32_t rows_per_group;
+    int32_t wave_rows;          // short rows get a wave each
     int32_t mid_row;
-    int32_t xcd_chunk;          // short-row workgroups per XCD-local run (0: plain order)
-    int64_t mid_blocks;         // workgroups of the mid tier (padded to whole rounds of runs when xcd_chunk_mid > 0)
-    int32_t xcd_chunk_mid;
+    int64_t seg_blocks, mid_blocks, short_blocks;   // workgroups of each tier and slice, padded (surplus ones exit at once)
+    int32_t run, run_mid;       // workgroups per XCD-local run of the short and mid tiers (0: plain order)
+    int32_t n_slices, slice_w;  // column slices of X
+    int32_t y_vec;              // Y rows allow vector stores
 };
 
-template <int LPR, int VEC, int XK>
-__global__ __launch_bounds__(256) void k_csr(CsrWork wk, SpmmArgs a)
+// Block b of a tier of `blocks` workgroups per slice -> (slice, block within the tier).
+// Workgroups go to the eight XCDs round-robin by their linear id, and each XCD has an L2 of its own.
+//  * The tier's blocks are handed out in runs of `run` consecutive ones that stay on one XCD: neighbouring rows -- which
+//    share columns in graphs with any locality -- meet in one L2 close in time, while all XCDs still advance through the
+//    matrix side by side (rows sorted by degree stay balanced).
+//  * With 2, 4 or 8 column slices XCD x works on slice x % n_slices only, so that its L2 holds rows of ONE slice.
+//  * Other slice counts take the slices one after the other.
+__device__ __forceinline__ int64_t csr_block(int64_t b, int64_t blocks, int run, int n_slices, int& slice)
 {
-    __shared__ float red[256 * VEC];
-    int64_t b = blockIdx.x;
-    if (b < wk.n_segs) {
-        csr_long_body<LPR, VEC, XK>(b, wk.segs, wk.partial, red, a);
-        return;
-    }
-    b -= wk.n_segs;
-    const int64_t mid_blocks = wk.mid_blocks;
-    if (b < mid_blocks) {
-        if (wk.xcd_chunk_mid > 0) {                              // same XCD-local runs as for the short rows below
-            const int64_t x = blockIdx.x & 7, q = b >> 3;
-            b = ((q / wk.xcd_chunk_mid) * 8 + x) * wk.xcd_chunk_mid + q % wk.xcd_chunk_mid;
+    const int x = blockIdx.x & 7;
+    slice = 0;
+    int nsub = 8, sub = x;
+    if (n_slices > 1) {
+        if (n_slices == 2 || n_slices == 4 || n_slices == 8) {
+            nsub = 8 / n_slices;
+            slice = x & (n_slices - 1);
+            sub = x / n_slices;
+            const int64_t q = b >> 3;
+            if (run < 1) run = 1;
+            return ((q / run) * nsub + sub) * run + q % run;
         }
-        csr_mid_body<LPR, VEC, XK>(b, wk.n_mid, wk.mid_rows, a);
+        slice = (int)(b / blocks);
+        b -= slice * blocks;
+    }
+    if (run <= 0) return b;
+    const int64_t q = b >> 3;
+    return ((q / run) * nsub + sub) * run + q % run;
+}
+
+// ---- short rows -----------------------------------------------------------------------------
+// A group walks rows_per_group (<= kRowsPerGroup) consecutive items (rows, or entries of row_list) in a
+// single flattened loop: each trip either moves to the next row (storing the finished one) or
+// consumes one batch of the current row, so groups of one wave stay busy on rows of unequal
+// length.  The rows' extents are fetched up front, one per lane.  `done(row, slot, acc)` takes a finished row.
+template <class G, class Done>
+__device__ __forceinline__ void walk_rows(const G& g, const SpmmArgs& a, int lig, int nr, int32_t my_row, int32_t my_s, int32_t my_e,
+                                          Done&& done)
+{
+    float acc[G::N];
+    vzero(acc);
+    int j = 0, k = 0, e = 0, slot = 0;
+    int32_t row = -1;
+    uint32_t mk = 0;
+    float mv = 0.f;
+    for (;;) {
+        if (k >= e) {
+            if (row >= 0) {
+                G::finish(acc);
+                done(row, slot, acc);
+            }
+            row = -1;
+            while (j < nr && row < 0) {
+                row = __shfl(my_row, j, kGroup);
+                k = __shfl(my_s, j, kGroup);
+                e = __shfl(my_e, j, kGroup);
+                slot = j;
+                ++j;
+            }
+            if (row < 0) break;
+            vzero(acc);
+            if (k < e) g.fetch(a, k + lig, e, mk, mv);
+            continue;                       // an empty row is finished (as zeros) on the next trip
+        }
+        uint32_t nk;
+        float nv;
+        g.fetch(a, k + kGroup + lig, e, nk, nv);
+        g.batch(mk, mv, min(kGroup, e - k), acc);
+        mk = nk;
+        mv = nv;
+        k += kGroup;
+    }
+}
+
+// extents of the items i0 .. i0+nr-1, one per lane; rows owned by the matrix path or by the mid/long tiers get row -1
+__device__ __forceinline__ void row_extents(int64_t i0, int lig, int nr, const int32_t* __restrict__ row_list,
+                                            const uint8_t* __restrict__ route, int mid_row, const SpmmArgs& a, int32_t& row,
+                                            int32_t& s, int32_t& e)
+{
+    row = -1; s = 0; e = 0;
+    if (lig < nr) {
+        row = row_list ? row_list[i0 + lig] : (int32_t)(i0 + lig);
+        s = a.rowptr[row];
+        e = a.rowptr[row + 1];
+        if (!row_list && (route[row / kH] != 0 || e - s > mid_row)) row = -1;
+    }
+}
+
+// ---- mid rows: one wave per row -------------------------------------------------------------
+template <class G>
+__device__ __forceinline__ void csr_wave_row(int32_t row, int s, int e, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a)
+{
+    const int lane = threadIdx.x & 63, gi = lane / kGroup, lig = lane % kGroup;
+    for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
+        G g;
+        g.init(a, c0, min(G::COLS, c_end - c0), lig);
+        float acc[G::N];
+        vzero(acc);
+        g.span(a, s + gi * kGroup, e, 64, lig, acc);
+        G::finish(acc);
+        // butterfly over the four groups: same operation order on every run
+#pragma unroll
+        for (int off = kGroup; off < 64; off <<= 1)
+#pragma unroll
+            for (int i = 0; i < G::N; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
+        if (gi == 0) g.store(a, wk.y_vec, row, c0, lig, acc);
+    }
+}
+
+template <class G>
+__device__ __forceinline__ void csr_mid_body(int64_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a,
+                                             int min_len = 0 /* rows this short belong to another tier */)
+{
+    const int64_t item = block * 4 + (threadIdx.x >> 6);
+    if (item >= wk.n_mid) return;
+    const int32_t row = wk.mid_rows[item];
+    const int32_t s = a.rowptr[row], e = a.rowptr[row + 1];
+    if (e - s <= min_len) return;
+    csr_wave_row<G>(row, s, e, c_begin, c_end, wk, a);
+}
+
+template <class G>
+__device__ __forceinline__ void csr_short_body(int64_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a)
+{
+    static_assert(kGroup >= kRowsPerGroup, "a group must be able to hold one row extent per lane");
+    const int lig = threadIdx.x % kGroup;
+    if (wk.wave_rows) {                                         // few rows: a wave each
+        const int64_t item = block * 4 + (threadIdx.x >> 6);
+        if (item >= wk.n_items) return;
+        int32_t row, s, e;
+        row_extents(item, 0, 1, wk.row_list, wk.route, wk.mid_row, a, row, s, e);
+        if (row >= 0) csr_wave_row<G>(row, s, e, c_begin, c_end, wk, a);
         return;
     }
-    b -= mid_blocks;
-    if (wk.xcd_chunk > 0) {
-        // Workgroups go to the eight XCDs round-robin by their linear id, and each XCD has an L2 of
-        // its own.  Hand out the short rows in runs of xcd_chunk consecutive workgroups, run r to XCD
-        // r % 8: neighbouring rows -- which share columns in graphs with any locality -- then meet in
-        // one L2 close in time, while all XCDs still advance through the matrix side by side (rows
-        // sorted by degree stay balanced).
-        const int64_t x = blockIdx.x & 7, q = b >> 3;
-        b = ((q / wk.xcd_chunk) * 8 + x) * wk.xcd_chunk + q % wk.xcd_chunk;
+    const int64_t i0 = (block * (256 / kGroup) + threadIdx.x / kGroup) * wk.rows_per_group;
+    if (i0 >= wk.n_items) return;
+    const int nr = (int)min((int64_t)wk.rows_per_group, (int64_t)wk.n_items - i0);
+    int32_t my_row, my_s, my_e;
+    row_extents(i0, lig, nr, wk.row_list, wk.route, wk.mid_row, a, my_row, my_s, my_e);
+    for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
+        G g;
+        g.init(a, c0, min(G::COLS, c_end - c0), lig);
+        walk_rows(g, a, lig, nr, my_row, my_s, my_e,
+                  [&](int32_t row, int, const float (&acc)[G::N]) { g.store(a, wk.y_vec, row, c0, lig, acc); });
     }
-    csr_short_body<LPR, VEC, XK>(b, wk.n_items, wk.row_list, wk.route, wk.rows_per_group, wk.mid_row, a);
+}
+
+// ---- short rows with the update stage fused in ------------------------------------------------
+// Same walk as csr_short_body, but a workgroup covers exactly 16 list entries and a finished row goes to a 16 x d tile in
+// LDS instead of memory; after a barrier the four waves share the tile, each multiplying it by an interleaved quarter of
+// W's 16-column blocks on the matrix cores, and write act(Z W) for the rows the workgroup owns
+// (Section V-A: the aggregation result of a window stays on chip for the update).
+// The width d must fit one pass of the group (d <= G::COLS) and be a multiple of 16.
+template <class G>
+__device__ __forceinline__ void csr_short_fused_body(int64_t block, const CsrWork& wk, const SpmmArgs& a, const UpdateArgs& u,
+                                                     float* __restrict__ zt, int32_t* __restrict__ rows_s)
+{
+    constexpr int LDZ = G::COLS + 4;
+    const int64_t b0 = block * 16;                              // first list entry of the workgroup
+    if (b0 >= wk.n_items) return;                               // whole workgroup past the end
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int gw = threadIdx.x / kGroup, lig = threadIdx.x % kGroup;
+    const int nr = b0 + gw < wk.n_items ? 1 : 0;
+    int32_t my_row, my_s, my_e;
+    row_extents(b0 + gw, lig, nr, wk.row_list, wk.route, wk.mid_row, a, my_row, my_s, my_e);
+    if (lig == 0) rows_s[gw] = my_row;
+    G g;
+    g.init(a, 0, a.d, lig);
+    walk_rows(g, a, lig, nr, my_row, my_s, my_e,
+              [&](int32_t, int, const float (&acc)[G::N]) { g.store_f32(zt + gw * LDZ, lig, acc); });
+    __syncthreads();
+    if (u.keep_z) store_tile_rows(zt, LDZ, rows_s, 16, a.d, a.Y, a.ldy, threadIdx.x, 256);
+    update_tile16(zt, LDZ, rows_s, a.d, u, lane, wave, 4);
+}
+
+// ---- long rows: one workgroup per segment of a row ------------------------------------------
+template <class G>
+__device__ __forceinline__ void csr_long_body(int64_t block, int c_begin, int c_end, const CsrWork& wk,
+                                              float* __restrict__ red /* LDS, 256 * G::N floats */, const SpmmArgs& a)
+{
+    constexpr int NG = 256 / kGroup;
+    if (block >= wk.n_segs) return;
+    const Segment sg = wk.segs[block];
+    const int gi = threadIdx.x / kGroup, lig = threadIdx.x % kGroup;
+    for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
+        G g;
+        g.init(a, c0, min(G::COLS, c_end - c0), lig);
+        float acc[G::N];
+        vzero(acc);
+        g.span(a, sg.k_begin + gi * kGroup, sg.k_end, 256, lig, acc);
+        G::finish(acc);
+        // fixed-order tree over the groups: the result does not depend on scheduling
+#pragma unroll
+        for (int i = 0; i < G::N; ++i) red[i * 256 + threadIdx.x] = acc[i];
+        __syncthreads();
+        for (int st = NG / 2; st > 0; st >>= 1) {
+            if (gi < st) {
+#pragma unroll
+                for (int i = 0; i < G::N; ++i) red[i * 256 + threadIdx.x] += red[i * 256 + threadIdx.x + st * kGroup];
+            }
+            __syncthreads();
+        }
+        if (gi == 0) {
+#pragma unroll
+            for (int i = 0; i < G::N; ++i) acc[i] = red[i * 256 + lig];
+            if (sg.slot < 0) g.store(a, wk.y_vec, sg.row, c0, lig, acc);
+            else g.store_f32(wk.partial + (int64_t)sg.slot * a.d + c0, lig, acc);
+        }
+        __syncthreads();
+    }
+}
+
+// ---- one launch for all three tiers ---------------------------------------------------------
+template <class G>
+__global__ __launch_bounds__(256, G::WAVES) void k_csr(CsrWork wk, SpmmArgs a)
+{
+    __shared__ float red[256 * G::N];
+    int64_t b = blockIdx.x;
+    int slice;
+    if (b < wk.seg_blocks * wk.n_slices) {
+        b = csr_block(b, wk.seg_blocks, 0, wk.n_slices, slice);
+        const int c0 = slice * wk.slice_w;
+        csr_long_body<G>(b, c0, min(a.d, c0 + wk.slice_w), wk, red, a);
+        return;
+    }
+    b -= wk.seg_blocks * wk.n_slices;
+    if (b < wk.mid_blocks * wk.n_slices) {
+        b = csr_block(b, wk.mid_blocks, wk.run_mid, wk.n_slices, slice);
+        const int c0 = slice * wk.slice_w;
+        csr_mid_body<G>(b, c0, min(a.d, c0 + wk.slice_w), wk, a);
+        return;
+    }
+    b -= wk.mid_blocks * wk.n_slices;
+    b = csr_block(b, wk.short_blocks, wk.run, wk.n_slices, slice);
+    const int c0 = slice * wk.slice_w;
+    csr_short_body<G>(b, c0, min(a.d, c0 + wk.slice_w), wk, a);
 }
 
 // The same launch with the update stage fused into the short rows; long and mid rows write their
 // aggregated rows to a.Y (the workspace Z) and are finished by k_update_rest.
-template <int LPR, int VEC, int XK>
+template <class G>
 __global__ __launch_bounds__(256) void k_csr_fused(CsrWork wk, SpmmArgs a, UpdateArgs u)
 {
-    using S = FusedShape<LPR, VEC>;
-    __shared__ float red[256 * VEC];
-    __shared__ float zt[S::ROWS * S::LDZ];
-    __shared__ int32_t rows16[S::ROWS];
+    constexpr int kTile = 16 * (G::COLS + 4), kRed = 256 * G::N;
+    __shared__ float lds[kTile > kRed ? kTile : kRed];          // the reduction of a long row and the tile of short rows never meet
+    __shared__ int32_t rows16[16];
     int64_t b = blockIdx.x;
-    if (b < wk.n_segs) {
-        csr_long_body<LPR, VEC, XK>(b, wk.segs, wk.partial, red, a);
+    int slice;
+    if (b < wk.seg_blocks) {
+        csr_long_body<G>(b, 0, a.d, wk, lds, a);
         return;
     }
-    b -= wk.n_segs;
-    const int64_t mid_blocks = wk.mid_blocks;
-    if (b < mid_blocks) {
-        csr_mid_body<LPR, VEC, XK>(b, wk.n_mid, wk.mid_rows, a, wk.mid_row);   // the fused tier takes rows up to mid_row
+    b -= wk.seg_blocks;
+    if (b < wk.mid_blocks) {
+        csr_mid_body<G>(b, 0, a.d, wk, a, wk.mid_row);          // the fused tier takes rows up to mid_row
         return;
     }
-    b -= mid_blocks;
-    if (wk.xcd_chunk > 0) {                                     // XCD-local runs, as in k_csr
-        const int64_t x = blockIdx.x & 7, q = b >> 3;
-        b = ((q / wk.xcd_chunk) * 8 + x) * wk.xcd_chunk + q % wk.xcd_chunk;
-    }
-    csr_short_fused_body<LPR, VEC, XK>(b, wk.n_items, wk.row_list, wk.route, wk.mid_row, a, u, zt, rows16);
+    b -= wk.mid_blocks;
+    b = csr_block(b, wk.short_blocks, wk.run, 1, slice);
+    csr_short_fused_body<G>(b, wk, a, u, lds, rows16);
 }
 
 // ---- rows the fused kernels did not finish: gather their aggregated rows and apply the update ---
@@ -497,116 +579,146 @@ __global__ __launch_bounds__(256) void k_reduce_partials(int32_t n_multi, const 
 }
 
 // ---- dispatch ---------------------------------------------------------------------------------
-struct CsrShape { int lpr, vec; };
+struct CsrShape { int vec, nv, split; bool wide; };
 
-static CsrShape pick_shape(const SpmmArgs& a, const float* partial)
+// Vectors of up to 16 bytes per lane: 8 lanes per row for rows of 65 to 128 bytes (two rows at a time, see Gather), 16 lanes
+// otherwise, with 4 bytes (2 for 16-bit X) each for the narrow rows and several vectors each for the wide ones.  A row of X
+// needs no more than 4-byte alignment for that; 16-bit X with odd rows or an odd base is read element by element.
+static CsrShape pick_shape(const SpmmArgs& a)
 {
-    int vec = 1;
-    const uintptr_t px = (uintptr_t)a.X, py = (uintptr_t)a.Y, pp = (uintptr_t)partial;
-    const bool y4 = a.ldy % 4 == 0 && py % 16 == 0 && pp % 16 == 0;
-    if (a.x_dtype == HCSPMM_F32) {
-        if (a.d % 4 == 0 && a.ldx % 4 == 0 && px % 16 == 0 && y4) vec = 4;
-        else if (a.d % 2 == 0 && a.ldx % 2 == 0 && a.ldy % 2 == 0 && px % 8 == 0 && py % 8 == 0 && pp % 8 == 0) vec = 2;
-    } else {
-        if (a.d % 8 == 0 && a.ldx % 8 == 0 && px % 16 == 0 && y4) vec = 8;
-        else if (a.d % 4 == 0 && a.ldx % 4 == 0 && px % 8 == 0 && y4) vec = 4;
+    const bool f32 = a.x_dtype == HCSPMM_F32;
+    const int es = f32 ? 4 : 2, per16 = 16 / es;
+    CsrShape sh{1, 1, 1, false};
+    if (f32 || (a.d % 2 == 0 && a.ldx % 2 == 0 && (uintptr_t)a.X % 4 == 0)) {
+        if (a.d * es > 64) {
+            sh.vec = per16;
+            if (a.d * es <= 128) sh.split = 2;
+        } else {
+            while (sh.vec < per16 && kGroup * sh.vec < a.d) sh.vec *= 2;
+        }
     }
-    // a group needs at least kRowsPerGroup lanes; narrow the vectors of narrow matrices instead of idling lanes
-    const int min_vec = 1;
-    while (vec > min_vec && (a.d + vec - 1) / vec < kRowsPerGroup) {
-        vec >>= 1;
-        if (a.x_dtype != HCSPMM_F32 && vec == 2) vec = 1;      // 16-bit inputs have no 2-wide variant
+    const int most = f32 ? 4 : (sh.vec == 1 ? 4 : 2);
+    while (sh.nv < most && kGroup / sh.split * sh.vec * sh.nv < a.d) sh.nv *= 2;
+    if (!f32 && sh.vec == 1 && sh.nv > 1) sh.nv = 4;
+    // 32-bit byte offsets reach 4 GiB of X (the last row is read to its end)
+    sh.wide = ((uint64_t)(a.n_cols > 0 ? a.n_cols - 1 : 0) * (uint64_t)a.ldx + (uint64_t)a.d) * es >= ((uint64_t)1 << 32);
+    return sh;
+}
+static int shape_cols(const CsrShape& sh) { return kGroup / sh.split * sh.vec * sh.nv; }
+
+#define HC_CSR_ONE(FN, XK, V, NVV, SP) do { if (sh.wide) { FN(XK, V, NVV, SP, true); } else { FN(XK, V, NVV, SP, false); } } while (0)
+#define HC_CSR_DISPATCH32(FN)                                                                      \
+    if (sh.vec == 1) HC_CSR_ONE(FN, 0, 1, 1, 1);                                                   \
+    else if (sh.split == 2) HC_CSR_ONE(FN, 0, 4, 1, 2);                                            \
+    else if (sh.nv == 1) HC_CSR_ONE(FN, 0, 4, 1, 1);                                               \
+    else if (sh.nv == 2) HC_CSR_ONE(FN, 0, 4, 2, 1);                                               \
+    else HC_CSR_ONE(FN, 0, 4, 4, 1);
+#define HC_CSR_DISPATCH16(FN, XK)                                                                  \
+    if (sh.vec == 1) { if (sh.nv == 1) HC_CSR_ONE(FN, XK, 1, 1, 1); else HC_CSR_ONE(FN, XK, 1, 4, 1); }  \
+    else if (sh.vec == 2) HC_CSR_ONE(FN, XK, 2, 1, 1);                                             \
+    else if (sh.split == 2) HC_CSR_ONE(FN, XK, 8, 1, 2);                                           \
+    else if (sh.nv == 1) HC_CSR_ONE(FN, XK, 8, 1, 1);                                              \
+    else HC_CSR_ONE(FN, XK, 8, 2, 1);
+#define HC_CSR_DISPATCH(FN)                                                                        \
+    if (a.x_dtype == HCSPMM_F32) { HC_CSR_DISPATCH32(FN) }                                         \
+    else if (a.x_dtype == HCSPMM_BF16) { HC_CSR_DISPATCH16(FN, 1) }                                \
+    else { HC_CSR_DISPATCH16(FN, 2) }
+
+// Column slices.  More than 512 bytes of a row per lane group would cost the registers that keep enough loads in flight
+// (fp32, 256 columns, 30,000 nodes: 138 us in one slice of four vectors per lane, 57 us in two slices), so wider rows are
+// always cut.  Beyond that, slices trade index and row-offset traffic (8 bytes per non-zero and slice) and one more set of
+// row chains for L2 hits: an XCD that works on one slice of every row keeps twice or four times as many rows of it.  That
+// pays where an X row is read often compared with the size of X -- measured on power-law graphs, fp32, 128 columns:
+// 30,000 nodes of degree 20: 37.7 -> 25.1 us with two slices, 169,000 of 15: 118 -> 111 us, 500,000 of 60: 1973 -> 1850 us
+// and 1754 us with four; but 500,000 of degree 6: 261 -> 285 us, 2.4 M of 51: 8.63 -> 8.69 ms -- i.e. from about five
+// non-zeros per row for every 64 MiB of X.  128-byte slices win over 256-byte ones from about 40 non-zeros per row (the
+// per-row chain is then small; 60,000 nodes of degree 100: 271 / 228 / 201 us with 1 / 2 / 4 slices).  Neighbouring rows
+// that share their columns (community graphs) already meet in one L2 and lose 6 %: they are left whole.
+static int pick_slices(const SpmmArgs& a, const CsrHints& h, int32_t& slice_w)
+{
+    const int64_t es = a.x_dtype == HCSPMM_F32 ? 4 : 2, row = a.d * es;
+    int64_t most = 512;                                         // bytes of a row per slice
+    const double degree = h.rows > 0 ? (double)h.nnz / (double)h.rows : 0.0;
+    if (h.scattered && degree >= 5.0 * ((double)a.n_cols * (double)row / (64.0 * (1 << 20)))) {
+        if (degree >= 40.0 && row >= 256) most = 128;
+        else if (row >= 512) most = 256;
     }
-    const int lanes = (a.d + vec - 1) / vec;       // lanes needed to cover the width once
-    int lpr = kRowsPerGroup;
-    while (lpr < 64 && lpr < lanes) lpr <<= 1;
-    return {lpr, vec};
+    int64_t n = (row + most - 1) / most;
+    while (n > 1 && n < 8 && (n & (n - 1)) != 0 && (row + n - 2) / (n - 1) <= 512) --n;     // a count that XCDs can own
+    const int64_t align = 128 / es;                             // whole 128-byte lines per slice
+    slice_w = (int32_t)(((a.d + n - 1) / n + align - 1) / align * align);
+    const int n_slices = (int)((a.d + slice_w - 1) / slice_w);
+    if (n_slices <= 1) slice_w = a.d;
+    return n_slices;
 }
 
-#define HC_CSR_CASES(FN, XK, V)                                                                    \
-    switch (sh.lpr) {                                                                              \
-        case 8: FN(8, V, XK); break;                                                               \
-        case 16: FN(16, V, XK); break;                                                             \
-        case 32: FN(32, V, XK); break;                                                             \
-        default: FN(64, V, XK); break;                                                             \
-    }
-
-#define HC_CSR_DISPATCH(FN)                                                                        \
-    if (a.x_dtype == HCSPMM_F32) {                                                                 \
-        if (sh.vec == 4) { HC_CSR_CASES(FN, 0, 4) } else if (sh.vec == 2) { HC_CSR_CASES(FN, 0, 2) } else { HC_CSR_CASES(FN, 0, 1) } \
-    } else if (a.x_dtype == HCSPMM_BF16) {                                                         \
-        if (sh.vec == 8) { HC_CSR_CASES(FN, 1, 8) } else if (sh.vec == 4) { HC_CSR_CASES(FN, 1, 4) } else { HC_CSR_CASES(FN, 1, 1) } \
-    } else {                                                                                       \
-        if (sh.vec == 8) { HC_CSR_CASES(FN, 2, 8) } else if (sh.vec == 4) { HC_CSR_CASES(FN, 2, 4) } else { HC_CSR_CASES(FN, 2, 1) } \
-    }
-
-// The fused update needs the whole aggregated row in one pass of a lane group, fp32 X read as
-// float4/float2 and a width that the update's K loop takes 16 at a time.
+// The fused update needs the whole aggregated row in one pass of a lane group and a width that the update's K loop takes
+// 16 at a time.
 bool update_fusable(const SpmmArgs& a)
 {
     if (a.d % 16 != 0 || a.d < 16 || a.d > 256) return false;
-    const CsrShape sh = pick_shape(a, nullptr);
-    const bool vec_ok = a.x_dtype == HCSPMM_F32 ? (sh.vec == 4 || sh.vec == 2) : (sh.vec == 8 || sh.vec == 4);
-    return vec_ok && sh.lpr * sh.vec >= a.d && a.ldy % 4 == 0 && (uintptr_t)a.Y % 16 == 0 && mfma_update_fusable(a);
+    const CsrShape sh = pick_shape(a);
+    return shape_cols(sh) >= a.d && a.ldy % 4 == 0 && (uintptr_t)a.Y % 16 == 0 && mfma_update_fusable(a);
 }
 
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
-                      int32_t mid_row, hipStream_t s, const UpdateArgs* upd)
+                      int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd)
 {
-    const CsrShape sh = pick_shape(a, partial);
-    // XCD-local runs (see k_csr): tiers of at least 1024 workgroups are padded to whole rounds of
-    // eight runs; the surplus workgroups exit at once
+    CsrShape sh = pick_shape(a);
+    CsrWork wk{};
+    wk.n_segs = n_segs; wk.segs = segs; wk.partial = partial; wk.n_mid = n_mid; wk.mid_rows = mid_rows;
+    wk.n_items = n_items; wk.row_list = row_list; wk.route = route; wk.mid_row = mid_row;
+    // vector stores need Y rows aligned for what a lane stores at once (16-bit results leave in pieces of up to 8 bytes)
+    const int yv = sh.vec < 4 ? sh.vec : 4;
+    wk.y_vec = a.ldy % yv == 0 && (uintptr_t)a.Y % (yv * (a.y_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
+    wk.n_slices = 1;
+    wk.slice_w = a.d;
+    if (!upd) {
+        wk.n_slices = pick_slices(a, hints, wk.slice_w);
+        if (wk.n_slices > 1) {
+            SpmmArgs t = a;
+            t.d = wk.slice_w;
+            const bool wide = sh.wide;
+            sh = pick_shape(t);
+            sh.wide = wide;
+        }
+    }
+    // XCD-local runs (see csr_block): tiers of at least 1024 workgroups are padded to whole rounds of runs over the XCDs
+    // that share a slice; the surplus workgroups exit at once
     int run = 32;
     if (tune().xcd_chunk >= 0) run = tune().xcd_chunk;
-    auto pad_runs = [run](int64_t n, int32_t& chunk) {
-        chunk = 0;
-        if (run <= 0 || n < 1024) return n;
-        chunk = run;
-        return (n + 8 * run - 1) / (8 * run) * (8 * (int64_t)run);
+    const bool owned = wk.n_slices == 2 || wk.n_slices == 4 || wk.n_slices == 8;
+    const int nsub = owned ? 8 / wk.n_slices : 8;
+    auto pad_runs = [&](int64_t n, int32_t& r) {
+        r = (run <= 0 || n < 1024) ? 0 : run;
+        const int64_t unit = (int64_t)nsub * (r > 0 ? r : 1);
+        return (r > 0 || owned) ? (n + unit - 1) / unit * unit : n;
     };
+    wk.seg_blocks = owned ? ((int64_t)n_segs + nsub - 1) / nsub * nsub : n_segs;
     if (upd) {
-        const int rows_per_wg = sh.lpr == 8 ? 32 : 16;          // FusedShape<LPR, VEC>::ROWS
-        int32_t xcd_chunk = 0;
-        const int64_t short_blocks = pad_runs(((int64_t)n_items + rows_per_wg - 1) / rows_per_wg, xcd_chunk);
-        const int64_t blocks = (int64_t)n_segs + ((int64_t)n_mid + 3) / 4 + short_blocks;
+        wk.rows_per_group = 1;
+        wk.mid_blocks = ((int64_t)n_mid + 3) / 4;
+        wk.short_blocks = pad_runs(((int64_t)n_items + 15) / 16, wk.run);
+        const int64_t blocks = wk.seg_blocks + wk.mid_blocks + wk.short_blocks;
         if (blocks <= 0) return hipSuccess;
-        CsrWork wk{n_segs, segs, partial, n_mid, mid_rows, n_items, row_list, route, 0, mid_row, xcd_chunk, ((int64_t)n_mid + 3) / 4, 0};
-#define HC_LAUNCH_CSRF(L, V, K) hipLaunchKernelGGL((k_csr_fused<L, V, K>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a, *upd)
-#define HC_CSRF_CASES(V, K)                                                                        \
-    switch (sh.lpr) {                                                                              \
-        case 8: HC_LAUNCH_CSRF(8, V, K); break;                                                    \
-        case 16: HC_LAUNCH_CSRF(16, V, K); break;                                                  \
-        case 32: HC_LAUNCH_CSRF(32, V, K); break;                                                  \
-        default: HC_LAUNCH_CSRF(64, V, K); break;                                                  \
-    }
-        if (a.x_dtype == HCSPMM_F32) {
-            if (sh.vec == 4) { HC_CSRF_CASES(4, 0) } else if (sh.vec == 2) { HC_CSRF_CASES(2, 0) } else return hipErrorInvalidValue;
-        } else if (a.x_dtype == HCSPMM_BF16) {
-            if (sh.vec == 8) { HC_CSRF_CASES(8, 1) } else if (sh.vec == 4) { HC_CSRF_CASES(4, 1) } else return hipErrorInvalidValue;
-        } else {
-            if (sh.vec == 8) { HC_CSRF_CASES(8, 2) } else if (sh.vec == 4) { HC_CSRF_CASES(4, 2) } else return hipErrorInvalidValue;
-        }
-#undef HC_CSRF_CASES
+#define HC_LAUNCH_CSRF(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr_fused<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a, *upd)
+        HC_CSR_DISPATCH(HC_LAUNCH_CSRF)
 #undef HC_LAUNCH_CSRF
         return hipGetLastError();
     }
-    // consecutive rows per lane group: measured best when a wave walks about four to eight rows in
-    // all (one row per group for 8- and 16-lane groups, two for 32, four for 64) -- more rows per
-    // group serialise dependent loads, fewer pay the per-row set-up too often -- and only while the
-    // launch still has tens of thousands of waves to hide the rows' dependent-load latencies
-    int rpg = sh.lpr / 16 > 1 ? sh.lpr / 16 : 1;
-    while (rpg > 1 && ((int64_t)n_items / rpg) * sh.lpr / 64 < 32768) rpg >>= 1;
+    int rpg = 1;
     if (tune().rpg >= 1 && tune().rpg <= kRowsPerGroup) rpg = tune().rpg;
+    wk.rows_per_group = rpg;
     const int64_t n_groups = ((int64_t)n_items + rpg - 1) / rpg;
-    const int gpb = 256 / sh.lpr;
-    int32_t xcd_chunk = 0, xcd_chunk_mid = 0;
-    const int64_t short_blocks = pad_runs((n_groups + gpb - 1) / gpb, xcd_chunk);
-    const int64_t mid_blocks = pad_runs(((int64_t)n_mid + 3) / 4, xcd_chunk_mid);
-    const int64_t blocks = (int64_t)n_segs + mid_blocks + short_blocks;
+    // While a wave per row and slice still fits the chip at once (256 CUs x 32 waves), a row's non-zeros are spread over
+    // its four groups instead of queueing in one (2,708 nodes, 32 columns: 5.6 -> 3.6 us of kernel time).
+    wk.wave_rows = (int64_t)n_items * wk.n_slices <= 8192;
+    wk.short_blocks = pad_runs(wk.wave_rows ? ((int64_t)n_items + 3) / 4 : (n_groups + 15) / 16, wk.run);
+    wk.mid_blocks = pad_runs(((int64_t)n_mid + 3) / 4, wk.run_mid);
+    const int64_t blocks = (wk.seg_blocks + wk.mid_blocks + wk.short_blocks) * wk.n_slices;
     if (blocks <= 0) return hipSuccess;
-    CsrWork wk{n_segs, segs, partial, n_mid, mid_rows, n_items, row_list, route, rpg, mid_row, xcd_chunk, mid_blocks, xcd_chunk_mid};
-#define HC_LAUNCH_CSR(L, V, K) hipLaunchKernelGGL((k_csr<L, V, K>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a)
+#define HC_LAUNCH_CSR(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a)
     HC_CSR_DISPATCH(HC_LAUNCH_CSR)
 #undef HC_LAUNCH_CSR
     return hipGetLastError();
@@ -656,41 +768,40 @@ hipError_t launch_update_rest(const SpmmArgs& a, int32_t n_rest, const int32_t* 
 
 // ---- measurement aid: the bare gather ------------------------------------------------------------
 // Reads row index[i] of X for every i and does nothing else a sparse product would do (no row
-// structure, no values, no output rows): a lane group takes a contiguous run of indices, LPR at a
-// time with one coalesced load, keeps eight row requests in flight like the scalar path, and adds
+// structure, no values, no output rows): a lane group takes a contiguous run of indices, 16 at a
+// time with one coalesced load, keeps as many row requests in flight as the scalar path, and adds
 // what arrives into registers; one vector per lane is stored at the end so the loads stay live.
-// Its duration is the floor of any kernel that fetches one X row per non-zero of the same stream.
-template <int LPR>
+// Its duration is what the scalar path's loop takes for the gather alone of the same stream.
+template <class G>
 __global__ __launch_bounds__(256) void k_probe_gather(const int32_t* __restrict__ index, int64_t n, int64_t per_group,
-                                                      const float* __restrict__ X, int64_t ldx, int32_t d,
-                                                      int32_t n_rows_x, float* __restrict__ out)
+                                                      SpmmArgs a, int32_t n_rows_x, float* __restrict__ out)
 {
     // workgroups in XCD-local runs of 32, like the scalar path's short rows (the grid is padded to whole rounds)
     const int64_t x = blockIdx.x & 7, q = blockIdx.x >> 3;
     const int64_t blk = ((q / 32) * 8 + x) * 32 + q % 32;
-    const int64_t grp = blk * (256 / LPR) + threadIdx.x / LPR;
-    const int lig = threadIdx.x % LPR;
+    const int64_t grp = blk * (256 / kGroup) + threadIdx.x / kGroup;
+    const int lig = threadIdx.x % kGroup;
     const int64_t b = min(n, grp * per_group), e = min(n, b + per_group);
-    const int c = 4 * lig < d ? 4 * lig : 0;
-    const char* __restrict__ Xc = reinterpret_cast<const char*>(X + c);
-    float acc[4];
-    vzero<4>(acc);
-    for (int64_t k0 = b; k0 < e; k0 += LPR) {                   // (a group past the end of the stream has b == e)
+    G g;
+    g.init(a, 0, a.d, lig);
+    float acc[G::N];
+    vzero(acc);
+    for (int64_t k0 = b; k0 < e; k0 += kGroup) {                // (a group past the end of the stream has b == e)
         const int64_t k = min(k0 + lig, e - 1);
-        const int32_t mc = min(max(index[k], 0), n_rows_x - 1);       // whatever the stream holds, the read stays inside X
-        batch_accumulate<LPR, 4, 0>(mc, 1.f, (int)min((int64_t)LPR, e - k0), Xc, ldx * 4, acc);
+        const int32_t c = min(max(index[k], 0), n_rows_x - 1);  // whatever the stream holds, the read stays inside X
+        g.batch(g.key(c), 1.f, (int)min((int64_t)kGroup, e - k0), acc);
     }
-    *reinterpret_cast<float4*>(out + ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < G::N; ++i) t[i & 3] += acc[i];
+    *reinterpret_cast<float4*>(out + ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4) = make_float4(t[0], t[1], t[2], t[3]);
 }
 
-// Launch shape of the probe: lanes per row from d like the scalar path; indices per lane group 512 (long enough
-// to amortise the start-up) unless the stream is too short to give every CU some tens of workgroups that way --
-// then fewer, down to 64.
-static void probe_gather_shape(int64_t n, int32_t d, int& lpr, int64_t& per_group, int64_t& blocks)
+// Launch shape of the probe: indices per lane group 512 (long enough to amortise the start-up) unless the stream is too
+// short to give every CU some tens of workgroups that way -- then fewer, down to 64.
+static void probe_gather_shape(int64_t n, int64_t& per_group, int64_t& blocks)
 {
-    lpr = 8;
-    while (lpr < 64 && lpr * 4 < d) lpr <<= 1;
-    const int64_t groups_per_block = 256 / lpr;
+    const int64_t groups_per_block = 256 / kGroup;
     per_group = (n / (8192 * groups_per_block) + 63) / 64 * 64;
     per_group = per_group < 64 ? 64 : (per_group > 512 ? 512 : per_group);
     const int64_t groups = (n + per_group - 1) / per_group;
@@ -700,9 +811,9 @@ static void probe_gather_shape(int64_t n, int32_t d, int& lpr, int64_t& per_grou
 
 int64_t probe_gather_blocks(int64_t n, int32_t d)
 {
-    int lpr;
+    (void)d;
     int64_t per_group, blocks;
-    probe_gather_shape(n, d, lpr, per_group, blocks);
+    probe_gather_shape(n, per_group, blocks);
     return blocks;
 }
 
@@ -710,16 +821,13 @@ hipError_t launch_probe_gather(const int32_t* index, int64_t n, const float* X, 
                                float* out, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    int lpr;
     int64_t per_group, blocks;
-    probe_gather_shape(n, d, lpr, per_group, blocks);
-#define HC_PROBE(L) hipLaunchKernelGGL((k_probe_gather<L>), dim3((unsigned)blocks), dim3(256), 0, s, index, n, per_group, X, ldx, d, n_rows_x, out)
-    switch (lpr) {
-        case 8: HC_PROBE(8); break;
-        case 16: HC_PROBE(16); break;
-        case 32: HC_PROBE(32); break;
-        default: HC_PROBE(64); break;
-    }
+    probe_gather_shape(n, per_group, blocks);
+    SpmmArgs a{};
+    a.n_cols = n_rows_x; a.X = X; a.ldx = ldx; a.d = d; a.x_dtype = HCSPMM_F32;
+    const CsrShape sh = pick_shape(a);
+#define HC_PROBE(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_probe_gather<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)blocks), dim3(256), 0, s, index, n, per_group, a, n_rows_x, out)
+    HC_CSR_DISPATCH32(HC_PROBE)
 #undef HC_PROBE
     return hipGetLastError();
 }

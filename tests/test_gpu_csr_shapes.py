@@ -1,0 +1,57 @@
+"""Scalar-path launch shapes against the oracle: vector widths and remainders of a lane group, column slices, row tiers."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import assert_close, gpu_spmm, oracle_pair
+from workloads import tiny_random_csr, to_bf16_bits, to_f16_bits
+from workloads.graphs import CSRGraph
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_of(lengths, n_cols, seed):
+    """CSR with the given row lengths, ascending distinct columns, normal values."""
+    rng = np.random.default_rng(seed)
+    cols = [np.sort(rng.choice(n_cols, k, replace=False)) for k in lengths]
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    colind = np.concatenate(cols).astype(np.int32) if cols else np.empty(0, np.int32)
+    return CSRGraph(len(lengths), n_cols, rowptr, colind, rng.standard_normal(colind.shape[0]).astype(np.float32))
+
+
+# every tier and batch edge: empty, around 8 and 16, around the wave-per-row and segment thresholds, several segments
+LENGTHS = [0, 1, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 127, 128, 129, 1023, 1024, 1025, 2049, 4999, 3, 0, 2]
+
+
+@pytest.mark.parametrize("d", [1, 3, 4, 15, 16, 17, 18, 31, 32, 33, 47, 63, 64, 65, 127, 129, 131, 160, 255, 257])
+def test_fp32_widths_and_row_lengths(d):
+    g = rows_of(LENGTHS, 5000, d)
+    X = np.random.default_rng(d).standard_normal((g.n_cols, d)).astype(np.float32)
+    Y, _ = gpu_spmm(g, X, 1, pad_x=d % 3, pad_y=d % 2)
+    ref, bound = oracle_pair(g, X)
+    assert_close(Y, ref, bound, 1e-5, "fp32 d=%d" % d)
+
+
+@pytest.mark.parametrize("kind", ["bf16", "f16"])
+@pytest.mark.parametrize("d,pad", [(1, 0), (2, 0), (15, 0), (16, 1), (18, 0), (32, 2), (34, 0), (62, 0), (64, 0), (66, 2), (128, 0),
+                                   (130, 0), (131, 0), (256, 0), (258, 0)])
+def test_16bit_widths_and_row_lengths(kind, d, pad):
+    g = rows_of(LENGTHS, 5000, d)
+    X = np.random.default_rng(d).standard_normal((g.n_cols, d)).astype(np.float32)
+    bits = to_bf16_bits(X) if kind == "bf16" else to_f16_bits(X)
+    code = oracle.DT_BF16 if kind == "bf16" else oracle.DT_F16
+    Y, _ = gpu_spmm(g, bits, 1, pad_x=pad, x_bits=kind)
+    ref, bound = oracle_pair(g, bits, x_dtype=code)
+    assert_close(Y, ref, bound, 1e-5, "%s d=%d" % (kind, d))
+
+
+# rows of degree 20 and 60: slices of 256 and of 128 bytes; counts that XCDs own (2, 4, 8) and counts taken in turn
+@pytest.mark.parametrize("d", [64, 96, 128, 160, 192, 256, 300, 520])
+@pytest.mark.parametrize("n,degree", [(700, 20), (700, 60), (20011, 12)])
+def test_column_slices(n, degree, d):
+    g = tiny_random_csr(n, n, degree / n, seed=d + degree)
+    X = np.random.default_rng(d).standard_normal((n, d)).astype(np.float32)
+    Y, _ = gpu_spmm(g, X, 1)
+    rows = np.unique(np.concatenate([np.arange(0, n, 37), np.arange(max(0, n - 40), n)]))
+    ref, bound = oracle_pair(g, X, rows=rows)
+    assert_close(Y[rows], ref, bound, 1e-5, "slices n=%d degree=%d d=%d" % (n, degree, d))
