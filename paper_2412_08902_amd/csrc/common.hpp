@@ -16,6 +16,7 @@ constexpr int64_t kGuardNnz = 1 << 18;
 constexpr int64_t kGuardShare = 8;
 
 // ---- preprocessing -----------------------------------------------------------------------------
+constexpr int kCountTinyCap = 1024;    // windows with at most this many non-zeros are counted in an 8 KB LDS hash set
 constexpr int kUniqueSmallCap = 4096;  // windows with at most this many non-zeros are condensed by an LDS sort
 constexpr int kCountMidCap = 16384;    // windows up to this many non-zeros are counted with an LDS hash set (128 KB)
 constexpr int kBitmapWords = 32768;    // LDS bitmap (1 Mi columns per pass) used to condense larger windows
@@ -83,9 +84,43 @@ struct ScanMulti { const int32_t* in[kScanMaxArrays]; int64_t* out[kScanMaxArray
 size_t scan_multi_scratch_elems(int64_t n);
 hipError_t exclusive_scan_multi(const ScanMulti& m, int64_t n, int64_t* totals_dev, int64_t* scratch, hipStream_t stream);
 
+// ---- preparation (prepare_kernels.hip): CSR arrays -> window features, routes, row tables -------
+struct PrepTotals {
+    int64_t total_ncols, nnz_mfma, wide_cols /* columns of wide matrix-path windows */, nnz_long, n_slots;
+    int32_t n_mfma, n_mfma_small, n_mfma_mid, n_mfma_big, n_short, n_mid, n_rest, n_multi, n_segs;
+    int32_t n_big_list, n_huge_list;      // windows above kUniqueSmallCap / kCountMidCap non-zeros
+    int32_t err;                          // 1 rowptr[0], 2 rowptr[n_rows], 4 decreasing rowptr, 8 column out of range
+};
+struct Prep {
+    int32_t n_rows, n_cols, W, n_tiles;
+    int64_t nnz;
+    const int32_t *rowptr, *colind;
+    int32_t* ctl;                         // zeroed: [0] errors, [1] [2] lengths of big_list, huge_list, [3] of count_1k
+    int32_t *big_list, *huge_list;        // every window of the two classes
+    int32_t *count_1k, *count_mid, *count_huge, *n_count_mid, *n_count_huge;   // windows whose columns are still to be counted
+    const int32_t* touched;               // windows to count (null: all)
+    const int32_t* old_ncols;             // counts carried over for the others
+    int32_t features;                     // distinct columns are wanted
+    int32_t big_takes_1k;                 // set by launch_prep
+    int32_t mode;
+    long long c0, c1, c2;
+    int32_t mid_row, long_row, fused_mid_row;
+    int32_t *ncols, *nnzw;
+    uint8_t* route;
+    int64_t* wptr;
+    unsigned long long *wt, *rt;          // sums per tile of 64 windows
+    int32_t *short_rows, *mid_rows, *rest_rows;   // row tables to fill (null: skip)
+    Segment* segs;
+    MultiRow* multi;
+    PrepTotals* out;                      // host or device memory (null: skip)
+};
+size_t prep_tile_count(int32_t W);
+size_t prep_tile_words(int32_t W);        // 64-bit words of wt and rt together (rt follows wt's prep_tile_count() * 8)
+hipError_t launch_prep(const Prep& p, int32_t n_touched, hipStream_t s);
+hipError_t launch_prep_fill(const Prep& p, hipStream_t s);      // another pass over the row tables
+hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* csr, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s);
+
 // ---- preprocessing launchers (prepare_kernels.hip) ---------------------------------------------
-hipError_t launch_validate(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t* rowptr, const int32_t* colind,
-                           int32_t* err_flag, hipStream_t s);
 hipError_t launch_window_nnz(int32_t W, int32_t n_rows, const int32_t* rowptr, int32_t* nnzw, int32_t* big_list,
                              int32_t* big_count, hipStream_t s);
 // sorted distinct-column lists (route: null = every window, else only windows with route != 0)
@@ -94,26 +129,12 @@ hipError_t launch_unique_small(int32_t W, int32_t n_rows, const int32_t* rowptr,
 hipError_t launch_unique_big(int32_t n_big, const int32_t* big_list, int32_t n_rows, int32_t n_cols,
                              const int32_t* rowptr, const int32_t* colind, int32_t* tmp_cols, int32_t* ncols,
                              const uint8_t* route, hipStream_t s);
-// distinct-column counts only (LDS hash sets); windows above kCountMidCap non-zeros go to launch_unique_big
-hipError_t launch_window_classes(int32_t W, int32_t n_rows, const int32_t* rowptr, int32_t* nnzw, int32_t* mid_list,
-                                 int32_t* huge_list, int32_t* counts, hipStream_t s);
-hipError_t launch_count_small(int32_t W, int32_t n_rows, const int32_t* rowptr, const int32_t* colind, int32_t* ncols,
-                              hipStream_t s);
-// incremental preparation: the touched windows by size class (+ range check of their columns), counts over a list
-hipError_t launch_touched_classes(int32_t n_touched, const int32_t* touched, int32_t n_rows, int32_t n_cols,
-                                  const int32_t* rowptr, const int32_t* colind, int32_t* t_small, int32_t* t_mid,
-                                  int32_t* t_huge, int32_t* counts, int32_t* err, hipStream_t s);
-hipError_t launch_count_small_list(int32_t n_list, const int32_t* list, int32_t n_rows, const int32_t* rowptr,
-                                   const int32_t* colind, int32_t* ncols, hipStream_t s);
-hipError_t launch_validate_rowptr(int32_t n_rows, int64_t nnz, const int32_t* rowptr, int32_t* err_flag, hipStream_t s);
 // incremental preparation: which matrix-path windows keep the previous plan's condensed structure, and its copy
 hipError_t launch_carry_mask(int32_t W, const uint8_t* old_route, const uint8_t* route, int32_t n_touched,
                              const int32_t* touched, uint8_t* carried, uint8_t* todo, hipStream_t s);
 hipError_t launch_carry_copy(int32_t W, int32_t n_rows, const uint8_t* carried, const int64_t* old_wptr, const int64_t* wptr,
                              const int32_t* old_wcols, int32_t* wcols, const int64_t* old_start, const int32_t* rowptr,
                              const int32_t* old_erc, int32_t* erc, hipStream_t s);
-hipError_t launch_count_mid(int32_t n_mid, const int32_t* mid_list, int32_t n_rows, const int32_t* rowptr,
-                            const int32_t* colind, int32_t* ncols, hipStream_t s);
 hipError_t launch_ecol(int32_t W, int32_t n_rows, const int32_t* rowptr, const int32_t* colind,
                        const int32_t* tmp_cols, const int32_t* ncols, const int64_t* wptr, int32_t* wcols,
                        int32_t* erc, int32_t* unsorted_flag, const uint8_t* route, int want,
@@ -123,15 +144,6 @@ hipError_t launch_condense_rank(int32_t n_list, const int32_t* list, int32_t n_r
                                 const int32_t* colind, const uint8_t* route, const int64_t* wptr, int32_t* wcols,
                                 int32_t* erc, int32_t* unsorted_flag, hipStream_t s);
 constexpr int64_t kRankMaxCols = (int64_t)8 << 19;   // beyond this many columns a window's bitmap passes cost more than searching
-hipError_t launch_select(int32_t W, const int32_t* ncols, const int32_t* nnzw, int64_t c0, int64_t c1, int64_t c2,
-                         int32_t mode, uint8_t* route, int32_t* f_mfma, int32_t* f_csr, int32_t* f_small,
-                         int32_t* f_mid, int32_t* f_big, int32_t* nnz_if_mfma, hipStream_t s);
-hipError_t launch_masked_copy(int32_t n, const int32_t* flags, const int32_t* src, int32_t* dst, hipStream_t s);
-hipError_t launch_compact_ids(int32_t n, const int32_t* flags, const int64_t* pos, int32_t* out, hipStream_t s);
-hipError_t launch_row_class(int32_t n_rows, const int32_t* rowptr, const uint8_t* route, int32_t mid_row,
-                            int32_t long_row, int32_t* f_short,
-                            int32_t* f_mid, int32_t* n_seg, int32_t* f_multi, int32_t* n_slot, int32_t* len_long,
-                            hipStream_t s);
 hipError_t launch_build_desc(int32_t n_list, const int32_t* win_list, int32_t n_rows, const int32_t* rowptr,
                              const int32_t* ncols, const int64_t* wptr, WinDesc* desc, hipStream_t s);
 hipError_t launch_slice_count(int32_t n_list, const int32_t* win_list, const int32_t* ncols, int32_t slice_cols,
@@ -139,9 +151,6 @@ hipError_t launch_slice_count(int32_t n_list, const int32_t* win_list, const int
 hipError_t launch_slice_fill(int32_t n_list, const int32_t* win_list, const int32_t* ncols, int32_t slice_cols,
                              const int64_t* slice_pos, const int64_t* multi_pos, const int64_t* slot_pos,
                              WgSlice* slices, MultiRow* multi, hipStream_t s);
-hipError_t launch_build_segments(int32_t n_rows, const int32_t* rowptr, const int32_t* n_seg, const int64_t* seg_pos,
-                                 const int64_t* multi_pos, const int64_t* slot_pos, Segment* segs, MultiRow* multi,
-                                 hipStream_t s);
 
 // ---- compute launchers -------------------------------------------------------------------------
 struct SpmmArgs {
@@ -242,8 +251,6 @@ hipError_t launch_update_rest(const SpmmArgs& a, int32_t n_rest, const int32_t* 
 bool gemm_rows16_usable(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx);
 hipError_t launch_gemm_rows16(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
                               float* T, int64_t ldt, int relu, hipStream_t s, int32_t t_dtype = HCSPMM_F32);
-hipError_t launch_rest_flag(int32_t n_rows, const int32_t* rowptr, const uint8_t* route, const int32_t* ncols,
-                            int32_t mid_row, int32_t* flag, hipStream_t s);
 hipError_t launch_reduce_partials(const SpmmArgs& a, int32_t n_multi, const MultiRow* multi, const float* partial,
                                   hipStream_t s);
 hipError_t launch_mfma_small(const SpmmArgs& a, int32_t n_list, const WinDesc* desc, const int32_t* wcols,

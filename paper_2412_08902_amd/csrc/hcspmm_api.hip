@@ -323,20 +323,23 @@ fail:
     return st;
 }
 
-// Small device-to-host read-backs of a preparation go through a page of pinned host memory: a copy into
-// pageable memory costs the runtime tens of microseconds each, and a preparation makes five to eight of them.
-// The pages are allocated on first use, handed out one per running preparation and kept until the process ends.
+// Small device-to-host read-backs of a preparation go through a block of pinned host memory: a copy into
+// pageable memory costs the runtime tens of microseconds each.  The totals that every preparation needs are stored there by
+// the kernels themselves, and the list of changed windows of an update is read from there, without any copy.
+// The blocks are allocated on first use, handed out one per running preparation and kept until the process ends.
 class PinnedPage {
 public:
-    static constexpr size_t kBytes = 4096;
+    // [0, kReadback): totals written by the kernels; [kReadback, kList): queued read-backs; from kList on: a list the kernels read
+    static constexpr size_t kBytes = 65536, kReadback = 1024, kList = 4096;
     PinnedPage()
     {
         std::lock_guard<std::mutex> g(mu());
         for (Slot& sl : pool())
             if (!sl.busy) { sl.busy = true; slot_ = &sl; return; }
-        void* q = nullptr;
-        if (hipHostMalloc(&q, kBytes, hipHostMallocPortable) != hipSuccess) { (void)hipGetLastError(); return; }
-        pool().push_back(Slot{q, true});
+        void *q = nullptr, *d = nullptr;
+        if (hipHostMalloc(&q, kBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) { (void)hipGetLastError(); return; }
+        if (hipHostGetDevicePointer(&d, q, 0) != hipSuccess) { (void)hipGetLastError(); (void)hipHostFree(q); return; }
+        pool().push_back(Slot{q, d, true});
         slot_ = &pool().back();
     }
     ~PinnedPage()
@@ -348,8 +351,9 @@ public:
     PinnedPage(const PinnedPage&) = delete;
     PinnedPage& operator=(const PinnedPage&) = delete;
     char* ptr() const { return slot_ ? static_cast<char*>(slot_->p) : nullptr; }
+    char* device_ptr() const { return slot_ ? static_cast<char*>(slot_->d) : nullptr; }
 private:
-    struct Slot { void* p; bool busy; };
+    struct Slot { void* p; void* d; bool busy; };
     static std::mutex& mu() { static std::mutex m; return m; }
     static std::deque<Slot>& pool() { static std::deque<Slot> v; return v; }   // (deque: growth keeps the slots in place)
     Slot* slot_ = nullptr;
@@ -366,7 +370,7 @@ struct Readback {
     hipError_t add(void* dst, const void* src, size_t n, hipStream_t stream)
     {
         const size_t off = (used + 15) & ~(size_t)15;
-        if (!page || n_pend == 16 || off + n > PinnedPage::kBytes) return hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, stream);
+        if (!page || n_pend == 16 || off + n > PinnedPage::kList - PinnedPage::kReadback) return hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, stream);
         pend[n_pend++] = Pending{dst, off, n};
         used = off + n;
         return hipMemcpyAsync(page + off, src, n, hipMemcpyDeviceToHost, stream);
@@ -383,7 +387,7 @@ struct Readback {
 };
 
 // What an incremental preparation carries over from the previous plan: the distinct-column counts of the windows
-// that hold no changed row (device array of the old plan) and the list of windows that do (device, distinct ids).
+// that hold no changed row (device array of the old plan) and the list of windows that do (host, distinct ids).
 struct PlanCarry {
     const int32_t* old_ncols; const int32_t* touched; int32_t n_touched;
     // the previous plan's condensed structure (matrix-path windows), when it has one whose rows were all sorted
@@ -398,31 +402,33 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     DevAlloc keep;     // plan-owned (chunks handed to the plan on success), freed on failure only
     PinnedPage pinned;
     Readback rb;
-    rb.page = pinned.ptr();
+    if (pinned.ptr()) rb.page = pinned.ptr() + PinnedPage::kReadback;
     tmp.cache = keep.cache = p->cache ? p->cache : small_block_cache(p->device);
     const int32_t n_rows = p->n_rows, W = p->W;
     const int64_t nnz = p->nnz;
     keep.chunk_min = (size_t)1 << 20;      // small graphs: all plan arrays in one or two device allocations
-    int32_t *err = nullptr, *big_list = nullptr, *huge_list = nullptr, *big_count = nullptr, *tmp_cols = nullptr;
-    int32_t *f_mfma = nullptr, *f_csr = nullptr, *f_small = nullptr, *f_midw = nullptr, *f_big = nullptr, *nnz_if = nullptr;
-    int32_t *f_short = nullptr, *f_mid = nullptr, *n_seg = nullptr, *f_multi = nullptr, *n_slot = nullptr, *len_long = nullptr;
-    int64_t *scan_tmp = nullptr, *pos_a = nullptr, *pos_b = nullptr, *pos_c = nullptr, *pos_d = nullptr, *pos_e = nullptr, *pos_f = nullptr;
-    int32_t* f_rest = nullptr;
-    int32_t *t_small = nullptr, *t_mid = nullptr, *t_huge = nullptr, *t_counts = nullptr;
-    int64_t *totals_dev = nullptr;
-    int32_t h_err = 0, h_big = 0, h_cls[2] = {0, 0}, h_tc[3] = {0, 0, 0};
+    int32_t *err = nullptr, *tmp_cols = nullptr, *touched_dev = nullptr;
+    int32_t *sc_n = nullptr, *sc_multi = nullptr, *sc_slots = nullptr;
+    int64_t *scan_tmp = nullptr, *pos_a = nullptr, *pos_b = nullptr, *pos_d = nullptr, *totals_dev = nullptr;
+    PrepTotals tot, *tot_dev = nullptr;
+    int32_t h_err = 0;
     int64_t h_tot[16];
-    const int64_t scan_n = (int64_t)(n_rows > W ? n_rows : W) + 1;
+    const int32_t n_touched = carry ? carry->n_touched : 0;
+    const bool zero_copy = pinned.ptr() && (size_t)n_touched * sizeof(int32_t) <= PinnedPage::kBytes - PinnedPage::kList;
+    // upper bounds of the scalar path's row tables (a row in one of them has that many non-zeros), so that they can be
+    // filled before the host knows how many entries they get
+    const int64_t wide_rows = p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR ? 0 : kH * (nnz / (kMfmaSmallMaxCols + 1));
+    const int64_t most_mid = std::min<int64_t>(n_rows, nnz / (p->mid_row + 1)), most_multi = nnz / (kSegLen + 1),
+                  most_segs = nnz / (p->long_row + 1) + nnz / kSegLen,
+                  most_rest = std::min<int64_t>(n_rows, nnz / (p->fused_mid_row + 1) + wide_rows);
+    Prep pr{};
 
     {
-        // every scratch array of this function has a size known from (n_rows, W, nnz): one allocation
-        const size_t i32 = sizeof(int32_t), i64 = sizeof(int64_t);
-        size_t total = DevAlloc::padded(4 * i32) + DevAlloc::padded((size_t)nnz * i32) + 2 * DevAlloc::padded((size_t)W * i32) +
-                       DevAlloc::padded((size_t)scan_multi_scratch_elems(scan_n) * i64) +
-                       6 * DevAlloc::padded((size_t)(scan_n + 1) * i64) +
-                       DevAlloc::padded(16 * i64) + 6 * DevAlloc::padded(((size_t)W + 1) * i32) +
-                       7 * DevAlloc::padded(((size_t)n_rows + 1) * i32) + 64 * 256 +
-                       (carry ? 3 * DevAlloc::padded((size_t)carry->n_touched * i32) + 256 : 0);
+        // the scratch arrays that every preparation needs: one allocation
+        const size_t i32 = sizeof(int32_t);
+        const size_t total = DevAlloc::padded(8 * i32) + 5 * DevAlloc::padded((size_t)W * i32) +
+                             DevAlloc::padded(prep_tile_words(W) * 8) + DevAlloc::padded(sizeof(PrepTotals)) + 16 * 256 +
+                             DevAlloc::padded((size_t)n_touched * i32);
         if (tmp.reserve(total) != hipSuccess) {
             (void)hipGetLastError();
             set_error("device allocation of %zu scratch bytes failed", total);
@@ -430,149 +436,117 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
             goto fail;
         }
     }
-    HC_ALLOC(tmp, err, 4);
-    big_count = err + 1;                           // two counters: windows for the large hash set, for the bitmap
-    HC_TRY(hipMemsetAsync(err, 0, 4 * sizeof(int32_t), stream));
-    if (carry) {
-        // the row offsets are checked in full (they all move when a row grows), the columns only where rows changed
-        HC_ALLOC(tmp, t_small, carry->n_touched);
-        HC_ALLOC(tmp, t_mid, carry->n_touched);
-        HC_ALLOC(tmp, t_huge, carry->n_touched);
-        HC_ALLOC(tmp, t_counts, 4);
-        HC_TRY(hipMemsetAsync(t_counts, 0, 4 * sizeof(int32_t), stream));
-        HC_TRY(launch_validate_rowptr(n_rows, nnz, p->rowptr, err, stream));
-        HC_TRY(rb.add(&h_err, err, sizeof h_err, stream));
-        HC_TRY(rb.sync(stream));
-        if (!h_err) {           // the windows' spans are only meaningful with sound row offsets
-            HC_TRY(launch_touched_classes(carry->n_touched, carry->touched, n_rows, p->n_cols, p->rowptr, p->colind, t_small,
-                                          t_mid, t_huge, t_counts, err, stream));
-            HC_TRY(rb.add(h_tc, t_counts, 3 * sizeof(int32_t), stream));
-        }
-    } else {
-        HC_TRY(launch_validate(n_rows, p->n_cols, nnz, p->rowptr, p->colind, err, stream));
-    }
-    HC_TRY(rb.add(&h_err, err, sizeof h_err, stream));
-    HC_TRY(rb.sync(stream));
-    if (h_err) {
-        set_error("invalid CSR: %s%s%s%s", (h_err & 1) ? "rowptr[0] != 0; " : "",
-                  (h_err & 2) ? "rowptr[n_rows] != nnz; " : "", (h_err & 4) ? "rowptr not non-decreasing; " : "",
-                  (h_err & 8) ? "column index out of range; " : "");
-        st = HCSPMM_EBADCSR;
-        goto fail;
-    }
-
     HC_ALLOC(keep, p->ncols, W);
     HC_ALLOC(keep, p->nnzw, W);
     HC_ALLOC(keep, p->route, W);
     HC_ALLOC(keep, p->wptr, (size_t)W + 1);
-    HC_ALLOC(tmp, tmp_cols, nnz);
-    HC_ALLOC(tmp, big_list, W);
-    HC_ALLOC(tmp, huge_list, W);
-    HC_ALLOC(tmp, scan_tmp, scan_multi_scratch_elems(scan_n));
-    HC_ALLOC(tmp, pos_a, scan_n + 1);
-    HC_ALLOC(tmp, pos_b, scan_n + 1);
-    HC_ALLOC(tmp, pos_c, scan_n + 1);
-    HC_ALLOC(tmp, pos_d, scan_n + 1);
-    HC_ALLOC(tmp, pos_e, scan_n + 1);
-    HC_ALLOC(tmp, pos_f, scan_n + 1);
-    HC_ALLOC(tmp, totals_dev, 16);
-
+    HC_ALLOC(keep, p->mid_rows, most_mid);
+    HC_ALLOC(keep, p->segs, most_segs);
+    HC_ALLOC(keep, p->multi, most_multi);
+    HC_ALLOC(keep, p->rest_rows, most_rest);
+    HC_ALLOC(tmp, err, 8);
+    HC_TRY(hipMemsetAsync(err, 0, 8 * sizeof(int32_t), stream));
+    if (carry && n_touched > 0) {
+        if (zero_copy) {
+            memcpy(pinned.ptr() + PinnedPage::kList, carry->touched, (size_t)n_touched * sizeof(int32_t));
+            touched_dev = reinterpret_cast<int32_t*>(pinned.device_ptr() + PinnedPage::kList);
+        } else {
+            HC_ALLOC(tmp, touched_dev, n_touched);
+            HC_TRY(hipMemcpyAsync(touched_dev, carry->touched, (size_t)n_touched * sizeof(int32_t), hipMemcpyHostToDevice, stream));
+        }
+    }
     // A scalar-only plan never reads the condensed structure (the paper has no preprocessing for its
     // scalar path either): its window features stay zero here and are computed when first asked for
     // (hcspmm_plan_info / hcspmm_plan_export), which makes prepare cheap for matrices that keep changing.
     p->features_complete = (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR && nnz > 0) ? 0 : 1;
-    if (W > 0) {
-        // windows, condensing (Section IV-A)
-        // The selector needs the number of distinct columns of every window but the sorted lists only
-        // for the windows it sends to the matrix path: count with LDS hash sets first (bitmap passes for
-        // the few windows beyond the hash set's capacity, which leave their lists behind as well).
-        HC_TRY(launch_window_classes(W, n_rows, p->rowptr, p->nnzw, big_list, huge_list, big_count, stream));
-        if (p->features_complete && carry) {
-            // counts of the untouched windows are the previous plan's; the touched ones are counted again
-            HC_TRY(hipMemcpyAsync(p->ncols, carry->old_ncols, (size_t)W * sizeof(int32_t), hipMemcpyDeviceToDevice, stream));
-            HC_TRY(rb.add(h_cls, big_count, sizeof h_cls, stream));
-            HC_TRY(rb.sync(stream));
-            h_big = h_cls[0];
-            HC_TRY(launch_count_small_list(h_tc[0], t_small, n_rows, p->rowptr, p->colind, p->ncols, stream));
-            HC_TRY(launch_count_mid(h_tc[1], t_mid, n_rows, p->rowptr, p->colind, p->ncols, stream));
-            HC_TRY(launch_unique_big(h_tc[2], t_huge, n_rows, p->n_cols, p->rowptr, p->colind, tmp_cols, p->ncols, nullptr,
-                                     stream));
-        } else if (p->features_complete) {
-            HC_TRY(launch_count_small(W, n_rows, p->rowptr, p->colind, p->ncols, stream));
-            HC_TRY(rb.add(h_cls, big_count, sizeof h_cls, stream));
-            HC_TRY(rb.sync(stream));
-            h_big = h_cls[0];
-            HC_TRY(launch_count_mid(h_big, big_list, n_rows, p->rowptr, p->colind, p->ncols, stream));
-            HC_TRY(launch_unique_big(h_cls[1], huge_list, n_rows, p->n_cols, p->rowptr, p->colind, tmp_cols, p->ncols,
-                                     nullptr, stream));
-        } else {
-            HC_TRY(hipMemsetAsync(p->ncols, 0, (size_t)W * sizeof(int32_t), stream));
-        }
-    }
-    if (p->features_complete) {
-        ScanMulti m{};
-        m.k = 1;
-        m.in[0] = p->ncols;
-        m.out[0] = p->wptr;
-        HC_TRY(exclusive_scan_multi(m, W, totals_dev + 8, scan_tmp, stream));     // the total is read back with the list sizes below
-    } else {
-        HC_TRY(hipMemsetAsync(p->wptr, 0, ((size_t)W + 1) * sizeof(int64_t), stream));
-        HC_TRY(hipMemsetAsync(totals_dev + 8, 0, sizeof(int64_t), stream));
-    }
-    p->total_ncols = 0;
     p->rows_sorted = 1;
-
-    // selection (Section IV-C) and the per-route window lists
-    HC_ALLOC(tmp, f_mfma, (size_t)W + 1);
-    HC_ALLOC(tmp, f_csr, (size_t)W + 1);
-    HC_ALLOC(tmp, f_small, (size_t)W + 1);
-    HC_ALLOC(tmp, f_midw, (size_t)W + 1);
-    HC_ALLOC(tmp, f_big, (size_t)W + 1);
-    HC_ALLOC(tmp, nnz_if, (size_t)W + 1);
-    // Selection, then the positions of every window in its lists and the non-zeros on the matrix path: six scans in
-    // one pass, their totals in one read-back.  Launch guard (hybrid mode): a path whose share cannot repay a kernel
-    // launch of its own joins the other path -- decided from the same totals, so only a plan that is actually merged
-    // pays a second selection pass.
-    for (int32_t mode = p->opt.route_mode, pass = 0;; ++pass) {
-        if (W > 0)
-            HC_TRY(launch_select(W, p->ncols, p->nnzw, p->coef[0], p->coef[1], p->coef[2], mode, p->route, f_mfma, f_csr,
-                                 f_small, f_midw, f_big, nnz_if, stream));
-        ScanMulti m{};
-        m.k = 6;
-        m.in[0] = f_mfma;  m.out[0] = pos_a;
-        m.in[1] = f_csr;   m.out[1] = pos_b;
-        m.in[2] = f_small; m.out[2] = pos_c;
-        m.in[3] = f_big;   m.out[3] = pos_d;
-        m.in[4] = f_midw;  m.out[4] = pos_e;
-        m.in[5] = nnz_if;  m.out[5] = nullptr;
-        HC_TRY(exclusive_scan_multi(m, W, totals_dev, scan_tmp, stream));
-        HC_TRY(rb.add(h_tot, totals_dev, 9 * sizeof(int64_t), stream));
-        HC_TRY(rb.sync(stream));
-        if (pass == 0 && p->opt.route_mode == HCSPMM_ROUTE_HYBRID) {
-            const int64_t on_matrix = h_tot[5], on_scalar = p->nnz - on_matrix;
-            int32_t forced = -1;
-            if (on_matrix > 0 && on_scalar > 0) {
-                if (on_matrix < kGuardNnz && kGuardShare * on_matrix < p->nnz) forced = HCSPMM_ROUTE_ALL_CSR;
-                else if (on_scalar < kGuardNnz && kGuardShare * on_scalar < p->nnz) forced = HCSPMM_ROUTE_ALL_MFMA;
-            }
-            if (forced >= 0) { mode = forced; continue; }
-        }
-        break;
+    pr.n_rows = n_rows; pr.n_cols = p->n_cols; pr.W = W; pr.n_tiles = (int32_t)prep_tile_count(W); pr.nnz = nnz;
+    pr.rowptr = p->rowptr; pr.colind = p->colind;
+    pr.ctl = err;
+    HC_ALLOC(tmp, pr.big_list, W);
+    HC_ALLOC(tmp, pr.huge_list, W);
+    HC_ALLOC(tmp, pr.count_1k, W);
+    pr.count_mid = pr.big_list; pr.count_huge = pr.huge_list; pr.n_count_mid = err + 1; pr.n_count_huge = err + 2;
+    if (carry) {
+        // counts of the untouched windows are the previous plan's; the touched ones are counted (and range-checked) again
+        pr.touched = touched_dev;
+        pr.old_ncols = carry->old_ncols;
+        HC_ALLOC(tmp, pr.count_mid, W);
+        HC_ALLOC(tmp, pr.count_huge, W);
+        pr.n_count_mid = err + 4; pr.n_count_huge = err + 5;
     }
-    p->total_ncols = h_tot[8];
-    p->n_mfma = (int32_t)h_tot[0];
+    pr.features = p->features_complete;
+    pr.mode = p->opt.route_mode;
+    pr.c0 = p->coef[0]; pr.c1 = p->coef[1]; pr.c2 = p->coef[2];
+    pr.mid_row = p->mid_row; pr.long_row = p->long_row; pr.fused_mid_row = p->fused_mid_row;
+    pr.ncols = p->ncols; pr.nnzw = p->nnzw; pr.route = p->route; pr.wptr = p->wptr;
+    HC_ALLOC(tmp, pr.wt, prep_tile_words(W));
+    pr.rt = pr.wt + 8 * prep_tile_count(W);
+    pr.mid_rows = p->mid_rows; pr.rest_rows = p->rest_rows; pr.segs = p->segs; pr.multi = p->multi;
+    HC_ALLOC(tmp, tot_dev, 1);
+    pr.out = pinned.ptr() ? reinterpret_cast<PrepTotals*>(pinned.device_ptr()) : tot_dev;
+    HC_TRY(launch_prep(pr, n_touched, stream));
+    if (pinned.ptr()) {
+        HC_TRY(hipStreamSynchronize(stream));
+        memcpy(&tot, pinned.ptr(), sizeof tot);
+    } else {
+        HC_TRY(hipMemcpyAsync(&tot, tot_dev, sizeof tot, hipMemcpyDeviceToHost, stream));
+        HC_TRY(hipStreamSynchronize(stream));
+    }
+    if (tot.err) {
+        set_error("invalid CSR: %s%s%s%s", (tot.err & 1) ? "rowptr[0] != 0; " : "",
+                  (tot.err & 2) ? "rowptr[n_rows] != nnz; " : "", (tot.err & 4) ? "rowptr not non-decreasing; " : "",
+                  (tot.err & 8) ? "column index out of range; " : "");
+        st = HCSPMM_EBADCSR;
+        goto fail;
+    }
+    p->total_ncols = tot.total_ncols;
+    p->n_mfma = tot.n_mfma;
     p->n_csr = W - p->n_mfma;
-    p->n_mfma_small = (int32_t)h_tot[2];
-    p->n_mfma_big = (int32_t)h_tot[3];
-    p->n_mfma_mid = (int32_t)h_tot[4];
-    p->nnz_mfma = h_tot[5];
+    p->n_mfma_small = tot.n_mfma_small;
+    p->n_mfma_big = tot.n_mfma_big;
+    p->n_mfma_mid = tot.n_mfma_mid;
+    p->nnz_mfma = tot.nnz_mfma;
+    p->nnz_long = tot.nnz_long;
+    p->n_short = tot.n_short;
+    p->n_segs = tot.n_segs;
+    p->n_multi = tot.n_multi;
+    p->n_slots = tot.n_slots;
+    p->n_mid = tot.n_mid;
+    p->n_rest = tot.n_rest;
+    p->n_long_rows = (int32_t)(p->n_segs - p->n_slots + p->n_multi);   // single-segment rows + multi-segment rows
     // condensed structure (column lists, condensed column of every non-zero) of the matrix-path
     // windows; scalar-path windows never read theirs at SpMM time and get it on export only, and a
     // plan without matrix-path windows does not even allocate the arrays
-    p->condensed_complete = 0;
+    p->condensed_complete = nnz == 0 ? 1 : 0;
+    // Walking every row and skipping the ones another kernel owns is cheaper than an index list
+    // while most rows are short scalar-path rows; otherwise keep the explicit list.
+    p->short_rows = nullptr;
+    if ((int64_t)p->n_short * 2 < n_rows) {
+        HC_ALLOC(keep, p->short_rows, p->n_short);
+        Prep fill = pr;
+        fill.mid_rows = fill.rest_rows = nullptr; fill.segs = nullptr; fill.multi = nullptr; fill.out = nullptr;
+        fill.short_rows = p->short_rows;
+        HC_TRY(launch_prep_fill(fill, stream));
+    }
     if (p->n_mfma > 0) {
+        HC_ALLOC(keep, p->mfma_windows, p->n_mfma);
+        HC_ALLOC(keep, p->csr_windows, p->n_csr);
+        HC_ALLOC(keep, p->mfma_small, p->n_mfma_small);
+        HC_ALLOC(keep, p->mfma_mid, p->n_mfma_mid);
+        HC_ALLOC(keep, p->mfma_big, p->n_mfma_big);
+        HC_TRY(launch_prep_windows(pr, p->mfma_windows, p->csr_windows, p->mfma_small, p->mfma_mid, p->mfma_big, stream));
         HC_ALLOC(keep, p->erc, nnz);
         HC_ALLOC(keep, p->wcols, p->total_ncols);
+        HC_ALLOC(tmp, tmp_cols, nnz);
+        HC_ALLOC(tmp, scan_tmp, scan_multi_scratch_elems((int64_t)W + 1));
+        HC_ALLOC(tmp, pos_a, (size_t)W + 2);
+        HC_ALLOC(tmp, pos_b, (size_t)W + 2);
+        HC_ALLOC(tmp, pos_d, (size_t)W + 2);
+        HC_ALLOC(tmp, totals_dev, 16);
+        HC_ALLOC(tmp, sc_n, (size_t)W + 1);
+        HC_ALLOC(tmp, sc_multi, (size_t)W + 1);
+        HC_ALLOC(tmp, sc_slots, (size_t)W + 1);
         // err[0] is zero here (validation passed): reuse it as the "some row is unsorted" flag.
         // Windows up to kUniqueSmallCap non-zeros: sorted list by the LDS sort, positions by binary search in it.
         // Larger ones: list and positions together from bitmap ranks, unless the matrix is so wide that the
@@ -588,7 +562,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
             HC_ALLOC(tmp, carried, (size_t)W);
             HC_ALLOC(tmp, todo, (size_t)W);
             HC_ALLOC(tmp, old_start, (size_t)W + 1);
-            HC_TRY(launch_carry_mask(W, carry->old_route, p->route, carry->n_touched, carry->touched, carried, todo, stream));
+            HC_TRY(launch_carry_mask(W, carry->old_route, p->route, n_touched, touched_dev, carried, todo, stream));
             HC_TRY(exclusive_scan_i32_i64(carry->old_nnzw, W, old_start, scan_tmp, stream));
             HC_TRY(launch_carry_copy(W, n_rows, carried, carry->old_wptr, p->wptr, carry->old_wcols, p->wcols, old_start,
                                      p->rowptr, carry->old_erc, p->erc, stream));
@@ -596,32 +570,22 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         }
         HC_TRY(launch_unique_small(W, n_rows, p->rowptr, p->colind, tmp_cols, p->ncols, todo_route, stream));
         if (by_rank) {
-            HC_TRY(launch_condense_rank(h_big, big_list, n_rows, p->rowptr, p->colind, todo_route, p->wptr, p->wcols, p->erc,
-                                        err, stream));
-            HC_TRY(launch_condense_rank(h_cls[1], huge_list, n_rows, p->rowptr, p->colind, todo_route, p->wptr, p->wcols,
+            HC_TRY(launch_condense_rank(tot.n_big_list, pr.big_list, n_rows, p->rowptr, p->colind, todo_route, p->wptr, p->wcols,
+                                        p->erc, err, stream));
+            HC_TRY(launch_condense_rank(tot.n_huge_list, pr.huge_list, n_rows, p->rowptr, p->colind, todo_route, p->wptr, p->wcols,
                                         p->erc, err, stream));
         } else {
-            HC_TRY(launch_unique_big(h_big, big_list, n_rows, p->n_cols, p->rowptr, p->colind, tmp_cols, p->ncols, todo_route,
-                                     stream));
+            HC_TRY(launch_unique_big(tot.n_big_list, pr.big_list, n_rows, p->n_cols, p->rowptr, p->colind, tmp_cols, p->ncols,
+                                     todo_route, stream));
+            HC_TRY(launch_unique_big(tot.n_huge_list, pr.huge_list, n_rows, p->n_cols, p->rowptr, p->colind, tmp_cols, p->ncols,
+                                     todo_route, stream));
         }
         HC_TRY(launch_ecol(W, n_rows, p->rowptr, p->colind, tmp_cols, p->ncols, p->wptr, p->wcols, p->erc, err, todo_route, 1,
                            by_rank ? kUniqueSmallCap : 0x7fffffff, stream));
         HC_TRY(rb.add(&h_err, err, sizeof h_err, stream));
         HC_TRY(rb.sync(stream));
         p->rows_sorted = h_err ? 0 : 1;
-    } else if (nnz == 0) {
-        p->condensed_complete = 1;
     }
-    HC_ALLOC(keep, p->mfma_windows, p->n_mfma);
-    HC_ALLOC(keep, p->csr_windows, p->n_csr);
-    HC_ALLOC(keep, p->mfma_small, p->n_mfma_small);
-    HC_ALLOC(keep, p->mfma_mid, p->n_mfma_mid);
-    HC_ALLOC(keep, p->mfma_big, p->n_mfma_big);
-    HC_TRY(launch_compact_ids(W, f_mfma, pos_a, p->mfma_windows, stream));
-    HC_TRY(launch_compact_ids(W, f_csr, pos_b, p->csr_windows, stream));
-    HC_TRY(launch_compact_ids(W, f_small, pos_c, p->mfma_small, stream));
-    HC_TRY(launch_compact_ids(W, f_big, pos_d, p->mfma_big, stream));
-    HC_TRY(launch_compact_ids(W, f_midw, pos_e, p->mfma_mid, stream));
     // Runs of matrix-path windows (kRunWindows consecutive list entries each): merged column lists and slots on the
     // device, the slice layout on the host from the union sizes (a few bytes per run cross the bus).
     p->runs_ok = 0;
@@ -681,12 +645,8 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         HC_TRY(rb.sync(stream));                    // the host vectors go out of scope
         p->runs_ok = 1;
     }
-    if (W > 0) HC_TRY(launch_masked_copy(W, f_big, p->ncols, nnz_if, stream));     // nnz_if <- ncols of wide windows, else 0
     // workgroup slices: one per medium window, slice_cols condensed columns each for wide windows
-    {
-        int32_t* sc_n = f_mfma;      // the flag arrays are free again: reuse them as scratch (W + 1 ints each)
-        int32_t* sc_multi = f_csr;
-        int32_t* sc_slots = f_small;
+    if (p->n_mfma > 0) {
         ScanMulti m{};
         m.k = 3;
         m.in[0] = sc_n;     m.out[0] = pos_a;
@@ -703,11 +663,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         // alignment of concurrently running windows on the same hot low-numbered columns): aim
         // at ~4 workgroups per CU over the summed width of the wide windows.
         if (tune().slice_cols < 0 && p->n_mfma_big > 0) {
-            HC_TRY(exclusive_scan_i32_i64(nnz_if, W, pos_a, scan_tmp, stream));     // nnz_if holds ncols of wide windows here
-            int64_t wide_cols = 0;
-            HC_TRY(rb.add(&wide_cols, pos_a + W, 8, stream));
-            HC_TRY(rb.sync(stream));
-            int64_t want = wide_cols / 1024;
+            int64_t want = tot.wide_cols / 1024;
             if (want < kKcBig) want = kKcBig;
             if (want > (1 << 27)) want = 1 << 27;
             p->slice_cols = (int32_t)((want + kKcBig - 1) / kKcBig * kKcBig);
@@ -778,62 +734,12 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
                                      stream));
         }
     }
-    HC_ALLOC(keep, p->mfma_small_desc, p->n_mfma_small);
-    HC_TRY(launch_build_desc(p->n_mfma_small, p->mfma_small, n_rows, p->rowptr, p->ncols, p->wptr, p->mfma_small_desc,
-                             stream));
-
-    // scalar-path launch tables
-    HC_ALLOC(tmp, f_short, (size_t)n_rows + 1);
-    HC_ALLOC(tmp, f_mid, (size_t)n_rows + 1);
-    HC_ALLOC(tmp, n_seg, (size_t)n_rows + 1);
-    HC_ALLOC(tmp, f_multi, (size_t)n_rows + 1);
-    HC_ALLOC(tmp, n_slot, (size_t)n_rows + 1);
-    HC_ALLOC(tmp, len_long, (size_t)n_rows + 1);
-    HC_ALLOC(tmp, f_rest, (size_t)n_rows + 1);
-    HC_TRY(launch_row_class(n_rows, p->rowptr, p->route, p->mid_row, p->long_row, f_short, f_mid, n_seg, f_multi, n_slot, len_long, stream));
-    // rows the fused update finishes through the workspace
-    HC_TRY(launch_rest_flag(n_rows, p->rowptr, p->route, p->ncols, p->fused_mid_row, f_rest, stream));
-    {
-        // all row-level positions and counts in one pass and one read-back
-        ScanMulti m{};
-        m.k = 7;
-        m.in[0] = len_long; m.out[0] = nullptr;
-        m.in[1] = f_short;  m.out[1] = pos_a;
-        m.in[2] = n_seg;    m.out[2] = pos_b;
-        m.in[3] = f_multi;  m.out[3] = pos_c;
-        m.in[4] = n_slot;   m.out[4] = pos_d;
-        m.in[5] = f_mid;    m.out[5] = pos_e;
-        m.in[6] = f_rest;   m.out[6] = pos_f;
-        HC_TRY(exclusive_scan_multi(m, n_rows, totals_dev, scan_tmp, stream));
-        HC_TRY(rb.add(h_tot, totals_dev, 7 * sizeof(int64_t), stream));
-        HC_TRY(rb.sync(stream));
+    if (p->n_mfma_small > 0) {
+        HC_ALLOC(keep, p->mfma_small_desc, p->n_mfma_small);
+        HC_TRY(launch_build_desc(p->n_mfma_small, p->mfma_small, n_rows, p->rowptr, p->ncols, p->wptr, p->mfma_small_desc,
+                                 stream));
     }
-    p->nnz_long = h_tot[0];
-    p->n_short = (int32_t)h_tot[1];
-    p->n_segs = (int32_t)h_tot[2];
-    p->n_multi = (int32_t)h_tot[3];
-    p->n_slots = h_tot[4];
-    p->n_mid = (int32_t)h_tot[5];
-    p->n_rest = (int32_t)h_tot[6];
-    p->n_long_rows = (int32_t)(p->n_segs - p->n_slots + p->n_multi);   // single-segment rows + multi-segment rows
-    HC_ALLOC(keep, p->segs, p->n_segs);
-    HC_ALLOC(keep, p->multi, p->n_multi);
-    if (p->n_segs > 0)
-        HC_TRY(launch_build_segments(n_rows, p->rowptr, n_seg, pos_b, pos_c, pos_d, p->segs, p->multi, stream));
-    // rows that get a whole wave
-    HC_ALLOC(keep, p->mid_rows, p->n_mid);
-    HC_TRY(launch_compact_ids(n_rows, f_mid, pos_e, p->mid_rows, stream));
-    // Walking every row and skipping the ones another kernel owns is cheaper than an index list
-    // while most rows are short scalar-path rows; otherwise keep the explicit list.
-    if ((int64_t)p->n_short * 2 < n_rows) {
-        HC_ALLOC(keep, p->short_rows, p->n_short);
-        HC_TRY(launch_compact_ids(n_rows, f_short, pos_a, p->short_rows, stream));
-    } else {
-        p->short_rows = nullptr;
-    }
-    HC_ALLOC(keep, p->rest_rows, p->n_rest);
-    HC_TRY(launch_compact_ids(n_rows, f_rest, pos_f, p->rest_rows, stream));
-    HC_TRY(rb.sync(stream));
+    if (p->n_mfma > 0 || p->short_rows) HC_TRY(rb.sync(stream));
     p->device_bytes = keep.bytes;
     if (keep.ptrs.size() > sizeof p->chunks / sizeof p->chunks[0]) {
         set_error("internal: too many plan chunks");
@@ -1130,24 +1036,13 @@ hcspmm_status hcspmm_plan_update(hcspmm_plan* plan, int64_t nnz, const int32_t* 
     // a plan that is updated keeps the device blocks of its updates (see BlockCache)
     if (!plan->cache) plan->cache = new (std::nothrow) BlockCache;
     fresh.cache = plan->cache;
-    int32_t* d_touched = nullptr;
-    size_t touched_bytes = 0;
-    PlanCarry carry{plan->ncols, nullptr, (int32_t)touched.size()};
+    PlanCarry carry{plan->ncols, touched.data(), (int32_t)touched.size()};
     // The counts of untouched windows are carried over whenever the old plan has them and fewer than an eighth of
     // the windows changed (beyond that the list-driven passes cost as much as the plain ones); otherwise this is a
     // preparation from scratch.
     const bool incremental = plan->features_complete && plan->nnz > 0 && !touched.empty() && 8 * (int64_t)touched.size() < plan->W &&
                              !(plan->opt.route_mode == HCSPMM_ROUTE_ALL_CSR);
     if (incremental) {
-        touched_bytes = touched.size() * sizeof(int32_t);
-        if (plan->cache) d_touched = static_cast<int32_t*>(plan->cache->take(touched_bytes, &touched_bytes));
-        if (!d_touched && hipMalloc((void**)&d_touched, touched_bytes) != hipSuccess) {
-            (void)hipGetLastError(); set_error("device allocation failed"); return HCSPMM_EALLOC;
-        }
-        if (hipMemcpyAsync(d_touched, touched.data(), touched.size() * sizeof(int32_t), hipMemcpyHostToDevice, s) != hipSuccess) {
-            (void)hipGetLastError(); (void)hipFree(d_touched); set_error("copy of the window list failed"); return HCSPMM_EHIP;
-        }
-        carry.touched = d_touched;
         // (a plan with an unsorted row somewhere does not say where: its structure is not carried)
         if (plan->n_mfma > 0 && plan->erc && plan->wcols && plan->rows_sorted) {
             carry.old_route = plan->route; carry.old_wptr = plan->wptr; carry.old_nnzw = plan->nnzw;
@@ -1161,10 +1056,6 @@ hcspmm_status hcspmm_plan_update(hcspmm_plan* plan, int64_t nnz, const int32_t* 
         return HCSPMM_OK;
     }
     st = build_plan(&fresh, s, incremental ? &carry : nullptr);
-    if (d_touched) {
-        if (plan->cache) plan->cache->give(d_touched, touched_bytes);
-        else (void)hipFree(d_touched);
-    }
     if (st != HCSPMM_OK) return st;                              // the old plan is untouched and still valid for the old arrays
     // the new tables replace the old ones; streams, events and the lazily sized scratch buffers stay
     fresh.partial = plan->partial; fresh.partial_elems = plan->partial_elems;
@@ -1224,7 +1115,9 @@ hcspmm_status hcspmm_plan_export(const hcspmm_plan* p, int32_t* ncols, int32_t* 
         for (int64_t k = 0; k < p->nnz; ++k) ecol[k] >>= 4;    // drop the packed row-in-window
     }
     if (mfma_windows && p->n_mfma) HC_HIP(hipMemcpy(mfma_windows, p->mfma_windows, (size_t)p->n_mfma * 4, hipMemcpyDeviceToHost));
-    if (csr_windows && p->n_csr) HC_HIP(hipMemcpy(csr_windows, p->csr_windows, (size_t)p->n_csr * 4, hipMemcpyDeviceToHost));
+    if (csr_windows && p->n_mfma == 0)                          // every window: the plan keeps no list
+        for (int32_t w = 0; w < p->n_csr; ++w) csr_windows[w] = w;
+    else if (csr_windows && p->n_csr) HC_HIP(hipMemcpy(csr_windows, p->csr_windows, (size_t)p->n_csr * 4, hipMemcpyDeviceToHost));
     return HCSPMM_OK;
 }
 

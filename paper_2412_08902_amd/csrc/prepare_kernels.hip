@@ -5,6 +5,8 @@
 // window's distinct column ids and (b) for every non-zero the position of its column in that
 // list.  Section IV-C: the per-window features (number of non-zero columns, sparsity) feed a
 // three-parameter linear model whose sign picks the path; it is evaluated in exact integers.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace hcspmm {
@@ -249,48 +251,6 @@ hipError_t exclusive_scan_multi(const ScanMulti& m, int64_t n, int64_t* totals_d
 }
 
 // ------------------------------------------------------------------------------------------------
-// CSR validation
-// ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_validate_rowptr(int32_t n_rows, int64_t nnz, const int32_t* __restrict__ rowptr,
-                                                         int32_t* __restrict__ err)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) {
-        if (rowptr[0] != 0) atomicOr(err, 1);
-        if ((int64_t)rowptr[n_rows] != nnz) atomicOr(err, 2);
-    }
-    if (i < n_rows) {
-        int32_t a = rowptr[i], b = rowptr[i + 1];
-        if (a < 0 || b < a) atomicOr(err, 4);
-    }
-}
-
-__global__ __launch_bounds__(256) void k_validate_cols(int32_t n_cols, int64_t nnz, const int32_t* __restrict__ colind,
-                                                       int32_t* __restrict__ err)
-{
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    bool bad = false;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nnz; k += stride) {
-        int32_t c = colind[k];
-        bad |= (c < 0 || c >= n_cols);
-    }
-    if (bad) atomicOr(err, 8);
-}
-
-hipError_t launch_validate(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t* rowptr, const int32_t* colind,
-                           int32_t* err_flag, hipStream_t s)
-{
-    unsigned g = (unsigned)(((int64_t)n_rows + 1 + 255) / 256);
-    hipLaunchKernelGGL(k_validate_rowptr, dim3(g), dim3(256), 0, s, n_rows, nnz, rowptr, err_flag);
-    if (nnz > 0) {
-        int64_t blocks = (nnz + 256 * 8 - 1) / (256 * 8);
-        if (blocks > 65536) blocks = 65536;
-        hipLaunchKernelGGL(k_validate_cols, dim3((unsigned)blocks), dim3(256), 0, s, n_cols, nnz, colind, err_flag);
-    }
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------
 // per-window non-zero count, and the list of windows too large for the LDS sort
 // ------------------------------------------------------------------------------------------------
 __device__ inline void window_span(int32_t w, int32_t n_rows, const int32_t* __restrict__ rowptr, int32_t& s,
@@ -436,45 +396,109 @@ hipError_t launch_unique_big(int32_t n_big, const int32_t* big_list, int32_t n_r
 }
 
 // ------------------------------------------------------------------------------------------------
-// window features without the lists: the selector needs only the NUMBER of distinct columns, which
-// an LDS hash set gives for a fraction of the sort's cost; the sorted lists are then built for the
-// matrix path's windows alone
+// From the CSR arrays to a plan's launch tables in seven launches and one read-back.
+//
+// A preparation's work is small (a medium graph: ~40 us of kernels), so launches and synchronisations are what it costs.
+// (27 launches, three-kernel scans over arrays of flags and six read-backs took 240 us on 17,000 rows and 490 us on
+// 169,000, most of it in the scans' few wavefronts and in waiting.)  Here every kernel leaves at once when an earlier one
+// has found the CSR arrays unsound, so nothing waits for the host in between; flags are recomputed from the row offsets
+// where they are needed instead of being written, scanned and read back; and a tile of 64 windows (1024 rows) writes its
+// sums once, from which every workgroup of the next kernel adds up its own offset (2,400 tiles, C4's number, are 57 KB
+// out of L2 per workgroup).  The totals go straight into a page of host memory.
+//   k_pre_validate   row offsets; non-zeros per window; windows by size class
+//   k_pre_count*     distinct columns per window by LDS hash sets (bitmap passes beyond their capacity), range of the columns
+//   k_pre_select     selection per window, sums per tile
+//   k_pre_rows       launch guard, route and list offset per window, row classes, sums per tile
+//   k_pre_fill       row lists, segments of long rows, totals
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_window_classes(int32_t W, int32_t n_rows, const int32_t* __restrict__ rowptr,
-                                                        int32_t* __restrict__ nnzw, int32_t* __restrict__ mid_list,
-                                                        int32_t* __restrict__ huge_list, int32_t* __restrict__ counts)
+constexpr int kTileWindows = 64, kTileRows = kTileWindows * kH;
+constexpr int kBigTakes1kWindows = 16384;
+constexpr int kWt = 8, kRt = 3;                                 // 64-bit sums per tile: windows, rows
+
+size_t prep_tile_count(int32_t W) { return (size_t)((W + kTileWindows - 1) / kTileWindows > 0 ? (W + kTileWindows - 1) / kTileWindows : 1); }
+size_t prep_tile_words(int32_t W) { return prep_tile_count(W) * (kWt + kRt); }
+
+template <class T> __device__ inline T wave_sum(T v)
 {
-    int32_t w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= W) return;
-    int32_t s, e;
-    window_span(w, n_rows, rowptr, s, e);
-    const int32_t n = e - s;
-    nnzw[w] = n;
-    if (n > kCountMidCap) huge_list[atomicAdd(counts + 1, 1)] = w;
-    else if (n > kUniqueSmallCap) mid_list[atomicAdd(counts, 1)] = w;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
 }
 
-hipError_t launch_window_classes(int32_t W, int32_t n_rows, const int32_t* rowptr, int32_t* nnzw, int32_t* mid_list,
-                                 int32_t* huge_list, int32_t* counts, hipStream_t s)
+// sum over the workgroup's 256 threads, in every thread
+__device__ inline unsigned long long block_sum_u64(unsigned long long v, unsigned long long* smem /* 4 */)
 {
-    hipLaunchKernelGGL(k_window_classes, dim3((W + 255) / 256), dim3(256), 0, s, W, n_rows, rowptr, nnzw, mid_list,
-                       huge_list, counts);
-    return hipGetLastError();
+    v = wave_sum(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return smem[0] + smem[1] + smem[2] + smem[3];
 }
 
-// Inserts the window's column ids into an open-addressing set of SLOTS >= 2n entries (linear probing,
-// empty = -1; ids are non-negative) and counts the insertions that found an empty slot.  The set is
-// never more than half full, so every probe sequence ends.
-template <int NT, int SLOTS>
-__device__ inline void count_distinct_body(int32_t w, int32_t n_rows, const int32_t* __restrict__ rowptr,
-                                           const int32_t* __restrict__ colind, int32_t* __restrict__ ncols,
-                                           int32_t* table, int* smem)
+// exclusive prefix over the workgroup's 256 threads
+__device__ inline unsigned long long block_scan_u64(unsigned long long v, unsigned long long* smem /* 4 */)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned long long inc = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long t = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += t;
+    }
+    __syncthreads();
+    if (lane == 63) smem[wave] = inc;
+    __syncthreads();
+    unsigned long long base = 0;
+    for (int i = 0; i < wave; ++i) base += smem[i];
+    return base + inc - v;
+}
+
+__global__ __launch_bounds__(256) void k_pre_validate(Prep p)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) {
+        if (p.rowptr[0] != 0) atomicOr(p.ctl, 1);
+        if ((int64_t)p.rowptr[p.n_rows] != p.nnz) atomicOr(p.ctl, 2);
+    }
+    if (i >= p.n_rows) return;
+    const int32_t a = p.rowptr[i], b = p.rowptr[i + 1];
+    if (a < 0 || b < a) atomicOr(p.ctl, 4);
+    if (i % kH != 0) return;
+    // (differences of unsound offsets are only ever compared; nothing indexes with them)
+    const int32_t w = (int32_t)(i / kH), n = p.rowptr[min(i + kH, (int64_t)p.n_rows)] - a;
+    p.nnzw[w] = n;
+    if (p.old_ncols) p.ncols[w] = p.old_ncols[w];               // counts of untouched windows are carried over
+    else if (!p.features) p.ncols[w] = 0;                       // a scalar-only plan counts on first request
+    if (!p.features) return;
+    if (n > kCountMidCap) p.huge_list[atomicAdd(p.ctl + 2, 1)] = w;
+    else if (n > kUniqueSmallCap) p.big_list[atomicAdd(p.ctl + 1, 1)] = w;
+    else if (n > kCountTinyCap && !p.touched) p.count_1k[atomicAdd(p.ctl + 3, 1)] = w;
+}
+
+// columns only (a plan that counts nothing still checks them)
+__global__ __launch_bounds__(256) void k_validate_cols(int32_t n_cols, int64_t nnz, const int32_t* __restrict__ colind,
+                                                       int32_t* __restrict__ err)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    bool bad = false;
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nnz; k += stride) {
+        const int32_t c = colind[k];
+        bad |= (c < 0 || c >= n_cols);
+    }
+    if (bad) atomicOr(err, 8);
+}
+
+// Inserts the window's column ids into an open-addressing set of at least 2n entries (linear probing, empty = -1; an id
+// outside the matrix is reported and left out) and counts the insertions that found an empty slot.  The set is never more
+// than half full, so every probe sequence ends.
+template <int NT>
+__device__ inline void count_distinct(int32_t w, const Prep& p, int32_t* table, int* smem)
 {
     int32_t s, e;
-    window_span(w, n_rows, rowptr, s, e);
+    window_span(w, p.n_rows, p.rowptr, s, e);
     const int32_t n = e - s;
     if (n == 0) {
-        if (threadIdx.x == 0) ncols[w] = 0;
+        if (threadIdx.x == 0) p.ncols[w] = 0;
         return;
     }
     int T = NT;                                   // power of two, at least twice the entries
@@ -483,74 +507,414 @@ __device__ inline void count_distinct_body(int32_t w, int32_t n_rows, const int3
     for (int i = threadIdx.x; i < T; i += NT) table[i] = -1;
     __syncthreads();
     int cnt = 0;
-    for (int32_t k = s + threadIdx.x; k < e; k += NT) {
-        const int32_t c = colind[k];
-        uint32_t h = ((uint32_t)c * 0x9E3779B1u >> 12) & mask;
-        for (;;) {
-            const int32_t prev = atomicCAS(&table[h], -1, c);
-            if (prev == -1) { ++cnt; break; }
-            if (prev == c) break;
-            h = (h + 1) & mask;
+    bool bad = false;
+    for (int32_t k0 = s + threadIdx.x; k0 < e; k0 += 4 * NT) {  // (four loads in flight: a window is little else than their latency)
+        int32_t col[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) col[j] = p.colind[min(k0 + j * NT, e - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (k0 + j * NT >= e) break;
+            const int32_t c = col[j];
+            if (c < 0 || c >= p.n_cols) { bad = true; continue; }
+            uint32_t h = ((uint32_t)c * 0x9E3779B1u >> 12) & mask;
+            for (;;) {
+                const int32_t prev = atomicCAS(&table[h], -1, c);
+                if (prev == -1) { ++cnt; break; }
+                if (prev == c) break;
+                h = (h + 1) & mask;
+            }
         }
     }
+    if (bad) atomicOr(p.ctl, 8);
     int total;
     (void)block_exclusive_scan<NT>(cnt, &total, smem);
-    if (threadIdx.x == 0) ncols[w] = total;
+    if (threadIdx.x == 0) p.ncols[w] = total;
 }
 
-__global__ __launch_bounds__(256) void k_count_small(int32_t W, int32_t n_rows, const int32_t* __restrict__ rowptr,
-                                                     const int32_t* __restrict__ colind, int32_t* __restrict__ ncols)
+// windows of up to kCountTinyCap non-zeros, one workgroup each: all windows, or -- after a structural change -- the
+// touched ones, whose larger members are listed for the kernels below
+__global__ __launch_bounds__(256) void k_pre_count(Prep p)
+{
+    __shared__ int32_t table[2 * kCountTinyCap];
+    __shared__ int smem[256 / 64 + 1];
+    if (*p.ctl & 7) return;
+    const int32_t w = p.touched ? p.touched[blockIdx.x] : (int32_t)blockIdx.x;
+    const int32_t n = p.nnzw[w];
+    if (n > kCountTinyCap) {
+        if (p.touched && threadIdx.x == 0) {
+            if (n > kCountMidCap) p.count_huge[atomicAdd(p.n_count_huge, 1)] = w;
+            else if (n > kUniqueSmallCap) p.count_mid[atomicAdd(p.n_count_mid, 1)] = w;
+            else p.count_1k[atomicAdd(p.ctl + 3, 1)] = w;
+        }
+        return;
+    }
+    count_distinct<256>(w, p, table, smem);
+}
+
+__global__ __launch_bounds__(256) void k_pre_count_1k(Prep p)
 {
     __shared__ int32_t table[2 * kUniqueSmallCap];
     __shared__ int smem[256 / 64 + 1];
-    const int32_t w = blockIdx.x;
-    int32_t s, e;
-    window_span(w, n_rows, rowptr, s, e);
-    if (e - s > kUniqueSmallCap) return;          // listed for k_count_mid or the bitmap kernel
-    count_distinct_body<256, 2 * kUniqueSmallCap>(w, n_rows, rowptr, colind, ncols, table, smem);
+    if (*p.ctl & 7) return;
+    const int32_t n = p.ctl[3];
+    for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        count_distinct<256>(p.count_1k[i], p, table, smem);
+        __syncthreads();
+    }
 }
 
-__global__ __launch_bounds__(1024) void k_count_mid(const int32_t* __restrict__ mid_list, int32_t n_rows,
-                                                    const int32_t* __restrict__ rowptr,
-                                                    const int32_t* __restrict__ colind, int32_t* __restrict__ ncols)
+__global__ __launch_bounds__(1024) void k_pre_count_big(Prep p)
 {
     __shared__ int32_t table[2 * kCountMidCap];
     __shared__ int smem[1024 / 64 + 1];
-    count_distinct_body<1024, 2 * kCountMidCap>(mid_list[blockIdx.x], n_rows, rowptr, colind, ncols, table, smem);
+    static_assert(2 * kCountMidCap >= kBitmapWords, "the bitmap shares the hash set's memory");
+    if (*p.ctl & 7) return;
+    const int32_t n_huge = *p.n_count_huge, n_mid = *p.n_count_mid, n_1k = p.big_takes_1k ? p.ctl[3] : 0;
+    for (int32_t i = blockIdx.x; i < n_huge + n_mid + n_1k; i += gridDim.x) {
+        if (i >= n_huge) {
+            count_distinct<1024>(i < n_huge + n_mid ? p.count_mid[i - n_huge] : p.count_1k[i - n_huge - n_mid], p, table, smem);
+        } else {
+            // more entries than the set holds: a bitmap over 2^20 columns per pass
+            uint32_t* __restrict__ bm = reinterpret_cast<uint32_t*>(table);
+            constexpr int kBits = kBitmapWords * 32;
+            const int32_t w = p.count_huge[i];
+            int32_t s, e;
+            window_span(w, p.n_rows, p.rowptr, s, e);
+            int cnt = 0;
+            bool bad = false;
+            for (int64_t base = 0; base < p.n_cols; base += kBits) {
+                for (int j = threadIdx.x; j < kBitmapWords; j += 1024) bm[j] = 0u;
+                __syncthreads();
+                for (int32_t k = s + threadIdx.x; k < e; k += 1024) {
+                    const int32_t col = p.colind[k];
+                    bad |= col < 0 || col >= p.n_cols;
+                    const int64_t c = (int64_t)col - base;
+                    if (c >= 0 && c < kBits) atomicOr(&bm[c >> 5], 1u << (c & 31));
+                }
+                __syncthreads();
+                for (int j = threadIdx.x; j < kBitmapWords; j += 1024) cnt += __popc(bm[j]);
+                __syncthreads();
+            }
+            if (bad) atomicOr(p.ctl, 8);
+            int total;
+            (void)block_exclusive_scan<1024>(cnt, &total, smem);
+            if (threadIdx.x == 0) p.ncols[w] = total;
+        }
+        __syncthreads();
+    }
 }
 
-// ---- incremental preparation: only the windows that hold a changed row are looked at again ------
-// classes of the touched windows by size (which counting kernel serves them), and the range check of their columns
-__global__ __launch_bounds__(256) void k_touched_classes(int32_t n_touched, const int32_t* __restrict__ touched,
-                                                         int32_t n_rows, int32_t n_cols, const int32_t* __restrict__ rowptr,
-                                                         const int32_t* __restrict__ colind, int32_t* __restrict__ t_small,
-                                                         int32_t* __restrict__ t_mid, int32_t* __restrict__ t_huge,
-                                                         int32_t* __restrict__ counts /* 3 */, int32_t* __restrict__ err)
+// selection (Section IV-C): z' = c0*H*ncols^2 + c1*(H*ncols - nnzw) + c2*H*ncols ; matrix path iff z' < 0
+__device__ inline int window_route(const Prep& p, int mode, long long nc, long long nz)
 {
-    const int32_t w = touched[blockIdx.x];
-    int32_t s, e;
-    window_span(w, n_rows, rowptr, s, e);
-    const int32_t n = e - s;
+    if (nc <= 0 || mode == HCSPMM_ROUTE_ALL_CSR) return 0;
+    if (mode == HCSPMM_ROUTE_ALL_MFMA) return 1;
+    // |c*| < 2^40 and H*ncols^2 < 2^58: 128-bit integers keep the sign exact
+    const __int128 hn = (__int128)kH * nc;
+    const __int128 z = (__int128)p.c0 * hn * nc + (__int128)p.c1 * (hn - nz) + (__int128)p.c2 * hn;
+    return z < 0 ? 1 : 0;
+}
+
+// windows on the matrix path | ... of the wave-per-window kernel | medium | wide, 16 bits each (a tile has 64 windows)
+__device__ inline unsigned long long window_counts(int r, long long nc)
+{
+    if (!r) return 0ull;
+    return 1ull | (nc <= kMfmaSmallMaxCols ? 1ull << 16 : nc <= kMfmaMidMaxCols ? 1ull << 32 : 1ull << 48);
+}
+
+// Per tile: [0] distinct columns; [1] non-zeros, [2] window counts, [3] columns of wide windows on the matrix path under
+// the plan's own mode; [4..6] the same with every window there (what the launch guard may decide for)
+__global__ __launch_bounds__(256) void k_pre_select(Prep p)
+{
+    if (*p.ctl) return;
+    const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (tile >= p.n_tiles) return;
+    const int32_t w = tile * kTileWindows + (threadIdx.x & 63);
+    const long long nc = w < p.W ? p.ncols[w] : 0, nz = w < p.W ? p.nnzw[w] : 0;
+    unsigned long long v[7] = {(unsigned long long)nc, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int set = 0; set < 2; ++set) {
+        const int r = window_route(p, set == 0 ? p.mode : HCSPMM_ROUTE_ALL_MFMA, nc, nz);
+        v[1 + 3 * set] = r ? (unsigned long long)nz : 0ull;
+        v[2 + 3 * set] = window_counts(r, nc);
+        v[3 + 3 * set] = r && nc > kMfmaMidMaxCols ? (unsigned long long)nc : 0ull;
+    }
+#pragma unroll
+    for (int i = 0; i < 7; ++i) v[i] = wave_sum(v[i]);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int i = 0; i < 7; ++i) p.wt[(int64_t)tile * kWt + i] = v[i];
+}
+
+// Launch guard: a path whose share cannot repay a kernel launch of its own joins the other path.
+__device__ inline int effective_mode(const Prep& p, unsigned long long on_matrix_)
+{
+    if (p.mode != HCSPMM_ROUTE_HYBRID) return p.mode;
+    const int64_t on_matrix = (int64_t)on_matrix_, on_scalar = p.nnz - on_matrix;
+    if (on_matrix > 0 && on_scalar > 0) {
+        if (on_matrix < kGuardNnz && kGuardShare * on_matrix < p.nnz) return HCSPMM_ROUTE_ALL_CSR;
+        if (on_scalar < kGuardNnz && kGuardShare * on_scalar < p.nnz) return HCSPMM_ROUTE_ALL_MFMA;
+    }
+    return p.mode;
+}
+__device__ inline int counts_set(const Prep& p, int mode)       // which set of the tile sums holds for the effective mode (-1: none)
+{
+    return mode == p.mode ? 0 : (mode == HCSPMM_ROUTE_ALL_MFMA ? 1 : -1);
+}
+
+// One row's place in the scalar path's tables.
+struct RowClass { int is_short, is_mid, n_seg, rest, len_long; };
+__device__ inline RowClass row_class(const Prep& p, int32_t len, int route, int wide_window)
+{
+    RowClass c;
+    const bool csr = route == 0, is_long = csr && len > p.long_row;
+    c.is_mid = csr && !is_long && len > p.mid_row;
+    c.is_short = csr && !is_long && !c.is_mid;
+    c.n_seg = is_long ? (len + kSegLen - 1) / kSegLen : 0;
+    // rows whose aggregated values reach memory even when the update stage is fused into the SpMM kernels: scalar-path
+    // rows above the fused tier and all rows of matrix-path windows too wide for the wave-per-window kernel
+    c.rest = csr ? len > p.fused_mid_row : wide_window;
+    c.len_long = (is_long || c.is_mid) ? len : 0;
+    return c;
+}
+// short | mid | rest | multi-segment rows, 16 bits each (a tile has 1024 rows); segments | partial rows, 32 bits each
+__device__ inline unsigned long long row_counts(const RowClass& c)
+{
+    return (unsigned long long)c.is_short | (unsigned long long)c.is_mid << 16 | (unsigned long long)c.rest << 32 |
+           (unsigned long long)(c.n_seg > 1) << 48;
+}
+__device__ inline unsigned long long seg_counts(const RowClass& c)
+{
+    return (unsigned long long)c.n_seg | (unsigned long long)(c.n_seg > 1 ? c.n_seg : 0) << 32;
+}
+
+__global__ __launch_bounds__(256) void k_pre_rows(Prep p)
+{
+    __shared__ unsigned long long smem[4];
+    __shared__ uint8_t s_route[kTileWindows], s_wide[kTileWindows];
+    if (*p.ctl) return;
+    const int tile = blockIdx.x;
+    unsigned long long before = 0, on_matrix = 0;
+    for (int t = threadIdx.x; t < p.n_tiles; t += 256) {
+        on_matrix += p.wt[(int64_t)t * kWt + 1];
+        if (t < tile) before += p.wt[(int64_t)t * kWt];
+    }
+    before = block_sum_u64(before, smem);
+    on_matrix = block_sum_u64(on_matrix, smem);
+    const int mode = effective_mode(p, on_matrix);
+    if (threadIdx.x < kTileWindows) {
+        const int32_t w = tile * kTileWindows + threadIdx.x;
+        const long long nc = w < p.W ? p.ncols[w] : 0, nz = w < p.W ? p.nnzw[w] : 0;
+        const int r = window_route(p, mode, nc, nz);
+        s_route[threadIdx.x] = (uint8_t)r;
+        s_wide[threadIdx.x] = nc > kMfmaSmallMaxCols ? 1 : 0;
+        unsigned long long inc = (unsigned long long)nc;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned long long t = __shfl_up(inc, off, 64);
+            if ((int)threadIdx.x >= off) inc += t;
+        }
+        if (w < p.W) {
+            p.route[w] = (uint8_t)r;
+            p.wptr[w] = (int64_t)(before + inc - (unsigned long long)nc);
+            if (w == p.W - 1) p.wptr[p.W] = (int64_t)(before + inc);
+        }
+        if (p.W == 0 && threadIdx.x == 0) p.wptr[0] = 0;
+    }
+    __syncthreads();
+    unsigned long long a = 0, b = 0, len_long = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int rl = threadIdx.x * 4 + j;
+        const int64_t i = (int64_t)tile * kTileRows + rl;
+        if (i >= p.n_rows) break;
+        const RowClass c = row_class(p, p.rowptr[i + 1] - p.rowptr[i], s_route[rl / kH], s_wide[rl / kH]);
+        a += row_counts(c);
+        b += seg_counts(c);
+        len_long += (unsigned long long)c.len_long;
+    }
+    a = block_sum_u64(a, smem);
+    b = block_sum_u64(b, smem);
+    len_long = block_sum_u64(len_long, smem);
     if (threadIdx.x == 0) {
-        if (n > kCountMidCap) t_huge[atomicAdd(counts + 2, 1)] = w;
-        else if (n > kUniqueSmallCap) t_mid[atomicAdd(counts + 1, 1)] = w;
-        else t_small[atomicAdd(counts, 1)] = w;
+        p.rt[(int64_t)tile * kRt] = a;
+        p.rt[(int64_t)tile * kRt + 1] = b;
+        p.rt[(int64_t)tile * kRt + 2] = len_long;
     }
-    bool bad = false;
-    for (int32_t k = s + threadIdx.x; k < e; k += 256) {
-        const int32_t c = colind[k];
-        bad |= (c < 0 || c >= n_cols);
-    }
-    if (bad) atomicOr(err, 8);
 }
 
-__global__ __launch_bounds__(256) void k_count_small_list(const int32_t* __restrict__ list, int32_t n_rows,
-                                                          const int32_t* __restrict__ rowptr,
-                                                          const int32_t* __restrict__ colind, int32_t* __restrict__ ncols)
+// Fills the row tables whose pointers are set; one workgroup behind the last tile's writes the totals (when p.out is set).
+__global__ __launch_bounds__(256) void k_pre_fill(Prep p)
 {
-    __shared__ int32_t table[2 * kUniqueSmallCap];
-    __shared__ int smem[256 / 64 + 1];
-    count_distinct_body<256, 2 * kUniqueSmallCap>(list[blockIdx.x], n_rows, rowptr, colind, ncols, table, smem);
+    __shared__ unsigned long long smem[4];
+    const int tile = blockIdx.x;
+    const bool last = tile == p.n_tiles;
+    if (*p.ctl) {
+        if (last && threadIdx.x == 0 && p.out) p.out->err = *p.ctl;
+        return;
+    }
+    unsigned long long sm = 0, rm = 0, seg = 0;                 // short | mid, rest | multi, segments | partial rows in front of the tile
+    for (int t = threadIdx.x; t < tile; t += 256) {
+        const unsigned long long a = p.rt[(int64_t)t * kRt], b = p.rt[(int64_t)t * kRt + 1];
+        sm += (a & 0xffffull) | (a >> 16 & 0xffffull) << 32;
+        rm += (a >> 32 & 0xffffull) | (a >> 48) << 32;
+        seg += b;
+    }
+    sm = block_sum_u64(sm, smem);
+    rm = block_sum_u64(rm, smem);
+    seg = block_sum_u64(seg, smem);
+    RowClass c[4];
+    int32_t start[5];
+    unsigned long long a = 0, b = 0;
+    const int64_t i0 = min((int64_t)tile * kTileRows + threadIdx.x * 4, (int64_t)p.n_rows);
+    const int32_t w = (int32_t)(i0 / kH);
+    const int route = w < p.W ? p.route[w] : 0, wide = w < p.W ? (p.ncols[w] > kMfmaSmallMaxCols ? 1 : 0) : 0;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) start[j] = p.rowptr[min(i0 + j, (int64_t)p.n_rows)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        c[j] = RowClass{0, 0, 0, 0, 0};
+        if (i0 + j < p.n_rows) c[j] = row_class(p, start[j + 1] - start[j], route, wide);
+        a += row_counts(c[j]);
+        b += seg_counts(c[j]);
+    }
+    const unsigned long long ea = block_scan_u64(a, smem);
+    const unsigned long long eb = block_scan_u64(b, smem);
+    uint32_t n_short = (uint32_t)sm + (uint32_t)(ea & 0xffffull), n_mid = (uint32_t)(sm >> 32) + (uint32_t)(ea >> 16 & 0xffffull);
+    uint32_t n_rest = (uint32_t)rm + (uint32_t)(ea >> 32 & 0xffffull), n_multi = (uint32_t)(rm >> 32) + (uint32_t)(ea >> 48);
+    uint32_t n_seg = (uint32_t)seg + (uint32_t)eb, n_slot = (uint32_t)(seg >> 32) + (uint32_t)(eb >> 32);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int32_t i = (int32_t)(i0 + j);
+        if (c[j].is_short) { if (p.short_rows) p.short_rows[n_short] = i; ++n_short; }
+        if (c[j].is_mid) { if (p.mid_rows) p.mid_rows[n_mid] = i; ++n_mid; }
+        if (c[j].rest) { if (p.rest_rows) p.rest_rows[n_rest] = i; ++n_rest; }
+        const int ns = c[j].n_seg;
+        if (ns == 0) continue;
+        if (p.segs)
+            for (int q = 0; q < ns; ++q) {
+                Segment sg;
+                sg.row = i;
+                sg.k_begin = start[j] + q * kSegLen;
+                sg.k_end = min(start[j + 1], sg.k_begin + kSegLen);
+                sg.slot = ns > 1 ? (int32_t)(n_slot + q) : -1;
+                p.segs[n_seg + q] = sg;
+            }
+        n_seg += ns;
+        if (ns > 1) {
+            if (p.multi) {
+                MultiRow m;
+                m.row = i; m.first_slot = (int32_t)n_slot; m.n_slots = ns; m.pad = 0;
+                p.multi[n_multi] = m;
+            }
+            ++n_multi;
+            n_slot += ns;
+        }
+    }
+    if (!last || !p.out) return;
+    // what is in front of the place behind the last tile are the row totals; the window totals come from the tile sums too
+    unsigned long long v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int t = threadIdx.x; t < p.n_tiles; t += 256) v[7] += p.wt[(int64_t)t * kWt + 1];
+    const int set = counts_set(p, effective_mode(p, block_sum_u64(v[7], smem)));
+    for (int t = threadIdx.x; t < p.n_tiles; t += 256) {
+        v[0] += p.wt[(int64_t)t * kWt];
+        v[1] += p.rt[(int64_t)t * kRt + 2];
+        if (set < 0) continue;
+        const unsigned long long n = p.wt[(int64_t)t * kWt + 2 + 3 * set];
+        v[2] += p.wt[(int64_t)t * kWt + 1 + 3 * set];
+        v[3] += (n & 0xffffull) | (n >> 16 & 0xffffull) << 32;
+        v[4] += (n >> 32 & 0xffffull) | (n >> 48) << 32;
+        v[5] += p.wt[(int64_t)t * kWt + 3 + 3 * set];
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = block_sum_u64(v[k], smem);
+    if (threadIdx.x == 0) {
+        PrepTotals t{};
+        t.total_ncols = (int64_t)v[0]; t.nnz_long = (int64_t)v[1]; t.nnz_mfma = (int64_t)v[2]; t.wide_cols = (int64_t)v[5];
+        t.n_mfma = (int32_t)v[3]; t.n_mfma_small = (int32_t)(v[3] >> 32);
+        t.n_mfma_mid = (int32_t)v[4]; t.n_mfma_big = (int32_t)(v[4] >> 32);
+        t.n_short = (int32_t)n_short; t.n_mid = (int32_t)n_mid; t.n_rest = (int32_t)n_rest; t.n_multi = (int32_t)n_multi;
+        t.n_segs = (int32_t)n_seg; t.n_slots = (int64_t)n_slot;
+        t.n_big_list = p.ctl[1]; t.n_huge_list = p.ctl[2];
+        t.err = 0;
+        *p.out = t;
+    }
+}
+
+// ascending window lists per route and kernel
+__global__ __launch_bounds__(256) void k_pre_windows(Prep p, int32_t* __restrict__ mfma, int32_t* __restrict__ csr,
+                                                     int32_t* __restrict__ small, int32_t* __restrict__ mid, int32_t* __restrict__ big)
+{
+    const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (tile >= p.n_tiles) return;
+    unsigned long long on_matrix = 0, lo = 0, hi = 0;           // matrix | small, medium | wide windows in front of the tile
+    for (int t = lane; t < p.n_tiles; t += 64) on_matrix += p.wt[(int64_t)t * kWt + 1];
+    const int set = counts_set(p, effective_mode(p, wave_sum(on_matrix)));
+    if (set >= 0)
+        for (int t = lane; t < tile; t += 64) {
+            const unsigned long long n = p.wt[(int64_t)t * kWt + 2 + 3 * set];
+            lo += (n & 0xffffull) | (n >> 16 & 0xffffull) << 32;
+            hi += (n >> 32 & 0xffffull) | (n >> 48) << 32;
+        }
+    lo = wave_sum(lo);
+    hi = wave_sum(hi);
+    const int32_t w = tile * kTileWindows + lane;
+    const int r = w < p.W ? p.route[w] : 0;
+    const unsigned long long n = w < p.W ? window_counts(r, p.ncols[w]) : 0;
+    unsigned long long inc = n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long t = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += t;
+    }
+    if (w >= p.W) return;
+    const unsigned long long ex = inc - n;
+    const uint32_t i_mfma = (uint32_t)lo + (uint32_t)(ex & 0xffffull);
+    if (!r) { csr[w - i_mfma] = w; return; }
+    mfma[i_mfma] = w;
+    if (n >> 16 & 0xffffull) small[(uint32_t)(lo >> 32) + (uint32_t)(ex >> 16 & 0xffffull)] = w;
+    else if (n >> 32 & 0xffffull) mid[(uint32_t)hi + (uint32_t)(ex >> 32 & 0xffffull)] = w;
+    else big[(uint32_t)(hi >> 32) + (uint32_t)(ex >> 48)] = w;
+}
+
+hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
+{
+    Prep p = p_;
+    p.big_takes_1k = (p.touched ? n_touched : p.W) <= kBigTakes1kWindows ? 1 : 0;
+    hipLaunchKernelGGL(k_pre_validate, dim3((unsigned)(((int64_t)p.n_rows + 1 + 255) / 256)), dim3(256), 0, s, p);
+    if (p.features && p.W > 0) {
+        const int64_t n_count = p.touched ? n_touched : p.W;
+        if (n_count > 0) hipLaunchKernelGGL(k_pre_count, dim3((unsigned)n_count), dim3(256), 0, s, p);
+        // windows beyond the small set's capacity; how many there are only the device knows, so the grids are bounded by
+        // what the matrix can hold and walk the lists
+        auto most = [&](int64_t cap, int64_t limit) { return (unsigned)std::min<int64_t>({n_count, p.nnz / (cap + 1), limit}); };
+        // (few windows to count: one launch serves both classes)
+        const int64_t cap_big = p.big_takes_1k ? kCountTinyCap : kUniqueSmallCap;
+        if (!p.big_takes_1k && most(kCountTinyCap, 2048) > 0)
+            hipLaunchKernelGGL(k_pre_count_1k, dim3(most(kCountTinyCap, 2048)), dim3(256), 0, s, p);
+        if (most(cap_big, 256) > 0) hipLaunchKernelGGL(k_pre_count_big, dim3(most(cap_big, 256)), dim3(1024), 0, s, p);
+    } else if (p.nnz > 0) {
+        int64_t blocks = (p.nnz + 256 * 8 - 1) / (256 * 8);
+        if (blocks > 65536) blocks = 65536;
+        hipLaunchKernelGGL(k_validate_cols, dim3((unsigned)blocks), dim3(256), 0, s, p.n_cols, p.nnz, p.colind, p.ctl);
+    }
+    hipLaunchKernelGGL(k_pre_select, dim3((unsigned)(p.n_tiles + 3) / 4), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(k_pre_rows, dim3((unsigned)p.n_tiles), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(k_pre_fill, dim3((unsigned)p.n_tiles + 1), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_prep_fill(const Prep& p, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_pre_fill, dim3((unsigned)p.n_tiles), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* csr, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_pre_windows, dim3((unsigned)(p.n_tiles + 3) / 4), dim3(256), 0, s, p, mfma, csr, small, mid, big);
+    return hipGetLastError();
 }
 
 // Which matrix-path windows keep the previous plan's condensed structure: on that path before and now, and not
@@ -614,47 +978,6 @@ hipError_t launch_carry_copy(int32_t W, int32_t n_rows, const uint8_t* carried, 
     if (W <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_carry_copy, dim3(W), dim3(256), 0, s, n_rows, carried, old_wptr, wptr, old_wcols, wcols, old_start,
                        rowptr, old_erc, erc);
-    return hipGetLastError();
-}
-
-hipError_t launch_touched_classes(int32_t n_touched, const int32_t* touched, int32_t n_rows, int32_t n_cols,
-                                  const int32_t* rowptr, const int32_t* colind, int32_t* t_small, int32_t* t_mid,
-                                  int32_t* t_huge, int32_t* counts, int32_t* err, hipStream_t s)
-{
-    if (n_touched <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_touched_classes, dim3(n_touched), dim3(256), 0, s, n_touched, touched, n_rows, n_cols, rowptr, colind,
-                       t_small, t_mid, t_huge, counts, err);
-    return hipGetLastError();
-}
-
-hipError_t launch_count_small_list(int32_t n_list, const int32_t* list, int32_t n_rows, const int32_t* rowptr,
-                                   const int32_t* colind, int32_t* ncols, hipStream_t s)
-{
-    if (n_list <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count_small_list, dim3(n_list), dim3(256), 0, s, list, n_rows, rowptr, colind, ncols);
-    return hipGetLastError();
-}
-
-hipError_t launch_validate_rowptr(int32_t n_rows, int64_t nnz, const int32_t* rowptr, int32_t* err_flag, hipStream_t s)
-{
-    const unsigned g = (unsigned)(((int64_t)n_rows + 1 + 255) / 256);
-    hipLaunchKernelGGL(k_validate_rowptr, dim3(g), dim3(256), 0, s, n_rows, nnz, rowptr, err_flag);
-    return hipGetLastError();
-}
-
-hipError_t launch_count_small(int32_t W, int32_t n_rows, const int32_t* rowptr, const int32_t* colind, int32_t* ncols,
-                              hipStream_t s)
-{
-    if (W <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count_small, dim3(W), dim3(256), 0, s, W, n_rows, rowptr, colind, ncols);
-    return hipGetLastError();
-}
-
-hipError_t launch_count_mid(int32_t n_mid, const int32_t* mid_list, int32_t n_rows, const int32_t* rowptr,
-                            const int32_t* colind, int32_t* ncols, hipStream_t s)
-{
-    if (n_mid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count_mid, dim3(n_mid), dim3(1024), 0, s, mid_list, n_rows, rowptr, colind, ncols);
     return hipGetLastError();
 }
 
@@ -940,75 +1263,6 @@ hipError_t launch_run_union(int32_t n_runs, const int32_t* win_list, int32_t n_l
 }
 
 // ------------------------------------------------------------------------------------------------
-// selection (Section IV-C): z' = c0*H*ncols^2 + c1*(H*ncols - nnzw) + c2*H*ncols ; matrix path iff z' < 0
-// ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_select(int32_t W, const int32_t* __restrict__ ncols,
-                                                const int32_t* __restrict__ nnzw, long long c0, long long c1,
-                                                long long c2, int32_t mode, uint8_t* __restrict__ route,
-                                                int32_t* __restrict__ f_mfma, int32_t* __restrict__ f_csr,
-                                                int32_t* __restrict__ f_small, int32_t* __restrict__ f_mid,
-                                                int32_t* __restrict__ f_big, int32_t* __restrict__ nnz_if_mfma)
-{
-    int32_t w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= W) return;
-    const long long nc = ncols[w], nz = nnzw[w];
-    int r = 0;
-    if (nc > 0) {
-        if (mode == HCSPMM_ROUTE_ALL_MFMA) r = 1;
-        else if (mode == HCSPMM_ROUTE_HYBRID || mode == HCSPMM_ROUTE_PER_WINDOW) {
-            // |c*| < 2^40 and H*ncols^2 < 2^58: 128-bit integers keep the sign exact
-            const __int128 hn = (__int128)kH * nc;
-            const __int128 z = (__int128)c0 * hn * nc + (__int128)c1 * (hn - nz) + (__int128)c2 * hn;
-            r = z < 0 ? 1 : 0;
-        }
-    }
-    route[w] = (uint8_t)r;
-    f_mfma[w] = r;
-    f_csr[w] = 1 - r;
-    f_small[w] = (r && nc <= kMfmaSmallMaxCols) ? 1 : 0;
-    f_mid[w] = (r && nc > kMfmaSmallMaxCols && nc <= kMfmaMidMaxCols) ? 1 : 0;
-    f_big[w] = (r && nc > kMfmaMidMaxCols) ? 1 : 0;
-    nnz_if_mfma[w] = r ? (int32_t)nz : 0;
-}
-
-hipError_t launch_select(int32_t W, const int32_t* ncols, const int32_t* nnzw, int64_t c0, int64_t c1, int64_t c2,
-                         int32_t mode, uint8_t* route, int32_t* f_mfma, int32_t* f_csr, int32_t* f_small,
-                         int32_t* f_mid, int32_t* f_big, int32_t* nnz_if_mfma, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_select, dim3((W + 255) / 256), dim3(256), 0, s, W, ncols, nnzw, (long long)c0, (long long)c1,
-                       (long long)c2, mode, route, f_mfma, f_csr, f_small, f_mid, f_big, nnz_if_mfma);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_compact_ids(int32_t n, const int32_t* __restrict__ flags,
-                                                     const int64_t* __restrict__ pos, int32_t* __restrict__ out)
-{
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && flags[i]) out[pos[i]] = i;
-}
-
-__global__ __launch_bounds__(256) void k_masked_copy(int32_t n, const int32_t* __restrict__ flags,
-                                                     const int32_t* __restrict__ src, int32_t* __restrict__ dst)
-{
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = flags[i] ? src[i] : 0;
-}
-
-hipError_t launch_masked_copy(int32_t n, const int32_t* flags, const int32_t* src, int32_t* dst, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_masked_copy, dim3((n + 255) / 256), dim3(256), 0, s, n, flags, src, dst);
-    return hipGetLastError();
-}
-
-hipError_t launch_compact_ids(int32_t n, const int32_t* flags, const int64_t* pos, int32_t* out, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_compact_ids, dim3((n + 255) / 256), dim3(256), 0, s, n, flags, pos, out);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------
 // matrix-path launch table: one descriptor per wave-per-window item
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_build_desc(int32_t n_list, const int32_t* __restrict__ win_list,
@@ -1123,102 +1377,6 @@ hipError_t launch_slice_fill(int32_t n_list, const int32_t* win_list, const int3
     if (n_list <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_slice_fill, dim3((n_list + 255) / 256), dim3(256), 0, s, n_list, win_list, ncols, slice_cols,
                        slice_pos, multi_pos, slot_pos, slices, multi);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------------
-// scalar-path launch tables: short rows, and segments of long rows
-// ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_row_class(int32_t n_rows, const int32_t* __restrict__ rowptr,
-                                                   const uint8_t* __restrict__ route, int32_t mid_row,
-                                                   int32_t long_row, int32_t* __restrict__ f_short,
-                                                   int32_t* __restrict__ f_mid, int32_t* __restrict__ n_seg, int32_t* __restrict__ f_multi,
-                                                   int32_t* __restrict__ n_slot, int32_t* __restrict__ len_long)
-{
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_rows) return;
-    const int32_t len = rowptr[i + 1] - rowptr[i];
-    const bool csr = route[i / kH] == 0;
-    const bool is_long = csr && len > long_row;
-    const bool is_mid = csr && !is_long && len > mid_row;
-    const int32_t ns = is_long ? (len + kSegLen - 1) / kSegLen : 0;
-    f_short[i] = (csr && !is_long && !is_mid) ? 1 : 0;
-    f_mid[i] = is_mid ? 1 : 0;
-    n_seg[i] = ns;
-    f_multi[i] = ns > 1 ? 1 : 0;
-    n_slot[i] = ns > 1 ? ns : 0;
-    len_long[i] = (is_long || is_mid) ? len : 0;
-}
-
-hipError_t launch_row_class(int32_t n_rows, const int32_t* rowptr, const uint8_t* route, int32_t mid_row,
-                            int32_t long_row, int32_t* f_short,
-                            int32_t* f_mid, int32_t* n_seg, int32_t* f_multi, int32_t* n_slot, int32_t* len_long,
-                            hipStream_t s)
-{
-    if (n_rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_row_class, dim3((n_rows + 255) / 256), dim3(256), 0, s, n_rows, rowptr, route, mid_row, long_row,
-                       f_short, f_mid,
-                       n_seg, f_multi, n_slot, len_long);
-    return hipGetLastError();
-}
-
-// rows whose aggregated values reach memory even when the update stage is fused into the SpMM
-// kernels: scalar-path rows above the short tier and all rows of matrix-path windows too wide for
-// the wave-per-window kernel
-__global__ __launch_bounds__(256) void k_rest_flag(int32_t n_rows, const int32_t* __restrict__ rowptr,
-                                                   const uint8_t* __restrict__ route, const int32_t* __restrict__ ncols,
-                                                   int32_t mid_row, int32_t* __restrict__ flag)
-{
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_rows) return;
-    const int32_t w = i / kH;
-    flag[i] = route[w] ? (ncols[w] > kMfmaSmallMaxCols ? 1 : 0) : (rowptr[i + 1] - rowptr[i] > mid_row ? 1 : 0);
-}
-
-hipError_t launch_rest_flag(int32_t n_rows, const int32_t* rowptr, const uint8_t* route, const int32_t* ncols,
-                            int32_t mid_row, int32_t* flag, hipStream_t s)
-{
-    if (n_rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rest_flag, dim3((n_rows + 255) / 256), dim3(256), 0, s, n_rows, rowptr, route, ncols, mid_row, flag);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_build_segments(int32_t n_rows, const int32_t* __restrict__ rowptr,
-                                                        const int32_t* __restrict__ n_seg,
-                                                        const int64_t* __restrict__ seg_pos,
-                                                        const int64_t* __restrict__ multi_pos,
-                                                        const int64_t* __restrict__ slot_pos,
-                                                        Segment* __restrict__ segs, MultiRow* __restrict__ multi)
-{
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_rows) return;
-    const int32_t ns = n_seg[i];
-    if (ns == 0) return;
-    const int32_t s = rowptr[i], e = rowptr[i + 1];
-    const int64_t sp = seg_pos[i];
-    const int32_t slot0 = ns > 1 ? (int32_t)slot_pos[i] : -1;
-    for (int32_t q = 0; q < ns; ++q) {
-        Segment sg;
-        sg.row = i;
-        sg.k_begin = s + q * kSegLen;
-        sg.k_end = min(e, sg.k_begin + kSegLen);
-        sg.slot = ns > 1 ? slot0 + q : -1;
-        segs[sp + q] = sg;
-    }
-    if (ns > 1) {
-        MultiRow m;
-        m.row = i; m.first_slot = slot0; m.n_slots = ns; m.pad = 0;
-        multi[multi_pos[i]] = m;
-    }
-}
-
-hipError_t launch_build_segments(int32_t n_rows, const int32_t* rowptr, const int32_t* n_seg, const int64_t* seg_pos,
-                                 const int64_t* multi_pos, const int64_t* slot_pos, Segment* segs, MultiRow* multi,
-                                 hipStream_t s)
-{
-    if (n_rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_build_segments, dim3((n_rows + 255) / 256), dim3(256), 0, s, n_rows, rowptr, n_seg, seg_pos,
-                       multi_pos, slot_pos, segs, multi);
     return hipGetLastError();
 }
 

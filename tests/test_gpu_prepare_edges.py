@@ -1,0 +1,93 @@
+"""Preparation at the edges of its size classes and tiles, against the CPU re-derivation, and the row tables through the product."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import assert_close, device_graph
+from test_gpu_plan import KEYS, check_plan
+from workloads import CSRGraph
+
+pytestmark = pytest.mark.gpu
+
+
+def ragged(lengths, n_cols, seed):
+    rng = np.random.default_rng(seed)
+    lengths = np.asarray(lengths, np.int64)
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    col = rng.integers(0, n_cols, int(lengths.sum()))
+    rows = np.repeat(np.arange(lengths.shape[0]), lengths)
+    col = col[np.lexsort((col, rows))].astype(np.int32)           # ascending inside a row; duplicates stay
+    return CSRGraph(lengths.shape[0], n_cols, rowptr, col, rng.standard_normal(col.shape[0]).astype(np.float32))
+
+
+@pytest.mark.parametrize("per_window", [1023, 1024, 1025, 4095, 4096, 4097, 16384, 16385])
+@pytest.mark.parametrize("mode", [0, 2])
+def test_windows_around_the_counting_classes(per_window, mode):
+    lengths = np.zeros(16 * 5, np.int64)
+    for w in (0, 2, 4):
+        lengths[16 * w: 16 * w + 15] = per_window // 15
+        lengths[16 * w + 15] = per_window - 15 * (per_window // 15)
+    check_plan(ragged(lengths, 20_000, per_window), mode, sel_coef=[1, 300, -200])
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 1023, 1024, 1025, 4 * 1024, 4 * 1024 + 1, 70_001])
+@pytest.mark.parametrize("mode", [0, 1, 3])
+def test_tiles_of_rows_and_their_tables(n, mode):
+    rng = np.random.default_rng(n)
+    lengths = rng.integers(0, 6, n)
+    heavy = rng.choice(n, min(n, 40), replace=False)
+    lengths[heavy] = rng.choice([60, 64, 65, 128, 129, 256, 257, 1024, 1025, 2048, 2049, 5000], heavy.shape[0])
+    g = ragged(lengths, 3000, n)
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    check_plan(g, mode, sel_coef=[1, 300, -280])
+    X = rng.standard_normal((g.n_cols, 32)).astype(np.float32)
+    W = rng.standard_normal((32, 16)).astype(np.float32)
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *device_graph(g), route_mode=mode, sel_coef=[1, 300, -280])
+    Xd, Wd = torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda()
+    Y = torch.full((n, 32), float("nan"), device="cuda")
+    hc.hcspmm_spmm(plan, Xd, Y)
+    ref, bound = (oracle.spmm(g.rowptr, g.colind, g.vals, X, use_abs=b) for b in (False, True))
+    assert_close(Y.cpu().numpy().astype(np.float64), ref, bound, 1e-5, "spmm")
+    # the fused layer walks the rest_rows table as well
+    hc.hcspmm_plan_set_update_fusion(plan, hc.HCSPMM_UPDATE_FUSED)
+    ws = torch.empty(max(256, hc.hcspmm_aggregate_update_workspace_bytes(plan, 32, 16)), dtype=torch.uint8, device="cuda")
+    Z = torch.full((n, 16), float("nan"), device="cuda")
+    hc.hcspmm_aggregate_update(plan, Xd, Wd, Z, ws)
+    ref, bound = (oracle.aggregate_update(g.rowptr, g.colind, g.vals, X, W, use_abs=b) for b in (False, True))
+    assert_close(Z.cpu().numpy().astype(np.float64), ref, bound, 1e-5, "aggregate-update")
+
+
+@pytest.mark.parametrize("where", ["first", "middle", "last"])
+@pytest.mark.parametrize("bad", [-1, 300])
+def test_bad_columns_are_found_in_every_size_class(where, bad):
+    import paper_2412_08902_amd.binding as hc
+    for per_row in (3, 100, 500, 1100):                           # windows of 48, 1600, 8000 and 17600 non-zeros
+        g = ragged(np.full(48, per_row), 300, per_row)
+        col = g.colind.copy()
+        col[{"first": 0, "middle": col.shape[0] // 2, "last": -1}[where]] = bad
+        for mode in (0, 1):
+            with pytest.raises(hc.HcspmmError) as e:
+                hc.hcspmm_prepare(g.n_rows, g.n_cols, *device_graph(CSRGraph(48, 300, g.rowptr, col, g.vals)), route_mode=mode)
+            assert e.value.status == hc.HCSPMM_EBADCSR
+
+
+def test_update_of_more_windows_than_the_pinned_list_holds():
+    """16,000 changed rows, each in a window of its own, of 2.1 M rows: equal to a preparation from scratch."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    n = 2_100_000
+    rng = np.random.default_rng(5)
+    rowptr = np.arange(n + 1, dtype=np.int32)
+    col = rng.integers(0, 1000, n).astype(np.int32)
+    rows = (np.arange(16_000) * 128 + 5).astype(np.int32)
+    col2 = col.copy()
+    col2[rows] += 1
+    va = torch.ones(n, device="cuda")
+    rp, c1, c2 = (torch.from_numpy(x).cuda() for x in (rowptr, col, col2))
+    plan = hc.hcspmm_prepare(n, 1002, rp, c1, va)
+    hc.hcspmm_plan_update(plan, rp, c2, va, rows)
+    fresh = hc.hcspmm_prepare(n, 1002, rp, c2, va)
+    a, b = hc.hcspmm_plan_export(plan), hc.hcspmm_plan_export(fresh)
+    for k in KEYS:
+        assert np.array_equal(a[k], b[k]), k
