@@ -88,6 +88,7 @@ hipError_t exclusive_scan_multi(const ScanMulti& m, int64_t n, int64_t* totals_d
 struct PrepTotals {
     int64_t total_ncols, nnz_mfma, wide_cols /* columns of wide matrix-path windows */, nnz_long, n_slots;
     int32_t n_mfma, n_mfma_small, n_mfma_mid, n_mfma_big, n_short, n_mid, n_rest, n_multi, n_segs;
+    int32_t unsorted;                     // some row's columns do not ascend (when asked for)
     int32_t n_big_list, n_huge_list;      // windows above kUniqueSmallCap / kCountMidCap non-zeros
     int32_t err;                          // 1 rowptr[0], 2 rowptr[n_rows], 4 decreasing rowptr, 8 column out of range
 };
@@ -101,6 +102,8 @@ struct Prep {
     const int32_t* touched;               // windows to count (null: all)
     const int32_t* old_ncols;             // counts carried over for the others
     int32_t features;                     // distinct columns are wanted
+    int32_t check_sorted;                 // also find out whether every row's columns ascend (ctl[6] otherwise)
+    int32_t scalar_exec;                  // row tables for a plan that runs every window on the scalar path, if the rows ascend
     int32_t big_takes_1k;                 // set by launch_prep
     int32_t mode;
     long long c0, c1, c2;
@@ -114,11 +117,26 @@ struct Prep {
     MultiRow* multi;
     PrepTotals* out;                      // host or device memory (null: skip)
 };
+// Column panels of the scalar path (see run_spmm): where every row enters each panel, and each panel's row tables.
+constexpr int kMaxPanels = 16, kPanelRowBytes = 128;            // panels for X rows of at least that many bytes
+struct PanelTotals { int64_t nnz, n_slots; int32_t n_mid, n_segs, n_multi, pad; };
+struct PanelArgs {
+    int32_t n_rows, n_cols, n_panels, n_tiles, mid_row, long_row;
+    const int32_t *rowptr, *colind;
+    int32_t* split;                       // n_panels - 1 arrays of n_rows: first non-zero at or beyond the panel's end
+    unsigned long long* sums;             // n_panels * n_tiles * 3
+    int64_t cap_mid, cap_segs, cap_multi; // entries per panel of
+    int32_t* mid_rows;
+    Segment* segs;
+    MultiRow* multi;
+    PanelTotals* out;                     // n_panels
+};
+hipError_t launch_panels(const PanelArgs& p, hipStream_t s);
 size_t prep_tile_count(int32_t W);
 size_t prep_tile_words(int32_t W);        // 64-bit words of wt and rt together (rt follows wt's prep_tile_count() * 8)
 hipError_t launch_prep(const Prep& p, int32_t n_touched, hipStream_t s);
 hipError_t launch_prep_fill(const Prep& p, hipStream_t s);      // another pass over the row tables
-hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* csr, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s);
+hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s);
 
 // ---- preprocessing launchers (prepare_kernels.hip) ---------------------------------------------
 hipError_t launch_window_nnz(int32_t W, int32_t n_rows, const int32_t* rowptr, int32_t* nnzw, int32_t* big_list,
@@ -157,6 +175,7 @@ struct SpmmArgs {
     int32_t n_rows;
     int32_t n_cols;       // rows of X
     const int32_t* rowptr;
+    const int32_t* rowend;    // scalar path: row i is [rowptr[i], rowend[i]) -- rowptr + 1, or a column panel's share of the row
     const int32_t* colind;
     const float* vals;
     const void* X;
@@ -167,6 +186,8 @@ struct SpmmArgs {
     int64_t ldy;
     int32_t relu;
     int32_t y_dtype;
+    const float* acc;     // scalar path: fp32 rows (pitch ldacc) added to the result before the activation and the store; may be Y
+    int64_t ldacc;
 };
 
 // Update stage of the aggregate-then-update layer: Y = act(Z W) for aggregated rows Z (Section V-A).
@@ -313,7 +334,6 @@ struct hcspmm_plan {
     int32_t* wcols;
     int32_t* erc;            // per non-zero: (ecol << 4) | row-in-window
     int32_t* mfma_windows;
-    int32_t* csr_windows;
     int64_t total_ncols;
     int32_t n_mfma, n_csr;
     int64_t nnz_mfma;
@@ -364,6 +384,13 @@ struct hcspmm_plan {
     int32_t n_chunks;
     struct BlockCache* cache;       // device blocks kept between hcspmm_plan_update calls (null until the first one)
     int32_t features_complete;    // ncols / wptr / total_ncols are filled (a scalar-only plan computes them on first request)
+    // column panels (n_panels > 1): the scalar path takes the columns panel by panel; scalar_exec: windows that the selector
+    // sends to the matrix path run on the scalar path as well, and their condensed structure is built on export only
+    int32_t n_panels, scalar_exec;
+    int32_t* panel_split;
+    struct { hcspmm::PanelTotals t; int32_t* mid_rows; hcspmm::Segment* segs; hcspmm::MultiRow* multi; } panel[hcspmm::kMaxPanels];
+    float* acc_rows;                // lazily sized: n_rows x d sums between panels when the output is not fp32
+    int64_t acc_rows_elems;
     int32_t n_rest;                 // rows finished through the workspace by the fused update
     int32_t* rest_rows;
     int64_t nnz_long;

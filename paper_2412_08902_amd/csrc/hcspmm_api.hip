@@ -257,7 +257,7 @@ static void free_plan_arrays(hcspmm_plan* p)
         else (void)hipFree(p->chunks[i]);
     }
     p->n_chunks = 0;
-    void* owned[] = {p->erc_own ? p->erc : nullptr, p->wcols_own ? p->wcols : nullptr, p->tile_partial, p->partial};
+    void* owned[] = {p->erc_own ? p->erc : nullptr, p->wcols_own ? p->wcols : nullptr, p->tile_partial, p->partial, p->acc_rows};
     for (void* q : owned)
         if (q) (void)hipFree(q);
 }
@@ -308,8 +308,8 @@ static hcspmm_status complete_condensed(hcspmm_plan* p, bool features_only)
             }
             p->wcols_own = 1;
         }
-        if (W > 0)
-            HC_TRY(launch_ecol(W, p->n_rows, p->rowptr, p->colind, tmp_cols, p->ncols, p->wptr, p->wcols, p->erc, cnt, p->route, 0,
+        for (int want = 0; want <= (p->scalar_exec ? 1 : 0) && W > 0; ++want)
+            HC_TRY(launch_ecol(W, p->n_rows, p->rowptr, p->colind, tmp_cols, p->ncols, p->wptr, p->wcols, p->erc, cnt, p->route, want,
                                0x7fffffff, nullptr));
         HC_TRY(hipDeviceSynchronize());
         p->condensed_complete = 1;
@@ -395,6 +395,28 @@ struct PlanCarry {
     const int32_t* old_wcols = nullptr; const int32_t* old_erc = nullptr;
 };
 
+// Column panels.  On a matrix with many non-zeros per row whose X is far larger than an L2, a row's gathers run over all of
+// X and most of them miss (232,965 rows of 492 non-zeros, 128 columns fp32: 36 GB behind L2, at the 6.6 TB/s that this path
+// gives: 5.45 ms; the matrix path, which fetches a column once per window, 5.24 ms).  Taking the columns in panels whose
+// 128-byte slices about fit an XCD's L2 (3.5 MiB) makes almost every gather a hit, for one more read and write of Y per
+// panel and the rows' chains once per panel: 3.5 ms with 9 panels.  A panel should keep some twenty non-zeros of a row, and
+// panels much larger than an L2 bring little: 100,000 rows of 300: 1144 -> 878 us with 4 panels, 500,000 of 60 (64 MB of
+// slices): 1752 -> 1614 us with 3, more of them lose; below a sixth of the panels that L2 asks for it is left alone.
+// The rows have to ascend in their columns, and every window then runs on the scalar path (with panels it is ahead of the
+// matrix path on such matrices), unless the caller chose the routing, the coefficients or the matrix kernels.
+static int panel_count(const hcspmm_plan* p)
+{
+    const hcspmm_options& o = p->opt;
+    if ((o.route_mode != HCSPMM_ROUTE_HYBRID && o.route_mode != HCSPMM_ROUTE_ALL_CSR) || o.use_custom_selector ||
+        o.matrix_kernels != HCSPMM_MATRIX_AUTO || p->n_rows == 0)
+        return 0;
+    const int64_t row_bytes = o.d_hint > 0 ? (int64_t)o.d_hint * (o.mfma_dtype == HCSPMM_F32 ? 4 : 2) : 128;
+    if (row_bytes < kPanelRowBytes) return 0;
+    const double want = (double)p->n_cols * 128.0 / (3.5 * (1 << 20)), most = (double)p->nnz / p->n_rows / 20.0;
+    int n = (int)std::min({want + 0.5, most, (double)kMaxPanels});
+    return n >= 2 && 6.0 * n >= want ? n : 0;
+}
+
 static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCarry* carry = nullptr)
 {
     hcspmm_status st = HCSPMM_OK;
@@ -421,6 +443,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     const int64_t most_mid = std::min<int64_t>(n_rows, nnz / (p->mid_row + 1)), most_multi = nnz / (kSegLen + 1),
                   most_segs = nnz / (p->long_row + 1) + nnz / kSegLen,
                   most_rest = std::min<int64_t>(n_rows, nnz / (p->fused_mid_row + 1) + wide_rows);
+    const int n_panels = panel_count(p);
     Prep pr{};
 
     {
@@ -476,6 +499,8 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         pr.n_count_mid = err + 4; pr.n_count_huge = err + 5;
     }
     pr.features = p->features_complete;
+    pr.check_sorted = n_panels > 1;
+    pr.scalar_exec = n_panels > 1;
     pr.mode = p->opt.route_mode;
     pr.c0 = p->coef[0]; pr.c1 = p->coef[1]; pr.c2 = p->coef[2];
     pr.mid_row = p->mid_row; pr.long_row = p->long_row; pr.fused_mid_row = p->fused_mid_row;
@@ -519,6 +544,31 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     // windows; scalar-path windows never read theirs at SpMM time and get it on export only, and a
     // plan without matrix-path windows does not even allocate the arrays
     p->condensed_complete = nnz == 0 ? 1 : 0;
+    p->n_panels = n_panels > 1 && !tot.unsorted ? n_panels : 0;
+    p->scalar_exec = p->n_panels > 1 ? 1 : 0;
+    if (p->n_panels > 1) {
+        PanelArgs pa{};
+        pa.n_rows = n_rows; pa.n_cols = p->n_cols; pa.n_panels = n_panels; pa.n_tiles = pr.n_tiles;
+        pa.mid_row = p->mid_row; pa.long_row = p->long_row; pa.rowptr = p->rowptr; pa.colind = p->colind;
+        pa.cap_mid = most_mid; pa.cap_segs = most_segs; pa.cap_multi = most_multi;
+        HC_ALLOC(keep, p->panel_split, (size_t)(n_panels - 1) * n_rows);
+        HC_ALLOC(keep, pa.mid_rows, (size_t)n_panels * most_mid);
+        HC_ALLOC(keep, pa.segs, (size_t)n_panels * most_segs);
+        HC_ALLOC(keep, pa.multi, (size_t)n_panels * most_multi);
+        HC_ALLOC(tmp, pa.sums, (size_t)n_panels * pa.n_tiles * 3);
+        HC_ALLOC(tmp, pa.out, n_panels);
+        pa.split = p->panel_split;
+        HC_TRY(launch_panels(pa, stream));
+        PanelTotals pt[kMaxPanels];
+        HC_TRY(rb.add(pt, pa.out, (size_t)n_panels * sizeof(PanelTotals), stream));
+        HC_TRY(rb.sync(stream));
+        for (int q = 0; q < n_panels; ++q) {
+            p->panel[q].t = pt[q];
+            p->panel[q].mid_rows = pa.mid_rows + q * pa.cap_mid;
+            p->panel[q].segs = pa.segs + q * pa.cap_segs;
+            p->panel[q].multi = pa.multi + q * pa.cap_multi;
+        }
+    }
     // Walking every row and skipping the ones another kernel owns is cheaper than an index list
     // while most rows are short scalar-path rows; otherwise keep the explicit list.
     p->short_rows = nullptr;
@@ -529,13 +579,12 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         fill.short_rows = p->short_rows;
         HC_TRY(launch_prep_fill(fill, stream));
     }
-    if (p->n_mfma > 0) {
+    if (p->n_mfma > 0 && !p->scalar_exec) {
         HC_ALLOC(keep, p->mfma_windows, p->n_mfma);
-        HC_ALLOC(keep, p->csr_windows, p->n_csr);
         HC_ALLOC(keep, p->mfma_small, p->n_mfma_small);
         HC_ALLOC(keep, p->mfma_mid, p->n_mfma_mid);
         HC_ALLOC(keep, p->mfma_big, p->n_mfma_big);
-        HC_TRY(launch_prep_windows(pr, p->mfma_windows, p->csr_windows, p->mfma_small, p->mfma_mid, p->mfma_big, stream));
+        HC_TRY(launch_prep_windows(pr, p->mfma_windows, p->mfma_small, p->mfma_mid, p->mfma_big, stream));
         HC_ALLOC(keep, p->erc, nnz);
         HC_ALLOC(keep, p->wcols, p->total_ncols);
         HC_ALLOC(tmp, tmp_cols, nnz);
@@ -646,7 +695,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         p->runs_ok = 1;
     }
     // workgroup slices: one per medium window, slice_cols condensed columns each for wide windows
-    if (p->n_mfma > 0) {
+    if (p->n_mfma > 0 && !p->scalar_exec) {
         ScanMulti m{};
         m.k = 3;
         m.in[0] = sc_n;     m.out[0] = pos_a;
@@ -734,7 +783,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
                                      stream));
         }
     }
-    if (p->n_mfma_small > 0) {
+    if (p->n_mfma_small > 0 && !p->scalar_exec) {
         HC_ALLOC(keep, p->mfma_small_desc, p->n_mfma_small);
         HC_TRY(launch_build_desc(p->n_mfma_small, p->mfma_small, n_rows, p->rowptr, p->ncols, p->wptr, p->mfma_small_desc,
                                  stream));
@@ -761,11 +810,19 @@ fail:
 // partial tiles a call may need: the slices of wide windows, or of wide runs when the run kernel serves the matrix path
 static int64_t tile_slots(const hcspmm_plan* p) { return p->n_tile_slots > p->n_run_tile_slots ? p->n_tile_slots : p->n_run_tile_slots; }
 
+// partial rows a call may need: long rows cut into segments, or the panels' (one panel runs at a time)
+static int64_t row_slots(const hcspmm_plan* p)
+{
+    int64_t n = p->n_slots;
+    for (int q = 0; q < p->n_panels; ++q) n = std::max(n, p->panel[q].t.n_slots);
+    return n;
+}
+
 // Scratch of one SpMM call: partial rows of long rows cut into several segments, then partial tiles of
 // wide windows cut into several slices (each part padded to 256 bytes).
 static size_t spmm_scratch_bytes(const hcspmm_plan* p, int32_t d, size_t* tile_off)
 {
-    const size_t part = ((size_t)p->n_slots * (size_t)d * sizeof(float) + 255) & ~(size_t)255;
+    const size_t part = ((size_t)row_slots(p) * (size_t)d * sizeof(float) + 255) & ~(size_t)255;
     const size_t tiles = ((size_t)tile_slots(p) * kH * (size_t)d * sizeof(float) + 255) & ~(size_t)255;
     if (tile_off) *tile_off = part;
     return part + tiles;
@@ -774,7 +831,8 @@ static size_t spmm_scratch_bytes(const hcspmm_plan* p, int32_t d, size_t* tile_o
 static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStream_t stream,
                               hipEvent_t* ev = nullptr /* 5 events when timing stages */,
                               const UpdateArgs* upd = nullptr /* fuse the update stage where a tile stays on chip */,
-                              char* scratch_mem = nullptr /* device, spmm_scratch_bytes(): used instead of the plan's own lazily sized buffers */)
+                              char* scratch_mem = nullptr /* device, spmm_scratch_bytes(): used instead of the plan's own lazily sized buffers */,
+                              bool acc_rows = false /* column panels may keep fp32 sums of a 16-bit output in a buffer of the plan */)
 {
     hcspmm_plan* p = const_cast<hcspmm_plan*>(plan);
     float* partial = p->partial;
@@ -786,9 +844,10 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         tile_partial = reinterpret_cast<float*>(scratch_mem + tile_off);
     }
     // long rows cut into several segments need one partial row per segment
-    if (!scratch_mem && p->n_slots > 0 && p->partial_elems < p->n_slots * (int64_t)a.d) {
+    const int64_t n_row_slots = row_slots(p);
+    if (!scratch_mem && n_row_slots > 0 && p->partial_elems < n_row_slots * (int64_t)a.d) {
         if (p->partial) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->partial); p->partial = nullptr; }
-        const int64_t want = p->n_slots * (int64_t)a.d;
+        const int64_t want = n_row_slots * (int64_t)a.d;
         if (hipMalloc((void**)&p->partial, (size_t)want * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             p->partial = nullptr;
@@ -812,9 +871,46 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         p->tile_partial_elems = want;
         tile_partial = p->tile_partial;
     }
+    // Column panels: the same kernel once per panel, each adding to what the previous ones left (in Y itself when it is fp32).
+    // hcspmm_spmm_noalloc has no room for the fp32 sums of a 16-bit output and hcspmm_spmm gives the same bits, so both
+    // take the columns of such a call in one go.
+    const int64_t row_bytes = (int64_t)a.d * (a.x_dtype == HCSPMM_F32 ? 4 : 2);
+    if (p->n_panels > 1 && !upd && row_bytes >= kPanelRowBytes && (a.y_dtype == HCSPMM_F32 || acc_rows)) {
+        float* sums = a.Y;
+        int64_t ld_sums = a.ldy;
+        if (a.y_dtype != HCSPMM_F32) {
+            const int64_t want = (int64_t)p->n_rows * a.d;
+            if (p->acc_rows_elems < want) {
+                if (p->acc_rows) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->acc_rows); p->acc_rows = nullptr; p->acc_rows_elems = 0; }
+                if (hipMalloc((void**)&p->acc_rows, (size_t)want * sizeof(float)) != hipSuccess) {
+                    (void)hipGetLastError();
+                    p->acc_rows = nullptr;
+                    set_error("allocation of %lld floats for row sums between column panels failed", (long long)want);
+                    return HCSPMM_EALLOC;
+                }
+                p->acc_rows_elems = want;
+            }
+            sums = p->acc_rows;
+            ld_sums = a.d;
+        }
+        if (ev) for (int i = 0; i < 3; ++i) HC_HIP(hipEventRecord(ev[i], stream));
+        for (int q = 0; q < p->n_panels; ++q) {
+            const PanelTotals& t = p->panel[q].t;
+            SpmmArgs b = a;
+            const bool final_panel = q == p->n_panels - 1;
+            if (q > 0) { b.rowptr = p->panel_split + (int64_t)(q - 1) * p->n_rows; b.acc = sums; b.ldacc = ld_sums; }
+            if (!final_panel) { b.rowend = p->panel_split + (int64_t)q * p->n_rows; b.Y = sums; b.ldy = ld_sums; b.y_dtype = HCSPMM_F32; b.relu = 0; }
+            const CsrHints hints{t.nnz, p->n_rows, true};
+            HC_HIP(launch_csr(b, t.n_segs, p->panel[q].segs, partial, t.n_mid, p->panel[q].mid_rows, p->n_rows, nullptr, nullptr, p->mid_row,
+                              hints, stream));
+            HC_HIP(launch_reduce_partials(b, t.n_multi, p->panel[q].multi, partial, stream));
+        }
+        if (ev) { HC_HIP(hipEventRecord(ev[3], stream)); HC_HIP(hipEventRecord(ev[4], stream)); }
+        return HCSPMM_OK;
+    }
     const bool use_runs = p->runs_ok && !upd && mfma_run_shape_supported(a);
-    const bool has_wg = use_runs ? p->n_run_slices > 0 : (p->n_big_slices > 0 || p->n_mfma_mid > 0);
-    const bool has_small = !use_runs && p->n_mfma_small > 0;
+    const bool has_wg = use_runs ? p->n_run_slices > 0 : !p->scalar_exec && (p->n_big_slices > 0 || p->n_mfma_mid > 0);
+    const bool has_small = !use_runs && !p->scalar_exec && p->n_mfma_small > 0;
     const bool has_csr = p->n_segs > 0 || p->n_mid > 0 || p->n_short > 0;
     // The paths own disjoint rows of Y.  When more than one has work (and the stages are not being
     // timed one by one) they run side by side: the matrix-path kernels on the plan's two side
@@ -832,6 +928,8 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         HC_HIP(launch_mfma_run(a, p->n_run_slices, p->run_slices, p->run_wins, p->ucols, p->wslot, p->erc, tile_partial, s_wg));
         HC_HIP(launch_reduce_tiles(a, p->n_run_multi, p->run_multi, tile_partial, s_wg));
         if (ev) { HC_HIP(hipEventRecord(ev[1], stream)); HC_HIP(hipEventRecord(ev[2], stream)); }
+    } else if (p->scalar_exec) {
+        if (ev) { HC_HIP(hipEventRecord(ev[1], stream)); HC_HIP(hipEventRecord(ev[2], stream)); }
     } else {
         HC_HIP(launch_mfma_wg(a, p->n_big_slices, p->big_slices, p->ncols, p->wptr, p->wcols, p->erc, p->rows_sorted,
                               p->big_slice_rows, tile_partial, tune().bands <= 0 || getenv("HCSPMM_TUNE_BANDS_WIDE"), s_wg));
@@ -845,13 +943,15 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
     // (the windows' distinct columns against their non-zeros say how much neighbouring rows share; a scalar-only plan does
     // not count them)
     const bool scattered = p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * p->total_ncols > 6 * p->nnz;
-    const CsrHints hints{p->nnz - p->nnz_mfma, (int64_t)p->n_csr * kH, scattered};
+    const int64_t nnz_matrix = p->scalar_exec ? 0 : p->nnz_mfma, n_scalar = p->scalar_exec ? p->W : p->n_csr;
+    const CsrHints hints{p->nnz - nnz_matrix, n_scalar * kH, scattered};
+    const uint8_t* route = p->scalar_exec ? nullptr : p->route;
     if (upd)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
-        HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, p->n_csr > 0 ? p->n_rows : 0, nullptr,
-                          p->route, p->fused_mid_row, hints, stream, upd));
+        HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, n_scalar > 0 ? p->n_rows : 0, nullptr,
+                          route, p->fused_mid_row, hints, stream, upd));
     else
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows,
-                          p->short_rows ? p->n_short : (p->n_short > 0 ? p->n_rows : 0), p->short_rows, p->route,
+                          p->short_rows ? p->n_short : (p->n_short > 0 ? p->n_rows : 0), p->short_rows, route,
                           p->mid_row, hints, stream));
     if (ev) HC_HIP(hipEventRecord(ev[3], stream));
     HC_HIP(launch_reduce_partials(a, p->n_multi, p->multi, partial, stream));
@@ -943,7 +1043,7 @@ static void setup_side_streams(hcspmm_plan* p)
 {
     if (p->side_ok || p->side[0]) return;
     p->side_ok = 0;
-    if (p->n_mfma > 0 && p->n_mfma < p->W && p->nnz >= (tune().side_nnz >= 0 ? tune().side_nnz : kSideStreamNnz) && !tune().serial) {
+    if (p->n_mfma > 0 && p->n_mfma < p->W && !p->scalar_exec && p->nnz >= (tune().side_nnz >= 0 ? tune().side_nnz : kSideStreamNnz) && !tune().serial) {
         bool ok = hipStreamCreateWithFlags(&p->side[0], hipStreamNonBlocking) == hipSuccess;
         ok = ok && hipStreamCreateWithFlags(&p->side[1], hipStreamNonBlocking) == hipSuccess;
         ok = ok && hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming) == hipSuccess;
@@ -1060,7 +1160,8 @@ hcspmm_status hcspmm_plan_update(hcspmm_plan* plan, int64_t nnz, const int32_t* 
     // the new tables replace the old ones; streams, events and the lazily sized scratch buffers stay
     fresh.partial = plan->partial; fresh.partial_elems = plan->partial_elems;
     fresh.tile_partial = plan->tile_partial; fresh.tile_partial_elems = plan->tile_partial_elems;
-    plan->partial = nullptr; plan->tile_partial = nullptr;
+    fresh.acc_rows = plan->acc_rows; fresh.acc_rows_elems = plan->acc_rows_elems;
+    plan->partial = nullptr; plan->tile_partial = nullptr; plan->acc_rows = nullptr;
     free_plan_arrays(plan);
     fresh.side_ok = plan->side_ok;
     fresh.side[0] = plan->side[0]; fresh.side[1] = plan->side[1];
@@ -1084,7 +1185,7 @@ hcspmm_status hcspmm_plan_info(const hcspmm_plan* p, hcspmm_plan_info_t* info)
     info->n_mfma_windows = p->n_mfma; info->n_csr_windows = p->n_csr; info->nnz_mfma = p->nnz_mfma;
     info->route_mode = p->opt.route_mode; info->mfma_dtype = p->opt.mfma_dtype; info->d_hint = p->opt.d_hint;
     for (int i = 0; i < 3; ++i) info->sel_coef[i] = p->coef[i];
-    info->device_bytes = p->device_bytes + (p->partial_elems + p->tile_partial_elems) * (int64_t)sizeof(float);
+    info->device_bytes = p->device_bytes + (p->partial_elems + p->tile_partial_elems + p->acc_rows_elems) * (int64_t)sizeof(float);
     info->n_short_rows = p->n_short; info->n_long_rows = p->n_long_rows; info->n_segments = p->n_segs;
     info->n_mid_rows = p->n_mid;
     info->nnz_long = p->nnz_long; info->n_mfma_small = p->n_mfma_small;
@@ -1114,10 +1215,14 @@ hcspmm_status hcspmm_plan_export(const hcspmm_plan* p, int32_t* ncols, int32_t* 
         HC_HIP(hipMemcpy(ecol, p->erc, (size_t)p->nnz * 4, hipMemcpyDeviceToHost));
         for (int64_t k = 0; k < p->nnz; ++k) ecol[k] >>= 4;    // drop the packed row-in-window
     }
-    if (mfma_windows && p->n_mfma) HC_HIP(hipMemcpy(mfma_windows, p->mfma_windows, (size_t)p->n_mfma * 4, hipMemcpyDeviceToHost));
-    if (csr_windows && p->n_mfma == 0)                          // every window: the plan keeps no list
-        for (int32_t w = 0; w < p->n_csr; ++w) csr_windows[w] = w;
-    else if (csr_windows && p->n_csr) HC_HIP(hipMemcpy(csr_windows, p->csr_windows, (size_t)p->n_csr * 4, hipMemcpyDeviceToHost));
+    if ((mfma_windows || csr_windows) && W) {
+        std::vector<uint8_t> h_route(W);
+        HC_HIP(hipMemcpy(h_route.data(), p->route, W, hipMemcpyDeviceToHost));
+        for (int32_t w = 0; w < p->W; ++w) {
+            int32_t*& list = h_route[(size_t)w] ? mfma_windows : csr_windows;
+            if (list) *list++ = w;
+        }
+    }
     return HCSPMM_OK;
 }
 
@@ -1189,10 +1294,10 @@ static hcspmm_status spmm_impl(const hcspmm_plan* plan, const void* d_X, int64_t
     if ((st = check_dense("X", d_X, ldx, d)) != HCSPMM_OK) return st;
     if ((st = check_dense("Y", d_Y, ldy, d)) != HCSPMM_OK) return st;
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.rowend = plan->rowptr + 1; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d; a.x_dtype = x_dtype; a.Y = static_cast<float*>(d_Y); a.ldy = ldy; a.relu = 0;
     a.y_dtype = y_dtype;
-    if (plan->n_mfma > 0 && !mfma_shape_supported(a)) {
+    if (plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) {
         set_error("16-bit X on the matrix path needs d, ldx and ldy to be multiples of 4 and 8-byte aligned X, 16-byte aligned Y");
         return HCSPMM_EUNSUPPORTED;
     }
@@ -1263,18 +1368,18 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
     if (((uintptr_t)d_workspace & 255) != 0) { set_error("workspace must be 256-byte aligned"); return HCSPMM_EINVAL; }
     hipStream_t s = static_cast<hipStream_t>(stream);
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.rowend = plan->rowptr + 1; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_workspace; a.ldx = d_out; a.d = d_out; a.x_dtype = t_dtype; a.Y = static_cast<float*>(d_Y); a.ldy = ldy;
     a.relu = apply_relu ? 1 : 0;
     a.y_dtype = y_dtype;
-    if (t_dtype != HCSPMM_F32 && plan->n_mfma > 0 && !mfma_shape_supported(a)) {
+    if (t_dtype != HCSPMM_F32 && plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) {
         set_error("the matrix path with 16-bit T needs d_out a multiple of 4 and 16-byte aligned Y rows");
         return HCSPMM_EUNSUPPORTED;
     }
     HC_HIP(launch_gemm_f32_out(plan->n_cols, d_in, d_out, static_cast<const float*>(d_X), ldx,
                                static_cast<const float*>(d_W), ldw, d_workspace, d_out, t_dtype, 0, s));
     if (plan->n_rows == 0) return HCSPMM_OK;
-    return run_spmm(plan, a, s);
+    return run_spmm(plan, a, s, nullptr, nullptr, nullptr, true);
 }
 
 // Where the separate update runs through the streaming 16-row kernel (narrow W, aggregated width 64 or 128) it
@@ -1313,12 +1418,12 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* Z = static_cast<float*>(d_workspace);
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.rowend = plan->rowptr + 1; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d_in; a.x_dtype = x_dtype; a.Y = Z; a.ldy = d_in; a.relu = 0;
     // The fused update pays where most rows can keep their tile on chip; rows that go through the
     // workspace anyway (wide matrix-path windows, mid and long rows) are finished 16 at a time, which
     // a plain GEMM does better once they are a large share of the matrix.
-    const bool worth = (4 * (int64_t)plan->n_rest < plan->n_rows &&
+    const bool worth = (4 * (int64_t)plan->n_rest < plan->n_rows && plan->n_panels < 2 &&
                         !(x_dtype == HCSPMM_F32 && split_update_faster(plan->n_rows, d_in, d_out, Z))) ||
                        plan->opt.update_fusion == HCSPMM_UPDATE_FUSED;
     if (update_fusable(a) && worth && plan->opt.update_fusion != HCSPMM_UPDATE_SPLIT) {
@@ -1389,13 +1494,13 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
     }
     if (plan->n_rows > 0) {
         SpmmArgs a{};
-        a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+        a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.rowend = plan->rowptr + 1; a.colind = plan->colind; a.vals = plan->vals;
         a.X = G; a.ldx = g_ld; a.d = d_out; a.x_dtype = HCSPMM_F32; a.Y = S; a.ldy = d_out; a.relu = 0;
         if (d_dX) {
             HC_HIP(launch_transpose(d_in, d_out, static_cast<const float*>(d_W), ldw, Wt, s));
             // as in hcspmm_aggregate_update; when dW needs S in memory as well, the fused kernels store every
             // tile besides multiplying it, which measured faster than the separate GEMM only for narrow S
-            const bool worth = (4 * (int64_t)plan->n_rest < plan->n_rows && (!d_dW || d_out <= 32) &&
+            const bool worth = (4 * (int64_t)plan->n_rest < plan->n_rows && plan->n_panels < 2 && (!d_dW || d_out <= 32) &&
                                 !split_update_faster(plan->n_rows, d_out, d_in, S)) ||
                                plan->opt.update_fusion == HCSPMM_UPDATE_FUSED;
             if (update_fusable(a) && worth && plan->opt.update_fusion != HCSPMM_UPDATE_SPLIT) {

@@ -488,6 +488,21 @@ __global__ __launch_bounds__(256) void k_validate_cols(int32_t n_cols, int64_t n
     if (bad) atomicOr(err, 8);
 }
 
+// rows whose columns do not ascend (a descent inside a row; descents at row starts are looked up)
+__global__ __launch_bounds__(256) void k_pre_sorted(Prep p)
+{
+    if (*p.ctl & 7) return;
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    bool bad = false;
+    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x + 1; k < p.nnz; k += stride) {
+        if (p.colind[k - 1] <= p.colind[k]) continue;
+        int32_t lo = 0, hi = p.n_rows;                          // first row that starts at or behind k
+        while (lo < hi) { const int32_t mid = lo + ((hi - lo) >> 1); if (p.rowptr[mid] < k) lo = mid + 1; else hi = mid; }
+        bad |= p.rowptr[lo] != k;
+    }
+    if (bad) atomicOr(p.ctl + 6, 1);
+}
+
 // Inserts the window's column ids into an open-addressing set of at least 2n entries (linear probing, empty = -1; an id
 // outside the matrix is reported and left out) and counts the insertions that found an empty slot.  The set is never more
 // than half full, so every probe sequence ends.
@@ -723,13 +738,14 @@ __global__ __launch_bounds__(256) void k_pre_rows(Prep p)
         if (p.W == 0 && threadIdx.x == 0) p.wptr[0] = 0;
     }
     __syncthreads();
+    const bool all_scalar = p.scalar_exec && p.ctl[6] == 0;
     unsigned long long a = 0, b = 0, len_long = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int rl = threadIdx.x * 4 + j;
         const int64_t i = (int64_t)tile * kTileRows + rl;
         if (i >= p.n_rows) break;
-        const RowClass c = row_class(p, p.rowptr[i + 1] - p.rowptr[i], s_route[rl / kH], s_wide[rl / kH]);
+        const RowClass c = row_class(p, p.rowptr[i + 1] - p.rowptr[i], all_scalar ? 0 : s_route[rl / kH], s_wide[rl / kH]);
         a += row_counts(c);
         b += seg_counts(c);
         len_long += (unsigned long long)c.len_long;
@@ -769,7 +785,7 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
     unsigned long long a = 0, b = 0;
     const int64_t i0 = min((int64_t)tile * kTileRows + threadIdx.x * 4, (int64_t)p.n_rows);
     const int32_t w = (int32_t)(i0 / kH);
-    const int route = w < p.W ? p.route[w] : 0, wide = w < p.W ? (p.ncols[w] > kMfmaSmallMaxCols ? 1 : 0) : 0;
+    const int route = w < p.W && !(p.scalar_exec && p.ctl[6] == 0) ? p.route[w] : 0, wide = w < p.W ? (p.ncols[w] > kMfmaSmallMaxCols ? 1 : 0) : 0;
 #pragma unroll
     for (int j = 0; j < 5; ++j) start[j] = p.rowptr[min(i0 + j, (int64_t)p.n_rows)];
 #pragma unroll
@@ -837,14 +853,15 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
         t.n_short = (int32_t)n_short; t.n_mid = (int32_t)n_mid; t.n_rest = (int32_t)n_rest; t.n_multi = (int32_t)n_multi;
         t.n_segs = (int32_t)n_seg; t.n_slots = (int64_t)n_slot;
         t.n_big_list = p.ctl[1]; t.n_huge_list = p.ctl[2];
+        t.unsorted = p.ctl[6];
         t.err = 0;
         *p.out = t;
     }
 }
 
-// ascending window lists per route and kernel
-__global__ __launch_bounds__(256) void k_pre_windows(Prep p, int32_t* __restrict__ mfma, int32_t* __restrict__ csr,
-                                                     int32_t* __restrict__ small, int32_t* __restrict__ mid, int32_t* __restrict__ big)
+// ascending lists of the matrix path's windows, all and per kernel
+__global__ __launch_bounds__(256) void k_pre_windows(Prep p, int32_t* __restrict__ mfma, int32_t* __restrict__ small,
+                                                     int32_t* __restrict__ mid, int32_t* __restrict__ big)
 {
     const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (tile >= p.n_tiles) return;
@@ -871,7 +888,7 @@ __global__ __launch_bounds__(256) void k_pre_windows(Prep p, int32_t* __restrict
     if (w >= p.W) return;
     const unsigned long long ex = inc - n;
     const uint32_t i_mfma = (uint32_t)lo + (uint32_t)(ex & 0xffffull);
-    if (!r) { csr[w - i_mfma] = w; return; }
+    if (!r) return;
     mfma[i_mfma] = w;
     if (n >> 16 & 0xffffull) small[(uint32_t)(lo >> 32) + (uint32_t)(ex >> 16 & 0xffffull)] = w;
     else if (n >> 32 & 0xffffull) mid[(uint32_t)hi + (uint32_t)(ex >> 32 & 0xffffull)] = w;
@@ -899,6 +916,11 @@ hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
         if (blocks > 65536) blocks = 65536;
         hipLaunchKernelGGL(k_validate_cols, dim3((unsigned)blocks), dim3(256), 0, s, p.n_cols, p.nnz, p.colind, p.ctl);
     }
+    if (p.check_sorted) {
+        int64_t blocks = (p.nnz + 256 * 16 - 1) / (256 * 16);
+        if (blocks > 65536) blocks = 65536;
+        hipLaunchKernelGGL(k_pre_sorted, dim3((unsigned)blocks), dim3(256), 0, s, p);
+    }
     hipLaunchKernelGGL(k_pre_select, dim3((unsigned)(p.n_tiles + 3) / 4), dim3(256), 0, s, p);
     hipLaunchKernelGGL(k_pre_rows, dim3((unsigned)p.n_tiles), dim3(256), 0, s, p);
     hipLaunchKernelGGL(k_pre_fill, dim3((unsigned)p.n_tiles + 1), dim3(256), 0, s, p);
@@ -911,9 +933,9 @@ hipError_t launch_prep_fill(const Prep& p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* csr, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s)
+hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pre_windows, dim3((unsigned)(p.n_tiles + 3) / 4), dim3(256), 0, s, p, mfma, csr, small, mid, big);
+    hipLaunchKernelGGL(k_pre_windows, dim3((unsigned)(p.n_tiles + 3) / 4), dim3(256), 0, s, p, mfma, small, mid, big);
     return hipGetLastError();
 }
 
@@ -1377,6 +1399,97 @@ hipError_t launch_slice_fill(int32_t n_list, const int32_t* win_list, const int3
     if (n_list <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_slice_fill, dim3((n_list + 255) / 256), dim3(256), 0, s, n_list, win_list, ncols, slice_cols,
                        slice_pos, multi_pos, slot_pos, slices, multi);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// column panels: panel q of n holds the columns [n_cols*q/n, n_cols*(q+1)/n)
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_panel_split(PanelArgs p)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= p.n_rows) return;
+    int32_t lo = p.rowptr[i];
+    const int32_t e = p.rowptr[i + 1];
+    for (int q = 1; q < p.n_panels; ++q) {
+        const int32_t c = (int32_t)((int64_t)p.n_cols * q / p.n_panels);
+        int32_t hi = e;
+        while (lo < hi) { const int32_t mid = lo + ((hi - lo) >> 1); if (p.colind[mid] < c) lo = mid + 1; else hi = mid; }
+        p.split[(int64_t)(q - 1) * p.n_rows + i] = lo;
+    }
+}
+
+struct PanelRow { int32_t s, e; int is_mid, n_seg; };
+__device__ inline PanelRow panel_row(const PanelArgs& p, int q, int64_t i)
+{
+    PanelRow r{0, 0, 0, 0};
+    if (i >= p.n_rows) return r;
+    r.s = q == 0 ? p.rowptr[i] : p.split[(int64_t)(q - 1) * p.n_rows + i];
+    r.e = q == p.n_panels - 1 ? p.rowptr[i + 1] : p.split[(int64_t)q * p.n_rows + i];
+    const int32_t len = r.e - r.s;
+    r.n_seg = len > p.long_row ? (len + kSegLen - 1) / kSegLen : 0;
+    r.is_mid = r.n_seg == 0 && len > p.mid_row;
+    return r;
+}
+
+// sums per panel and tile of 1024 rows: mid rows | rows of several segments, segments | partial rows, non-zeros
+__global__ __launch_bounds__(256) void k_panel_count(PanelArgs p)
+{
+    __shared__ unsigned long long smem[4];
+    const int tile = blockIdx.x, q = blockIdx.y;
+    unsigned long long a = 0, b = 0, n = 0;
+    for (int j = 0; j < 4; ++j) {
+        const PanelRow r = panel_row(p, q, (int64_t)tile * kTileRows + j * 256 + threadIdx.x);
+        a += (unsigned long long)r.is_mid | (unsigned long long)(r.n_seg > 1) << 32;
+        b += (unsigned long long)r.n_seg | (unsigned long long)(r.n_seg > 1 ? r.n_seg : 0) << 32;
+        n += (unsigned long long)(r.e - r.s);
+    }
+    a = block_sum_u64(a, smem);
+    b = block_sum_u64(b, smem);
+    n = block_sum_u64(n, smem);
+    if (threadIdx.x == 0) {
+        unsigned long long* __restrict__ t = p.sums + ((int64_t)q * p.n_tiles + tile) * 3;
+        t[0] = a; t[1] = b; t[2] = n;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_panel_fill(PanelArgs p)
+{
+    __shared__ unsigned long long smem[4];
+    const int tile = blockIdx.x, q = blockIdx.y;
+    unsigned long long a = 0, b = 0, n = 0;                     // in front of the tile
+    for (int t = threadIdx.x; t < tile; t += 256) {
+        const unsigned long long* __restrict__ u = p.sums + ((int64_t)q * p.n_tiles + t) * 3;
+        a += u[0]; b += u[1]; n += u[2];
+    }
+    a = block_sum_u64(a, smem);
+    b = block_sum_u64(b, smem);
+    n = block_sum_u64(n, smem);
+    if (tile == p.n_tiles) {                                    // behind the last tile: the totals
+        if (threadIdx.x == 0) p.out[q] = PanelTotals{(int64_t)n, (int64_t)(b >> 32), (int32_t)a, (int32_t)b, (int32_t)(a >> 32), 0};
+        return;
+    }
+    for (int j = 0; j < 4; ++j) {
+        const int64_t i = (int64_t)tile * kTileRows + j * 256 + threadIdx.x;
+        const PanelRow r = panel_row(p, q, i);
+        const unsigned long long va = (unsigned long long)r.is_mid | (unsigned long long)(r.n_seg > 1) << 32;
+        const unsigned long long vb = (unsigned long long)r.n_seg | (unsigned long long)(r.n_seg > 1 ? r.n_seg : 0) << 32;
+        const unsigned long long ea = a + block_scan_u64(va, smem), eb = b + block_scan_u64(vb, smem);
+        a += block_sum_u64(va, smem);
+        b += block_sum_u64(vb, smem);
+        if (r.is_mid) p.mid_rows[q * p.cap_mid + (uint32_t)ea] = (int32_t)i;
+        for (int k = 0; k < r.n_seg; ++k)
+            p.segs[q * p.cap_segs + (uint32_t)eb + k] = Segment{(int32_t)i, r.s + k * kSegLen, min(r.e, r.s + (k + 1) * kSegLen),
+                                                               r.n_seg > 1 ? (int32_t)(eb >> 32) + k : -1};
+        if (r.n_seg > 1) p.multi[q * p.cap_multi + (uint32_t)(ea >> 32)] = MultiRow{(int32_t)i, (int32_t)(eb >> 32), r.n_seg, 0};
+    }
+}
+
+hipError_t launch_panels(const PanelArgs& p, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_panel_split, dim3((unsigned)(((int64_t)p.n_rows + 255) / 256)), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(k_panel_count, dim3((unsigned)p.n_tiles, (unsigned)p.n_panels), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(k_panel_fill, dim3((unsigned)p.n_tiles + 1, (unsigned)p.n_panels), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 

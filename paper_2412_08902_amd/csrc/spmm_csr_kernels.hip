@@ -64,6 +64,9 @@ template <int BYTES> __device__ __forceinline__ void raw_load(const char* __rest
     else { r.w[0] = *reinterpret_cast<const unsigned short*>(p); }
 }
 
+// VEC consecutive floats at any 4-byte aligned place
+template <int VEC> struct __attribute__((packed, aligned(4))) f32_any { float v[VEC]; };
+
 // XK: element kind of X -- 0 fp32, 1 bf16, 2 fp16.  16-bit elements are widened to fp32; all arithmetic is fp32.
 template <int XK> __device__ __forceinline__ float widened(const uint32_t* w, int i)
 {
@@ -204,6 +207,11 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE> struct Gather {
             float y[VEC];
 #pragma unroll
             for (int i = 0; i < VEC; ++i) y[i] = acc[v * VEC + i];
+            if (a.acc) {                                        // (the row has VEC columns at this place: see init)
+                const f32_any<VEC> t = *reinterpret_cast<const f32_any<VEC>*>(a.acc + row * a.ldacc + (off - row * a.ldy));
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) y[i] += t.v[i];
+            }
             if (y_vec && shift[v] == 0) {
                 out_store<VEC>(a.Y, a.y_dtype, off, y, a.relu);
             } else {
@@ -249,6 +257,7 @@ struct CsrWork {
     int32_t run, run_mid;       // workgroups per XCD-local run of the short and mid tiers (0: plain order)
     int32_t n_slices, slice_w;  // column slices of X
     int32_t y_vec;              // Y rows allow vector stores
+    int32_t skip_empty;         // a row without non-zeros changes nothing (a column panel that adds to Y)
 };
 
 // Block b of a tier of `blocks` workgroups per slice -> (slice, block within the tier).
@@ -326,15 +335,16 @@ __device__ __forceinline__ void walk_rows(const G& g, const SpmmArgs& a, int lig
 
 // extents of the items i0 .. i0+nr-1, one per lane; rows owned by the matrix path or by the mid/long tiers get row -1
 __device__ __forceinline__ void row_extents(int64_t i0, int lig, int nr, const int32_t* __restrict__ row_list,
-                                            const uint8_t* __restrict__ route, int mid_row, const SpmmArgs& a, int32_t& row,
-                                            int32_t& s, int32_t& e)
+                                            const uint8_t* __restrict__ route, int mid_row, int skip_empty, const SpmmArgs& a,
+                                            int32_t& row, int32_t& s, int32_t& e)
 {
     row = -1; s = 0; e = 0;
     if (lig < nr) {
         row = row_list ? row_list[i0 + lig] : (int32_t)(i0 + lig);
         s = a.rowptr[row];
-        e = a.rowptr[row + 1];
-        if (!row_list && (route[row / kH] != 0 || e - s > mid_row)) row = -1;
+        e = a.rowend[row];
+        if (!row_list && ((route && route[row / kH] != 0) || e - s > mid_row)) row = -1;
+        if (skip_empty && s == e) row = -1;
     }
 }
 
@@ -366,7 +376,7 @@ __device__ __forceinline__ void csr_mid_body(int64_t block, int c_begin, int c_e
     const int64_t item = block * 4 + (threadIdx.x >> 6);
     if (item >= wk.n_mid) return;
     const int32_t row = wk.mid_rows[item];
-    const int32_t s = a.rowptr[row], e = a.rowptr[row + 1];
+    const int32_t s = a.rowptr[row], e = a.rowend[row];
     if (e - s <= min_len) return;
     csr_wave_row<G>(row, s, e, c_begin, c_end, wk, a);
 }
@@ -380,7 +390,7 @@ __device__ __forceinline__ void csr_short_body(int64_t block, int c_begin, int c
         const int64_t item = block * 4 + (threadIdx.x >> 6);
         if (item >= wk.n_items) return;
         int32_t row, s, e;
-        row_extents(item, 0, 1, wk.row_list, wk.route, wk.mid_row, a, row, s, e);
+        row_extents(item, 0, 1, wk.row_list, wk.route, wk.mid_row, wk.skip_empty, a, row, s, e);
         if (row >= 0) csr_wave_row<G>(row, s, e, c_begin, c_end, wk, a);
         return;
     }
@@ -388,7 +398,7 @@ __device__ __forceinline__ void csr_short_body(int64_t block, int c_begin, int c
     if (i0 >= wk.n_items) return;
     const int nr = (int)min((int64_t)wk.rows_per_group, (int64_t)wk.n_items - i0);
     int32_t my_row, my_s, my_e;
-    row_extents(i0, lig, nr, wk.row_list, wk.route, wk.mid_row, a, my_row, my_s, my_e);
+    row_extents(i0, lig, nr, wk.row_list, wk.route, wk.mid_row, wk.skip_empty, a, my_row, my_s, my_e);
     for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
         G g;
         g.init(a, c0, min(G::COLS, c_end - c0), lig);
@@ -414,7 +424,7 @@ __device__ __forceinline__ void csr_short_fused_body(int64_t block, const CsrWor
     const int gw = threadIdx.x / kGroup, lig = threadIdx.x % kGroup;
     const int nr = b0 + gw < wk.n_items ? 1 : 0;
     int32_t my_row, my_s, my_e;
-    row_extents(b0 + gw, lig, nr, wk.row_list, wk.route, wk.mid_row, a, my_row, my_s, my_e);
+    row_extents(b0 + gw, lig, nr, wk.row_list, wk.route, wk.mid_row, 0, a, my_row, my_s, my_e);
     if (lig == 0) rows_s[gw] = my_row;
     G g;
     g.init(a, 0, a.d, lig);
@@ -573,6 +583,7 @@ __global__ __launch_bounds__(256) void k_reduce_partials(int32_t n_multi, const 
     for (int c = threadIdx.x; c < a.d; c += 256) {
         float acc = 0.f;
         for (int q = 0; q < m.n_slots; ++q) acc += partial[(int64_t)(m.first_slot + q) * a.d + c];
+        if (a.acc) acc += a.acc[(int64_t)m.row * a.ldacc + c];
         const float one[1] = {acc};
         out_store<1>(a.Y, a.y_dtype, (int64_t)m.row * a.ldy + c, one, a.relu);
     }
@@ -672,6 +683,7 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     // vector stores need Y rows aligned for what a lane stores at once (16-bit results leave in pieces of up to 8 bytes)
     const int yv = sh.vec < 4 ? sh.vec : 4;
     wk.y_vec = a.ldy % yv == 0 && (uintptr_t)a.Y % (yv * (a.y_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
+    wk.skip_empty = a.acc && !a.relu && (const void*)a.acc == (const void*)a.Y && a.ldacc == a.ldy && a.y_dtype == HCSPMM_F32;
     wk.n_slices = 1;
     wk.slice_w = a.d;
     if (!upd) {
