@@ -175,7 +175,7 @@ struct SpmmArgs {
     int32_t n_rows;
     int32_t n_cols;       // rows of X
     const int32_t* rowptr;
-    const int32_t* rowend;    // scalar path: row i is [rowptr[i], rowend[i]) -- rowptr + 1, or a column panel's share of the row
+    const int32_t* rowend;    // null, or a column panel's share of the rows: row i is [rowptr[i], rowend[i])
     const int32_t* colind;
     const float* vals;
     const void* X;
@@ -262,10 +262,12 @@ struct CsrHints {
     int64_t nnz;          // non-zeros of the scalar-path windows
     int64_t rows;
     bool scattered;       // neighbouring rows are known to share few columns
+    int32_t long_row;     // rows with more non-zeros are cut into segments
 };
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
                       int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd = nullptr);
+bool csr_panels_usable(const SpmmArgs& a);   // the launch has kernels that add to rows of sums for this shape
 hipError_t launch_update_rest(const SpmmArgs& a, int32_t n_rest, const int32_t* rest_rows, const UpdateArgs& upd,
                               hipStream_t s);
 // dense product through the 16-row update kernel (narrow W), see spmm_csr_kernels.hip

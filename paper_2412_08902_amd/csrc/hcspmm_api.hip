@@ -874,8 +874,7 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
     // Column panels: the same kernel once per panel, each adding to what the previous ones left (in Y itself when it is fp32).
     // hcspmm_spmm_noalloc has no room for the fp32 sums of a 16-bit output and hcspmm_spmm gives the same bits, so both
     // take the columns of such a call in one go.
-    const int64_t row_bytes = (int64_t)a.d * (a.x_dtype == HCSPMM_F32 ? 4 : 2);
-    if (p->n_panels > 1 && !upd && row_bytes >= kPanelRowBytes && (a.y_dtype == HCSPMM_F32 || acc_rows)) {
+    if (p->n_panels > 1 && !upd && csr_panels_usable(a) && (a.y_dtype == HCSPMM_F32 || acc_rows)) {
         float* sums = a.Y;
         int64_t ld_sums = a.ldy;
         if (a.y_dtype != HCSPMM_F32) {
@@ -899,8 +898,9 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
             SpmmArgs b = a;
             const bool final_panel = q == p->n_panels - 1;
             if (q > 0) { b.rowptr = p->panel_split + (int64_t)(q - 1) * p->n_rows; b.acc = sums; b.ldacc = ld_sums; }
-            if (!final_panel) { b.rowend = p->panel_split + (int64_t)q * p->n_rows; b.Y = sums; b.ldy = ld_sums; b.y_dtype = HCSPMM_F32; b.relu = 0; }
-            const CsrHints hints{t.nnz, p->n_rows, true};
+            b.rowend = final_panel ? p->rowptr + 1 : p->panel_split + (int64_t)q * p->n_rows;
+            if (!final_panel) { b.Y = sums; b.ldy = ld_sums; b.y_dtype = HCSPMM_F32; b.relu = 0; }
+            const CsrHints hints{t.nnz, p->n_rows, true, p->long_row};
             HC_HIP(launch_csr(b, t.n_segs, p->panel[q].segs, partial, t.n_mid, p->panel[q].mid_rows, p->n_rows, nullptr, nullptr, p->mid_row,
                               hints, stream));
             HC_HIP(launch_reduce_partials(b, t.n_multi, p->panel[q].multi, partial, stream));
@@ -944,7 +944,7 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
     // not count them)
     const bool scattered = p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * p->total_ncols > 6 * p->nnz;
     const int64_t nnz_matrix = p->scalar_exec ? 0 : p->nnz_mfma, n_scalar = p->scalar_exec ? p->W : p->n_csr;
-    const CsrHints hints{p->nnz - nnz_matrix, n_scalar * kH, scattered};
+    const CsrHints hints{p->nnz - nnz_matrix, n_scalar * kH, scattered, p->long_row};
     const uint8_t* route = p->scalar_exec ? nullptr : p->route;
     if (upd)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, n_scalar > 0 ? p->n_rows : 0, nullptr,
@@ -1294,7 +1294,7 @@ static hcspmm_status spmm_impl(const hcspmm_plan* plan, const void* d_X, int64_t
     if ((st = check_dense("X", d_X, ldx, d)) != HCSPMM_OK) return st;
     if ((st = check_dense("Y", d_Y, ldy, d)) != HCSPMM_OK) return st;
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.rowend = plan->rowptr + 1; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d; a.x_dtype = x_dtype; a.Y = static_cast<float*>(d_Y); a.ldy = ldy; a.relu = 0;
     a.y_dtype = y_dtype;
     if (plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) {
@@ -1368,7 +1368,7 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
     if (((uintptr_t)d_workspace & 255) != 0) { set_error("workspace must be 256-byte aligned"); return HCSPMM_EINVAL; }
     hipStream_t s = static_cast<hipStream_t>(stream);
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.rowend = plan->rowptr + 1; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_workspace; a.ldx = d_out; a.d = d_out; a.x_dtype = t_dtype; a.Y = static_cast<float*>(d_Y); a.ldy = ldy;
     a.relu = apply_relu ? 1 : 0;
     a.y_dtype = y_dtype;
@@ -1418,7 +1418,7 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* Z = static_cast<float*>(d_workspace);
     SpmmArgs a{};
-    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.rowend = plan->rowptr + 1; a.colind = plan->colind; a.vals = plan->vals;
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d_in; a.x_dtype = x_dtype; a.Y = Z; a.ldy = d_in; a.relu = 0;
     // The fused update pays where most rows can keep their tile on chip; rows that go through the
     // workspace anyway (wide matrix-path windows, mid and long rows) are finished 16 at a time, which
@@ -1494,7 +1494,7 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
     }
     if (plan->n_rows > 0) {
         SpmmArgs a{};
-        a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.rowend = plan->rowptr + 1; a.colind = plan->colind; a.vals = plan->vals;
+        a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
         a.X = G; a.ldx = g_ld; a.d = d_out; a.x_dtype = HCSPMM_F32; a.Y = S; a.ldy = d_out; a.relu = 0;
         if (d_dX) {
             HC_HIP(launch_transpose(d_in, d_out, static_cast<const float*>(d_W), ldw, Wt, s));

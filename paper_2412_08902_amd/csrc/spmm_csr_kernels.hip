@@ -49,6 +49,28 @@ template <int I> __device__ __forceinline__ uint32_t row_bcast(uint32_t x)
 }
 template <int I> __device__ __forceinline__ float row_bcast(float x) { return __uint_as_float(row_bcast<I>(__float_as_uint(x))); }
 
+// ---- launch description ---------------------------------------------------------------------
+// Workgroups are numbered heaviest first: long-row segments, then mid rows (four per workgroup),
+// then the blocks of short rows, so the short rows fill the machine while the last long rows
+// drain instead of each tier waiting for the previous one's tail.
+struct CsrWork {
+    int32_t n_segs;
+    const Segment* segs;
+    float* partial;
+    int32_t n_mid;
+    const int32_t* mid_rows;
+    int32_t n_items;
+    const int32_t* row_list;
+    const uint8_t* route;
+    int32_t rows_per_group;
+    int32_t mid_row;            // longest row of the short tier, or of the mid tier when that has no list (a matrix of few rows)
+    uint32_t seg_blocks, mid_blocks, short_blocks;  // workgroups of each tier and slice, padded (surplus ones exit at once)
+    int32_t run, run_mid;       // log2 of the workgroups per XCD-local run of the short and mid tiers (-1: plain order)
+    int32_t n_slices, slice_w;  // column slices of X
+    int32_t y_vec;              // Y rows allow vector stores
+    int32_t skip_empty;         // a row without non-zeros changes nothing (a column panel that adds to Y)
+};
+
 // One gathered vector as it sits in registers (16-bit elements stay packed until they are multiplied).  Loads are
 // aligned to 4 bytes at least (2 for single 16-bit elements), which is all the hardware asks for.
 typedef uint32_t raw4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -80,7 +102,10 @@ template <int XK> __device__ __forceinline__ float widened(const uint32_t* w, in
 // are added when the row is done.  A vector-memory instruction takes the CU's load path 16 clocks whether its lanes ask for
 // 8 or 16 bytes (measured on cache hits: 140 G rows of 128 bytes per second with 16 lanes x 8 bytes, 206 G with 8 x 16), so
 // rows of up to 128 bytes are read by 8 lanes; the second broadcast that this takes is free, the VALU has slack.
-template <int XK, int VEC, int NV, int SPLIT, bool WIDE> struct Gather {
+// PANEL: a column panel's share of the rows -- each row's end is read from a.rowend, and results may be added to rows of fp32
+// sums.  (Kept out of the plain kernels, which have no scalar register to spare in 128-byte rows: power law, fp32, 32
+// columns, 39.7 -> 35.1 us.)
+template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> struct Gather {
     static constexpr int ES = XK == 0 ? 4 : 2;
     static constexpr int BYTES = VEC * ES;
     static constexpr int LANES = kGroup / SPLIT;                // lanes per X row
@@ -93,7 +118,7 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE> struct Gather {
     // vectors with one accumulator set are squeezed into 64 registers for all 8 waves (community graph, bf16, 64 columns:
     // 37.0 -> 32.2 us; power law, fp32, 32 columns: 36.7 -> 35.1 us); wider rows are bound by the traffic behind L2 and
     // lose more to the squeeze (fp32, 128 columns: 120.8 -> 137 us).
-    static constexpr int WAVES = SPLIT == 2 ? 8 : (XK != 0 && VEC == 8 && NV == 1) ? 6 : 1;
+    static constexpr int WAVES = SPLIT == 2 ? (XK == 0 && PANEL ? 7 : 8) : (XK != 0 && VEC == 8 && NV == 1) ? 6 : 1;
 
     const char* X;              // uniform: first column of the slice
     uint64_t ldxb;              // bytes between rows (uniform)
@@ -197,6 +222,13 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE> struct Gather {
                 acc[i] += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(acc[i]), 0x128 /* row_ror:8 */, 0xf, 0xf, true));
         }
     }
+    static __device__ __forceinline__ void extent(const SpmmArgs& a, int32_t row, int32_t& s, int32_t& e)
+    {
+        s = a.rowptr[row];
+        e = PANEL ? a.rowend[row] : a.rowptr[row + 1];
+    }
+    // a panel's share of a row that adds nothing to rows of sums
+    static __device__ __forceinline__ bool skipped(const CsrWork& wk, int32_t s, int32_t e) { return PANEL && wk.skip_empty && s == e; }
     // stores the lane's columns of output row `row` (element type a.y_dtype); c0: first column of the slice
     __device__ __forceinline__ void store(const SpmmArgs& a, int y_vec, int64_t row, int c0, int lig, const float (&acc)[N]) const
     {
@@ -207,7 +239,7 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE> struct Gather {
             float y[VEC];
 #pragma unroll
             for (int i = 0; i < VEC; ++i) y[i] = acc[v * VEC + i];
-            if (a.acc) {                                        // (the row has VEC columns at this place: see init)
+            if (PANEL && a.acc) {                               // (the row has VEC columns at this place: see init)
                 const f32_any<VEC> t = *reinterpret_cast<const f32_any<VEC>*>(a.acc + row * a.ldacc + (off - row * a.ldy));
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) y[i] += t.v[i];
@@ -237,29 +269,6 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE> struct Gather {
     }
 };
 
-// ---- launch description ---------------------------------------------------------------------
-// Workgroups are numbered heaviest first: long-row segments, then mid rows (four per workgroup),
-// then the blocks of short rows, so the short rows fill the machine while the last long rows
-// drain instead of each tier waiting for the previous one's tail.
-struct CsrWork {
-    int32_t n_segs;
-    const Segment* segs;
-    float* partial;
-    int32_t n_mid;
-    const int32_t* mid_rows;
-    int32_t n_items;
-    const int32_t* row_list;
-    const uint8_t* route;
-    int32_t rows_per_group;
-    int32_t wave_rows;          // short rows get a wave each
-    int32_t mid_row;
-    int64_t seg_blocks, mid_blocks, short_blocks;   // workgroups of each tier and slice, padded (surplus ones exit at once)
-    int32_t run, run_mid;       // workgroups per XCD-local run of the short and mid tiers (0: plain order)
-    int32_t n_slices, slice_w;  // column slices of X
-    int32_t y_vec;              // Y rows allow vector stores
-    int32_t skip_empty;         // a row without non-zeros changes nothing (a column panel that adds to Y)
-};
-
 // Block b of a tier of `blocks` workgroups per slice -> (slice, block within the tier).
 // Workgroups go to the eight XCDs round-robin by their linear id, and each XCD has an L2 of its own.
 //  * The tier's blocks are handed out in runs of `run` consecutive ones that stay on one XCD: neighbouring rows -- which
@@ -267,26 +276,25 @@ struct CsrWork {
 //    matrix side by side (rows sorted by degree stay balanced).
 //  * With 2, 4 or 8 column slices XCD x works on slice x % n_slices only, so that its L2 holds rows of ONE slice.
 //  * Other slice counts take the slices one after the other.
-__device__ __forceinline__ int64_t csr_block(int64_t b, int64_t blocks, int run, int n_slices, int& slice)
+__device__ __forceinline__ uint32_t csr_block(uint32_t b, uint32_t blocks, int run, int n_slices, int& slice)
 {
-    const int x = blockIdx.x & 7;
+    const uint32_t x = blockIdx.x & 7;
     slice = 0;
-    int nsub = 8, sub = x;
+    uint32_t nsub = 8, sub = x;
     if (n_slices > 1) {
         if (n_slices == 2 || n_slices == 4 || n_slices == 8) {
             nsub = 8 / n_slices;
-            slice = x & (n_slices - 1);
+            slice = (int)(x & (n_slices - 1));
             sub = x / n_slices;
-            const int64_t q = b >> 3;
-            if (run < 1) run = 1;
-            return ((q / run) * nsub + sub) * run + q % run;
+            run = max(run, 0);
+        } else {
+            slice = (int)(b / blocks);
+            b -= (uint32_t)slice * blocks;
         }
-        slice = (int)(b / blocks);
-        b -= slice * blocks;
     }
-    if (run <= 0) return b;
-    const int64_t q = b >> 3;
-    return ((q / run) * nsub + sub) * run + q % run;
+    if (run < 0) return b;
+    const uint32_t q = b >> 3;
+    return ((((q >> run) * nsub) + sub) << run) + (q & ((1u << run) - 1));
 }
 
 // ---- short rows -----------------------------------------------------------------------------
@@ -334,24 +342,30 @@ __device__ __forceinline__ void walk_rows(const G& g, const SpmmArgs& a, int lig
 }
 
 // extents of the items i0 .. i0+nr-1, one per lane; rows owned by the matrix path or by the mid/long tiers get row -1
-__device__ __forceinline__ void row_extents(int64_t i0, int lig, int nr, const int32_t* __restrict__ row_list,
-                                            const uint8_t* __restrict__ route, int mid_row, int skip_empty, const SpmmArgs& a,
+template <class G>
+__device__ __forceinline__ void row_extents(uint32_t i0, int lig, int nr, const CsrWork& wk, const SpmmArgs& a,
                                             int32_t& row, int32_t& s, int32_t& e)
 {
     row = -1; s = 0; e = 0;
     if (lig < nr) {
-        row = row_list ? row_list[i0 + lig] : (int32_t)(i0 + lig);
-        s = a.rowptr[row];
-        e = a.rowend[row];
-        if (!row_list && ((route && route[row / kH] != 0) || e - s > mid_row)) row = -1;
-        if (skip_empty && s == e) row = -1;
+        row = wk.row_list ? wk.row_list[i0 + lig] : (int32_t)(i0 + lig);
+        G::extent(a, row, s, e);
+        if (!wk.row_list && ((wk.route && wk.route[row / kH] != 0) || e - s > wk.mid_row)) row = -1;
+        if (G::skipped(wk, s, e)) row = -1;
     }
 }
 
 // ---- mid rows: one wave per row -------------------------------------------------------------
 template <class G>
-__device__ __forceinline__ void csr_wave_row(int32_t row, int s, int e, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a)
+__device__ __forceinline__ void csr_mid_body(uint32_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a,
+                                             int min_len = 0 /* rows this short belong to another tier */)
 {
+    const uint32_t item = block * 4 + (threadIdx.x >> 6);
+    if (item >= (uint32_t)wk.n_mid) return;
+    const int32_t row = wk.mid_rows ? wk.mid_rows[item] : (int32_t)item;
+    int32_t s, e;
+    G::extent(a, row, s, e);
+    if (wk.mid_rows ? e - s <= min_len : e - s > wk.mid_row || (wk.route && wk.route[row / kH] != 0) || G::skipped(wk, s, e)) return;
     const int lane = threadIdx.x & 63, gi = lane / kGroup, lig = lane % kGroup;
     for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
         G g;
@@ -370,35 +384,15 @@ __device__ __forceinline__ void csr_wave_row(int32_t row, int s, int e, int c_be
 }
 
 template <class G>
-__device__ __forceinline__ void csr_mid_body(int64_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a,
-                                             int min_len = 0 /* rows this short belong to another tier */)
-{
-    const int64_t item = block * 4 + (threadIdx.x >> 6);
-    if (item >= wk.n_mid) return;
-    const int32_t row = wk.mid_rows[item];
-    const int32_t s = a.rowptr[row], e = a.rowend[row];
-    if (e - s <= min_len) return;
-    csr_wave_row<G>(row, s, e, c_begin, c_end, wk, a);
-}
-
-template <class G>
-__device__ __forceinline__ void csr_short_body(int64_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a)
+__device__ __forceinline__ void csr_short_body(uint32_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a)
 {
     static_assert(kGroup >= kRowsPerGroup, "a group must be able to hold one row extent per lane");
     const int lig = threadIdx.x % kGroup;
-    if (wk.wave_rows) {                                         // few rows: a wave each
-        const int64_t item = block * 4 + (threadIdx.x >> 6);
-        if (item >= wk.n_items) return;
-        int32_t row, s, e;
-        row_extents(item, 0, 1, wk.row_list, wk.route, wk.mid_row, wk.skip_empty, a, row, s, e);
-        if (row >= 0) csr_wave_row<G>(row, s, e, c_begin, c_end, wk, a);
-        return;
-    }
-    const int64_t i0 = (block * (256 / kGroup) + threadIdx.x / kGroup) * wk.rows_per_group;
-    if (i0 >= wk.n_items) return;
-    const int nr = (int)min((int64_t)wk.rows_per_group, (int64_t)wk.n_items - i0);
+    const uint32_t i0 = (block * (256 / kGroup) + threadIdx.x / kGroup) * wk.rows_per_group;
+    if (i0 >= (uint32_t)wk.n_items) return;
+    const int nr = min(wk.rows_per_group, wk.n_items - (int)i0);
     int32_t my_row, my_s, my_e;
-    row_extents(i0, lig, nr, wk.row_list, wk.route, wk.mid_row, wk.skip_empty, a, my_row, my_s, my_e);
+    row_extents<G>(i0, lig, nr, wk, a, my_row, my_s, my_e);
     for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
         G g;
         g.init(a, c0, min(G::COLS, c_end - c0), lig);
@@ -414,17 +408,17 @@ __device__ __forceinline__ void csr_short_body(int64_t block, int c_begin, int c
 // (Section V-A: the aggregation result of a window stays on chip for the update).
 // The width d must fit one pass of the group (d <= G::COLS) and be a multiple of 16.
 template <class G>
-__device__ __forceinline__ void csr_short_fused_body(int64_t block, const CsrWork& wk, const SpmmArgs& a, const UpdateArgs& u,
+__device__ __forceinline__ void csr_short_fused_body(uint32_t block, const CsrWork& wk, const SpmmArgs& a, const UpdateArgs& u,
                                                      float* __restrict__ zt, int32_t* __restrict__ rows_s)
 {
     constexpr int LDZ = G::COLS + 4;
-    const int64_t b0 = block * 16;                              // first list entry of the workgroup
-    if (b0 >= wk.n_items) return;                               // whole workgroup past the end
+    const uint32_t b0 = block * 16;                             // first list entry of the workgroup
+    if (b0 >= (uint32_t)wk.n_items) return;                               // whole workgroup past the end
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int gw = threadIdx.x / kGroup, lig = threadIdx.x % kGroup;
-    const int nr = b0 + gw < wk.n_items ? 1 : 0;
+    const int nr = b0 + gw < (uint32_t)wk.n_items ? 1 : 0;
     int32_t my_row, my_s, my_e;
-    row_extents(b0 + gw, lig, nr, wk.row_list, wk.route, wk.mid_row, 0, a, my_row, my_s, my_e);
+    row_extents<G>(b0 + gw, lig, nr, wk, a, my_row, my_s, my_e);
     if (lig == 0) rows_s[gw] = my_row;
     G g;
     g.init(a, 0, a.d, lig);
@@ -437,11 +431,11 @@ __device__ __forceinline__ void csr_short_fused_body(int64_t block, const CsrWor
 
 // ---- long rows: one workgroup per segment of a row ------------------------------------------
 template <class G>
-__device__ __forceinline__ void csr_long_body(int64_t block, int c_begin, int c_end, const CsrWork& wk,
+__device__ __forceinline__ void csr_long_body(uint32_t block, int c_begin, int c_end, const CsrWork& wk,
                                               float* __restrict__ red /* LDS, 256 * G::N floats */, const SpmmArgs& a)
 {
     constexpr int NG = 256 / kGroup;
-    if (block >= wk.n_segs) return;
+    if (block >= (uint32_t)wk.n_segs) return;
     const Segment sg = wk.segs[block];
     const int gi = threadIdx.x / kGroup, lig = threadIdx.x % kGroup;
     for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
@@ -477,10 +471,10 @@ template <class G>
 __global__ __launch_bounds__(256, G::WAVES) void k_csr(CsrWork wk, SpmmArgs a)
 {
     __shared__ float red[256 * G::N];
-    int64_t b = blockIdx.x;
+    uint32_t b = blockIdx.x;
     int slice;
     if (b < wk.seg_blocks * wk.n_slices) {
-        b = csr_block(b, wk.seg_blocks, 0, wk.n_slices, slice);
+        b = csr_block(b, wk.seg_blocks, -1, wk.n_slices, slice);
         const int c0 = slice * wk.slice_w;
         csr_long_body<G>(b, c0, min(a.d, c0 + wk.slice_w), wk, red, a);
         return;
@@ -506,7 +500,7 @@ __global__ __launch_bounds__(256) void k_csr_fused(CsrWork wk, SpmmArgs a, Updat
     constexpr int kTile = 16 * (G::COLS + 4), kRed = 256 * G::N;
     __shared__ float lds[kTile > kRed ? kTile : kRed];          // the reduction of a long row and the tile of short rows never meet
     __shared__ int32_t rows16[16];
-    int64_t b = blockIdx.x;
+    uint32_t b = blockIdx.x;
     int slice;
     if (b < wk.seg_blocks) {
         csr_long_body<G>(b, 0, a.d, wk, lds, a);
@@ -617,6 +611,10 @@ static CsrShape pick_shape(const SpmmArgs& a)
 }
 static int shape_cols(const CsrShape& sh) { return kGroup / sh.split * sh.vec * sh.nv; }
 
+#define HC_CSR_PANEL_DISPATCH(FN, XK, V)                                                             \
+    if (sh.split == 2) HC_CSR_ONE(FN, XK, V, 1, 2);                                                \
+    else if (sh.nv == 1) HC_CSR_ONE(FN, XK, V, 1, 1);                                              \
+    else HC_CSR_ONE(FN, XK, V, 2, 1);
 #define HC_CSR_ONE(FN, XK, V, NVV, SP) do { if (sh.wide) { FN(XK, V, NVV, SP, true); } else { FN(XK, V, NVV, SP, false); } } while (0)
 #define HC_CSR_DISPATCH32(FN)                                                                      \
     if (sh.vec == 1) HC_CSR_ONE(FN, 0, 1, 1, 1);                                                   \
@@ -672,6 +670,12 @@ bool update_fusable(const SpmmArgs& a)
     return shape_cols(sh) >= a.d && a.ldy % 4 == 0 && (uintptr_t)a.Y % 16 == 0 && mfma_update_fusable(a);
 }
 
+bool csr_panels_usable(const SpmmArgs& a)
+{
+    const CsrShape sh = pick_shape(a);
+    return (int64_t)a.d * (a.x_dtype == HCSPMM_F32 ? 4 : 2) >= kPanelRowBytes && sh.vec == (a.x_dtype == HCSPMM_F32 ? 4 : 8);
+}
+
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
                       int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd)
@@ -698,21 +702,21 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     }
     // XCD-local runs (see csr_block): tiers of at least 1024 workgroups are padded to whole rounds of runs over the XCDs
     // that share a slice; the surplus workgroups exit at once
-    int run = 32;
-    if (tune().xcd_chunk >= 0) run = tune().xcd_chunk;
+    int run = 5;
+    if (tune().xcd_chunk >= 0) for (run = -1; tune().xcd_chunk >> (run + 1);) ++run;
     const bool owned = wk.n_slices == 2 || wk.n_slices == 4 || wk.n_slices == 8;
     const int nsub = owned ? 8 / wk.n_slices : 8;
     auto pad_runs = [&](int64_t n, int32_t& r) {
-        r = (run <= 0 || n < 1024) ? 0 : run;
-        const int64_t unit = (int64_t)nsub * (r > 0 ? r : 1);
-        return (r > 0 || owned) ? (n + unit - 1) / unit * unit : n;
+        r = n < 1024 ? -1 : run;
+        const int64_t unit = (int64_t)nsub << (r > 0 ? r : 0);
+        return (uint32_t)((r >= 0 || owned) ? (n + unit - 1) / unit * unit : n);
     };
-    wk.seg_blocks = owned ? ((int64_t)n_segs + nsub - 1) / nsub * nsub : n_segs;
+    wk.seg_blocks = (uint32_t)(owned ? ((int64_t)n_segs + nsub - 1) / nsub * nsub : n_segs);
     if (upd) {
         wk.rows_per_group = 1;
-        wk.mid_blocks = ((int64_t)n_mid + 3) / 4;
+        wk.mid_blocks = (uint32_t)(((int64_t)n_mid + 3) / 4);
         wk.short_blocks = pad_runs(((int64_t)n_items + 15) / 16, wk.run);
-        const int64_t blocks = wk.seg_blocks + wk.mid_blocks + wk.short_blocks;
+        const int64_t blocks = (int64_t)wk.seg_blocks + wk.mid_blocks + wk.short_blocks;
         if (blocks <= 0) return hipSuccess;
 #define HC_LAUNCH_CSRF(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr_fused<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a, *upd)
         HC_CSR_DISPATCH(HC_LAUNCH_CSRF)
@@ -723,15 +727,30 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     if (tune().rpg >= 1 && tune().rpg <= kRowsPerGroup) rpg = tune().rpg;
     wk.rows_per_group = rpg;
     const int64_t n_groups = ((int64_t)n_items + rpg - 1) / rpg;
-    // While a wave per row and slice still fits the chip at once (256 CUs x 32 waves), a row's non-zeros are spread over
-    // its four groups instead of queueing in one (2,708 nodes, 32 columns: 5.6 -> 3.6 us of kernel time).
-    wk.wave_rows = (int64_t)n_items * wk.n_slices <= 8192;
-    wk.short_blocks = pad_runs(wk.wave_rows ? ((int64_t)n_items + 3) / 4 : (n_groups + 15) / 16, wk.run);
-    wk.mid_blocks = pad_runs(((int64_t)n_mid + 3) / 4, wk.run_mid);
-    const int64_t blocks = (wk.seg_blocks + wk.mid_blocks + wk.short_blocks) * wk.n_slices;
+    // While a wave per row and slice still fits the chip at once (256 CUs x 32 waves), every row is a mid row: its non-zeros
+    // are spread over four groups instead of queueing in one (2,708 nodes, 32 columns: 5.6 -> 3.6 us of kernel time).
+    if (n_items > 0 && (int64_t)a.n_rows * wk.n_slices <= 8192) {
+        wk.n_mid = a.n_rows;
+        wk.mid_rows = nullptr;
+        wk.mid_row = hints.long_row;
+        wk.n_items = 0;
+    }
+    wk.short_blocks = wk.n_items > 0 ? pad_runs((n_groups + 15) / 16, wk.run) : 0;
+    wk.mid_blocks = pad_runs(((int64_t)wk.n_mid + 3) / 4, wk.run_mid);
+    const int64_t blocks = ((int64_t)wk.seg_blocks + wk.mid_blocks + wk.short_blocks) * wk.n_slices;
     if (blocks <= 0) return hipSuccess;
 #define HC_LAUNCH_CSR(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a)
+#define HC_LAUNCH_PANEL(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W, true>>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a)
+    if (a.rowend) {
+        // panels are taken for rows of kPanelRowBytes and more: 16-byte vectors, at most two per lane and slice
+        if (sh.vec != (a.x_dtype == HCSPMM_F32 ? 4 : 8) || sh.nv > 2) return hipErrorInvalidValue;
+        if (a.x_dtype == HCSPMM_F32) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 0, 4) }
+        else if (a.x_dtype == HCSPMM_BF16) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 1, 8) }
+        else { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 2, 8) }
+        return hipGetLastError();
+    }
     HC_CSR_DISPATCH(HC_LAUNCH_CSR)
+#undef HC_LAUNCH_PANEL
 #undef HC_LAUNCH_CSR
     return hipGetLastError();
 }
