@@ -2,111 +2,184 @@
 // over all rows of the graph, plus the two small helpers around it (activation mask on the incoming
 // gradient, transpose of W for the product S W^T that the update epilogue computes).
 //
-// dW = X^T S is a product with a short output (d_in x d) and a contraction as long as the graph has
-// rows, so it is bound by reading X and S once.  The rows are cut into contiguous spans, one per
-// workgroup column; a workgroup streams its span 64 rows at a time through LDS (next stage's global
-// loads are in flight while the current one is multiplied), each of its four waves owning a 16-row
-// strip of the output and all its 16-column blocks in accumulators (v_mfma_f32_16x16x4_f32: lane
-// (i = l%16, q = l/16) supplies A(i, k=q) = X[row q][i] and B(k=q, i) = S[row q][i]).  Every span
-// writes its partial product and a second kernel adds the partials in span order, so the result
-// does not depend on scheduling.
+// dW = X^T S is a product with a short output (d_in x d) and a contraction as long as the graph has rows: reading X and S
+// once and the matrix units (v_mfma_f32_16x16x4_f32) bound it about equally at 128 x 128.  Both operands of a step of four
+// rows are rows as they lie in memory -- lane (c = l%16, q = l/16) supplies A(column, k = q) = X[row q][..] and B(k = q,
+// column) = S[row q][..] -- so they are loaded straight into registers: a wave owns up to 4 x 4 tiles of 16 x 16 outputs
+// (tile i of MT holds the columns base + MT*c + i, so MT values are one vector load; or base + 16*i + c, one value each,
+// where the width is no multiple of MT), keeps a ring of four steps in flight and never meets a barrier before its end.
+// A workgroup's waves are Q such blocks times RG row groups; the row groups' sums are added through LDS, every workgroup
+// (one per CU) writes one partial product and a second kernel adds the partials, all in an order that depends on sizes only.
+// (64-row stages through LDS with two barriers each, 512 partial products: 169,343 x 128 x 128 took 106 us + 8 us,
+// now 61 us + 6 us.)
 #include "common.hpp"
 
 namespace hcspmm {
 
 typedef float v4f_bw __attribute__((ext_vector_type(4)));
+template <int N> struct __attribute__((packed, aligned(4))) f32_vec { float v[N]; };
 
-constexpr int kTnRows = 64;       // rows of X and S per stage
-constexpr int kTnM = 64;          // output rows (columns of X) per workgroup: 16 per wave
-constexpr int kTnLdx = kTnM + 16; // LDS row pitches: = 16 mod 64, so the four k rows of an operand read fall in distinct banks
+constexpr int kTnSteps = 4, kTnBatch = 4 * kTnSteps;                // steps and rows per batch
+constexpr int kTnWaves = 8;                                         // waves per workgroup at most
 
-template <int NB> struct TnShape {
-    static constexpr int N = NB * 16;                               // output columns (columns of S) per workgroup
-    static constexpr int LDS_S = (N + 63) / 64 * 64 + 16;
-    static constexpr int XV = kTnRows * kTnM / 4 / 256;             // float4 per thread per stage, X
-    static constexpr int SV = (kTnRows * N / 4 + 255) / 256;        // float4 per thread per stage, S
-};
-
-// one float4 of a row-major matrix with zero fill outside [0, rows) x [0, cols); vec: rows are 16-byte aligned
-__device__ inline float4 load4_guarded(const float* __restrict__ p, int64_t ld, int64_t r, int64_t rows, int c, int cols,
-                                       bool vec)
+// How a d_in x d output is cut: MT x NT tiles per wave, qm x qn waves side by side in a workgroup, ny x nz workgroups, rg row
+// groups per workgroup, `spans` workgroups along the rows.
+struct TnShape { int mt, nt, qm, qn, ny, nz, rg; int32_t spans; };
+static TnShape tn_shape(int64_t n_rows, int32_t d_in, int32_t d)
 {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (r >= rows || c >= cols) return v;
-    const float* __restrict__ q = p + r * ld + c;
-    if (vec && c + 4 <= cols) return *reinterpret_cast<const float4*>(q);
-    v.x = q[0];
-    if (c + 1 < cols) v.y = q[1];
-    if (c + 2 < cols) v.z = q[2];
-    if (c + 3 < cols) v.w = q[3];
-    return v;
+    TnShape t;
+    const int m16 = (d_in + 15) / 16, n16 = (d + 15) / 16;
+    const int qm_all = (m16 + 3) / 4, qn_all = (n16 + 3) / 4;
+    t.mt = (m16 + qm_all - 1) / qm_all;
+    t.nt = (n16 + qn_all - 1) / qn_all;
+    // One wave per SIMD where it has more than eight tiles (a step's products take four times as long as its loads then, and
+    // more waves only cost start-up, reduction and larger outputs per workgroup: 60,000 x 256 x 256: 16 waves 115 us, 8 waves
+    // 90 us, 4 waves 80 us; 169,343 x 128 x 128: 82, 77, 74 us), two for smaller blocks, which are bound by their loads
+    // (400,000 x 32 x 128: 4 waves 56.7 us, 8 waves 54.3 us).
+    const int waves = t.mt * t.nt > 8 ? 4 : kTnWaves;
+    t.nz = (qn_all + waves - 1) / waves;
+    t.qn = (qn_all + t.nz - 1) / t.nz;
+    const int most = waves / t.qn;
+    t.ny = (qm_all + most - 1) / most;
+    t.qm = (qm_all + t.ny - 1) / t.ny;
+    // row groups: the four SIMDs of a CU should carry equally many waves, and as many as fit
+    const int q = t.qm * t.qn;
+    t.rg = 1;
+    double best = 0.0;
+    for (int rg = 1; rg * q <= waves; ++rg) {
+        const double even = (double)(rg * q) / ((rg * q + 3) / 4 * 4);
+        if (even >= best) { best = even; t.rg = rg; }
+    }
+    const int64_t batches = (n_rows + kTnBatch - 1) / kTnBatch;
+    int64_t spans = 256 / ((int64_t)t.ny * t.nz);                   // a workgroup per CU
+    if (spans > batches / (2 * t.rg)) spans = batches / (2 * t.rg); // two batches per wave at least
+    t.spans = (int32_t)(spans < 1 ? 1 : spans);
+    return t;
 }
 
-template <int NB>
-__global__ __launch_bounds__(256) void k_gemm_tn(int64_t n_rows, int64_t rows_per_span, const float* __restrict__ X,
-                                                 int64_t ldx, int32_t d_in, const float* __restrict__ S, int64_t lds_,
-                                                 int32_t d, float* __restrict__ partial, int xvec, int svec)
+template <int MT, int NT, bool VEC>
+__global__ __launch_bounds__(64 * kTnWaves) void k_gemm_tn(int64_t n_rows, const float* __restrict__ X, int64_t ldx, int32_t d_in,
+                                                           const float* __restrict__ S, int64_t lds_, int32_t d, int qm, int qn,
+                                                           int rg_count, float* __restrict__ partial)
 {
-    using T = TnShape<NB>;
-    extern __shared__ float smem[];
-    float* __restrict__ xs = smem;                                  // kTnRows x kTnLdx
-    float* __restrict__ ss = smem + kTnRows * kTnLdx;               // kTnRows x LDS_S
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int i = lane & 15, q = lane >> 4;
-    const int m0 = blockIdx.y * kTnM, n0 = blockIdx.z * 256;
-    const int64_t r_begin = (int64_t)blockIdx.x * rows_per_span;
-    const int64_t r_end = min(n_rows, r_begin + rows_per_span);
-    v4f_bw acc[NB];
+    extern __shared__ float red[];                                  // rg_count / 2 * qm * qn blocks of 64 x 4*MT*NT sums
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
+    const int blocks = qm * qn, rg = wave / blocks, blk = wave % blocks;
+    const int m0 = ((int)blockIdx.y * qm + blk / qn) * 16 * MT, n0 = ((int)blockIdx.z * qn + blk % qn) * 16 * NT;
+    const bool live = m0 < d_in && n0 < d;                          // (uniform; a block of the last y or z may be all padding)
+    // column offsets of this lane's values inside a row; past the matrix they repeat its last columns (and are not stored)
+    int xo[VEC ? 1 : MT], so[VEC ? 1 : NT];
+    if constexpr (VEC) {
+        xo[0] = min(m0 + MT * c, d_in - MT);
+        so[0] = min(n0 + NT * c, d - NT);
+    } else {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = (v4f_bw){0.f, 0.f, 0.f, 0.f};
-    float4 xr[T::XV], sr[T::SV];
-    auto fetch = [&](int64_t r0) {
+        for (int i = 0; i < MT; ++i) xo[i] = min(m0 + 16 * i + c, d_in - 1);
 #pragma unroll
-        for (int j = 0; j < T::XV; ++j) {
-            const int idx = tid + 256 * j, r = idx / (kTnM / 4), c = (idx % (kTnM / 4)) * 4;
-            xr[j] = load4_guarded(X, ldx, r0 + r, r_end, m0 + c, d_in, xvec);
-        }
+        for (int j = 0; j < NT; ++j) so[j] = min(n0 + 16 * j + c, d - 1);
+    }
+    v4f_bw acc[MT][NT];
 #pragma unroll
-        for (int j = 0; j < T::SV; ++j) {
-            const int idx = tid + 256 * j, r = idx / (T::N / 4), c = (idx % (T::N / 4)) * 4;
-            sr[j] = r < kTnRows ? load4_guarded(S, lds_, r0 + r, r_end, n0 + c, d, svec) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = (v4f_bw){0.f, 0.f, 0.f, 0.f};
+    constexpr int RING = 4;                                         // steps in flight
+    float x[RING][MT], y[RING][NT];
+    auto fetch = [&](int64_t r0 /* uniform */, int dr, float (&a)[MT], float (&b)[NT]) {
+        const float* __restrict__ px = X + r0 * ldx + dr * ldx;
+        const float* __restrict__ ps = S + r0 * lds_ + dr * lds_;
+        if constexpr (VEC) {
+            const f32_vec<MT> va = *reinterpret_cast<const f32_vec<MT>*>(px + xo[0]);
+            const f32_vec<NT> vb = *reinterpret_cast<const f32_vec<NT>*>(ps + so[0]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = va.v[i];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) b[j] = vb.v[j];
+        } else {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = px[xo[i]];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) b[j] = ps[so[j]];
         }
     };
-    if (r_begin < r_end) fetch(r_begin);
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += kTnRows) {
-        __syncthreads();                                            // the previous stage's reads are done
+    auto multiply = [&](const float (&a)[MT], const float (&b)[NT]) {
 #pragma unroll
-        for (int j = 0; j < T::XV; ++j) {
-            const int idx = tid + 256 * j, r = idx / (kTnM / 4), c = (idx % (kTnM / 4)) * 4;
-            *reinterpret_cast<float4*>(&xs[r * kTnLdx + c]) = xr[j];
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    };
+    // the workgroup's whole batches, taken in turn by its row groups (each reads a stretch of its own close to the others')
+    const int64_t whole = n_rows / kTnBatch, G = gridDim.x;
+    const int64_t b_end = (blockIdx.x + 1) * whole / G;
+    int64_t b = blockIdx.x * whole / G + rg;
+    if (live && b < b_end) {
+        const int64_t last = b_end - 1;
+        // row of step u of batch b; requests past the span repeat its last batch (branches would cost waits at their joins)
+        auto row = [&](int64_t bb, int u) { return min(bb, last) * kTnBatch + 4 * u; };
+#pragma unroll
+        for (int u = 0; u < RING; ++u) {
+            fetch(row(b, u), q, x[u], y[u]);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        for (; b < b_end; b += rg_count) {
 #pragma unroll
-        for (int j = 0; j < T::SV; ++j) {
-            const int idx = tid + 256 * j, r = idx / (T::N / 4), c = (idx % (T::N / 4)) * 4;
-            if (r < kTnRows) *reinterpret_cast<float4*>(&ss[r * T::LDS_S + c]) = sr[j];
+            for (int u = 0; u < kTnSteps; ++u) {
+                multiply(x[u % RING], y[u % RING]);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(u + RING < kTnSteps ? row(b, u + RING) : row(b + rg_count, u + RING - kTnSteps), q, x[u % RING], y[u % RING]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    // the last rows of the matrix, fewer than a batch: the last workgroup's first row group, zero-filled
+    if (live && rg == 0 && blockIdx.x == gridDim.x - 1) {
+        for (int64_t r0 = whole * kTnBatch; r0 < n_rows; r0 += 4) {
+            fetch(r0, (int)min((int64_t)q, n_rows - 1 - r0), x[0], y[0]);
+            if (r0 + q >= n_rows) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i) x[0][i] = 0.f;
+#pragma unroll
+                for (int j = 0; j < NT; ++j) y[0][j] = 0.f;
+            }
+            multiply(x[0], y[0]);
+        }
+    }
+    // add the row groups: the upper half's sums go through LDS to the lower half, until one is left
+    for (int n = rg_count; n > 1;) {
+        const int half = (n + 1) / 2;
+        if (rg >= half && rg < n) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    *reinterpret_cast<v4f_bw*>(red + ((((rg - half) * blocks + blk) * MT * NT + i * NT + j) * 64 + lane) * 4) = acc[i][j];
         }
         __syncthreads();
-        if (r0 + kTnRows < r_end) fetch(r0 + kTnRows);
-#pragma unroll 4
-        for (int k = 0; k < kTnRows; k += 4) {
-            const float a = xs[(k + q) * kTnLdx + 16 * wave + i];
+        if (rg + half < n) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, ss[(k + q) * T::LDS_S + 16 * b + i], acc[b], 0, 0, 0);
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[i][j] += *reinterpret_cast<const v4f_bw*>(red + (((rg * blocks + blk) * MT * NT + i * NT + j) * 64 + lane) * 4);
         }
+        __syncthreads();
+        n = half;
     }
-    // partial[span][m][n], m < d_in, n < d; accumulator r of lane (i, q) is output (16*wave + 4q + r, 16b + i)
+    if (rg != 0 || !live) return;
+    // partial[span][m][n]; register r of lane (c, q) in tile (i, j) is the output of X's column 4q + r and S's column c there
     float* __restrict__ out = partial + (int64_t)blockIdx.x * d_in * d;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int n = n0 + 16 * b + i;
-        if (n >= d) continue;
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int m = m0 + 16 * wave + 4 * q + r;
-            if (m < d_in) out[(int64_t)m * d + n] = acc[b][r];
+            const int m = VEC ? m0 + MT * (4 * q + r) + i : m0 + 16 * i + 4 * q + r;
+            if (m >= d_in) continue;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const int n = VEC ? n0 + NT * c + j : n0 + 16 * j + c;
+                if (n < d) out[(int64_t)m * d + n] = acc[i][j][r];
+            }
         }
-    }
 }
 
 // out[e] = sum over spans of partial[span][e], in an order that depends only on the span count: 16
@@ -121,7 +194,7 @@ __global__ __launch_bounds__(256) void k_sum_partials(int32_t n_spans, int64_t c
     const int64_t e = (int64_t)blockIdx.x * 16 + o;
     float s = 0.f;
     if (e < count) {
-#pragma unroll 4
+#pragma unroll 16
         for (int32_t p = j; p < n_spans; p += 16) s += partial[(int64_t)p * count + e];
     }
     red[j][o] = s;
@@ -134,50 +207,34 @@ __global__ __launch_bounds__(256) void k_sum_partials(int32_t n_spans, int64_t c
     }
 }
 
-int32_t gemm_tn_spans(int64_t n_rows, int32_t d_in, int32_t d)
-{
-    const int64_t gy = (d_in + kTnM - 1) / kTnM, gz = (d + 255) / 256;
-    const int64_t stages = (n_rows + kTnRows - 1) / kTnRows;
-    int64_t spans = 1024 / (gy * gz);                                // about four workgroups per CU in all
-    if (spans > stages / 8) spans = stages / 8;                      // at least eight stages per span
-    if (spans < 1) spans = 1;
-    return (int32_t)spans;
-}
+int32_t gemm_tn_spans(int64_t n_rows, int32_t d_in, int32_t d) { return tn_shape(n_rows, d_in, d).spans; }
 
 // dW (d_in x d, pitch lddw) = X^T S for X n_rows x d_in and S n_rows x d; partial holds
 // gemm_tn_spans(n_rows, d_in, d) * d_in * d floats.
 hipError_t launch_gemm_tn(int64_t n_rows, const float* X, int64_t ldx, int32_t d_in, const float* S, int64_t lds_,
                           int32_t d, float* dW, int64_t lddw, float* partial, hipStream_t s)
 {
-    const int32_t spans = gemm_tn_spans(n_rows, d_in, d);
-    const int64_t stages = (n_rows + kTnRows - 1) / kTnRows;
-    const int64_t rows_per_span = (stages + spans - 1) / spans * kTnRows;
-    const dim3 grid((unsigned)spans, (unsigned)((d_in + kTnM - 1) / kTnM), (unsigned)((d + 255) / 256));
-    const int xvec = ldx % 4 == 0 && (uintptr_t)X % 16 == 0, svec = lds_ % 4 == 0 && (uintptr_t)S % 16 == 0;
-    const int blocks16 = (min(d, 256) + 15) / 16;
-#define HC_TN(NB)                                                                                              \
+    const TnShape t = tn_shape(n_rows, d_in, d);
+    const dim3 grid((unsigned)t.spans, (unsigned)t.ny, (unsigned)t.nz), block(64 * t.qm * t.qn * t.rg);
+    const size_t lds_bytes = (size_t)(t.rg / 2) * t.qm * t.qn * 64 * 4 * t.mt * t.nt * sizeof(float);      // 64 KB at most
+    const bool vec = d_in % t.mt == 0 && d % t.nt == 0;
+    hipError_t e = hipSuccess;
+#define HC_TN(MT, NT, V)                                                                                       \
     {                                                                                                          \
-        const size_t lds_bytes = (size_t)(kTnRows * kTnLdx + kTnRows * TnShape<NB>::LDS_S) * sizeof(float);    \
-        static bool attr_set = false;      /* once per process: later calls may run under stream capture */    \
-        if (!attr_set) {                                                                                       \
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_tn<NB>),                  \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);    \
-            if (e != hipSuccess) return e;                                                                     \
-            attr_set = true;                                                                                   \
-        }                                                                                                      \
-        hipLaunchKernelGGL((k_gemm_tn<NB>), grid, dim3(256), lds_bytes, s, n_rows, rows_per_span, X, ldx, d_in, S, lds_, \
-                           d, partial, xvec, svec);                                                            \
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_tn<MT, NT, V>), \
+            hipFuncAttributeMaxDynamicSharedMemorySize, kTnWaves / 2 * 64 * 4 * MT * NT * (int)sizeof(float)); \
+        if (attr != hipSuccess) return attr;     /* (once per process: later calls may run under stream capture) */ \
+        hipLaunchKernelGGL((k_gemm_tn<MT, NT, V>), grid, block, lds_bytes, s, n_rows, X, ldx, d_in, S, lds_, d, t.qm, t.qn, t.rg, partial); \
     }
-    if (blocks16 <= 1) HC_TN(1)
-    else if (blocks16 <= 2) HC_TN(2)
-    else if (blocks16 <= 4) HC_TN(4)
-    else if (blocks16 <= 8) HC_TN(8)
-    else HC_TN(16)
+#define HC_TN_V(MT, NT) if (vec) HC_TN(MT, NT, true) else HC_TN(MT, NT, false) break
+#define HC_TN_N(MT) switch (t.nt) { case 1: HC_TN_V(MT, 1); case 2: HC_TN_V(MT, 2); case 3: HC_TN_V(MT, 3); default: HC_TN_V(MT, 4); } break
+    switch (t.mt) { case 1: HC_TN_N(1); case 2: HC_TN_N(2); case 3: HC_TN_N(3); default: HC_TN_N(4); }
+#undef HC_TN_N
+#undef HC_TN_V
 #undef HC_TN
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     const int64_t count = (int64_t)d_in * d;
-    hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)((count + 15) / 16)), dim3(256), 0, s, spans, count, d, partial,
+    hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)((count + 15) / 16)), dim3(256), 0, s, t.spans, count, d, partial,
                        dW, lddw);
     return hipGetLastError();
 }

@@ -60,7 +60,7 @@ void set_error(const char* fmt, ...);
 // Experiment knobs (HCSPMM_TUNE_* environment variables; not part of the ABI), read ONCE per process on first use.
 // A value of -1 means "not set": the built-in choice applies.
 struct Tune {
-    int mid_row, long_row, slice_cols, serial, xcd_chunk, rpg, tiles_per_wave, no_rows16, runs, run_slice, side_nnz, bands;
+    int mid_row, long_row, slice_cols, serial, xcd_chunk, rpg, tiles_per_wave, runs, run_slice, side_nnz, bands;
 };
 const Tune& tune();
 
@@ -270,10 +270,6 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
 bool csr_panels_usable(const SpmmArgs& a);   // the launch has kernels that add to rows of sums for this shape
 hipError_t launch_update_rest(const SpmmArgs& a, int32_t n_rest, const int32_t* rest_rows, const UpdateArgs& upd,
                               hipStream_t s);
-// dense product through the 16-row update kernel (narrow W), see spmm_csr_kernels.hip
-bool gemm_rows16_usable(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx);
-hipError_t launch_gemm_rows16(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
-                              float* T, int64_t ldt, int relu, hipStream_t s, int32_t t_dtype = HCSPMM_F32);
 hipError_t launch_reduce_partials(const SpmmArgs& a, int32_t n_multi, const MultiRow* multi, const float* partial,
                                   hipStream_t s);
 hipError_t launch_mfma_small(const SpmmArgs& a, int32_t n_list, const WinDesc* desc, const int32_t* wcols,

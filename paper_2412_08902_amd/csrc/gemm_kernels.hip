@@ -1,240 +1,317 @@
-// Dense update T = act(X W) (Eq. 2; the activation is optional) in true fp32 on the MFMA units: v_mfma_f32_32x32x2_f32.
+// Dense update T = act(X W) (Eq. 2; the activation is optional) in true fp32 on the MFMA units: v_mfma_f32_16x16x4_f32.
 //
-// Operand layout per lane l: A: row l%32, k = l/32.  B: k = l/32, column l%32.
-// D (32x32, 16 registers): column l%32, row 8*(v/4) + 4*(l/32) + v%4 for register v.
+// Operand layout per lane l = (c = l%16, q = l/16): A: row c, k = q.  B: k = q, column c.  D: rows 4q .. 4q+3, column c.
+// The contraction may be taken in any order, so in step t of a unit of 16 a lane's k is 4q + t: its four A values are one
+// 16-byte piece of its X row, read from memory straight into registers (a wave's 16 rows are nobody else's; LDS would only
+// add a trip), at whatever 4-byte aligned place the row starts.  Column tiles come in groups of up to four, tile j of a
+// group of R holding the columns base + R*c + j, so that a lane's B values are one vector of a W row in LDS and its
+// results leave as one vector per row.
 //
-// Workgroup tile 128 x 128 with K advanced 32 at a time; four waves in a 2 x 2 grid, each computing a 64 x 64
-// sub-tile as 2 x 2 MFMA tiles.  The X slab sits in LDS row-major (a lane's two k values of two consecutive MFMA
-// steps are one 8-byte read), the W slab k-major, and a wave's two column tiles interleave (tile j holds the columns
-// base + 2*(l%32) + j) so that its two B values are one 8-byte read as well and the results go back as column pairs.
-// The global loads of the next slab are issued before the MFMAs of the current one (register double buffering).
-//
-// X rows that are only 8-byte aligned (ldx even but not a multiple of 4: 602 features, say) are still read with 16-byte
-// loads: a row's slab is fetched as the nine aligned 16-byte pieces that cover it, and the 8-byte halves of those
-// pieces that belong to the slab are stored where they belong (two floats to the left when the row starts in the
-// middle of a piece), so the LDS image and its readers are the same as for aligned rows.
-//
-// The row tiles of a launch come in two heights.  As many 128-row tiles as fill whole rounds of the chip's 256 CUs,
-// and the rows that are left as 32-row tiles (four waves side by side, one MFMA tile each): the last, partly filled
-// round of tall tiles would otherwise leave most CUs idle for a whole tile's duration.
-#include <cstdlib>
+// A workgroup has four waves of 16 rows each and 16*NT columns (NT <= 8), twice that with 512 threads (two column groups
+// that read the same X rows at the same time).  K is advanced 32 at a time through two W slabs in LDS with one barrier per
+// slab: the next slab's X pieces and W values are requested before the current one is multiplied.  The product is bound by
+// the matrix units where K and N are a hundred or more and by reading X and writing T below; both need memory and matrix
+// work of different workgroups to overlap all the time, hence the small tiles, at least four waves per SIMD: tiles of 128
+// rows, staged through LDS with two barriers per slab, ran through their load, multiply and store phases in step
+// (169,343 x 128 x 128: 75 us, the phases one after the other; now 70 us; 232,965 x 602 x 128: 362 -> 335 us, against 253 us for
+// the products alone at the 142 TFLOP/s the matrix units hold over such times).  X rows and W need no alignment beyond four
+// bytes and no width pays for padding beyond its last 16 columns (200,000 x 300 x 33: 168 -> 74 us).
+#include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 
 namespace hcspmm {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f_gemm __attribute__((ext_vector_type(4)));
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <int N> struct __attribute__((packed, aligned(4))) f32_any { float v[N]; };
 
-constexpr int BM = 128, BN = 128, BK = 32, BM_TAIL = 32;
-constexpr int LDA_S = BK + 2;     // A image: rows 136 bytes apart, so the 8-byte reads of 16 consecutive rows fall into 16 different bank pairs
-constexpr int LDB_S = BN + 4;     // B image: k rows 528 bytes apart (16-byte aligned for the vector stores)
+constexpr int kGemmWaves = 4, kGemmRows = 16 * kGemmWaves, kGemmBK = 32;
 
-// One row tile of height H (128 or 32).
-//   XV  4: X and ldx allow aligned 16-byte loads; 1: 4-byte loads; 2: rows are 8-byte aligned, read as the aligned
-//       16-byte pieces covering them (xoff = floats between the 16-byte boundary below X and X: 0 or 2)
-//   WV  floats per global load of W (4 or 1)
-// Rows past M re-read row M-1 and columns past N read column N-WV: what they produce is never stored.  Only k >= K is
-// zeroed (in the last slab), in both operands.
-template <int XV, int WV, int H>
-__device__ inline void gemm_tile(int64_t m0, int n0, int64_t M, int32_t K, int32_t N, const float* __restrict__ X,
-                                 int64_t ldx, const float* __restrict__ Wm, int64_t ldw, float* __restrict__ T,
-                                 int64_t ldt, int32_t t_dtype, int relu, int pair_ok, int xoff, float* __restrict__ As,
-                                 float* __restrict__ Bs)
+// Stores a wave's 16 rows from m0 on and 16*NT columns from n0 on.  tvec: T takes vector stores of four (or of the two columns
+// of a group of two); N is a multiple of four then.
+template <int NT>
+__device__ __forceinline__ void store_tile(const v4f_gemm (&acc)[NT], int64_t m0, int n0, int64_t M, int32_t N, float* __restrict__ T,
+                                           int64_t ldt, int32_t t_dtype, int relu, int tvec, int c, int q)
 {
-    constexpr bool SHIFT = XV == 2;
-    constexpr int MI = H == BM ? 2 : 1, NJ = H == BM ? 2 : 1;        // MFMA tiles per wave
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = H == BM ? (wave >> 1) * 64 : 0;
-    const int wn = H == BM ? (wave & 1) * 64 : wave * 32;
-
-    // global -> register staging maps.  X slab: H rows x 32 k, thread -> (row, k piece); W slab: 32 k x 128 columns
-    constexpr int XL = SHIFT ? 4 : XV;            // floats per load
-    constexpr int LPRW = BK / XL;                 // loads per row (the shifted form adds one piece per row, see below)
-    constexpr int ROWS_PER_IT = 256 / LPRW;
-    constexpr int A_ITERS = H / ROWS_PER_IT;
-    static_assert(A_ITERS >= 1, "a 32-row slab is at least one load per thread");
-    constexpr int A_REGS = A_ITERS + (SHIFT ? 1 : 0);
-    const int a_row = tid / LPRW, a_k = (tid % LPRW) * XL;
-    constexpr int B_TPR = BN / WV;                // threads per k row
-    constexpr int B_KPI = 256 / B_TPR;            // k rows per iteration
-    constexpr int B_ITERS = BK / B_KPI;
-    const int b_k = tid / B_TPR, b_col = (tid % B_TPR) * WV;
-    const int b_cc = min(n0 + b_col, N - WV);     // (N >= WV: WV = 4 needs N % 4 == 0)
-
-    float a_reg[A_REGS][XL];
-    float b_reg[B_ITERS][WV];
-
-    // Loads only: nothing here touches a loaded value, so the requests stay in flight behind the MFMAs of the
-    // current slab.  k >= K is zeroed when the slab goes to LDS.
-    const float* __restrict__ Xa = X - xoff;                        // (xoff = 0 unless SHIFT)
-    const int64_t last = xoff + (M - 1) * ldx + K - 1;              // last float of the matrix, from Xa
-    // piece c of tile row r: the four floats at the 16-byte boundary at or below the row's k0, plus 4c.  The guarded
-    // form is for pieces that may stick out of the matrix (in front of its first float or behind its last one).
-    auto piece = [&](int k0, int r, int c, bool guard, float (&dst)[4]) {
-        const int64_t e = min(m0 + r, M - 1) * ldx + xoff;          // the row's first float, from Xa
-        const int64_t b = ((e + k0) & ~(int64_t)3) + 4 * c;
-        if (!guard) {
-            const float4 v = *reinterpret_cast<const float4*>(Xa + b);
-            dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-        } else {
+    constexpr int G4 = NT / 4, R = NT % 4;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)      // (volatile: keeps these rare loads apart from the 16-byte one above)
-                dst[i] = *static_cast<const volatile float*>(Xa + min(max(b + i, (int64_t)xoff), last));
-        }
-    };
-    constexpr int NP = LPRW + (SHIFT ? 1 : 0);                      // pieces per row
-    const int64_t e_max = min(m0 + H - 1, M - 1) * ldx + xoff;      // first float of the tile's last row
-    auto load_slab = [&](int k0) {
-        if constexpr (XL == 4) {
-            // uniform: can a piece of this tile and slab reach past the matrix?  (the tile that holds the last row, in
-            // its last slabs; the first tile's first slab when X starts off a 16-byte boundary)
-            const bool guard = e_max + k0 + 4 * NP + 3 > last || (xoff > 0 && m0 == 0 && k0 == 0);
+    for (int r = 0; r < 4; ++r) {
+        const int64_t row = m0 + 4 * q + r;
+        if (row >= M) continue;
 #pragma unroll
-            for (int it = 0; it < A_ITERS; ++it) piece(k0, a_row + it * ROWS_PER_IT, tid % LPRW, guard, a_reg[it]);
-            if constexpr (SHIFT) {
-                if (tid < H) piece(k0, tid, LPRW, guard, a_reg[A_ITERS]);
-            }
-        } else {
-#pragma unroll
-            for (int it = 0; it < A_ITERS; ++it)
-                a_reg[it][0] = X[min(m0 + a_row + it * ROWS_PER_IT, M - 1) * ldx + min(k0 + a_k, K - 1)];
-        }
-#pragma unroll
-        for (int it = 0; it < B_ITERS; ++it) {
-            const float* __restrict__ p = Wm + (int64_t)min(k0 + b_k + it * B_KPI, K - 1) * ldw + b_cc;
-            if constexpr (WV == 4) {
-                const float4 v = *reinterpret_cast<const float4*>(p);
-                b_reg[it][0] = v.x; b_reg[it][1] = v.y; b_reg[it][2] = v.z; b_reg[it][3] = v.w;
+        for (int g = 0; g < G4; ++g) {
+            const int col = n0 + 64 * g + 4 * c;
+            const float y[4] = {acc[4 * g][r], acc[4 * g + 1][r], acc[4 * g + 2][r], acc[4 * g + 3][r]};
+            if (tvec) {
+                if (col < N) out_store<4>(T, t_dtype, row * ldt + col, y, relu);
             } else {
-                b_reg[it][0] = *p;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float one[1] = {y[j]};
+                    if (col + j < N) out_store<1>(T, t_dtype, row * ldt + col + j, one, relu);
+                }
             }
         }
-    };
-    // half h of piece c holds the row's slab floats 4c + 2h - shift .. + 1 (shift = 0 or 2; always 0 for aligned rows):
-    // the halves in front of the slab and behind it are dropped
-    auto put = [&](int k0, bool full, int r, int c, float (&src)[4]) {
-        const int shift = SHIFT ? (int)((min(m0 + r, M - 1) * ldx + xoff) & 3) : 0;
-        const int t = 4 * c - shift;
-        if (!full) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) src[i] = k0 + t + i < K ? src[i] : 0.f;
-        }
-        float* __restrict__ q = &As[r * LDA_S + t];
-        if (t >= 0 && t < BK) *reinterpret_cast<float2*>(q) = make_float2(src[0], src[1]);
-        if (t + 2 < BK) *reinterpret_cast<float2*>(q + 2) = make_float2(src[2], src[3]);
-    };
-    auto store_slab = [&](int k0) {
-        const bool full = k0 + BK <= K;           // uniform
-        if constexpr (XL == 4) {
-#pragma unroll
-            for (int it = 0; it < A_ITERS; ++it) put(k0, full, a_row + it * ROWS_PER_IT, tid % LPRW, a_reg[it]);
-            if constexpr (SHIFT) {
-                if (tid < H) put(k0, full, tid, LPRW, a_reg[A_ITERS]);
-            }
+        const int col = n0 + 64 * G4 + R * c;
+        if (R == 2 && tvec) {
+            const float y[2] = {acc[R > 0 ? 4 * G4 : 0][r], acc[R > 1 ? 4 * G4 + 1 : 0][r]};
+            if (col < N) out_store<2>(T, t_dtype, row * ldt + col, y, relu);
         } else {
 #pragma unroll
-            for (int it = 0; it < A_ITERS; ++it)
-                As[(a_row + it * ROWS_PER_IT) * LDA_S + a_k] = (full || k0 + a_k < K) ? a_reg[it][0] : 0.f;
-        }
-#pragma unroll
-        for (int it = 0; it < B_ITERS; ++it) {
-            const bool live = full || k0 + b_k + it * B_KPI < K;
-            float* __restrict__ q = &Bs[(b_k + it * B_KPI) * LDB_S + b_col];
-            if constexpr (WV == 4)
-                *reinterpret_cast<float4*>(q) = live ? make_float4(b_reg[it][0], b_reg[it][1], b_reg[it][2], b_reg[it][3])
-                                                     : make_float4(0.f, 0.f, 0.f, 0.f);
-            else
-                *q = live ? b_reg[it][0] : 0.f;
-        }
-    };
-
-    v16f acc[MI][NJ];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    const int li = lane & 31, lk = lane >> 5;
-    if (K > 0) load_slab(0);                 // (K = 0: the product is all zeros)
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        __syncthreads();                     // previous slab fully consumed
-        store_slab(k0);
-        __syncthreads();
-        if (k0 + BK < K) load_slab(k0 + BK);
-        // four k per step: the lane's A pair is k = 4s + 2*lk + {0, 1}; the first MFMA takes k = 4s + 2*lk from both
-        // operands, the second k = 4s + 2*lk + 1
-#pragma unroll
-        for (int s = 0; s < BK / 4; ++s) {
-            float2 av[MI];
-#pragma unroll
-            for (int i = 0; i < MI; ++i) av[i] = *reinterpret_cast<const float2*>(&As[(wm + 32 * i + li) * LDA_S + 4 * s + 2 * lk]);
-            float b0[NJ], b1[NJ];
-            if constexpr (NJ == 2) {
-                const float2 u0 = *reinterpret_cast<const float2*>(&Bs[(4 * s + 2 * lk) * LDB_S + wn + 2 * li]);
-                const float2 u1 = *reinterpret_cast<const float2*>(&Bs[(4 * s + 2 * lk + 1) * LDB_S + wn + 2 * li]);
-                b0[0] = u0.x; b0[1] = u0.y; b1[0] = u1.x; b1[1] = u1.y;
-            } else {
-                b0[0] = Bs[(4 * s + 2 * lk) * LDB_S + wn + li];
-                b1[0] = Bs[(4 * s + 2 * lk + 1) * LDB_S + wn + li];
+            for (int j = 0; j < R; ++j) {
+                const float one[1] = {acc[4 * G4 + j][r]};
+                if (col + j < N) out_store<1>(T, t_dtype, row * ldt + col + j, one, relu);
             }
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].x, b0[j], acc[i][j], 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i].y, b1[j], acc[i][j], 0, 0, 0);
         }
     }
-
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t row = m0 + wm + 32 * i + 8 * (v >> 2) + 4 * lk + (v & 3);
-            if (row >= M) continue;
-            if constexpr (NJ == 2) {
-                const int col = n0 + wn + 2 * li;
-                if (col >= N) continue;
-                if (pair_ok) {                   // N is even then: col + 1 < N
-                    const float y[2] = {acc[i][0][v], acc[i][1][v]};
-                    out_store<2>(T, t_dtype, row * ldt + col, y, relu);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        if (col + j >= N) continue;
-                        const float y[1] = {acc[i][j][v]};
-                        out_store<1>(T, t_dtype, row * ldt + col + j, y, relu);
-                    }
-                }
-            } else {
-                const int col = n0 + wn + li;
-                if (col >= N) continue;
-                const float y[1] = {acc[i][0][v]};
-                out_store<1>(T, t_dtype, row * ldt + col, y, relu);
-            }
-        }
 }
 
-// Row tiles 0 .. n_tall-1 are 128 rows tall; the rows from n_tall*128 on are cut into 32-row tiles.
-template <int XV, int WV>
-__global__ __launch_bounds__(256) void k_gemm_f32(int64_t M, int32_t K, int32_t N, const float* __restrict__ X,
-                                                  int64_t ldx, const float* __restrict__ Wm, int64_t ldw,
-                                                  float* __restrict__ T, int64_t ldt, int32_t t_dtype, int relu,
-                                                  int pair_ok, int xoff, int64_t n_tall)
+// WV: floats per global load of W (4: W's rows are 16-byte aligned and N is a multiple of 4).
+// Rows past M re-read row M-1 and columns past N read column N-WV: what they produce is never stored.  k >= K is zero in both
+// operands.
+template <int NT, int WV>
+__global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k_gemm_f32(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
+                                                     const float* __restrict__ Wm, int64_t ldw, float* __restrict__ T, int64_t ldt,
+                                                     int32_t t_dtype, int relu, int tvec)
 {
-    __shared__ __attribute__((aligned(16))) float As[BM * LDA_S];
-    __shared__ __attribute__((aligned(16))) float Bs[BK * LDB_S];
-    const int n0 = blockIdx.y * BN;
-    const int64_t bx = blockIdx.x;
-    if (bx < n_tall)
-        gemm_tile<XV, WV, BM>(bx * BM, n0, M, K, N, X, ldx, Wm, ldw, T, ldt, t_dtype, relu, pair_ok, xoff, As, Bs);
-    else
-        gemm_tile<XV, WV, BM_TAIL>(n_tall * BM + (bx - n_tall) * BM_TAIL, n0, M, K, N, X, ldx, Wm, ldw, T, ldt, t_dtype,
-                                   relu, pair_ok, xoff, As, Bs);
+    constexpr int COLS = 16 * NT, SLAB = kGemmBK * COLS;
+    constexpr int G4 = NT / 4, R = NT % 4, READS = G4 + (R ? 1 : 0);   // groups of four tiles, tiles of the last group
+    constexpr int kThreads = 64 * kGemmWaves;                       // of a column group
+    using Offset = std::conditional_t<NT == 1, int64_t, uint32_t>;
+    constexpr int ITERS = (SLAB / WV + kThreads - 1) / kThreads;                  // loads of W per thread and slab
+    extern __shared__ __attribute__((aligned(16))) float smem[];    // two slabs per column group
+    const int tid = threadIdx.x % kThreads, wave = tid >> 6, lane = tid & 63;
+    const int cw = threadIdx.x / kThreads, n0 = (int)(blockIdx.y * (blockDim.x / kThreads) + cw) * COLS;
+    float* __restrict__ bs = smem + cw * 2 * SLAB;
+    const int c = lane & 15, q = lane >> 4;
+    const int64_t m0 = (int64_t)blockIdx.x * kGemmRows + wave * 16;
+    const float* __restrict__ xp = X + min(m0 + c, M - 1) * ldx + 4 * q;
+
+    // this thread's pieces of a W slab: (k row, column) inside the slab, WV floats each
+    auto at = [&](int i, int& k, int& col) { const int idx = (tid + kThreads * i) * WV; k = idx / COLS; col = idx % COLS; };
+    Offset wo[ITERS];                                               // (a 64-bit one for pitches of 2^25 floats and more: NT = 1)
+#pragma unroll
+    for (int i = 0; i < ITERS; ++i) {
+        int k, col;
+        at(i, k, col);
+        wo[i] = ((Offset)k * (Offset)ldw + (Offset)min(n0 + col, N - WV)) * 4;
+    }
+    auto w_at = [&](int k0, int i) { return reinterpret_cast<const float*>(reinterpret_cast<const char*>(Wm + (int64_t)k0 * ldw) + wo[i]); };
+    float b_next[ITERS][WV];
+    auto request_x = [&](int k0, float4 (&a)[2]) {                  // a whole slab
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const f4_any v = *reinterpret_cast<const f4_any*>(xp + k0 + 16 * u);
+            a[u] = make_float4(v.x, v.y, v.z, v.w);
+        }
+    };
+    auto request_w = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < ITERS; ++i) {
+            if (SLAB / WV % kThreads != 0 && (tid + kThreads * i) * WV >= SLAB) break;
+            const float* __restrict__ p = w_at(k0, i);
+            if constexpr (WV == 4) {
+                const float4 v = *reinterpret_cast<const float4*>(p);
+                b_next[i][0] = v.x; b_next[i][1] = v.y; b_next[i][2] = v.z; b_next[i][3] = v.w;
+            } else {
+                b_next[i][0] = *p;
+            }
+        }
+    };
+    auto stage = [&](float* __restrict__ dst) {
+#pragma unroll
+        for (int i = 0; i < ITERS; ++i) {
+            const int idx = (tid + kThreads * i) * WV;
+            if (SLAB / WV % kThreads != 0 && idx >= SLAB) break;
+            if constexpr (WV == 4) *reinterpret_cast<float4*>(dst + idx) = make_float4(b_next[i][0], b_next[i][1], b_next[i][2], b_next[i][3]);
+            else dst[idx] = b_next[i][0];
+        }
+    };
+    v4f_gemm acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = (v4f_gemm){0.f, 0.f, 0.f, 0.f};
+    // UNITS times 16 k of the slab at b: the W values of a step are read while the products of the step before run
+    auto multiply = [&](auto units, const float* __restrict__ b, const float4 (&a)[2]) {
+        constexpr int STEPS = decltype(units)::value * 4;
+        const float av[8] = {a[0].x, a[0].y, a[0].z, a[0].w, a[1].x, a[1].y, a[1].z, a[1].w};
+        float w[2][NT];
+        auto read = [&](int t, float (&o)[NT]) {
+            const float* __restrict__ row = b + (t / 4 * 16 + t % 4) * COLS;
+#pragma unroll
+            for (int g = 0; g < G4; ++g) {
+                const float4 v = *reinterpret_cast<const float4*>(row + 64 * g + 4 * c);
+                o[4 * g] = v.x; o[4 * g + 1] = v.y; o[4 * g + 2] = v.z; o[4 * g + 3] = v.w;
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) o[4 * G4 + j] = row[64 * G4 + R * c + j];
+        };
+        read(0, w[0]);
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+            if (t + 1 < STEPS) read(t + 1, w[(t + 1) & 1]);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t], w[t & 1][j], acc[j], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);      // in this order: reads of step 0, then a step's reads before
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {                           // the products of the one before it
+            if (t + 1 < STEPS) __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+            __builtin_amdgcn_sched_group_barrier(0x8, NT, 0);
+        }
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    const int whole = K / kGemmBK * kGemmBK;
+    int buf = 0;
+    if (whole > 0) {
+        float4 even[2], odd[2];
+        // X pieces are asked for two slabs ahead, behind the W values of the next slab: the wait for those leaves them in
+        // flight.  The requests past the end repeat the last slab (branches around them would cost waits at their joins).
+        const int last = whole - kGemmBK;
+        auto slab = [&](int k0, float4 (&x)[2]) {
+            const float4 a[2] = {x[0], x[1]};
+            request_w(min(k0 + kGemmBK, last));
+            request_x(min(k0 + 2 * kGemmBK, last), x);
+            __builtin_amdgcn_sched_barrier(0);                      // (the compiler would move the requests to where they are used)
+            multiply(Two{}, bs + buf * SLAB + 4 * q * COLS, a);
+            __builtin_amdgcn_sched_barrier(0);
+            buf ^= 1;
+            stage(bs + buf * SLAB);
+            __syncthreads();                                        // the slab is in place, and nobody reads the one before
+        };
+        request_w(0);
+        request_x(0, even);
+        request_x(min(kGemmBK, last), odd);
+        stage(bs);
+        __syncthreads();
+        for (int k0 = 0;;) {
+            slab(k0, even);
+            if ((k0 += kGemmBK) > last) break;
+            slab(k0, odd);
+            if ((k0 += kGemmBK) > last) break;
+        }
+    }
+    if (whole < K) {                                                // the rest of K, zero-filled to one or two units
+        float4 a[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int k = whole + 16 * u + 4 * q;
+            const float* __restrict__ p = xp + whole + 16 * u;
+            a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k + 3 < K) {
+                const f4_any v = *reinterpret_cast<const f4_any*>(p);
+                a[u] = make_float4(v.x, v.y, v.z, v.w);
+            } else if (k < K) {
+                a[u].x = p[0];
+                if (k + 1 < K) a[u].y = p[1];
+                if (k + 2 < K) a[u].z = p[2];
+            }
+        }
+        float* __restrict__ dst = bs + buf * SLAB;
+#pragma unroll
+        for (int i = 0; i < ITERS; ++i) {
+            int k, col;
+            at(i, k, col);
+            if (k >= kGemmBK) break;
+            const float* __restrict__ p = w_at(whole, i);
+#pragma unroll
+            for (int j = 0; j < WV; ++j) dst[k * COLS + col + j] = whole + k < K ? p[j] : 0.f;
+        }
+        __syncthreads();
+        const float* __restrict__ b = dst + 4 * q * COLS;
+        if (whole + 16 < K) multiply(Two{}, b, a);
+        else multiply(One{}, b, a);
+    }
+    store_tile<NT>(acc, m0, n0, M, N, T, ldt, t_dtype, relu, tvec, c, q);
+}
+
+// The product with W kept in registers (K <= 128 and a multiple of four): a wave holds the 16*NT columns of W that are its
+// share -- K/4 * NT values per lane, 128 at most -- and walks 16-row tiles of X, whose pieces are asked for one tile ahead,
+// each as soon as the one before it in the ring of K/16 is used up.  No barrier inside the walk, waves on their own, so
+// loads, products and stores of different waves overlap all the time.  The waves of a workgroup are `groups` column groups
+// times some row streams; those that hold different columns of the same rows share X through L1.  W comes through LDS once
+// per workgroup, every workgroup starting at another row of it: waves that each read their columns from memory cost 10 us more
+// at 17,000 x 128 x 128 (the CUs of an XCD asking one L2 channel for the same lines at the same time).
+template <int K16, int NT>
+__global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
+                                                         const float* __restrict__ Wm, int64_t ldw, float* __restrict__ T, int64_t ldt,
+                                                         int32_t t_dtype, int relu, int tvec, int wvec, int32_t groups)
+{
+    extern __shared__ __attribute__((aligned(16))) float smem[];    // 16*K16 rows of W, groups * 16*NT columns each
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
+    const int cols = groups * 16 * NT, first = (int)blockIdx.y * cols;
+    const int per_block = 8 / groups;                               // row streams of a workgroup (groups is 1, 2 or 4)
+    const int64_t stream = (int64_t)blockIdx.x * per_block + wave / groups, streams = (int64_t)gridDim.x * per_block;
+    const int n0 = first + wave % groups * 16 * NT;
+    const int64_t n_tiles = (M + 15) / 16;
+    float4 x[K16];
+    auto request = [&](int64_t tile, int u) {
+        const int k = 16 * u + 4 * q;
+        const float* __restrict__ p = X + min(tile * 16 + c, M - 1) * ldx;
+        const f4_any v = *reinterpret_cast<const f4_any*>(p + (u == K16 - 1 && k >= K ? 0 : k));    // (zeroed when it is used)
+        x[u] = make_float4(v.x, v.y, v.z, v.w);
+    };
+#pragma unroll
+    for (int u = 0; u < K16; ++u) request(min(stream, n_tiles - 1), u);
+    {   // thread -> (row, four columns); rows past K and columns past N are zeros
+        const int per_row = cols / 4, step = 512 / per_row, r0 = (int)threadIdx.x / per_row, col = (int)threadIdx.x % per_row * 4;
+        const int turn = (int)((blockIdx.x * 37u) % (16 * K16));
+        auto put = [&](auto vec) {
+            for (int r = r0; r < 16 * K16 + r0; r += 4 * step) {
+                float4 v[4];
+                int at[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int rr = r + b * step;
+                    at[b] = rr + turn < 16 * K16 ? rr + turn : rr + turn - 16 * K16;        // (past the end: another row's)
+                    const float* __restrict__ p = Wm + (int64_t)min(at[b], K - 1) * ldw;
+                    if constexpr (decltype(vec)::value) {
+                        v[b] = *reinterpret_cast<const float4*>(p + min(first + col, N - 4));
+                    } else {
+                        v[b].x = p[min(first + col, N - 1)];
+                        v[b].y = p[min(first + col + 1, N - 1)];
+                        v[b].z = p[min(first + col + 2, N - 1)];
+                        v[b].w = p[min(first + col + 3, N - 1)];
+                    }
+                    if (at[b] >= K) v[b] = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (r + b * step < 16 * K16 && r0 < step) *reinterpret_cast<float4*>(smem + at[b] * cols + col) = v[b];
+            }
+        };
+        if (wvec) put(std::true_type{});
+        else put(std::false_type{});
+    }
+    __syncthreads();
+    float w[K16 * 4][NT];
+#pragma unroll
+    for (int k4 = 0; k4 < K16 * 4; ++k4) {
+        const f32_any<NT> v = *reinterpret_cast<const f32_any<NT>*>(smem + (k4 / 4 * 16 + 4 * q + k4 % 4) * cols + n0 - first + NT * c);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) w[k4][j] = v.v[j];
+    }
+    const int64_t last = n_tiles - 1;
+    for (int64_t tile = n0 < N ? stream : n_tiles; tile < n_tiles; tile += streams) {
+        v4f_gemm acc[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[j] = (v4f_gemm){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < K16; ++u) {
+            float a[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+            if (u == K16 - 1 && 16 * u + 4 * q >= K) a[0] = a[1] = a[2] = a[3] = 0.f;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], w[4 * u + t][j], acc[j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            request(min(tile + streams, last), u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        store_tile<NT>(acc, tile * 16, n0, M, N, T, ldt, t_dtype, relu, tvec, c, q);
+    }
 }
 
 hipError_t launch_gemm_f32(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
@@ -248,25 +325,44 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
 {
     if (m <= 0 || n <= 0) return hipSuccess;
     if (t_dtype != HCSPMM_F32 && t_dtype != HCSPMM_BF16 && t_dtype != HCSPMM_F16) return hipErrorInvalidValue;
-    if (gemm_rows16_usable(m, k, n, X, ldx) && !tune().no_rows16)
-        return launch_gemm_rows16(m, k, n, X, ldx, W, ldw, static_cast<float*>(T), ldt, relu, s, t_dtype);
-    // tall tiles for whole rounds of the 256 CUs, 32-row tiles for what is left
-    const int64_t tall_all = m / BM;
-    const int64_t n_tall = tall_all / 256 * 256;
-    const int64_t rest = m - n_tall * BM;
-    const int64_t n_tail = (rest + BM_TAIL - 1) / BM_TAIL;
-    dim3 grid((unsigned)(n_tall + n_tail), (unsigned)((n + BN - 1) / BN));
-    const uintptr_t px = (uintptr_t)X, pw = (uintptr_t)W, pt = (uintptr_t)T;
-    // 4: aligned 16-byte loads; 2: rows 8-byte aligned, read through the aligned pieces that cover them; 1: the rest
-    const int xv = (ldx % 4 == 0 && px % 16 == 0) ? 4 : ((ldx % 2 == 0 && px % 8 == 0 && k >= BK) ? 2 : 1);
-    const int xoff = (int)((px % 16) / 4);
-    const int wv = (n % 4 == 0 && ldw % 4 == 0 && pw % 16 == 0) ? 4 : 1;
-    const size_t es = t_dtype == HCSPMM_F32 ? 4 : 2;
-    const int pair_ok = (n % 2 == 0 && ldt % 2 == 0 && pt % (2 * es) == 0) ? 1 : 0;
+    // W in registers where it is small and the product streams: 2.4 M x 64 x 32: 199 -> 170 us, 2.4 M x 16 x 16: 109 -> 58 us,
+    // 169,343 x 128 x 64: 41 -> 37 us.  Wider products are bound by the matrix units and level or behind (400,000 x 128 x 96:
+    // 111 -> 123 us), short ones spend more on bringing all of W in first (20,000 x 128 x 64: 8.0 -> 9.7 us).
+    if (k % 4 == 0 && k > 0 && k <= 128 && (int64_t)k * n <= 8192 && (m >= 65536 || (int64_t)k * n <= 1024)) {
+        // column groups: 1, 2 or 4 per workgroup
+        const int k16 = (k + 15) / 16;
+        const int64_t tiles16 = ((int64_t)n + 15) / 16, ny = (tiles16 + 15) / 16, per_y = (tiles16 + ny - 1) / ny;
+        const int groups = per_y <= 4 ? 1 : per_y <= 8 ? 2 : 4, nt = (int)((per_y + groups - 1) / groups);
+        // two waves per SIMD where W takes most of the registers, up to eight where a wave asks for little at a time
+        const int64_t per_block = 8 / groups, want = ((m + 15) / 16 + per_block - 1) / per_block;
+        const dim3 grid((unsigned)std::min<int64_t>(want, k16 * nt > 16 ? 256 : k16 * nt > 4 ? 512 : 1024), (unsigned)ny);
+        const size_t lds = (size_t)16 * k16 * groups * 16 * nt * sizeof(float);                     // 48 KB at most
+        const int wvec = n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0;
+        const int tvec = n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
+        float* Tf = static_cast<float*>(T);
+#define HC_REG(KK, NT) hipLaunchKernelGGL((k_gemm_f32_reg<KK, NT>), grid, dim3(512), lds, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, tvec, wvec, groups)
+#define HC_REG_NT(KK) case KK: if (nt == 4) HC_REG(KK, 4); else if (nt == 3) HC_REG(KK, 3); else if (nt == 2) HC_REG(KK, 2); else HC_REG(KK, 1); break
+        switch (k16) {
+            HC_REG_NT(1); HC_REG_NT(2); HC_REG_NT(3); HC_REG_NT(4); HC_REG_NT(5); HC_REG_NT(6); HC_REG_NT(7); HC_REG_NT(8);
+        }
+#undef HC_REG_NT
+#undef HC_REG
+        return hipGetLastError();
+    }
+    // columns: as few groups of up to 128 as hold them, equally wide; two groups to a workgroup where they come in pairs
+    const int64_t tiles = ((int64_t)n + 15) / 16, groups = (tiles + 7) / 8;
+    const int nt = (int)((tiles + groups - 1) / groups), pair = groups % 2 == 0 ? 2 : 1;
+    const dim3 grid((unsigned)((m + kGemmRows - 1) / kGemmRows), (unsigned)(groups / pair));
+    const size_t lds = (size_t)pair * 2 * kGemmBK * 16 * nt * sizeof(float);
+    const int wv = (n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0) ? 4 : 1;
+    const int tvec = n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
     float* Tf = static_cast<float*>(T);
-#define HC_LAUNCH_GEMM(V, WVV) hipLaunchKernelGGL((k_gemm_f32<V, WVV>), grid, dim3(256), 0, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, pair_ok, xoff, n_tall)
-    if (wv == 4) { if (xv == 4) HC_LAUNCH_GEMM(4, 4); else if (xv == 2) HC_LAUNCH_GEMM(2, 4); else HC_LAUNCH_GEMM(1, 4); }
-    else { if (xv == 4) HC_LAUNCH_GEMM(4, 1); else if (xv == 2) HC_LAUNCH_GEMM(2, 1); else HC_LAUNCH_GEMM(1, 1); }
+#define HC_LAUNCH_GEMM(NT, WV) hipLaunchKernelGGL((k_gemm_f32<NT, WV>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, tvec)
+#define HC_GEMM_NT(NT) case NT: if (wv == 4) HC_LAUNCH_GEMM(NT, 4); else HC_LAUNCH_GEMM(NT, 1); break
+    switch (nt) {
+        HC_GEMM_NT(1); HC_GEMM_NT(2); HC_GEMM_NT(3); HC_GEMM_NT(4); HC_GEMM_NT(5); HC_GEMM_NT(6); HC_GEMM_NT(7); HC_GEMM_NT(8);
+    }
+#undef HC_GEMM_NT
 #undef HC_LAUNCH_GEMM
     return hipGetLastError();
 }

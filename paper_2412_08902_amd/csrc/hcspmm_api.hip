@@ -104,7 +104,7 @@ const Tune& tune()
 {
     static const Tune t = {env_int("HCSPMM_TUNE_MID_ROW"), env_int("HCSPMM_TUNE_LONG_ROW"), env_int("HCSPMM_TUNE_SLICE_COLS"),
                            getenv("HCSPMM_TUNE_SERIAL") ? 1 : 0, env_int("HCSPMM_TUNE_XCD_CHUNK"), env_int("HCSPMM_TUNE_RPG"),
-                           env_int("HCSPMM_TUNE_TILES_PER_WAVE"), getenv("HCSPMM_TUNE_NO_ROWS16") ? 1 : 0,
+                           env_int("HCSPMM_TUNE_TILES_PER_WAVE"),
                            getenv("HCSPMM_TUNE_RUNS") ? 1 : 0, env_int("HCSPMM_TUNE_RUN_SLICE"), env_int("HCSPMM_TUNE_SIDE_NNZ"), env_int("HCSPMM_TUNE_BANDS")};
     return t;
 }
@@ -1387,7 +1387,7 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
 // (aggregated width up to 32 or of 256, wide W, small graphs) the fused kernels are level or ahead.
 static bool split_update_faster(int64_t n_rows, int32_t agg_width, int32_t out_width, const float* Z)
 {
-    return n_rows >= 32768 && agg_width > 32 && gemm_rows16_usable(n_rows, agg_width, out_width, Z, agg_width);
+    return n_rows >= 32768 && agg_width > 32 && agg_width % 16 == 0 && agg_width <= 128 && out_width <= 64;
 }
 
 size_t hcspmm_aggregate_update_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)

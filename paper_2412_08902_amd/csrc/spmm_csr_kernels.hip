@@ -542,7 +542,7 @@ __global__ __launch_bounds__(256) void k_update_rest(int32_t n_rest, const int32
     // the next tile's rows are requested as soon as the current tile is parked in LDS, so they arrive during its MFMAs.
     auto request = [&](int64_t tile, int32_t* __restrict__ rows16) {
         const int64_t i0 = tile * 16;
-        if (lane < 16) rows16[lane] = i0 + lane < n_rest ? (rest_rows ? rest_rows[i0 + lane] : (int32_t)(i0 + lane)) : -1;
+        if (lane < 16) rows16[lane] = i0 + lane < n_rest ? rest_rows[i0 + lane] : -1;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
@@ -753,23 +753,6 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
 #undef HC_LAUNCH_PANEL
 #undef HC_LAUNCH_CSR
     return hipGetLastError();
-}
-
-// The same kernel as a dense product for narrow outputs: T = act(X W) for X m x k (k a multiple of 16 up to 128, rows
-// 16-byte aligned), every wave taking 16 consecutive rows.  A 128-column GEMM tile would spend most of its matrix work
-// on padding when W has 64 columns or fewer; here the product streams X once and W stays in L1/L2.
-bool gemm_rows16_usable(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx)
-{
-    return m < ((int64_t)1 << 31) && k % 16 == 0 && k >= 16 && k <= 128 && n <= 64 && ldx % 4 == 0 && (uintptr_t)X % 16 == 0;
-}
-
-hipError_t launch_gemm_rows16(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
-                              float* T, int64_t ldt, int relu, hipStream_t s, int32_t t_dtype)
-{
-    SpmmArgs a{};
-    a.n_rows = (int32_t)m; a.d = k; a.Y = const_cast<float*>(X); a.ldy = ldx;      // the kernel only reads these rows
-    const UpdateArgs u{W, ldw, n, T, ldt, relu ? 1 : 0, 0, nullptr, 0, t_dtype};
-    return launch_update_rest(a, (int32_t)m, nullptr, u, s);
 }
 
 hipError_t launch_update_rest(const SpmmArgs& a, int32_t n_rest, const int32_t* rest_rows, const UpdateArgs& upd,
