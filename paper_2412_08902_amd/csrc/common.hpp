@@ -88,7 +88,7 @@ hipError_t exclusive_scan_multi(const ScanMulti& m, int64_t n, int64_t* totals_d
 struct PrepTotals {
     int64_t total_ncols, nnz_mfma, wide_cols /* columns of wide matrix-path windows */, nnz_long, n_slots;
     int32_t n_mfma, n_mfma_small, n_mfma_mid, n_mfma_big, n_short, n_mid, n_rest, n_multi, n_segs;
-    int32_t unsorted;                     // some row's columns do not ascend (when asked for)
+    int32_t all_scalar;                   // every window is executed on the scalar path (see scattered_rows)
     int32_t n_big_list, n_huge_list;      // windows above kUniqueSmallCap / kCountMidCap non-zeros
     int32_t err;                          // 1 rowptr[0], 2 rowptr[n_rows], 4 decreasing rowptr, 8 column out of range
 };
@@ -103,7 +103,7 @@ struct Prep {
     const int32_t* old_ncols;             // counts carried over for the others
     int32_t features;                     // distinct columns are wanted
     int32_t check_sorted;                 // also find out whether every row's columns ascend (ctl[6] otherwise)
-    int32_t scalar_exec;                  // row tables for a plan that runs every window on the scalar path, if the rows ascend
+    int32_t scalar_exec;                  // row tables for a plan that runs every window on the scalar path, if it is one (scattered_rows)
     int32_t big_takes_1k;                 // set by launch_prep
     int32_t mode;
     long long c0, c1, c2;
@@ -307,9 +307,12 @@ hipError_t launch_gemm_tn(int64_t n_rows, const float* X, int64_t ldx, int32_t d
 hipError_t launch_relu_mask(int64_t n, int32_t d, const float* G, int64_t ldg, const float* Yf, int64_t ldy, float* Gm,
                             int64_t ldo, hipStream_t s);
 hipError_t launch_transpose(int32_t rows, int32_t cols, const float* W, int64_t ldw, float* Wt, hipStream_t s);
-// same product with the output stored as t_dtype (fp32, or bf16 / fp16 rounded from the fp32 accumulators)
+// same product with the output stored as t_dtype (fp32, or bf16 / fp16 rounded from the fp32 accumulators).  done_route,
+// done_cols: rows of windows that the wave-per-window matrix kernel owns (route != 0, at most kMfmaSmallMaxCols columns) are
+// left alone.
 hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
-                               void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s);
+                               void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s,
+                               const uint8_t* done_route = nullptr, const int32_t* done_cols = nullptr);
 
 }  // namespace hcspmm
 

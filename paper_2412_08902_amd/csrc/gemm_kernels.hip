@@ -74,7 +74,8 @@ __device__ __forceinline__ void store_tile(const v4f_gemm (&acc)[NT], int64_t m0
 template <int NT, int WV>
 __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k_gemm_f32(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
                                                      const float* __restrict__ Wm, int64_t ldw, float* __restrict__ T, int64_t ldt,
-                                                     int32_t t_dtype, int relu, int tvec)
+                                                     int32_t t_dtype, int relu, int tvec, const uint8_t* __restrict__ done_route,
+                                                     const int32_t* __restrict__ done_cols, int32_t done_max)
 {
     constexpr int COLS = 16 * NT, SLAB = kGemmBK * COLS;
     constexpr int G4 = NT / 4, R = NT % 4, READS = G4 + (R ? 1 : 0);   // groups of four tiles, tiles of the last group
@@ -82,11 +83,23 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
     using Offset = std::conditional_t<NT == 1, int64_t, uint32_t>;
     constexpr int ITERS = (SLAB / WV + kThreads - 1) / kThreads;                  // loads of W per thread and slab
     extern __shared__ __attribute__((aligned(16))) float smem[];    // two slabs per column group
-    const int tid = threadIdx.x % kThreads, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x % kThreads, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int cw = threadIdx.x / kThreads, n0 = (int)(blockIdx.y * (blockDim.x / kThreads) + cw) * COLS;
     float* __restrict__ bs = smem + cw * 2 * SLAB;
     const int c = lane & 15, q = lane >> 4;
     const int64_t m0 = (int64_t)blockIdx.x * kGemmRows + wave * 16;
+    // 16-row tiles that another kernel finishes: a wave leaves its tile alone, a workgroup with nothing to do ends
+    bool skip = false;
+    if (done_route) {
+        const int64_t t0 = (int64_t)blockIdx.x * kGemmWaves, tiles = (M + 15) / 16;
+        bool all = true;
+        for (int i = 0; i < kGemmWaves; ++i) {
+            const bool done = t0 + i >= tiles || (done_route[t0 + i] != 0 && done_cols[t0 + i] <= done_max);
+            all = all && done;
+            if (i == wave) skip = done;
+        }
+        if (all) return;
+    }
     const float* __restrict__ xp = X + min(m0 + c, M - 1) * ldx + 4 * q;
 
     // this thread's pieces of a W slab: (k row, column) inside the slab, WV floats each
@@ -175,7 +188,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
             request_w(min(k0 + kGemmBK, last));
             request_x(min(k0 + 2 * kGemmBK, last), x);
             __builtin_amdgcn_sched_barrier(0);                      // (the compiler would move the requests to where they are used)
-            multiply(Two{}, bs + buf * SLAB + 4 * q * COLS, a);
+            if (!skip) multiply(Two{}, bs + buf * SLAB + 4 * q * COLS, a);
             __builtin_amdgcn_sched_barrier(0);
             buf ^= 1;
             stage(bs + buf * SLAB);
@@ -224,7 +237,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
         if (whole + 16 < K) multiply(Two{}, b, a);
         else multiply(One{}, b, a);
     }
-    store_tile<NT>(acc, m0, n0, M, N, T, ldt, t_dtype, relu, tvec, c, q);
+    if (!skip) store_tile<NT>(acc, m0, n0, M, N, T, ldt, t_dtype, relu, tvec, c, q);
 }
 
 // The product with W kept in registers (K <= 128 and a multiple of four): a wave holds the 16*NT columns of W that are its
@@ -321,14 +334,15 @@ hipError_t launch_gemm_f32(int64_t m, int32_t k, int32_t n, const float* X, int6
 }
 
 hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
-                               void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s)
+                               void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s, const uint8_t* done_route,
+                               const int32_t* done_cols)
 {
     if (m <= 0 || n <= 0) return hipSuccess;
     if (t_dtype != HCSPMM_F32 && t_dtype != HCSPMM_BF16 && t_dtype != HCSPMM_F16) return hipErrorInvalidValue;
     // W in registers where it is small and the product streams: 2.4 M x 64 x 32: 199 -> 170 us, 2.4 M x 16 x 16: 109 -> 58 us,
     // 169,343 x 128 x 64: 41 -> 37 us.  Wider products are bound by the matrix units and level or behind (400,000 x 128 x 96:
     // 111 -> 123 us), short ones spend more on bringing all of W in first (20,000 x 128 x 64: 8.0 -> 9.7 us).
-    if (k % 4 == 0 && k > 0 && k <= 128 && (int64_t)k * n <= 8192 && (m >= 65536 || (int64_t)k * n <= 1024)) {
+    if (!done_route && k % 4 == 0 && k > 0 && k <= 128 && (int64_t)k * n <= 8192 && (m >= 65536 || (int64_t)k * n <= 1024)) {
         // column groups: 1, 2 or 4 per workgroup
         const int k16 = (k + 15) / 16;
         const int64_t tiles16 = ((int64_t)n + 15) / 16, ny = (tiles16 + 15) / 16, per_y = (tiles16 + ny - 1) / ny;
@@ -357,7 +371,7 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
     const int wv = (n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0) ? 4 : 1;
     const int tvec = n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
     float* Tf = static_cast<float*>(T);
-#define HC_LAUNCH_GEMM(NT, WV) hipLaunchKernelGGL((k_gemm_f32<NT, WV>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, tvec)
+#define HC_LAUNCH_GEMM(NT, WV) hipLaunchKernelGGL((k_gemm_f32<NT, WV>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, tvec, done_route, done_cols, kMfmaSmallMaxCols)
 #define HC_GEMM_NT(NT) case NT: if (wv == 4) HC_LAUNCH_GEMM(NT, 4); else HC_LAUNCH_GEMM(NT, 1); break
     switch (nt) {
         HC_GEMM_NT(1); HC_GEMM_NT(2); HC_GEMM_NT(3); HC_GEMM_NT(4); HC_GEMM_NT(5); HC_GEMM_NT(6); HC_GEMM_NT(7); HC_GEMM_NT(8);

@@ -399,22 +399,35 @@ struct PlanCarry {
 // X and most of them miss (232,965 rows of 492 non-zeros, 128 columns fp32: 36 GB behind L2, at the 6.6 TB/s that this path
 // gives: 5.45 ms; the matrix path, which fetches a column once per window, 5.24 ms).  Taking the columns in panels whose
 // 128-byte slices about fit an XCD's L2 (3.5 MiB) makes almost every gather a hit, for one more read and write of Y per
-// panel and the rows' chains once per panel: 3.5 ms with 9 panels.  A panel should keep some twenty non-zeros of a row, and
-// panels much larger than an L2 bring little: 100,000 rows of 300: 1144 -> 878 us with 4 panels, 500,000 of 60 (64 MB of
-// slices): 1752 -> 1614 us with 3, more of them lose; below a sixth of the panels that L2 asks for it is left alone.
+// panel and the rows' chains once per panel: 3.5 ms with 9 panels.  A panel should keep some forty non-zeros of a row, and
+// panels much larger than an L2 bring little.  Measured against the scalar path in one go: 100,000 rows of 200, 128 columns
+// fp32: 759 -> 691 us with 3 panels, 200,000 of 300: 2851 -> 2157 us with 7; but 300,000 of 100, with 5: 1527 -> 1489 us in
+// fp32, 752 -> 873 us in bf16 (the sums between panels are fp32), 150,000 of 60: 400 -> 413 us -- i.e. from about 150
+// non-zeros per row on, and from 400 for 16-bit rows of 128 bytes (200,000 of 300: 660 -> 695 us).
 // The rows have to ascend in their columns, and every window then runs on the scalar path (with panels it is ahead of the
-// matrix path on such matrices), unless the caller chose the routing, the coefficients or the matrix kernels.
+// matrix path on such matrices).
+static bool choice_is_ours(const hcspmm_options& o) { return !o.use_custom_selector && o.matrix_kernels == HCSPMM_MATRIX_AUTO; }
 static int panel_count(const hcspmm_plan* p)
 {
     const hcspmm_options& o = p->opt;
-    if ((o.route_mode != HCSPMM_ROUTE_HYBRID && o.route_mode != HCSPMM_ROUTE_ALL_CSR) || o.use_custom_selector ||
-        o.matrix_kernels != HCSPMM_MATRIX_AUTO || p->n_rows == 0)
-        return 0;
-    const int64_t row_bytes = o.d_hint > 0 ? (int64_t)o.d_hint * (o.mfma_dtype == HCSPMM_F32 ? 4 : 2) : 128;
+    if ((o.route_mode != HCSPMM_ROUTE_HYBRID && o.route_mode != HCSPMM_ROUTE_ALL_CSR) || !choice_is_ours(o) || p->n_rows == 0) return 0;
+    const bool f32 = o.mfma_dtype == HCSPMM_F32;
+    const int64_t row_bytes = o.d_hint > 0 ? (int64_t)o.d_hint * (f32 ? 4 : 2) : 128;
     if (row_bytes < kPanelRowBytes) return 0;
-    const double want = (double)p->n_cols * 128.0 / (3.5 * (1 << 20)), most = (double)p->nnz / p->n_rows / 20.0;
-    int n = (int)std::min({want + 0.5, most, (double)kMaxPanels});
-    return n >= 2 && 6.0 * n >= want ? n : 0;
+    const double degree = (double)p->nnz / p->n_rows;
+    if (degree < (!f32 && row_bytes < 2 * kPanelRowBytes ? 400.0 : 150.0)) return 0;
+    const double want = (double)p->n_cols * 128.0 / (3.5 * (1 << 20));
+    const int n = (int)std::min({want + 0.5, degree / 40.0, (double)kMaxPanels});
+    return n >= 2 && 4.0 * n >= want ? n : 0;
+}
+
+// Whether windows that the selector sends to the matrix path may run on the scalar path (see scattered_rows in
+// prepare_kernels.hip for when they do).  The scalar path's column slices live in L2 as long as the graph is not too large:
+// 300,000 rows of 60, 128 columns, fp32: 1077 -> 918 us, bf16: 590 -> 457 us; 1 M rows of 20: 1453 -> 1355 us; but 1 M rows
+// of 100: 5992 -> 6441 us, 2 M of 40: 5455 -> 5486 us.
+static bool scalar_candidate(const hcspmm_plan* p)
+{
+    return p->opt.route_mode == HCSPMM_ROUTE_HYBRID && choice_is_ours(p->opt) && p->n_rows > 0 && p->nnz <= 40000000;
 }
 
 static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCarry* carry = nullptr)
@@ -481,7 +494,8 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     // A scalar-only plan never reads the condensed structure (the paper has no preprocessing for its
     // scalar path either): its window features stay zero here and are computed when first asked for
     // (hcspmm_plan_info / hcspmm_plan_export), which makes prepare cheap for matrices that keep changing.
-    p->features_complete = (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR && nnz > 0) ? 0 : 1;
+    // (a scalar-only plan counts columns on first request, unless it has to know whether panels pay)
+    p->features_complete = (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR && nnz > 0 && n_panels < 2) ? 0 : 1;
     p->rows_sorted = 1;
     pr.n_rows = n_rows; pr.n_cols = p->n_cols; pr.W = W; pr.n_tiles = (int32_t)prep_tile_count(W); pr.nnz = nnz;
     pr.rowptr = p->rowptr; pr.colind = p->colind;
@@ -500,7 +514,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     }
     pr.features = p->features_complete;
     pr.check_sorted = n_panels > 1;
-    pr.scalar_exec = n_panels > 1;
+    pr.scalar_exec = n_panels > 1 || scalar_candidate(p);
     pr.mode = p->opt.route_mode;
     pr.c0 = p->coef[0]; pr.c1 = p->coef[1]; pr.c2 = p->coef[2];
     pr.mid_row = p->mid_row; pr.long_row = p->long_row; pr.fused_mid_row = p->fused_mid_row;
@@ -544,8 +558,8 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     // windows; scalar-path windows never read theirs at SpMM time and get it on export only, and a
     // plan without matrix-path windows does not even allocate the arrays
     p->condensed_complete = nnz == 0 ? 1 : 0;
-    p->n_panels = n_panels > 1 && !tot.unsorted ? n_panels : 0;
-    p->scalar_exec = p->n_panels > 1 ? 1 : 0;
+    p->scalar_exec = tot.all_scalar;
+    p->n_panels = n_panels > 1 && p->scalar_exec ? n_panels : 0;
     if (p->n_panels > 1) {
         PanelArgs pa{};
         pa.n_rows = n_rows; pa.n_cols = p->n_cols; pa.n_panels = n_panels; pa.n_tiles = pr.n_tiles;
@@ -831,6 +845,7 @@ static size_t spmm_scratch_bytes(const hcspmm_plan* p, int32_t d, size_t* tile_o
 static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStream_t stream,
                               hipEvent_t* ev = nullptr /* 5 events when timing stages */,
                               const UpdateArgs* upd = nullptr /* fuse the update stage where a tile stays on chip */,
+                              bool windows_only = false /* ... in the wave-per-window matrix kernel only */,
                               char* scratch_mem = nullptr /* device, spmm_scratch_bytes(): used instead of the plan's own lazily sized buffers */,
                               bool acc_rows = false /* column panels may keep fp32 sums of a 16-bit output in a buffer of the plan */)
 {
@@ -946,7 +961,7 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
     const int64_t nnz_matrix = p->scalar_exec ? 0 : p->nnz_mfma, n_scalar = p->scalar_exec ? p->W : p->n_csr;
     const CsrHints hints{p->nnz - nnz_matrix, n_scalar * kH, scattered, p->long_row};
     const uint8_t* route = p->scalar_exec ? nullptr : p->route;
-    if (upd)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
+    if (upd && !windows_only)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, n_scalar > 0 ? p->n_rows : 0, nullptr,
                           route, p->fused_mid_row, hints, stream, upd));
     else
@@ -960,12 +975,15 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         HC_HIP(hipEventRecord(p->ev_join[0], s_wg));
         HC_HIP(hipStreamWaitEvent(stream, p->ev_join[0], 0));
     }
+    // rows whose aggregation went to memory: all but the fused windows' rows, or long and mid rows and wide matrix-path windows
+    if (windows_only)
+        HC_HIP(launch_gemm_f32_out(p->n_rows, a.d, upd->d_out, a.Y, a.ldy, upd->W, upd->ldw, upd->Y, upd->ldy, upd->y_dtype, upd->relu,
+                                   stream, p->route, p->ncols));
     if (s_small != stream) {
         HC_HIP(hipEventRecord(p->ev_join[1], s_small));
         HC_HIP(hipStreamWaitEvent(stream, p->ev_join[1], 0));
     }
-    // rows whose aggregation went to memory (long and mid rows, wide matrix-path windows)
-    if (upd) HC_HIP(launch_update_rest(a, p->n_rest, p->rest_rows, *upd, stream));
+    if (upd && !windows_only) HC_HIP(launch_update_rest(a, p->n_rest, p->rest_rows, *upd, stream));
     return HCSPMM_OK;
 }
 
@@ -1144,7 +1162,7 @@ hcspmm_status hcspmm_plan_update(hcspmm_plan* plan, int64_t nnz, const int32_t* 
                              !(plan->opt.route_mode == HCSPMM_ROUTE_ALL_CSR);
     if (incremental) {
         // (a plan with an unsorted row somewhere does not say where: its structure is not carried)
-        if (plan->n_mfma > 0 && plan->erc && plan->wcols && plan->rows_sorted) {
+        if (plan->n_mfma > 0 && plan->erc && plan->wcols && plan->rows_sorted && !plan->scalar_exec) {
             carry.old_route = plan->route; carry.old_wptr = plan->wptr; carry.old_nnzw = plan->nnzw;
             carry.old_wcols = plan->wcols; carry.old_erc = plan->erc;
         }
@@ -1311,7 +1329,7 @@ static hcspmm_status spmm_impl(const hcspmm_plan* plan, const void* d_X, int64_t
         }
         if ((st = static_scratch_ptr(plan, &scratch_mem)) != HCSPMM_OK) return st;
     }
-    return run_spmm(plan, a, static_cast<hipStream_t>(stream), ev, nullptr, scratch_mem);
+    return run_spmm(plan, a, static_cast<hipStream_t>(stream), ev, nullptr, false, scratch_mem);
 }
 
 hcspmm_status hcspmm_spmm_noalloc(const hcspmm_plan* plan, const void* d_X, int64_t ldx, int32_t d, int32_t x_dtype,
@@ -1379,15 +1397,30 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
     HC_HIP(launch_gemm_f32_out(plan->n_cols, d_in, d_out, static_cast<const float*>(d_X), ldx,
                                static_cast<const float*>(d_W), ldw, d_workspace, d_out, t_dtype, 0, s));
     if (plan->n_rows == 0) return HCSPMM_OK;
-    return run_spmm(plan, a, s, nullptr, nullptr, nullptr, true);
+    return run_spmm(plan, a, s, nullptr, nullptr, false, nullptr, true);
 }
 
-// Where the separate update runs through the streaming 16-row kernel (narrow W, aggregated width 64 or 128) it
-// measured 4-23 % ahead of the fused update on graphs large enough not to be launch-bound; everywhere else
-// (aggregated width up to 32 or of 256, wide W, small graphs) the fused kernels are level or ahead.
-static bool split_update_faster(int64_t n_rows, int32_t agg_width, int32_t out_width, const float* Z)
+// Which windows keep their aggregated rows on chip for the update, when the caller leaves the choice to the library.
+//  * A graph so small that launches dominate: all of them, in one pass (2,708 rows: 64 -> 128 columns 8.2 us against 9.9 us
+//    with the product apart; at 16,934 rows it is 28.6 us against 19.7 us, and the line moves with the width).
+//  * Otherwise the scalar path's rows always go through the workspace: its own kernel with column slices and a whole product
+//    are ahead of tiles of 16 rows that wait for their longest row (169,343 rows, 32 -> 32: 73 us against 47 us, 128 -> 128:
+//    195 us against 175 us).
+//  * The wave-per-window matrix kernel multiplies its tile while other waves gather (131,072 rows in communities of degree
+//    50, 128 -> 128 columns: 157 us against 202 us), unless the multiplication outweighs the gather it hides behind: at
+//    degree 20, 128 -> 64 is 68 us against 74 us, 192 -> 128 153 us against 133 us; and few windows do not hide it (16,384
+//    rows, 96 -> 256: 40 us against 32 us).
+enum UpdatePlace { kUpdateApart, kUpdateInWindows, kUpdateEverywhere };
+static UpdatePlace update_place(const hcspmm_plan* plan, int32_t agg_width, int32_t out_width)
 {
-    return n_rows >= 32768 && agg_width > 32 && agg_width % 16 == 0 && agg_width <= 128 && out_width <= 64;
+    if ((int64_t)plan->n_rows * agg_width <= 200000 && plan->n_rows <= 8192 && plan->n_panels < 2 && 4 * (int64_t)plan->n_rest < plan->n_rows)
+        return kUpdateEverywhere;
+    const int64_t product = (int64_t)agg_width * out_width;
+    const bool deep = plan->nnz_mfma >= 40 * (int64_t)kH * plan->n_mfma;
+    if (!plan->scalar_exec && 2 * plan->n_mfma_small >= plan->W &&
+        (product <= 12288 || (plan->n_mfma_small >= 4096 && (product <= 16384 || deep))))
+        return kUpdateInWindows;
+    return kUpdateApart;
 }
 
 size_t hcspmm_aggregate_update_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)
@@ -1420,16 +1453,13 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
     SpmmArgs a{};
     a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d_in; a.x_dtype = x_dtype; a.Y = Z; a.ldy = d_in; a.relu = 0;
-    // The fused update pays where most rows can keep their tile on chip; rows that go through the
-    // workspace anyway (wide matrix-path windows, mid and long rows) are finished 16 at a time, which
-    // a plain GEMM does better once they are a large share of the matrix.
-    const bool worth = (4 * (int64_t)plan->n_rest < plan->n_rows && plan->n_panels < 2 &&
-                        !(x_dtype == HCSPMM_F32 && split_update_faster(plan->n_rows, d_in, d_out, Z))) ||
-                       plan->opt.update_fusion == HCSPMM_UPDATE_FUSED;
-    if (update_fusable(a) && worth && plan->opt.update_fusion != HCSPMM_UPDATE_SPLIT) {
+    const UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
+                              : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
+                                                                               : update_place(plan, d_in, d_out);
+    if (place != kUpdateApart && update_fusable(a)) {
         const UpdateArgs u{static_cast<const float*>(d_W), ldw, d_out, static_cast<float*>(d_Y), ldy, apply_relu ? 1 : 0, 0,
                            nullptr, 0, y_dtype};
-        return run_spmm(plan, a, s, nullptr, &u);
+        return run_spmm(plan, a, s, nullptr, &u, place == kUpdateInWindows);
     }
     if ((st = run_spmm(plan, a, s)) != HCSPMM_OK) return st;
     HC_HIP(launch_gemm_f32_out(plan->n_rows, d_in, d_out, Z, d_in, static_cast<const float*>(d_W), ldw, d_Y, ldy, y_dtype,
@@ -1498,16 +1528,17 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
         a.X = G; a.ldx = g_ld; a.d = d_out; a.x_dtype = HCSPMM_F32; a.Y = S; a.ldy = d_out; a.relu = 0;
         if (d_dX) {
             HC_HIP(launch_transpose(d_in, d_out, static_cast<const float*>(d_W), ldw, Wt, s));
-            // as in hcspmm_aggregate_update; when dW needs S in memory as well, the fused kernels store every
-            // tile besides multiplying it, which measured faster than the separate GEMM only for narrow S
-            const bool worth = (4 * (int64_t)plan->n_rest < plan->n_rows && plan->n_panels < 2 && (!d_dW || d_out <= 32) &&
-                                !split_update_faster(plan->n_rows, d_out, d_in, S)) ||
-                               plan->opt.update_fusion == HCSPMM_UPDATE_FUSED;
-            if (update_fusable(a) && worth && plan->opt.update_fusion != HCSPMM_UPDATE_SPLIT) {
+            // as in hcspmm_aggregate_update; when dW needs S in memory or the mask an epilogue, only a graph that is all
+            // launches has its update fused
+            UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
+                                : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
+                                                                                 : update_place(plan, d_out, d_in);
+            if (place == kUpdateInWindows && (d_dW || mask_dx_by_x)) place = kUpdateApart;
+            if (place != kUpdateApart && update_fusable(a)) {
                 // the next layer's activation mask (its output is this layer's input X) goes into the update's epilogue
                 const UpdateArgs u{Wt, d_in, d_in, static_cast<float*>(d_dX), lddx, 0, d_dW ? 1 : 0,
                                    mask_dx_by_x ? static_cast<const float*>(d_X) : nullptr, ldx};
-                if ((st = run_spmm(plan, a, s, nullptr, &u)) != HCSPMM_OK) return st;
+                if ((st = run_spmm(plan, a, s, nullptr, &u, place == kUpdateInWindows)) != HCSPMM_OK) return st;
             } else {
                 if ((st = run_spmm(plan, a, s)) != HCSPMM_OK) return st;
                 HC_HIP(launch_gemm_f32(plan->n_rows, d_out, d_in, S, d_out, Wt, d_in, static_cast<float*>(d_dX), lddx, 0, s));

@@ -678,6 +678,19 @@ __device__ inline int counts_set(const Prep& p, int mode)       // which set of 
     return mode == p.mode ? 0 : (mode == HCSPMM_ROUTE_ALL_MFMA ? 1 : -1);
 }
 
+// Whether every window runs on the scalar path, where panel_count or scalar_candidate ask.  It depends on how much the rows
+// of a window share: the matrix path fetches a distinct column of a window once, the scalar path a row of X per non-zero but
+// in large part from L2.  Distinct columns are 0.16 of the non-zeros in communities of degree 51 (131,072 rows, 128 columns,
+// fp32: 107 us on the matrix path, 131 us on the scalar path, 157 us in panels) and 0.8 to 0.95 in power-law graphs of degree
+// 20 to 500.  Panels fetch from L2 almost only (16 TB/s against 6.6 TB/s from behind it) and take over at 0.4, the plain
+// scalar path at 0.6.  Panels need rows whose columns ascend.
+__device__ inline bool scattered_rows(const Prep& p, int64_t total_ncols)
+{
+    if (!p.scalar_exec) return false;
+    if (p.check_sorted) return p.ctl[6] == 0 && 10 * total_ncols > 4 * p.nnz;
+    return 10 * total_ncols > 6 * p.nnz;
+}
+
 // One row's place in the scalar path's tables.
 struct RowClass { int is_short, is_mid, n_seg, rest, len_long; };
 __device__ inline RowClass row_class(const Prep& p, int32_t len, int route, int wide_window)
@@ -710,12 +723,15 @@ __global__ __launch_bounds__(256) void k_pre_rows(Prep p)
     __shared__ uint8_t s_route[kTileWindows], s_wide[kTileWindows];
     if (*p.ctl) return;
     const int tile = blockIdx.x;
-    unsigned long long before = 0, on_matrix = 0;
+    unsigned long long before = 0, behind = 0, on_matrix = 0;
     for (int t = threadIdx.x; t < p.n_tiles; t += 256) {
         on_matrix += p.wt[(int64_t)t * kWt + 1];
-        if (t < tile) before += p.wt[(int64_t)t * kWt];
+        const unsigned long long nc = p.wt[(int64_t)t * kWt];
+        if (t < tile) before += nc;
+        else behind += nc;
     }
     before = block_sum_u64(before, smem);
+    if (p.scalar_exec) behind = block_sum_u64(behind, smem);
     on_matrix = block_sum_u64(on_matrix, smem);
     const int mode = effective_mode(p, on_matrix);
     if (threadIdx.x < kTileWindows) {
@@ -738,7 +754,8 @@ __global__ __launch_bounds__(256) void k_pre_rows(Prep p)
         if (p.W == 0 && threadIdx.x == 0) p.wptr[0] = 0;
     }
     __syncthreads();
-    const bool all_scalar = p.scalar_exec && p.ctl[6] == 0;
+    const bool all_scalar = scattered_rows(p, (int64_t)(before + behind));
+    if (tile == 0 && threadIdx.x == 0) p.ctl[7] = all_scalar ? 1 : 0;
     unsigned long long a = 0, b = 0, len_long = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -785,7 +802,7 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
     unsigned long long a = 0, b = 0;
     const int64_t i0 = min((int64_t)tile * kTileRows + threadIdx.x * 4, (int64_t)p.n_rows);
     const int32_t w = (int32_t)(i0 / kH);
-    const int route = w < p.W && !(p.scalar_exec && p.ctl[6] == 0) ? p.route[w] : 0, wide = w < p.W ? (p.ncols[w] > kMfmaSmallMaxCols ? 1 : 0) : 0;
+    const int route = w < p.W && p.ctl[7] == 0 ? p.route[w] : 0, wide = w < p.W ? (p.ncols[w] > kMfmaSmallMaxCols ? 1 : 0) : 0;
 #pragma unroll
     for (int j = 0; j < 5; ++j) start[j] = p.rowptr[min(i0 + j, (int64_t)p.n_rows)];
 #pragma unroll
@@ -853,7 +870,7 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
         t.n_short = (int32_t)n_short; t.n_mid = (int32_t)n_mid; t.n_rest = (int32_t)n_rest; t.n_multi = (int32_t)n_multi;
         t.n_segs = (int32_t)n_seg; t.n_slots = (int64_t)n_slot;
         t.n_big_list = p.ctl[1]; t.n_huge_list = p.ctl[2];
-        t.unsorted = p.ctl[6];
+        t.all_scalar = p.ctl[7];
         t.err = 0;
         *p.out = t;
     }
