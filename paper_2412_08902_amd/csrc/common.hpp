@@ -38,6 +38,11 @@ constexpr int kMidRow = 128;           // rows with more non-zeros than this get
 constexpr int kMidRowSmall = 64, kMidRowFewRows = 65536;
 constexpr int kFusedMidRow = 256;      // with the update stage fused in, rows up to this length stay in the workgroup's tile
 constexpr int kLongRow = 1024;         // rows with more non-zeros than this are cut into workgroup-sized segments
+// ... from 256 non-zeros on where rows have fewer than 100 on average: a wave that walks 1000 non-zeros outlasts everything
+// else there (16,934 rows of 14, 128 columns, bf16: 15.8 -> 11.3 us; 50,000 of 28, 64 columns, bf16: 30.2 -> 18.9 us; level
+// from 169,000 rows on), and 256 threads per row only add their reduction where such rows are many (30,000 of 200: 183 -> 192 us)
+constexpr int kLongRowSparse = 256;
+constexpr int64_t kLongRowDegree = 100;
 constexpr int kSegLen = 2048;          // non-zeros per segment of a long row
 
 struct Segment { int32_t row, k_begin, k_end, slot; };    // slot < 0: writes Y directly
@@ -86,7 +91,7 @@ hipError_t exclusive_scan_multi(const ScanMulti& m, int64_t n, int64_t* totals_d
 
 // ---- preparation (prepare_kernels.hip): CSR arrays -> window features, routes, row tables -------
 struct PrepTotals {
-    int64_t total_ncols, nnz_mfma, wide_cols /* columns of wide matrix-path windows */, nnz_long, n_slots;
+    int64_t total_ncols, nnz_mfma, wide_cols /* columns of wide matrix-path windows */, mfma_cols /* of all of them */, nnz_long, n_slots;
     int32_t n_mfma, n_mfma_small, n_mfma_mid, n_mfma_big, n_short, n_mid, n_rest, n_multi, n_segs;
     int32_t all_scalar;                   // every window is executed on the scalar path (see scattered_rows)
     int32_t n_big_list, n_huge_list;      // windows above kUniqueSmallCap / kCountMidCap non-zeros
@@ -337,7 +342,7 @@ struct hcspmm_plan {
     int32_t* mfma_windows;
     int64_t total_ncols;
     int32_t n_mfma, n_csr;
-    int64_t nnz_mfma;
+    int64_t nnz_mfma, mfma_ncols;   // non-zeros and distinct columns of the matrix-path windows
     // owned, launch tables
     int32_t* mfma_small;
     hcspmm::WinDesc* mfma_small_desc;

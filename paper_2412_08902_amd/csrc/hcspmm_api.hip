@@ -427,6 +427,8 @@ static int panel_count(const hcspmm_plan* p)
 // of 100: 5992 -> 6441 us, 2 M of 40: 5455 -> 5486 us.
 static bool scalar_candidate(const hcspmm_plan* p)
 {
+    // (rows of X off the 128-byte lines cost slices a second line each: 300,000 rows of 60, 144 columns, bf16: 825 -> 1029 us)
+    if ((int64_t)p->opt.d_hint * (p->opt.mfma_dtype == HCSPMM_F32 ? 4 : 2) % 128 != 0) return false;
     return p->opt.route_mode == HCSPMM_ROUTE_HYBRID && choice_is_ours(p->opt) && p->n_rows > 0 && p->nnz <= 40000000;
 }
 
@@ -546,6 +548,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     p->n_mfma_big = tot.n_mfma_big;
     p->n_mfma_mid = tot.n_mfma_mid;
     p->nnz_mfma = tot.nnz_mfma;
+    p->mfma_ncols = tot.mfma_cols;
     p->nnz_long = tot.nnz_long;
     p->n_short = tot.n_short;
     p->n_segs = tot.n_segs;
@@ -957,9 +960,10 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
     }
     // (the windows' distinct columns against their non-zeros say how much neighbouring rows share; a scalar-only plan does
     // not count them)
-    const bool scattered = p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * p->total_ncols > 6 * p->nnz;
-    const int64_t nnz_matrix = p->scalar_exec ? 0 : p->nnz_mfma, n_scalar = p->scalar_exec ? p->W : p->n_csr;
-    const CsrHints hints{p->nnz - nnz_matrix, n_scalar * kH, scattered, p->long_row};
+    const int64_t nnz_scalar = p->nnz - (p->scalar_exec ? 0 : p->nnz_mfma), n_scalar = p->scalar_exec ? p->W : p->n_csr;
+    const int64_t cols_scalar = p->total_ncols - (p->scalar_exec ? 0 : p->mfma_ncols);
+    const bool scattered = p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * cols_scalar > 6 * nnz_scalar;
+    const CsrHints hints{nnz_scalar, n_scalar * kH, scattered, p->long_row};
     const uint8_t* route = p->scalar_exec ? nullptr : p->route;
     if (upd && !windows_only)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, n_scalar > 0 ? p->n_rows : 0, nullptr,
@@ -1029,7 +1033,7 @@ static hcspmm_status init_plan_header(hcspmm_plan* p, int32_t n_rows, int32_t n_
     p->rowptr = d_rowptr; p->colind = d_colind; p->vals = d_vals;
     p->opt = o;
     p->mid_row = n_rows <= kMidRowFewRows ? kMidRowSmall : kMidRow;
-    p->long_row = kLongRow;
+    p->long_row = nnz < kLongRowDegree * n_rows ? kLongRowSparse : kLongRow;
     // tuning knobs for experiments (not part of the ABI): override the row-tier thresholds
     if (tune().mid_row >= 1) p->mid_row = tune().mid_row;
     if (tune().long_row >= p->mid_row) p->long_row = tune().long_row;

@@ -647,19 +647,20 @@ __global__ __launch_bounds__(256) void k_pre_select(Prep p)
     if (tile >= p.n_tiles) return;
     const int32_t w = tile * kTileWindows + (threadIdx.x & 63);
     const long long nc = w < p.W ? p.ncols[w] : 0, nz = w < p.W ? p.nnzw[w] : 0;
-    unsigned long long v[7] = {(unsigned long long)nc, 0, 0, 0, 0, 0, 0};
+    unsigned long long v[8] = {(unsigned long long)nc, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int set = 0; set < 2; ++set) {
         const int r = window_route(p, set == 0 ? p.mode : HCSPMM_ROUTE_ALL_MFMA, nc, nz);
         v[1 + 3 * set] = r ? (unsigned long long)nz : 0ull;
         v[2 + 3 * set] = window_counts(r, nc);
         v[3 + 3 * set] = r && nc > kMfmaMidMaxCols ? (unsigned long long)nc : 0ull;
+        if (set == 0 && r) v[7] = (unsigned long long)nc;
     }
 #pragma unroll
-    for (int i = 0; i < 7; ++i) v[i] = wave_sum(v[i]);
+    for (int i = 0; i < 8; ++i) v[i] = wave_sum(v[i]);
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
-        for (int i = 0; i < 7; ++i) p.wt[(int64_t)tile * kWt + i] = v[i];
+        for (int i = 0; i < 8; ++i) p.wt[(int64_t)tile * kWt + i] = v[i];
 }
 
 // Launch guard: a path whose share cannot repay a kernel launch of its own joins the other path.
@@ -859,12 +860,13 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
         v[3] += (n & 0xffffull) | (n >> 16 & 0xffffull) << 32;
         v[4] += (n >> 32 & 0xffffull) | (n >> 48) << 32;
         v[5] += p.wt[(int64_t)t * kWt + 3 + 3 * set];
+        v[6] += p.wt[(int64_t)t * kWt + (set == 0 ? 7 : 0)];
     }
 #pragma unroll
-    for (int k = 0; k < 6; ++k) v[k] = block_sum_u64(v[k], smem);
+    for (int k = 0; k < 7; ++k) v[k] = block_sum_u64(v[k], smem);
     if (threadIdx.x == 0) {
         PrepTotals t{};
-        t.total_ncols = (int64_t)v[0]; t.nnz_long = (int64_t)v[1]; t.nnz_mfma = (int64_t)v[2]; t.wide_cols = (int64_t)v[5];
+        t.total_ncols = (int64_t)v[0]; t.nnz_long = (int64_t)v[1]; t.nnz_mfma = (int64_t)v[2]; t.wide_cols = (int64_t)v[5]; t.mfma_cols = (int64_t)v[6];
         t.n_mfma = (int32_t)v[3]; t.n_mfma_small = (int32_t)(v[3] >> 32);
         t.n_mfma_mid = (int32_t)v[4]; t.n_mfma_big = (int32_t)(v[4] >> 32);
         t.n_short = (int32_t)n_short; t.n_mid = (int32_t)n_mid; t.n_rest = (int32_t)n_rest; t.n_multi = (int32_t)n_multi;

@@ -641,20 +641,32 @@ static int shape_cols(const CsrShape& sh) { return kGroup / sh.split * sh.vec * 
 // 30,000 nodes of degree 20: 37.7 -> 25.1 us with two slices, 169,000 of 15: 118 -> 111 us, 500,000 of 60: 1973 -> 1850 us
 // and 1754 us with four; but 500,000 of degree 6: 261 -> 285 us, 2.4 M of 51: 8.63 -> 8.69 ms -- i.e. from about five
 // non-zeros per row for every 64 MiB of X.  128-byte slices win over 256-byte ones from about 40 non-zeros per row (the
-// per-row chain is then small; 60,000 nodes of degree 100: 271 / 228 / 201 us with 1 / 2 / 4 slices).  Neighbouring rows
-// that share their columns (community graphs) already meet in one L2 and lose 6 %: they are left whole.
+// per-row chain is then small; 60,000 nodes of degree 100: 271 / 228 / 201 us with 1 / 2 / 4 slices), as long as rows of X
+// start on a 128-byte line: off it, every slice costs a second line (300,000 of degree 60, bf16, 224 columns: 1345 us in
+// four slices, 256 columns 969 us).  Neighbouring rows that share their columns (community graphs) already meet in one L2
+// and lose 6 %: they are left whole.
+// 16-bit rows of more than 256 and less than 512 bytes leave lanes of the two-vector form idle, at half the waves: three
+// slices of 128 bytes where rows start on lines (16,934 nodes of 14, 192 columns, bf16: 26 -> 17 us; 1 M of 20: 1207 -> 1094 us),
+// two halves while X fits the L2s (16,934 of 14, 160 columns: 25 -> 15 us; 100,000 of 20: 91 -> 92 us).
 static int pick_slices(const SpmmArgs& a, const CsrHints& h, int32_t& slice_w)
 {
     const int64_t es = a.x_dtype == HCSPMM_F32 ? 4 : 2, row = a.d * es;
-    int64_t most = 512;                                         // bytes of a row per slice
+    const bool on_lines = a.ldx * es % 128 == 0 && (uintptr_t)a.X % 128 == 0;
+    int64_t most = 512, align = 128 / es;                       // bytes of a row per slice; slices of whole 128-byte lines
     const double degree = h.rows > 0 ? (double)h.nnz / (double)h.rows : 0.0;
-    if (h.scattered && degree >= 5.0 * ((double)a.n_cols * (double)row / (64.0 * (1 << 20)))) {
-        if (degree >= 40.0 && row >= 256) most = 128;
-        else if (row >= 512) most = 256;
+    const bool often = h.scattered && degree >= 5.0 * ((double)a.n_cols * (double)row / (64.0 * (1 << 20)));
+    if (often && on_lines && degree >= 40.0 && row >= 256) most = 128;
+    else if (often && row >= 512) most = 256;
+    else if (es == 2 && h.scattered && row > 256 && row < 512) {
+        if (on_lines) most = 128;
+        else if ((double)a.n_cols * (double)row <= 20.0 * (1 << 20)) { most = 256; align = 32; }
     }
     int64_t n = (row + most - 1) / most;
-    while (n > 1 && n < 8 && (n & (n - 1)) != 0 && (row + n - 2) / (n - 1) <= 512) --n;     // a count that XCDs can own
-    const int64_t align = 128 / es;                             // whole 128-byte lines per slice
+    // a count that XCDs can own, where the slices come out about equally wide; other counts are taken in turn
+    for (int64_t m = n; m > 1 && n < 8 && (row + m - 1) / m <= 512; --m) {
+        const int64_t w = ((a.d + m - 1) / m + align - 1) / align * align;
+        if ((m & (m - 1)) == 0 && 5 * m * w <= 6 * a.d) { n = m; break; }
+    }
     slice_w = (int32_t)(((a.d + n - 1) / n + align - 1) / align * align);
     const int n_slices = (int)((a.d + slice_w - 1) / slice_w);
     if (n_slices <= 1) slice_w = a.d;
