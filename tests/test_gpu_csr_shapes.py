@@ -55,3 +55,21 @@ def test_column_slices(n, degree, d):
     rows = np.unique(np.concatenate([np.arange(0, n, 37), np.arange(max(0, n - 40), n)]))
     ref, bound = oracle_pair(g, X, rows=rows)
     assert_close(Y[rows], ref, bound, 1e-5, "slices n=%d degree=%d d=%d" % (n, degree, d))
+
+
+# rows are cut into segments from 257 non-zeros on between 4,000 and 170,000 rows of a sparse matrix, from 1025 on elsewhere
+@pytest.mark.parametrize("n,long_rows", [(3999, 1), (4000, 3), (170_000, 3), (170_001, 1)])
+def test_long_rows_of_sparse_matrices(n, long_rows):
+    lengths = np.ones(n, np.int64)
+    hubs = np.array([5, n // 2, n // 2 + 1, n - 1])
+    lengths[hubs] = [256, 257, 1024, 1025]
+    rng = np.random.default_rng(n)
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    g = CSRGraph(n, 2000, rowptr, rng.integers(0, 2000, rowptr[-1]).astype(np.int32),
+                 rng.standard_normal(rowptr[-1]).astype(np.float32))
+    X = rng.standard_normal((g.n_cols, 64)).astype(np.float32)
+    Y, info = gpu_spmm(g, X, 1)
+    assert info["n_long_rows"] == info["n_segments"] == long_rows
+    rows = np.unique(np.concatenate([hubs, np.arange(0, n, 97)]))
+    ref, bound = oracle_pair(g, X, rows=rows)
+    assert_close(Y[rows], ref, bound, 1e-5, "n=%d" % n)
