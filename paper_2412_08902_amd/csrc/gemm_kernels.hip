@@ -70,8 +70,8 @@ __device__ __forceinline__ void store_tile(const v4f_gemm (&acc)[NT], int64_t m0
 
 // WV: floats per global load of W (4: W's rows are 16-byte aligned and N is a multiple of 4).
 // Rows past M re-read row M-1 and columns past N read column N-WV: what they produce is never stored.  k >= K is zero in both
-// operands.
-template <int NT, int WV>
+// operands.  WIDE: byte offsets inside a slab of W need 64 bits (launch_gemm_f32_out says when).
+template <int NT, int WV, bool WIDE>
 __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k_gemm_f32(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
                                                      const float* __restrict__ Wm, int64_t ldw, float* __restrict__ T, int64_t ldt,
                                                      int32_t t_dtype, int relu, int tvec, const uint8_t* __restrict__ done_route,
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
     constexpr int COLS = 16 * NT, SLAB = kGemmBK * COLS;
     constexpr int G4 = NT / 4, R = NT % 4, READS = G4 + (R ? 1 : 0);   // groups of four tiles, tiles of the last group
     constexpr int kThreads = 64 * kGemmWaves;                       // of a column group
-    using Offset = std::conditional_t<NT == 1, int64_t, uint32_t>;
+    using Offset = std::conditional_t<WIDE, uint64_t, uint32_t>;
     constexpr int ITERS = (SLAB / WV + kThreads - 1) / kThreads;                  // loads of W per thread and slab
     extern __shared__ __attribute__((aligned(16))) float smem[];    // two slabs per column group
     const int tid = threadIdx.x % kThreads, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
 
     // this thread's pieces of a W slab: (k row, column) inside the slab, WV floats each
     auto at = [&](int i, int& k, int& col) { const int idx = (tid + kThreads * i) * WV; k = idx / COLS; col = idx % COLS; };
-    Offset wo[ITERS];                                               // (a 64-bit one for pitches of 2^25 floats and more: NT = 1)
+    Offset wo[ITERS];
 #pragma unroll
     for (int i = 0; i < ITERS; ++i) {
         int k, col;
@@ -365,15 +365,18 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
     }
     // columns: as few groups of up to 128 as hold them, equally wide; two groups to a workgroup where they come in pairs
     const int64_t tiles = ((int64_t)n + 15) / 16, groups = (tiles + 7) / 8;
-    const int nt = (int)((tiles + groups - 1) / groups), pair = groups % 2 == 0 ? 2 : 1;
+    // a slab's last row of W ends beyond 4 GiB of its first (a pitch of 34.6 M floats and more): 64-bit offsets, in full groups
+    const bool wide = ((uint64_t)(std::min(k, kGemmBK) - (k > 0)) * (uint64_t)ldw + (uint64_t)n) * 4 > ((uint64_t)1 << 32);
+    const int nt = wide ? 8 : (int)((tiles + groups - 1) / groups), pair = groups % 2 == 0 ? 2 : 1;
     const dim3 grid((unsigned)((m + kGemmRows - 1) / kGemmRows), (unsigned)(groups / pair));
     const size_t lds = (size_t)pair * 2 * kGemmBK * 16 * nt * sizeof(float);
     const int wv = (n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0) ? 4 : 1;
     const int tvec = n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
     float* Tf = static_cast<float*>(T);
-#define HC_LAUNCH_GEMM(NT, WV) hipLaunchKernelGGL((k_gemm_f32<NT, WV>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, tvec, done_route, done_cols, kMfmaSmallMaxCols)
-#define HC_GEMM_NT(NT) case NT: if (wv == 4) HC_LAUNCH_GEMM(NT, 4); else HC_LAUNCH_GEMM(NT, 1); break
-    switch (nt) {
+#define HC_LAUNCH_GEMM(NT, WV, WIDE) hipLaunchKernelGGL((k_gemm_f32<NT, WV, WIDE>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, tvec, done_route, done_cols, kMfmaSmallMaxCols)
+#define HC_GEMM_NT(NT) case NT: if (wv == 4) HC_LAUNCH_GEMM(NT, 4, false); else HC_LAUNCH_GEMM(NT, 1, false); break
+    if (wide) HC_LAUNCH_GEMM(8, 1, true);
+    else switch (nt) {
         HC_GEMM_NT(1); HC_GEMM_NT(2); HC_GEMM_NT(3); HC_GEMM_NT(4); HC_GEMM_NT(5); HC_GEMM_NT(6); HC_GEMM_NT(7); HC_GEMM_NT(8);
     }
 #undef HC_GEMM_NT

@@ -57,3 +57,20 @@ def test_weight_gradient(n, d_in, d_out):
     G, X, W = dense_normal(n, d_out, seed=1), dense_normal(n, d_in, seed=2), glorot_uniform(d_in, d_out, seed=3)
     dX, dW, S = run_backward(g, G, X, W, mode=1, pad=d_in % 2)
     check(g, G, X, W, dX, dW, S)
+
+
+def test_slab_product_with_a_pitch_beyond_32_bit_offsets():
+    """W as a column slice of a very wide array: 31 rows of its pitch are more than 4 GiB.  Full slabs of 32 and a rest of K;
+    one column group, two in a workgroup, three."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    pitch, k, m = 34_700_001, 37, 70
+    big = torch.empty((k, pitch), device="cuda")                  # 5.1 GB, of which the slice below is written and read
+    X = dense_normal(m, k, seed=1)
+    for n in (20, 130, 300):
+        W = dense_normal(k, n, seed=n)
+        big[:, 8:8 + n] = torch.from_numpy(W).cuda()
+        T = torch.full((m, n), float("nan"), device="cuda")
+        hc.hcspmm_gemm_f32(torch.from_numpy(X).cuda(), big[:, 8:8 + n], T)
+        torch.cuda.synchronize()
+        assert_close(T.cpu().numpy().astype(np.float64), oracle.gemm(X, W), oracle.gemm(X, W, use_abs=True), 1e-5, "n=%d" % n)
