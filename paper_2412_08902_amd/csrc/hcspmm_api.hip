@@ -406,7 +406,10 @@ struct PlanCarry {
 // non-zeros per row on, and from 400 for 16-bit rows of 128 bytes (200,000 of 300: 660 -> 695 us).
 // The rows have to ascend in their columns, and every window then runs on the scalar path (with panels it is ahead of the
 // matrix path on such matrices).
-static bool choice_is_ours(const hcspmm_options& o) { return !o.use_custom_selector && o.matrix_kernels == HCSPMM_MATRIX_AUTO; }
+static bool choice_is_ours(const hcspmm_options& o)
+{
+    return !o.use_custom_selector && o.matrix_kernels == HCSPMM_MATRIX_AUTO && !tune().runs;
+}
 static int panel_count(const hcspmm_plan* p)
 {
     const hcspmm_options& o = p->opt;
@@ -655,7 +658,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     // Runs of matrix-path windows (kRunWindows consecutive list entries each): merged column lists and slots on the
     // device, the slice layout on the host from the union sizes (a few bytes per run cross the bus).
     p->runs_ok = 0;
-    if (p->n_mfma > 0 && p->rows_sorted && p->n_cols <= kRankMaxCols && (p->opt.matrix_kernels == HCSPMM_MATRIX_RUNS || tune().runs)) {
+    if (p->n_mfma > 0 && !p->scalar_exec && p->rows_sorted && p->n_cols <= kRankMaxCols && (p->opt.matrix_kernels == HCSPMM_MATRIX_RUNS || tune().runs)) {
         const int32_t n_runs = (p->n_mfma + kRunWindows - 1) / kRunWindows;
         HC_ALLOC(keep, p->ucols, p->total_ncols);
         HC_ALLOC(keep, p->wslot, p->total_ncols);

@@ -121,3 +121,45 @@ def test_configs_full_size(name, kind):
     g, X, _ = make_config(name)
     info = run_spmm(g, X, kind=kind, check_table=(name != "C2"))
     assert info["n_runs"] > 0 and info["run_union_cols"] <= info["total_ncols"]
+
+
+RUNS_BY_KNOB = """
+import sys, numpy as np, torch, oracle
+sys.path.insert(0, "tests")
+import paper_2412_08902_amd.binding as hc
+from gpu_util import assert_close, device_graph, oracle_pair
+from test_gpu_runs import scattered_windows
+from workloads import dense_normal, to_bf16_bits
+g = scattered_windows()
+bits = to_bf16_bits(dense_normal(g.n_cols, 128, seed=5))
+plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *device_graph(g), d_hint=128, mfma_dtype=hc.HCSPMM_BF16)
+info = hc.hcspmm_plan_info(plan)
+assert info["n_mfma_windows"] > 900 and info["n_runs"] > 0, info
+Y = torch.full((g.n_rows, 128), float("nan"), device="cuda")
+hc.hcspmm_spmm(plan, torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16), Y)
+torch.cuda.synchronize()
+assert_close(Y.cpu().numpy().astype(np.float64), *oracle_pair(g, bits, x_dtype=oracle.DT_BF16), 2e-2, "runs by knob")
+print("runs by knob ok")
+"""
+
+
+def scattered_windows(windows=1000, per_row=4, pool=64, seed=3):
+    """Windows of 64 non-zeros in about 41 distinct columns: the 16-bit selector sends them to the matrix path, and they are
+    scattered enough for the library to run all of them on the scalar path."""
+    rng = np.random.default_rng(seed)
+    base = np.repeat(rng.integers(0, 4000, windows), 16)
+    cols = np.stack([b + np.sort(rng.choice(pool, per_row, replace=False)) for b in base]).astype(np.int32)
+    rowptr = (per_row * np.arange(16 * windows + 1)).astype(np.int32)
+    return CSRGraph(16 * windows, 4100, rowptr, cols.ravel(), rng.standard_normal(cols.size).astype(np.float32))
+
+
+def test_run_tables_asked_for_by_the_experiment_knob():
+    """HCSPMM_TUNE_RUNS is read once per process: a process of its own.  The plan keeps its matrix-path tables then, also where
+    the library would run every window on the scalar path."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", RUNS_BY_KNOB], cwd=root, env=dict(os.environ, HCSPMM_TUNE_RUNS="1"),
+                       capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "runs by knob ok" in r.stdout, r.stderr[-2000:]
