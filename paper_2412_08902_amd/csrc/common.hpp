@@ -31,7 +31,6 @@ constexpr int kKcBig = 1024;           // condensed columns staged per workgroup
 constexpr int kSliceCols = 4096;       // condensed columns per workgroup; wider windows are cut into slices
 
 // ---- scalar path -------------------------------------------------------------------------------
-constexpr int kRowsPerGroup = 8;       // most consecutive rows one lane group may walk (short rows); also the narrowest group
 constexpr int kMidRow = 128;           // rows with more non-zeros than this get a whole wave
 // On a matrix of few rows the longest chain of dependent loads is what a call takes, so a wave takes rows over earlier
 // (30,000 rows, fp32, 64 columns: 16.4 -> 14.9 us; 16,000 rows, bf16, 128 columns: 11.1 -> 8.0 us); large ones lose 3-7 %.

@@ -14,8 +14,9 @@
 // WIDE form with 64-bit row offsets.  X is read directly from global memory / L2 (the paper found
 // staging X in shared memory a loss on this path).  Three tiers by row length balance power-law
 // degree distributions:
-//   short rows  a lane group walks one to four consecutive rows in one flattened loop, and the
-//               workgroups reach the XCDs in runs so that neighbouring rows share an L2;
+//   short rows  a lane group owns a row (or walks a few consecutive ones in one flattened loop, on
+//               matrices whose launch would not fit otherwise: csr_grid.hpp), and the workgroups
+//               reach the XCDs in runs so that neighbouring rows share an L2;
 //   mid rows    one wave per row, the groups stride over the row and combine with cross-lane adds;
 //   long rows   one workgroup per segment of kSegLen non-zeros, combined through LDS in a fixed
 //               order (and, for rows of several segments, through partial rows in memory).
@@ -24,11 +25,10 @@
 #include <utility>
 
 #include "common.hpp"
+#include "csr_grid.hpp"
 #include "update_tile.hpp"
 
 namespace hcspmm {
-
-constexpr int kGroup = 16;                                     // lanes per group: one DPP row
 
 template <int VEC> __device__ inline void vzero(float (&a)[VEC])
 {
@@ -62,11 +62,8 @@ struct CsrWork {
     int32_t n_items;
     const int32_t* row_list;
     const uint8_t* route;
-    int32_t rows_per_group;
     int32_t mid_row;            // longest row of the short tier, or of the mid tier when that has no list (a matrix of few rows)
-    uint32_t seg_blocks, mid_blocks, short_blocks;  // workgroups of each tier and slice, padded (surplus ones exit at once)
-    int32_t run, run_mid;       // log2 of the workgroups per XCD-local run of the short and mid tiers (-1: plain order)
-    int32_t n_slices, slice_w;  // column slices of X
+    CsrGrid grid;
     int32_t y_vec;              // Y rows allow vector stores
     int32_t skip_empty;         // a row without non-zeros changes nothing (a column panel that adds to Y)
 };
@@ -269,36 +266,8 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> str
     }
 };
 
-// Block b of a tier of `blocks` workgroups per slice -> (slice, block within the tier).
-// Workgroups go to the eight XCDs round-robin by their linear id, and each XCD has an L2 of its own.
-//  * The tier's blocks are handed out in runs of `run` consecutive ones that stay on one XCD: neighbouring rows -- which
-//    share columns in graphs with any locality -- meet in one L2 close in time, while all XCDs still advance through the
-//    matrix side by side (rows sorted by degree stay balanced).
-//  * With 2, 4 or 8 column slices XCD x works on slice x % n_slices only, so that its L2 holds rows of ONE slice.
-//  * Other slice counts take the slices one after the other.
-__device__ __forceinline__ uint32_t csr_block(uint32_t b, uint32_t blocks, int run, int n_slices, int& slice)
-{
-    const uint32_t x = blockIdx.x & 7;
-    slice = 0;
-    uint32_t nsub = 8, sub = x;
-    if (n_slices > 1) {
-        if (n_slices == 2 || n_slices == 4 || n_slices == 8) {
-            nsub = 8 / n_slices;
-            slice = (int)(x & (n_slices - 1));
-            sub = x / n_slices;
-            run = max(run, 0);
-        } else {
-            slice = (int)(b / blocks);
-            b -= (uint32_t)slice * blocks;
-        }
-    }
-    if (run < 0) return b;
-    const uint32_t q = b >> 3;
-    return ((((q >> run) * nsub) + sub) << run) + (q & ((1u << run) - 1));
-}
-
 // ---- short rows -----------------------------------------------------------------------------
-// A group walks rows_per_group (<= kRowsPerGroup) consecutive items (rows, or entries of row_list) in a
+// A group walks grid.rows_per_group (<= kRowsPerGroup) consecutive items (rows, or entries of row_list) in a
 // single flattened loop: each trip either moves to the next row (storing the finished one) or
 // consumes one batch of the current row, so groups of one wave stay busy on rows of unequal
 // length.  The rows' extents are fetched up front, one per lane.  `done(row, slot, acc)` takes a finished row.
@@ -388,9 +357,9 @@ __device__ __forceinline__ void csr_short_body(uint32_t block, int c_begin, int 
 {
     static_assert(kGroup >= kRowsPerGroup, "a group must be able to hold one row extent per lane");
     const int lig = threadIdx.x % kGroup;
-    const uint32_t i0 = (block * (256 / kGroup) + threadIdx.x / kGroup) * wk.rows_per_group;
+    const uint32_t i0 = (block * (256 / kGroup) + threadIdx.x / kGroup) * wk.grid.rows_per_group;
     if (i0 >= (uint32_t)wk.n_items) return;
-    const int nr = min(wk.rows_per_group, wk.n_items - (int)i0);
+    const int nr = min(wk.grid.rows_per_group, wk.n_items - (int)i0);
     int32_t my_row, my_s, my_e;
     row_extents<G>(i0, lig, nr, wk, a, my_row, my_s, my_e);
     for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
@@ -473,23 +442,23 @@ __global__ __launch_bounds__(256, G::WAVES) void k_csr(CsrWork wk, SpmmArgs a)
     __shared__ float red[256 * G::N];
     uint32_t b = blockIdx.x;
     int slice;
-    if (b < wk.seg_blocks * wk.n_slices) {
-        b = csr_block(b, wk.seg_blocks, -1, wk.n_slices, slice);
-        const int c0 = slice * wk.slice_w;
-        csr_long_body<G>(b, c0, min(a.d, c0 + wk.slice_w), wk, red, a);
+    if (b < wk.grid.seg_blocks * wk.grid.n_slices) {
+        b = csr_block(blockIdx.x, b, wk.grid.seg_blocks, -1, wk.grid.n_slices, slice);
+        const int c0 = slice * wk.grid.slice_w;
+        csr_long_body<G>(b, c0, min(a.d, c0 + wk.grid.slice_w), wk, red, a);
         return;
     }
-    b -= wk.seg_blocks * wk.n_slices;
-    if (b < wk.mid_blocks * wk.n_slices) {
-        b = csr_block(b, wk.mid_blocks, wk.run_mid, wk.n_slices, slice);
-        const int c0 = slice * wk.slice_w;
-        csr_mid_body<G>(b, c0, min(a.d, c0 + wk.slice_w), wk, a);
+    b -= wk.grid.seg_blocks * wk.grid.n_slices;
+    if (b < wk.grid.mid_blocks * wk.grid.n_slices) {
+        b = csr_block(blockIdx.x, b, wk.grid.mid_blocks, wk.grid.run_mid, wk.grid.n_slices, slice);
+        const int c0 = slice * wk.grid.slice_w;
+        csr_mid_body<G>(b, c0, min(a.d, c0 + wk.grid.slice_w), wk, a);
         return;
     }
-    b -= wk.mid_blocks * wk.n_slices;
-    b = csr_block(b, wk.short_blocks, wk.run, wk.n_slices, slice);
-    const int c0 = slice * wk.slice_w;
-    csr_short_body<G>(b, c0, min(a.d, c0 + wk.slice_w), wk, a);
+    b -= wk.grid.mid_blocks * wk.grid.n_slices;
+    b = csr_block(blockIdx.x, b, wk.grid.short_blocks, wk.grid.run, wk.grid.n_slices, slice);
+    const int c0 = slice * wk.grid.slice_w;
+    csr_short_body<G>(b, c0, min(a.d, c0 + wk.grid.slice_w), wk, a);
 }
 
 // The same launch with the update stage fused into the short rows; long and mid rows write their
@@ -502,17 +471,17 @@ __global__ __launch_bounds__(256) void k_csr_fused(CsrWork wk, SpmmArgs a, Updat
     __shared__ int32_t rows16[16];
     uint32_t b = blockIdx.x;
     int slice;
-    if (b < wk.seg_blocks) {
+    if (b < wk.grid.seg_blocks) {
         csr_long_body<G>(b, 0, a.d, wk, lds, a);
         return;
     }
-    b -= wk.seg_blocks;
-    if (b < wk.mid_blocks) {
+    b -= wk.grid.seg_blocks;
+    if (b < wk.grid.mid_blocks) {
         csr_mid_body<G>(b, 0, a.d, wk, a, wk.mid_row);          // the fused tier takes rows up to mid_row
         return;
     }
-    b -= wk.mid_blocks;
-    b = csr_block(b, wk.short_blocks, wk.run, 1, slice);
+    b -= wk.grid.mid_blocks;
+    b = csr_block(blockIdx.x, b, wk.grid.short_blocks, wk.grid.run, 1, slice);
     csr_short_fused_body<G>(b, wk, a, u, lds, rows16);
 }
 
@@ -674,10 +643,10 @@ static int pick_slices(const SpmmArgs& a, const CsrHints& h, int32_t& slice_w)
 }
 
 // The fused update needs the whole aggregated row in one pass of a lane group and a width that the update's K loop takes
-// 16 at a time.
+// 16 at a time, and a launch holds 16 rows per workgroup of no more than 2^26 rows (and what mid and long rows they may be).
 bool update_fusable(const SpmmArgs& a)
 {
-    if (a.d % 16 != 0 || a.d < 16 || a.d > 256) return false;
+    if (a.d % 16 != 0 || a.d < 16 || a.d > 256 || a.n_rows > (1 << 26)) return false;
     const CsrShape sh = pick_shape(a);
     return shape_cols(sh) >= a.d && a.ldy % 4 == 0 && (uintptr_t)a.Y % 16 == 0 && mfma_update_fusable(a);
 }
@@ -700,62 +669,42 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     const int yv = sh.vec < 4 ? sh.vec : 4;
     wk.y_vec = a.ldy % yv == 0 && (uintptr_t)a.Y % (yv * (a.y_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
     wk.skip_empty = a.acc && !a.relu && (const void*)a.acc == (const void*)a.Y && a.ldacc == a.ldy && a.y_dtype == HCSPMM_F32;
-    wk.n_slices = 1;
-    wk.slice_w = a.d;
-    if (!upd) {
-        wk.n_slices = pick_slices(a, hints, wk.slice_w);
-        if (wk.n_slices > 1) {
-            SpmmArgs t = a;
-            t.d = wk.slice_w;
-            const bool wide = sh.wide;
-            sh = pick_shape(t);
-            sh.wide = wide;
-        }
-    }
-    // XCD-local runs (see csr_block): tiers of at least 1024 workgroups are padded to whole rounds of runs over the XCDs
-    // that share a slice; the surplus workgroups exit at once
     int run = 5;
     if (tune().xcd_chunk >= 0) for (run = -1; tune().xcd_chunk >> (run + 1);) ++run;
-    const bool owned = wk.n_slices == 2 || wk.n_slices == 4 || wk.n_slices == 8;
-    const int nsub = owned ? 8 / wk.n_slices : 8;
-    auto pad_runs = [&](int64_t n, int32_t& r) {
-        r = n < 1024 ? -1 : run;
-        const int64_t unit = (int64_t)nsub << (r > 0 ? r : 0);
-        return (uint32_t)((r >= 0 || owned) ? (n + unit - 1) / unit * unit : n);
-    };
-    wk.seg_blocks = (uint32_t)(owned ? ((int64_t)n_segs + nsub - 1) / nsub * nsub : n_segs);
     if (upd) {
-        wk.rows_per_group = 1;
-        wk.mid_blocks = (uint32_t)(((int64_t)n_mid + 3) / 4);
-        wk.short_blocks = pad_runs(((int64_t)n_items + 15) / 16, wk.run);
-        const int64_t blocks = (int64_t)wk.seg_blocks + wk.mid_blocks + wk.short_blocks;
-        if (blocks <= 0) return hipSuccess;
-#define HC_LAUNCH_CSRF(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr_fused<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a, *upd)
+        // one slice, and a workgroup per 16 rows whatever the matrix
+        wk.grid = csr_grid(n_segs, n_mid, n_items, a.d, 1, a.d, run);
+        if (wk.grid.rows_per_group > 1) return hipErrorInvalidValue;        // (update_fusable bounds the rows)
+        if (wk.grid.blocks <= 0) return hipSuccess;
+#define HC_LAUNCH_CSRF(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr_fused<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)wk.grid.blocks), dim3(256), 0, s, wk, a, *upd)
         HC_CSR_DISPATCH(HC_LAUNCH_CSRF)
 #undef HC_LAUNCH_CSRF
         return hipGetLastError();
     }
-    int rpg = 1;
-    if (tune().rpg >= 1 && tune().rpg <= kRowsPerGroup) rpg = tune().rpg;
-    wk.rows_per_group = rpg;
-    const int64_t n_groups = ((int64_t)n_items + rpg - 1) / rpg;
+    int32_t slice_w = a.d;
+    const int n_slices = pick_slices(a, hints, slice_w);
     // While a wave per row and slice still fits the chip at once (256 CUs x 32 waves), every row is a mid row: its non-zeros
     // are spread over four groups instead of queueing in one (2,708 nodes, 32 columns: 5.6 -> 3.6 us of kernel time).
-    if (n_items > 0 && (int64_t)a.n_rows * wk.n_slices <= 8192) {
+    if (n_items > 0 && (int64_t)a.n_rows * n_slices <= 8192) {
         wk.n_mid = a.n_rows;
         wk.mid_rows = nullptr;
         wk.mid_row = hints.long_row;
         wk.n_items = 0;
     }
-    wk.short_blocks = wk.n_items > 0 ? pad_runs((n_groups + 15) / 16, wk.run) : 0;
-    wk.mid_blocks = pad_runs(((int64_t)wk.n_mid + 3) / 4, wk.run_mid);
-    const int64_t blocks = ((int64_t)wk.seg_blocks + wk.mid_blocks + wk.short_blocks) * wk.n_slices;
-    if (blocks <= 0) return hipSuccess;
-#define HC_LAUNCH_CSR(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a)
-#define HC_LAUNCH_PANEL(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W, true>>), dim3((unsigned)blocks), dim3(256), 0, s, wk, a)
+    wk.grid = csr_grid(n_segs, wk.n_mid, wk.n_items, a.d, n_slices, slice_w, run, tune().rpg >= 1 && tune().rpg <= kRowsPerGroup ? tune().rpg : 1);
+    if (wk.grid.blocks <= 0) return hipSuccess;
+    if (wk.grid.n_slices > 1) {
+        SpmmArgs t = a;
+        t.d = wk.grid.slice_w;
+        const bool wide = sh.wide;
+        sh = pick_shape(t);
+        sh.wide = wide;
+    }
+#define HC_LAUNCH_CSR(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)wk.grid.blocks), dim3(256), 0, s, wk, a)
+#define HC_LAUNCH_PANEL(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W, true>>), dim3((unsigned)wk.grid.blocks), dim3(256), 0, s, wk, a)
     if (a.rowend) {
-        // panels are taken for rows of kPanelRowBytes and more: 16-byte vectors, at most two per lane and slice
-        if (sh.vec != (a.x_dtype == HCSPMM_F32 ? 4 : 8) || sh.nv > 2) return hipErrorInvalidValue;
+        // panels are taken for rows of kPanelRowBytes and more: 16-byte vectors, two per lane at most (wider slices take turns)
+        if (sh.vec != (a.x_dtype == HCSPMM_F32 ? 4 : 8)) return hipErrorInvalidValue;
         if (a.x_dtype == HCSPMM_F32) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 0, 4) }
         else if (a.x_dtype == HCSPMM_BF16) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 1, 8) }
         else { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 2, 8) }

@@ -33,3 +33,14 @@ def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True, env=env, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
     assert "host sanitize driver: ok" in r.stdout
+
+
+def test_scalar_path_grids_cover_their_work_and_fit_a_launch(tmp_path):
+    exe = tmp_path / "csr_grid_driver"
+    csrc = os.path.join(ROOT, "paper_2412_08902_amd", "csrc")
+    r = subprocess.run([shutil.which("g++"), "-fsanitize=undefined", "-fno-sanitize-recover=all", "-O2", "-std=c++17", "-I", csrc,
+                        os.path.join(ROOT, "tests", "host_sanitize", "csr_grid_driver.cpp"), "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0 and "csr grid driver: ok" in r.stdout, (r.stdout[-2000:], r.stderr[-4000:])
