@@ -119,7 +119,8 @@ struct Prep {
     int32_t *ncols, *nnzw;
     uint8_t* route;
     int64_t* wptr;
-    unsigned long long *wt, *rt;          // sums per tile of 64 windows
+    unsigned long long *wt, *rt;          // sums per tile of 64 windows: of its windows, of its rows (see prep_bind_sums)
+    unsigned long long *wg, *rg;          // ... and per group of tiles (null: a matrix of few tiles)
     int32_t *short_rows, *mid_rows, *rest_rows;   // row tables to fill (null: skip)
     Segment* segs;
     MultiRow* multi;
@@ -132,7 +133,9 @@ struct PanelArgs {
     int32_t n_rows, n_cols, n_panels, n_tiles, mid_row, long_row;
     const int32_t *rowptr, *colind;
     int32_t* split;                       // n_panels - 1 arrays of n_rows: first non-zero at or beyond the panel's end
-    unsigned long long* sums;             // n_panels * n_tiles * 3
+    unsigned long long* sums;             // panel_sum_words: 3 per panel and tile, and per panel and group of tiles
+    unsigned long long* groups;           // set by launch_panels, as n_groups
+    int32_t n_groups;
     int64_t cap_mid, cap_segs, cap_multi; // entries per panel of
     int32_t* mid_rows;
     Segment* segs;
@@ -141,7 +144,9 @@ struct PanelArgs {
 };
 hipError_t launch_panels(const PanelArgs& p, hipStream_t s);
 size_t prep_tile_count(int32_t W);
-size_t prep_tile_words(int32_t W);        // 64-bit words of wt and rt together (rt follows wt's prep_tile_count() * 8)
+size_t prep_tile_words(int32_t W);        // 64-bit words of all sums of a preparation
+void prep_bind_sums(Prep& p, unsigned long long* words);       // sets n_tiles, wt, rt, wg and rg (from W)
+size_t panel_sum_words(int32_t n_panels, int32_t n_tiles);
 hipError_t launch_prep(const Prep& p, int32_t n_touched, hipStream_t s);
 hipError_t launch_prep_fill(const Prep& p, hipStream_t s);      // another pass over the row tables
 hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s);

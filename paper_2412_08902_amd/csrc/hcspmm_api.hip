@@ -451,6 +451,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     int32_t *sc_n = nullptr, *sc_multi = nullptr, *sc_slots = nullptr;
     int64_t *scan_tmp = nullptr, *pos_a = nullptr, *pos_b = nullptr, *pos_d = nullptr, *totals_dev = nullptr;
     PrepTotals tot, *tot_dev = nullptr;
+    unsigned long long* sums = nullptr;
     int32_t h_err = 0;
     int64_t h_tot[16];
     const int32_t n_touched = carry ? carry->n_touched : 0;
@@ -502,7 +503,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     // (a scalar-only plan counts columns on first request, unless it has to know whether panels pay)
     p->features_complete = (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR && nnz > 0 && n_panels < 2) ? 0 : 1;
     p->rows_sorted = 1;
-    pr.n_rows = n_rows; pr.n_cols = p->n_cols; pr.W = W; pr.n_tiles = (int32_t)prep_tile_count(W); pr.nnz = nnz;
+    pr.n_rows = n_rows; pr.n_cols = p->n_cols; pr.W = W; pr.nnz = nnz;
     pr.rowptr = p->rowptr; pr.colind = p->colind;
     pr.ctl = err;
     HC_ALLOC(tmp, pr.big_list, W);
@@ -524,8 +525,8 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     pr.c0 = p->coef[0]; pr.c1 = p->coef[1]; pr.c2 = p->coef[2];
     pr.mid_row = p->mid_row; pr.long_row = p->long_row; pr.fused_mid_row = p->fused_mid_row;
     pr.ncols = p->ncols; pr.nnzw = p->nnzw; pr.route = p->route; pr.wptr = p->wptr;
-    HC_ALLOC(tmp, pr.wt, prep_tile_words(W));
-    pr.rt = pr.wt + 8 * prep_tile_count(W);
+    HC_ALLOC(tmp, sums, prep_tile_words(W));
+    prep_bind_sums(pr, sums);
     pr.mid_rows = p->mid_rows; pr.rest_rows = p->rest_rows; pr.segs = p->segs; pr.multi = p->multi;
     HC_ALLOC(tmp, tot_dev, 1);
     pr.out = pinned.ptr() ? reinterpret_cast<PrepTotals*>(pinned.device_ptr()) : tot_dev;
@@ -575,7 +576,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         HC_ALLOC(keep, pa.mid_rows, (size_t)n_panels * most_mid);
         HC_ALLOC(keep, pa.segs, (size_t)n_panels * most_segs);
         HC_ALLOC(keep, pa.multi, (size_t)n_panels * most_multi);
-        HC_ALLOC(tmp, pa.sums, (size_t)n_panels * pa.n_tiles * 3);
+        HC_ALLOC(tmp, pa.sums, panel_sum_words(n_panels, pa.n_tiles));
         HC_ALLOC(tmp, pa.out, n_panels);
         pa.split = p->panel_split;
         HC_TRY(launch_panels(pa, stream));

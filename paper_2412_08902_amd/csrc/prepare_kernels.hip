@@ -403,8 +403,11 @@ hipError_t launch_unique_big(int32_t n_big, const int32_t* big_list, int32_t n_r
 // 169,000, most of it in the scans' few wavefronts and in waiting.)  Here every kernel leaves at once when an earlier one
 // has found the CSR arrays unsound, so nothing waits for the host in between; flags are recomputed from the row offsets
 // where they are needed instead of being written, scanned and read back; and a tile of 64 windows (1024 rows) writes its
-// sums once, from which every workgroup of the next kernel adds up its own offset (2,400 tiles, C4's number, are 57 KB
-// out of L2 per workgroup).  The totals go straight into a page of host memory.
+// sums once, from which every workgroup of the next kernel adds up its own offset (2,400 tiles, those of 2.4 M rows, are
+// 153 KB of window sums out of L2 per workgroup).  That grows with the square of the rows, so matrices of more than
+// kDirectTiles tiles also get sums per group of 256 tiles (k_group_sums, a launch more per array of sums), and a workgroup
+// adds up groups and the tiles of its own group: 1.02 G rows are 1 M tiles and 3,900 groups.  The totals go straight into a
+// page of host memory.
 //   k_pre_validate   row offsets; non-zeros per window; windows by size class
 //   k_pre_count*     distinct columns per window by LDS hash sets (bitmap passes beyond their capacity), range of the columns
 //   k_pre_select     selection per window, sums per tile
@@ -413,10 +416,22 @@ hipError_t launch_unique_big(int32_t n_big, const int32_t* big_list, int32_t n_r
 // ------------------------------------------------------------------------------------------------
 constexpr int kTileWindows = 64, kTileRows = kTileWindows * kH;
 constexpr int kBigTakes1kWindows = 16384;
-constexpr int kWt = 8, kRt = 3;                                 // 64-bit sums per tile: windows, rows
+constexpr int kWt = 8, kRt = 4;                                 // 64-bit sums per tile: windows, rows
+constexpr int kGroupTiles = 256, kDirectTiles = 4096;
 
+static int32_t group_count(int32_t n_tiles) { return n_tiles > kDirectTiles ? (n_tiles + kGroupTiles - 1) / kGroupTiles : 0; }
 size_t prep_tile_count(int32_t W) { return (size_t)((W + kTileWindows - 1) / kTileWindows > 0 ? (W + kTileWindows - 1) / kTileWindows : 1); }
-size_t prep_tile_words(int32_t W) { return prep_tile_count(W) * (kWt + kRt); }
+size_t prep_tile_words(int32_t W) { const size_t n = prep_tile_count(W); return (n + (size_t)group_count((int32_t)n)) * (kWt + kRt); }
+void prep_bind_sums(Prep& p, unsigned long long* words)
+{
+    p.n_tiles = (int32_t)prep_tile_count(p.W);
+    const int32_t groups = group_count(p.n_tiles);
+    p.wt = words;
+    p.rt = p.wt + (size_t)kWt * p.n_tiles;
+    p.wg = groups ? p.rt + (size_t)kRt * p.n_tiles : nullptr;
+    p.rg = groups ? p.wg + (size_t)kWt * groups : nullptr;
+}
+size_t panel_sum_words(int32_t n_panels, int32_t n_tiles) { return 3 * (size_t)n_panels * ((size_t)n_tiles + (size_t)group_count(n_tiles)); }
 
 template <class T> __device__ inline T wave_sum(T v)
 {
@@ -435,6 +450,20 @@ __device__ inline unsigned long long block_sum_u64(unsigned long long v, unsigne
     return smem[0] + smem[1] + smem[2] + smem[3];
 }
 
+// the same for several values at once: two barriers for all of them
+template <int N> __device__ inline void block_sums_u64(unsigned long long (&v)[N], unsigned long long* smem /* 4 * N */)
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int i = 0; i < N; ++i) smem[(threadIdx.x >> 6) * N + i] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = smem[i] + smem[N + i] + smem[2 * N + i] + smem[3 * N + i];
+}
+
 // exclusive prefix over the workgroup's 256 threads
 __device__ inline unsigned long long block_scan_u64(unsigned long long v, unsigned long long* smem /* 4 */)
 {
@@ -451,6 +480,39 @@ __device__ inline unsigned long long block_scan_u64(unsigned long long v, unsign
     unsigned long long base = 0;
     for (int i = 0; i < wave; ++i) base += smem[i];
     return base + inc - v;
+}
+
+// sums of 256 tiles each (K values per tile); blockIdx.y: one array of tiles after the other
+template <int K>
+__global__ __launch_bounds__(256) void k_group_sums(int32_t n_tiles, const unsigned long long* __restrict__ tiles, unsigned long long* __restrict__ groups)
+{
+    __shared__ unsigned long long smem[4 * K];
+    const int t = blockIdx.x * kGroupTiles + threadIdx.x;
+    const unsigned long long* __restrict__ in = tiles + ((int64_t)blockIdx.y * n_tiles + t) * K;
+    unsigned long long v[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) v[i] = t < n_tiles ? in[i] : 0ull;
+    block_sums_u64<K>(v, smem);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int i = 0; i < K; ++i) groups[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * K + i] = v[i];
+}
+
+// Calls f(sums, in front of tile `at`) for tiles, or groups of tiles, that make up all tiles together (ALL) or those in
+// front of `at`; the callers `thread` of `threads` share them.  groups: null where there are no group sums.
+template <int K, bool ALL, class F>
+__device__ __forceinline__ void for_sums(const unsigned long long* __restrict__ tiles, const unsigned long long* __restrict__ groups, int n_tiles,
+                                         int at, int thread, int threads, F&& f)
+{
+    int first = 0, last = ALL ? n_tiles : at;
+    if (groups) {
+        const int own = at / kGroupTiles, n = ALL ? (n_tiles + kGroupTiles - 1) / kGroupTiles : own;
+        for (int g = thread; g < n; g += threads)
+            if (g != own) f(groups + (int64_t)g * K, g < own);
+        first = own * kGroupTiles;
+        last = min(last, first + kGroupTiles);
+    }
+    for (int t = first + thread; t < last; t += threads) f(tiles + (int64_t)t * K, t < at);
 }
 
 __global__ __launch_bounds__(256) void k_pre_validate(Prep p)
@@ -631,7 +693,8 @@ __device__ inline int window_route(const Prep& p, int mode, long long nc, long l
     return z < 0 ? 1 : 0;
 }
 
-// windows on the matrix path | ... of the wave-per-window kernel | medium | wide, 16 bits each (a tile has 64 windows)
+// windows on the matrix path | ... of the wave-per-window kernel | medium | wide, 16 bits each (a tile has 64 windows, a
+// group of tiles 16,384)
 __device__ inline unsigned long long window_counts(int r, long long nc)
 {
     if (!r) return 0ull;
@@ -720,21 +783,18 @@ __device__ inline unsigned long long seg_counts(const RowClass& c)
 
 __global__ __launch_bounds__(256) void k_pre_rows(Prep p)
 {
-    __shared__ unsigned long long smem[4];
+    __shared__ unsigned long long smem[16];
     __shared__ uint8_t s_route[kTileWindows], s_wide[kTileWindows];
     if (*p.ctl) return;
     const int tile = blockIdx.x;
-    unsigned long long before = 0, behind = 0, on_matrix = 0;
-    for (int t = threadIdx.x; t < p.n_tiles; t += 256) {
-        on_matrix += p.wt[(int64_t)t * kWt + 1];
-        const unsigned long long nc = p.wt[(int64_t)t * kWt];
-        if (t < tile) before += nc;
-        else behind += nc;
-    }
-    before = block_sum_u64(before, smem);
-    if (p.scalar_exec) behind = block_sum_u64(behind, smem);
-    on_matrix = block_sum_u64(on_matrix, smem);
-    const int mode = effective_mode(p, on_matrix);
+    unsigned long long all[3] = {0, 0, 0};                      // columns in front of the tile, from it on; non-zeros on the matrix path
+    for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, tile, threadIdx.x, 256, [&](const unsigned long long* v, bool in_front) {
+        all[2] += v[1];
+        all[in_front ? 0 : 1] += v[0];
+    });
+    block_sums_u64<3>(all, smem);
+    const unsigned long long before = all[0];
+    const int mode = effective_mode(p, all[2]);
     if (threadIdx.x < kTileWindows) {
         const int32_t w = tile * kTileWindows + threadIdx.x;
         const long long nc = w < p.W ? p.ncols[w] : 0, nz = w < p.W ? p.nnzw[w] : 0;
@@ -755,49 +815,40 @@ __global__ __launch_bounds__(256) void k_pre_rows(Prep p)
         if (p.W == 0 && threadIdx.x == 0) p.wptr[0] = 0;
     }
     __syncthreads();
-    const bool all_scalar = scattered_rows(p, (int64_t)(before + behind));
+    const bool all_scalar = scattered_rows(p, (int64_t)(all[0] + all[1]));
     if (tile == 0 && threadIdx.x == 0) p.ctl[7] = all_scalar ? 1 : 0;
-    unsigned long long a = 0, b = 0, len_long = 0;
+    unsigned long long sum[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int rl = threadIdx.x * 4 + j;
         const int64_t i = (int64_t)tile * kTileRows + rl;
         if (i >= p.n_rows) break;
         const RowClass c = row_class(p, p.rowptr[i + 1] - p.rowptr[i], all_scalar ? 0 : s_route[rl / kH], s_wide[rl / kH]);
-        a += row_counts(c);
-        b += seg_counts(c);
-        len_long += (unsigned long long)c.len_long;
+        sum[0] += (unsigned long long)c.is_short | (unsigned long long)c.is_mid << 32;
+        sum[1] += (unsigned long long)c.rest | (unsigned long long)(c.n_seg > 1) << 32;
+        sum[2] += seg_counts(c);
+        sum[3] += (unsigned long long)c.len_long;
     }
-    a = block_sum_u64(a, smem);
-    b = block_sum_u64(b, smem);
-    len_long = block_sum_u64(len_long, smem);
-    if (threadIdx.x == 0) {
-        p.rt[(int64_t)tile * kRt] = a;
-        p.rt[(int64_t)tile * kRt + 1] = b;
-        p.rt[(int64_t)tile * kRt + 2] = len_long;
-    }
+    block_sums_u64<4>(sum, smem);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p.rt[(int64_t)tile * kRt + i] = sum[i];
 }
 
 // Fills the row tables whose pointers are set; one workgroup behind the last tile's writes the totals (when p.out is set).
 __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
 {
-    __shared__ unsigned long long smem[4];
+    __shared__ unsigned long long smem[4 * 7];
     const int tile = blockIdx.x;
     const bool last = tile == p.n_tiles;
     if (*p.ctl) {
         if (last && threadIdx.x == 0 && p.out) p.out->err = *p.ctl;
         return;
     }
-    unsigned long long sm = 0, rm = 0, seg = 0;                 // short | mid, rest | multi, segments | partial rows in front of the tile
-    for (int t = threadIdx.x; t < tile; t += 256) {
-        const unsigned long long a = p.rt[(int64_t)t * kRt], b = p.rt[(int64_t)t * kRt + 1];
-        sm += (a & 0xffffull) | (a >> 16 & 0xffffull) << 32;
-        rm += (a >> 32 & 0xffffull) | (a >> 48) << 32;
-        seg += b;
-    }
-    sm = block_sum_u64(sm, smem);
-    rm = block_sum_u64(rm, smem);
-    seg = block_sum_u64(seg, smem);
+    unsigned long long front[3] = {0, 0, 0};                    // short | mid, rest | multi, segments | partial rows in front of the tile
+    for_sums<kRt, false>(p.rt, p.rg, p.n_tiles, tile, threadIdx.x, 256, [&](const unsigned long long* v, bool) { front[0] += v[0]; front[1] += v[1]; front[2] += v[2]; });
+    block_sums_u64<3>(front, smem);
+    const unsigned long long sm = front[0], rm = front[1], seg = front[2];
     RowClass c[4];
     int32_t start[5];
     unsigned long long a = 0, b = 0;
@@ -848,22 +899,21 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
     }
     if (!last || !p.out) return;
     // what is in front of the place behind the last tile are the row totals; the window totals come from the tile sums too
-    unsigned long long v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int t = threadIdx.x; t < p.n_tiles; t += 256) v[7] += p.wt[(int64_t)t * kWt + 1];
-    const int set = counts_set(p, effective_mode(p, block_sum_u64(v[7], smem)));
-    for (int t = threadIdx.x; t < p.n_tiles; t += 256) {
-        v[0] += p.wt[(int64_t)t * kWt];
-        v[1] += p.rt[(int64_t)t * kRt + 2];
-        if (set < 0) continue;
-        const unsigned long long n = p.wt[(int64_t)t * kWt + 2 + 3 * set];
-        v[2] += p.wt[(int64_t)t * kWt + 1 + 3 * set];
+    unsigned long long v[7] = {0, 0, 0, 0, 0, 0, 0}, on_matrix = 0;
+    for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, p.n_tiles, threadIdx.x, 256, [&](const unsigned long long* u, bool) { on_matrix += u[1]; });
+    const int set = counts_set(p, effective_mode(p, block_sum_u64(on_matrix, smem)));
+    for_sums<kRt, true>(p.rt, p.rg, p.n_tiles, p.n_tiles, threadIdx.x, 256, [&](const unsigned long long* u, bool) { v[1] += u[3]; });
+    for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, p.n_tiles, threadIdx.x, 256, [&](const unsigned long long* u, bool) {
+        v[0] += u[0];
+        if (set < 0) return;
+        const unsigned long long n = u[2 + 3 * set];
+        v[2] += u[1 + 3 * set];
         v[3] += (n & 0xffffull) | (n >> 16 & 0xffffull) << 32;
         v[4] += (n >> 32 & 0xffffull) | (n >> 48) << 32;
-        v[5] += p.wt[(int64_t)t * kWt + 3 + 3 * set];
-        v[6] += p.wt[(int64_t)t * kWt + (set == 0 ? 7 : 0)];
-    }
-#pragma unroll
-    for (int k = 0; k < 7; ++k) v[k] = block_sum_u64(v[k], smem);
+        v[5] += u[3 + 3 * set];
+        v[6] += u[set == 0 ? 7 : 0];
+    });
+    block_sums_u64<7>(v, smem);
     if (threadIdx.x == 0) {
         PrepTotals t{};
         t.total_ncols = (int64_t)v[0]; t.nnz_long = (int64_t)v[1]; t.nnz_mfma = (int64_t)v[2]; t.wide_cols = (int64_t)v[5]; t.mfma_cols = (int64_t)v[6];
@@ -885,14 +935,14 @@ __global__ __launch_bounds__(256) void k_pre_windows(Prep p, int32_t* __restrict
     const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (tile >= p.n_tiles) return;
     unsigned long long on_matrix = 0, lo = 0, hi = 0;           // matrix | small, medium | wide windows in front of the tile
-    for (int t = lane; t < p.n_tiles; t += 64) on_matrix += p.wt[(int64_t)t * kWt + 1];
+    for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, tile, lane, 64, [&](const unsigned long long* v, bool) { on_matrix += v[1]; });
     const int set = counts_set(p, effective_mode(p, wave_sum(on_matrix)));
     if (set >= 0)
-        for (int t = lane; t < tile; t += 64) {
-            const unsigned long long n = p.wt[(int64_t)t * kWt + 2 + 3 * set];
+        for_sums<kWt, false>(p.wt, p.wg, p.n_tiles, tile, lane, 64, [&](const unsigned long long* v, bool) {
+            const unsigned long long n = v[2 + 3 * set];
             lo += (n & 0xffffull) | (n >> 16 & 0xffffull) << 32;
             hi += (n >> 32 & 0xffffull) | (n >> 48) << 32;
-        }
+        });
     lo = wave_sum(lo);
     hi = wave_sum(hi);
     const int32_t w = tile * kTileWindows + lane;
@@ -941,7 +991,10 @@ hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
         hipLaunchKernelGGL(k_pre_sorted, dim3((unsigned)blocks), dim3(256), 0, s, p);
     }
     hipLaunchKernelGGL(k_pre_select, dim3((unsigned)(p.n_tiles + 3) / 4), dim3(256), 0, s, p);
+    const int32_t groups = group_count(p.n_tiles);
+    if (groups) hipLaunchKernelGGL(k_group_sums<kWt>, dim3((unsigned)groups), dim3(256), 0, s, p.n_tiles, p.wt, p.wg);
     hipLaunchKernelGGL(k_pre_rows, dim3((unsigned)p.n_tiles), dim3(256), 0, s, p);
+    if (groups) hipLaunchKernelGGL(k_group_sums<kRt>, dim3((unsigned)groups), dim3(256), 0, s, p.n_tiles, p.rt, p.rg);
     hipLaunchKernelGGL(k_pre_fill, dim3((unsigned)p.n_tiles + 1), dim3(256), 0, s, p);
     return hipGetLastError();
 }
@@ -1454,36 +1507,31 @@ __device__ inline PanelRow panel_row(const PanelArgs& p, int q, int64_t i)
 // sums per panel and tile of 1024 rows: mid rows | rows of several segments, segments | partial rows, non-zeros
 __global__ __launch_bounds__(256) void k_panel_count(PanelArgs p)
 {
-    __shared__ unsigned long long smem[4];
+    __shared__ unsigned long long smem[12];
     const int tile = blockIdx.x, q = blockIdx.y;
-    unsigned long long a = 0, b = 0, n = 0;
+    unsigned long long sum[3] = {0, 0, 0};
     for (int j = 0; j < 4; ++j) {
         const PanelRow r = panel_row(p, q, (int64_t)tile * kTileRows + j * 256 + threadIdx.x);
-        a += (unsigned long long)r.is_mid | (unsigned long long)(r.n_seg > 1) << 32;
-        b += (unsigned long long)r.n_seg | (unsigned long long)(r.n_seg > 1 ? r.n_seg : 0) << 32;
-        n += (unsigned long long)(r.e - r.s);
+        sum[0] += (unsigned long long)r.is_mid | (unsigned long long)(r.n_seg > 1) << 32;
+        sum[1] += (unsigned long long)r.n_seg | (unsigned long long)(r.n_seg > 1 ? r.n_seg : 0) << 32;
+        sum[2] += (unsigned long long)(r.e - r.s);
     }
-    a = block_sum_u64(a, smem);
-    b = block_sum_u64(b, smem);
-    n = block_sum_u64(n, smem);
-    if (threadIdx.x == 0) {
-        unsigned long long* __restrict__ t = p.sums + ((int64_t)q * p.n_tiles + tile) * 3;
-        t[0] = a; t[1] = b; t[2] = n;
-    }
+    block_sums_u64<3>(sum, smem);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) p.sums[((int64_t)q * p.n_tiles + tile) * 3 + i] = sum[i];
 }
 
 __global__ __launch_bounds__(256) void k_panel_fill(PanelArgs p)
 {
-    __shared__ unsigned long long smem[4];
+    __shared__ unsigned long long smem[12];
     const int tile = blockIdx.x, q = blockIdx.y;
-    unsigned long long a = 0, b = 0, n = 0;                     // in front of the tile
-    for (int t = threadIdx.x; t < tile; t += 256) {
-        const unsigned long long* __restrict__ u = p.sums + ((int64_t)q * p.n_tiles + t) * 3;
-        a += u[0]; b += u[1]; n += u[2];
-    }
-    a = block_sum_u64(a, smem);
-    b = block_sum_u64(b, smem);
-    n = block_sum_u64(n, smem);
+    unsigned long long front[3] = {0, 0, 0};
+    for_sums<3, false>(p.sums + (int64_t)q * p.n_tiles * 3, p.groups ? p.groups + (int64_t)q * p.n_groups * 3 : nullptr, p.n_tiles, tile, threadIdx.x, 256,
+                       [&](const unsigned long long* u, bool) { front[0] += u[0]; front[1] += u[1]; front[2] += u[2]; });
+    block_sums_u64<3>(front, smem);
+    unsigned long long a = front[0], b = front[1];
+    const unsigned long long n = front[2];
     if (tile == p.n_tiles) {                                    // behind the last tile: the totals
         if (threadIdx.x == 0) p.out[q] = PanelTotals{(int64_t)n, (int64_t)(b >> 32), (int32_t)a, (int32_t)b, (int32_t)(a >> 32), 0};
         return;
@@ -1504,10 +1552,14 @@ __global__ __launch_bounds__(256) void k_panel_fill(PanelArgs p)
     }
 }
 
-hipError_t launch_panels(const PanelArgs& p, hipStream_t s)
+hipError_t launch_panels(const PanelArgs& p_, hipStream_t s)
 {
+    PanelArgs p = p_;
+    p.n_groups = group_count(p.n_tiles);
+    p.groups = p.n_groups ? p.sums + 3 * (size_t)p.n_panels * p.n_tiles : nullptr;
     hipLaunchKernelGGL(k_panel_split, dim3((unsigned)(((int64_t)p.n_rows + 255) / 256)), dim3(256), 0, s, p);
     hipLaunchKernelGGL(k_panel_count, dim3((unsigned)p.n_tiles, (unsigned)p.n_panels), dim3(256), 0, s, p);
+    if (p.groups) hipLaunchKernelGGL(k_group_sums<3>, dim3((unsigned)p.n_groups, (unsigned)p.n_panels), dim3(256), 0, s, p.n_tiles, p.sums, p.groups);
     hipLaunchKernelGGL(k_panel_fill, dim3((unsigned)p.n_tiles + 1, (unsigned)p.n_panels), dim3(256), 0, s, p);
     return hipGetLastError();
 }

@@ -91,3 +91,59 @@ def test_update_of_more_windows_than_the_pinned_list_holds():
     a, b = hc.hcspmm_plan_export(plan), hc.hcspmm_plan_export(fresh)
     for k in KEYS:
         assert np.array_equal(a[k], b[k]), k
+
+
+# one row behind the last matrix whose tiles of 1024 rows are added up directly, and whole and ragged groups of 256 tiles
+@pytest.mark.parametrize("n", [4096 * 1024, 4096 * 1024 + 1, 4352 * 1024 + 17])
+def test_more_tiles_than_are_added_up_directly(n):
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    rng = np.random.default_rng(n)
+    lengths = rng.integers(0, 3, n)
+    heavy = rng.choice(n, 3000, replace=False)
+    lengths[heavy] = rng.choice([128, 129, 257, 1024, 1025, 2049], heavy.shape[0])
+    g = ragged(lengths, 5000, n)
+    coef = [1, 300, -300]                                         # both routes get about half of the windows
+    check_plan(g, 3, sel_coef=coef)
+    X = rng.standard_normal((g.n_cols, 4)).astype(np.float32)
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *device_graph(g), route_mode=3, sel_coef=coef)
+    assert min(hc.hcspmm_plan_info(plan)[k] for k in ("n_mfma_small", "n_mid_rows", "n_long_rows", "n_short_rows")) > 0
+    Y = torch.full((n, 4), float("nan"), device="cuda")
+    hc.hcspmm_spmm(plan, torch.from_numpy(X).cuda(), Y)
+    ref, bound = (oracle.spmm(g.rowptr, g.colind, g.vals, X, use_abs=b) for b in (False, True))
+    assert_close(Y.cpu().numpy().astype(np.float64), ref, bound, 1e-5, "spmm")
+
+
+def test_panels_of_more_tiles_than_are_added_up_directly():
+    """4.2 M rows of 150 non-zeros (631 M in all) in column panels: short rows, rows that lie in one panel, rows of several
+    segments; sampled rows in 64 bits."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    n, n_cols, d = 4097 * 1024 + 5, 120_000, 32
+    length = torch.full((n,), 150, dtype=torch.int64, device="cuda")
+    length[::40_000] = 3000
+    rowptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(length, 0, out=rowptr[1:])
+    col = torch.empty(int(rowptr[-1]), dtype=torch.int32, device="cuda")
+    for r0 in range(0, n, 1 << 20):                               # (in pieces: a 64-bit row number per non-zero is 5 GB)
+        r = torch.arange(r0, min(n, r0 + (1 << 20)), device="cuda")
+        row = r.repeat_interleave(length[r])
+        j = torch.arange(int(rowptr[r[0]]), int(rowptr[r[-1] + 1]), device="cuda") - rowptr[row]
+        step = torch.where(length[row] == 3000, 40, torch.where(row % 97 == 0, 150, 800))
+        col[int(rowptr[r[0]]):int(rowptr[r[-1] + 1])] = (j * step + (row * 7 + j * 13) % step).to(torch.int32)
+    vals = torch.rand(col.numel(), device="cuda") - 0.5
+    rp = rowptr.to(torch.int32)
+    X = torch.randn((n_cols, d), device="cuda")
+    Y = torch.full((n, d), float("nan"), device="cuda")
+    plan = hc.hcspmm_prepare(n, n_cols, rp, col, vals, route_mode=1, d_hint=d)
+    hc.hcspmm_spmm(plan, X, Y)
+    sample = torch.cat([torch.arange(0, n, 40_000), torch.arange(0, n, 97 * 331), torch.arange(3, n, 9973), torch.arange(n - 40, n)]).unique().cuda()
+    for r in sample.split(512):
+        row = torch.arange(r.numel(), device="cuda").repeat_interleave(length[r])
+        first = torch.cumsum(length[r], 0) - length[r]
+        k = rowptr[r][row] + torch.arange(row.numel(), device="cuda") - first[row]
+        terms = vals[k].double()[:, None] * X[col[k].long()].double()
+        ref = torch.zeros((r.numel(), d), dtype=torch.float64, device="cuda").index_add_(0, row, terms)
+        bound = torch.zeros_like(ref).index_add_(0, row, terms.abs())
+        assert_close(Y[r].double().cpu().numpy(), ref.cpu().numpy(), bound.cpu().numpy(), 1e-5, "panels")
+    assert torch.isfinite(Y).all()
