@@ -96,22 +96,27 @@ hipError_t exclusive_scan_multi(const ScanMulti& m, int64_t n, int64_t* totals_d
 struct PrepTotals {
     int64_t total_ncols, nnz_mfma, wide_cols /* columns of wide matrix-path windows */, mfma_cols /* of all of them */, nnz_long, n_slots;
     int32_t n_mfma, n_mfma_small, n_mfma_mid, n_mfma_big, n_short, n_mid, n_rest, n_multi, n_segs;
-    int32_t all_scalar;                   // every window is executed on the scalar path (see scattered_rows)
+    int32_t all_scalar;                   // every window runs on the scalar path, 2: in column panels (see scalar_form)
+    int32_t sample_distinct;              // see sample_share
     int32_t n_big_list, n_huge_list;      // windows above kUniqueSmallCap / kCountMidCap non-zeros
     int32_t err;                          // 1 rowptr[0], 2 rowptr[n_rows], 4 decreasing rowptr, 8 column out of range
 };
+constexpr int kPrepCtl = 16;
+constexpr int32_t kSampleSlices = 16384, kSamplePanels = 65536;   // non-zeros per stretch of the sample (see build_plan)
 struct Prep {
     int32_t n_rows, n_cols, W, n_tiles;
     int64_t nnz;
     const int32_t *rowptr, *colind;
-    int32_t* ctl;                         // zeroed: [0] errors, [1] [2] lengths of big_list, huge_list, [3] of count_1k
+    int32_t* ctl;                         // kPrepCtl zeros: [0] errors, [1] [2] lengths of big_list, huge_list, [3] of count_1k,
+                                          // [4] [5] of count_mid, count_huge, [6] unsorted rows, [7] all scalar, [8] sample
     int32_t *big_list, *huge_list;        // every window of the two classes
     int32_t *count_1k, *count_mid, *count_huge, *n_count_mid, *n_count_huge;   // windows whose columns are still to be counted
     const int32_t* touched;               // windows to count (null: all)
     const int32_t* old_ncols;             // counts carried over for the others
     int32_t features;                     // distinct columns are wanted
-    int32_t check_sorted;                 // also find out whether every row's columns ascend (ctl[6] otherwise)
-    int32_t scalar_exec;                  // row tables for a plan that runs every window on the scalar path, if it is one (scattered_rows)
+    int32_t sample_len;                   // non-zeros per stretch of the sample, nnz at most (0: no sample)
+    int32_t panels_from;                  // panels are asked for: from this percentage of distinct columns in the sample on (0: not)
+    int32_t scalar_exec;                  // every window may run on the scalar path (see scalar_form)
     int32_t big_takes_1k;                 // set by launch_prep
     int32_t mode;
     long long c0, c1, c2;
@@ -147,6 +152,7 @@ size_t prep_tile_count(int32_t W);
 size_t prep_tile_words(int32_t W);        // 64-bit words of all sums of a preparation
 void prep_bind_sums(Prep& p, unsigned long long* words);       // sets n_tiles, wt, rt, wg and rg (from W)
 size_t panel_sum_words(int32_t n_panels, int32_t n_tiles);
+double sample_share(const Prep& p, int32_t distinct);          // distinct columns per non-zero of the sampled stretches (1: no sample)
 hipError_t launch_prep(const Prep& p, int32_t n_touched, hipStream_t s);
 hipError_t launch_prep_fill(const Prep& p, hipStream_t s);      // another pass over the row tables
 hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s);
@@ -401,6 +407,7 @@ struct hcspmm_plan {
     // column panels (n_panels > 1): the scalar path takes the columns panel by panel; scalar_exec: windows that the selector
     // sends to the matrix path run on the scalar path as well, and their condensed structure is built on export only
     int32_t n_panels, scalar_exec;
+    int32_t local;                  // neighbouring rows are known to share most of their columns (see build_plan)
     int32_t* panel_split;
     struct { hcspmm::PanelTotals t; int32_t* mid_rows; hcspmm::Segment* segs; hcspmm::MultiRow* multi; } panel[hcspmm::kMaxPanels];
     float* acc_rows;                // lazily sized: n_rows x d sums between panels when the output is not fp32

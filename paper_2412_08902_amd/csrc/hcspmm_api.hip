@@ -410,12 +410,13 @@ static bool choice_is_ours(const hcspmm_options& o)
 {
     return !o.use_custom_selector && o.matrix_kernels == HCSPMM_MATRIX_AUTO && !tune().runs;
 }
+static int32_t d_or_default(const hcspmm_options& o) { return o.d_hint > 0 ? o.d_hint : 64; }
 static int panel_count(const hcspmm_plan* p)
 {
     const hcspmm_options& o = p->opt;
     if ((o.route_mode != HCSPMM_ROUTE_HYBRID && o.route_mode != HCSPMM_ROUTE_ALL_CSR) || !choice_is_ours(o) || p->n_rows == 0) return 0;
     const bool f32 = o.mfma_dtype == HCSPMM_F32;
-    const int64_t row_bytes = o.d_hint > 0 ? (int64_t)o.d_hint * (f32 ? 4 : 2) : 128;
+    const int64_t row_bytes = (int64_t)d_or_default(o) * (f32 ? 4 : 2);
     if (row_bytes < kPanelRowBytes) return 0;
     const double degree = (double)p->nnz / p->n_rows;
     if (degree < (!f32 && row_bytes < 2 * kPanelRowBytes ? 400.0 : 150.0)) return 0;
@@ -424,7 +425,7 @@ static int panel_count(const hcspmm_plan* p)
     return n >= 2 && 4.0 * n >= want ? n : 0;
 }
 
-// Whether windows that the selector sends to the matrix path may run on the scalar path (see scattered_rows in
+// Whether windows that the selector sends to the matrix path may run on the scalar path (see scalar_form in
 // prepare_kernels.hip for when they do).  The scalar path's column slices live in L2 as long as the graph is not too large:
 // 300,000 rows of 60, 128 columns, fp32: 1077 -> 918 us, bf16: 590 -> 457 us; 1 M rows of 20: 1453 -> 1355 us; but 1 M rows
 // of 100: 5992 -> 6441 us, 2 M of 40: 5455 -> 5486 us.
@@ -434,6 +435,15 @@ static bool scalar_candidate(const hcspmm_plan* p)
     if ((int64_t)p->opt.d_hint * (p->opt.mfma_dtype == HCSPMM_F32 ? 4 : 2) % 128 != 0) return false;
     return p->opt.route_mode == HCSPMM_ROUTE_HYBRID && choice_is_ours(p->opt) && p->n_rows > 0 && p->nnz <= 40000000;
 }
+
+// The sample of a preparation (sample_stretch in prepare_kernels.hip).  Where it is small, rows that run side by side share
+// most of their columns and X rows are taken whole: column slices gain no hits (p->local).  Communities of 256 to 1,024 nodes
+// have 0.05 to 0.14 distinct columns per non-zero in stretches of 16,384 and 0.03 to 0.05 in stretches of 65,536 (131,072 rows
+// of 50, 128 columns, fp32, scalar-only plan: 141 -> 111 us, 400,000 of 83: 982 -> 770 us), communities of 4,096 0.10 in the
+// long ones (2036 us in panels, 1442 in slices, 1264 whole); communities of 64 next to scattered edges 0.27 in the short
+// ones, power-law graphs 0.53 and more (0.4 in the long ones).  A scalar-only plan counts no columns and goes by the short
+// sample, taken beside its check of the columns (169,343 rows of 15: 44 -> 50 us); a plan that may take panels has the long one.
+constexpr int64_t kSampleNnz = 1 << 20;     // below, a scalar-only preparation is little but its launches
 
 static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCarry* carry = nullptr)
 {
@@ -468,7 +478,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     {
         // the scratch arrays that every preparation needs: one allocation
         const size_t i32 = sizeof(int32_t);
-        const size_t total = DevAlloc::padded(8 * i32) + 5 * DevAlloc::padded((size_t)W * i32) +
+        const size_t total = DevAlloc::padded(kPrepCtl * i32) + 5 * DevAlloc::padded((size_t)W * i32) +
                              DevAlloc::padded(prep_tile_words(W) * 8) + DevAlloc::padded(sizeof(PrepTotals)) + 16 * 256 +
                              DevAlloc::padded((size_t)n_touched * i32);
         if (tmp.reserve(total) != hipSuccess) {
@@ -486,8 +496,8 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     HC_ALLOC(keep, p->segs, most_segs);
     HC_ALLOC(keep, p->multi, most_multi);
     HC_ALLOC(keep, p->rest_rows, most_rest);
-    HC_ALLOC(tmp, err, 8);
-    HC_TRY(hipMemsetAsync(err, 0, 8 * sizeof(int32_t), stream));
+    HC_ALLOC(tmp, err, kPrepCtl);
+    HC_TRY(hipMemsetAsync(err, 0, kPrepCtl * sizeof(int32_t), stream));
     if (carry && n_touched > 0) {
         if (zero_copy) {
             memcpy(pinned.ptr() + PinnedPage::kList, carry->touched, (size_t)n_touched * sizeof(int32_t));
@@ -500,8 +510,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     // A scalar-only plan never reads the condensed structure (the paper has no preprocessing for its
     // scalar path either): its window features stay zero here and are computed when first asked for
     // (hcspmm_plan_info / hcspmm_plan_export), which makes prepare cheap for matrices that keep changing.
-    // (a scalar-only plan counts columns on first request, unless it has to know whether panels pay)
-    p->features_complete = (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR && nnz > 0 && n_panels < 2) ? 0 : 1;
+    p->features_complete = (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR && nnz > 0) ? 0 : 1;
     p->rows_sorted = 1;
     pr.n_rows = n_rows; pr.n_cols = p->n_cols; pr.W = W; pr.nnz = nnz;
     pr.rowptr = p->rowptr; pr.colind = p->colind;
@@ -519,8 +528,10 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         pr.n_count_mid = err + 4; pr.n_count_huge = err + 5;
     }
     pr.features = p->features_complete;
-    pr.check_sorted = n_panels > 1;
-    pr.scalar_exec = n_panels > 1 || scalar_candidate(p);
+    if (n_panels > 1) pr.panels_from = (int64_t)d_or_default(p->opt) * (p->opt.mfma_dtype == HCSPMM_F32 ? 4 : 2) % 128 == 0 ? 50 : 40;
+    pr.sample_len = n_panels > 1 ? kSamplePanels : p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR && nnz >= kSampleNnz ? kSampleSlices : 0;
+    if (pr.sample_len > nnz) pr.sample_len = (int32_t)nnz;
+    pr.scalar_exec = scalar_candidate(p);
     pr.mode = p->opt.route_mode;
     pr.c0 = p->coef[0]; pr.c1 = p->coef[1]; pr.c2 = p->coef[2];
     pr.mid_row = p->mid_row; pr.long_row = p->long_row; pr.fused_mid_row = p->fused_mid_row;
@@ -565,8 +576,9 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     // windows; scalar-path windows never read theirs at SpMM time and get it on export only, and a
     // plan without matrix-path windows does not even allocate the arrays
     p->condensed_complete = nnz == 0 ? 1 : 0;
-    p->scalar_exec = tot.all_scalar;
-    p->n_panels = n_panels > 1 && p->scalar_exec ? n_panels : 0;
+    p->scalar_exec = tot.all_scalar != 0;
+    p->n_panels = tot.all_scalar == 2 ? n_panels : 0;
+    p->local = sample_share(pr, tot.sample_distinct) < (pr.sample_len > kSampleSlices ? 0.15 : 0.2);
     if (p->n_panels > 1) {
         PanelArgs pa{};
         pa.n_rows = n_rows; pa.n_cols = p->n_cols; pa.n_panels = n_panels; pa.n_tiles = pr.n_tiles;
@@ -962,11 +974,11 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         HC_HIP(launch_mfma_small(a, p->n_mfma_small, p->mfma_small_desc, p->wcols, p->erc, s_small, upd));
         if (ev) HC_HIP(hipEventRecord(ev[2], stream));
     }
-    // (the windows' distinct columns against their non-zeros say how much neighbouring rows share; a scalar-only plan does
-    // not count them)
+    // (the windows' distinct columns against their non-zeros say how much the rows of a window share; a scalar-only plan does
+    // not count them and goes by its sample)
     const int64_t nnz_scalar = p->nnz - (p->scalar_exec ? 0 : p->nnz_mfma), n_scalar = p->scalar_exec ? p->W : p->n_csr;
     const int64_t cols_scalar = p->total_ncols - (p->scalar_exec ? 0 : p->mfma_ncols);
-    const bool scattered = p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * cols_scalar > 6 * nnz_scalar;
+    const bool scattered = !p->local && (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * cols_scalar > 6 * nnz_scalar);
     const CsrHints hints{nnz_scalar, n_scalar * kH, scattered, p->long_row};
     const uint8_t* route = p->scalar_exec ? nullptr : p->route;
     if (upd && !windows_only)        // the fused launch walks every row: its tile tier also takes the shorter mid rows

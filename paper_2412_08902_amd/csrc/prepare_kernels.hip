@@ -410,6 +410,7 @@ hipError_t launch_unique_big(int32_t n_big, const int32_t* big_list, int32_t n_r
 // page of host memory.
 //   k_pre_validate   row offsets; non-zeros per window; windows by size class
 //   k_pre_count*     distinct columns per window by LDS hash sets (bitmap passes beyond their capacity), range of the columns
+//   k_pre_sorted, k_pre_sample   where they decide something: whether rows ascend, how much neighbouring rows share
 //   k_pre_select     selection per window, sums per tile
 //   k_pre_rows       launch guard, route and list offset per window, row classes, sums per tile
 //   k_pre_fill       row lists, segments of long rows, totals
@@ -537,17 +538,58 @@ __global__ __launch_bounds__(256) void k_pre_validate(Prep p)
     else if (n > kCountTinyCap && !p.touched) p.count_1k[atomicAdd(p.ctl + 3, 1)] = w;
 }
 
-// columns only (a plan that counts nothing still checks them)
-__global__ __launch_bounds__(256) void k_validate_cols(int32_t n_cols, int64_t nnz, const int32_t* __restrict__ colind,
-                                                       int32_t* __restrict__ err)
+// Distinct columns of kSamples stretches of p.sample_len consecutive non-zeros, spread over the matrix, added up in ctl[8]: how
+// many X rows the rows that run side by side share (windows of 16 rows say nothing of that: a community of a few thousand
+// nodes is as scattered inside a window as a power-law graph).  One bit per column of a set of 32 * WORDS bits, eight times
+// the stretch; columns that share a bit hide some six in a hundred distinct ones at most.
+constexpr int kSamples = 64;
+template <int NT, int WORDS>
+__device__ inline void sample_stretch(const Prep& p, int s, uint32_t* bm /* WORDS + 1 */)
 {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    bool bad = false;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nnz; k += stride) {
-        const int32_t c = colind[k];
-        bad |= (c < 0 || c >= n_cols);
+    const int64_t k0 = (p.nnz - p.sample_len) * s / (kSamples - 1);
+    for (int i = threadIdx.x; i <= WORDS; i += NT) bm[i] = 0u;
+    __syncthreads();
+    constexpr int AHEAD = 16;
+    for (int i = threadIdx.x; i < p.sample_len; i += NT * AHEAD) {
+        uint32_t c[AHEAD];
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) c[j] = (uint32_t)p.colind[k0 + min(i + NT * j, p.sample_len - 1)];
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            const uint32_t bit = (c[j] ^ (c[j] / (WORDS * 32)) * 0x9E375u) % (WORDS * 32);
+            atomicOr(&bm[bit >> 5], 1u << (bit & 31));
+        }
     }
-    if (bad) atomicOr(err, 8);
+    __syncthreads();
+    uint32_t n = 0;
+    for (int i = threadIdx.x; i < WORDS; i += NT) n += __popc(bm[i]);
+    atomicAdd(&bm[WORDS], n);
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(p.ctl + 8, (int)bm[WORDS]);
+}
+__global__ __launch_bounds__(1024) void k_pre_sample(Prep p)
+{
+    __shared__ uint32_t bm[kSamplePanels * 8 / 32 + 1];
+    if (*p.ctl & 7) return;
+    sample_stretch<1024, kSamplePanels * 8 / 32>(p, blockIdx.x, bm);
+}
+double sample_share(const Prep& p, int32_t distinct) { return p.sample_len > 0 ? (double)distinct / ((double)kSamples * p.sample_len) : 1.0; }
+
+// columns only (a plan that counts nothing still checks them); the first kSamples workgroups take the short sample, if any
+__global__ __launch_bounds__(256) void k_validate_cols(Prep p, int samples)
+{
+    __shared__ uint32_t bm[kSampleSlices * 8 / 32 + 1];
+    if ((int)blockIdx.x < samples) {
+        sample_stretch<256, kSampleSlices * 8 / 32>(p, blockIdx.x, bm);
+        return;
+    }
+    const int64_t stride = (int64_t)(gridDim.x - samples) * 256;
+    bool bad = false;
+    for (int64_t k = (int64_t)(blockIdx.x - samples) * 256 + threadIdx.x; k < p.nnz; k += stride) {
+        const int32_t c = p.colind[k];
+        bad |= (c < 0 || c >= p.n_cols);
+    }
+    if (bad) atomicOr(p.ctl, 8);
 }
 
 // rows whose columns do not ascend (a descent inside a row; descents at row starts are looked up)
@@ -742,17 +784,29 @@ __device__ inline int counts_set(const Prep& p, int mode)       // which set of 
     return mode == p.mode ? 0 : (mode == HCSPMM_ROUTE_ALL_MFMA ? 1 : -1);
 }
 
-// Whether every window runs on the scalar path, where panel_count or scalar_candidate ask.  It depends on how much the rows
-// of a window share: the matrix path fetches a distinct column of a window once, the scalar path a row of X per non-zero but
-// in large part from L2.  Distinct columns are 0.16 of the non-zeros in communities of degree 51 (131,072 rows, 128 columns,
-// fp32: 107 us on the matrix path, 131 us on the scalar path, 157 us in panels) and 0.8 to 0.95 in power-law graphs of degree
-// 20 to 500.  Panels fetch from L2 almost only (16 TB/s against 6.6 TB/s from behind it) and take over at 0.4, the plain
-// scalar path at 0.6.  Panels need rows whose columns ascend.
-__device__ inline bool scattered_rows(const Prep& p, int64_t total_ncols)
+// Whether every window runs on the scalar path (1) and in column panels (2), where panel_count or scalar_candidate ask.
+//  * Panels fetch from L2 almost only, and pay where rows that run side by side do not find each other's X rows there anyway:
+//    more than half of the columns of 65,536 consecutive non-zeros are distinct.  Against the plain scalar path, 64 columns,
+//    fp32: power law, 200,000 rows of 300 (0.66): 1358 -> 1130 us, 100,000 of 200 (0.55): 357 -> 329 us, 120,000 of 150
+//    (0.51): 302 -> 306 us, 60,000 of 150 (0.41 to 0.48): 130 -> 139 us; communities of 4,096 (0.10) and 32,768 (0.46) nodes:
+//    776 -> 1090 us and 756 -> 980 us.  Rows of X off the 128-byte lines have no column slices to fall back on and take panels
+//    from 0.4 on (60,000 of 150, 48 columns: 154 -> 134 us).  The matrix's rows must ascend.
+//  * The plain scalar path takes over the matrix path's windows where the windows' distinct columns are more than 0.6 of their
+//    non-zeros: the matrix path fetches a distinct column of a window once, the scalar path a row of X per non-zero but in
+//    large part from L2.  They are 0.16 of them in communities of degree 51 (131,072 rows, 128 columns, fp32: 107 us on the
+//    matrix path, 131 us on the scalar path) and 0.8 to 0.95 in power-law graphs of degree 20 to 500.  The whole matrix is
+//    asked, not the matrix path's windows alone, because the two paths' stages follow each other: communities next to a
+//    power law, 128 columns, per window / all scalar: 0.48 on the matrix path's windows, 0.63 on all: 792 / 723 us in fp32,
+//    480 / 404 us in bf16; 0.16 and 0.75: 655 / 650 and 357 / 345 us; 0.16 and 0.61: 732 / 740 and 498 / 480 us.  At 256
+//    columns they are level within 2 % (one of nine graphs, bf16: 1467 / 1563 us).
+//    Where panels were asked for and neighbouring rows turn out to share, their X rows meet in L2 and the matrix may be of any
+//    size (communities of 16,384, 60 M non-zeros, 128 columns, fp32: 2746 us on the matrix path, 2104 in panels, 1666 us).
+__device__ inline int scalar_form(const Prep& p, int64_t total_ncols)
 {
-    if (!p.scalar_exec) return false;
-    if (p.check_sorted) return p.ctl[6] == 0 && 10 * total_ncols > 4 * p.nnz;
-    return 10 * total_ncols > 6 * p.nnz;
+    const bool sample = p.panels_from > 0;
+    const bool scattered = sample && 100 * (int64_t)p.ctl[8] > (int64_t)p.panels_from * kSamples * p.sample_len;
+    if (scattered && p.ctl[6] == 0) return 2;
+    return (p.scalar_exec || (sample && !scattered)) && p.features && 10 * total_ncols > 6 * p.nnz ? 1 : 0;
 }
 
 // One row's place in the scalar path's tables.
@@ -815,15 +869,15 @@ __global__ __launch_bounds__(256) void k_pre_rows(Prep p)
         if (p.W == 0 && threadIdx.x == 0) p.wptr[0] = 0;
     }
     __syncthreads();
-    const bool all_scalar = scattered_rows(p, (int64_t)(all[0] + all[1]));
-    if (tile == 0 && threadIdx.x == 0) p.ctl[7] = all_scalar ? 1 : 0;
+    const int all_scalar = scalar_form(p, (int64_t)(all[0] + all[1]));
+    if (tile == 0 && threadIdx.x == 0) p.ctl[7] = all_scalar;
     unsigned long long sum[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int rl = threadIdx.x * 4 + j;
         const int64_t i = (int64_t)tile * kTileRows + rl;
         if (i >= p.n_rows) break;
-        const RowClass c = row_class(p, p.rowptr[i + 1] - p.rowptr[i], all_scalar ? 0 : s_route[rl / kH], s_wide[rl / kH]);
+        const RowClass c = row_class(p, p.rowptr[i + 1] - p.rowptr[i], all_scalar != 0 ? 0 : s_route[rl / kH], s_wide[rl / kH]);
         sum[0] += (unsigned long long)c.is_short | (unsigned long long)c.is_mid << 32;
         sum[1] += (unsigned long long)c.rest | (unsigned long long)(c.n_seg > 1) << 32;
         sum[2] += seg_counts(c);
@@ -923,6 +977,7 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
         t.n_segs = (int32_t)n_seg; t.n_slots = (int64_t)n_slot;
         t.n_big_list = p.ctl[1]; t.n_huge_list = p.ctl[2];
         t.all_scalar = p.ctl[7];
+        t.sample_distinct = p.ctl[8];
         t.err = 0;
         *p.out = t;
     }
@@ -983,9 +1038,11 @@ hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
     } else if (p.nnz > 0) {
         int64_t blocks = (p.nnz + 256 * 8 - 1) / (256 * 8);
         if (blocks > 65536) blocks = 65536;
-        hipLaunchKernelGGL(k_validate_cols, dim3((unsigned)blocks), dim3(256), 0, s, p.n_cols, p.nnz, p.colind, p.ctl);
+        const int samples = p.sample_len > 0 && p.panels_from == 0 ? kSamples : 0;
+        hipLaunchKernelGGL(k_validate_cols, dim3((unsigned)(blocks + samples)), dim3(256), 0, s, p, samples);
     }
-    if (p.check_sorted) {
+    if (p.panels_from > 0) {
+        hipLaunchKernelGGL(k_pre_sample, dim3(kSamples), dim3(1024), 0, s, p);
         int64_t blocks = (p.nnz + 256 * 16 - 1) / (256 * 16);
         if (blocks > 65536) blocks = 65536;
         hipLaunchKernelGGL(k_pre_sorted, dim3((unsigned)blocks), dim3(256), 0, s, p);

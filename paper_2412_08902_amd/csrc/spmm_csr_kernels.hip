@@ -613,10 +613,12 @@ static int shape_cols(const CsrShape& sh) { return kGroup / sh.split * sh.vec * 
 // per-row chain is then small; 60,000 nodes of degree 100: 271 / 228 / 201 us with 1 / 2 / 4 slices), as long as rows of X
 // start on a 128-byte line: off it, every slice costs a second line (300,000 of degree 60, bf16, 224 columns: 1345 us in
 // four slices, 256 columns 969 us).  Neighbouring rows that share their columns (community graphs) already meet in one L2
-// and lose 6 %: they are left whole.
+// and lose 6 to 27 %: they are left whole.
 // 16-bit rows of more than 256 and less than 512 bytes leave lanes of the two-vector form idle, at half the waves: three
 // slices of 128 bytes where rows start on lines (16,934 nodes of 14, 192 columns, bf16: 26 -> 17 us; 1 M of 20: 1207 -> 1094 us),
-// two halves while X fits the L2s (16,934 of 14, 160 columns: 25 -> 15 us; 100,000 of 20: 91 -> 92 us).
+// two halves while X fits the L2s (16,934 of 14, 160 columns: 25 -> 15 us; 100,000 of 20: 91 -> 92 us).  Whole 16-bit rows of
+// 512 bytes are slow where most rows take a wave each, also where nothing is gained in L2 (communities of 512, 232,960 rows
+// of 165, bf16: 1268 -> 922 us in halves).
 static int pick_slices(const SpmmArgs& a, const CsrHints& h, int32_t& slice_w)
 {
     const int64_t es = a.x_dtype == HCSPMM_F32 ? 4 : 2, row = a.d * es;
@@ -629,6 +631,8 @@ static int pick_slices(const SpmmArgs& a, const CsrHints& h, int32_t& slice_w)
     else if (es == 2 && h.scattered && row > 256 && row < 512) {
         if (on_lines) most = 128;
         else if ((double)a.n_cols * (double)row <= 20.0 * (1 << 20)) { most = 256; align = 32; }
+    } else if (es == 2 && row >= 512 && degree > kMidRow) {
+        most = 256;
     }
     int64_t n = (row + most - 1) / most;
     // a count that XCDs can own, where the slices come out about equally wide; other counts are taken in turn

@@ -73,3 +73,13 @@ def test_long_rows_of_sparse_matrices(n, long_rows):
     rows = np.unique(np.concatenate([hubs, np.arange(0, n, 97)]))
     ref, bound = oracle_pair(g, X, rows=rows)
     assert_close(Y[rows], ref, bound, 1e-5, "n=%d" % n)
+
+
+@pytest.mark.parametrize("d", [256, 260, 320, 512])
+def test_halves_of_16bit_rows_that_take_a_wave_each(d):
+    """Rows of more non-zeros than the short tier takes, in few columns (nothing to gain from narrow slices)."""
+    g = rows_of([150] * 700, 300, d)
+    bits = to_bf16_bits(np.random.default_rng(d).standard_normal((300, d)).astype(np.float32))
+    Y, _ = gpu_spmm(g, bits, 0, x_bits="bf16", mfma_dtype=1, sel_coef=[0, 0, 1])
+    ref, bound = oracle_pair(g, bits, x_dtype=oracle.DT_BF16)
+    assert_close(Y, ref, bound, 1e-5, "bf16 d=%d" % d)

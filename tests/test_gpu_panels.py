@@ -9,14 +9,14 @@ from test_gpu_y16 import close_16, from_dev_16, torch_16, widen
 from workloads import CSRGraph, to_bf16_bits
 
 pytestmark = pytest.mark.gpu
-N_COLS = 120_000                     # four panels of 128-byte slices from 80 non-zeros per row on
+N_COLS = 120_000                     # four panels of 128-byte slices from 150 non-zeros per row on (400 for 16-bit rows of 128 bytes)
 
 
-def graph(n_rows, n_cols=N_COLS, seed=1, ascending=True):
-    """Rows of about 100 non-zeros that favour low columns; empty rows, hubs of one and several segments, rows that miss
-    whole panels, repeated columns."""
+def graph(n_rows, n_cols=N_COLS, seed=1, ascending=True, times=1):
+    """Rows of about 170 non-zeros (or so many times that) that favour low columns; empty rows, hubs of one and several
+    segments, rows that miss whole panels, repeated columns."""
     rng = np.random.default_rng(seed)
-    length = rng.integers(60, 190, n_rows)
+    length = times * rng.integers(110, 240, n_rows)
     length[rng.choice(n_rows, n_rows // 20, replace=False)] = 0
     length[rng.choice(n_rows, 6, replace=False)] = [1023, 1025, 2049, 4096, 5000, 9000]
     length[-1], length[0] = 0, 3
@@ -32,12 +32,25 @@ def graph(n_rows, n_cols=N_COLS, seed=1, ascending=True):
     return CSRGraph(n_rows, n_cols, rowptr, col.astype(np.int32), rng.standard_normal(col.shape[0]).astype(np.float32))
 
 
+def has_panels(g, d, mfma_dtype=0):
+    """A scalar-only plan holds more memory with panels (their tables) than a plan of the same matrix that may not take any."""
+    import paper_2412_08902_amd.binding as hc
+    dev = device_graph(g)
+    size = []
+    for kernels in (hc.HCSPMM_MATRIX_AUTO, hc.HCSPMM_MATRIX_PER_WINDOW):
+        plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *dev, route_mode=1, d_hint=d, mfma_dtype=mfma_dtype, matrix_kernels=kernels)
+        size.append(hc.hcspmm_plan_info(plan)["device_bytes"])
+        plan.destroy()
+    return size[0] > size[1]
+
+
 # 300: a wave per row and slice; 9001: the short tier and a ragged last block
 @pytest.mark.parametrize("n_rows", [300, 9001])
 @pytest.mark.parametrize("d,pad", [(32, 0), (33, 0), (64, 1), (128, 0), (130, 3), (256, 0)])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_fp32_panels(n_rows, d, pad, mode):
     g = graph(n_rows)
+    assert has_panels(g, d)
     X = np.random.default_rng(d).standard_normal((N_COLS, d)).astype(np.float32)
     Y, _ = gpu_spmm(g, X, mode, pad_x=pad, pad_y=pad)
     rows = np.unique(np.concatenate([np.arange(0, n_rows, 1 + n_rows // 300), np.flatnonzero(np.diff(g.rowptr) > 1000), [n_rows - 1]]))
@@ -48,7 +61,8 @@ def test_fp32_panels(n_rows, d, pad, mode):
 # an odd pitch is read element by element and takes no panels
 @pytest.mark.parametrize("d,pad", [(64, 0), (66, 2), (128, 0), (64, 1), (256, 0)])
 def test_16bit_panels(d, pad):
-    g = graph(300)
+    g = graph(300, times=3)
+    assert has_panels(g, d, 1)
     bits = to_bf16_bits(np.random.default_rng(d).standard_normal((N_COLS, d)).astype(np.float32))
     Y, _ = gpu_spmm(g, bits, 0, pad_x=pad, x_bits="bf16", mfma_dtype=1)
     ref, bound = oracle_pair(g, bits, x_dtype=oracle.DT_BF16)
@@ -57,10 +71,29 @@ def test_16bit_panels(d, pad):
 
 def test_rows_that_do_not_ascend_take_no_panels():
     g = graph(300, ascending=False)
+    assert not has_panels(g, 64)
     X = np.random.default_rng(3).standard_normal((N_COLS, 64)).astype(np.float32)
     Y, _ = gpu_spmm(g, X, 0)
     ref, bound = oracle_pair(g, X)
     assert_close(Y, ref, bound, 1e-5, "unsorted")
+
+
+# communities in consecutive rows: their X rows meet in L2 without panels, and in the small ones without column slices
+@pytest.mark.parametrize("size,panels", [(1000, False), (20_000, False), (120_000, True)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_communities_take_no_panels(size, panels, mode):
+    n_rows, per_row = 8000, 160
+    rng = np.random.default_rng(size)
+    first = np.arange(n_rows) * N_COLS // n_rows // size * size
+    col = np.sort(first[:, None] + rng.integers(0, size, (n_rows, per_row)), axis=1).astype(np.int32).ravel()
+    g = CSRGraph(n_rows, N_COLS, (per_row * np.arange(n_rows + 1)).astype(np.int32), col, rng.standard_normal(col.shape[0]).astype(np.float32))
+    assert has_panels(g, 64) == panels
+    for d in (64, 130):
+        X = rng.standard_normal((N_COLS, d)).astype(np.float32)
+        Y, _ = gpu_spmm(g, X, mode)
+        rows = np.arange(0, n_rows, 41)
+        ref, bound = oracle_pair(g, X, rows=rows)
+        assert_close(Y[rows], ref, bound, 1e-5, "communities of %d, d=%d" % (size, d))
 
 
 @pytest.mark.parametrize("ykind", ["f32", "bf16"])

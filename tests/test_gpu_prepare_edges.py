@@ -147,3 +147,30 @@ def test_panels_of_more_tiles_than_are_added_up_directly():
         bound = torch.zeros_like(ref).index_add_(0, row, terms.abs())
         assert_close(Y[r].double().cpu().numpy(), ref.cpu().numpy(), bound.cpu().numpy(), 1e-5, "panels")
     assert torch.isfinite(Y).all()
+
+
+# 1.2 M non-zeros: a scalar-only preparation samples the columns beside its check of them
+@pytest.mark.parametrize("community", [500, 40_000])
+def test_scalar_only_plans_that_sample_their_columns(community):
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    n, per_row = 40_000, 30
+    rng = np.random.default_rng(community)
+    first = np.arange(n) // community * community
+    col = np.sort(first[:, None] + rng.integers(0, community, (n, per_row)), axis=1).astype(np.int32).ravel()
+    g = CSRGraph(n, n, (per_row * np.arange(n + 1)).astype(np.int32), col, rng.standard_normal(col.shape[0]).astype(np.float32))
+    check_plan(g, 1)
+    X = rng.standard_normal((n, 128)).astype(np.float32)
+    plan = hc.hcspmm_prepare(n, n, *device_graph(g), route_mode=1, d_hint=128)
+    Y = torch.full((n, 128), float("nan"), device="cuda")
+    hc.hcspmm_spmm(plan, torch.from_numpy(X).cuda(), Y)
+    rows = np.arange(0, n, 53)
+    ref, bound = (oracle.spmm_rows(rows, g.rowptr, g.colind, g.vals, X, None, use_abs=b) for b in (False, True))
+    assert_close(Y.cpu().numpy()[rows].astype(np.float64), ref, bound, 1e-5, "spmm")
+    for at in (0, col.shape[0] // 2, col.shape[0] - 1):
+        for bad in (-1, n):
+            c = col.copy()
+            c[at] = bad
+            with pytest.raises(hc.HcspmmError) as e:
+                hc.hcspmm_prepare(n, n, *device_graph(CSRGraph(n, n, g.rowptr, c, g.vals)), route_mode=1)
+            assert e.value.status == hc.HCSPMM_EBADCSR
