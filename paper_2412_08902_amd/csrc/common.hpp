@@ -410,8 +410,9 @@ struct hcspmm_plan {
     int32_t local;                  // neighbouring rows are known to share most of their columns (see build_plan)
     int32_t* panel_split;
     struct { hcspmm::PanelTotals t; int32_t* mid_rows; hcspmm::Segment* segs; hcspmm::MultiRow* multi; } panel[hcspmm::kMaxPanels];
-    float* acc_rows;                // lazily sized: n_rows x d sums between panels when the output is not fp32
-    int64_t acc_rows_elems;
+    float* acc_rows;                // n_rows x d sums between panels when the output is not fp32: reserved for 16-bit plans
+    int64_t acc_rows_elems;         // (acc_width columns, see reserve_row_sums), lazily sized for the layers otherwise
+    int32_t acc_width;
     int32_t n_rest;                 // rows finished through the workspace by the fused update
     int32_t* rest_rows;
     int64_t nnz_long;

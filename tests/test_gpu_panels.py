@@ -142,3 +142,37 @@ def test_update_of_a_plan_with_panels():
                   np.concatenate([cut(p, r, p.vals) for r, p in enumerate(parts)]))
     update_and_check(plan, g2, changed, 0, d=64)
     plan.destroy()
+
+
+@pytest.mark.parametrize("kind", ["bf16", "f16"])
+@pytest.mark.parametrize("d,hint", [(128, 128), (64, 128), (256, 128)])
+def test_16bit_outputs_keep_fp32_sums_between_panels(kind, d, hint):
+    """16-bit X and Y: rounded once, the same bits from both entry points (the second allocates nothing), whatever ran before;
+    a width beyond the plan's takes all columns at once.  The sums outlive an update."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    from workloads import to_f16_bits
+    g = graph(300, times=3)
+    x = np.random.default_rng(d).standard_normal((N_COLS, d)).astype(np.float32)
+    bits, code = (to_bf16_bits(x), oracle.DT_BF16) if kind == "bf16" else (to_f16_bits(x), oracle.DT_F16)
+    X = torch.from_numpy(bits.view(np.int16)).cuda().view(torch_16(kind))
+    dev = device_graph(g)
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *dev, d_hint=hint, mfma_dtype=1 if kind == "bf16" else 2)
+    ref, bound = oracle_pair(g, bits, x_dtype=code)
+    for _ in range(2):
+        Y, Z = (torch.full((g.n_rows, d), 3.0, dtype=torch_16(kind), device="cuda") for _ in range(2))
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        hc.hcspmm_spmm_noalloc(plan, X, Z)
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] == free
+        hc.hcspmm_spmm(plan, X, Y)
+        assert torch.equal(Y, Z)
+        close_16(widen(from_dev_16(Y), kind), ref, bound, 1e-5, kind, "d=%d" % d)
+        # a layer grows the sums for its own width; the products' route must not follow
+        W = torch.eye(512, device="cuda")[:, :512]
+        T = torch.empty((g.n_rows, 512), dtype=torch_16(kind), device="cuda")
+        ws = torch.empty(hc.hcspmm_gcn_workspace_bytes(plan, 512, 512), dtype=torch.uint8, device="cuda")
+        hc.hcspmm_gcn_layer_ex(plan, torch.zeros((N_COLS, 512), device="cuda"), W, T, ws, t_dtype=1 if kind == "bf16" else 2)
+        hc.hcspmm_plan_update(plan, *dev, np.array([1, 2], np.int32))
+    plan.destroy()
