@@ -11,8 +11,6 @@
 
 namespace hcspmm {
 
-constexpr int kGroup = 16;             // lanes per group: one DPP row
-constexpr int kRowsPerGroup = 16;      // most consecutive rows that one group walks (it holds one row's extent per lane)
 constexpr int64_t kMaxBlocks = ((int64_t)1 << 24) - 1;   // workgroups of 256 threads in a launch: fewer than 2^32 threads
 
 struct CsrGrid {
@@ -20,15 +18,16 @@ struct CsrGrid {
     int32_t rows_per_group;
     int32_t run, run_mid;              // log2 of the workgroups per XCD-local run of the short and mid tiers (-1: plain order)
     int32_t n_slices, slice_w;         // column slices
-    int64_t blocks;                    // of the whole launch
+    HC_HOST_DEVICE int64_t blocks() const { return ((int64_t)seg_blocks + mid_blocks + short_blocks) * n_slices; }
 };
 
 // Tiers: n_segs segments of long rows, n_mid rows of a wave each (four to a workgroup), n_items short rows of a group each.
 // XCD-local runs (see csr_block): tiers of at least 1024 workgroups are padded to whole rounds of runs of 2^run workgroups
-// over the XCDs that share a slice.  A group takes one row -- what one after the other adds is only the chain of its loads --
-// unless the launch would have more threads than a launch may: then first more rows to a group, then wider slices.
+// over the XCDs that share a slice.  A group (of 8 or 16 lanes) takes one row -- what one after the other adds is only the chain of its loads --
+// unless the launch would have more threads than a launch may: then first more rows to a group (one per lane at most, the
+// lanes hold their extents), then wider slices.
 inline CsrGrid csr_grid(int64_t n_segs, int64_t n_mid, int64_t n_items, int32_t d, int32_t n_slices, int32_t slice_w, int run,
-                        int rows_per_group = 1)
+                        int group, int rows_per_group = 1)
 {
     CsrGrid g{};
     g.rows_per_group = rows_per_group;
@@ -42,21 +41,20 @@ inline CsrGrid csr_grid(int64_t n_segs, int64_t n_mid, int64_t n_items, int32_t 
             const int64_t unit = nsub << (r > 0 ? r : 0);
             return r >= 0 || owned ? (n + unit - 1) / unit * unit : n;
         };
-        const int64_t per_block = (int64_t)(256 / kGroup) * g.rows_per_group;
+        const int64_t per_block = (int64_t)(256 / group) * g.rows_per_group;
         const int64_t segs = owned ? (n_segs + nsub - 1) / nsub * nsub : n_segs;
         const int64_t mid = padded((n_mid + 3) / 4, g.run_mid), shorts = padded((n_items + per_block - 1) / per_block, g.run);
-        g.blocks = (segs + mid + shorts) * g.n_slices;
-        if (g.blocks <= kMaxBlocks || (g.n_slices == 1 && g.rows_per_group == kRowsPerGroup)) {
+        if ((segs + mid + shorts) * g.n_slices <= kMaxBlocks || (g.n_slices == 1 && g.rows_per_group == group)) {
             g.seg_blocks = (uint32_t)segs; g.mid_blocks = (uint32_t)mid; g.short_blocks = (uint32_t)shorts;
             return g;
         }
-        if (shorts > 0 && g.rows_per_group < kRowsPerGroup) {
-            g.rows_per_group = 2 * g.rows_per_group < kRowsPerGroup ? 2 * g.rows_per_group : kRowsPerGroup;
+        if (shorts > 0 && g.rows_per_group < group) {
+            g.rows_per_group = 2 * g.rows_per_group < group ? 2 * g.rows_per_group : group;
         } else if (g.n_slices > 1) {
             g.slice_w = 2 * (int64_t)g.slice_w < d ? 2 * g.slice_w : d;
             g.n_slices = (int32_t)(((int64_t)d + g.slice_w - 1) / g.slice_w);
         } else {
-            g.rows_per_group = kRowsPerGroup;
+            g.rows_per_group = group;
         }
     }
 }

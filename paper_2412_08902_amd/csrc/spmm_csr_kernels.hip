@@ -4,7 +4,7 @@
 //
 // wave64 mapping: a group of 16 lanes -- one DPP row -- owns an output row, every lane holds NV
 // vectors of VEC consecutive columns; a wave works on four rows (short rows) or on four non-zeros
-// of the same row (mid and long rows) per load instruction.  Column indices and values are fetched
+// of the same row (mid and long rows) per load instruction.  (Other forms for narrow rows: Gather.)  Column indices and values are fetched
 // 16 at a time with one coalesced load per group and handed round by DPP row broadcasts, which are
 // operands of the address add and of the multiply-adds themselves: per non-zero and group one add,
 // NV loads and NV*VEC multiply-adds, nothing else.  (Handing them round through LDS, 64-bit row
@@ -63,7 +63,7 @@ struct CsrWork {
     const int32_t* row_list;
     const uint8_t* route;
     int32_t mid_row;            // longest row of the short tier, or of the mid tier when that has no list (a matrix of few rows)
-    CsrGrid grid;
+    CsrGrid grid;               // (right behind mid_row: one load brings what a short row's workgroup needs)
     int32_t y_vec;              // Y rows allow vector stores
     int32_t skip_empty;         // a row without non-zeros changes nothing (a column panel that adds to Y)
 };
@@ -94,18 +94,23 @@ template <int XK> __device__ __forceinline__ float widened(const uint32_t* w, in
     else return (float)__builtin_bit_cast(_Float16, (unsigned short)((i & 1) ? (w[i >> 1] >> 16) : (w[i >> 1] & 0xffffu)));
 }
 
-// The gather of one lane group: the 16 lanes hold NV vectors of VEC elements each, COLS columns of an X row in all.
-// SPLIT = 2: the two halves of the group work on two non-zeros at a time (slots 2t and 2t+1), 8 lanes covering the row, and
-// are added when the row is done.  A vector-memory instruction takes the CU's load path 16 clocks whether its lanes ask for
-// 8 or 16 bytes (measured on cache hits: 140 G rows of 128 bytes per second with 16 lanes x 8 bytes, 206 G with 8 x 16), so
-// rows of up to 128 bytes are read by 8 lanes; the second broadcast that this takes is free, the VALU has slack.
+// The gather of one lane group: GROUP lanes own an output row, LANES of them read a row of X, NV vectors of VEC elements each:
+// COLS columns of an X row in all.  Three forms:
+//   16 of 16   one non-zero at a time;
+//   8 of 16    the two halves of the group work on two non-zeros at a time (slots 2t and 2t+1) and are added when the row is
+//              done.  A vector-memory instruction takes the CU's load path 16 clocks whether its lanes ask for 8 or 16 bytes
+//              (measured on cache hits: 140 G rows of 128 bytes per second with 16 lanes x 8 bytes, 206 G with 8 x 16), so
+//              rows of up to 128 bytes are read by 8 lanes; the second broadcast that this takes is free, the VALU has slack;
+//   8 of 8     a half of the 16 DPP lanes owns a row of its own.  Twice the output rows per wave: where rows are short and
+//              narrow a launch is bound by how fast waves start and drain (see narrow_rows).
 // PANEL: a column panel's share of the rows -- each row's end is read from a.rowend, and results may be added to rows of fp32
 // sums.  (Kept out of the plain kernels, which have no scalar register to spare in 128-byte rows: power law, fp32, 32
 // columns, 39.7 -> 35.1 us.)
-template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> struct Gather {
+template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL = false> struct Gather {
+    static constexpr int LANES = LANES_, GROUP = GROUP_, SPLIT = GROUP / LANES, STEPS = GROUP / SPLIT;
+    static_assert((GROUP == 16 && (LANES == 16 || LANES == 8)) || (GROUP == 8 && LANES == 8), "forms");
     static constexpr int ES = XK == 0 ? 4 : 2;
     static constexpr int BYTES = VEC * ES;
-    static constexpr int LANES = kGroup / SPLIT;                // lanes per X row
     static constexpr int COLS = LANES * VEC * NV;
     static constexpr int N = VEC * NV;                          // columns per lane
     static constexpr int WORDS = (BYTES < 4 ? 1 : BYTES / 4) * NV;
@@ -115,7 +120,7 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> str
     // vectors with one accumulator set are squeezed into 64 registers for all 8 waves (community graph, bf16, 64 columns:
     // 37.0 -> 32.2 us; power law, fp32, 32 columns: 36.7 -> 35.1 us); wider rows are bound by the traffic behind L2 and
     // lose more to the squeeze (fp32, 128 columns: 120.8 -> 137 us).
-    static constexpr int WAVES = SPLIT == 2 ? (XK == 0 && PANEL ? 7 : 8) : (XK != 0 && VEC == 8 && NV == 1) ? 6 : 1;
+    static constexpr int WAVES = LANES == 8 ? (XK == 0 && PANEL ? 7 : 8) : (XK != 0 && VEC == 8 && NV == 1) ? 6 : 1;
 
     const char* X;              // uniform: first column of the slice
     uint64_t ldxb;              // bytes between rows (uniform)
@@ -146,8 +151,9 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> str
     // step T's entry: slot T of the group, or slots 2T and 2T+1 for its two halves
     template <int T> static __device__ __forceinline__ uint32_t slot(uint32_t x)
     {
-        if constexpr (SPLIT == 1) return row_bcast<T>(x);
-        else return (uint32_t)__builtin_amdgcn_update_dpp((int)row_bcast<2 * T>(x), (int)x, 0x150 + 2 * T + 1, 0xf, 0xc, false);
+        if constexpr (LANES == 16) return row_bcast<T>(x);
+        constexpr int LO = GROUP == 16 ? 2 * T : T, HI = GROUP == 16 ? 2 * T + 1 : 8 + T;      // DPP lanes for its halves
+        return (uint32_t)__builtin_amdgcn_update_dpp((int)row_bcast<LO>(x), (int)x, 0x150 + HI, 0xf, 0xc, false);
     }
     template <int T> __device__ __forceinline__ void load(uint32_t key_, Raw<RAW> (&x)[NV]) const
     {
@@ -173,16 +179,16 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> str
         unrolled<COUNT>([&](auto u) { this->template load<T0 + decltype(u)::value>(key_, x[decltype(u)::value]); });
         unrolled<COUNT>([&](auto u) { this->template add<T0 + decltype(u)::value>(val, x[decltype(u)::value], acc); });
     }
-    // Up to 16 non-zeros (cnt of them, uniform within the group), U steps at a time.  Slots past the row's end carry the
+    // Up to GROUP non-zeros (cnt of them, uniform within the group), U steps at a time.  Slots past the row's end carry the
     // row's last column with value 0, so the loads carry no branches.
     __device__ __forceinline__ void batch(uint32_t key_, float val, int cnt, float (&acc)[N]) const
     {
         if constexpr (SPLIT == 2 && XK == 0) {
             // a wave whose groups all have more than half a batch left keeps the whole batch in flight (16-bit rows have twice
             // the accumulators and would spill)
-            if (__all(cnt > kGroup / 2)) { steps<0, LANES>(key_, val, acc); return; }
+            if (__all(cnt > GROUP / 2)) { steps<0, STEPS>(key_, val, acc); return; }
         }
-        unrolled<LANES / U>([&](auto blk) {
+        unrolled<STEPS / U>([&](auto blk) {
             constexpr int T0 = decltype(blk)::value * U;
             if (T0 == 0 || cnt > T0 * SPLIT) this->template steps<T0, U>(key_, val, acc);
         });
@@ -196,7 +202,7 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> str
         key_ = key(c);
         v = k < e ? t : 0.f;
     }
-    // a span [kb, ke) of one row taken 16 non-zeros at a time with stride `stride` (16 when one group owns the span)
+    // a span [kb, ke) of one row taken GROUP non-zeros at a time with stride `stride` (GROUP when one group owns the span)
     __device__ __forceinline__ void span(const SpmmArgs& a, int kb, int ke, int stride, int lig, float (&acc)[N]) const
     {
         if (kb >= ke) return;
@@ -205,7 +211,7 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> str
         fetch(a, kb + lig, ke, mk, mv);
         for (int k0 = kb; k0 < ke; k0 += stride) {
             fetch(a, k0 + stride + lig, ke, nk, nv);            // the next batch's indices before this batch's X rows
-            batch(mk, mv, min(kGroup, ke - k0), acc);
+            batch(mk, mv, min(GROUP, ke - k0), acc);
             mk = nk;
             mv = nv;
         }
@@ -267,7 +273,7 @@ template <int XK, int VEC, int NV, int SPLIT, bool WIDE, bool PANEL = false> str
 };
 
 // ---- short rows -----------------------------------------------------------------------------
-// A group walks grid.rows_per_group (<= kRowsPerGroup) consecutive items (rows, or entries of row_list) in a
+// A group walks grid.rows_per_group (one per lane at most) consecutive items (rows, or entries of row_list) in a
 // single flattened loop: each trip either moves to the next row (storing the finished one) or
 // consumes one batch of the current row, so groups of one wave stay busy on rows of unequal
 // length.  The rows' extents are fetched up front, one per lane.  `done(row, slot, acc)` takes a finished row.
@@ -289,9 +295,9 @@ __device__ __forceinline__ void walk_rows(const G& g, const SpmmArgs& a, int lig
             }
             row = -1;
             while (j < nr && row < 0) {
-                row = __shfl(my_row, j, kGroup);
-                k = __shfl(my_s, j, kGroup);
-                e = __shfl(my_e, j, kGroup);
+                row = __shfl(my_row, j, G::GROUP);
+                k = __shfl(my_s, j, G::GROUP);
+                e = __shfl(my_e, j, G::GROUP);
                 slot = j;
                 ++j;
             }
@@ -302,11 +308,11 @@ __device__ __forceinline__ void walk_rows(const G& g, const SpmmArgs& a, int lig
         }
         uint32_t nk;
         float nv;
-        g.fetch(a, k + kGroup + lig, e, nk, nv);
-        g.batch(mk, mv, min(kGroup, e - k), acc);
+        g.fetch(a, k + G::GROUP + lig, e, nk, nv);
+        g.batch(mk, mv, min(G::GROUP, e - k), acc);
         mk = nk;
         mv = nv;
-        k += kGroup;
+        k += G::GROUP;
     }
 }
 
@@ -335,17 +341,17 @@ __device__ __forceinline__ void csr_mid_body(uint32_t block, int c_begin, int c_
     int32_t s, e;
     G::extent(a, row, s, e);
     if (wk.mid_rows ? e - s <= min_len : e - s > wk.mid_row || (wk.route && wk.route[row / kH] != 0) || G::skipped(wk, s, e)) return;
-    const int lane = threadIdx.x & 63, gi = lane / kGroup, lig = lane % kGroup;
+    const int lane = threadIdx.x & 63, gi = lane / G::GROUP, lig = lane % G::GROUP;
     for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
         G g;
         g.init(a, c0, min(G::COLS, c_end - c0), lig);
         float acc[G::N];
         vzero(acc);
-        g.span(a, s + gi * kGroup, e, 64, lig, acc);
+        g.span(a, s + gi * G::GROUP, e, 64, lig, acc);
         G::finish(acc);
-        // butterfly over the four groups: same operation order on every run
+        // butterfly over the groups: same operation order on every run
 #pragma unroll
-        for (int off = kGroup; off < 64; off <<= 1)
+        for (int off = G::GROUP; off < 64; off <<= 1)
 #pragma unroll
             for (int i = 0; i < G::N; ++i) acc[i] += __shfl_xor(acc[i], off, 64);
         if (gi == 0) g.store(a, wk.y_vec, row, c0, lig, acc);
@@ -355,9 +361,8 @@ __device__ __forceinline__ void csr_mid_body(uint32_t block, int c_begin, int c_
 template <class G>
 __device__ __forceinline__ void csr_short_body(uint32_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a)
 {
-    static_assert(kGroup >= kRowsPerGroup, "a group must be able to hold one row extent per lane");
-    const int lig = threadIdx.x % kGroup;
-    const uint32_t i0 = (block * (256 / kGroup) + threadIdx.x / kGroup) * wk.grid.rows_per_group;
+    const int lig = threadIdx.x % G::GROUP;
+    const uint32_t i0 = (block * (256 / G::GROUP) + threadIdx.x / G::GROUP) * wk.grid.rows_per_group;
     if (i0 >= (uint32_t)wk.n_items) return;
     const int nr = min(wk.grid.rows_per_group, wk.n_items - (int)i0);
     int32_t my_row, my_s, my_e;
@@ -371,20 +376,20 @@ __device__ __forceinline__ void csr_short_body(uint32_t block, int c_begin, int 
 }
 
 // ---- short rows with the update stage fused in ------------------------------------------------
-// Same walk as csr_short_body, but a workgroup covers exactly 16 list entries and a finished row goes to a 16 x d tile in
-// LDS instead of memory; after a barrier the four waves share the tile, each multiplying it by an interleaved quarter of
-// W's 16-column blocks on the matrix cores, and write act(Z W) for the rows the workgroup owns
+// Same walk as csr_short_body, but a workgroup covers exactly one list entry per group (16 or 32) and a finished row goes to
+// one of one or two 16 x d tiles in LDS instead of memory; after a barrier the four waves share the tiles, each multiplying
+// one by an interleaved quarter or half of W's 16-column blocks on the matrix cores, and write act(Z W) for the rows the workgroup owns
 // (Section V-A: the aggregation result of a window stays on chip for the update).
 // The width d must fit one pass of the group (d <= G::COLS) and be a multiple of 16.
 template <class G>
 __device__ __forceinline__ void csr_short_fused_body(uint32_t block, const CsrWork& wk, const SpmmArgs& a, const UpdateArgs& u,
                                                      float* __restrict__ zt, int32_t* __restrict__ rows_s)
 {
-    constexpr int LDZ = G::COLS + 4;
-    const uint32_t b0 = block * 16;                             // first list entry of the workgroup
+    constexpr int LDZ = G::COLS + 4, ROWS = 256 / G::GROUP, WPT = 64 / ROWS;   // waves per tile
+    const uint32_t b0 = block * ROWS;                           // first list entry of the workgroup
     if (b0 >= (uint32_t)wk.n_items) return;                               // whole workgroup past the end
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int gw = threadIdx.x / kGroup, lig = threadIdx.x % kGroup;
+    const int gw = threadIdx.x / G::GROUP, lig = threadIdx.x % G::GROUP;
     const int nr = b0 + gw < (uint32_t)wk.n_items ? 1 : 0;
     int32_t my_row, my_s, my_e;
     row_extents<G>(b0 + gw, lig, nr, wk, a, my_row, my_s, my_e);
@@ -394,8 +399,9 @@ __device__ __forceinline__ void csr_short_fused_body(uint32_t block, const CsrWo
     walk_rows(g, a, lig, nr, my_row, my_s, my_e,
               [&](int32_t, int, const float (&acc)[G::N]) { g.store_f32(zt + gw * LDZ, lig, acc); });
     __syncthreads();
-    if (u.keep_z) store_tile_rows(zt, LDZ, rows_s, 16, a.d, a.Y, a.ldy, threadIdx.x, 256);
-    update_tile16(zt, LDZ, rows_s, a.d, u, lane, wave, 4);
+    if (u.keep_z) store_tile_rows(zt, LDZ, rows_s, ROWS, a.d, a.Y, a.ldy, threadIdx.x, 256);
+    const int tile = wave / WPT;
+    update_tile16(zt + tile * 16 * LDZ, LDZ, rows_s + tile * 16, a.d, u, lane, wave % WPT, WPT);
 }
 
 // ---- long rows: one workgroup per segment of a row ------------------------------------------
@@ -403,16 +409,16 @@ template <class G>
 __device__ __forceinline__ void csr_long_body(uint32_t block, int c_begin, int c_end, const CsrWork& wk,
                                               float* __restrict__ red /* LDS, 256 * G::N floats */, const SpmmArgs& a)
 {
-    constexpr int NG = 256 / kGroup;
+    constexpr int NG = 256 / G::GROUP;
     if (block >= (uint32_t)wk.n_segs) return;
     const Segment sg = wk.segs[block];
-    const int gi = threadIdx.x / kGroup, lig = threadIdx.x % kGroup;
+    const int gi = threadIdx.x / G::GROUP, lig = threadIdx.x % G::GROUP;
     for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
         G g;
         g.init(a, c0, min(G::COLS, c_end - c0), lig);
         float acc[G::N];
         vzero(acc);
-        g.span(a, sg.k_begin + gi * kGroup, sg.k_end, 256, lig, acc);
+        g.span(a, sg.k_begin + gi * G::GROUP, sg.k_end, 256, lig, acc);
         G::finish(acc);
         // fixed-order tree over the groups: the result does not depend on scheduling
 #pragma unroll
@@ -421,7 +427,7 @@ __device__ __forceinline__ void csr_long_body(uint32_t block, int c_begin, int c
         for (int st = NG / 2; st > 0; st >>= 1) {
             if (gi < st) {
 #pragma unroll
-                for (int i = 0; i < G::N; ++i) red[i * 256 + threadIdx.x] += red[i * 256 + threadIdx.x + st * kGroup];
+                for (int i = 0; i < G::N; ++i) red[i * 256 + threadIdx.x] += red[i * 256 + threadIdx.x + st * G::GROUP];
             }
             __syncthreads();
         }
@@ -466,9 +472,9 @@ __global__ __launch_bounds__(256, G::WAVES) void k_csr(CsrWork wk, SpmmArgs a)
 template <class G>
 __global__ __launch_bounds__(256) void k_csr_fused(CsrWork wk, SpmmArgs a, UpdateArgs u)
 {
-    constexpr int kTile = 16 * (G::COLS + 4), kRed = 256 * G::N;
+    constexpr int kTile = 256 / G::GROUP * (G::COLS + 4), kRed = 256 * G::N;
     __shared__ float lds[kTile > kRed ? kTile : kRed];          // the reduction of a long row and the tile of short rows never meet
-    __shared__ int32_t rows16[16];
+    __shared__ int32_t rows_s[256 / G::GROUP];
     uint32_t b = blockIdx.x;
     int slice;
     if (b < wk.grid.seg_blocks) {
@@ -482,7 +488,7 @@ __global__ __launch_bounds__(256) void k_csr_fused(CsrWork wk, SpmmArgs a, Updat
     }
     b -= wk.grid.mid_blocks;
     b = csr_block(blockIdx.x, b, wk.grid.short_blocks, wk.grid.run, 1, slice);
-    csr_short_fused_body<G>(b, wk, a, u, lds, rows16);
+    csr_short_fused_body<G>(b, wk, a, u, lds, rows_s);
 }
 
 // ---- rows the fused kernels did not finish: gather their aggregated rows and apply the update ---
@@ -553,50 +559,66 @@ __global__ __launch_bounds__(256) void k_reduce_partials(int32_t n_multi, const 
 }
 
 // ---- dispatch ---------------------------------------------------------------------------------
-struct CsrShape { int vec, nv, split; bool wide; };
+struct CsrShape { int vec, nv, lanes, group; bool wide; };
 
 // Vectors of up to 16 bytes per lane: 8 lanes per row for rows of 65 to 128 bytes (two rows at a time, see Gather), 16 lanes
 // otherwise, with 4 bytes (2 for 16-bit X) each for the narrow rows and several vectors each for the wide ones.  A row of X
 // needs no more than 4-byte alignment for that; 16-bit X with odd rows or an odd base is read element by element.
-static CsrShape pick_shape(const SpmmArgs& a)
+// narrow: rows of up to 128 bytes in the form of 8 lanes to an output row, if their alignment allows it.
+static CsrShape pick_shape(const SpmmArgs& a, bool narrow)
 {
     const bool f32 = a.x_dtype == HCSPMM_F32;
     const int es = f32 ? 4 : 2, per16 = 16 / es;
-    CsrShape sh{1, 1, 1, false};
+    CsrShape sh{1, 1, 16, 16, false};
     if (f32 || (a.d % 2 == 0 && a.ldx % 2 == 0 && (uintptr_t)a.X % 4 == 0)) {
-        if (a.d * es > 64) {
+        if (narrow && a.d * es <= 128) {
+            sh.lanes = sh.group = 8;
+            sh.vec = 4 / es;
+            while (8 * sh.vec < a.d) sh.vec *= 2;
+        } else if (a.d * es > 64) {
             sh.vec = per16;
-            if (a.d * es <= 128) sh.split = 2;
+            if (a.d * es <= 128) sh.lanes = 8;
         } else {
-            while (sh.vec < per16 && kGroup * sh.vec < a.d) sh.vec *= 2;
+            while (sh.vec < per16 && 16 * sh.vec < a.d) sh.vec *= 2;
         }
     }
     const int most = f32 ? 4 : (sh.vec == 1 ? 4 : 2);
-    while (sh.nv < most && kGroup / sh.split * sh.vec * sh.nv < a.d) sh.nv *= 2;
+    while (sh.nv < most && sh.lanes * sh.vec * sh.nv < a.d) sh.nv *= 2;
     if (!f32 && sh.vec == 1 && sh.nv > 1) sh.nv = 4;
     // 32-bit byte offsets reach 4 GiB of X (the last row is read to its end)
     sh.wide = ((uint64_t)(a.n_cols > 0 ? a.n_cols - 1 : 0) * (uint64_t)a.ldx + (uint64_t)a.d) * es >= ((uint64_t)1 << 32);
     return sh;
 }
-static int shape_cols(const CsrShape& sh) { return kGroup / sh.split * sh.vec * sh.nv; }
+static int shape_cols(const CsrShape& sh) { return sh.lanes * sh.vec * sh.nv; }
 
-#define HC_CSR_PANEL_DISPATCH(FN, XK, V)                                                             \
-    if (sh.split == 2) HC_CSR_ONE(FN, XK, V, 1, 2);                                                \
-    else if (sh.nv == 1) HC_CSR_ONE(FN, XK, V, 1, 1);                                              \
-    else HC_CSR_ONE(FN, XK, V, 2, 1);
-#define HC_CSR_ONE(FN, XK, V, NVV, SP) do { if (sh.wide) { FN(XK, V, NVV, SP, true); } else { FN(XK, V, NVV, SP, false); } } while (0)
+// FN(element kind, vector, vectors, lanes, group, wide)
+#define HC_CSR_ONE(FN, XK, V, NVV, L, GR) do { if (sh.wide) { FN(XK, V, NVV, L, GR, true); } else { FN(XK, V, NVV, L, GR, false); } } while (0)
+#define HC_CSR_PANEL_DISPATCH(FN, XK, V)                                                           \
+    if (sh.lanes == 8) HC_CSR_ONE(FN, XK, V, 1, 8, 16);                                            \
+    else if (sh.nv == 1) HC_CSR_ONE(FN, XK, V, 1, 16, 16);                                         \
+    else HC_CSR_ONE(FN, XK, V, 2, 16, 16);
+#define HC_CSR_DISPATCH32_16(FN)                                                                   \
+    if (sh.vec == 1) HC_CSR_ONE(FN, 0, 1, 1, 16, 16);                                              \
+    else if (sh.lanes == 8) HC_CSR_ONE(FN, 0, 4, 1, 8, 16);                                        \
+    else if (sh.nv == 1) HC_CSR_ONE(FN, 0, 4, 1, 16, 16);                                          \
+    else if (sh.nv == 2) HC_CSR_ONE(FN, 0, 4, 2, 16, 16);                                          \
+    else HC_CSR_ONE(FN, 0, 4, 4, 16, 16);
 #define HC_CSR_DISPATCH32(FN)                                                                      \
-    if (sh.vec == 1) HC_CSR_ONE(FN, 0, 1, 1, 1);                                                   \
-    else if (sh.split == 2) HC_CSR_ONE(FN, 0, 4, 1, 2);                                            \
-    else if (sh.nv == 1) HC_CSR_ONE(FN, 0, 4, 1, 1);                                               \
-    else if (sh.nv == 2) HC_CSR_ONE(FN, 0, 4, 2, 1);                                               \
-    else HC_CSR_ONE(FN, 0, 4, 4, 1);
+    if (sh.group == 8) {                                                                           \
+        if (sh.vec == 1) HC_CSR_ONE(FN, 0, 1, 1, 8, 8);                                            \
+        else if (sh.vec == 2) HC_CSR_ONE(FN, 0, 2, 1, 8, 8);                                       \
+        else HC_CSR_ONE(FN, 0, 4, 1, 8, 8);                                                        \
+    } else { HC_CSR_DISPATCH32_16(FN) }
 #define HC_CSR_DISPATCH16(FN, XK)                                                                  \
-    if (sh.vec == 1) { if (sh.nv == 1) HC_CSR_ONE(FN, XK, 1, 1, 1); else HC_CSR_ONE(FN, XK, 1, 4, 1); }  \
-    else if (sh.vec == 2) HC_CSR_ONE(FN, XK, 2, 1, 1);                                             \
-    else if (sh.split == 2) HC_CSR_ONE(FN, XK, 8, 1, 2);                                           \
-    else if (sh.nv == 1) HC_CSR_ONE(FN, XK, 8, 1, 1);                                              \
-    else HC_CSR_ONE(FN, XK, 8, 2, 1);
+    if (sh.group == 8) {                                                                           \
+        if (sh.vec == 2) HC_CSR_ONE(FN, XK, 2, 1, 8, 8);                                           \
+        else if (sh.vec == 4) HC_CSR_ONE(FN, XK, 4, 1, 8, 8);                                      \
+        else HC_CSR_ONE(FN, XK, 8, 1, 8, 8);                                                       \
+    } else if (sh.vec == 1) { if (sh.nv == 1) HC_CSR_ONE(FN, XK, 1, 1, 16, 16); else HC_CSR_ONE(FN, XK, 1, 4, 16, 16); }  \
+    else if (sh.vec == 2) HC_CSR_ONE(FN, XK, 2, 1, 16, 16);                                        \
+    else if (sh.lanes == 8) HC_CSR_ONE(FN, XK, 8, 1, 8, 16);                                       \
+    else if (sh.nv == 1) HC_CSR_ONE(FN, XK, 8, 1, 16, 16);                                         \
+    else HC_CSR_ONE(FN, XK, 8, 2, 16, 16);
 #define HC_CSR_DISPATCH(FN)                                                                        \
     if (a.x_dtype == HCSPMM_F32) { HC_CSR_DISPATCH32(FN) }                                         \
     else if (a.x_dtype == HCSPMM_BF16) { HC_CSR_DISPATCH16(FN, 1) }                                \
@@ -646,26 +668,53 @@ static int pick_slices(const SpmmArgs& a, const CsrHints& h, int32_t& slice_w)
     return n_slices;
 }
 
+// With the update fused in, a workgroup of 8-lane groups has 32 rows to multiply instead of 16, at the same barrier, loads of W
+// and epilogue: 2.4 M rows of 51, 32 -> 32: 2371 -> 2165 us, 300,000 of 20: 141 -> 111 us.  A graph that is all launches
+// prefers the shorter chains of 16 (2,708 rows: 6.9 us against 8.6 us).
+static bool fused_narrow(const SpmmArgs& a) { return a.n_rows > kMidRowFewRows; }
+
 // The fused update needs the whole aggregated row in one pass of a lane group and a width that the update's K loop takes
 // 16 at a time, and a launch holds 16 rows per workgroup of no more than 2^26 rows (and what mid and long rows they may be).
 bool update_fusable(const SpmmArgs& a)
 {
     if (a.d % 16 != 0 || a.d < 16 || a.d > 256 || a.n_rows > (1 << 26)) return false;
-    const CsrShape sh = pick_shape(a);
+    const CsrShape sh = pick_shape(a, fused_narrow(a));
     return shape_cols(sh) >= a.d && a.ldy % 4 == 0 && (uintptr_t)a.Y % 16 == 0 && mfma_update_fusable(a);
 }
 
 bool csr_panels_usable(const SpmmArgs& a)
 {
-    const CsrShape sh = pick_shape(a);
+    const CsrShape sh = pick_shape(a, false);
     return (int64_t)a.d * (a.x_dtype == HCSPMM_F32 ? 4 : 2) >= kPanelRowBytes && sh.vec == (a.x_dtype == HCSPMM_F32 ? 4 : 8);
+}
+
+// Where 8 lanes per output row (Gather's third form) are ahead of 16: on matrices of many short rows, which are bound by how
+// fast waves start and drain, and where rows of X off the 16-byte pieces make 16 narrow lanes touch more lines than 8 wider
+// ones.  16 against 8 lanes, fp32, us (16 columns bf16 as 8 columns fp32):
+//                               8 columns      16 columns     32 columns     7 columns
+//   2.4 M rows of 9             349 / 280      389 / 342      463 / 407      406 / 315
+//   169,343 of 15               26.2 / 22.1    28.1 / 28.2    33.1 / 32.5    35.4 / 27.2
+//   131,072 in communities, 20  17.5 / 13.7    18.6 / 20.7    22.7 / 22.3    28.0 / 19.4
+//   1 M of 21                   222 / 213      268 / 263      315 / 319      256 / 233
+//   50,021 of 29                10.0 / 9.7     12.1 / 14.2    14.6 / 15.8    16.3 / 12.9
+//   16,934 of 15                4.8 / 5.0      4.8 / 6.1      5.4 / 6.3      6.5 / 5.5
+//   300,000 of 61               129 / 137      170 / 178      --             161 / 150
+//   2.4 M of 51                 1607 / 1679    1878 / 1907    2100 / --      1797 / 1835
+static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
+{
+    const int64_t es = a.x_dtype == HCSPMM_F32 ? 4 : 2, row = a.d * es;
+    if (row > 128 || h.rows <= 0) return false;
+    const double degree = (double)h.nnz / (double)h.rows;
+    const bool off = a.ldx * es % 16 != 0 || (uintptr_t)a.X % 16 != 0;
+    return (off && row <= 64 && degree < 40.0) || (h.rows >= 100000 && degree <= (row <= 32 ? 24.0 : 16.0));
 }
 
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
                       int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd)
 {
-    CsrShape sh = pick_shape(a);
+    const bool narrow = upd ? fused_narrow(a) : !a.rowend && narrow_rows(a, hints);
+    CsrShape sh = pick_shape(a, narrow);
     CsrWork wk{};
     wk.n_segs = n_segs; wk.segs = segs; wk.partial = partial; wk.n_mid = n_mid; wk.mid_rows = mid_rows;
     wk.n_items = n_items; wk.row_list = row_list; wk.route = route; wk.mid_row = mid_row;
@@ -676,11 +725,11 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     int run = 5;
     if (tune().xcd_chunk >= 0) for (run = -1; tune().xcd_chunk >> (run + 1);) ++run;
     if (upd) {
-        // one slice, and a workgroup per 16 rows whatever the matrix
-        wk.grid = csr_grid(n_segs, n_mid, n_items, a.d, 1, a.d, run);
+        // one slice, and a row per group whatever the matrix
+        wk.grid = csr_grid(n_segs, n_mid, n_items, a.d, 1, a.d, run, sh.group);
         if (wk.grid.rows_per_group > 1) return hipErrorInvalidValue;        // (update_fusable bounds the rows)
-        if (wk.grid.blocks <= 0) return hipSuccess;
-#define HC_LAUNCH_CSRF(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr_fused<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)wk.grid.blocks), dim3(256), 0, s, wk, a, *upd)
+        if (wk.grid.blocks() <= 0) return hipSuccess;
+#define HC_LAUNCH_CSRF(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_csr_fused<Gather<XK, V, NVV, L, GR, W>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a, *upd)
         HC_CSR_DISPATCH(HC_LAUNCH_CSRF)
 #undef HC_LAUNCH_CSRF
         return hipGetLastError();
@@ -695,17 +744,17 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
         wk.mid_row = hints.long_row;
         wk.n_items = 0;
     }
-    wk.grid = csr_grid(n_segs, wk.n_mid, wk.n_items, a.d, n_slices, slice_w, run, tune().rpg >= 1 && tune().rpg <= kRowsPerGroup ? tune().rpg : 1);
-    if (wk.grid.blocks <= 0) return hipSuccess;
+    wk.grid = csr_grid(n_segs, wk.n_mid, wk.n_items, a.d, n_slices, slice_w, run, sh.group, tune().rpg >= 1 && tune().rpg <= sh.group ? tune().rpg : 1);
+    if (wk.grid.blocks() <= 0) return hipSuccess;
     if (wk.grid.n_slices > 1) {
         SpmmArgs t = a;
         t.d = wk.grid.slice_w;
         const bool wide = sh.wide;
-        sh = pick_shape(t);
+        sh = pick_shape(t, false);
         sh.wide = wide;
     }
-#define HC_LAUNCH_CSR(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)wk.grid.blocks), dim3(256), 0, s, wk, a)
-#define HC_LAUNCH_PANEL(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, SP, W, true>>), dim3((unsigned)wk.grid.blocks), dim3(256), 0, s, wk, a)
+#define HC_LAUNCH_CSR(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, L, GR, W>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
+#define HC_LAUNCH_PANEL(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, L, GR, W, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
     if (a.rowend) {
         // panels are taken for rows of kPanelRowBytes and more: 16-byte vectors, two per lane at most (wider slices take turns)
         if (sh.vec != (a.x_dtype == HCSPMM_F32 ? 4 : 8)) return hipErrorInvalidValue;
@@ -758,17 +807,17 @@ __global__ __launch_bounds__(256) void k_probe_gather(const int32_t* __restrict_
     // workgroups in XCD-local runs of 32, like the scalar path's short rows (the grid is padded to whole rounds)
     const int64_t x = blockIdx.x & 7, q = blockIdx.x >> 3;
     const int64_t blk = ((q / 32) * 8 + x) * 32 + q % 32;
-    const int64_t grp = blk * (256 / kGroup) + threadIdx.x / kGroup;
-    const int lig = threadIdx.x % kGroup;
+    const int64_t grp = blk * (256 / G::GROUP) + threadIdx.x / G::GROUP;
+    const int lig = threadIdx.x % G::GROUP;
     const int64_t b = min(n, grp * per_group), e = min(n, b + per_group);
     G g;
     g.init(a, 0, a.d, lig);
     float acc[G::N];
     vzero(acc);
-    for (int64_t k0 = b; k0 < e; k0 += kGroup) {                // (a group past the end of the stream has b == e)
+    for (int64_t k0 = b; k0 < e; k0 += G::GROUP) {                // (a group past the end of the stream has b == e)
         const int64_t k = min(k0 + lig, e - 1);
         const int32_t c = min(max(index[k], 0), n_rows_x - 1);  // whatever the stream holds, the read stays inside X
-        g.batch(g.key(c), 1.f, (int)min((int64_t)kGroup, e - k0), acc);
+        g.batch(g.key(c), 1.f, (int)min((int64_t)G::GROUP, e - k0), acc);
     }
     float t[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -776,11 +825,12 @@ __global__ __launch_bounds__(256) void k_probe_gather(const int32_t* __restrict_
     *reinterpret_cast<float4*>(out + ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4) = make_float4(t[0], t[1], t[2], t[3]);
 }
 
+constexpr int kProbeGroup = 16;
 // Launch shape of the probe: indices per lane group 512 (long enough to amortise the start-up) unless the stream is too
 // short to give every CU some tens of workgroups that way -- then fewer, down to 64.
 static void probe_gather_shape(int64_t n, int64_t& per_group, int64_t& blocks)
 {
-    const int64_t groups_per_block = 256 / kGroup;
+    const int64_t groups_per_block = 256 / kProbeGroup;
     per_group = (n / (8192 * groups_per_block) + 63) / 64 * 64;
     per_group = per_group < 64 ? 64 : (per_group > 512 ? 512 : per_group);
     const int64_t groups = (n + per_group - 1) / per_group;
@@ -804,9 +854,9 @@ hipError_t launch_probe_gather(const int32_t* index, int64_t n, const float* X, 
     probe_gather_shape(n, per_group, blocks);
     SpmmArgs a{};
     a.n_cols = n_rows_x; a.X = X; a.ldx = ldx; a.d = d; a.x_dtype = HCSPMM_F32;
-    const CsrShape sh = pick_shape(a);
-#define HC_PROBE(XK, V, NVV, SP, W) hipLaunchKernelGGL((k_probe_gather<Gather<XK, V, NVV, SP, W>>), dim3((unsigned)blocks), dim3(256), 0, s, index, n, per_group, a, n_rows_x, out)
-    HC_CSR_DISPATCH32(HC_PROBE)
+    const CsrShape sh = pick_shape(a, false);
+#define HC_PROBE(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_probe_gather<Gather<XK, V, NVV, L, GR, W>>), dim3((unsigned)blocks), dim3(256), 0, s, index, n, per_group, a, n_rows_x, out)
+    HC_CSR_DISPATCH32_16(HC_PROBE)
 #undef HC_PROBE
     return hipGetLastError();
 }

@@ -4,7 +4,7 @@ import pytest
 
 import oracle
 from workloads import (make_config, dense_normal, glorot_uniform, chung_lu_graph, gcn_normalise, tiny_random_csr,
-                       sbm_graph)
+                       sbm_graph, CSRGraph)
 from gpu_util import device_graph, assert_close
 
 pytestmark = pytest.mark.gpu
@@ -327,3 +327,22 @@ def test_backward_of_a_directed_graph_through_the_transposed_plan():
     scale = float(np.sum(np.abs(G) * oracle.gcn_layer(g.rowptr, g.colind, g.vals, X, W, use_abs=True)))
     assert abs(float(np.sum(dW * W)) - L) <= 1e-5 * scale
     assert abs(float(np.sum(dX * X)) - L) <= 1e-5 * scale
+
+
+# more than 65,536 rows: 32 rows per workgroup in the fused pass for rows of up to 128 bytes; a ragged last workgroup
+@pytest.mark.parametrize("din,dout", [(1, 16), (17, 32), (64, 32), (33, 16), (48, 64)])
+@pytest.mark.parametrize("mode", [1, 3])
+def test_fused_update_of_many_rows(din, dout, mode):
+    n = 65_600 + 13
+    rng = np.random.default_rng(din)
+    lengths = rng.integers(0, 9, n)
+    lengths[[3, 70, 31_000, n - 1]] = [130, 300, 1100, 2100]
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    g = CSRGraph(n, 3000, rowptr, rng.integers(0, 3000, rowptr[-1]).astype(np.int32), rng.standard_normal(rowptr[-1]).astype(np.float32))
+    X, W, G = dense_normal(n, din, seed=1), glorot_uniform(din, dout, seed=2), dense_normal(3000, dout, seed=3)
+    dX, dW, S = run_backward(g, G, X, W, mode, pad=din % 3, sel_coef=[1, 0, -64] if mode == 3 else None, mask_dx=True, update_fusion=1)
+    rows = np.unique(np.concatenate([np.arange(0, n, 37), [3, 70, 31_000], np.arange(n - 70, n)]))
+    S_ref, S_abs = (oracle.spmm_rows(rows, g.rowptr, g.colind, g.vals, G, None, use_abs=b) for b in (False, True))
+    assert_close(S[rows], S_ref, S_abs, TOL_F32, "S")
+    ref = np.where(X[rows] > 0, S_ref @ W.astype(np.float64).T, 0.0)
+    assert_close(dX[rows], ref, S_abs @ np.abs(W).astype(np.float64).T, TOL_F32, "masked dX")

@@ -32,6 +32,46 @@ def test_fp32_widths_and_row_lengths(d):
     assert_close(Y, ref, bound, 1e-5, "fp32 d=%d" % d)
 
 
+# four lanes to a row: one, two and four (16-bit: two, four, eight) columns per lane, the last vector moved left or whole
+@pytest.mark.parametrize("d", [1, 2, 4, 5, 6, 7, 8, 9, 10, 13, 14, 16])
+@pytest.mark.parametrize("n", [40, 20_000])
+def test_narrow_rows(n, d):
+    g = rows_of(np.resize(LENGTHS[:16] if n > 1000 else LENGTHS, n), 5000, d)
+    X = np.random.default_rng(d).standard_normal((g.n_cols, d)).astype(np.float32)
+    rows = np.unique(np.concatenate([np.arange(0, n, 1 + n // 2000), np.arange(n - 20, n)]))
+    Y, _ = gpu_spmm(g, X, 1, pad_x=d % 3, pad_y=d % 4)
+    ref, bound = oracle_pair(g, X, rows=rows)
+    assert_close(Y[rows], ref, bound, 1e-5, "fp32 d=%d" % d)
+    for kind, code, bits in (("bf16", oracle.DT_BF16, to_bf16_bits), ("f16", oracle.DT_F16, to_f16_bits)):
+        X = bits(np.random.default_rng(d).standard_normal((g.n_cols, 2 * d)).astype(np.float32))
+        Y, _ = gpu_spmm(g, X, 1, pad_x=2 * (d % 3), pad_y=d % 4, x_bits=kind)
+        ref, bound = oracle_pair(g, X, rows=rows, x_dtype=code)
+        assert_close(Y[rows], ref, bound, 1e-5, "%s d=%d" % (kind, 2 * d))
+
+
+# eight lanes to an output row: a matrix of many short rows, or rows of X off the 16-byte pieces; one, two and four columns per
+# lane (16-bit: two, four, eight), the last vector moved left or whole
+@pytest.mark.parametrize("d", [1, 4, 5, 7, 8, 9, 10, 13, 16, 17, 30, 31, 32])
+@pytest.mark.parametrize("n", [48, 100_003])
+def test_narrow_rows(n, d):
+    lengths = np.resize([3, 0, 7, 8, 9, 1, 16, 17, 12, 2, 20], n)
+    lengths[[5, n - 1]] = [129, 64]
+    if n > 1000:
+        lengths[[77, 50_000, 99_999]] = [300, 1025, 2049]
+    g = rows_of(lengths, 5000, d)
+    rows = np.unique(np.concatenate([np.arange(0, n, 1 + n // 3000), np.flatnonzero(lengths > 20), np.arange(n - 40, n)]))
+    pad = 0 if n > 1000 else 1 + (d + 1) % 4 + (d % 4 == 3)           # (the small matrix: an odd pitch)
+    X = np.random.default_rng(d).standard_normal((g.n_cols, d)).astype(np.float32)
+    Y, _ = gpu_spmm(g, X, 1, pad_x=pad, pad_y=d % 4)
+    ref, bound = oracle_pair(g, X, rows=rows)
+    assert_close(Y[rows], ref, bound, 1e-5, "fp32 d=%d" % d)
+    for kind, code, bits in (("bf16", oracle.DT_BF16, to_bf16_bits), ("f16", oracle.DT_F16, to_f16_bits)):
+        X = bits(np.random.default_rng(d).standard_normal((g.n_cols, 2 * d)).astype(np.float32))
+        Y, _ = gpu_spmm(g, X, 1, pad_x=2 * pad, pad_y=d % 4, x_bits=kind)
+        ref, bound = oracle_pair(g, X, rows=rows, x_dtype=code)
+        assert_close(Y[rows], ref, bound, 1e-5, "%s d=%d" % (kind, 2 * d))
+
+
 @pytest.mark.parametrize("kind", ["bf16", "f16"])
 @pytest.mark.parametrize("d,pad", [(1, 0), (2, 0), (15, 0), (16, 1), (18, 0), (32, 2), (34, 0), (62, 0), (64, 0), (66, 2), (128, 0),
                                    (130, 0), (131, 0), (256, 0), (258, 0)])
