@@ -317,8 +317,9 @@ constexpr int kRunMinSlice = 2048;     // union columns per workgroup slice of a
 constexpr int kRunTargetSlices = 4096; // ... and about this many slices over all runs of a large matrix
 hipError_t launch_reduce_tiles(const SpmmArgs& a, int32_t n_multi, const MultiRow* multi, const float* tile_partial,
                                hipStream_t s);
+// T = X W; with a mask (m x n, pitch ldm) T is stored as 0 where it is not positive
 hipError_t launch_gemm_f32(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
-                           float* T, int64_t ldt, int relu, hipStream_t s);
+                           float* T, int64_t ldt, const float* mask, int64_t ldm, hipStream_t s);
 // backward pass (Eq. 3): dW = X^T S over row spans, activation mask, transpose of W
 int32_t gemm_tn_spans(int64_t n_rows, int32_t d_in, int32_t d);
 hipError_t launch_gemm_tn(int64_t n_rows, const float* X, int64_t ldx, int32_t d_in, const float* S, int64_t lds_,
@@ -331,7 +332,8 @@ hipError_t launch_transpose(int32_t rows, int32_t cols, const float* W, int64_t 
 // left alone.
 hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
                                void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s,
-                               const uint8_t* done_route = nullptr, const int32_t* done_cols = nullptr);
+                               const uint8_t* done_route = nullptr, const int32_t* done_cols = nullptr,
+                               const float* mask = nullptr, int64_t ldm = 0);
 
 }  // namespace hcspmm
 

@@ -29,13 +29,46 @@ template <int N> struct __attribute__((packed, aligned(4))) f32_any { float v[N]
 
 constexpr int kGemmWaves = 4, kGemmRows = 16 * kGemmWaves, kGemmBK = 32;
 
-// Stores a wave's 16 rows from m0 on and 16*NT columns from n0 on.  tvec: T takes vector stores of four (or of the two columns
-// of a group of two); N is a multiple of four then.
+// Where the product goes: T (M x N, pitch ldt, element type t_dtype), max(0, .) applied first with relu; with a mask (pitch
+// ldm) results are stored as 0 where it is not positive.  vec: T takes vector stores of four (or of the two columns of a group
+// of two); N is a multiple of four then.
+struct GemmOut { float* T; int64_t ldt; const float* mask; int64_t ldm; int32_t t_dtype, relu, vec; };
+
+// Stores a wave's 16 rows from m0 on and 16*NT columns from n0 on.
 template <int NT>
-__device__ __forceinline__ void store_tile(const v4f_gemm (&acc)[NT], int64_t m0, int n0, int64_t M, int32_t N, float* __restrict__ T,
-                                           int64_t ldt, int32_t t_dtype, int relu, int tvec, int c, int q)
+__device__ __forceinline__ void store_tile(v4f_gemm (&acc)[NT], int64_t m0, int n0, int64_t M, int32_t N, const GemmOut& o, int c, int q)
 {
     constexpr int G4 = NT / 4, R = NT % 4;
+    float* __restrict__ T = o.T;
+    const int64_t ldt = o.ldt;
+    const int t_dtype = o.t_dtype, relu = o.relu, tvec = o.vec;
+    if (o.mask) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t row = m0 + 4 * q + r;
+            if (row >= M) continue;
+            const float* __restrict__ mk = o.mask + row * o.ldm;
+#pragma unroll
+            for (int g = 0; g < G4; ++g) {
+                const int col = n0 + 64 * g + 4 * c;
+                float mv[4] = {0.f, 0.f, 0.f, 0.f};
+                if (col + 3 < N) {
+                    const f4_any v = *reinterpret_cast<const f4_any*>(mk + col);
+                    mv[0] = v.x; mv[1] = v.y; mv[2] = v.z; mv[3] = v.w;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) if (col + j < N) mv[j] = mk[col + j];
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) if (!(mv[j] > 0.f)) acc[4 * g + j][r] = 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int col = n0 + 64 * G4 + R * c + j;
+                if (col < N && !(mk[col] > 0.f)) acc[4 * G4 + j][r] = 0.f;
+            }
+        }
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t row = m0 + 4 * q + r;
@@ -73,8 +106,8 @@ __device__ __forceinline__ void store_tile(const v4f_gemm (&acc)[NT], int64_t m0
 // operands.  WIDE: byte offsets inside a slab of W need 64 bits (launch_gemm_f32_out says when).
 template <int NT, int WV, bool WIDE>
 __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k_gemm_f32(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
-                                                     const float* __restrict__ Wm, int64_t ldw, float* __restrict__ T, int64_t ldt,
-                                                     int32_t t_dtype, int relu, int tvec, const uint8_t* __restrict__ done_route,
+                                                     const float* __restrict__ Wm, int64_t ldw, GemmOut out,
+                                                     const uint8_t* __restrict__ done_route,
                                                      const int32_t* __restrict__ done_cols, int32_t done_max)
 {
     constexpr int COLS = 16 * NT, SLAB = kGemmBK * COLS;
@@ -237,7 +270,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
         if (whole + 16 < K) multiply(Two{}, b, a);
         else multiply(One{}, b, a);
     }
-    if (!skip) store_tile<NT>(acc, m0, n0, M, N, T, ldt, t_dtype, relu, tvec, c, q);
+    if (!skip) store_tile<NT>(acc, m0, n0, M, N, out, c, q);
 }
 
 // The product with W kept in registers (K <= 128 and a multiple of four): a wave holds the 16*NT columns of W that are its
@@ -249,8 +282,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
 // at 17,000 x 128 x 128 (the CUs of an XCD asking one L2 channel for the same lines at the same time).
 template <int K16, int NT>
 __global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
-                                                         const float* __restrict__ Wm, int64_t ldw, float* __restrict__ T, int64_t ldt,
-                                                         int32_t t_dtype, int relu, int tvec, int wvec, int32_t groups)
+                                                         const float* __restrict__ Wm, int64_t ldw, GemmOut out, int wvec, int32_t groups)
 {
     extern __shared__ __attribute__((aligned(16))) float smem[];    // 16*K16 rows of W, groups * 16*NT columns each
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 15, q = lane >> 4;
@@ -323,22 +355,24 @@ __global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, i
             request(min(tile + streams, last), u);
             __builtin_amdgcn_sched_barrier(0);
         }
-        store_tile<NT>(acc, tile * 16, n0, M, N, T, ldt, t_dtype, relu, tvec, c, q);
+        store_tile<NT>(acc, tile * 16, n0, M, N, out, c, q);
     }
 }
 
 hipError_t launch_gemm_f32(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
-                           float* T, int64_t ldt, int relu, hipStream_t s)
+                           float* T, int64_t ldt, const float* mask, int64_t ldm, hipStream_t s)
 {
-    return launch_gemm_f32_out(m, k, n, X, ldx, W, ldw, T, ldt, HCSPMM_F32, relu, s);
+    return launch_gemm_f32_out(m, k, n, X, ldx, W, ldw, T, ldt, HCSPMM_F32, 0, s, nullptr, nullptr, mask, ldm);
 }
 
 hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
                                void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s, const uint8_t* done_route,
-                               const int32_t* done_cols)
+                               const int32_t* done_cols, const float* mask, int64_t ldm)
 {
     if (m <= 0 || n <= 0) return hipSuccess;
     if (t_dtype != HCSPMM_F32 && t_dtype != HCSPMM_BF16 && t_dtype != HCSPMM_F16) return hipErrorInvalidValue;
+    const GemmOut out{static_cast<float*>(T), ldt, mask, ldm, t_dtype, relu,
+                      n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0};
     // W in registers where it is small and the product streams: 2.4 M x 64 x 32: 199 -> 170 us, 2.4 M x 16 x 16: 109 -> 58 us,
     // 169,343 x 128 x 64: 41 -> 37 us.  Wider products are bound by the matrix units and level or behind (400,000 x 128 x 96:
     // 111 -> 123 us), short ones spend more on bringing all of W in first (20,000 x 128 x 64: 8.0 -> 9.7 us).
@@ -352,9 +386,7 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
         const dim3 grid((unsigned)std::min<int64_t>(want, k16 * nt > 16 ? 256 : k16 * nt > 4 ? 512 : 1024), (unsigned)ny);
         const size_t lds = (size_t)16 * k16 * groups * 16 * nt * sizeof(float);                     // 48 KB at most
         const int wvec = n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0;
-        const int tvec = n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
-        float* Tf = static_cast<float*>(T);
-#define HC_REG(KK, NT) hipLaunchKernelGGL((k_gemm_f32_reg<KK, NT>), grid, dim3(512), lds, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, tvec, wvec, groups)
+#define HC_REG(KK, NT) hipLaunchKernelGGL((k_gemm_f32_reg<KK, NT>), grid, dim3(512), lds, s, m, k, n, X, ldx, W, ldw, out, wvec, groups)
 #define HC_REG_NT(KK) case KK: if (nt == 4) HC_REG(KK, 4); else if (nt == 3) HC_REG(KK, 3); else if (nt == 2) HC_REG(KK, 2); else HC_REG(KK, 1); break
         switch (k16) {
             HC_REG_NT(1); HC_REG_NT(2); HC_REG_NT(3); HC_REG_NT(4); HC_REG_NT(5); HC_REG_NT(6); HC_REG_NT(7); HC_REG_NT(8);
@@ -371,9 +403,7 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
     const dim3 grid((unsigned)((m + kGemmRows - 1) / kGemmRows), (unsigned)(groups / pair));
     const size_t lds = (size_t)pair * 2 * kGemmBK * 16 * nt * sizeof(float);
     const int wv = (n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0) ? 4 : 1;
-    const int tvec = n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0;
-    float* Tf = static_cast<float*>(T);
-#define HC_LAUNCH_GEMM(NT, WV, WIDE) hipLaunchKernelGGL((k_gemm_f32<NT, WV, WIDE>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, Tf, ldt, t_dtype, relu, tvec, done_route, done_cols, kMfmaSmallMaxCols)
+#define HC_LAUNCH_GEMM(NT, WV, WIDE) hipLaunchKernelGGL((k_gemm_f32<NT, WV, WIDE>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, out, done_route, done_cols, kMfmaSmallMaxCols)
 #define HC_GEMM_NT(NT) case NT: if (wv == 4) HC_LAUNCH_GEMM(NT, 4, false); else HC_LAUNCH_GEMM(NT, 1, false); break
     if (wide) HC_LAUNCH_GEMM(8, 1, true);
     else switch (nt) {

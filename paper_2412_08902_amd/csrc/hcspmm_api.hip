@@ -1399,7 +1399,7 @@ hcspmm_status hcspmm_gemm_f32(int64_t m, int32_t k, int32_t n, const float* d_X,
     if (k > 0 && (st = check_dense("X", d_X, ldx, k)) != HCSPMM_OK) return st;
     if (k > 0 && (st = check_dense("W", d_W, ldw, n)) != HCSPMM_OK) return st;
     if ((st = check_dense("T", d_T, ldt, n)) != HCSPMM_OK) return st;
-    HC_HIP(launch_gemm_f32(m, k, n, d_X, ldx, d_W, ldw, d_T, ldt, 0, static_cast<hipStream_t>(stream)));
+    HC_HIP(launch_gemm_f32(m, k, n, d_X, ldx, d_W, ldw, d_T, ldt, nullptr, 0, static_cast<hipStream_t>(stream)));
     return HCSPMM_OK;
 }
 
@@ -1583,10 +1583,8 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
                 if ((st = run_spmm(plan, a, s, nullptr, &u, place == kUpdateInWindows)) != HCSPMM_OK) return st;
             } else {
                 if ((st = run_spmm(plan, a, s)) != HCSPMM_OK) return st;
-                HC_HIP(launch_gemm_f32(plan->n_rows, d_out, d_in, S, d_out, Wt, d_in, static_cast<float*>(d_dX), lddx, 0, s));
-                if (mask_dx_by_x)
-                    HC_HIP(launch_relu_mask(plan->n_rows, d_in, static_cast<const float*>(d_dX), lddx,
-                                            static_cast<const float*>(d_X), ldx, static_cast<float*>(d_dX), lddx, s));
+                HC_HIP(launch_gemm_f32(plan->n_rows, d_out, d_in, S, d_out, Wt, d_in, static_cast<float*>(d_dX), lddx,
+                                       mask_dx_by_x ? static_cast<const float*>(d_X) : nullptr, ldx, s));
             }
         } else if ((st = run_spmm(plan, a, s)) != HCSPMM_OK) {
             return st;

@@ -329,6 +329,24 @@ def test_backward_of_a_directed_graph_through_the_transposed_plan():
     assert abs(float(np.sum(dX * X)) - L) <= 1e-5 * scale
 
 
+# the mask in the separate product's epilogue: one to eight column tiles and remainders, W in slabs and in registers
+@pytest.mark.parametrize("n", [300, 65_541])
+@pytest.mark.parametrize("din,dout", [(1, 4), (16, 16), (17, 32), (32, 32), (33, 20), (64, 64), (100, 33), (130, 48), (47, 128), (256, 24)])
+def test_masked_dx_through_the_separate_product(n, din, dout):
+    g = tiny_random_csr(n, 200, 0.01, seed=n + din)
+    X, W, G = dense_normal(n, din, seed=1), glorot_uniform(din, dout, seed=2), dense_normal(200, dout, seed=3)
+    X[::5] = 0.0
+    dX, dW, S = run_backward(g, G, X, W, pad=din % 3, mask_dx=True, want_dw=n < 1000, update_fusion=2)
+    rows = np.unique(np.concatenate([np.arange(0, n, 1 + n // 1500), np.arange(max(0, n - 70), n)]))
+    S_ref, S_abs = (oracle.spmm_rows(rows, g.rowptr, g.colind, g.vals, G, None, use_abs=b) for b in (False, True))
+    on = X[rows] > 0
+    ref = np.where(on, S_ref @ W.astype(np.float64).T, 0.0)
+    assert np.all(dX[X <= 0] == 0.0)
+    assert_close(dX[rows], ref, S_abs @ np.abs(W).astype(np.float64).T, TOL_F32, "masked dX")
+    if dW is not None:
+        check(g, G, X, W, None, dW, S)
+
+
 # more than 65,536 rows: 32 rows per workgroup in the fused pass for rows of up to 128 bytes; a ragged last workgroup
 @pytest.mark.parametrize("din,dout", [(1, 16), (17, 32), (64, 32), (33, 16), (48, 64)])
 @pytest.mark.parametrize("mode", [1, 3])
