@@ -1445,24 +1445,31 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
 // Which windows keep their aggregated rows on chip for the update, when the caller leaves the choice to the library.
 //  * A graph so small that launches dominate: all of them, in one pass (2,708 rows: 64 -> 128 columns 8.2 us against 9.9 us
 //    with the product apart; at 16,934 rows it is 28.6 us against 19.7 us, and the line moves with the width).
-//  * Otherwise the scalar path's rows always go through the workspace: its own kernel with column slices and a whole product
+//  * A large aggregation is bound by what it fetches from behind L2 and hides the product, and the round trip of the
+//    aggregated rows is what is left to save (apart / in one pass, us): 1 M rows of 60, 32 -> 32: 910 / 883, 64 -> 64: 1946 /
+//    1892, 128 -> 128: 4221 / 3908; 2.4 M of 51: 2236 / 2165, 4652 / 4415, 9374 / 8658; but 2.4 M of 20: 972 / 1027, 1911 /
+//    2209.  A product of 128 x 128 or more is large enough to be hidden earlier: 500,000 of 60: 1926 / 1814, 2.4 M of 20: 4245 /
+//    4081, 300,000 of 60: 1040 / 1027.  When the pass has to store the aggregated rows all the same (the weight gradient reads
+//    them) it takes 40 non-zeros per row: 1 M of 40, 128 -> 128: 3268 / 3083, 2.4 M of 20: 4879 / 4945.
+//  * Otherwise the scalar path's rows go through the workspace: its own kernel with column slices and a whole product
 //    are ahead of tiles of 16 rows that wait for their longest row (169,343 rows, 32 -> 32: 73 us against 47 us, 128 -> 128:
 //    195 us against 175 us).
-//  * The wave-per-window matrix kernel multiplies its tile while other waves gather (131,072 rows in communities of degree
-//    50, 128 -> 128 columns: 157 us against 202 us), unless the multiplication outweighs the gather it hides behind: at
-//    degree 20, 128 -> 64 is 68 us against 74 us, 192 -> 128 153 us against 133 us; and few windows do not hide it (16,384
-//    rows, 96 -> 256: 40 us against 32 us).
+//  * The wave-per-window matrix kernel multiplies its tile while other waves gather, unless the multiplication outweighs the
+//    gather it hides behind (apart / in the windows; communities of degree 51, 131,072 rows: 64 -> 256: 124 / 108 us, 128 ->
+//    128: 153 / 153 us, 128 -> 160: 170 / 181 us, 256 -> 80: 308 / 349 us; of degree 20: 128 -> 64 74 / 68 us, 192 -> 128 133 /
+//    153 us); few windows do not hide it (16,384 rows, 96 -> 256: 32 / 40 us).
 enum UpdatePlace { kUpdateApart, kUpdateInWindows, kUpdateEverywhere };
-static UpdatePlace update_place(const hcspmm_plan* plan, int32_t agg_width, int32_t out_width)
+static UpdatePlace update_place(const hcspmm_plan* plan, int32_t agg_width, int32_t out_width, bool keep_z)
 {
-    if ((int64_t)plan->n_rows * agg_width <= 200000 && plan->n_rows <= 8192 && plan->n_panels < 2 && 4 * (int64_t)plan->n_rest < plan->n_rows)
-        return kUpdateEverywhere;
     const int64_t product = (int64_t)agg_width * out_width;
-    const bool deep = plan->nnz_mfma >= 40 * (int64_t)kH * plan->n_mfma;
-    if (!plan->scalar_exec && 2 * plan->n_mfma_small >= plan->W &&
-        (product <= 12288 || (plan->n_mfma_small >= 4096 && (product <= 16384 || deep))))
-        return kUpdateInWindows;
-    return kUpdateApart;
+    const bool windows = !plan->scalar_exec && 2 * plan->n_mfma_small >= plan->W;
+    if (plan->n_panels < 2 && 4 * (int64_t)plan->n_rest < plan->n_rows) {
+        const double degree = plan->n_rows > 0 ? (double)plan->nnz / plan->n_rows : 0.0;
+        if ((int64_t)plan->n_rows * agg_width <= 200000 && plan->n_rows <= 8192) return kUpdateEverywhere;
+        if (!windows && plan->n_rows >= 1000000 && degree >= 50.0) return kUpdateEverywhere;
+        if (!windows && product >= 16384 && plan->n_rows >= 300000 && plan->nnz >= 16000000 && (!keep_z || degree >= 40.0)) return kUpdateEverywhere;
+    }
+    return windows && product <= (plan->n_mfma_small >= 4096 ? 16384 : 12288) ? kUpdateInWindows : kUpdateApart;
 }
 
 size_t hcspmm_aggregate_update_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)
@@ -1497,7 +1504,7 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
     a.X = d_X; a.ldx = ldx; a.d = d_in; a.x_dtype = x_dtype; a.Y = Z; a.ldy = d_in; a.relu = 0;
     const UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
                               : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
-                                                                               : update_place(plan, d_in, d_out);
+                                                                               : update_place(plan, d_in, d_out, false);
     if (place != kUpdateApart && update_fusable(a)) {
         const UpdateArgs u{static_cast<const float*>(d_W), ldw, d_out, static_cast<float*>(d_Y), ldy, apply_relu ? 1 : 0, 0,
                            nullptr, 0, y_dtype};
@@ -1570,11 +1577,10 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
         a.X = G; a.ldx = g_ld; a.d = d_out; a.x_dtype = HCSPMM_F32; a.Y = S; a.ldy = d_out; a.relu = 0;
         if (d_dX) {
             HC_HIP(launch_transpose(d_in, d_out, static_cast<const float*>(d_W), ldw, Wt, s));
-            // as in hcspmm_aggregate_update; when dW needs S in memory or the mask an epilogue, only a graph that is all
-            // launches has its update fused
+            // as in hcspmm_aggregate_update; the wave-per-window kernel neither stores S for dW nor applies the mask
             UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
                                 : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
-                                                                                 : update_place(plan, d_out, d_in);
+                                                                                 : update_place(plan, d_out, d_in, d_dW != nullptr);
             if (place == kUpdateInWindows && (d_dW || mask_dx_by_x)) place = kUpdateApart;
             if (place != kUpdateApart && update_fusable(a)) {
                 // the next layer's activation mask (its output is this layer's input X) goes into the update's epilogue
