@@ -37,16 +37,16 @@ constexpr int kMidRow = 128;           // rows with more non-zeros than this get
 constexpr int kMidRowSmall = 64, kMidRowFewRows = 65536;
 constexpr int kFusedMidRow = 256;      // with the update stage fused in, rows up to this length stay in the workgroup's tile
 constexpr int kLongRow = 1024;         // rows with more non-zeros than this are cut into workgroup-sized segments
-// ... from 256 non-zeros on where rows have fewer than 100 on average and the matrix has 256 to 170,000 of them: a wave that
-// walks 1000 non-zeros outlasts everything else there (rows cut from 1024 / from 256 non-zeros on, 64 columns, bf16: 320 rows
-// of 20 with some of 1000: 13.7 / 5.6 us, 2,000 of 60 with some of 400: 7.7 / 5.0 us, 16,000 of 60: 16.5 / 10.6 us, 65,000 of
-// 20: 28.2 / 17.7 us, 100,000 of 8: 24.0 / 17.7 us, 169,000 of 20: 45.1 / 44.4 us; 128 columns, fp32: 320 rows: 9.7 / 5.0 us,
-// 16,000: 29.2 / 29.3, 65,000: 52.4 / 51.5 and 169,000: 162 / 162 us).  Above, other rows hide the long ones; a matrix of a
-// handful of rows keeps the plain tiers.  256 threads per row only add their reduction where long rows are many (30,000 of
-// 200: 183 -> 192 us).
+// ... from 256 non-zeros on where rows have fewer than 100 on average: a wave that walks 1000 non-zeros outlasts everything
+// else there (rows cut from 1024 / from 256 non-zeros on, 64 columns, bf16: 320 rows of 20 with some of 1000: 13.7 / 5.6 us,
+// 2,000 of 60 with some of 400: 7.7 / 5.0 us, 16,000 of 60: 16.5 / 10.6 us, 65,000 of 20: 28.2 / 17.7 us, 169,000 of 20: 45.1 /
+// 44.4 us; 128 columns, fp32: 9.7 / 5.0 us for the first, 29.2 / 29.3, 52.4 / 51.5 and 162 / 162 us; 8 lanes to a row, 32
+// columns: 200,000 rows of 10: 42 / 29.5 us, 350,000: 56 / 50.6 us).  On more rows the long ones are hidden: level within 2 %
+// to 2.4 M rows.  A matrix of a handful of rows keeps the plain tiers.  256 threads per row only add their reduction where
+// long rows are many (30,000 of 200: 183 -> 192 us).
 constexpr int kLongRowSparse = 256;
 constexpr int64_t kLongRowDegree = 100;
-constexpr int32_t kLongRowFewRows = 256, kLongRowManyRows = 170000;
+constexpr int32_t kLongRowFewRows = 256;
 constexpr int kSegLen = 2048;          // non-zeros per segment of a long row
 
 struct Segment { int32_t row, k_begin, k_end, slot; };    // slot < 0: writes Y directly

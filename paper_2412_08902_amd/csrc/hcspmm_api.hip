@@ -1069,7 +1069,7 @@ static hcspmm_status init_plan_header(hcspmm_plan* p, int32_t n_rows, int32_t n_
     p->rowptr = d_rowptr; p->colind = d_colind; p->vals = d_vals;
     p->opt = o;
     p->mid_row = n_rows <= kMidRowFewRows ? kMidRowSmall : kMidRow;
-    p->long_row = n_rows >= kLongRowFewRows && n_rows <= kLongRowManyRows && nnz < kLongRowDegree * n_rows ? kLongRowSparse : kLongRow;
+    p->long_row = n_rows >= kLongRowFewRows && nnz < kLongRowDegree * n_rows ? kLongRowSparse : kLongRow;
     // tuning knobs for experiments (not part of the ABI): override the row-tier thresholds
     if (tune().mid_row >= 1) p->mid_row = tune().mid_row;
     if (tune().long_row >= p->mid_row) p->long_row = tune().long_row;
