@@ -1449,7 +1449,7 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
 //    aggregated rows is what is left to save (apart / in one pass, us): 1 M rows of 60, 32 -> 32: 910 / 883, 64 -> 64: 1946 /
 //    1892, 128 -> 128: 4221 / 3908; 2.4 M of 51: 2236 / 2165, 4652 / 4415, 9374 / 8658; but 2.4 M of 20: 972 / 1027, 1911 /
 //    2209.  A product of 128 x 128 or more is large enough to be hidden earlier: 500,000 of 60: 1926 / 1814, 2.4 M of 20: 4245 /
-//    4081, 300,000 of 60: 1040 / 1027.  When the pass has to store the aggregated rows all the same (the weight gradient reads
+//    4081, 300,000 of 60: 1040 / 1027; f16 470,000 of 57: 896 / 859.  When the pass has to store the aggregated rows all the same (the weight gradient reads
 //    them) it takes 40 non-zeros per row: 1 M of 40, 128 -> 128: 3268 / 3083, 2.4 M of 20: 4879 / 4945.
 //  * Otherwise the scalar path's rows go through the workspace: its own kernel with column slices and a whole product
 //    are ahead of tiles of 16 rows that wait for their longest row (169,343 rows, 32 -> 32: 73 us against 47 us, 128 -> 128:
@@ -1459,15 +1459,22 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
 //    128: 153 / 153 us, 128 -> 160: 170 / 181 us, 256 -> 80: 308 / 349 us; of degree 20: 128 -> 64 74 / 68 us, 192 -> 128 133 /
 //    153 us); few windows do not hide it (16,384 rows, 96 -> 256: 32 / 40 us).
 enum UpdatePlace { kUpdateApart, kUpdateInWindows, kUpdateEverywhere };
-static UpdatePlace update_place(const hcspmm_plan* plan, int32_t agg_width, int32_t out_width, bool keep_z)
+static UpdatePlace update_place(const hcspmm_plan* plan, int32_t agg_width, int32_t out_width, int32_t x_dtype, bool keep_z)
 {
     const int64_t product = (int64_t)agg_width * out_width;
     const bool windows = !plan->scalar_exec && 2 * plan->n_mfma_small >= plan->W;
     if (plan->n_panels < 2 && 4 * (int64_t)plan->n_rest < plan->n_rows) {
         const double degree = plan->n_rows > 0 ? (double)plan->nnz / plan->n_rows : 0.0;
         if ((int64_t)plan->n_rows * agg_width <= 200000 && plan->n_rows <= 8192) return kUpdateEverywhere;
-        if (!windows && plan->n_rows >= 1000000 && degree >= 50.0) return kUpdateEverywhere;
-        if (!windows && product >= 16384 && plan->n_rows >= 300000 && plan->nnz >= 16000000 && (!keep_z || degree >= 40.0)) return kUpdateEverywhere;
+        // (the pass reads a row with all lanes of its form at once; 16-bit rows that leave some of them idle are better cut
+        // into column slices: 2.4 M of 51, f16, 208 -> 183: 10.7 ms apart, 12.3 ms in one pass)
+        const bool f32 = x_dtype == HCSPMM_F32, full = (agg_width & (agg_width - 1)) == 0;
+        if (!windows && (f32 || full)) {
+            if (plan->n_rows >= 1000000 && degree >= 50.0) return kUpdateEverywhere;
+            if (product >= 16384 && plan->n_rows >= 300000 && plan->nnz >= 16000000 && (full || agg_width <= 128) &&
+                degree >= (!f32 ? 50.0 : keep_z ? 40.0 : 0.0))
+                return kUpdateEverywhere;
+        }
     }
     return windows && product <= (plan->n_mfma_small >= 4096 ? 16384 : 12288) ? kUpdateInWindows : kUpdateApart;
 }
@@ -1504,7 +1511,7 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
     a.X = d_X; a.ldx = ldx; a.d = d_in; a.x_dtype = x_dtype; a.Y = Z; a.ldy = d_in; a.relu = 0;
     const UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
                               : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
-                                                                               : update_place(plan, d_in, d_out, false);
+                                                                               : update_place(plan, d_in, d_out, x_dtype, false);
     if (place != kUpdateApart && update_fusable(a)) {
         const UpdateArgs u{static_cast<const float*>(d_W), ldw, d_out, static_cast<float*>(d_Y), ldy, apply_relu ? 1 : 0, 0,
                            nullptr, 0, y_dtype};
@@ -1580,7 +1587,7 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
             // as in hcspmm_aggregate_update; the wave-per-window kernel neither stores S for dW nor applies the mask
             UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
                                 : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
-                                                                                 : update_place(plan, d_out, d_in, d_dW != nullptr);
+                                                                                 : update_place(plan, d_out, d_in, HCSPMM_F32, d_dW != nullptr);
             if (place == kUpdateInWindows && (d_dW || mask_dx_by_x)) place = kUpdateApart;
             if (place != kUpdateApart && update_fusable(a)) {
                 // the next layer's activation mask (its output is this layer's input X) goes into the update's epilogue
