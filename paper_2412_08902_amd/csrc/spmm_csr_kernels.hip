@@ -641,6 +641,14 @@ static int shape_cols(const CsrShape& sh) { return sh.lanes * sh.vec * sh.nv; }
 // two halves while X fits the L2s (16,934 of 14, 160 columns: 25 -> 15 us; 100,000 of 20: 91 -> 92 us).  Whole 16-bit rows of
 // 512 bytes are slow where most rows take a wave each, also where nothing is gained in L2 (communities of 512, 232,960 rows
 // of 165, bf16: 1268 -> 922 us in halves).
+// fp32 rows of more than 512 and up to 1024 bytes off the 128-byte lines: a cut costs every row another line, and where the X
+// rows come from behind L2 the whole row in four vectors per lane wins although fewer loads are in flight -- earlier where two
+// halves of whole lines are uneven or rows are not even on half lines (two slices / whole, us, 200 columns: 100,000 rows of 60:
+// 652 / 552, 478,000 of 93: 6454 / 4795, 1 M of 20: 2810 / 2402; 130 columns: 100,000 of 20: 182 / 148; but 50,000 of 60: 260 /
+// 266) than where they are (240 columns: 70,000 of 60: 398 / 425, 300,000 of 60: 2381 / 2100, 1 M of 6: 1117 / 1136).
+// Communities share their rows in L2 and take whole rows on the largest X only (300,000 of 29, 200 columns: 544 / 478 us;
+// 131,072 of 51: 248 / 257), and up to 768 bytes slices of 256 bytes, which need one vector per lane (131,072 of 51, 144
+// columns: 220 -> 182 us, 160 columns: 215 -> 175 us).
 static int pick_slices(const SpmmArgs& a, const CsrHints& h, int32_t& slice_w)
 {
     const int64_t es = a.x_dtype == HCSPMM_F32 ? 4 : 2, row = a.d * es;
@@ -656,9 +664,17 @@ static int pick_slices(const SpmmArgs& a, const CsrHints& h, int32_t& slice_w)
     } else if (es == 2 && row >= 512 && degree > kMidRow) {
         most = 256;
     }
+    if (es == 4 && row > 512 && row <= 1024) {
+        const double x_mb = (double)a.n_cols * (double)row / (1 << 20);
+        const bool uneven = a.ldx * es % 64 != 0 || 10 * ((a.d + 63) / 64 * 32) > 6 * a.d;
+        const bool whole = h.scattered ? x_mb >= 48.0 && (uneven || (x_mb >= 96.0 && degree >= 15.0)) : x_mb >= 200.0 && row > 768;
+        if (!on_lines && whole) most = 1024;
+        else if (!h.scattered && row <= 768) most = 256;
+    }
     int64_t n = (row + most - 1) / most;
-    // a count that XCDs can own, where the slices come out about equally wide; other counts are taken in turn
-    for (int64_t m = n; m > 1 && n < 8 && (row + m - 1) / m <= 512; --m) {
+    // a count that XCDs can own, where the slices come out about equally wide; other counts are taken in turn (as are the
+    // narrow slices of rows that share what they read: nothing is gained by owners)
+    for (int64_t m = n; m > 1 && n < 8 && (row + m - 1) / m <= 512 && !(most == 256 && !h.scattered); --m) {
         const int64_t w = ((a.d + m - 1) / m + align - 1) / align * align;
         if ((m & (m - 1)) == 0 && 5 * m * w <= 6 * a.d) { n = m; break; }
     }
