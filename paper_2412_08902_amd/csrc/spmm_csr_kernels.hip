@@ -752,9 +752,12 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     }
     int32_t slice_w = a.d;
     const int n_slices = pick_slices(a, hints, slice_w);
-    // While a wave per row and slice still fits the chip at once (256 CUs x 32 waves), every row is a mid row: its non-zeros
-    // are spread over four groups instead of queueing in one (2,708 nodes, 32 columns: 5.6 -> 3.6 us of kernel time).
-    if (n_items > 0 && (int64_t)a.n_rows * n_slices <= 8192) {
+    // On the smallest matrices every row is a mid row: its non-zeros are spread over four groups instead of queueing in one
+    // (2,708 nodes, 32 columns: 5.6 -> 3.6 us of kernel time).  From half of the chip's waves on (256 CUs x 32) starting them
+    // costs more than the shorter chains save (a group / a wave per row, us, fp32: 2,000 rows of 11, 96 columns: 6.7 / 5.1;
+    // 3,000 of 21, 160 columns in two slices: 7.8 / 10.3; communities of 20, 7,936 rows, 128 columns: 7.4 / 11.1; bf16, 128
+    // columns: 4,000 of 11: 6.6 / 5.9; 6,000 of 13: 7.1 / 6.7; 8,000 of 31: 8.1 / 8.9).
+    if (n_items > 0 && (int64_t)a.n_rows * n_slices <= (a.x_dtype == HCSPMM_F32 ? 4096 : 6144)) {
         wk.n_mid = a.n_rows;
         wk.mid_rows = nullptr;
         wk.mid_row = hints.long_row;
