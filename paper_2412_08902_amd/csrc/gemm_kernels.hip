@@ -35,14 +35,15 @@ constexpr int kGemmWaves = 4, kGemmRows = 16 * kGemmWaves, kGemmBK = 32;
 struct GemmOut { float* T; int64_t ldt; const float* mask; int64_t ldm; int32_t t_dtype, relu, vec; };
 
 // Stores a wave's 16 rows from m0 on and 16*NT columns from n0 on.
-template <int NT>
+// MASK is a form of its own: the branch alone costs the short products (299,968 x 64 x 16: 19.0 -> 21.2 us).
+template <bool MASK, int NT>
 __device__ __forceinline__ void store_tile(v4f_gemm (&acc)[NT], int64_t m0, int n0, int64_t M, int32_t N, const GemmOut& o, int c, int q)
 {
     constexpr int G4 = NT / 4, R = NT % 4;
     float* __restrict__ T = o.T;
     const int64_t ldt = o.ldt;
     const int t_dtype = o.t_dtype, relu = o.relu, tvec = o.vec;
-    if (o.mask) {
+    if constexpr (MASK) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int64_t row = m0 + 4 * q + r;
@@ -104,7 +105,7 @@ __device__ __forceinline__ void store_tile(v4f_gemm (&acc)[NT], int64_t m0, int 
 // WV: floats per global load of W (4: W's rows are 16-byte aligned and N is a multiple of 4).
 // Rows past M re-read row M-1 and columns past N read column N-WV: what they produce is never stored.  k >= K is zero in both
 // operands.  WIDE: byte offsets inside a slab of W need 64 bits (launch_gemm_f32_out says when).
-template <int NT, int WV, bool WIDE>
+template <int NT, int WV, bool WIDE, bool MASK>
 __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k_gemm_f32(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
                                                      const float* __restrict__ Wm, int64_t ldw, GemmOut out,
                                                      const uint8_t* __restrict__ done_route,
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
         if (whole + 16 < K) multiply(Two{}, b, a);
         else multiply(One{}, b, a);
     }
-    if (!skip) store_tile<NT>(acc, m0, n0, M, N, out, c, q);
+    if (!skip) store_tile<MASK>(acc, m0, n0, M, N, out, c, q);
 }
 
 // The product with W kept in registers (K <= 128 and a multiple of four): a wave holds the 16*NT columns of W that are its
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
 // times some row streams; those that hold different columns of the same rows share X through L1.  W comes through LDS once
 // per workgroup, every workgroup starting at another row of it: waves that each read their columns from memory cost 10 us more
 // at 17,000 x 128 x 128 (the CUs of an XCD asking one L2 channel for the same lines at the same time).
-template <int K16, int NT>
+template <int K16, int NT, bool MASK>
 __global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
                                                          const float* __restrict__ Wm, int64_t ldw, GemmOut out, int wvec, int32_t groups)
 {
@@ -355,7 +356,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, i
             request(min(tile + streams, last), u);
             __builtin_amdgcn_sched_barrier(0);
         }
-        store_tile<NT>(acc, tile * 16, n0, M, N, out, c, q);
+        store_tile<MASK>(acc, tile * 16, n0, M, N, out, c, q);
     }
 }
 
@@ -386,13 +387,15 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
         const dim3 grid((unsigned)std::min<int64_t>(want, k16 * nt > 16 ? 256 : k16 * nt > 4 ? 512 : 1024), (unsigned)ny);
         const size_t lds = (size_t)16 * k16 * groups * 16 * nt * sizeof(float);                     // 48 KB at most
         const int wvec = n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0;
-#define HC_REG(KK, NT) hipLaunchKernelGGL((k_gemm_f32_reg<KK, NT>), grid, dim3(512), lds, s, m, k, n, X, ldx, W, ldw, out, wvec, groups)
+#define HC_REG(KK, NT) do { if (mask) HC_REG1(KK, NT, true); else HC_REG1(KK, NT, false); } while (0)
+#define HC_REG1(KK, NT, MASK) hipLaunchKernelGGL((k_gemm_f32_reg<KK, NT, MASK>), grid, dim3(512), lds, s, m, k, n, X, ldx, W, ldw, out, wvec, groups)
 #define HC_REG_NT(KK) case KK: if (nt == 4) HC_REG(KK, 4); else if (nt == 3) HC_REG(KK, 3); else if (nt == 2) HC_REG(KK, 2); else HC_REG(KK, 1); break
         switch (k16) {
             HC_REG_NT(1); HC_REG_NT(2); HC_REG_NT(3); HC_REG_NT(4); HC_REG_NT(5); HC_REG_NT(6); HC_REG_NT(7); HC_REG_NT(8);
         }
 #undef HC_REG_NT
 #undef HC_REG
+#undef HC_REG1
         return hipGetLastError();
     }
     // columns: as few groups of up to 128 as hold them, equally wide; two groups to a workgroup where they come in pairs
@@ -403,7 +406,8 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
     const dim3 grid((unsigned)((m + kGemmRows - 1) / kGemmRows), (unsigned)(groups / pair));
     const size_t lds = (size_t)pair * 2 * kGemmBK * 16 * nt * sizeof(float);
     const int wv = (n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0) ? 4 : 1;
-#define HC_LAUNCH_GEMM(NT, WV, WIDE) hipLaunchKernelGGL((k_gemm_f32<NT, WV, WIDE>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, out, done_route, done_cols, kMfmaSmallMaxCols)
+#define HC_LAUNCH_GEMM(NT, WV, WIDE) do { if (mask) HC_GEMM1(NT, WV, WIDE, true); else HC_GEMM1(NT, WV, WIDE, false); } while (0)
+#define HC_GEMM1(NT, WV, WIDE, MASK) hipLaunchKernelGGL((k_gemm_f32<NT, WV, WIDE, MASK>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, out, done_route, done_cols, kMfmaSmallMaxCols)
 #define HC_GEMM_NT(NT) case NT: if (wv == 4) HC_LAUNCH_GEMM(NT, 4, false); else HC_LAUNCH_GEMM(NT, 1, false); break
     if (wide) HC_LAUNCH_GEMM(8, 1, true);
     else switch (nt) {
@@ -411,6 +415,7 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
     }
 #undef HC_GEMM_NT
 #undef HC_LAUNCH_GEMM
+#undef HC_GEMM1
     return hipGetLastError();
 }
 
