@@ -706,23 +706,29 @@ bool csr_panels_usable(const SpmmArgs& a)
 
 // Where 8 lanes per output row (Gather's third form) are ahead of 16: on matrices of many short rows, which are bound by how
 // fast waves start and drain, and where rows of X off the 16-byte pieces make 16 narrow lanes touch more lines than 8 wider
-// ones.  16 against 8 lanes, fp32, us (16 columns bf16 as 8 columns fp32):
-//                               8 columns      16 columns     32 columns     7 columns
-//   2.4 M rows of 9             349 / 280      389 / 342      463 / 407      406 / 315
-//   169,343 of 15               26.2 / 22.1    28.1 / 28.2    33.1 / 32.5    35.4 / 27.2
-//   131,072 in communities, 20  17.5 / 13.7    18.6 / 20.7    22.7 / 22.3    28.0 / 19.4
-//   1 M of 21                   222 / 213      268 / 263      315 / 319      256 / 233
-//   50,021 of 29                10.0 / 9.7     12.1 / 14.2    14.6 / 15.8    16.3 / 12.9
-//   16,934 of 15                4.8 / 5.0      4.8 / 6.1      5.4 / 6.3      6.5 / 5.5
-//   300,000 of 61               129 / 137      170 / 178      --             161 / 150
-//   2.4 M of 51                 1607 / 1679    1878 / 1907    2100 / --      1797 / 1835
+// ones.  On fewer rows the chain of a row that is just short of the wave-per-row tier, twice as long then, outlasts the rest.
+// 16 against 8 lanes, us, fp32 (two columns of 16 bits like one of fp32; * off the 16-byte pieces):
+//                               8 columns      16 columns     32 columns     7 columns *    9 columns *
+//   2.4 M rows of 9             349 / 280      389 / 342      463 / 407      406 / 315      --
+//   400,000 of 11               --             60 / 57        92 / 93        --             65 / 54
+//   200,000 of 15               --             34 / 33        54 / 56        --             38 / 32
+//   169,343 of 15               26.2 / 22.1    28.1 / 28.2    33.1 / 32.5    35.4 / 27.2    --
+//   131,072 in communities, 20  17.5 / 13.7    18.6 / 20.7    22.7 / 22.3    28.0 / 19.4    28.1 / 21.0
+//   102,271 of 9                --             14.1 / 15.8    19.2 / 21.2    --             17.3 / 15.6
+//   1 M of 21                   222 / 213      268 / 263      315 / 319      256 / 233      --
+//   50,021 of 29                10.0 / 9.7     12.1 / 14.2    14.6 / 15.8    16.3 / 12.9    --
+//   16,934 of 15                4.8 / 5.0      4.8 / 6.1      5.4 / 6.3      6.5 / 5.5      --
+//   300,000 of 61               129 / 137      170 / 178      --             161 / 150      --
+//   2.4 M of 51                 1607 / 1679    1878 / 1907    2100 / --      1797 / 1835    --
 static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
 {
     const int64_t es = a.x_dtype == HCSPMM_F32 ? 4 : 2, row = a.d * es;
     if (row > 128 || h.rows <= 0) return false;
     const double degree = (double)h.nnz / (double)h.rows;
     const bool off = a.ldx * es % 16 != 0 || (uintptr_t)a.X % 16 != 0;
-    return (off && row <= 64 && degree < 40.0) || (h.rows >= 100000 && degree <= (row <= 32 ? 24.0 : 16.0));
+    if (off && row <= 64 && degree < 40.0 && ((es == 4 && row <= 40) || h.rows <= kMidRowFewRows || h.rows >= 130000)) return true;
+    if (row <= 32) return h.rows >= 100000 && degree <= 24.0;
+    return degree <= 16.0 && h.rows >= (row <= 64 ? 200000 : 1000000);
 }
 
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
