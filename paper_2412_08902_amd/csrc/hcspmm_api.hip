@@ -1248,8 +1248,10 @@ hcspmm_status hcspmm_plan_info(const hcspmm_plan* p, hcspmm_plan_info_t* info)
     info->device_bytes = p->device_bytes + (p->partial_elems + p->tile_partial_elems + p->acc_rows_elems) * (int64_t)sizeof(float);
     info->n_short_rows = p->n_short; info->n_long_rows = p->n_long_rows; info->n_segments = p->n_segs;
     info->n_mid_rows = p->n_mid;
-    info->nnz_long = p->nnz_long; info->n_mfma_small = p->n_mfma_small;
-    info->n_mfma_big = p->n_mfma_mid + p->n_mfma_big;
+    info->nnz_long = p->nnz_long;
+    // (launch tables: none of the matrix path's kernels runs where the scalar path has taken its windows over)
+    info->n_mfma_small = p->scalar_exec ? 0 : p->n_mfma_small;
+    info->n_mfma_big = p->scalar_exec ? 0 : p->n_mfma_mid + p->n_mfma_big;
     info->n_runs = p->runs_ok ? p->n_runs : 0;
     info->n_run_slices = p->runs_ok ? p->n_run_slices : 0;
     info->run_union_cols = p->runs_ok ? p->run_union_cols : 0;

@@ -174,3 +174,18 @@ def test_scalar_only_plans_that_sample_their_columns(community):
             with pytest.raises(hc.HcspmmError) as e:
                 hc.hcspmm_prepare(n, n, *device_graph(CSRGraph(n, n, g.rowptr, c, g.vals)), route_mode=1)
             assert e.value.status == hc.HCSPMM_EBADCSR
+
+
+def test_plan_info_tells_windows_that_the_scalar_path_has_taken_over():
+    """The canonical plan keeps its routes; the launch tables say that no matrix-path kernel runs."""
+    import paper_2412_08902_amd.binding as hc
+    from test_gpu_runs import scattered_windows
+    g = scattered_windows()
+    dev = device_graph(g)
+    for kernels, runs in ((hc.HCSPMM_MATRIX_AUTO, False), (hc.HCSPMM_MATRIX_PER_WINDOW, True)):
+        plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *dev, d_hint=128, mfma_dtype=1, matrix_kernels=kernels)
+        info = hc.hcspmm_plan_info(plan)
+        assert info["n_mfma_windows"] > 900 and (info["n_mfma_small"] + info["n_mfma_big"] == info["n_mfma_windows"]) == runs
+        assert runs or info["n_mfma_small"] + info["n_mfma_big"] == 0
+        assert hc.hcspmm_plan_export(plan)["route"].sum() == info["n_mfma_windows"]
+        plan.destroy()
