@@ -49,16 +49,27 @@ def test_narrow_rows(n, d):
         assert_close(Y[rows], ref, bound, 1e-5, "%s d=%d" % (kind, 2 * d))
 
 
-# eight lanes to an output row: a matrix of many short rows, or rows of X off the 16-byte pieces; one, two and four columns per
-# lane (16-bit: two, four, eight), the last vector moved left or whole
-@pytest.mark.parametrize("d", [1, 4, 5, 7, 8, 9, 10, 13, 16, 17, 30, 31, 32])
-@pytest.mark.parametrize("n", [48, 100_003])
-def test_narrow_rows(n, d):
+def short_rows(lengths, n_cols, seed):
+    """CSR with the given row lengths (at most n_cols), distinct columns in no order, for many rows."""
+    rng = np.random.default_rng(seed)
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    at = np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], lengths)
+    step = 7 if n_cols % 7 else 11
+    colind = ((np.repeat(rng.integers(0, n_cols, len(lengths)), lengths) + step * at) % n_cols).astype(np.int32)
+    return CSRGraph(len(lengths), n_cols, rowptr, colind, rng.standard_normal(colind.shape[0]).astype(np.float32))
+
+
+# eight lanes to an output row: rows of X off the 16-byte pieces, or a matrix of rows that are many for their width (100,000 of
+# up to 32 bytes, 200,000 of up to 64, a million of up to 128); one, two and four columns per lane (16-bit: two, four, eight),
+# the last vector moved left or whole
+@pytest.mark.parametrize("n,d", [(n, d) for n in (48, 100_003) for d in (1, 4, 5, 7, 8, 9, 10, 13, 16, 17, 30, 31, 32)] +
+                         [(200_003, 9), (200_003, 16), (1_000_003, 17), (1_000_003, 32)])
+def test_eight_lanes_to_a_row(n, d):
     lengths = np.resize([3, 0, 7, 8, 9, 1, 16, 17, 12, 2, 20], n)
     lengths[[5, n - 1]] = [129, 64]
     if n > 1000:
         lengths[[77, 50_000, 99_999]] = [300, 1025, 2049]
-    g = rows_of(lengths, 5000, d)
+    g = short_rows(lengths, 5000, d)
     rows = np.unique(np.concatenate([np.arange(0, n, 1 + n // 3000), np.flatnonzero(lengths > 20), np.arange(n - 40, n)]))
     pad = 0 if n > 1000 else 1 + (d + 1) % 4 + (d % 4 == 3)           # (the small matrix: an odd pitch)
     X = np.random.default_rng(d).standard_normal((g.n_cols, d)).astype(np.float32)
@@ -113,6 +124,19 @@ def test_long_rows_of_sparse_matrices(n, long_rows):
     rows = np.unique(np.concatenate([hubs, np.arange(0, n, 97)]))
     ref, bound = oracle_pair(g, X, rows=rows)
     assert_close(Y[rows], ref, bound, 1e-5, "n=%d" % n)
+
+
+@pytest.mark.parametrize("kind", ["bf16", "f16"])
+@pytest.mark.parametrize("d,pad", [(192, 0), (160, 32), (132, 60)])
+def test_three_slices_of_16bit_rows(kind, d, pad):
+    """Rows of 257 to 511 bytes that start on 128-byte lines: three slices of a line, taken in turn by lane groups (more rows
+    than the small matrices' wave per row takes) and by the waves and workgroups of longer rows."""
+    g = short_rows(np.concatenate([np.resize(LENGTHS, 48), np.resize([20, 0, 33, 8, 17, 1], 4001)]), 20000, d)
+    X = np.random.default_rng(d).standard_normal((g.n_cols, d)).astype(np.float32)
+    bits = to_bf16_bits(X) if kind == "bf16" else to_f16_bits(X)
+    Y, _ = gpu_spmm(g, bits, 1, pad_x=pad, x_bits=kind)
+    ref, bound = oracle_pair(g, bits, x_dtype=oracle.DT_BF16 if kind == "bf16" else oracle.DT_F16)
+    assert_close(Y, ref, bound, 1e-5, "%s d=%d" % (kind, d))
 
 
 @pytest.mark.parametrize("d", [256, 260, 320, 512])
