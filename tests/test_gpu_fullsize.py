@@ -129,13 +129,15 @@ def test_c4_matrix_path_at_full_size(c4, mode):
         assert info["n_mfma_small"] > 0 and info["n_mfma_big"] > 0
 
 
-@pytest.mark.parametrize("mode", ["hybrid", "all_csr", "all_mfma", "per_window"])
+@pytest.mark.parametrize("mode", ["hybrid", "all_csr", "all_mfma", "per_window", "both_paths"])
 def test_c5_spmm_at_full_size(mode):
     """C5's aggregation stage (d = 128) on every routing, 4,096 sampled rows against the oracle."""
     g, _ = cached_config("C5")
     T = dense_normal(g.n_cols, CONFIGS["C5"]["d"], seed=1)
     rows = sample_rows(g, 4096, seed=12)
     args = {"hybrid": dict(route_mode=0), "all_csr": dict(route_mode=1), "all_mfma": dict(route_mode=2),
+            # the selector's split on both paths (left to the library, this graph takes column panels on the scalar path)
+            "both_paths": dict(route_mode=0, matrix_kernels=1),
             # windows with fewer than 6,000 distinct columns take the matrix path
             "per_window": dict(route_mode=3, sel_coef=[1, 0, -6000])}[mode]
     info = spmm_sampled(g, T, rows, "C5 " + mode, **args)
@@ -156,17 +158,20 @@ def test_mixed_graph_routes_both_ways():
     assert info["n_windows"] > n_comm
 
 
-def test_c5_hybrid_call_replays_from_a_hip_graph():
-    """A call that forks onto the plan's side streams (large matrix, work on both paths) captured in a HIP graph:
-    every replay, with eager work between the replays, reproduces the eager result bit for bit."""
+@pytest.mark.parametrize("matrix_kernels", [0, 1], ids=["panels", "side_streams"])
+def test_c5_hybrid_call_replays_from_a_hip_graph(matrix_kernels):
+    """A call captured in a HIP graph: every replay, with eager work between the replays, reproduces the eager result bit for
+    bit.  Left to the library the graph takes column panels on the caller's stream; with the matrix path's kernels chosen
+    it forks onto the plan's side streams (large matrix, work on both paths)."""
     import torch
     import paper_2412_08902_amd.binding as hc
     g, _ = cached_config("C5")
     T = dense_normal(g.n_cols, CONFIGS["C5"]["d"], seed=1)
     rp, ci, va = device_graph(g)
-    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, rp, ci, va, d_hint=T.shape[1])
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, rp, ci, va, d_hint=T.shape[1], matrix_kernels=matrix_kernels)
     info = hc.hcspmm_plan_info(plan)
     assert 0 < info["n_mfma_windows"] < info["n_windows"] and g.nnz >= 16000000       # the side-stream route
+    assert (info["n_mfma_small"] + info["n_mfma_big"] > 0) == (matrix_kernels == 1)
     Xd = torch.from_numpy(T).cuda()
     Y_eager = torch.empty((g.n_rows, T.shape[1]), device="cuda")
     hc.hcspmm_spmm(plan, Xd, Y_eager)                       # also sizes the plan's scratch before the capture
@@ -191,15 +196,17 @@ def test_c5_hybrid_call_replays_from_a_hip_graph():
     plan.destroy()
 
 
-def test_c5_layer_and_plan():
+@pytest.mark.parametrize("matrix_kernels", [0, 1], ids=["panels", "both_paths"])
+def test_c5_layer_and_plan(matrix_kernels):
     import torch
     import paper_2412_08902_amd.binding as hc
     g, X, Wm = cached_config("C5", with_w=True)
     rp, ci, va = device_graph(g)
     d_out = Wm.shape[1]
-    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, rp, ci, va, d_hint=d_out)
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, rp, ci, va, d_hint=d_out, matrix_kernels=matrix_kernels)
     info = hc.hcspmm_plan_info(plan)
-    assert info["n_mfma_windows"] > 0 and info["n_csr_windows"] > 0          # both paths are exercised
+    assert info["n_mfma_windows"] > 0 and info["n_csr_windows"] > 0
+    assert (info["n_mfma_small"] + info["n_mfma_big"] > 0) == (matrix_kernels == 1)     # then both paths are exercised
     ws = torch.empty(hc.hcspmm_gcn_workspace_bytes(plan, X.shape[1], d_out), dtype=torch.uint8, device="cuda")
     Y = torch.full((g.n_rows, d_out), float("nan"), device="cuda")
     hc.hcspmm_gcn_layer(plan, torch.from_numpy(X).cuda(), torch.from_numpy(Wm).cuda(), Y, ws)
