@@ -9,7 +9,8 @@
  *   - a three-parameter linear model on (number of non-zero columns, sparsity)
  *     decides per window whether the matrix cores or the scalar cores compute
  *     it; the decision is taken once, in preprocessing, and stored as one flag
- *     per window (0 = scalar path, 1 = matrix path)      (Section IV-C);
+ *     per window (0 = scalar path, 1 = matrix path)      (Section IV-C; a plan
+ *     may then run ALL its windows on the scalar path, see hcspmm_route_mode);
  *   - Z = A X is then computed window by window on the chosen path, windows
  *     own disjoint output rows so nothing is merged      (Alg. 1-4, Eq. 1);
  *   - the GNN layer couples the aggregation with the dense update X W
@@ -69,11 +70,22 @@ typedef enum { HCSPMM_F32 = 0, HCSPMM_BF16 = 1, HCSPMM_F16 = 2 } hcspmm_dtype;
  * first) -- a launch that cannot repay its fixed cost is not made.  The two ALL_* modes force one
  * path for every non-empty window (used to measure the selector against the pure paths).
  * Empty windows always take the scalar path.
+ * Scalar takeover: with HYBRID, the shipped selector and matrix_kernels = AUTO, the windows that the
+ * selector sends to the matrix path run on the scalar path as well where the whole matrix is faster
+ * there: X rows of whole 128-byte lines (at d_hint), at most 40 M non-zeros, and windows that share few
+ * columns on average; or a dense scattered graph, which the scalar path walks in column panels (rows
+ * with ascending columns, 150 non-zeros to a row on average, 400 for 16-bit rows of less than 256 bytes,
+ * X rows of at least 128 bytes).  route, n_mfma_windows and nnz_mfma still tell the selector's
+ * decision; n_mfma_small and n_mfma_big of hcspmm_plan_info are both 0 then, and the matrix path's
+ * restrictions on 16-bit operands and its treatment of non-finite X do not apply.
+ * PER_WINDOW, ALL_MFMA, custom coefficients and a choice of matrix_kernels are always followed.
  * ALL_CSR is also the plan for a matrix whose structure keeps changing: the scalar path reads
  * plain CSR (the paper's scalar path has no preprocessing either), so hcspmm_prepare skips the
- * condensing step and only validates the arrays and builds the row-length launch tables; the
- * window features (ncols, wptr, total_ncols) of such a plan are computed on the first
- * hcspmm_plan_info / hcspmm_plan_export call instead. */
+ * condensing step and the columns of each window are not counted.  It validates the arrays, builds the
+ * row-length launch tables, counts the distinct columns of a few samples (64 stretches of
+ * non-zeros, to see whether neighbouring rows share columns) and, where the rows are dense enough for
+ * column panels, finds the panels' boundaries in every row.  The window features (ncols, wptr,
+ * total_ncols) of such a plan are computed on the first hcspmm_plan_info / hcspmm_plan_export call. */
 typedef enum {
     HCSPMM_ROUTE_HYBRID = 0, HCSPMM_ROUTE_ALL_CSR = 1, HCSPMM_ROUTE_ALL_MFMA = 2, HCSPMM_ROUTE_PER_WINDOW = 3
 } hcspmm_route_mode;
@@ -140,8 +152,10 @@ hcspmm_status hcspmm_default_selector(int32_t mfma_dtype, int32_t d_hint, int64_
  * structure only (windows, condensed columns, selector features are functions of the indices),
  * and every kernel reads the values through d_vals at call time: the CALLER MAY OVERWRITE
  * d_vals IN PLACE between calls (edge weights that change per layer or per epoch) without
- * preparing again.  A structural change needs a new plan (a prepare costs about two SpMM calls on
- * the large configurations).  Everything the plan allocates it owns.
+ * preparing again.  A structural change needs a new plan (a prepare costs about half an SpMM call on
+ * the large configurations).  Everything the plan allocates it owns.  A plan made for 16-bit features
+ * (mfma_dtype) whose graph takes column panels also holds the panels' fp32 sums of a 16-bit Y,
+ * 4 * n_rows * d_hint bytes, from the start (hcspmm_spmm_noalloc must not allocate them).
  * Validates the CSR on the device (HCSPMM_EBADCSR).  Synchronises with `stream`.
  */
 hcspmm_status hcspmm_prepare(int32_t n_rows, int32_t n_cols, int64_t nnz,
@@ -185,7 +199,7 @@ typedef struct {
     int64_t nnz;
     int32_t n_windows;        /* W = ceil(n_rows / H) */
     int64_t total_ncols;      /* sum over windows of ncols = length of wcols */
-    int32_t n_mfma_windows;   /* windows with route 1 */
+    int32_t n_mfma_windows;   /* windows with route 1 (the selector's decision; see n_mfma_small for what runs) */
     int32_t n_csr_windows;    /* windows with route 0 */
     int64_t nnz_mfma;         /* non-zeros inside route-1 windows */
     int32_t route_mode;
@@ -193,14 +207,15 @@ typedef struct {
     int32_t d_hint;
     int64_t sel_coef[3];      /* coefficients the routes were computed with */
     int64_t device_bytes;     /* device memory owned by the plan */
-    /* how the scalar path's rows are scheduled (launch tables, not part of the canonical plan) */
-    int32_t n_short_rows;     /* rows walked by lane groups, several consecutive rows per group */
+    /* how the scalar path's rows are scheduled when the matrix is walked in one pass (launch tables, not part of the
+     * canonical plan; column panels have tables of their own, which are not reported) */
+    int32_t n_short_rows;     /* rows walked by lane groups, one row per group at a time */
     int32_t n_mid_rows;       /* rows handled one wave per row */
     int32_t n_long_rows;      /* rows cut into segments, one workgroup per segment */
     int32_t n_segments;
     int64_t nnz_long;         /* non-zeros inside mid and long rows */
-    int32_t n_mfma_small;     /* route-1 windows handled one wave per window */
-    int32_t n_mfma_big;       /* route-1 windows handled one workgroup per window */
+    int32_t n_mfma_small;     /* windows the matrix path runs one wave per window; 0 when all windows run on the scalar path */
+    int32_t n_mfma_big;       /* windows the matrix path runs one workgroup per window; likewise */
     /* runs of neighbouring route-1 windows with merged column lists (0 when the plan has no run tables) */
     int32_t n_runs;
     int32_t n_run_slices;     /* workgroups of the run kernel */
@@ -216,7 +231,8 @@ hcspmm_status hcspmm_plan_info(const hcspmm_plan* plan, hcspmm_plan_info_t* info
  * skip that array; sizes from hcspmm_plan_info):
  *   ncols  int32[W]    distinct columns per window                    (Section IV-A / V-B)
  *   nnzw   int32[W]    non-zeros per window
- *   route  uint8[W]    0 = scalar path, 1 = matrix path                (Section IV-C)
+ *   route  uint8[W]    0 = scalar path, 1 = matrix path                (Section IV-C; the selector's decision,
+ *                      also in a plan that runs all its windows on the scalar path)
  *   wptr   int64[W+1]  offsets into wcols
  *   wcols  int32[total_ncols]  per window: its distinct column ids, ascending
  *   ecol   int32[nnz]  per non-zero (CSR order): position of its column in its window's wcols
@@ -243,7 +259,8 @@ hcspmm_status hcspmm_plan_export_runs(const hcspmm_plan* plan, int32_t* run_nu, 
 
 /*
  * Y = A X on the hybrid paths (Eq. 1; Alg. 1/3 for route-0 windows, Alg. 2/4
- * for route-1 windows).  Y is overwritten (rows without entries become 0).
+ * for route-1 windows, unless the plan runs those on the scalar path too, see
+ * hcspmm_route_mode).  Y is overwritten (rows without entries become 0).
  *
  *   d_X      device, n_cols x d, row-major, leading dimension ldx >= d, dtype x_dtype
  *   d_Y      device, n_rows x d, row-major, leading dimension ldy >= d, dtype y_dtype
@@ -254,11 +271,17 @@ hcspmm_status hcspmm_plan_export_runs(const hcspmm_plan* plan, int32_t* run_nu, 
  *   y_dtype  HCSPMM_F32, or HCSPMM_BF16 / HCSPMM_F16: the fp32 result of either path is rounded ONCE, to
  *            nearest even, when it is stored (the next layer can then gather 16-bit rows without a
  *            conversion pass in between).  ldy counts elements of that type.
+ * 16-bit X on a plan whose matrix path runs needs d, ldx and ldy to be multiples of 4, 8-byte aligned X and
+ * 16-byte aligned Y (HCSPMM_EUNSUPPORTED otherwise); the scalar path takes every width, pitch and alignment of
+ * whole elements.  hcspmm_plan_info tells which it is: n_mfma_small + n_mfma_big > 0 when the matrix path runs.
+ * A graph that takes column panels is walked panel by panel, sums kept between panels in fp32: in Y itself, or for a
+ * 16-bit Y in sums that the plan holds (d up to d_hint on plans made for 16-bit features; without them such a call
+ * walks the matrix in one pass, with the same result up to the order of summation).
  * X and Y must not overlap.  1 <= d <= 2^20.  Asynchronous on `stream`.
  *
  * A plan holds scratch buffers of its own (partial rows of long rows, partial tiles of wide
- * windows; allocated on the first call that needs them, which synchronises `stream` if it has to
- * grow them): calls that use the same plan must be ordered, i.e. issued on one stream or
+ * windows, and for layers with a 16-bit Y the fp32 sums between column panels; allocated on the first
+ * call that needs them, which synchronises `stream` if it has to grow them): calls that use the same plan must be ordered, i.e. issued on one stream or
  * otherwise serialised by the caller.  Different plans are independent.  Once a call with the
  * largest d in use has been made, later calls allocate nothing and can be captured in a HIP graph.
  * The same holds for hcspmm_gcn_layer(_ex), hcspmm_aggregate_update and hcspmm_layer_backward: after
@@ -279,11 +302,13 @@ hcspmm_status hcspmm_spmm(const hcspmm_plan* plan, const void* d_X, int64_t ldx,
  * into segments and the partial tiles of wide matrix-path windows cut into slices): not in buffers the
  * plan allocates on first use, but in one fixed array of HCSPMM_STATIC_SCRATCH_BYTES that is part of the
  * library's device image (every GPU the library runs on holds its own copy until the process ends).
- * The call allocates and frees nothing, on the device or through any library.
+ * The call allocates and frees nothing, on the device or through any library (the sums between column panels of a
+ * 16-bit Y are the plan's, allocated when it was prepared; a call whose sums are not there takes one pass, as
+ * hcspmm_spmm does).
  *
  *   HCSPMM_EUNSUPPORTED  when the plan needs more scratch at this d than the array holds
- *                        (256-byte-padded 4*d*(segments of multi-segment rows) plus 64*d*(slices of
- *                        multi-slice windows) bytes); nothing is launched then, use hcspmm_spmm
+ *                        (256-byte-padded 4*d*(segments of multi-segment rows, of the whole matrix or of
+ *                        the panel that has most) plus 64*d*(slices of multi-slice windows) bytes); nothing is launched then, use hcspmm_spmm
  *   HCSPMM_EINVAL        also when the current device is not the plan's
  *
  * Every call on a GPU shares that GPU's array, across plans and streams: calls of this entry point that
@@ -318,7 +343,7 @@ hcspmm_status hcspmm_spmm_timed(const hcspmm_plan* plan, const void* d_X, int64_
 
 /*
  * GCN layer  Y = act(A (X W))  (Eq. 1 and Eq. 2; Section V-A couples the two
- * phases).  The update X W is formed first by an fp32 MFMA GEMM into the
+ * phases).  The update X W is formed first by an fp32 MFMA product into the
  * workspace and the hybrid SpMM gathers its rows from there at once; the
  * activation (ReLU when apply_relu != 0) is applied in the SpMM epilogue, after
  * the complete row sum, so the call is two kernel families and no separate
@@ -359,14 +384,19 @@ size_t hcspmm_gcn_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t
 /*
  * Aggregate-then-update layer  Y = act((A X) W)  -- the association of GIN's forward pass and of
  * GCN's backward pass, for which Section V-A describes the coupled kernel (aggregate a window,
- * then multiply its result tile by W).  With d_in a multiple of 16 up to 256 (and X aligned for
- * vector loads) the update
- * is fused into the aggregation kernels: short scalar-path rows and wave-per-window matrix-path
- * tiles stay in LDS and are multiplied by W on the fp32 matrix cores before anything is stored;
- * the remaining rows (long rows, very wide windows) pass through the workspace.  Otherwise, and when
- * those remaining rows are a quarter of the matrix or more, Z = A X is written to the workspace
- * and one fp32 MFMA kernel applies W and the activation (also for fp32 X with d_in of 48..128 and
- * d_out <= 64 on matrices of 32,768 rows or more, where that route measured faster).
+ * then multiply its result tile by W).  Three forms, with the same results up to the order of summation:
+ *   fused   short scalar-path rows and wave-per-window matrix-path tiles stay in LDS and are multiplied by W
+ *           on the fp32 matrix cores before anything is stored; the remaining rows (long rows, very wide
+ *           windows) pass through the workspace.  Taken for graphs of a few thousand rows, where launches
+ *           dominate, and for large ones that are mostly on the scalar path (from 300,000 rows on, depending
+ *           on degree and widths), whose gathers hide the product.
+ *   windows the same in the matrix path's wave-per-window kernel only; the scalar path's rows go through the
+ *           workspace.  Taken where at least half of the windows are such windows and d_in * d_out is at most
+ *           16384 (12288 below 4,096 windows).
+ *   apart   Z = A X is written to the workspace and one fp32 MFMA kernel applies W and the activation.  Taken
+ *           otherwise, and always when d_in is no multiple of 16 or above 256, X is not aligned for vector
+ *           loads, or the graph is walked in column panels.
+ * HCSPMM_UPDATE_FUSED takes the first form whenever widths and alignment allow it, HCSPMM_UPDATE_SPLIT the last.
  *
  *   d_X   device, n_cols x d_in, element type x_dtype (ldx >= d_in)
  *   d_W   device, d_in x d_out fp32 (ldw >= d_out)
@@ -374,7 +404,7 @@ size_t hcspmm_gcn_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t
  *         rounding of the fp32 result when it is stored -- a chain of such layers with 16-bit X and Y needs no
  *         conversion pass between layers
  *   d_workspace  device, at least hcspmm_aggregate_update_workspace_bytes(plan, d_in, d_out) bytes,
- *                256-byte aligned; holds Z (n_rows x d_in fp32) on return when the update was not fused
+ *                256-byte aligned; holds Z (n_rows x d_in fp32) on return when the update was taken apart
  * Asynchronous on `stream`.  Errors as hcspmm_spmm.
  */
 hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, int64_t ldx, int32_t d_in,
@@ -394,9 +424,9 @@ size_t hcspmm_aggregate_update_workspace_bytes(const hcspmm_plan* plan, int32_t 
  *     dW = X^T S                            (d_in x d_out)
  * This is the stage of training where the update follows the aggregation (Section V-A): dX is
  * computed like hcspmm_aggregate_update computes its Y, the aggregated tile multiplied by W^T on the
- * matrix cores without a round trip (under the same conditions: d_out a multiple of 16 up to 256,
- * few long rows; with d_dW given, which makes the kernels store the tile as well, only for d_out <= 32,
- * where that measured faster), else by a GEMM.  dW is a reduction over all rows of the graph: S is also written
+ * matrix cores without a round trip (in the same three forms, chosen by the same rules with d_out for the
+ * aggregated width; with d_dW given, which makes the kernels store the tile as well, medium-sized graphs take
+ * it apart more often), or by a product of its own, which applies the mask of dX as it stores.  dW is a reduction over all rows of the graph: S is also written
  * to the workspace, and one streaming fp32 MFMA kernel forms X^T S from contiguous row spans whose
  * partial products are added in span order (the result does not depend on scheduling).
  * Eq. 3 as printed, W' = Z^T X' with the aggregated Z = A X_k, is the same call with the dense
