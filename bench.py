@@ -34,10 +34,10 @@ HBM_PEAK_GBS = 8000.0
 # each with the full command that produced it).  Counters cannot be read from inside this process, so the bench line
 # carries "traffic": null and names the summary instead.
 TRAFFIC_PROFILE = {
-    ("C4", "k_csr"): "profiles/k_csr_C4_large_powerlaw.md",
-    ("C5", "k_mfma_wg"): "profiles/k_mfma_wg_C5_dense_powerlaw.md",
-    ("C2", "k_csr"): "profiles/k_csr_C2_C3.md",
-    ("C3", "k_csr"): "profiles/k_csr_C2_C3.md",
+    ("C2", "k_csr"): "profiles/main_cases.md",
+    ("C4", "k_csr"): "profiles/main_cases.md",
+    ("C5", "k_csr"): "profiles/main_cases.md",
+    ("C6", "k_csr"): "profiles/main_cases.md",
 }
 
 WORKLOAD_TEXT = {
