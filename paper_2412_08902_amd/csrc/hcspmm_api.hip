@@ -934,13 +934,15 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         if (a.y_dtype != HCSPMM_F32) {
             const int64_t want = (int64_t)p->n_rows * a.d;
             if (p->acc_rows_elems < want) {
-                if (p->acc_rows) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->acc_rows); p->acc_rows = nullptr; p->acc_rows_elems = 0; }
-                if (hipMalloc((void**)&p->acc_rows, (size_t)want * sizeof(float)) != hipSuccess) {
+                // (the sums at hand are given up only for larger ones: calls that must not allocate count on them)
+                float* larger = nullptr;
+                if (hipMalloc((void**)&larger, (size_t)want * sizeof(float)) != hipSuccess) {
                     (void)hipGetLastError();
-                    p->acc_rows = nullptr;
                     set_error("allocation of %lld floats for row sums between column panels failed", (long long)want);
                     return HCSPMM_EALLOC;
                 }
+                if (p->acc_rows) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->acc_rows); }
+                p->acc_rows = larger;
                 p->acc_rows_elems = want;
             }
             sums = p->acc_rows;
