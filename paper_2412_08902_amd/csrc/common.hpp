@@ -25,7 +25,6 @@ constexpr int kEcolLdsCap = 4096;      // distinct-column lists up to this lengt
 // ---- matrix path -------------------------------------------------------------------------------
 constexpr int kMfmaSmallMaxCols = 256; // windows with more condensed columns go to a workgroup-per-window kernel
 constexpr int kMfmaMidMaxCols = 1024;  // ... with the small LDS chunk up to here, the large chunk beyond
-constexpr int kKcSmall = 128;          // condensed columns staged per wave and chunk (wave-per-window kernel)
 constexpr int kKcMid = 256;            // condensed columns staged per workgroup and chunk, medium windows
 constexpr int kKcBig = 1024;           // condensed columns staged per workgroup and chunk, wide windows
 constexpr int kSliceCols = 4096;       // condensed columns per workgroup; wider windows are cut into slices

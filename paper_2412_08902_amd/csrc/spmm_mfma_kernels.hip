@@ -266,25 +266,47 @@ __device__ inline void store_tile(const v4f (&acc)[NG][VW], int lane, int32_t r0
 }
 
 // ---- wave per window --------------------------------------------------------------------------
-// Four independent waves per workgroup; each owns a private kKcSmall x 16 LDS tile and one window.
+// Four independent waves per workgroup; each owns a private LDS tile (small_cols x 16) and one window.
 // No workgroup barrier: LDS traffic of a wave is issued and completed in program order.
 // The dependent chain of a window is kept short: one descriptor read (scalar), then the column
 // list and the first kEdgeRegs*64 non-zeros in one go, then the first X rows, and only then the
 // LDS work that builds the A tile.
-constexpr int kEdgeRegs = 6;
+//
+// Bound by that chain and by how many waves wait on it side by side.  A window of a community of 64 at 75 % has some 830
+// non-zeros on some 128 columns, half of them scattered.  Past the first kEdgeRegs*64 the non-zeros used to come 64 at a
+// time, one memory latency each, and half of the windows had a few columns more than the tile and walked all their
+// non-zeros again for those.  Now kEdgeMore*64 more are requested with the first ones (into registers that the second stage
+// of X rows takes over later), any others kEdgeMore*64 at a time; the forms with 8 accumulator tiles are held to 128 registers, for
+// four waves per SIMD instead of three (16 tiles of 16-bit rows: three); and the tile has as many columns as the LDS of that
+// many waves allows.  131,072 nodes in such communities, 128 columns: fp32 104 -> 85 us (92 us with three waves), bf16 74 ->
+// 49 us (61 us with three), 256 columns bf16 104 -> 73 us.
+constexpr int kEdgeRegs = 6, kEdgeMore = 8;
+template <int XK, int VW, int NG, bool FUSE> constexpr int small_waves()      // waves per SIMD
+{
+    constexpr int tiles = NG * VW;
+    if (tiles == 16) return XK == 0 || FUSE ? 1 : 3;
+    if (XK != 0 && VW == 8 && FUSE) return 3;
+    return tiles >= 4 ? 4 : 5;
+}
+template <int XK, int VW, int NG, bool FUSE> constexpr int small_cols()       // columns of the tile
+{
+    constexpr int waves = small_waves<XK, VW, NG, FUSE>();
+    return waves <= 3 ? 192 : waves == 4 && !FUSE ? 160 : 128;
+}
 
 // FUSE: instead of storing the window's 16 x d result, the wave parks it in its LDS region (the A
 // tile is dead by then), multiplies it by W on the matrix cores and stores act(Z W): the update
 // stage of the aggregate-then-update layer (Section V-A).  Needs d in one launch (col0 = 0).
 template <int XK, int VW, int NG, bool FUSE = false>
-__global__ __launch_bounds__(256) void k_mfma_small(int32_t n_list, const WinDesc* __restrict__ desc,
+__global__ __launch_bounds__(256, (small_waves<XK, VW, NG, FUSE>())) void k_mfma_small(int32_t n_list, const WinDesc* __restrict__ desc,
                                                     const int32_t* __restrict__ wcols,
                                                     const int32_t* __restrict__ erc, int col0, int xcd_chunk,
                                                     SpmmArgs a, UpdateArgs u)
 {
     using P = Path<XK, VW, NG>;
     constexpr int kLdz = NG * 16 * VW + 4;
-    constexpr int kRegion = (FUSE && 16 * kLdz > kKcSmall * 16) ? 16 * kLdz : kKcSmall * 16;
+    constexpr int kKc = small_cols<XK, VW, NG, FUSE>();
+    constexpr int kRegion = (FUSE && 16 * kLdz > kKc * 16) ? 16 * kLdz : kKc * 16;
     __shared__ float tiles[4][kRegion];
     __shared__ int32_t rows_s[FUSE ? 64 : 1];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -304,7 +326,7 @@ __global__ __launch_bounds__(256) void k_mfma_small(int32_t n_list, const WinDes
     const char* __restrict__ X = static_cast<const char*>(a.X) + (int64_t)col0 * P::ES;
     const int64_t ldxb = a.ldx * P::ES;
     const int d = min(a.d - col0, NG * 16 * VW);
-    constexpr int NB = kKcSmall / 64;                          // 64-column blocks per chunk
+    constexpr int NB = (kKc + 63) / 64;                        // 64-column blocks per chunk
     v4f acc[NG][VW];
 #pragma unroll
     for (int g = 0; g < NG; ++g)
@@ -316,31 +338,46 @@ __global__ __launch_bounds__(256) void k_mfma_small(int32_t n_list, const WinDes
     int32_t mycol[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) mycol[i] = wcols[wp + min(64 * i + lane, nc - 1)];
-    int32_t pe[kEdgeRegs];
-    float ve[kEdgeRegs];
-#pragma unroll
-    for (int q = 0; q < kEdgeRegs; ++q) {
-        const int32_t k = min(s + 64 * q + lane, e - 1);
-        pe[q] = erc[k];
-        ve[q] = a.vals[k];
-    }
+    int32_t pe[kEdgeRegs], pm[kEdgeMore];
+    float ve[kEdgeRegs], vm[kEdgeMore];
+    auto edges = [&](auto& p, auto& v, int32_t k0) {
+        unsigned q = 0;
+        for (int32_t& at : p) {
+            const int32_t k = min(k0 + (int32_t)(64 * q) + lane, e - 1);
+            at = erc[k];
+            v[q++] = a.vals[k];
+        }
+    };
+    auto scatter = [&](const auto& p, const auto& v, int32_t k0, int32_t kc0) {
+        unsigned q = 0;
+        for (const int32_t& at : p) {
+            const int32_t ec = (at >> 4) - kc0;
+            if (k0 + (int32_t)(64 * q) + lane < e && ec >= 0 && ec < kKc) atomicAdd(&tile[P::tidx(ec, at & 15)], v[q]);
+            ++q;
+        }
+    };
+    // the columns of a chunk that the window has, in whole blocks of 64
+    auto clear = [&](int32_t kc0) {
+        const int n = min(kKc, (nc - kc0 + 63) / 64 * 64) * 16;
+        for (int i = lane * 4; i < n; i += 256) *reinterpret_cast<float4*>(&tile[i]) = make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    edges(pe, ve, s);
+    const bool more = s + 64 * kEdgeRegs < e;
+    if (more) edges(pm, vm, s + 64 * kEdgeRegs);
     P::load(0, mycol[0], lane, X, ldxb, d, xa[0]);
-    for (int i = lane * 4; i < kKcSmall * 16; i += 256)
-        *reinterpret_cast<float4*>(&tile[i]) = make_float4(0.f, 0.f, 0.f, 0.f);
+    clear(0);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-#pragma unroll
-    for (int q = 0; q < kEdgeRegs; ++q) {
-        const int32_t ec = pe[q] >> 4;
-        if (s + 64 * q + lane < e && ec < kKcSmall) atomicAdd(&tile[P::tidx(ec, pe[q] & 15)], ve[q]);
-    }
-    for (int32_t k = s + 64 * kEdgeRegs + lane; k < e; k += 64) {
-        const int32_t p = erc[k];
-        const int32_t ec = p >> 4;
-        if (ec < kKcSmall) atomicAdd(&tile[P::tidx(ec, p & 15)], a.vals[k]);
+    scatter(pe, ve, s, 0);
+    if (more) {
+        scatter(pm, vm, s + 64 * kEdgeRegs, 0);
+        for (int32_t k0 = s + 64 * (kEdgeRegs + kEdgeMore); k0 < e; k0 += 64 * kEdgeMore) {
+            edges(pm, vm, k0);
+            scatter(pm, vm, k0, 0);
+        }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     for (int32_t kc0 = 0;;) {
-        const int kend = min(kKcSmall, nc - kc0);
+        const int kend = min(kKc, nc - kc0);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             if (64 * b < kend) {
@@ -351,18 +388,16 @@ __global__ __launch_bounds__(256) void k_mfma_small(int32_t n_list, const WinDes
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         // further chunks of wider windows: rebuild the tile from all the window's non-zeros
-        kc0 += kKcSmall;
+        kc0 += kKc;
         if (kc0 >= nc) break;
 #pragma unroll
         for (int i = 0; i < NB; ++i) mycol[i] = wcols[wp + min(kc0 + 64 * i + lane, nc - 1)];
-        for (int i = lane * 4; i < kKcSmall * 16; i += 256)
-            *reinterpret_cast<float4*>(&tile[i]) = make_float4(0.f, 0.f, 0.f, 0.f);
+        clear(kc0);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         P::load(0, mycol[0], lane, X, ldxb, d, xa[0]);
-        for (int32_t k = s + lane; k < e; k += 64) {
-            const int32_t p = erc[k];
-            const int32_t ec = (p >> 4) - kc0;
-            if (ec >= 0 && ec < kKcSmall) atomicAdd(&tile[P::tidx(ec, p & 15)], a.vals[k]);
+        for (int32_t k0 = s; k0 < e; k0 += 64 * kEdgeMore) {
+            edges(pm, vm, k0);
+            scatter(pm, vm, k0, kc0);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
