@@ -602,10 +602,13 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
             p->panel[q].multi = pa.multi + q * pa.cap_multi;
         }
     }
-    // Walking every row and skipping the ones another kernel owns is cheaper than an index list
-    // while most rows are short scalar-path rows; otherwise keep the explicit list.
+    // Walking every row and skipping the ones another tier owns is cheaper than an index list while most rows are short
+    // scalar-path rows.  Rows of matrix-path windows come in whole windows, i.e. whole workgroups that start only to find
+    // nothing to do, and the list pays from a sixteenth of the windows on (walk / list, us, communities + power law, fp32, 128
+    // columns: 131,072 + 169,343 rows 225 / 212, 131,072 + 400,000 453 / 447, 65,536 + 169,343 177 / 172, 32,768 + 300,000
+    // 167 / 164; bf16 121 / 116).
     p->short_rows = nullptr;
-    if ((int64_t)p->n_short * 2 < n_rows) {
+    if ((int64_t)p->n_short * 2 < n_rows || (!p->scalar_exec && (int64_t)p->n_mfma * 16 >= W)) {
         HC_ALLOC(keep, p->short_rows, p->n_short);
         Prep fill = pr;
         fill.mid_rows = fill.rest_rows = nullptr; fill.segs = nullptr; fill.multi = nullptr; fill.out = nullptr;

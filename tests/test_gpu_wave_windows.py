@@ -1,5 +1,5 @@
-"""GPU parity of the wave-per-window matrix kernel at the edges of its column tile (128, 160 and 192 columns by form) and of its
-rounds of non-zeros (384, 896 and 512 more at a time)."""
+"""GPU parity of the wave-per-window matrix kernel at the edges of its column tile (128, 160 and 192 columns by form), of its
+rounds of non-zeros (384, 896 and 512 more at a time), and of graphs with windows of both kinds and a list of the scalar rows."""
 import numpy as np
 import pytest
 
@@ -8,7 +8,7 @@ from workloads import CSRGraph, dense_normal, to_bf16_bits, to_f16_bits
 from gpu_util import gpu_spmm, assert_close, oracle_pair
 
 pytestmark = pytest.mark.gpu
-ALL_MFMA = 2
+ALL_MFMA, PER_WINDOW = 2, 3
 
 
 def windows(cols_nnz, n_cols=1000, seed=0):
@@ -46,3 +46,16 @@ def test_tile_and_round_edges(x_bits, d):
         tol = 2e-2                                              # A is rounded to the 16-bit type on this path
     assert info["n_mfma_small"] == len(EDGES)
     assert_close(Y, ref, bound, tol, "%s d=%d" % (x_bits, d))
+
+
+@pytest.mark.parametrize("matrix_windows", [0, 1, 6, 7, 50, 99, 100])
+def test_scalar_rows_beside_matrix_windows(matrix_windows):
+    # a sixteenth of 100 windows is between 6 and 7; windows of few non-zeros per column stay scalar
+    kinds = [(40, 500)] * matrix_windows + [(120, 130)] * (100 - matrix_windows)
+    np.random.default_rng(3).shuffle(kinds)
+    g = windows(kinds, seed=matrix_windows)
+    X = dense_normal(g.n_cols, 48, seed=1)
+    Y, info = gpu_spmm(g, X, PER_WINDOW, sel_coef=[1, 0, -100])  # columns > 100: scalar
+    assert info["n_mfma_windows"] == matrix_windows
+    ref, bound = oracle_pair(g, X)
+    assert_close(Y, ref, bound, 1e-5)
