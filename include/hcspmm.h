@@ -384,7 +384,7 @@ size_t hcspmm_gcn_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t
 /*
  * Aggregate-then-update layer  Y = act((A X) W)  -- the association of GIN's forward pass and of
  * GCN's backward pass, for which Section V-A describes the coupled kernel (aggregate a window,
- * then multiply its result tile by W).  Three forms, with the same results up to the order of summation:
+ * then multiply its result tile by W).  Four forms, with the same results up to the order of summation:
  *   fused   short scalar-path rows and wave-per-window matrix-path tiles stay in LDS and are multiplied by W
  *           on the fp32 matrix cores before anything is stored; the remaining rows (long rows, very wide
  *           windows) pass through the workspace.  Taken for graphs of a few thousand rows, where launches
@@ -396,7 +396,10 @@ size_t hcspmm_gcn_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t
  *   apart   Z = A X is written to the workspace and one fp32 MFMA kernel applies W and the activation.  Taken
  *           otherwise, and always when d_in is no multiple of 16 or above 256, X is not aligned for vector
  *           loads, or the graph is walked in column panels.
- * HCSPMM_UPDATE_FUSED takes the first form whenever widths and alignment allow it, HCSPMM_UPDATE_SPLIT the last.
+ *   before  X W goes to the workspace in fp32 and is aggregated from there, with the activation in the aggregation's
+ *           epilogue.  Taken, before any of the above, where rows of X W touch fewer memory lines than rows of X (on
+ *           graphs of some ten thousand rows and more, n_cols <= n_rows).
+ * HCSPMM_UPDATE_FUSED takes the first form whenever widths and alignment allow it, HCSPMM_UPDATE_SPLIT the third.
  *
  *   d_X   device, n_cols x d_in, element type x_dtype (ldx >= d_in)
  *   d_W   device, d_in x d_out fp32 (ldw >= d_out)
@@ -404,7 +407,8 @@ size_t hcspmm_gcn_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t
  *         rounding of the fp32 result when it is stored -- a chain of such layers with 16-bit X and Y needs no
  *         conversion pass between layers
  *   d_workspace  device, at least hcspmm_aggregate_update_workspace_bytes(plan, d_in, d_out) bytes,
- *                256-byte aligned; holds Z (n_rows x d_in fp32) on return when the update was taken apart
+ *                256-byte aligned; holds Z (n_rows x d_in fp32) on return when the update was taken apart, X W
+ *                (n_cols x d_out fp32) when it came before
  * Asynchronous on `stream`.  Errors as hcspmm_spmm.
  */
 hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, int64_t ldx, int32_t d_in,

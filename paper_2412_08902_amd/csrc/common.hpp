@@ -320,6 +320,10 @@ hipError_t launch_reduce_tiles(const SpmmArgs& a, int32_t n_multi, const MultiRo
 // T = X W; with a mask (m x n, pitch ldm) T is stored as 0 where it is not positive
 hipError_t launch_gemm_f32(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
                            float* T, int64_t ldt, const float* mask, int64_t ldm, hipStream_t s);
+// T = X W in fp32 for X of any element type; 16-bit X needs rows and a base on whole 4-byte words (gemm_x16_usable)
+bool gemm_x16_usable(const void* X, int64_t ldx);
+hipError_t launch_gemm_x(int64_t m, int32_t k, int32_t n, const void* X, int64_t ldx, int32_t x_dtype, const float* W, int64_t ldw,
+                         float* T, int64_t ldt, hipStream_t s);
 // backward pass (Eq. 3): dW = X^T S over row spans, activation mask, transpose of W
 int32_t gemm_tn_spans(int64_t n_rows, int32_t d_in, int32_t d);
 hipError_t launch_gemm_tn(int64_t n_rows, const float* X, int64_t ldx, int32_t d_in, const float* S, int64_t lds_,

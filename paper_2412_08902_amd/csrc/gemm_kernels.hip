@@ -27,6 +27,43 @@ typedef float v4f_gemm __attribute__((ext_vector_type(4)));
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 template <int N> struct __attribute__((packed, aligned(4))) f32_any { float v[N]; };
 
+// Four consecutive values of a row of X as they were loaded: fp32 (XK 0), or bf16 (1) / fp16 (2) that are widened, exactly,
+// when they are multiplied.  4-byte alignment is enough for both.
+typedef uint32_t u2_any __attribute__((ext_vector_type(2), aligned(4)));
+template <int XK> struct XPiece { f4_any v; };
+template <> struct XPiece<1> { u2_any v; };
+template <> struct XPiece<2> { u2_any v; };
+template <int XK> using XElem = std::conditional_t<XK == 0, float, unsigned short>;
+template <int XK> __device__ __forceinline__ float x_widen(uint32_t bits)
+{
+    if constexpr (XK == 1) return __uint_as_float(bits << 16);
+    else return (float)__builtin_bit_cast(_Float16, (unsigned short)bits);
+}
+template <int XK> __device__ __forceinline__ XPiece<XK> x_load(const XElem<XK>* __restrict__ p)
+{
+    return {*reinterpret_cast<const decltype(XPiece<XK>::v)*>(p)};
+}
+template <int XK> __device__ __forceinline__ float x_at(const XPiece<XK>& x, int i)
+{
+    if constexpr (XK == 0) return x.v[i];
+    else if constexpr (XK == 1) return __uint_as_float((i & 1) ? (x.v[i >> 1] & 0xffff0000u) : (x.v[i >> 1] << 16));
+    else return x_widen<XK>((i & 1) ? x.v[i >> 1] >> 16 : x.v[i >> 1] & 0xffffu);
+}
+// the first n < 4 values at p, the others zero
+template <int XK> __device__ __forceinline__ XPiece<XK> x_load_some(const XElem<XK>* __restrict__ p, int n)
+{
+    XPiece<XK> x{};
+    if constexpr (XK == 0) {
+        x.v[0] = n > 0 ? p[0] : 0.f;
+        x.v[1] = n > 1 ? p[1] : 0.f;
+        x.v[2] = n > 2 ? p[2] : 0.f;
+    } else {
+        x.v[0] = (n > 0 ? (uint32_t)p[0] : 0u) | (n > 1 ? (uint32_t)p[1] << 16 : 0u);
+        x.v[1] = n > 2 ? (uint32_t)p[2] : 0u;
+    }
+    return x;
+}
+
 constexpr int kGemmWaves = 4, kGemmRows = 16 * kGemmWaves, kGemmBK = 32;
 
 // Where the product goes: T (M x N, pitch ldt, element type t_dtype), max(0, .) applied first with relu; with a mask (pitch
@@ -105,8 +142,8 @@ __device__ __forceinline__ void store_tile(v4f_gemm (&acc)[NT], int64_t m0, int 
 // WV: floats per global load of W (4: W's rows are 16-byte aligned and N is a multiple of 4).
 // Rows past M re-read row M-1 and columns past N read column N-WV: what they produce is never stored.  k >= K is zero in both
 // operands.  WIDE: byte offsets inside a slab of W need 64 bits (launch_gemm_f32_out says when).
-template <int NT, int WV, bool WIDE, bool MASK>
-__global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k_gemm_f32(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
+template <int XK, int NT, int WV, bool WIDE, bool MASK>
+__global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k_gemm_f32(int64_t M, int32_t K, int32_t N, const XElem<XK>* __restrict__ X, int64_t ldx,
                                                      const float* __restrict__ Wm, int64_t ldw, GemmOut out,
                                                      const uint8_t* __restrict__ done_route,
                                                      const int32_t* __restrict__ done_cols, int32_t done_max)
@@ -134,7 +171,7 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
         }
         if (all) return;
     }
-    const float* __restrict__ xp = X + min(m0 + c, M - 1) * ldx + 4 * q;
+    const XElem<XK>* __restrict__ xp = X + min(m0 + c, M - 1) * ldx + 4 * q;
 
     // this thread's pieces of a W slab: (k row, column) inside the slab, WV floats each
     auto at = [&](int i, int& k, int& col) { const int idx = (tid + kThreads * i) * WV; k = idx / COLS; col = idx % COLS; };
@@ -147,12 +184,10 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
     }
     auto w_at = [&](int k0, int i) { return reinterpret_cast<const float*>(reinterpret_cast<const char*>(Wm + (int64_t)k0 * ldw) + wo[i]); };
     float b_next[ITERS][WV];
-    auto request_x = [&](int k0, float4 (&a)[2]) {                  // a whole slab
+    using Piece = XPiece<XK>;
+    auto request_x = [&](int k0, Piece (&a)[2]) {                   // a whole slab
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const f4_any v = *reinterpret_cast<const f4_any*>(xp + k0 + 16 * u);
-            a[u] = make_float4(v.x, v.y, v.z, v.w);
-        }
+        for (int u = 0; u < 2; ++u) a[u] = x_load<XK>(xp + k0 + 16 * u);
     };
     auto request_w = [&](int k0) {
 #pragma unroll
@@ -180,9 +215,11 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = (v4f_gemm){0.f, 0.f, 0.f, 0.f};
     // UNITS times 16 k of the slab at b: the W values of a step are read while the products of the step before run
-    auto multiply = [&](auto units, const float* __restrict__ b, const float4 (&a)[2]) {
+    auto multiply = [&](auto units, const float* __restrict__ b, const Piece (&a)[2]) {
         constexpr int STEPS = decltype(units)::value * 4;
-        const float av[8] = {a[0].x, a[0].y, a[0].z, a[0].w, a[1].x, a[1].y, a[1].z, a[1].w};
+        float av[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) av[i] = x_at<XK>(a[i / 4], i % 4);
         float w[2][NT];
         auto read = [&](int t, float (&o)[NT]) {
             const float* __restrict__ row = b + (t / 4 * 16 + t % 4) * COLS;
@@ -213,12 +250,12 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
     const int whole = K / kGemmBK * kGemmBK;
     int buf = 0;
     if (whole > 0) {
-        float4 even[2], odd[2];
+        Piece even[2], odd[2];
         // X pieces are asked for two slabs ahead, behind the W values of the next slab: the wait for those leaves them in
         // flight.  The requests past the end repeat the last slab (branches around them would cost waits at their joins).
         const int last = whole - kGemmBK;
-        auto slab = [&](int k0, float4 (&x)[2]) {
-            const float4 a[2] = {x[0], x[1]};
+        auto slab = [&](int k0, Piece (&x)[2]) {
+            const Piece a[2] = {x[0], x[1]};
             request_w(min(k0 + kGemmBK, last));
             request_x(min(k0 + 2 * kGemmBK, last), x);
             __builtin_amdgcn_sched_barrier(0);                      // (the compiler would move the requests to where they are used)
@@ -241,20 +278,13 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
         }
     }
     if (whole < K) {                                                // the rest of K, zero-filled to one or two units
-        float4 a[2];
+        Piece a[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int k = whole + 16 * u + 4 * q;
-            const float* __restrict__ p = xp + whole + 16 * u;
-            a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (k + 3 < K) {
-                const f4_any v = *reinterpret_cast<const f4_any*>(p);
-                a[u] = make_float4(v.x, v.y, v.z, v.w);
-            } else if (k < K) {
-                a[u].x = p[0];
-                if (k + 1 < K) a[u].y = p[1];
-                if (k + 2 < K) a[u].z = p[2];
-            }
+            const int left = K - (whole + 16 * u + 4 * q);
+            const XElem<XK>* __restrict__ p = xp + whole + 16 * u;
+            if (left > 3) a[u] = x_load<XK>(p);
+            else a[u] = x_load_some<XK>(p, left);
         }
         float* __restrict__ dst = bs + buf * SLAB;
 #pragma unroll
@@ -281,8 +311,8 @@ __global__ __launch_bounds__(kGemmWaves * 128, WV == 1 && NT > 6 ? 3 : 4) void k
 // times some row streams; those that hold different columns of the same rows share X through L1.  W comes through LDS once
 // per workgroup, every workgroup starting at another row of it: waves that each read their columns from memory cost 10 us more
 // at 17,000 x 128 x 128 (the CUs of an XCD asking one L2 channel for the same lines at the same time).
-template <int K16, int NT, bool MASK>
-__global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, int32_t N, const float* __restrict__ X, int64_t ldx,
+template <int XK, int K16, int NT, bool MASK>
+__global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, int32_t N, const XElem<XK>* __restrict__ X, int64_t ldx,
                                                          const float* __restrict__ Wm, int64_t ldw, GemmOut out, int wvec, int32_t groups)
 {
     extern __shared__ __attribute__((aligned(16))) float smem[];    // 16*K16 rows of W, groups * 16*NT columns each
@@ -292,12 +322,11 @@ __global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, i
     const int64_t stream = (int64_t)blockIdx.x * per_block + wave / groups, streams = (int64_t)gridDim.x * per_block;
     const int n0 = first + wave % groups * 16 * NT;
     const int64_t n_tiles = (M + 15) / 16;
-    float4 x[K16];
+    XPiece<XK> x[K16];
     auto request = [&](int64_t tile, int u) {
         const int k = 16 * u + 4 * q;
-        const float* __restrict__ p = X + min(tile * 16 + c, M - 1) * ldx;
-        const f4_any v = *reinterpret_cast<const f4_any*>(p + (u == K16 - 1 && k >= K ? 0 : k));    // (zeroed when it is used)
-        x[u] = make_float4(v.x, v.y, v.z, v.w);
+        const XElem<XK>* __restrict__ p = X + min(tile * 16 + c, M - 1) * ldx;
+        x[u] = x_load<XK>(p + (u == K16 - 1 && k >= K ? 0 : k));    // (zeroed when it is used)
     };
 #pragma unroll
     for (int u = 0; u < K16; ++u) request(min(stream, n_tiles - 1), u);
@@ -346,7 +375,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, i
         for (int j = 0; j < NT; ++j) acc[j] = (v4f_gemm){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < K16; ++u) {
-            float a[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+            float a[4] = {x_at<XK>(x[u], 0), x_at<XK>(x[u], 1), x_at<XK>(x[u], 2), x_at<XK>(x[u], 3)};
             if (u == K16 - 1 && 16 * u + 4 * q >= K) a[0] = a[1] = a[2] = a[3] = 0.f;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -366,9 +395,10 @@ hipError_t launch_gemm_f32(int64_t m, int32_t k, int32_t n, const float* X, int6
     return launch_gemm_f32_out(m, k, n, X, ldx, W, ldw, T, ldt, HCSPMM_F32, 0, s, nullptr, nullptr, mask, ldm);
 }
 
-hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
-                               void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s, const uint8_t* done_route,
-                               const int32_t* done_cols, const float* mask, int64_t ldm)
+template <int XK>
+static hipError_t launch_gemm_of(int64_t m, int32_t k, int32_t n, const XElem<XK>* X, int64_t ldx, const float* W, int64_t ldw,
+                                 void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s, const uint8_t* done_route,
+                                 const int32_t* done_cols, const float* mask, int64_t ldm)
 {
     if (m <= 0 || n <= 0) return hipSuccess;
     if (t_dtype != HCSPMM_F32 && t_dtype != HCSPMM_BF16 && t_dtype != HCSPMM_F16) return hipErrorInvalidValue;
@@ -387,8 +417,8 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
         const dim3 grid((unsigned)std::min<int64_t>(want, k16 * nt > 16 ? 256 : k16 * nt > 4 ? 512 : 1024), (unsigned)ny);
         const size_t lds = (size_t)16 * k16 * groups * 16 * nt * sizeof(float);                     // 48 KB at most
         const int wvec = n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0;
-#define HC_REG(KK, NT) do { if (mask) HC_REG1(KK, NT, true); else HC_REG1(KK, NT, false); } while (0)
-#define HC_REG1(KK, NT, MASK) hipLaunchKernelGGL((k_gemm_f32_reg<KK, NT, MASK>), grid, dim3(512), lds, s, m, k, n, X, ldx, W, ldw, out, wvec, groups)
+#define HC_REG(KK, NT) do { if constexpr (XK == 0) { if (mask) { HC_REG1(KK, NT, true); break; } } HC_REG1(KK, NT, false); } while (0)
+#define HC_REG1(KK, NT, MASK) hipLaunchKernelGGL((k_gemm_f32_reg<XK, KK, NT, MASK>), grid, dim3(512), lds, s, m, k, n, X, ldx, W, ldw, out, wvec, groups)
 #define HC_REG_NT(KK) case KK: if (nt == 4) HC_REG(KK, 4); else if (nt == 3) HC_REG(KK, 3); else if (nt == 2) HC_REG(KK, 2); else HC_REG(KK, 1); break
         switch (k16) {
             HC_REG_NT(1); HC_REG_NT(2); HC_REG_NT(3); HC_REG_NT(4); HC_REG_NT(5); HC_REG_NT(6); HC_REG_NT(7); HC_REG_NT(8);
@@ -406,8 +436,8 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
     const dim3 grid((unsigned)((m + kGemmRows - 1) / kGemmRows), (unsigned)(groups / pair));
     const size_t lds = (size_t)pair * 2 * kGemmBK * 16 * nt * sizeof(float);
     const int wv = (n % 4 == 0 && ldw % 4 == 0 && (uintptr_t)W % 16 == 0) ? 4 : 1;
-#define HC_LAUNCH_GEMM(NT, WV, WIDE) do { if (mask) HC_GEMM1(NT, WV, WIDE, true); else HC_GEMM1(NT, WV, WIDE, false); } while (0)
-#define HC_GEMM1(NT, WV, WIDE, MASK) hipLaunchKernelGGL((k_gemm_f32<NT, WV, WIDE, MASK>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, out, done_route, done_cols, kMfmaSmallMaxCols)
+#define HC_LAUNCH_GEMM(NT, WV, WIDE) do { if constexpr (XK == 0) { if (mask) { HC_GEMM1(NT, WV, WIDE, true); break; } } HC_GEMM1(NT, WV, WIDE, false); } while (0)
+#define HC_GEMM1(NT, WV, WIDE, MASK) hipLaunchKernelGGL((k_gemm_f32<XK, NT, WV, WIDE, MASK>), grid, dim3(64 * kGemmWaves * pair), lds, s, m, k, n, X, ldx, W, ldw, out, done_route, done_cols, kMfmaSmallMaxCols)
 #define HC_GEMM_NT(NT) case NT: if (wv == 4) HC_LAUNCH_GEMM(NT, 4, false); else HC_LAUNCH_GEMM(NT, 1, false); break
     if (wide) HC_LAUNCH_GEMM(8, 1, true);
     else switch (nt) {
@@ -417,6 +447,25 @@ hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, 
 #undef HC_LAUNCH_GEMM
 #undef HC_GEMM1
     return hipGetLastError();
+}
+
+hipError_t launch_gemm_f32_out(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
+                               void* T, int64_t ldt, int32_t t_dtype, int relu, hipStream_t s, const uint8_t* done_route,
+                               const int32_t* done_cols, const float* mask, int64_t ldm)
+{
+    return launch_gemm_of<0>(m, k, n, X, ldx, W, ldw, T, ldt, t_dtype, relu, s, done_route, done_cols, mask, ldm);
+}
+
+bool gemm_x16_usable(const void* X, int64_t ldx) { return ldx % 2 == 0 && (uintptr_t)X % 4 == 0; }
+
+hipError_t launch_gemm_x(int64_t m, int32_t k, int32_t n, const void* X, int64_t ldx, int32_t x_dtype, const float* W, int64_t ldw,
+                         float* T, int64_t ldt, hipStream_t s)
+{
+    if (x_dtype == HCSPMM_F32) return launch_gemm_f32(m, k, n, static_cast<const float*>(X), ldx, W, ldw, T, ldt, nullptr, 0, s);
+    if (!gemm_x16_usable(X, ldx)) return hipErrorInvalidValue;
+    const unsigned short* x = static_cast<const unsigned short*>(X);
+    return x_dtype == HCSPMM_BF16 ? launch_gemm_of<1>(m, k, n, x, ldx, W, ldw, T, ldt, HCSPMM_F32, 0, s, nullptr, nullptr, nullptr, 0)
+                                  : launch_gemm_of<2>(m, k, n, x, ldx, W, ldw, T, ldt, HCSPMM_F32, 0, s, nullptr, nullptr, nullptr, 0);
 }
 
 }  // namespace hcspmm

@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <deque>
 #include <mutex>
 #include <new>
@@ -1486,6 +1487,45 @@ static UpdatePlace update_place(const hcspmm_plan* plan, int32_t agg_width, int3
     return windows && product <= (plan->n_mfma_small >= 4096 ? 16384 : 12288) ? kUpdateInWindows : kUpdateApart;
 }
 
+// 128-byte lines that a row of w elements of es bytes touches on average, by what its base and pitch are multiples of
+static double row_lines(const void* base, int64_t ld, int32_t w, int es)
+{
+    const uint64_t all = (uint64_t)(uintptr_t)base | (uint64_t)ld * (uint64_t)es | 128u;
+    const double unit = (double)(all & (~all + 1));             // the largest power of two that divides both, 128 at most
+    const double bytes = (double)w * es;
+    return std::ceil(bytes / unit) * unit / 128.0 + (128.0 - unit) / 128.0;
+}
+
+// Whether Y = act((A X) W) is computed as act(A (X W)): the same sums in fp32, associated the other way.  Where W makes rows
+// shorter the gather, which is most of the call, then reads rows of d_out instead of d_in columns, and one trip of the rows
+// through memory (X in, X W out) takes the place of the aggregated rows' (out and in again).  In this order / X W first, us:
+// 169,343 rows of 14, fp32: 64 -> 32 columns 85 / 51, 128 -> 64 165 / 102, 256 -> 128 380 / 232; 400,000 of 40, 128 -> 64: 975 /
+// 498; 1 M of 60 (in one pass with the product): 3825 / 2274; 131,072 in communities, 128 -> 64: 96 / 64.  X W is held in fp32, so
+// that 16-bit rows have to become half as long for the same bytes: 169,343 of 14, bf16, 128 -> 64: 109 / 98, 128 -> 48: 106 / 90;
+// 400,000 of 40, f16, 256 -> 96: 1162 / 803.
+// What counts is the lines that a gathered row touches.  Fewer by an eighth or so pay on graphs of some ten thousand rows and
+// more (103,368 of 190, 144 -> 115: 1258 / 922; 257,395 of 36, 149 -> 119: 833 / 680; but 11,806 of 16, 176 -> 140: 30 / 34), fewer
+// by a fifth on smaller ones with work to save (16,934 of 14, 128 -> 64: 20.6 / 20.1; 11,735 of 8, 160 -> 96: 21.3 / 22.6).  As
+// many lines pay for 16-bit rows of a line and more that would go through the workspace (1 M of 60, bf16, 128 -> 64, in one
+// pass: 2049 / 2267; 16 -> 8 columns: 103 / 107).  Matrix-path windows fetch a 16-bit row once per window and multiply on chip:
+// 131,072 in communities, bf16, 128 -> 64: 60 / 68, 54,144, 112 -> 33: 43 / 68.
+// What the other order refuses stays refused, and nothing is allocated that it would not have allocated.
+static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, int32_t y_dtype, size_t workspace)
+{
+    if (plan->opt.update_fusion != HCSPMM_UPDATE_AUTO) return false;
+    if (plan->n_cols > plan->n_rows || (size_t)plan->n_cols * d_out * sizeof(float) > workspace) return false;
+    const bool f32 = a.x_dtype == HCSPMM_F32;
+    if (!f32 && !gemm_x16_usable(a.X, a.ldx)) return false;
+    if (plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) return false;
+    if (plan->n_panels > 1 && y_dtype != HCSPMM_F32 && plan->acc_rows_elems < (int64_t)plan->n_rows * d_out) return false;
+    const bool windows = !plan->scalar_exec && 2 * plan->n_mfma_small >= plan->W, many = plan->n_rows >= 40000;
+    const bool apart = update_place(plan, a.d, d_out, a.x_dtype, false) == kUpdateApart;
+    if (!many && (plan->nnz < 100000 || (plan->n_rows <= 8192 && !apart))) return false;
+    const double before = row_lines(a.X, a.ldx, a.d, f32 ? 4 : 2), after = row_lines(nullptr, d_out, d_out, 4);
+    if (after <= (!f32 && windows ? 0.6 : many ? 0.92 : 0.8) * before) return true;
+    return !f32 && !windows && many && 2 * a.d >= 128 && after <= before && plan->n_panels < 2 && apart;
+}
+
 size_t hcspmm_aggregate_update_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)
 {
     (void)d_out;
@@ -1516,6 +1556,12 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
     SpmmArgs a{};
     a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d_in; a.x_dtype = x_dtype; a.Y = Z; a.ldy = d_in; a.relu = 0;
+    if (update_before(plan, a, d_out, y_dtype, need)) {
+        HC_HIP(launch_gemm_x(plan->n_cols, d_in, d_out, d_X, ldx, x_dtype, static_cast<const float*>(d_W), ldw, Z, d_out, s));
+        a.X = Z; a.ldx = d_out; a.d = d_out; a.x_dtype = HCSPMM_F32;
+        a.Y = static_cast<float*>(d_Y); a.ldy = ldy; a.y_dtype = y_dtype; a.relu = apply_relu ? 1 : 0;
+        return run_spmm(plan, a, s, nullptr, nullptr, false, nullptr, true);
+    }
     const UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
                               : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
                                                                                : update_place(plan, d_in, d_out, x_dtype, false);

@@ -1,0 +1,88 @@
+"""GPU parity of Y = act((A X) W) where the library computes act(A (X W)): widths and types on both sides of the rule, the
+product with 16-bit X at its remainders, and the calls that keep the other order.  The route is read off the workspace, which
+then starts with X W."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import CSRGraph, dense_normal, glorot_uniform, to_bf16_bits, to_f16_bits
+from gpu_util import device_graph, assert_close
+
+pytestmark = pytest.mark.gpu
+KINDS = {"f32": (0, None), "bf16": (1, oracle.DT_BF16), "f16": (2, oracle.DT_F16)}
+
+
+def graph(n_rows, n_cols, degree, seed):
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 2 * degree + 1, n_rows)
+    lens[0] = min(n_cols, 3000)                                 # a long row of several segments, and empty rows
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    colind = rng.integers(0, n_cols, rowptr[-1]).astype(np.int32)
+    row = np.repeat(np.arange(n_rows), lens)
+    colind = colind[np.lexsort((colind, row))]
+    return CSRGraph(n_rows, n_cols, rowptr, colind, rng.uniform(-1, 1, len(colind)).astype(np.float32))
+
+
+def run(g, X, W, kind, x_pad=0, x_off=0, relu=True, **options):
+    """(Y, the workspace's first n_cols x d_out floats, reference, bound)"""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    code, dt = KINDS[kind]
+    bits = X if kind == "f32" else (to_bf16_bits if kind == "bf16" else to_f16_bits)(X)
+    host = torch.from_numpy(bits if kind == "f32" else bits.view(np.int16))
+    flat = torch.zeros(x_off + g.n_cols * (X.shape[1] + x_pad), dtype=host.dtype, device="cuda")
+    Xd = torch.as_strided(flat, X.shape, (X.shape[1] + x_pad, 1), x_off)
+    Xd.copy_(host)
+    if kind != "f32":
+        Xd = Xd.view(torch.bfloat16 if kind == "bf16" else torch.float16)
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *device_graph(g), d_hint=X.shape[1], mfma_dtype=code, **options)
+    d_out = W.shape[1]
+    ws = torch.zeros(hc.hcspmm_aggregate_update_workspace_bytes(plan, X.shape[1], d_out), dtype=torch.uint8, device="cuda")
+    Y = torch.full((g.n_rows, d_out), -777.0, device="cuda")
+    hc.hcspmm_aggregate_update(plan, Xd, torch.from_numpy(W).cuda(), Y, ws, apply_relu=relu)
+    torch.cuda.synchronize()
+    plan.destroy()
+    T = ws.view(torch.float32)[: min(ws.numel() // 4, g.n_cols * d_out)].cpu().numpy()
+    ref = oracle.aggregate_update(g.rowptr, g.colind, g.vals, bits, W, relu=relu, x_dtype=dt)
+    bound = oracle.aggregate_update(g.rowptr, g.colind, g.vals, bits, W, relu=relu, x_dtype=dt, use_abs=True)
+    XW = oracle.gemm(bits, W, x_dtype=dt)
+    first = T.size == XW.size and np.allclose(T.reshape(XW.shape), XW, rtol=0, atol=1e-4 * np.abs(XW).max())
+    return Y.cpu().numpy().astype(np.float64), first, ref, bound
+
+
+# n_rows, degree, d_in, d_out, kind, taken
+CASES = [(9000, 12, 32, 16, "f32", False),                      # one line either way
+         (9000, 12, 64, 32, "f32", True), (9000, 12, 128, 96, "f32", True), (9000, 12, 128, 112, "f32", False),
+         (8192, 30, 33, 7, "f32", True), (9000, 5, 64, 32, "f32", False),       # too little to save
+         (40001, 3, 64, 28, "f32", True), (40001, 3, 64, 33, "f32", False), (40001, 3, 144, 115, "f32", True), (40001, 3, 64, 64, "f32", False),
+         (40001, 3, 128, 64, "bf16", True), (40001, 3, 128, 65, "f16", False), (40001, 3, 16, 8, "bf16", False),
+         (9000, 12, 128, 64, "bf16", False), (9000, 12, 128, 17, "bf16", True),
+         # 16-bit X: K below, at and above the slabs and units of the product, ragged widths of W
+         (9000, 12, 66, 3, "bf16", True), (9000, 12, 100, 1, "f16", True), (9000, 12, 131, 5, "bf16", True),
+         (9000, 12, 160, 31, "f16", True), (9000, 12, 254, 62, "bf16", True), (9000, 12, 257, 47, "f16", True),
+         # ... and with W in registers (from 65,536 rows on, or k n <= 1024)
+         (65537, 2, 128, 64, "f16", True), (65537, 2, 100, 20, "bf16", True), (65537, 2, 84, 24, "bf16", True),
+         (9000, 12, 80, 4, "bf16", True), (9000, 12, 68, 15, "f16", True)]
+
+
+@pytest.mark.parametrize("n_rows,degree,d_in,d_out,kind,taken", CASES)
+def test_both_sides_of_the_rule(n_rows, degree, d_in, d_out, kind, taken):
+    g = graph(n_rows, n_rows, degree, seed=d_in + d_out)
+    X, W = dense_normal(n_rows, d_in, seed=1), glorot_uniform(d_in, d_out, seed=2)
+    pad = d_in % 2                                              # rows of 16-bit X on whole words
+    Y, first, ref, bound = run(g, X, W, kind, x_pad=pad, relu=d_out % 2 == 0, route_mode=1)
+    assert first == taken
+    assert_close(Y, ref, bound, 1e-5)
+
+
+@pytest.mark.parametrize("kind,n_rows,n_cols,x_pad,x_off,options", [
+    ("f32", 9000, 9001, 0, 0, {}),                              # X W would be larger than the other order's rows
+    ("bf16", 9000, 9000, 1, 0, {}), ("f16", 9000, 9000, 0, 1, {}),      # X off the 4-byte words
+    ("f32", 9000, 9000, 0, 0, {"update_fusion": 1}), ("f32", 9000, 9000, 0, 0, {"update_fusion": 2}),
+    ("f32", 9000, 1000, 1, 1, {}), ("bf16", 9000, 1000, 2, 2, {})])
+def test_calls_that_keep_their_order(kind, n_rows, n_cols, x_pad, x_off, options):
+    g = graph(n_rows, n_cols, 12, seed=5)
+    X, W = dense_normal(n_cols, 128, seed=1), glorot_uniform(128, 16, seed=2)
+    Y, first, ref, bound = run(g, X, W, kind, x_pad=x_pad, x_off=x_off, route_mode=1, **options)
+    assert first == (n_cols == 1000)                            # the last two are taken
+    assert_close(Y, ref, bound, 1e-5)
