@@ -1006,7 +1006,7 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
     const int64_t cols_scalar = p->total_ncols - (p->scalar_exec ? 0 : p->mfma_ncols);
     const bool scattered = !p->local && (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * cols_scalar > 6 * nnz_scalar);
     const CsrHints hints{nnz_scalar, n_scalar * kH, scattered, p->long_row};
-    const uint8_t* route = p->scalar_exec ? nullptr : p->route;
+    const uint8_t* route = p->scalar_exec || p->n_mfma == 0 ? nullptr : p->route;
     if (upd && !windows_only)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, n_scalar > 0 ? p->n_rows : 0, nullptr,
                           route, p->fused_mid_row, hints, stream, upd));

@@ -14,8 +14,8 @@
 // WIDE form with 64-bit row offsets.  X is read directly from global memory / L2 (the paper found
 // staging X in shared memory a loss on this path).  Three tiers by row length balance power-law
 // degree distributions:
-//   short rows  a lane group owns a row (or walks a few consecutive ones in one flattened loop, on
-//               matrices whose launch would not fit otherwise: csr_grid.hpp), and the workgroups
+//   short rows  a lane group owns a row (or takes a few consecutive ones, on matrices whose launch
+//               would not fit otherwise: csr_grid.hpp), and the workgroups
 //               reach the XCDs in runs so that neighbouring rows share an L2;
 //   mid rows    one wave per row, the groups stride over the row and combine with cross-lane adds;
 //   long rows   one workgroup per segment of kSegLen non-zeros, combined through LDS in a fixed
@@ -107,6 +107,7 @@ template <int XK> __device__ __forceinline__ float widened(const uint32_t* w, in
 // sums.  (Kept out of the plain kernels, which have no scalar register to spare in 128-byte rows: power law, fp32, 32
 // columns, 39.7 -> 35.1 us.)
 template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL = false> struct Gather {
+    static constexpr bool MANY = WIDE;                          // several rows to a group
     static constexpr int LANES = LANES_, GROUP = GROUP_, SPLIT = GROUP / LANES, STEPS = GROUP / SPLIT;
     static_assert((GROUP == 16 && (LANES == 16 || LANES == 8)) || (GROUP == 8 && LANES == 8), "forms");
     static constexpr int ES = XK == 0 ? 4 : 2;
@@ -118,9 +119,10 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
     static constexpr int RAW = BYTES;
     // Waves per SIMD the registers are held to.  Short rows are bound by their chain of dependent loads, so 16-byte
     // vectors with one accumulator set are squeezed into 64 registers for all 8 waves (community graph, bf16, 64 columns:
-    // 37.0 -> 32.2 us; power law, fp32, 32 columns: 36.7 -> 35.1 us); wider rows are bound by the traffic behind L2 and
-    // lose more to the squeeze (fp32, 128 columns: 120.8 -> 137 us).
-    static constexpr int WAVES = LANES == 8 ? (XK == 0 && PANEL ? 7 : 8) : (XK != 0 && VEC == 8 && NV == 1) ? 6 : 1;
+    // 37.0 -> 32.2 us), in fp32 into 72 for 7: the whole batch of steps() spills at 64 (2.4 M rows of 51, 32 columns: 2102 us
+    // with 7 waves, 2122 with 8 and half a batch in flight, 2234 with 8 and the spill); wider rows are bound by the traffic
+    // behind L2 and lose more to the squeeze (fp32, 128 columns: 120.8 -> 137 us).
+    static constexpr int WAVES = LANES == 8 ? (XK == 0 ? 7 : 8) : (XK != 0 && VEC == 8 && NV == 1) ? 6 : 1;
 
     const char* X;              // uniform: first column of the slice
     uint64_t ldxb;              // bytes between rows (uniform)
@@ -172,25 +174,34 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[v * VEC + i] = fmaf(w, widened<XK>(x[v].w, i), acc[v * VEC + i]);
     }
-    // steps T0 .. T0+COUNT-1: the rows requested together, then multiplied
-    template <int T0, int COUNT> __device__ __forceinline__ void steps(uint32_t key_, float val, float (&acc)[N]) const
+    // Steps T0 .. T0+COUNT-1: the rows requested together, then multiplied.  The order is fixed here: left alone the compiler
+    // widens the first 16-bit row, and waits for it, before it asks for the others (communities, bf16: 64 columns 26.0 -> 23.0
+    // us, 128 columns 48.9 -> 34.5 us; f16, 64 columns: 37.6 -> 24.1 us; power law of 169,343 rows, f16, 64 columns: 41 -> 33 us).
+    template <int T0, int COUNT, class Next> __device__ __forceinline__ void steps(uint32_t key_, float val, float (&acc)[N], Next&& next) const
     {
         Raw<RAW> x[COUNT][NV];
         unrolled<COUNT>([&](auto u) { this->template load<T0 + decltype(u)::value>(key_, x[decltype(u)::value]); });
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (T0 == 0) {
+            next();
+            __builtin_amdgcn_sched_barrier(0);
+        }
         unrolled<COUNT>([&](auto u) { this->template add<T0 + decltype(u)::value>(val, x[decltype(u)::value], acc); });
     }
     // Up to GROUP non-zeros (cnt of them, uniform within the group), U steps at a time.  Slots past the row's end carry the
     // row's last column with value 0, so the loads carry no branches.
-    __device__ __forceinline__ void batch(uint32_t key_, float val, int cnt, float (&acc)[N]) const
+    // next(): requests the next batch's indices, behind the first X rows: loads come back in order, and indices, which
+    // mostly come from behind L2, would hold up X rows that hit it.
+    template <class Next> __device__ __forceinline__ void batch(uint32_t key_, float val, int cnt, float (&acc)[N], Next&& next) const
     {
         if constexpr (SPLIT == 2 && XK == 0) {
             // a wave whose groups all have more than half a batch left keeps the whole batch in flight (16-bit rows have twice
             // the accumulators and would spill)
-            if (__all(cnt > GROUP / 2)) { steps<0, STEPS>(key_, val, acc); return; }
+            if (__all(cnt > GROUP / 2)) { steps<0, STEPS>(key_, val, acc, next); return; }
         }
         unrolled<STEPS / U>([&](auto blk) {
             constexpr int T0 = decltype(blk)::value * U;
-            if (T0 == 0 || cnt > T0 * SPLIT) this->template steps<T0, U>(key_, val, acc);
+            if (T0 == 0 || cnt > T0 * SPLIT) this->template steps<T0, U>(key_, val, acc, next);
         });
     }
     // (key, value) of non-zero k of a row ending at e (k may run past the end: value 0, last column)
@@ -210,8 +221,7 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
         float mv, nv;
         fetch(a, kb + lig, ke, mk, mv);
         for (int k0 = kb; k0 < ke; k0 += stride) {
-            fetch(a, k0 + stride + lig, ke, nk, nv);            // the next batch's indices before this batch's X rows
-            batch(mk, mv, min(GROUP, ke - k0), acc);
+            batch(mk, mv, min(GROUP, ke - k0), acc, [&] { fetch(a, k0 + stride + lig, ke, nk, nv); });
             mk = nk;
             mv = nv;
         }
@@ -272,64 +282,6 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
     }
 };
 
-// ---- short rows -----------------------------------------------------------------------------
-// A group walks grid.rows_per_group (one per lane at most) consecutive items (rows, or entries of row_list) in a
-// single flattened loop: each trip either moves to the next row (storing the finished one) or
-// consumes one batch of the current row, so groups of one wave stay busy on rows of unequal
-// length.  The rows' extents are fetched up front, one per lane.  `done(row, slot, acc)` takes a finished row.
-template <class G, class Done>
-__device__ __forceinline__ void walk_rows(const G& g, const SpmmArgs& a, int lig, int nr, int32_t my_row, int32_t my_s, int32_t my_e,
-                                          Done&& done)
-{
-    float acc[G::N];
-    vzero(acc);
-    int j = 0, k = 0, e = 0, slot = 0;
-    int32_t row = -1;
-    uint32_t mk = 0;
-    float mv = 0.f;
-    for (;;) {
-        if (k >= e) {
-            if (row >= 0) {
-                G::finish(acc);
-                done(row, slot, acc);
-            }
-            row = -1;
-            while (j < nr && row < 0) {
-                row = __shfl(my_row, j, G::GROUP);
-                k = __shfl(my_s, j, G::GROUP);
-                e = __shfl(my_e, j, G::GROUP);
-                slot = j;
-                ++j;
-            }
-            if (row < 0) break;
-            vzero(acc);
-            if (k < e) g.fetch(a, k + lig, e, mk, mv);
-            continue;                       // an empty row is finished (as zeros) on the next trip
-        }
-        uint32_t nk;
-        float nv;
-        g.fetch(a, k + G::GROUP + lig, e, nk, nv);
-        g.batch(mk, mv, min(G::GROUP, e - k), acc);
-        mk = nk;
-        mv = nv;
-        k += G::GROUP;
-    }
-}
-
-// extents of the items i0 .. i0+nr-1, one per lane; rows owned by the matrix path or by the mid/long tiers get row -1
-template <class G>
-__device__ __forceinline__ void row_extents(uint32_t i0, int lig, int nr, const CsrWork& wk, const SpmmArgs& a,
-                                            int32_t& row, int32_t& s, int32_t& e)
-{
-    row = -1; s = 0; e = 0;
-    if (lig < nr) {
-        row = wk.row_list ? wk.row_list[i0 + lig] : (int32_t)(i0 + lig);
-        G::extent(a, row, s, e);
-        if (!wk.row_list && ((wk.route && wk.route[row / kH] != 0) || e - s > wk.mid_row)) row = -1;
-        if (G::skipped(wk, s, e)) row = -1;
-    }
-}
-
 // ---- mid rows: one wave per row -------------------------------------------------------------
 template <class G>
 __device__ __forceinline__ void csr_mid_body(uint32_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a,
@@ -358,20 +310,41 @@ __device__ __forceinline__ void csr_mid_body(uint32_t block, int c_begin, int c_
     }
 }
 
+// ---- short rows -----------------------------------------------------------------------------
+// A group owns a row, or grid.rows_per_group consecutive ones on matrices whose launch would not fit otherwise (the WIDE forms
+// serve those: the loop costs the plain ones registers).  Every lane
+// reads the row's extent itself (one request per group): handing it round between the loads of the chain, and a row's route
+// on plans that have no matrix-path windows, cost 2.5 to 10 % of a launch (communities, bf16, 64 columns: 29.1 -> 26.0 us;
+// power law, fp32, 128 columns: 119.5 -> 116.4 us).
+template <class G>
+__device__ __forceinline__ void csr_short_row(uint32_t i, int lig, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a)
+{
+    const int32_t row = wk.row_list ? wk.row_list[i] : (int32_t)i;
+    int32_t s, e;
+    G::extent(a, row, s, e);
+    // rows owned by the matrix path or by the other tiers
+    if (!wk.row_list && ((wk.route && wk.route[row / kH] != 0) || e - s > wk.mid_row)) return;
+    if (G::skipped(wk, s, e)) return;
+    for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
+        G g;
+        g.init(a, c0, min(G::COLS, c_end - c0), lig);
+        float acc[G::N];
+        vzero(acc);
+        g.span(a, s, e, G::GROUP, lig, acc);
+        G::finish(acc);
+        g.store(a, wk.y_vec, row, c0, lig, acc);
+    }
+}
 template <class G>
 __device__ __forceinline__ void csr_short_body(uint32_t block, int c_begin, int c_end, const CsrWork& wk, const SpmmArgs& a)
 {
     const int lig = threadIdx.x % G::GROUP;
-    const uint32_t i0 = (block * (256 / G::GROUP) + threadIdx.x / G::GROUP) * wk.grid.rows_per_group;
-    if (i0 >= (uint32_t)wk.n_items) return;
-    const int nr = min(wk.grid.rows_per_group, wk.n_items - (int)i0);
-    int32_t my_row, my_s, my_e;
-    row_extents<G>(i0, lig, nr, wk, a, my_row, my_s, my_e);
-    for (int c0 = c_begin; c0 < c_end; c0 += G::COLS) {
-        G g;
-        g.init(a, c0, min(G::COLS, c_end - c0), lig);
-        walk_rows(g, a, lig, nr, my_row, my_s, my_e,
-                  [&](int32_t row, int, const float (&acc)[G::N]) { g.store(a, wk.y_vec, row, c0, lig, acc); });
+    const uint32_t group = block * (256 / G::GROUP) + threadIdx.x / G::GROUP;
+    if constexpr (G::MANY) {
+        const uint32_t i0 = group * wk.grid.rows_per_group, i1 = min(i0 + (uint32_t)wk.grid.rows_per_group, (uint32_t)wk.n_items);
+        for (uint32_t i = i0; i < i1; ++i) csr_short_row<G>(i, lig, c_begin, c_end, wk, a);
+    } else if (group < (uint32_t)wk.n_items) {
+        csr_short_row<G>(group, lig, c_begin, c_end, wk, a);
     }
 }
 
@@ -390,14 +363,22 @@ __device__ __forceinline__ void csr_short_fused_body(uint32_t block, const CsrWo
     if (b0 >= (uint32_t)wk.n_items) return;                               // whole workgroup past the end
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int gw = threadIdx.x / G::GROUP, lig = threadIdx.x % G::GROUP;
-    const int nr = b0 + gw < (uint32_t)wk.n_items ? 1 : 0;
-    int32_t my_row, my_s, my_e;
-    row_extents<G>(b0 + gw, lig, nr, wk, a, my_row, my_s, my_e);
-    if (lig == 0) rows_s[gw] = my_row;
+    int32_t row = -1, k = 0, e = 0;                             // (the fused launch has no list)
+    if (b0 + gw < (uint32_t)wk.n_items) {
+        row = (int32_t)(b0 + gw);
+        G::extent(a, row, k, e);
+        if ((wk.route && wk.route[row / kH] != 0) || e - k > wk.mid_row) row = -1;
+    }
+    if (lig == 0) rows_s[gw] = row;
     G g;
     g.init(a, 0, a.d, lig);
-    walk_rows(g, a, lig, nr, my_row, my_s, my_e,
-              [&](int32_t, int, const float (&acc)[G::N]) { g.store_f32(zt + gw * LDZ, lig, acc); });
+    if (row >= 0) {
+        float acc[G::N];
+        vzero(acc);
+        g.span(a, k, e, G::GROUP, lig, acc);
+        G::finish(acc);
+        g.store_f32(zt + gw * LDZ, lig, acc);
+    }
     __syncthreads();
     if (u.keep_z) store_tile_rows(zt, LDZ, rows_s, ROWS, a.d, a.Y, a.ldy, threadIdx.x, 256);
     const int tile = wave / WPT;
@@ -771,6 +752,7 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     }
     wk.grid = csr_grid(n_segs, wk.n_mid, wk.n_items, a.d, n_slices, slice_w, run, sh.group, tune().rpg >= 1 && tune().rpg <= sh.group ? tune().rpg : 1);
     if (wk.grid.blocks() <= 0) return hipSuccess;
+    if (wk.grid.rows_per_group > 1) sh.wide = true;
     if (wk.grid.n_slices > 1) {
         SpmmArgs t = a;
         t.d = wk.grid.slice_w;
@@ -842,7 +824,7 @@ __global__ __launch_bounds__(256) void k_probe_gather(const int32_t* __restrict_
     for (int64_t k0 = b; k0 < e; k0 += G::GROUP) {                // (a group past the end of the stream has b == e)
         const int64_t k = min(k0 + lig, e - 1);
         const int32_t c = min(max(index[k], 0), n_rows_x - 1);  // whatever the stream holds, the read stays inside X
-        g.batch(g.key(c), 1.f, (int)min((int64_t)G::GROUP, e - k0), acc);
+        g.batch(g.key(c), 1.f, (int)min((int64_t)G::GROUP, e - k0), acc, [] {});
     }
     float t[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
