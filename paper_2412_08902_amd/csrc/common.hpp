@@ -328,6 +328,9 @@ hipError_t launch_gemm_x(int64_t m, int32_t k, int32_t n, const void* X, int64_t
 int32_t gemm_tn_spans(int64_t n_rows, int32_t d_in, int32_t d);
 hipError_t launch_gemm_tn(int64_t n_rows, const float* X, int64_t ldx, int32_t d_in, const float* S, int64_t lds_,
                           int32_t d, float* dW, int64_t lddw, float* partial, hipStream_t s);
+bool gemm_grad_usable(int64_t n_rows, int64_t ldx, int32_t d_in, int32_t d);
+hipError_t launch_gemm_grad(int64_t n_rows, const float* X, int64_t ldx, int32_t d_in, const float* S, int64_t lds_, int32_t d,
+                            const float* W, int64_t ldw, float* dX, int64_t lddx, float* dW, int64_t lddw, float* partial, hipStream_t s);
 hipError_t launch_relu_mask(int64_t n, int32_t d, const float* G, int64_t ldg, const float* Yf, int64_t ldy, float* Gm,
                             int64_t ldo, hipStream_t s);
 hipError_t launch_transpose(int32_t rows, int32_t cols, const float* W, int64_t ldw, float* Wt, hipStream_t s);

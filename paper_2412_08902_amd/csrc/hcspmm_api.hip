@@ -1636,13 +1636,20 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
         a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
         a.X = G; a.ldx = g_ld; a.d = d_out; a.x_dtype = HCSPMM_F32; a.Y = S; a.ldy = d_out; a.relu = 0;
         if (d_dX) {
-            HC_HIP(launch_transpose(d_in, d_out, static_cast<const float*>(d_W), ldw, Wt, s));
             // as in hcspmm_aggregate_update; the wave-per-window kernel neither stores S for dW nor applies the mask
             UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
                                 : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
                                                                                  : update_place(plan, d_out, d_in, HCSPMM_F32, d_dW != nullptr);
             if (place == kUpdateInWindows && (d_dW || mask_dx_by_x)) place = kUpdateApart;
-            if (place != kUpdateApart && update_fusable(a)) {
+            if (place != kUpdateApart && !update_fusable(a)) place = kUpdateApart;
+            if (place == kUpdateApart && d_dW && !mask_dx_by_x && gemm_grad_usable(plan->n_rows, ldx, d_in, d_out)) {
+                if ((st = run_spmm(plan, a, s)) != HCSPMM_OK) return st;
+                HC_HIP(launch_gemm_grad(plan->n_rows, static_cast<const float*>(d_X), ldx, d_in, S, d_out, d_out, static_cast<const float*>(d_W), ldw,
+                                        static_cast<float*>(d_dX), lddx, static_cast<float*>(d_dW), lddw, part, s));
+                return HCSPMM_OK;
+            }
+            HC_HIP(launch_transpose(d_in, d_out, static_cast<const float*>(d_W), ldw, Wt, s));
+            if (place != kUpdateApart) {
                 // the next layer's activation mask (its output is this layer's input X) goes into the update's epilogue
                 const UpdateArgs u{Wt, d_in, d_in, static_cast<float*>(d_dX), lddx, 0, d_dW ? 1 : 0,
                                    mask_dx_by_x ? static_cast<const float*>(d_X) : nullptr, ldx};
