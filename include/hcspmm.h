@@ -398,7 +398,8 @@ size_t hcspmm_gcn_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t
  *           loads, or the graph is walked in column panels.
  *   before  X W goes to the workspace in fp32 and is aggregated from there, with the activation in the aggregation's
  *           epilogue.  Taken, before any of the above, where rows of X W touch fewer memory lines than rows of X (on
- *           graphs of some ten thousand rows and more, n_cols <= n_rows).
+ *           graphs of some ten thousand rows and more, n_cols <= n_rows).  X and W have to be finite for the forms to agree:
+ *           an infinity in W is one in the rows that are gathered here.
  * HCSPMM_UPDATE_FUSED takes the first form whenever widths and alignment allow it, HCSPMM_UPDATE_SPLIT the third.
  *
  *   d_X   device, n_cols x d_in, element type x_dtype (ldx >= d_in)

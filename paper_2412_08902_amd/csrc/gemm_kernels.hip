@@ -389,6 +389,165 @@ __global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, i
     }
 }
 
+// X W for bf16 X on the bf16 units (v_mfma_f32_16x16x32_bf16), at no loss: an fp32 value of W is the sum of three bf16 values
+// exactly (its 24 bits of significand cut in three), X is bf16 as it is, and products of two bf16 values are exact in fp32, where
+// they are summed -- those of the leading parts and all others each for themselves, added at the end.  Three products of K = 32
+// take 48 clocks of the matrix units where eight of K = 4 in fp32 take 256, and fewer sums are rounded: the error against 64 bits is a third
+// (relative 2-norm, 128 and 512 terms: normal X 2.0e-7 and 4.1e-7 -> 6.2e-8 and 1.2e-7, X >= 0 1.4e-7 and 2.9e-7 -> 5.0e-8 and
+// 9.3e-8).  169,343 x 128 x 64: 35 -> 27 us; bound by reading X and writing T and by the splitting from here on.  (The same with
+// fp32 X takes nine products and the splitting of X: 325 -> 337 us for 232,965 x 602 x 128, no gain.)
+//
+// A workgroup has four waves of 16*RT rows and 16*NT columns.  A slab of 32 rows of W goes through LDS, split, in the order in which a
+// lane (c, q) reads it: eight k = 8q .. 8q+7 of a column in 16 bytes.  An infinity in X or W takes a slab (for W: the rest of K)
+// to the fp32 units, with W put together again: infinity times the zero of a split would be NaN.
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// bf16 values hi | lo from the upper halves of two fp32 values
+__device__ __forceinline__ uint32_t upper_halves(float lo, float hi)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ __forceinline__ float truncated(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
+
+template <int NT, int RT>
+__global__ __launch_bounds__(256) void k_gemm_bf16(int64_t M, int32_t K, int32_t N, const unsigned short* __restrict__ X, int64_t ldx,
+                                                                    const float* __restrict__ Wm, int64_t ldw, GemmOut out)
+{
+    constexpr int COLS = 16 * NT, G4 = NT / 4, R = NT % 4, TASKS = (4 * COLS + 255) / 256;
+    __shared__ u32x4 slab[2][3][4][COLS];                           // W: part, group of eight k, column
+    __shared__ int w_inf;                                           // set by the first infinity of W, for the rest of K
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, c = lane & 15, q = lane >> 4;
+    const int n0 = (int)blockIdx.y * COLS;
+    const int64_t m0 = (int64_t)blockIdx.x * (64 * RT) + wave * 16 * RT;
+    const unsigned short* __restrict__ xp[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) xp[t] = X + min(m0 + 16 * t + c, M - 1) * ldx + 8 * q;
+    // this thread's tasks: eight k of a column of W
+    const float* __restrict__ wp[TASKS];
+    int wk[TASKS], pos[TASKS];
+    bool task[TASKS];
+#pragma unroll
+    for (int i = 0; i < TASKS; ++i) {
+        const int at = tid + 256 * i, col = at % COLS;
+        task[i] = at < 4 * COLS;
+        wk[i] = task[i] ? at / COLS : 0;
+        wp[i] = Wm + min(n0 + col, N - 1);
+        // column -> place: tile j of a group of four holds columns 4c + j, of the last R those R*c + j (see store_tile)
+        const int rest = col - 64 * G4;
+        pos[i] = rest < 0 ? (col / 64 * 4 + col % 4) * 16 + col % 64 / 4 : (4 * G4 + (R ? rest % (R ? R : 1) : 0)) * 16 + (R ? rest / (R ? R : 1) : 0);
+    }
+    float wn[TASKS][8];
+    u4_any xn[RT], xc[RT];
+    auto request_w = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < TASKS; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) wn[i][j] = wp[i][(int64_t)min(k0 + 8 * wk[i] + j, K - 1) * ldw];
+    };
+    auto request_x = [&](int k0, u4_any (&x)[RT]) {                  // eight values; what sticks out of the row is zero
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const unsigned short* __restrict__ p = xp[t] + k0;
+            if (k0 + 32 <= K) {
+                x[t] = *reinterpret_cast<const u4_any*>(p);
+            } else {
+                const int left = K - k0 - 8 * q;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[t][j] = (2 * j < left ? (uint32_t)p[2 * j] : 0u) | (2 * j + 1 < left ? (uint32_t)p[2 * j + 1] << 16 : 0u);
+            }
+        }
+    };
+    auto stage = [&](int k0, int buf) {
+        float most = 0.f;
+#pragma unroll
+        for (int i = 0; i < TASKS; ++i) {
+            if (4 * COLS % 256 != 0 && !task[i]) continue;
+            float r[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { r[j] = k0 + 8 * wk[i] + j < K ? wn[i][j] : 0.f; most = fmaxf(most, fabsf(r[j])); }
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                u32x4 part;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) part[j] = upper_halves(r[2 * j], r[2 * j + 1]);
+                slab[buf][p][wk[i]][pos[i]] = part;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) r[j] -= truncated(r[j]);
+                if (most > 3.402823466e38f)                         // an infinity has no remainder
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) r[j] = fabsf(wn[i][j]) > 3.402823466e38f ? 0.f : r[j];
+            }
+        }
+        if (most > 3.402823466e38f) w_inf = 1;
+    };
+    v4f_gemm acc[RT][NT], low[RT][NT];                                // products of W's leading parts; all others
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[t][j] = low[t][j] = (v4f_gemm){0.f, 0.f, 0.f, 0.f};
+    if (tid == 0) w_inf = 0;
+    request_w(0);
+    request_x(0, xc);
+    __syncthreads();
+    stage(0, 0);
+    __syncthreads();
+    int buf = 0;
+    for (int k0 = 0; k0 < K; k0 += 32) {
+        const int k1 = k0 + 32;
+        if (k1 < K) { request_w(k1); request_x(k1, xn); }
+        u16x2 top = {0, 0};                                         // largest magnitudes, as bit patterns
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, xc[t][j] & 0x7fff7fffu));
+        if (__any(max(top.x, top.y) >= 0x7f80) || w_inf) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll 1
+                for (int i = 0; i < 8; ++i) {
+                    float w = 0.f;
+#pragma unroll
+                    for (int p = 2; p >= 0; --p) {
+                        const uint32_t b = slab[buf][p][q][j * 16 + c][i / 2];
+                        w += __uint_as_float((i & 1) ? b & 0xffff0000u : b << 16);
+                    }
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) {
+                        const uint32_t x = xc[t][i / 2];
+                        acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float((i & 1) ? x & 0xffff0000u : x << 16), w, acc[t][j], 0, 0, 0);
+                    }
+                }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int p = 2; p >= 0; --p) {
+                    const bf16x8 b = __builtin_bit_cast(bf16x8, slab[buf][p][q][j * 16 + c]);
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) {
+                        v4f_gemm& to = p ? low[t][j] : acc[t][j];
+                        to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xc[t]), b, to, 0, 0, 0);
+                    }
+                }
+        }
+        buf ^= 1;
+        if (k1 < K) {
+            stage(k1, buf);                                         // (the readers of this buffer met the last barrier)
+#pragma unroll
+            for (int t = 0; t < RT; ++t) xc[t] = xn[t];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[t][j] += low[t][j];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) store_tile<false>(acc[t], m0 + 16 * t, n0, M, N, out, c, q);
+}
+
 hipError_t launch_gemm_f32(int64_t m, int32_t k, int32_t n, const float* X, int64_t ldx, const float* W, int64_t ldw,
                            float* T, int64_t ldt, const float* mask, int64_t ldm, hipStream_t s)
 {
@@ -404,6 +563,24 @@ static hipError_t launch_gemm_of(int64_t m, int32_t k, int32_t n, const XElem<XK
     if (t_dtype != HCSPMM_F32 && t_dtype != HCSPMM_BF16 && t_dtype != HCSPMM_F16) return hipErrorInvalidValue;
     const GemmOut out{static_cast<float*>(T), ldt, mask, ldm, t_dtype, relu,
                       n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0};
+    // bf16 X on the bf16 units: groups of up to 64 columns, equally wide, 32 rows to a wave where they leave it the registers.
+    // Fp32 units / bf16 units, us, with an aggregation of one non-zero per row behind it: 169,343 x 128 x 64: 51 / 43, x 256 x 96:
+    // 102 / 85, x 256 x 16: 42 / 38, x 512 x 128: 228 / 180; 1 M x 128 x 64: 292 / 275, x 64 x 16: 95 / 86; but 40,000 x 256 x 16: 15.4 /
+    // 17.0, 9,000 x 256 x 96: 17.6 / 19.7 (too few rows for the splitting of W), and 1 M x 200 x 70: 568 / 622 (columns of padding).
+    if constexpr (XK == 1) {
+        const int64_t tiles = ((int64_t)n + 15) / 16, groups = (tiles + 3) / 4, nt = (tiles + groups - 1) / groups;
+        if (m >= 65536 && k >= 64 && 8 * (int64_t)n >= 7 * groups * nt * 16) {
+            const int64_t rows = nt > 3 ? 64 : 128;
+            const dim3 grid((unsigned)((m + rows - 1) / rows), (unsigned)groups);
+#define HC_BF16(NT, RT) hipLaunchKernelGGL((k_gemm_bf16<NT, RT>), grid, dim3(256), 0, s, m, k, n, X, ldx, W, ldw, out)
+            if (nt == 4) HC_BF16(4, 1);
+            else if (nt == 3) HC_BF16(3, 2);
+            else if (nt == 2) HC_BF16(2, 2);
+            else HC_BF16(1, 2);
+#undef HC_BF16
+            return hipGetLastError();
+        }
+    }
     // W in registers where it is small and the product streams: 2.4 M x 64 x 32: 199 -> 170 us, 2.4 M x 16 x 16: 109 -> 58 us,
     // 169,343 x 128 x 64: 41 -> 37 us.  Wider products are bound by the matrix units and level or behind (400,000 x 128 x 96:
     // 111 -> 123 us), short ones spend more on bringing all of W in first (20,000 x 128 x 64: 8.0 -> 9.7 us).

@@ -62,7 +62,10 @@ CASES = [(9000, 12, 32, 16, "f32", False),                      # one line eithe
          (9000, 12, 160, 31, "f16", True), (9000, 12, 254, 62, "bf16", True), (9000, 12, 257, 47, "f16", True),
          # ... and with W in registers (from 65,536 rows on, or k n <= 1024)
          (65537, 2, 128, 64, "f16", True), (65537, 2, 100, 20, "bf16", True), (65537, 2, 84, 24, "bf16", True),
-         (9000, 12, 80, 4, "bf16", True), (9000, 12, 68, 15, "f16", True)]
+         (9000, 12, 80, 4, "bf16", True), (9000, 12, 68, 15, "f16", True),
+         # bf16 X on the bf16 units (from 65,536 rows on): K around its slabs of 32, one to four column tiles, two groups of them
+         (65537, 2, 128, 64, "bf16", True), (65600, 2, 98, 47, "bf16", True), (65536, 2, 65, 16, "bf16", True),
+         (65541, 2, 127, 31, "bf16", True), (65536, 2, 256, 95, "bf16", True), (65537, 2, 322, 128, "bf16", True)]
 
 
 @pytest.mark.parametrize("n_rows,degree,d_in,d_out,kind,taken", CASES)
@@ -86,3 +89,34 @@ def test_calls_that_keep_their_order(kind, n_rows, n_cols, x_pad, x_off, options
     Y, first, ref, bound = run(g, X, W, kind, x_pad=x_pad, x_off=x_off, route_mode=1, **options)
     assert first == (n_cols == 1000)                            # the last two are taken
     assert_close(Y, ref, bound, 1e-5)
+
+
+def test_infinities_and_nan_in_bf16_products():
+    """Y = I (X W): an infinity meets the zero remainders of split values nowhere, a NaN stays one.  (Sixteen entries of a
+    sixteenth to a row of I: the aggregation multiplies a row's last X row with zeros where its last batch is not full.)"""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    n, d_in, d_out = 65600, 130, 60
+    dev = "cuda"
+    ip = torch.arange(0, 16 * n + 1, 16, dtype=torch.int32, device=dev)
+    ci, va = torch.arange(n, dtype=torch.int32, device=dev).repeat_interleave(16), torch.full((16 * n,), 1 / 16, device=dev)
+    torch.manual_seed(3)
+    X, W = torch.randn(n, d_in).bfloat16(), torch.randn(d_in, d_out)
+    W[7, 3] = 0.5                                               # a value whose remainders are zero
+    X[5, 7], X[77, 129], X[65599, 0], X[200, 64] = float("inf"), float("-inf"), float("nan"), torch.finfo(torch.bfloat16).max
+    for w_at in (None, (40, 11), (129, 59)):
+        if w_at:
+            W[w_at] = float("inf") if w_at[0] == 40 else torch.finfo(torch.float32).max
+        plan = hc.hcspmm_prepare(n, n, ip, ci, va, route_mode=1, d_hint=d_in, mfma_dtype=1)
+        ws = torch.empty(hc.hcspmm_aggregate_update_workspace_bytes(plan, d_in, d_out), dtype=torch.uint8, device=dev)
+        Y = torch.zeros(n, d_out, device=dev)
+        hc.hcspmm_aggregate_update(plan, X.cuda(), W.cuda(), Y, ws, apply_relu=False)
+        torch.cuda.synchronize()
+        plan.destroy()
+        got, want = Y.cpu().double(), X.double() @ W.double()
+        want = want.float().double()                            # (what overflows fp32 is an infinity)
+        assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf())
+        assert torch.equal(got[want.isinf()], want[want.isinf()])
+        fin = want.isfinite()
+        bound = (X.double().abs() @ W.double().abs())[fin]
+        assert torch.all((got[fin] - want[fin]).abs() <= 1e-5 * bound)
