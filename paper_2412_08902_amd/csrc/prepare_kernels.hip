@@ -409,7 +409,8 @@ hipError_t launch_unique_big(int32_t n_big, const int32_t* big_list, int32_t n_r
 // adds up groups and the tiles of its own group: 1.02 G rows are 1 M tiles and 3,900 groups.  The totals go straight into a
 // page of host memory.
 //   k_pre_validate   row offsets; non-zeros per window; windows by size class
-//   k_pre_count*     distinct columns per window by LDS hash sets (bitmap passes beyond their capacity), range of the columns
+//   k_pre_count*     distinct columns per window by LDS hash sets (bitmap passes beyond their capacity), range of the columns;
+//                    one launch for few windows, one per size class for many
 //   k_pre_sorted, k_pre_sample   where they decide something: whether rows ascend, how much neighbouring rows share
 //   k_pre_select     selection per window, sums per tile
 //   k_pre_rows       launch guard, route and list offset per window, row classes, sums per tile
@@ -609,25 +610,24 @@ __global__ __launch_bounds__(256) void k_pre_sorted(Prep p)
 
 // Inserts the window's column ids into an open-addressing set of at least 2n entries (linear probing, empty = -1; an id
 // outside the matrix is reported and left out) and counts the insertions that found an empty slot.  The set is never more
-// than half full, so every probe sequence ends.
+// than half full, so every probe sequence ends.  NT threads count one window (tid: the caller's place among them); several
+// such groups of a workgroup may each count their own, one that has none calls with take = false (the barriers are the
+// workgroup's).
 template <int NT>
-__device__ inline void count_distinct(int32_t w, const Prep& p, int32_t* table, int* smem)
+__device__ inline void count_distinct(int32_t w, const Prep& p, int32_t* table, int* smem /* NT / 64 */, int tid, bool take = true)
 {
-    int32_t s, e;
-    window_span(w, p.n_rows, p.rowptr, s, e);
+    int32_t s = 0, e = 0;
+    if (take) window_span(w, p.n_rows, p.rowptr, s, e);
     const int32_t n = e - s;
-    if (n == 0) {
-        if (threadIdx.x == 0) p.ncols[w] = 0;
-        return;
-    }
     int T = NT;                                   // power of two, at least twice the entries
     while (T < 2 * n) T <<= 1;
     const uint32_t mask = (uint32_t)T - 1;
-    for (int i = threadIdx.x; i < T; i += NT) table[i] = -1;
+    if (n > 0)
+        for (int i = tid; i < T; i += NT) table[i] = -1;
     __syncthreads();
     int cnt = 0;
     bool bad = false;
-    for (int32_t k0 = s + threadIdx.x; k0 < e; k0 += 4 * NT) {  // (four loads in flight: a window is little else than their latency)
+    for (int32_t k0 = s + tid; k0 < e; k0 += 4 * NT) {          // (four loads in flight: a window is little else than their latency)
         int32_t col[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) col[j] = p.colind[min(k0 + j * NT, e - 1)];
@@ -646,9 +646,53 @@ __device__ inline void count_distinct(int32_t w, const Prep& p, int32_t* table, 
         }
     }
     if (bad) atomicOr(p.ctl, 8);
-    int total;
-    (void)block_exclusive_scan<NT>(cnt, &total, smem);
-    if (threadIdx.x == 0) p.ncols[w] = total;
+    cnt = wave_sum(cnt);
+    if ((tid & 63) == 0) smem[tid >> 6] = cnt;
+    __syncthreads();
+    if (tid != 0 || !take) return;
+    int total = 0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) total += smem[i];
+    p.ncols[w] = total;
+}
+
+// A window of any size, counted by the workgroup's 1024 threads: with a hash set, and beyond half of the table's entries with
+// a bitmap of 32 * WORDS columns a pass.
+template <int WORDS>
+__device__ inline void count_window(int32_t w, const Prep& p, int32_t* table /* WORDS */, int* smem /* 16 */)
+{
+    int32_t s, e;
+    window_span(w, p.n_rows, p.rowptr, s, e);
+    if (e - s <= WORDS / 2) {
+        count_distinct<1024>(w, p, table, smem, threadIdx.x);
+        return;
+    }
+    uint32_t* __restrict__ bm = reinterpret_cast<uint32_t*>(table);
+    constexpr int kBits = WORDS * 32;
+    int cnt = 0;
+    bool bad = false;
+    for (int64_t base = 0; base < p.n_cols; base += kBits) {
+        for (int j = threadIdx.x; j < WORDS; j += 1024) bm[j] = 0u;
+        __syncthreads();
+        for (int32_t k = s + threadIdx.x; k < e; k += 1024) {
+            const int32_t col = p.colind[k];
+            bad |= col < 0 || col >= p.n_cols;
+            const int64_t c = (int64_t)col - base;
+            if (c >= 0 && c < kBits) atomicOr(&bm[c >> 5], 1u << (c & 31));
+        }
+        __syncthreads();
+        for (int j = threadIdx.x; j < WORDS; j += 1024) cnt += __popc(bm[j]);
+        __syncthreads();
+    }
+    if (bad) atomicOr(p.ctl, 8);
+    cnt = wave_sum(cnt);
+    if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = cnt;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int total = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) total += smem[i];
+    p.ncols[w] = total;
 }
 
 // windows of up to kCountTinyCap non-zeros, one workgroup each: all windows, or -- after a structural change -- the
@@ -656,7 +700,7 @@ __device__ inline void count_distinct(int32_t w, const Prep& p, int32_t* table, 
 __global__ __launch_bounds__(256) void k_pre_count(Prep p)
 {
     __shared__ int32_t table[2 * kCountTinyCap];
-    __shared__ int smem[256 / 64 + 1];
+    __shared__ int smem[256 / 64];
     if (*p.ctl & 7) return;
     const int32_t w = p.touched ? p.touched[blockIdx.x] : (int32_t)blockIdx.x;
     const int32_t n = p.nnzw[w];
@@ -668,17 +712,17 @@ __global__ __launch_bounds__(256) void k_pre_count(Prep p)
         }
         return;
     }
-    count_distinct<256>(w, p, table, smem);
+    count_distinct<256>(w, p, table, smem, threadIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_pre_count_1k(Prep p)
 {
     __shared__ int32_t table[2 * kUniqueSmallCap];
-    __shared__ int smem[256 / 64 + 1];
+    __shared__ int smem[256 / 64];
     if (*p.ctl & 7) return;
     const int32_t n = p.ctl[3];
     for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
-        count_distinct<256>(p.count_1k[i], p, table, smem);
+        count_distinct<256>(p.count_1k[i], p, table, smem, threadIdx.x);
         __syncthreads();
     }
 }
@@ -686,41 +730,48 @@ __global__ __launch_bounds__(256) void k_pre_count_1k(Prep p)
 __global__ __launch_bounds__(1024) void k_pre_count_big(Prep p)
 {
     __shared__ int32_t table[2 * kCountMidCap];
-    __shared__ int smem[1024 / 64 + 1];
-    static_assert(2 * kCountMidCap >= kBitmapWords, "the bitmap shares the hash set's memory");
+    __shared__ int smem[1024 / 64];
     if (*p.ctl & 7) return;
     const int32_t n_huge = *p.n_count_huge, n_mid = *p.n_count_mid, n_1k = p.big_takes_1k ? p.ctl[3] : 0;
     for (int32_t i = blockIdx.x; i < n_huge + n_mid + n_1k; i += gridDim.x) {
-        if (i >= n_huge) {
-            count_distinct<1024>(i < n_huge + n_mid ? p.count_mid[i - n_huge] : p.count_1k[i - n_huge - n_mid], p, table, smem);
-        } else {
-            // more entries than the set holds: a bitmap over 2^20 columns per pass
-            uint32_t* __restrict__ bm = reinterpret_cast<uint32_t*>(table);
-            constexpr int kBits = kBitmapWords * 32;
-            const int32_t w = p.count_huge[i];
-            int32_t s, e;
-            window_span(w, p.n_rows, p.rowptr, s, e);
-            int cnt = 0;
-            bool bad = false;
-            for (int64_t base = 0; base < p.n_cols; base += kBits) {
-                for (int j = threadIdx.x; j < kBitmapWords; j += 1024) bm[j] = 0u;
-                __syncthreads();
-                for (int32_t k = s + threadIdx.x; k < e; k += 1024) {
-                    const int32_t col = p.colind[k];
-                    bad |= col < 0 || col >= p.n_cols;
-                    const int64_t c = (int64_t)col - base;
-                    if (c >= 0 && c < kBits) atomicOr(&bm[c >> 5], 1u << (c & 31));
-                }
-                __syncthreads();
-                for (int j = threadIdx.x; j < kBitmapWords; j += 1024) cnt += __popc(bm[j]);
-                __syncthreads();
-            }
-            if (bad) atomicOr(p.ctl, 8);
-            int total;
-            (void)block_exclusive_scan<1024>(cnt, &total, smem);
-            if (threadIdx.x == 0) p.ncols[w] = total;
-        }
+        count_window<2 * kCountMidCap>(i < n_huge ? p.count_huge[i] : i < n_huge + n_mid ? p.count_mid[i - n_huge] : p.count_1k[i - n_huge - n_mid], p, table, smem);
         __syncthreads();
+    }
+}
+
+// Few windows to count (all of a small matrix, or the touched ones): one launch for all sizes, where by class the larger
+// windows wait for the small ones' launch and a few workgroups walk their list.  512 workgroups take every 512th window, four
+// at most (neighbouring windows, often alike in size, go to different ones): those of up to kCountTinyCap non-zeros side by
+// side on 256 threads each, the others after them, one by one, on all 1024.  Bound by its longest chain of reads and by
+// launches.  The table is half of k_pre_count_big's, so that two workgroups fit a CU and 2,048 windows run at once (one to a
+// CU: uniform rows lose, 48.4 us by class, 52.4 us here for 32,000 of 60); the bitmap of larger windows then takes two passes
+// for a matrix of 2^20 columns, and wider ones stay with the classes.  Whole preparations, by class / here: power laws of
+// 8,000 rows of 60, 32,000 of 15 and 32,000 of 60: 51.4 / 45.8, 52.0 / 47.4 and 73.0 / 62.5 us, 16,934 of 14 with their
+// product 71.7 / 68.1 us; uniform rows level up to 2,048 windows.  4,000 windows of 64 or 960 non-zeros lose (43.6 / 45.1 and
+// 53.7 / 56.0 us), so the line is at the windows that run at once.
+constexpr int kFewWords = 16384, kFewWindows = 2048, kFewCols = 2 * 32 * kFewWords;
+static_assert(4 * 2 * kCountTinyCap <= kFewWords, "four sets share the table");
+__global__ __launch_bounds__(1024) void k_pre_count_few(Prep p, int32_t n_count)
+{
+    __shared__ int32_t table[kFewWords];
+    __shared__ int smem[1024 / 64];
+    if (*p.ctl & 7) return;
+    int32_t w[4], n[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int32_t i = (int32_t)(blockIdx.x + j * gridDim.x);
+        w[j] = i >= n_count ? -1 : p.touched ? p.touched[i] : i;
+        n[j] = w[j] < 0 ? 0 : p.nnzw[w[j]];
+    }
+    const int group = threadIdx.x >> 8;
+    const int32_t own = group == 0 ? w[0] : group == 1 ? w[1] : group == 2 ? w[2] : w[3];
+    const int32_t len = group == 0 ? n[0] : group == 1 ? n[1] : group == 2 ? n[2] : n[3];
+    count_distinct<256>(own, p, table + group * 2 * kCountTinyCap, smem + group * 4, threadIdx.x & 255, own >= 0 && len <= kCountTinyCap);
+#pragma unroll 1
+    for (int j = 0; j < 4; ++j) {
+        if ((j == 0 ? n[0] : j == 1 ? n[1] : j == 2 ? n[2] : n[3]) <= kCountTinyCap) continue;
+        __syncthreads();
+        count_window<kFewWords>(j == 0 ? w[0] : j == 1 ? w[1] : j == 2 ? w[2] : w[3], p, table, smem);
     }
 }
 
@@ -1026,15 +1077,20 @@ hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
     hipLaunchKernelGGL(k_pre_validate, dim3((unsigned)(((int64_t)p.n_rows + 1 + 255) / 256)), dim3(256), 0, s, p);
     if (p.features && p.W > 0) {
         const int64_t n_count = p.touched ? n_touched : p.W;
-        if (n_count > 0) hipLaunchKernelGGL(k_pre_count, dim3((unsigned)n_count), dim3(256), 0, s, p);
-        // windows beyond the small set's capacity; how many there are only the device knows, so the grids are bounded by
-        // what the matrix can hold and walk the lists
-        auto most = [&](int64_t cap, int64_t limit) { return (unsigned)std::min<int64_t>({n_count, p.nnz / (cap + 1), limit}); };
-        // (few windows to count: one launch serves both classes)
-        const int64_t cap_big = p.big_takes_1k ? kCountTinyCap : kUniqueSmallCap;
-        if (!p.big_takes_1k && most(kCountTinyCap, 2048) > 0)
-            hipLaunchKernelGGL(k_pre_count_1k, dim3(most(kCountTinyCap, 2048)), dim3(256), 0, s, p);
-        if (most(cap_big, 256) > 0) hipLaunchKernelGGL(k_pre_count_big, dim3(most(cap_big, 256)), dim3(1024), 0, s, p);
+        if (n_count <= kFewWindows && p.n_cols <= kFewCols) {
+            if (n_count > 0)
+                hipLaunchKernelGGL(k_pre_count_few, dim3((unsigned)std::min<int64_t>(n_count, kFewWindows / 4)), dim3(1024), 0, s, p, (int32_t)n_count);
+        } else {
+            if (n_count > 0) hipLaunchKernelGGL(k_pre_count, dim3((unsigned)n_count), dim3(256), 0, s, p);
+            // windows beyond the small set's capacity; how many there are only the device knows, so the grids are bounded by
+            // what the matrix can hold and walk the lists
+            auto most = [&](int64_t cap, int64_t limit) { return (unsigned)std::min<int64_t>({n_count, p.nnz / (cap + 1), limit}); };
+            // (up to kBigTakes1kWindows windows to count: one launch serves both larger classes)
+            const int64_t cap_big = p.big_takes_1k ? kCountTinyCap : kUniqueSmallCap;
+            if (!p.big_takes_1k && most(kCountTinyCap, 2048) > 0)
+                hipLaunchKernelGGL(k_pre_count_1k, dim3(most(kCountTinyCap, 2048)), dim3(256), 0, s, p);
+            if (most(cap_big, 256) > 0) hipLaunchKernelGGL(k_pre_count_big, dim3(most(cap_big, 256)), dim3(1024), 0, s, p);
+        }
     } else if (p.nnz > 0) {
         int64_t blocks = (p.nnz + 256 * 8 - 1) / (256 * 8);
         if (blocks > 65536) blocks = 65536;

@@ -189,3 +189,54 @@ def test_plan_info_tells_windows_that_the_scalar_path_has_taken_over():
         assert runs or info["n_mfma_small"] + info["n_mfma_big"] == 0
         assert hc.hcspmm_plan_export(plan)["route"].sum() == info["n_mfma_windows"]
         plan.destroy()
+
+
+def mixed_sizes(n, seed, per_class=3, n_cols=3000):
+    """Mostly small windows; some around every counting class, next to each other and far apart; rows of every tier."""
+    rng = np.random.default_rng(seed)
+    lengths = rng.integers(0, 7, n)
+    windows = rng.permutation(n // 16)
+    sizes = [1024, 1025, 4096, 4097, 8192, 8193, 16384, 16385]
+    for i, size in enumerate(np.repeat(sizes, per_class)[: windows.shape[0] // 2]):
+        w = windows[i] if i % 2 else min(i, n // 16 - 1)
+        lengths[16 * w: 16 * w + 15] = size // 15
+        lengths[16 * w + 15] = size - 15 * (size // 15)
+    return ragged(lengths, n_cols, seed)
+
+
+# one, two and four windows to a workgroup, whole and ragged; the last matrices whose windows one launch counts and the first beyond, by rows and
+# by columns (one pass of the bitmap, two, and the classes)
+@pytest.mark.parametrize("n,n_cols", [(2000, 3000), (16 * 513, 3000), (16 * 1021, 3000), (2048 * 16, 3000), (2048 * 16 + 1, 3000),
+                                      (3000, 1 << 19), (3000, (1 << 19) + 1), (3000, 1 << 20), (3000, (1 << 20) + 1)])
+@pytest.mark.parametrize("mode", [0, 3])
+def test_one_launch_counts_few_windows_of_every_size(n, n_cols, mode):
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    g = mixed_sizes(n, n, n_cols=n_cols)
+    coef = [1, 300, -328]                                         # (windows of up to some 47 columns on the matrix path)
+    check_plan(g, mode, sel_coef=coef)
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *device_graph(g), route_mode=mode, sel_coef=coef)
+    X = np.random.default_rng(n).standard_normal((g.n_cols, 8)).astype(np.float32)
+    Y = torch.full((n, 8), float("nan"), device="cuda")
+    hc.hcspmm_spmm(plan, torch.from_numpy(X).cuda(), Y)
+    ref, bound = (oracle.spmm(g.rowptr, g.colind, g.vals, X, use_abs=b) for b in (False, True))
+    assert_close(Y.cpu().numpy().astype(np.float64), ref, bound, 1e-5, "spmm")
+
+
+@pytest.mark.parametrize("n,every", [(30_000, 16), (70_000, 16), (70_000, 400)])
+def test_updates_that_touch_every_size_class(n, every):
+    """Windows of every counting class among the touched ones, counted by one launch (up to 2,048) or by class."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    g = mixed_sizes(n, n, 4)
+    rows = np.flatnonzero((np.arange(n) % every == 0) | (np.diff(g.rowptr) > 60))
+    rows = rows[np.diff(g.rowptr)[rows] > 0].astype(np.int32)
+    col2 = g.colind.copy()
+    last = g.rowptr[rows + 1] - 1
+    col2[last] = 3000 + rows % 5                                  # (rows stay ascending)
+    rp, c1, c2, va = (torch.from_numpy(a).cuda() for a in (g.rowptr, g.colind, col2, g.vals))
+    plan = hc.hcspmm_prepare(n, 3005, rp, c1, va)
+    hc.hcspmm_plan_update(plan, rp, c2, va, rows)
+    a, b = hc.hcspmm_plan_export(plan), hc.hcspmm_plan_export(hc.hcspmm_prepare(n, 3005, rp, c2, va))
+    for k in KEYS:
+        assert np.array_equal(a[k], b[k]), k
