@@ -352,6 +352,11 @@ hcspmm_status hcspmm_spmm_timed(const hcspmm_plan* plan, const void* d_X, int64_
  * says the same of update-before-aggregate), and at the benchmark's layer size
  * the call costs what the two stages cost separately (hcspmm_gcn_layer_ex can
  * store the intermediate in 16 bits, which halves the gather bytes).
+ * Where rows of X touch fewer memory lines than rows of X W would (d_out > d_in),
+ * update_fusion is HCSPMM_UPDATE_AUTO and n_rows * d_in <= n_cols * d_out, the same
+ * sums are associated as act((A X) W), in one of hcspmm_aggregate_update's forms;
+ * the workspace then holds A X or nothing of use.  X, W and the values have to be
+ * finite for the two orders to agree.
  *
  *   d_X   device, n_cols x d_in fp32 (ldx >= d_in);  d_W  device, d_in x d_out fp32 (ldw >= d_out)
  *   d_Y   device, n_rows x d_out fp32 (ldy >= d_out)

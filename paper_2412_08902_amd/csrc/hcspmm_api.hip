@@ -1411,6 +1411,10 @@ hcspmm_status hcspmm_gemm_f32(int64_t m, int32_t k, int32_t n, const float* d_X,
     return HCSPMM_OK;
 }
 
+static bool aggregate_first(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, size_t workspace);
+static hcspmm_status aggregate_then_update(const hcspmm_plan* plan, const SpmmArgs& a, const float* W, int64_t ldw, int32_t d_out, void* Y,
+                                           int64_t ldy, int32_t y_dtype, int32_t apply_relu, hipStream_t s);
+
 hcspmm_status hcspmm_gcn_layer(const hcspmm_plan* plan, const void* d_X, int64_t ldx, int32_t d_in, const void* d_W,
                                int64_t ldw, int32_t d_out, void* d_Y, int64_t ldy, int32_t apply_relu,
                                void* d_workspace, size_t workspace_bytes, void* stream)
@@ -1443,6 +1447,12 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
     if (t_dtype != HCSPMM_F32 && plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) {
         set_error("the matrix path with 16-bit T needs d_out a multiple of 4 and 16-byte aligned Y rows");
         return HCSPMM_EUNSUPPORTED;
+    }
+    if (t_dtype == HCSPMM_F32) {
+        SpmmArgs z = a;
+        z.X = d_X; z.ldx = ldx; z.d = d_in; z.Y = static_cast<float*>(d_workspace); z.ldy = d_in; z.relu = 0; z.y_dtype = HCSPMM_F32;
+        if (aggregate_first(plan, z, d_out, need))
+            return aggregate_then_update(plan, z, static_cast<const float*>(d_W), ldw, d_out, d_Y, ldy, y_dtype, apply_relu, s);
     }
     HC_HIP(launch_gemm_f32_out(plan->n_cols, d_in, d_out, static_cast<const float*>(d_X), ldx,
                                static_cast<const float*>(d_W), ldw, d_workspace, d_out, t_dtype, 0, s));
@@ -1526,6 +1536,41 @@ static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_
     return !f32 && !windows && many && 2 * a.d >= 128 && after <= before && plan->n_panels < 2 && apart;
 }
 
+// Y = act((A X) W) in that order, A X (a.Y, where it reaches memory) in the caller's workspace.
+static hcspmm_status aggregate_then_update(const hcspmm_plan* plan, const SpmmArgs& a, const float* W, int64_t ldw, int32_t d_out, void* Y,
+                                           int64_t ldy, int32_t y_dtype, int32_t apply_relu, hipStream_t s)
+{
+    const UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
+                              : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
+                                                                               : update_place(plan, a.d, d_out, a.x_dtype, false);
+    if (place != kUpdateApart && update_fusable(a)) {
+        const UpdateArgs u{W, ldw, d_out, static_cast<float*>(Y), ldy, apply_relu ? 1 : 0, 0, nullptr, 0, y_dtype};
+        return run_spmm(plan, a, s, nullptr, &u, place == kUpdateInWindows);
+    }
+    const hcspmm_status st = run_spmm(plan, a, s);
+    if (st != HCSPMM_OK) return st;
+    HC_HIP(launch_gemm_f32_out(plan->n_rows, a.d, d_out, a.Y, a.ldy, W, ldw, Y, ldy, y_dtype, apply_relu ? 1 : 0, s));
+    return HCSPMM_OK;
+}
+
+// Whether the layer Y = act(A (X W)) is computed as act((A X) W), T = X W being asked for in fp32: the same trade as in
+// update_before the other way.  Where W makes rows longer, rows of X are what a gather should read, and the aggregated rows' trip
+// through memory is shorter than that of X W (or stays on chip, see update_place).  X W first / this order, fp32, us: power laws
+// of 615,315 rows of 97, 32 -> 144 columns: 5923 / 1510; 66,756 of 161, 40 -> 188: 863 / 172; 58,920 of 40, 105 -> 176: 202 / 142;
+// 371,268 of 6, 56 -> 112: 227 / 163; 2,323 of 18, 96 -> 173: 21.9 / 19.4; communities, 114,816 of 58, 112 -> 160: 223 / 140.  What
+// counts is the lines that a gathered row touches, as there (167 -> 176, 299,968 in communities, one more line: 565 / 620); as
+// many lines pay where the rows are clearly shorter and read in whole vectors (142,285 of 16, 8 -> 16: 35.0 / 27.0; but 75,504 of 63,
+// 48 -> 64: 96 / 98, 14 -> 16, 1 M of 13: 207 / 237).  Smallest gain: one launch less.
+static bool aggregate_first(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, size_t workspace)
+{
+    if (plan->opt.update_fusion != HCSPMM_UPDATE_AUTO || plan->n_rows == 0) return false;
+    if ((size_t)plan->n_rows * a.d * sizeof(float) > workspace) return false;
+    if (plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) return false;
+    const double first = row_lines(a.X, a.ldx, a.d, 4), after = row_lines(nullptr, d_out, d_out, 4);
+    const bool vectors = a.d % 4 == 0 && a.ldx % 4 == 0 && (uintptr_t)a.X % 16 == 0;
+    return first <= 0.92 * after || (vectors && 3 * (int64_t)a.d <= 2 * (int64_t)d_out && first <= after);
+}
+
 size_t hcspmm_aggregate_update_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)
 {
     (void)d_out;
@@ -1562,18 +1607,7 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
         a.Y = static_cast<float*>(d_Y); a.ldy = ldy; a.y_dtype = y_dtype; a.relu = apply_relu ? 1 : 0;
         return run_spmm(plan, a, s, nullptr, nullptr, false, nullptr, true);
     }
-    const UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
-                              : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
-                                                                               : update_place(plan, d_in, d_out, x_dtype, false);
-    if (place != kUpdateApart && update_fusable(a)) {
-        const UpdateArgs u{static_cast<const float*>(d_W), ldw, d_out, static_cast<float*>(d_Y), ldy, apply_relu ? 1 : 0, 0,
-                           nullptr, 0, y_dtype};
-        return run_spmm(plan, a, s, nullptr, &u, place == kUpdateInWindows);
-    }
-    if ((st = run_spmm(plan, a, s)) != HCSPMM_OK) return st;
-    HC_HIP(launch_gemm_f32_out(plan->n_rows, d_in, d_out, Z, d_in, static_cast<const float*>(d_W), ldw, d_Y, ldy, y_dtype,
-                               apply_relu ? 1 : 0, s));
-    return HCSPMM_OK;
+    return aggregate_then_update(plan, a, static_cast<const float*>(d_W), ldw, d_out, d_Y, ldy, y_dtype, apply_relu, s);
 }
 
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
