@@ -1509,16 +1509,17 @@ static double row_lines(const void* base, int64_t ld, int32_t w, int es)
 // Whether Y = act((A X) W) is computed as act(A (X W)): the same sums in fp32, associated the other way.  Where W makes rows
 // shorter the gather, which is most of the call, then reads rows of d_out instead of d_in columns, and one trip of the rows
 // through memory (X in, X W out) takes the place of the aggregated rows' (out and in again).  In this order / X W first, us:
-// 169,343 rows of 14, fp32: 64 -> 32 columns 85 / 51, 128 -> 64 165 / 102, 256 -> 128 380 / 232; 400,000 of 40, 128 -> 64: 975 /
+// 169,343 rows of 14, fp32: 64 -> 32 columns 85 / 51, 128 -> 64 144 / 93, 256 -> 128 380 / 232; 400,000 of 40, 128 -> 64: 975 /
 // 498; 1 M of 60 (in one pass with the product): 3825 / 2274; 131,072 in communities, 128 -> 64: 96 / 64.  X W is held in fp32, so
-// that 16-bit rows have to become half as long for the same bytes: 169,343 of 14, bf16, 128 -> 64: 109 / 98, 128 -> 48: 106 / 90;
-// 400,000 of 40, f16, 256 -> 96: 1162 / 803.
+// that 16-bit rows have to become half as long for the same bytes: 169,343 of 14, bf16, 128 -> 64: 98 / 80, 128 -> 48: 95 / 75 (but
+// 128 -> 72: 104 / 119); 400,000 of 40, f16, 256 -> 96: 974 / 693, 1 M of 20, bf16, 128 -> 64: 789 / 642.
 // What counts is the lines that a gathered row touches.  Fewer by an eighth or so pay on graphs of some ten thousand rows and
 // more (103,368 of 190, 144 -> 115: 1258 / 922; 257,395 of 36, 149 -> 119: 833 / 680; but 11,806 of 16, 176 -> 140: 30 / 34), fewer
 // by a fifth on smaller ones with work to save (16,934 of 14, 128 -> 64: 20.6 / 20.1; 11,735 of 8, 160 -> 96: 21.3 / 22.6).  As
-// many lines pay for 16-bit rows of a line and more that would go through the workspace (1 M of 60, bf16, 128 -> 64, in one
-// pass: 2049 / 2267; 16 -> 8 columns: 103 / 107).  Matrix-path windows fetch a 16-bit row once per window and multiply on chip:
-// 131,072 in communities, bf16, 128 -> 64: 60 / 68, 54,144, 112 -> 33: 43 / 68.
+// many lines pay for 16-bit rows of a line and more that would go through the workspace, if no window runs on the matrix path
+// (1 M of 60, bf16, 128 -> 64, 3,145 windows there: 1885 / 2075; 169,343 of 14, 16 -> 8 columns: 29.6 / 32.6).  Matrix-path
+// windows fetch a 16-bit row once per window and multiply on chip: 131,072 in communities, bf16, 128 -> 64: 60 / 63, 54,144,
+// 112 -> 33: 47 / 76.
 // What the other order refuses stays refused, and nothing is allocated that it would not have allocated.
 static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, int32_t y_dtype, size_t workspace)
 {
@@ -1533,7 +1534,7 @@ static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_
     if (!many && (plan->nnz < 100000 || (plan->n_rows <= 8192 && !apart))) return false;
     const double before = row_lines(a.X, a.ldx, a.d, f32 ? 4 : 2), after = row_lines(nullptr, d_out, d_out, 4);
     if (after <= (!f32 && windows ? 0.6 : many ? 0.92 : 0.8) * before) return true;
-    return !f32 && !windows && many && 2 * a.d >= 128 && after <= before && plan->n_panels < 2 && apart;
+    return !f32 && (plan->scalar_exec || plan->n_mfma == 0) && many && 2 * a.d >= 128 && after <= before && plan->n_panels < 2 && apart;
 }
 
 // Y = act((A X) W) in that order, A X (a.Y, where it reaches memory) in the caller's workspace.
