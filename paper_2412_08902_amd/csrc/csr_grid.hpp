@@ -24,8 +24,8 @@ struct CsrGrid {
 // Tiers: n_segs segments of long rows, n_mid rows of a wave each (four to a workgroup), n_items short rows of a group each.
 // XCD-local runs (see csr_block): tiers of at least 1024 workgroups are padded to whole rounds of runs of 2^run workgroups
 // over the XCDs that share a slice.  A group (of 8 or 16 lanes) takes one row -- what one after the other adds is only the chain of its loads --
-// unless the launch would have more threads than a launch may: then first more rows to a group (one per lane at most, the
-// lanes hold their extents), then wider slices.
+// unless the launch would have more threads than a launch may: then first more rows to a group (at most as many as it has
+// lanes; the kernel's wide forms walk them one after the other), then wider slices.
 inline CsrGrid csr_grid(int64_t n_segs, int64_t n_mid, int64_t n_items, int32_t d, int32_t n_slices, int32_t slice_w, int run,
                         int group, int rows_per_group = 1)
 {
