@@ -390,8 +390,8 @@ __global__ __launch_bounds__(512, 2) void k_gemm_f32_reg(int64_t M, int32_t K, i
 }
 
 // X W for bf16 X on the bf16 units (v_mfma_f32_16x16x32_bf16), at no loss: an fp32 value of W is the sum of three bf16 values
-// exactly (its 24 bits of significand cut in three), X is bf16 as it is, and products of two bf16 values are exact in fp32, where
-// they are summed -- those of the leading parts and all others each for themselves, added at the end.  Three products of K = 32
+// exactly (its 24 bits of significand cut in three; below 2^-103 the last part leaves the normal range), X is bf16 as it is, and
+// products of two bf16 values are exact in fp32, where they are summed -- those of the leading parts and all others each for themselves, added at the end.  Three products of K = 32
 // take 48 clocks of the matrix units where eight of K = 4 in fp32 take 256, and fewer sums are rounded: the error against 64 bits is a third
 // (relative 2-norm, 128 and 512 terms: normal X 2.0e-7 and 4.1e-7 -> 6.2e-8 and 1.2e-7, X >= 0 1.4e-7 and 2.9e-7 -> 5.0e-8 and
 // 9.3e-8).  169,343 x 128 x 64: 35 -> 27 us; bound by reading X and writing T and by the splitting from here on.  (The same with

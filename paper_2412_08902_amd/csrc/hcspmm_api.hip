@@ -1524,6 +1524,7 @@ static double row_lines(const void* base, int64_t ld, int32_t w, int es)
 static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, int32_t y_dtype, size_t workspace)
 {
     if (plan->opt.update_fusion != HCSPMM_UPDATE_AUTO) return false;
+    if (d_out > a.d) return false;      // (a row off the lines may touch more of them and be narrower: partial sums grow with the width)
     if (plan->n_cols > plan->n_rows || (size_t)plan->n_cols * d_out * sizeof(float) > workspace) return false;
     const bool f32 = a.x_dtype == HCSPMM_F32;
     if (!f32 && !gemm_x16_usable(a.X, a.ldx)) return false;
@@ -1564,7 +1565,7 @@ static hcspmm_status aggregate_then_update(const hcspmm_plan* plan, const SpmmAr
 // 48 -> 64: 96 / 98, 14 -> 16, 1 M of 13: 207 / 237).  Smallest gain: one launch less.
 static bool aggregate_first(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, size_t workspace)
 {
-    if (plan->opt.update_fusion != HCSPMM_UPDATE_AUTO || plan->n_rows == 0) return false;
+    if (plan->opt.update_fusion != HCSPMM_UPDATE_AUTO || plan->n_rows == 0 || a.d > d_out) return false;
     if ((size_t)plan->n_rows * a.d * sizeof(float) > workspace) return false;
     if (plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) return false;
     const double first = row_lines(a.X, a.ldx, a.d, 4), after = row_lines(nullptr, d_out, d_out, 4);

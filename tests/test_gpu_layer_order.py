@@ -53,6 +53,14 @@ def test_both_sides_of_the_rule(n, degree, d_in, d_out, first, mode):
     assert_close(Y, ref, bound, 1e-5)
 
 
+def test_narrower_rows_that_touch_more_lines_keep_their_order():
+    """Rows of 63 fp32 values off the 128-byte lines touch more of them than rows of 64 (2.94 against 2); the scratch of a product grows
+    with its width, so that a call whose rows would become wider keeps the order that it was made room for."""
+    Y, got, ref, bound = run(graph(2000, 9000, 12, seed=3), 64, 63, route_mode=1)
+    assert got
+    assert_close(Y, ref, bound, 1e-5)
+
+
 @pytest.mark.parametrize("n_rows,n_cols,x_pad,x_off,options,first", [
     (9000, 2000, 0, 0, {}, True),                               # A X has no room in the workspace
     (2000, 9000, 0, 0, {}, False), (9000, 9000, 1, 1, {}, False),

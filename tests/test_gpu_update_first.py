@@ -91,6 +91,15 @@ def test_calls_that_keep_their_order(kind, n_rows, n_cols, x_pad, x_off, options
     assert_close(Y, ref, bound, 1e-5)
 
 
+def test_rows_that_would_become_wider_keep_their_order():
+    """63 fp32 values off the 128-byte lines, and 64 of them on two lines: partial sums grow with the width, not with the lines."""
+    g = graph(9000, 1000, 12, seed=5)
+    X, W = dense_normal(1000, 63, seed=1), glorot_uniform(63, 64, seed=2)
+    Y, first, ref, bound = run(g, X, W, "f32", route_mode=1)
+    assert not first
+    assert_close(Y, ref, bound, 1e-5)
+
+
 def test_infinities_and_nan_in_bf16_products():
     """Y = I (X W): an infinity meets the zero remainders of split values nowhere, a NaN stays one.  (Sixteen entries of a
     sixteenth to a row of I: the aggregation multiplies a row's last X row with zeros where its last batch is not full.)"""
