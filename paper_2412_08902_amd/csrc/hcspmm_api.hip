@@ -886,6 +886,60 @@ static hcspmm_status reserve_row_sums(hcspmm_plan* p, int64_t have)
     return HCSPMM_OK;
 }
 
+// Room in the plan's own scratch for calls of width d: partial rows of long rows cut into several segments, partial tiles of
+// wide windows.  Growing it waits for the calls that use it.
+static hcspmm_status reserve_scratch(hcspmm_plan* p, int32_t d, hipStream_t stream)
+{
+    const int64_t rows = row_slots(p) * (int64_t)d;
+    if (p->partial_elems < rows) {
+        if (p->partial) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->partial); p->partial = nullptr; }
+        if (hipMalloc((void**)&p->partial, (size_t)rows * sizeof(float)) != hipSuccess) {
+            (void)hipGetLastError();
+            p->partial = nullptr;
+            p->partial_elems = 0;
+            set_error("allocation of %lld floats for long-row partial sums failed", (long long)rows);
+            return HCSPMM_EALLOC;
+        }
+        p->partial_elems = rows;
+    }
+    const int64_t tiles = tile_slots(p) * kH * (int64_t)d;
+    if (p->tile_partial_elems < tiles) {
+        if (p->tile_partial) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->tile_partial); p->tile_partial = nullptr; }
+        if (hipMalloc((void**)&p->tile_partial, (size_t)tiles * sizeof(float)) != hipSuccess) {
+            (void)hipGetLastError();
+            p->tile_partial = nullptr;
+            p->tile_partial_elems = 0;
+            set_error("allocation of %lld floats for wide-window partial tiles failed", (long long)tiles);
+            return HCSPMM_EALLOC;
+        }
+        p->tile_partial_elems = tiles;
+    }
+    return HCSPMM_OK;
+}
+
+// Whether a call keeps its rows' sums between column panels in the plan (fp32 results keep them in Y itself).
+static bool panel_sums_needed(const hcspmm_plan* p, const SpmmArgs& a)
+{
+    return p->n_panels > 1 && a.y_dtype != HCSPMM_F32 && csr_panels_usable(a);
+}
+
+// Room for those sums.  The ones at hand are given up only for larger ones: calls that must not allocate count on them.
+static hcspmm_status reserve_panel_sums(hcspmm_plan* p, int32_t d, hipStream_t stream)
+{
+    const int64_t want = (int64_t)p->n_rows * d;
+    if (p->acc_rows_elems >= want) return HCSPMM_OK;
+    float* larger = nullptr;
+    if (hipMalloc((void**)&larger, (size_t)want * sizeof(float)) != hipSuccess) {
+        (void)hipGetLastError();
+        set_error("allocation of %lld floats for row sums between column panels failed", (long long)want);
+        return HCSPMM_EALLOC;
+    }
+    if (p->acc_rows) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->acc_rows); }
+    p->acc_rows = larger;
+    p->acc_rows_elems = want;
+    return HCSPMM_OK;
+}
+
 static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStream_t stream,
                               hipEvent_t* ev = nullptr /* 5 events when timing stages */,
                               const UpdateArgs* upd = nullptr /* fuse the update stage where a tile stays on chip */,
@@ -894,6 +948,10 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
                               bool acc_rows = false /* column panels may keep fp32 sums of a 16-bit output in a buffer of the plan */)
 {
     hcspmm_plan* p = const_cast<hcspmm_plan*>(plan);
+    if (!scratch_mem) {
+        const hcspmm_status st = reserve_scratch(p, a.d, stream);
+        if (st != HCSPMM_OK) return st;
+    }
     float* partial = p->partial;
     float* tile_partial = p->tile_partial;
     if (scratch_mem) {
@@ -902,53 +960,14 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         partial = reinterpret_cast<float*>(scratch_mem);
         tile_partial = reinterpret_cast<float*>(scratch_mem + tile_off);
     }
-    // long rows cut into several segments need one partial row per segment
-    const int64_t n_row_slots = row_slots(p);
-    if (!scratch_mem && n_row_slots > 0 && p->partial_elems < n_row_slots * (int64_t)a.d) {
-        if (p->partial) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->partial); p->partial = nullptr; }
-        const int64_t want = n_row_slots * (int64_t)a.d;
-        if (hipMalloc((void**)&p->partial, (size_t)want * sizeof(float)) != hipSuccess) {
-            (void)hipGetLastError();
-            p->partial = nullptr;
-            p->partial_elems = 0;
-            set_error("allocation of %lld floats for long-row partial sums failed", (long long)want);
-            return HCSPMM_EALLOC;
-        }
-        p->partial_elems = want;
-        partial = p->partial;
-    }
-    if (!scratch_mem && tile_slots(p) > 0 && p->tile_partial_elems < tile_slots(p) * kH * (int64_t)a.d) {
-        if (p->tile_partial) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->tile_partial); p->tile_partial = nullptr; }
-        const int64_t want = tile_slots(p) * kH * (int64_t)a.d;
-        if (hipMalloc((void**)&p->tile_partial, (size_t)want * sizeof(float)) != hipSuccess) {
-            (void)hipGetLastError();
-            p->tile_partial = nullptr;
-            p->tile_partial_elems = 0;
-            set_error("allocation of %lld floats for wide-window partial tiles failed", (long long)want);
-            return HCSPMM_EALLOC;
-        }
-        p->tile_partial_elems = want;
-        tile_partial = p->tile_partial;
-    }
     // Column panels: the same kernel once per panel, each adding to what the previous ones left (in Y itself when it is fp32,
     // in fp32 sums of the plan otherwise).
     if (p->n_panels > 1 && !upd && csr_panels_usable(a) && (a.y_dtype == HCSPMM_F32 || acc_rows)) {
         float* sums = a.Y;
         int64_t ld_sums = a.ldy;
         if (a.y_dtype != HCSPMM_F32) {
-            const int64_t want = (int64_t)p->n_rows * a.d;
-            if (p->acc_rows_elems < want) {
-                // (the sums at hand are given up only for larger ones: calls that must not allocate count on them)
-                float* larger = nullptr;
-                if (hipMalloc((void**)&larger, (size_t)want * sizeof(float)) != hipSuccess) {
-                    (void)hipGetLastError();
-                    set_error("allocation of %lld floats for row sums between column panels failed", (long long)want);
-                    return HCSPMM_EALLOC;
-                }
-                if (p->acc_rows) { HC_HIP(hipStreamSynchronize(stream)); (void)hipFree(p->acc_rows); }
-                p->acc_rows = larger;
-                p->acc_rows_elems = want;
-            }
+            const hcspmm_status st = reserve_panel_sums(p, a.d, stream);
+            if (st != HCSPMM_OK) return st;
             sums = p->acc_rows;
             ld_sums = a.d;
         }
@@ -1448,6 +1467,11 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
         set_error("the matrix path with 16-bit T needs d_out a multiple of 4 and 16-byte aligned Y rows");
         return HCSPMM_EUNSUPPORTED;
     }
+    // The order of the two products depends on X's base and pitch; scratch follows from the shapes alone and serves both orders
+    // (the other order's rows are no wider), so that after one call any call of the same shapes allocates nothing.
+    hcspmm_plan* p = const_cast<hcspmm_plan*>(plan);
+    if (plan->n_rows > 0 && (st = reserve_scratch(p, d_out, s)) != HCSPMM_OK) return st;
+    if (plan->n_rows > 0 && panel_sums_needed(plan, a) && (st = reserve_panel_sums(p, d_out, s)) != HCSPMM_OK) return st;
     if (t_dtype == HCSPMM_F32) {
         SpmmArgs z = a;
         z.X = d_X; z.ldx = ldx; z.d = d_in; z.Y = static_cast<float*>(d_workspace); z.ldy = d_in; z.relu = 0; z.y_dtype = HCSPMM_F32;
@@ -1603,6 +1627,8 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
     SpmmArgs a{};
     a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
     a.X = d_X; a.ldx = ldx; a.d = d_in; a.x_dtype = x_dtype; a.Y = Z; a.ldy = d_in; a.relu = 0;
+    // scratch from the shapes alone, for both orders (X W is no wider where it comes first): see hcspmm_gcn_layer_ex
+    if ((st = reserve_scratch(const_cast<hcspmm_plan*>(plan), d_in, s)) != HCSPMM_OK) return st;
     if (update_before(plan, a, d_out, y_dtype, need)) {
         HC_HIP(launch_gemm_x(plan->n_cols, d_in, d_out, d_X, ldx, x_dtype, static_cast<const float*>(d_W), ldw, Z, d_out, s));
         a.X = Z; a.ldx = d_out; a.d = d_out; a.x_dtype = HCSPMM_F32;
