@@ -1553,7 +1553,8 @@ static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_
     const bool f32 = a.x_dtype == HCSPMM_F32;
     if (!f32 && !gemm_x16_usable(a.X, a.ldx)) return false;
     if (plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) return false;
-    if (plan->n_panels > 1 && y_dtype != HCSPMM_F32 && plan->acc_rows_elems < (int64_t)plan->n_rows * d_out) return false;
+    // (sums between panels that the plan was made with, not what an earlier call may have left: the order must not depend on that)
+    if (plan->n_panels > 1 && y_dtype != HCSPMM_F32 && d_out > plan->acc_width) return false;
     const bool windows = !plan->scalar_exec && 2 * plan->n_mfma_small >= plan->W, many = plan->n_rows >= 40000;
     const bool apart = update_place(plan, a.d, d_out, a.x_dtype, false) == kUpdateApart;
     if (!many && (plan->nnz < 100000 || (plan->n_rows <= 8192 && !apart))) return false;

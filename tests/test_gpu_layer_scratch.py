@@ -120,3 +120,28 @@ def test_sums_between_panels_follow_from_the_shapes(first):
     torch.cuda.synchronize()
     plan.destroy()
     assert held[0] == held[1]
+
+
+def test_order_does_not_depend_on_earlier_calls():
+    """A layer call may leave sums between panels in a plan that was made without them; another call's order, and with it the
+    last bits of its result, are the same before and after."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    n, degree, d_in, d_out = 60_000, 160, 128, 64               # two panels
+    rng = np.random.default_rng(1)
+    col = rng.integers(0, n // degree, (n, 1)) + n // degree * np.arange(degree)
+    g = CSRGraph(n, n, np.arange(0, n * degree + 1, degree, dtype=np.int32), col.ravel().astype(np.int32),
+                 rng.standard_normal(n * degree).astype(np.float32))
+    X = torch.from_numpy(dense_normal(n, d_in, seed=1)).cuda()
+    W = torch.from_numpy(glorot_uniform(d_in, d_out, seed=2)).cuda()
+    plan = hc.hcspmm_prepare(n, n, *device_graph(g), route_mode=1, d_hint=d_in)
+    ws = torch.zeros(max(hc.hcspmm_gcn_workspace_bytes(plan, d_in, d_in), hc.hcspmm_aggregate_update_workspace_bytes(plan, d_in, d_out)),
+                     dtype=torch.uint8, device="cuda")
+    Y = [torch.empty((n, d_out), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    hc.hcspmm_aggregate_update(plan, X, W, Y[0], ws)
+    big = torch.empty((n, d_in), dtype=torch.bfloat16, device="cuda")
+    hc.hcspmm_gcn_layer_ex(plan, X, torch.eye(d_in, device="cuda"), big, ws)
+    hc.hcspmm_aggregate_update(plan, X, W, Y[1], ws)
+    torch.cuda.synchronize()
+    plan.destroy()
+    assert torch.equal(Y[0], Y[1])
