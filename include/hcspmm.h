@@ -356,7 +356,8 @@ hcspmm_status hcspmm_spmm_timed(const hcspmm_plan* plan, const void* d_X, int64_
  * update_fusion is HCSPMM_UPDATE_AUTO and n_rows * d_in <= n_cols * d_out, the same
  * sums are associated as act((A X) W), in one of hcspmm_aggregate_update's forms;
  * the workspace then holds A X or nothing of use.  X, W and the values have to be
- * finite for the two orders to agree.
+ * finite for the two orders to agree.  Y may lie over X or W: X W, which is complete
+ * before Y is written, then always comes first.
  *
  *   d_X   device, n_cols x d_in fp32 (ldx >= d_in);  d_W  device, d_in x d_out fp32 (ldw >= d_out)
  *   d_Y   device, n_rows x d_out fp32 (ldy >= d_out)

@@ -1430,6 +1430,13 @@ hcspmm_status hcspmm_gemm_f32(int64_t m, int32_t k, int32_t n, const float* d_X,
     return HCSPMM_OK;
 }
 
+// bytes from the first to the last element of a matrix with rows of w elements
+static size_t extent_bytes(int64_t rows, int64_t ld, int64_t w, size_t element) { return rows > 0 ? (size_t)((rows - 1) * ld + w) * element : 0; }
+static bool overlap(const void* a, size_t na, const void* b, size_t nb)
+{
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 static bool aggregate_first(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, size_t workspace);
 static hcspmm_status aggregate_then_update(const hcspmm_plan* plan, const SpmmArgs& a, const float* W, int64_t ldw, int32_t d_out, void* Y,
                                            int64_t ldy, int32_t y_dtype, int32_t apply_relu, hipStream_t s);
@@ -1472,7 +1479,11 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
     hcspmm_plan* p = const_cast<hcspmm_plan*>(plan);
     if (plan->n_rows > 0 && (st = reserve_scratch(p, d_out, s)) != HCSPMM_OK) return st;
     if (plan->n_rows > 0 && panel_sums_needed(plan, a) && (st = reserve_panel_sums(p, d_out, s)) != HCSPMM_OK) return st;
-    if (t_dtype == HCSPMM_F32) {
+    // (X W in the workspace is complete before anything is stored to Y, so that Y may lie over X or W; the other order reads both
+    // while it stores)
+    const size_t y_size = extent_bytes(plan->n_rows, ldy, d_out, y_dtype == HCSPMM_F32 ? 4 : 2);
+    const bool apart = !overlap(d_Y, y_size, d_X, extent_bytes(plan->n_cols, ldx, d_in, 4)) && !overlap(d_Y, y_size, d_W, extent_bytes(d_in, ldw, d_out, 4));
+    if (t_dtype == HCSPMM_F32 && apart) {
         SpmmArgs z = a;
         z.X = d_X; z.ldx = ldx; z.d = d_in; z.Y = static_cast<float*>(d_workspace); z.ldy = d_in; z.relu = 0; z.y_dtype = HCSPMM_F32;
         if (aggregate_first(plan, z, d_out, need))

@@ -84,3 +84,42 @@ def test_16_bit_results_round_once():
     Y, got, ref, bound = run(graph(9000, 9000, 12, seed=3), 32, 96, y="bf16", route_mode=1)
     assert not got
     assert np.all(np.abs(Y - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5 * bound)
+
+
+@pytest.mark.parametrize("n", [1500, 20_001])                   # in one pass and apart, where the library has the choice
+@pytest.mark.parametrize("over,first", [("X", True), ("the last value of X", True), ("W", True), ("nothing", False)])
+@pytest.mark.parametrize("mode", [1, 2])
+def test_results_over_the_inputs(n, over, first, mode):
+    """Y in the memory of X or of W: X W is complete before anything is stored, and the bits are those of that order."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    d_in, d_out = 32, 96
+    g = graph(n, n, 12, seed=4)
+    X, W = dense_normal(n, d_in, seed=1), glorot_uniform(d_in, d_out, seed=2)
+    dev, X_size = device_graph(g), n * d_in
+
+    def run(over, fusion):
+        flat = torch.full((X_size + n * d_out,), -777.0, device="cuda")
+        Y = flat[X_size:].view(n, d_out)
+        Xd, Wd = flat[:X_size].view(n, d_in), torch.empty((d_in, d_out), device="cuda")         # X ends where Y begins
+        if over == "X":
+            Xd = Y[:, :d_in]
+        elif over == "the last value of X":
+            Y = flat[X_size - 1:-1].view(n, d_out)
+        elif over == "W":
+            Wd = Y[n - d_in:]
+        Xd.copy_(torch.from_numpy(X))
+        Wd.copy_(torch.from_numpy(W))
+        plan = hc.hcspmm_prepare(n, n, *dev, route_mode=mode, d_hint=d_out, update_fusion=fusion)
+        ws = torch.zeros(hc.hcspmm_gcn_workspace_bytes(plan, d_in, d_out), dtype=torch.uint8, device="cuda")
+        hc.hcspmm_gcn_layer(plan, Xd, Wd, Y, ws)
+        torch.cuda.synchronize()
+        plan.destroy()
+        return Y.cpu().numpy(), ws[:4 * n * d_out].view(torch.float32).cpu().numpy()
+
+    want, XW = run("nothing", 2)
+    Y, T = run(over, 0)
+    assert np.array_equal(T, XW) == first
+    assert not first or np.array_equal(Y, want)
+    ref, bound = (oracle.gcn_layer(g.rowptr, g.colind, g.vals, X, W, use_abs=b) for b in (False, True))
+    assert_close(Y.astype(np.float64), ref, bound, 1e-5)
