@@ -417,7 +417,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(int64_t M, int32_t K, int32_t
 {
     constexpr int COLS = 16 * NT, G4 = NT / 4, R = NT % 4, TASKS = (4 * COLS + 255) / 256;
     __shared__ u32x4 slab[2][3][4][COLS];                           // W: part, group of eight k, column
-    __shared__ int w_inf;                                           // set by the first infinity of W, for the rest of K
+    __shared__ int w_inf[2];                                        // an infinity of W in the slab of that buffer, or in one before it there
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, c = lane & 15, q = lane >> 4;
     const int n0 = (int)blockIdx.y * COLS;
     const int64_t m0 = (int64_t)blockIdx.x * (64 * RT) + wave * 16 * RT;
@@ -480,14 +480,15 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(int64_t M, int32_t K, int32_t
                     for (int j = 0; j < 8; ++j) r[j] = fabsf(wn[i][j]) > 3.402823466e38f ? 0.f : r[j];
             }
         }
-        if (most > 3.402823466e38f) w_inf = 1;
+        if (most > 3.402823466e38f) w_inf[buf] = 1;
     };
     v4f_gemm acc[RT][NT], low[RT][NT];                                // products of W's leading parts; all others
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[t][j] = low[t][j] = (v4f_gemm){0.f, 0.f, 0.f, 0.f};
-    if (tid == 0) w_inf = 0;
+    if (tid < 2) w_inf[tid] = 0;
+    bool inf_so_far = false;                                        // for the rest of K
     request_w(0);
     request_x(0, xc);
     __syncthreads();
@@ -497,12 +498,13 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(int64_t M, int32_t K, int32_t
     for (int k0 = 0; k0 < K; k0 += 32) {
         const int k1 = k0 + 32;
         if (k1 < K) { request_w(k1); request_x(k1, xn); }
+        inf_so_far |= w_inf[buf] != 0;                              // (what other waves stage meanwhile goes to the other buffer's)
         u16x2 top = {0, 0};                                         // largest magnitudes, as bit patterns
 #pragma unroll
         for (int t = 0; t < RT; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, xc[t][j] & 0x7fff7fffu));
-        if (__any(max(top.x, top.y) >= 0x7f80) || w_inf) {
+        if (__any(max(top.x, top.y) >= 0x7f80) || inf_so_far) {
 #pragma unroll
             for (int j = 0; j < NT; ++j)
 #pragma unroll 1

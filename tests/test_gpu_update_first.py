@@ -129,3 +129,28 @@ def test_infinities_and_nan_in_bf16_products():
         fin = want.isfinite()
         bound = (X.double().abs() @ W.double().abs())[fin]
         assert torch.all((got[fin] - want[fin]).abs() <= 1e-5 * bound)
+
+
+def test_bits_beside_an_infinity_do_not_depend_on_timing():
+    """An infinity in one column of W takes its slab and those behind it to the fp32 units, in every wave alike: rows that are equal
+    have equal results, wherever they are multiplied."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    n, d_in, d_out = 80000, 256, 64
+    ip = torch.arange(0, 16 * n + 1, 16, dtype=torch.int32, device="cuda")
+    ci, va = torch.arange(n, dtype=torch.int32, device="cuda").repeat_interleave(16), torch.full((16 * n,), 1 / 16, device="cuda")
+    torch.manual_seed(5)
+    X, W = torch.randn(16, d_in).bfloat16().cuda().repeat(n // 16, 1), torch.randn(d_in, d_out).cuda()
+    W[100, 11] = float("inf")
+    plan = hc.hcspmm_prepare(n, n, ip, ci, va, route_mode=1, d_hint=d_in, mfma_dtype=1)
+    ws = torch.empty(hc.hcspmm_aggregate_update_workspace_bytes(plan, d_in, d_out), dtype=torch.uint8, device="cuda")
+    Y = torch.empty(n, d_out, device="cuda")
+    hc.hcspmm_aggregate_update(plan, X, W, Y, ws, apply_relu=False)
+    torch.cuda.synchronize()
+    plan.destroy()
+    T = ws[:4 * n * d_out].view(torch.int32).view(n // 16, 16, d_out)          # X W, as bits
+    finite = torch.arange(d_out, device="cuda") != 11
+    assert torch.equal(T[:, :, finite], T[:1, :, finite].expand(n // 16, -1, -1))
+    assert bool(T.view(torch.float32)[:, :, 11].isinf().all())
+    want = X[:16].double() @ W[:, finite].double()
+    assert torch.all((T[0][:, finite].view(torch.float32).double() - want).abs() <= 1e-5 * (X[:16].double().abs() @ W[:, finite].double().abs()))
