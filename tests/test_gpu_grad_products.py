@@ -22,6 +22,18 @@ def padded(a, pad):
 @pytest.mark.parametrize("d_in,d,pad", [(128, 128, 0), (128, 128, 3), (112, 72, 0), (66, 96, 1), (69, 100, 0), (100, 84, 2),
                                         (120, 124, 5), (96, 68, 0), (127, 80, 0)])       # the last three: two kernels
 def test_products(n, d_in, d, pad):
+    products(n, d_in, d, pad)
+
+
+# Spans of 5 and 6, 9 and 10, 17 and 18 batches: both buffers of a half come round several times, and either half has the last turn.
+# From 65,536 rows on widths of X up to 96 are left to the two kernels.
+@pytest.mark.parametrize("n,d_in,d,pad", [(20481, 128, 128, 0), (20481, 100, 84, 2), (40007, 96, 96, 0), (40007, 128, 72, 1), (40007, 72, 128, 0),
+                                          (65535, 96, 96, 0), (70001, 128, 128, 0), (70001, 112, 72, 3), (70001, 96, 96, 0)])
+def test_products_of_many_batches(n, d_in, d, pad):
+    products(n, d_in, d, pad)
+
+
+def products(n, d_in, d, pad):
     import torch
     import paper_2412_08902_amd.binding as hc
     g = tiny_random_csr(n, n, min(1.0, 8.0 / n), seed=n + d)
