@@ -1541,20 +1541,36 @@ static double row_lines(const void* base, int64_t ld, int32_t w, int es)
     return std::ceil(bytes / unit) * unit / 128.0 + (128.0 - unit) / 128.0;
 }
 
+// The form that a lane group reads a row of so many bytes in: up to 128, 256, 512 bytes, or more of them.
+static int row_form(int64_t bytes) { return bytes <= 128 ? 0 : bytes <= 256 ? 1 : bytes <= 512 ? 2 : 3; }
+// Values per load of the matrix path's kernels, by what rows and base are multiples of.
+static int row_vector(const void* base, int64_t ld, int32_t w)
+{
+    const uint64_t all = (uint64_t)(uintptr_t)base / 4 | (uint64_t)ld | (uint64_t)w;
+    return all % 4 == 0 ? 4 : all % 2 == 0 ? 2 : 1;
+}
+
 // Whether Y = act((A X) W) is computed as act(A (X W)): the same sums in fp32, associated the other way.  Where W makes rows
 // shorter the gather, which is most of the call, then reads rows of d_out instead of d_in columns, and one trip of the rows
 // through memory (X in, X W out) takes the place of the aggregated rows' (out and in again).  In this order / X W first, us:
 // 169,343 rows of 14, fp32: 64 -> 32 columns 85 / 51, 128 -> 64 144 / 93, 256 -> 128 380 / 232; 400,000 of 40, 128 -> 64: 975 /
-// 498; 1 M of 60 (in one pass with the product): 3825 / 2274; 131,072 in communities, 128 -> 64: 96 / 64.  X W is held in fp32, so
-// that 16-bit rows have to become half as long for the same bytes: 169,343 of 14, bf16, 128 -> 64: 98 / 80, 128 -> 48: 95 / 75 (but
-// 128 -> 72: 104 / 119); 400,000 of 40, f16, 256 -> 96: 974 / 693, 1 M of 20, bf16, 128 -> 64: 789 / 642.
-// What counts is the lines that a gathered row touches.  Fewer by an eighth or so pay on graphs of some ten thousand rows and
-// more (103,368 of 190, 144 -> 115: 1258 / 922; 257,395 of 36, 149 -> 119: 833 / 680; but 11,806 of 16, 176 -> 140: 30 / 34), fewer
-// by a fifth on smaller ones with work to save (16,934 of 14, 128 -> 64: 20.6 / 20.1; 11,735 of 8, 160 -> 96: 21.3 / 22.6).  As
-// many lines pay for 16-bit rows of a line and more that would go through the workspace, if no window runs on the matrix path
-// (1 M of 60, bf16, 128 -> 64, 3,145 windows there: 1885 / 2075; 169,343 of 14, 16 -> 8 columns: 29.6 / 32.6).  Matrix-path
-// windows fetch a 16-bit row once per window and multiply on chip: 131,072 in communities, bf16, 128 -> 64: 60 / 63, 54,144,
-// 112 -> 33: 47 / 76.
+// 498; 1 M of 60 (in one pass with the product): 3825 / 2274; 131,072 in communities, 128 -> 64: 96 / 64.
+//
+// What counts is the share of the lines that a gathered row still touches, and where X stays in the L2s also whether the row takes
+// fewer loads of a lane group (row_form).  Power laws, fp32: 24,000 rows of 15, 160 -> 128 (.80, fewer loads) 39 / 35, 144 -> 115
+// (.91, fewer) 47 / 45, but 128 -> 96 (.75, as many) 27 / 31, 192 -> 160 (.83, as many) 47 / 48; 41,000 of 15: 176 -> 140 (.88, as
+// many) 79 / 83; 60,000 of 15: 192 -> 160 108 / 99.  So: up to .6 always, up to .92 with fewer loads or from 48 MB of X on; and
+// with some work to save (16,934 of 6, 224 -> 80: 26.6 / 27.4; 3,780 of 32, bf16, 224 -> 80: 18 / 20).  The matrix path reads rows off
+// the 16-byte pieces value by value: 11,008 in communities, 80 -> 33 (.67): 25 / 32, 69,144 of 31, 256 -> 129 (.62): 166 / 199.
+//
+// X W is held in fp32, so that 16-bit rows have to become half as long for the same bytes: 169,343 of 14, bf16, 128 -> 64: 98 / 80,
+// 128 -> 48: 95 / 75 (but 128 -> 72: 104 / 119); 400,000 of 40, f16, 256 -> 96: 974 / 693.  Up to .83 of the lines, and as many
+// lines for rows of a line and more that come from behind L2 and go through the workspace (bf16: 169,343 of 14, 128 -> 64 above,
+// 156,832 of 32, 64 -> 32: 53 / 49; but 46,367 of 7, 64 -> 32: 15.9 / 17.8, 102,206 of 16, 48 -> 13 (.92): 33 / 34, 81,692 of 35, 52
+// -> 11, off the 16-byte pieces: 36 / 41), if no window runs on the matrix path (1 M of 60, bf16, 128 -> 64, 3,145 windows there:
+// 1885 / 2075).  Matrix-path windows fetch a 16-bit row once per window and multiply on chip: 67,520 in communities, bf16, 80 -> 32:
+// 41 / 52, 32,128, f16, 128 -> 32: 25 / 29; rows of more than 256 bytes still gain where they are many (88,576, f16, 232 -> 14: 70 /
+// 47; but 11,008, 176 -> 32: 17.6 / 18.3).
 // What the other order refuses stays refused, and nothing is allocated that it would not have allocated.
 static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, int32_t y_dtype, size_t workspace)
 {
@@ -1563,15 +1579,23 @@ static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_
     if (plan->n_cols > plan->n_rows || (size_t)plan->n_cols * d_out * sizeof(float) > workspace) return false;
     const bool f32 = a.x_dtype == HCSPMM_F32;
     if (!f32 && !gemm_x16_usable(a.X, a.ldx)) return false;
-    if (plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) return false;
+    const bool matrix = plan->n_mfma > 0 && !plan->scalar_exec, windows = matrix && 2 * plan->n_mfma_small >= plan->W;
+    if (matrix && !mfma_shape_supported(a)) return false;
     // (sums between panels that the plan was made with, not what an earlier call may have left: the order must not depend on that)
     if (plan->n_panels > 1 && y_dtype != HCSPMM_F32 && d_out > plan->acc_width) return false;
-    const bool windows = !plan->scalar_exec && 2 * plan->n_mfma_small >= plan->W, many = plan->n_rows >= 40000;
-    const bool apart = update_place(plan, a.d, d_out, a.x_dtype, false) == kUpdateApart;
-    if (!many && (plan->nnz < 100000 || (plan->n_rows <= 8192 && !apart))) return false;
-    const double before = row_lines(a.X, a.ldx, a.d, f32 ? 4 : 2), after = row_lines(nullptr, d_out, d_out, 4);
-    if (after <= (!f32 && windows ? 0.6 : many ? 0.92 : 0.8) * before) return true;
-    return !f32 && (plan->scalar_exec || plan->n_mfma == 0) && many && 2 * a.d >= 128 && after <= before && plan->n_panels < 2 && apart;
+    const int es = f32 ? 4 : 2;
+    const double share = row_lines(nullptr, d_out, d_out, 4) / row_lines(a.X, a.ldx, a.d, es);
+    const double x_mb = (double)plan->n_cols * a.d * es / (1 << 20);
+    const bool apart = update_place(plan, a.d, d_out, a.x_dtype, false) == kUpdateApart, many = plan->n_rows >= 40000;
+    if ((!many && plan->nnz < (share <= 0.5 ? 100000 : 150000)) || (plan->n_rows <= 8192 && !apart)) return false;
+    if (f32) {
+        if (matrix && share > 0.5 && row_vector(nullptr, d_out, d_out) < row_vector(a.X, a.ldx, a.d)) return false;
+        if (share <= 0.6) return 4 * (int64_t)d_out <= 3 * (int64_t)a.d;    // (not for a better place of rows alone)
+        return share <= 0.92 && (row_form(4 * (int64_t)d_out) < row_form(4 * (int64_t)a.d) || (x_mb >= 48.0 && plan->n_panels < 2));
+    }
+    if (matrix && (windows || !many)) return 2 * a.d > 256 && share <= 0.5 && (many || !windows);
+    const bool pieces = d_out % 4 == 0 || row_form(4 * (int64_t)d_out) < row_form(2 * (int64_t)a.d);
+    return share <= (pieces ? 0.83 : 0.6) || (share <= 1.0 && pieces && !matrix && 2 * a.d >= 128 && x_mb >= 16.0 && plan->n_panels < 2 && apart);
 }
 
 // Y = act((A X) W) in that order, A X (a.Y, where it reaches memory) in the caller's workspace.

@@ -52,20 +52,24 @@ def run(g, X, W, kind, x_pad=0, x_off=0, relu=True, **options):
 
 # n_rows, degree, d_in, d_out, kind, taken
 CASES = [(9000, 12, 32, 16, "f32", False),                      # one line either way
-         (9000, 12, 64, 32, "f32", True), (9000, 12, 128, 96, "f32", True), (9000, 12, 128, 112, "f32", False),
-         (8192, 30, 33, 7, "f32", True), (9000, 5, 64, 32, "f32", False),       # too little to save
+         (9000, 12, 64, 32, "f32", True), (9000, 18, 160, 128, "f32", True), (9000, 18, 144, 115, "f32", True),     # fewer loads of a row
+         (9000, 18, 128, 96, "f32", False), (9000, 12, 128, 112, "f32", False), (9000, 18, 192, 160, "f32", False),    # as many
+         (65537, 2, 192, 160, "f32", True), (65000, 2, 192, 166, "f32", False),      # ... X of 48 MB; lines
+         (8192, 30, 33, 7, "f32", True), (9000, 12, 160, 128, "f32", False), (9000, 5, 64, 32, "f32", False),   # too little to save
          (40001, 3, 64, 28, "f32", True), (40001, 3, 64, 33, "f32", False), (40001, 3, 144, 115, "f32", True), (40001, 3, 64, 64, "f32", False),
-         (40001, 3, 128, 64, "bf16", True), (40001, 3, 128, 65, "f16", False), (40001, 3, 16, 8, "bf16", False),
-         (9000, 12, 128, 64, "bf16", False), (9000, 12, 128, 17, "bf16", True),
+         (65537, 2, 128, 64, "bf16", True), (40001, 3, 128, 64, "bf16", False),      # as many lines: X of 16 MB
+         (40001, 3, 128, 65, "f16", False), (90000, 2, 98, 47, "bf16", False), (40001, 3, 16, 8, "bf16", False),
+         (40001, 3, 56, 11, "bf16", False), (40001, 3, 56, 12, "bf16", True),        # off the 16-byte pieces and on them
+         (9000, 12, 128, 64, "bf16", False), (9000, 18, 128, 17, "bf16", True),
          # 16-bit X: K below, at and above the slabs and units of the product, ragged widths of W
-         (9000, 12, 66, 3, "bf16", True), (9000, 12, 100, 1, "f16", True), (9000, 12, 131, 5, "bf16", True),
-         (9000, 12, 160, 31, "f16", True), (9000, 12, 254, 62, "bf16", True), (9000, 12, 257, 47, "f16", True),
+         (9000, 18, 66, 3, "bf16", True), (9000, 12, 100, 1, "f16", True), (9000, 12, 131, 5, "bf16", True),
+         (9000, 18, 160, 31, "f16", True), (9000, 18, 254, 62, "bf16", True), (9000, 12, 257, 47, "f16", True),
          # ... and with W in registers (from 65,536 rows on, or k n <= 1024)
          (65537, 2, 128, 64, "f16", True), (65537, 2, 100, 20, "bf16", True), (65537, 2, 84, 24, "bf16", True),
-         (9000, 12, 80, 4, "bf16", True), (9000, 12, 68, 15, "f16", True),
+         (9000, 12, 80, 4, "bf16", True), (9000, 18, 68, 15, "f16", True),
          # bf16 X on the bf16 units (from 65,536 rows on): K around its slabs of 32, one to four column tiles, two groups of them
-         (65537, 2, 128, 64, "bf16", True), (65600, 2, 98, 47, "bf16", True), (65536, 2, 65, 16, "bf16", True),
-         (65541, 2, 127, 31, "bf16", True), (65536, 2, 256, 95, "bf16", True), (65537, 2, 322, 128, "bf16", True)]
+         (65600, 2, 130, 47, "bf16", True), (65536, 2, 65, 16, "bf16", True),
+         (65541, 2, 159, 31, "bf16", True), (65536, 2, 288, 95, "bf16", True), (65537, 2, 322, 128, "bf16", True)]
 
 
 @pytest.mark.parametrize("n_rows,degree,d_in,d_out,kind,taken", CASES)
