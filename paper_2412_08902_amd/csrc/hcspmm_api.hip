@@ -1619,18 +1619,44 @@ static hcspmm_status aggregate_then_update(const hcspmm_plan* plan, const SpmmAr
 // update_before the other way.  Where W makes rows longer, rows of X are what a gather should read, and the aggregated rows' trip
 // through memory is shorter than that of X W (or stays on chip, see update_place).  X W first / this order, fp32, us: power laws
 // of 615,315 rows of 97, 32 -> 144 columns: 5923 / 1510; 66,756 of 161, 40 -> 188: 863 / 172; 58,920 of 40, 105 -> 176: 202 / 142;
-// 371,268 of 6, 56 -> 112: 227 / 163; 2,323 of 18, 96 -> 173: 21.9 / 19.4; communities, 114,816 of 58, 112 -> 160: 223 / 140.  What
-// counts is the lines that a gathered row touches, as there (167 -> 176, 299,968 in communities, one more line: 565 / 620); as
-// many lines pay where the rows are clearly shorter and read in whole vectors (142,285 of 16, 8 -> 16: 35.0 / 27.0; but 75,504 of 63,
-// 48 -> 64: 96 / 98, 14 -> 16, 1 M of 13: 207 / 237).  Smallest gain: one launch less.
+// 371,268 of 6, 56 -> 112: 227 / 163; communities, 114,816 of 58, 112 -> 160: 223 / 140.
+//
+// The lines of a gathered row and its loads decide, as there: up to .7 of the lines (.6 where rows of X are off the 16-byte pieces
+// and take as many loads: 72,512 in communities, 9 -> 27, .69: 34 / 37); up to .92 with fewer loads of a lane group, or from 48 MB of
+// X W on where both go through memory in one walk and alike (58,368 in communities, 14 -> 24, .92, as many loads: 28 / 35; 30,214
+// of 36, 143 -> 176, .91: 87 / 94; 22,423 of 18, 136 -> 192, .83: 50 / 52; 56,233 of 79, 156 -> 224, .82, slices of a line against
+// rows off the lines: 347 / 403); as many lines where one holds the row of either and it is clearly shorter and read in whole
+// vectors (142,285 of 16, 8 -> 16: 35.0 / 27.0; but 85,184 of 39, 40 -> 64, two lines: 50 / 52; 75,504 of 63, 48 -> 64: 96 / 98).
+// Windows on the matrix path share their rows and leave less to save: up to .4, beyond it only rows read in as large pieces, and
+// where most windows are there up to .6, .67 with the product in them (in communities: 3,008 rows, 37 -> 128, .53, value by value: 21
+// / 26; 54,400, 144 -> 256, .62: 135 / 140; 174,848, in the windows, 96 -> 112, .75: 169 / 178, 121,344, 64 -> 80, .67: 111 / 92).
+// The one pass over a few thousand rows walks a hub's non-zeros in one lane group: where more than one row in 48 is no short one it
+// takes 128 MB less to gather to be ahead (2,170 rows of 60, 32 -> 96: 12.2 / 19.9, 3,376 of 80, 32 -> 96: 15.7 / 20.0, 3,862 of
+// 163, 48 -> 96: 23.9 / 29.1; 6,850 of 58, 16 -> 113: 24.8 / 18.6).
 static bool aggregate_first(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, size_t workspace)
 {
     if (plan->opt.update_fusion != HCSPMM_UPDATE_AUTO || plan->n_rows == 0 || a.d > d_out) return false;
     if ((size_t)plan->n_rows * a.d * sizeof(float) > workspace) return false;
-    if (plan->n_mfma > 0 && !plan->scalar_exec && !mfma_shape_supported(a)) return false;
-    const double first = row_lines(a.X, a.ldx, a.d, 4), after = row_lines(nullptr, d_out, d_out, 4);
-    const bool vectors = a.d % 4 == 0 && a.ldx % 4 == 0 && (uintptr_t)a.X % 16 == 0;
-    return first <= 0.92 * after || (vectors && 3 * (int64_t)a.d <= 2 * (int64_t)d_out && first <= after);
+    const bool matrix = plan->n_mfma > 0 && !plan->scalar_exec, windows = matrix && 2 * plan->n_mfma_small >= plan->W;
+    if (matrix && !mfma_shape_supported(a)) return false;
+    const UpdatePlace place = update_fusable(a) ? update_place(plan, a.d, d_out, HCSPMM_F32, false) : kUpdateApart;
+    const double share = row_lines(a.X, a.ldx, a.d, 4) / row_lines(nullptr, d_out, d_out, 4);
+    const bool hubs = 48 * ((int64_t)plan->n_mid + plan->n_segs) > plan->n_rows;
+    if (place == kUpdateEverywhere && plan->n_rows <= 8192 && hubs && plan->nnz * (d_out - a.d) * 4 < ((int64_t)128 << 20)) return false;
+    if (matrix) {
+        if (share <= 0.4) return true;
+        if (row_vector(a.X, a.ldx, a.d) < row_vector(nullptr, d_out, d_out)) return false;
+        if (windows) return share <= (place == kUpdateInWindows ? 0.67 : 0.6);
+    }
+    const bool fewer = row_form(4 * (int64_t)a.d) < row_form(4 * (int64_t)d_out), pieces = row_vector(a.X, a.ldx, a.d) == 4;
+    if (share <= (fewer || pieces ? 0.7 : 0.6)) return true;
+    if (share <= 0.92) {
+        if (fewer) return true;
+        const bool on_lines = a.ldx % 32 == 0 && (uintptr_t)a.X % 128 == 0;
+        const bool sliced = a.d > 128 && !on_lines && d_out % 32 == 0 && plan->nnz >= 40 * (int64_t)plan->n_rows;
+        return !sliced && plan->n_panels < 2 && (double)plan->n_cols * d_out * 4 >= 48.0 * (1 << 20);
+    }
+    return share <= 1.0 && pieces && 3 * (int64_t)a.d <= 2 * (int64_t)d_out && 4 * (int64_t)d_out <= 128;
 }
 
 size_t hcspmm_aggregate_update_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)

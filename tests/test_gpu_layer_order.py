@@ -37,8 +37,13 @@ def run(g, d_in, d_out, x_pad=0, x_off=0, y="f32", t=0, relu=True, **options):
 
 # n_rows, degree, d_in, d_out, X W first
 CASES = [(300, 5, 8, 16, False), (300, 5, 32, 144, False), (300, 5, 1, 32, True), (2000, 9, 96, 173, False),     # in one pass
-         (20_001, 12, 16, 32, False), (20_001, 12, 40, 188, False), (20_001, 12, 33, 70, False), (20_001, 12, 256, 300, False),
-         (20_001, 12, 128, 160, False), (20_001, 12, 300, 602, False), (20_001, 12, 11, 21, False),
+         (2000, 60, 32, 96, True), (6000, 60, 32, 144, False),      # ... with hubs, less and more than it costs
+         (20_001, 12, 16, 32, False), (20_001, 12, 40, 188, False), (20_001, 12, 33, 70, False), (20_001, 12, 150, 300, False),
+         (20_001, 12, 128, 160, False), (20_001, 12, 300, 602, False),
+         # as many loads of a row, and nearly as many lines: X W of 48 MB
+         (20_001, 12, 256, 300, True), (50_001, 3, 256, 300, False), (20_001, 12, 96, 128, True),
+         # ... off the 16-byte pieces
+         (20_001, 12, 11, 21, True), (20_001, 12, 9, 27, True), (20_001, 12, 9, 64, False), (20_001, 12, 11, 40, False),
          # as many lines, or more
          (20_001, 12, 32, 32, True), (20_001, 12, 48, 64, True), (20_001, 12, 15, 16, True), (20_001, 12, 167, 176, True),
          (20_001, 12, 64, 32, True), (20_001, 12, 9, 16, True)]

@@ -33,7 +33,7 @@ def placed(X, offset):
 
 # widths for which aligned X takes the layer's other order and X one element off the lines does not, or the other way round
 @pytest.mark.parametrize("call,d_in,d_out,kind,order_changes", [
-    ("layer", 96, 128, "f32", True), ("layer", 64, 96, "f32", True), ("layer", 32, 96, "f32", False), ("layer", 128, 64, "f32", False),
+    ("layer", 64, 80, "f32", True), ("layer", 64, 96, "f32", True), ("layer", 16, 160, "f32", False), ("layer", 128, 64, "f32", False),
     ("aggregate", 128, 16, "bf16", True), ("aggregate", 128, 64, "f32", False), ("aggregate", 64, 96, "f32", False)])
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("first", [0, 1])
