@@ -424,9 +424,8 @@ __device__ __forceinline__ void csr_long_body(uint32_t block, int c_begin, int c
 
 // ---- one launch for all three tiers ---------------------------------------------------------
 template <class G>
-__global__ __launch_bounds__(256, G::WAVES) void k_csr(CsrWork wk, SpmmArgs a)
+__device__ __forceinline__ void csr_body(const CsrWork& wk, const SpmmArgs& a, float* __restrict__ red /* LDS, 256 * G::N floats */)
 {
-    __shared__ float red[256 * G::N];
     uint32_t b = blockIdx.x;
     int slice;
     if (b < wk.grid.seg_blocks * wk.grid.n_slices) {
@@ -446,6 +445,20 @@ __global__ __launch_bounds__(256, G::WAVES) void k_csr(CsrWork wk, SpmmArgs a)
     b = csr_block(blockIdx.x, b, wk.grid.short_blocks, wk.grid.run, wk.grid.n_slices, slice);
     const int c0 = slice * wk.grid.slice_w;
     csr_short_body<G>(b, c0, min(a.d, c0 + wk.grid.slice_w), wk, a);
+}
+template <class G>
+__global__ __launch_bounds__(256, G::WAVES) void k_csr(CsrWork wk, SpmmArgs a)
+{
+    __shared__ float red[256 * G::N];
+    csr_body<G>(wk, a, red);
+}
+// The same with MOST waves per SIMD and no more, which the register allocation is rounded up for (few_waves says when; LDS to the
+// same end is held until a workgroup's last wave is done: 2,383 us where this takes 2,225).
+template <class G, int MOST>
+__global__ __attribute__((amdgpu_flat_work_group_size(1, 256), amdgpu_waves_per_eu(1, MOST))) void k_csr_few(CsrWork wk, SpmmArgs a)
+{
+    __shared__ float red[256 * G::N];
+    csr_body<G>(wk, a, red);
 }
 
 // The same launch with the update stage fused into the short rows; long and mid rows write their
@@ -712,6 +725,21 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
     return degree <= 16.0 && h.rows >= (row <= 64 ? 200000 : 1000000);
 }
 
+// Waves per SIMD that whole rows of more than 512 bytes of fp32, 256 of 16 bits, are held to on scattered matrices (0: what the
+// registers allow, five to six).  The forms that read them ask for eight vectors per lane at once, and all those waves for more than the
+// L2s keep for each other.  Where rows have many non-zeros, which is where X rows are read again, fewer waves are ahead, and
+// where they have very many and are wide, two (all / three / two, us, power laws; fp32: 1 M rows of 20, 150 columns: 2428 / 2225 /
+// 2361, of 15: 1941 / 1748 / 1903, 300,000 of 60, 200: 2042 / 2014 / 1819, 478,000 of 93, 200: 4900 / 4839 / 4520, 90,000 of 45, 150:
+// 282 / 278 / 285; but 800,000 of 13, 172: 1124 / 1141, 400,000 of 6, 140: 261 / 283; bf16: 500,000 of 30, 252: 1152 / 1139, 300,000
+// of 60, 200: 1038 / 1029 / 970, f16 200,000 of 45, 160: 345 / 341 / 367; but 2 M of 16, 144: 1780 / 1865, 600,000 of 20, 180: level).
+static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh)
+{
+    const bool f32 = a.x_dtype == HCSPMM_F32;
+    if (!h.scattered || sh.lanes != 16 || sh.vec * sh.nv != 16 || !(f32 || sh.vec == 8) || h.rows <= 0) return 0;
+    const double degree = (double)h.nnz / (double)h.rows;
+    return degree >= 40.0 && a.d >= 168 ? 2 : degree >= (f32 ? 15.0 : 28.0) ? 3 : 0;
+}
+
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
                       int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd)
@@ -768,6 +796,16 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
         if (a.x_dtype == HCSPMM_F32) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 0, 4) }
         else if (a.x_dtype == HCSPMM_BF16) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 1, 8) }
         else { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 2, 8) }
+        return hipGetLastError();
+    }
+    if (const int most = few_waves(a, hints, sh)) {
+#define HC_LAUNCH_FEW(XK, V, NVV, L, GR, W)                                                                                                     \
+        if (most == 2) hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W>, 2>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a); \
+        else hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W>, 3>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
+        if (a.x_dtype == HCSPMM_F32) HC_CSR_ONE(HC_LAUNCH_FEW, 0, 4, 4, 16, 16);
+        else if (a.x_dtype == HCSPMM_BF16) HC_CSR_ONE(HC_LAUNCH_FEW, 1, 8, 2, 16, 16);
+        else HC_CSR_ONE(HC_LAUNCH_FEW, 2, 8, 2, 16, 16);
+#undef HC_LAUNCH_FEW
         return hipGetLastError();
     }
     HC_CSR_DISPATCH(HC_LAUNCH_CSR)

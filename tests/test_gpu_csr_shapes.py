@@ -147,3 +147,25 @@ def test_halves_of_16bit_rows_that_take_a_wave_each(d):
     Y, _ = gpu_spmm(g, bits, 0, x_bits="bf16", mfma_dtype=1, sel_coef=[0, 0, 1])
     ref, bound = oracle_pair(g, bits, x_dtype=oracle.DT_BF16)
     assert_close(Y, ref, bound, 1e-5, "bf16 d=%d" % d)
+
+
+# whole rows of four vectors (16-bit: two) off the 128-byte lines, on either side of the degrees from which they take three and two waves per SIMD
+@pytest.mark.parametrize("kind,degree,d,pad", [(None, 14, 131, 0), (None, 16, 131, 0), (None, 16, 203, 2), (None, 16, 256, 1), (None, 45, 167, 0),
+                                               (None, 45, 203, 1), ("bf16", 27, 202, 0), ("bf16", 29, 202, 0), ("bf16", 29, 250, 2),
+                                               ("f16", 29, 138, 0), ("bf16", 45, 202, 0), ("f16", 45, 250, 2)])
+def test_whole_rows_of_several_vectors(kind, degree, d, pad):
+    n, n_cols = 5000, 110_000
+    rng = np.random.default_rng(d)
+    lengths = rng.integers(degree - 13, degree + 14, n)
+    lengths[:4] = [0, 300, 2500, 129]                           # (0.6 on average)
+    g = short_rows(lengths, n_cols, seed=d)
+    X = rng.standard_normal((n_cols, d)).astype(np.float32)
+    if kind is None:
+        Y, _ = gpu_spmm(g, X, 1, pad_x=pad, pad_y=1)
+        ref, bound = oracle_pair(g, X)
+    else:
+        bits, code = (to_bf16_bits, oracle.DT_BF16) if kind == "bf16" else (to_f16_bits, oracle.DT_F16)
+        X = bits(X)
+        Y, _ = gpu_spmm(g, X, 1, pad_x=pad, pad_y=1, x_bits=kind)
+        ref, bound = oracle_pair(g, X, x_dtype=code)
+    assert_close(Y, ref, bound, 1e-5, "%s d=%d degree=%d" % (kind, d, degree))
