@@ -433,8 +433,18 @@ __global__ __launch_bounds__(256, (small_waves<XK, VW, NG, FUSE>())) void k_mfma
 // slice width are cut into several slices so that a hub window is not one workgroup's serial
 // work; the slices' partial tiles go to memory and k_reduce_tiles adds them in slice order
 // (deterministic).
+//
+// Waves per SIMD are stated for the medium windows in fp32: what the compiler takes by itself changes with the code around (70
+// registers or 86 for the same source), and where it costs a wave, the launch loses (2.4 M rows of 51, all windows here, 32 columns,
+// 5 / 4 waves: 1,011 / 1,146 us of 3.6 ms).  Wide windows have room for two workgroups in LDS, 16-bit rows differ by nothing.
+template <int XK, int VW, int NG, int KC> constexpr int wg_waves()
+{
+    if (XK != 0 || KC != kKcMid) return 1;
+    constexpr int tiles = NG * VW;
+    return tiles == 1 ? 8 : tiles == 2 ? 5 : tiles == 4 ? 4 : tiles == 8 ? 3 : 2;
+}
 template <int XK, int VW, int NG, int KC>
-__global__ __launch_bounds__(256) void k_mfma_wg(const WgSlice* __restrict__ slices,
+__global__ __launch_bounds__(256, (wg_waves<XK, VW, NG, KC>())) void k_mfma_wg(const WgSlice* __restrict__ slices,
                                                   const int32_t* __restrict__ ncols, const int64_t* __restrict__ wptr,
                                                   const int32_t* __restrict__ wcols, const int32_t* __restrict__ erc,
                                                   int rows_sorted, const int32_t* __restrict__ slice_rows,
