@@ -174,17 +174,20 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[v * VEC + i] = fmaf(w, widened<XK>(x[v].w, i), acc[v * VEC + i]);
     }
-    // Steps T0 .. T0+COUNT-1: the rows requested together, then multiplied.  The order is fixed here: left alone the compiler
+    // Steps T0 .. T0+COUNT-1: the rows requested together, then multiplied.  With FIXED the order is fixed here: left alone the compiler
     // widens the first 16-bit row, and waits for it, before it asks for the others (communities, bf16: 64 columns 26.0 -> 23.0
     // us, 128 columns 48.9 -> 34.5 us; f16, 64 columns: 37.6 -> 24.1 us; power law of 169,343 rows, f16, 64 columns: 41 -> 33 us).
-    template <int T0, int COUNT, class Next> __device__ __forceinline__ void steps(uint32_t key_, float val, float (&acc)[N], Next&& next) const
+    // 16-bit rows of a word per lane and less that take a wave or more each have little to widen and lose by it (bf16, order
+    // fixed / left alone: 4,875 rows of 196, 32 columns 9.05 / 8.35 us, 6,627 of 137, 16 columns 8.27 / 7.90).
+    static constexpr bool FIXED_WAVE = XK == 0 || BYTES > 4;
+    template <bool FIXED, int T0, int COUNT, class Next> __device__ __forceinline__ void steps(uint32_t key_, float val, float (&acc)[N], Next&& next) const
     {
         Raw<RAW> x[COUNT][NV];
         unrolled<COUNT>([&](auto u) { this->template load<T0 + decltype(u)::value>(key_, x[decltype(u)::value]); });
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
         if constexpr (T0 == 0) {
             next();
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
         }
         unrolled<COUNT>([&](auto u) { this->template add<T0 + decltype(u)::value>(val, x[decltype(u)::value], acc); });
     }
@@ -192,16 +195,16 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
     // row's last column with value 0, so the loads carry no branches.
     // next(): requests the next batch's indices, behind the first X rows: loads come back in order, and indices, which
     // mostly come from behind L2, would hold up X rows that hit it.
-    template <class Next> __device__ __forceinline__ void batch(uint32_t key_, float val, int cnt, float (&acc)[N], Next&& next) const
+    template <bool FIXED = true, class Next> __device__ __forceinline__ void batch(uint32_t key_, float val, int cnt, float (&acc)[N], Next&& next) const
     {
         if constexpr (SPLIT == 2 && XK == 0) {
             // a wave whose groups all have more than half a batch left keeps the whole batch in flight (16-bit rows have twice
             // the accumulators and would spill)
-            if (__all(cnt > GROUP / 2)) { steps<0, STEPS>(key_, val, acc, next); return; }
+            if (__all(cnt > GROUP / 2)) { steps<FIXED, 0, STEPS>(key_, val, acc, next); return; }
         }
         unrolled<STEPS / U>([&](auto blk) {
             constexpr int T0 = decltype(blk)::value * U;
-            if (T0 == 0 || cnt > T0 * SPLIT) this->template steps<T0, U>(key_, val, acc, next);
+            if (T0 == 0 || cnt > T0 * SPLIT) this->template steps<FIXED, T0, U>(key_, val, acc, next);
         });
     }
     // (key, value) of non-zero k of a row ending at e (k may run past the end: value 0, last column)
@@ -214,14 +217,14 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
         v = k < e ? t : 0.f;
     }
     // a span [kb, ke) of one row taken GROUP non-zeros at a time with stride `stride` (GROUP when one group owns the span)
-    __device__ __forceinline__ void span(const SpmmArgs& a, int kb, int ke, int stride, int lig, float (&acc)[N]) const
+    template <bool FIXED = true> __device__ __forceinline__ void span(const SpmmArgs& a, int kb, int ke, int stride, int lig, float (&acc)[N]) const
     {
         if (kb >= ke) return;
         uint32_t mk, nk;
         float mv, nv;
         fetch(a, kb + lig, ke, mk, mv);
         for (int k0 = kb; k0 < ke; k0 += stride) {
-            batch(mk, mv, min(GROUP, ke - k0), acc, [&] { fetch(a, k0 + stride + lig, ke, nk, nv); });
+            this->template batch<FIXED>(mk, mv, min(GROUP, ke - k0), acc, [&] { fetch(a, k0 + stride + lig, ke, nk, nv); });
             mk = nk;
             mv = nv;
         }
@@ -299,7 +302,7 @@ __device__ __forceinline__ void csr_mid_body(uint32_t block, int c_begin, int c_
         g.init(a, c0, min(G::COLS, c_end - c0), lig);
         float acc[G::N];
         vzero(acc);
-        g.span(a, s + gi * G::GROUP, e, 64, lig, acc);
+        g.template span<G::FIXED_WAVE>(a, s + gi * G::GROUP, e, 64, lig, acc);
         G::finish(acc);
         // butterfly over the groups: same operation order on every run
 #pragma unroll
@@ -399,7 +402,7 @@ __device__ __forceinline__ void csr_long_body(uint32_t block, int c_begin, int c
         g.init(a, c0, min(G::COLS, c_end - c0), lig);
         float acc[G::N];
         vzero(acc);
-        g.span(a, sg.k_begin + gi * G::GROUP, sg.k_end, 256, lig, acc);
+        g.template span<G::FIXED_WAVE>(a, sg.k_begin + gi * G::GROUP, sg.k_end, 256, lig, acc);
         G::finish(acc);
         // fixed-order tree over the groups: the result does not depend on scheduling
 #pragma unroll
