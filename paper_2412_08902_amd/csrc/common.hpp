@@ -282,6 +282,7 @@ struct CsrHints {
     int64_t rows;
     bool scattered;       // neighbouring rows are known to share few columns
     int32_t long_row;     // rows with more non-zeros are cut into segments
+    bool beside;          // the matrix path runs at the same time on streams of its own
 };
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,

@@ -735,10 +735,15 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
 // 2361, of 15: 1941 / 1748 / 1903, 300,000 of 60, 200: 2042 / 2014 / 1819, 478,000 of 93, 200: 4900 / 4839 / 4520, 90,000 of 45, 150:
 // 282 / 278 / 285; but 800,000 of 13, 172: 1124 / 1141, 400,000 of 6, 140: 261 / 283; bf16: 500,000 of 30, 252: 1152 / 1139, 300,000
 // of 60, 200: 1038 / 1029 / 970, f16 200,000 of 45, 160: 345 / 341 / 367; but 2 M of 16, 144: 1780 / 1865, 600,000 of 20, 180: level).
+// Beside the matrix path's kernels they are held to three whatever the matrix, which leaves those the room to run at all (all / three,
+// us, fp32: 1 M rows of 20, 150 columns: 2433 / 2231, communities + power law, 1.2 M rows, 186: 2030 / 1883, 250: 2554 / 2334; bf16,
+// 1 M of 20, 180: 1429 / 1366).
 static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh)
 {
     const bool f32 = a.x_dtype == HCSPMM_F32;
-    if (!h.scattered || sh.lanes != 16 || sh.vec * sh.nv != 16 || !(f32 || sh.vec == 8) || h.rows <= 0) return 0;
+    if (sh.lanes != 16 || sh.vec * sh.nv != 16 || !(f32 || sh.vec == 8) || h.rows <= 0) return 0;
+    if (h.beside) return 3;
+    if (!h.scattered) return 0;
     const double degree = (double)h.nnz / (double)h.rows;
     return degree >= 40.0 && a.d >= 168 ? 2 : degree >= (f32 ? 15.0 : 28.0) ? 3 : 0;
 }
