@@ -466,8 +466,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, 256), amdgpu_waves_per_
 
 // The same launch with the update stage fused into the short rows; long and mid rows write their
 // aggregated rows to a.Y (the workspace Z) and are finished by k_update_rest.
+// (Four waves per SIMD for 16-bit rows of 129 to 256 bytes, whose form the compiler else gives a few registers too many: 1.2 M rows of
+// 55, bf16, 128 -> 128: 2,438 -> 2,372 us.)
 template <class G>
-__global__ __launch_bounds__(256) void k_csr_fused(CsrWork wk, SpmmArgs a, UpdateArgs u)
+__global__ __launch_bounds__(256, G::ES == 2 && G::BYTES == 16 && G::N == 8 && G::LANES == 16 ? 4 : 1) void k_csr_fused(CsrWork wk, SpmmArgs a, UpdateArgs u)
 {
     constexpr int kTile = 256 / G::GROUP * (G::COLS + 4), kRed = 256 * G::N;
     __shared__ float lds[kTile > kRed ? kTile : kRed];          // the reduction of a long row and the tile of short rows never meet
