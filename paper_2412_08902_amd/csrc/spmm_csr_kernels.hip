@@ -742,15 +742,16 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
 // 282 / 278 / 285; but 800,000 of 13, 172: 1124 / 1141, 400,000 of 6, 140: 261 / 283; bf16: 500,000 of 30, 252: 1152 / 1139, 300,000
 // of 60, 200: 1038 / 1029 / 970, f16 200,000 of 45, 160: 345 / 341 / 367; but 2 M of 16, 144: 1780 / 1865, 600,000 of 20, 180: level).
 // Beside the matrix path's kernels they are held to three whatever the matrix, which leaves those the room to run at all (all / three,
-// us, fp32: 1 M rows of 20, 150 columns: 2433 / 2231, communities + power law, 1.2 M rows, 186: 2030 / 1883, 250: 2554 / 2334; bf16,
-// 1 M of 20, 180: 1429 / 1366).
+// us, fp32: 1 M rows of 20, 150 columns: 2433 / 2231, communities + power law, 1.2 M rows, 186: 2030 / 1883, 250: 2554 / 2334), 16-bit
+// rows only where the rows left to this path are of 12 and more (bf16, 1 M of 20, 136: 1087 / 1058, 184: 1339 / 1311; communities + power law, 1.2 M of
+// 20, 200: level, but 2 M of 9, 160: 1304 / 1400, 2.4 M of 7, 144: 1274 / 1443).
 static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh)
 {
     const bool f32 = a.x_dtype == HCSPMM_F32;
     if (sh.lanes != 16 || sh.vec * sh.nv != 16 || !(f32 || sh.vec == 8) || h.rows <= 0) return 0;
-    if (h.beside) return 3;
-    if (!h.scattered) return 0;
     const double degree = (double)h.nnz / (double)h.rows;
+    if (h.beside) return f32 || degree >= 12.0 ? 3 : 0;
+    if (!h.scattered) return 0;
     return degree >= 40.0 && a.d >= 168 ? 2 : degree >= (f32 ? 15.0 : 28.0) ? 3 : 0;
 }
 
