@@ -743,12 +743,16 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
 // of 60, 200: 1038 / 1029 / 970, f16 200,000 of 45, 160: 345 / 341 / 367; but 2 M of 16, 144: 1780 / 1865, 600,000 of 20, 180: level).
 // Beside the matrix path's kernels they are held to three whatever the matrix, which leaves those the room to run at all (all / three,
 // us, fp32: 1 M rows of 20, 150 columns: 2433 / 2231, communities + power law, 1.2 M rows, 186: 2030 / 1883, 250: 2554 / 2334), 16-bit
-// rows only where the rows left to this path are of 12 and more (bf16, 1 M of 20, 136: 1087 / 1058, 184: 1339 / 1311; communities + power law, 1.2 M of
-// 20, 200: level, but 2 M of 9, 160: 1304 / 1400, 2.4 M of 7, 144: 1274 / 1443).
-static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh)
+// rows only where those left to this path have 12 non-zeros and more (bf16, 1 M of 20, 136: 1087 / 1058, 184: 1339 / 1311; communities
+// + power law, 1.2 M of 20, 200: level, but 2 M of 9, 160: 1304 / 1400, 2.4 M of 7, 144: 1274 / 1443).
+// In column panels, whose X rows are meant to stay in the L2s, 16-bit rows are held to three from 168 columns on and to two from 224
+// (all / three / two, us, bf16: 104,000 rows of 193, 136 columns: 533 / 559 / 675, 184: 713 / 690 / 753, 252: 1040 / 998 / 985; 66,576
+// of 180, 184: 415 / 395 / 409, 252: 603 / 577 / 551; f16 the same).
+static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh, int32_t width)
 {
     const bool f32 = a.x_dtype == HCSPMM_F32;
     if (sh.lanes != 16 || sh.vec * sh.nv != 16 || !(f32 || sh.vec == 8) || h.rows <= 0) return 0;
+    if (a.rowend) return f32 || width < 168 ? 0 : width < 224 ? 3 : 2;
     const double degree = (double)h.nnz / (double)h.rows;
     if (h.beside) return f32 || degree >= 12.0 ? 3 : 0;
     if (!h.scattered) return 0;
@@ -805,25 +809,33 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     }
 #define HC_LAUNCH_CSR(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, L, GR, W>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
 #define HC_LAUNCH_PANEL(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_csr<Gather<XK, V, NVV, L, GR, W, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
+    const int most = few_waves(a, hints, sh, wk.grid.n_slices > 1 ? wk.grid.slice_w : a.d);
+#define HC_LAUNCH_FEW(XK, V, NVV, L, GR, W)                                                                                                     \
+    if (most == 2) hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W>, 2>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a); \
+    else hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W>, 3>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
+#define HC_LAUNCH_FEW_PANEL(XK, V, NVV, L, GR, W)                                                                                                     \
+    if (most == 2) hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W, true>, 2>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a); \
+    else hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W, true>, 3>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
     if (a.rowend) {
         // panels are taken for rows of kPanelRowBytes and more: 16-byte vectors, two per lane at most (wider slices take turns)
         if (sh.vec != (a.x_dtype == HCSPMM_F32 ? 4 : 8)) return hipErrorInvalidValue;
-        if (a.x_dtype == HCSPMM_F32) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 0, 4) }
+        if (most > 0) {
+            if (a.x_dtype == HCSPMM_BF16) HC_CSR_ONE(HC_LAUNCH_FEW_PANEL, 1, 8, 2, 16, 16);
+            else HC_CSR_ONE(HC_LAUNCH_FEW_PANEL, 2, 8, 2, 16, 16);
+        } else if (a.x_dtype == HCSPMM_F32) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 0, 4) }
         else if (a.x_dtype == HCSPMM_BF16) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 1, 8) }
         else { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 2, 8) }
         return hipGetLastError();
     }
-    if (const int most = few_waves(a, hints, sh)) {
-#define HC_LAUNCH_FEW(XK, V, NVV, L, GR, W)                                                                                                     \
-        if (most == 2) hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W>, 2>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a); \
-        else hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W>, 3>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
+    if (most > 0) {
         if (a.x_dtype == HCSPMM_F32) HC_CSR_ONE(HC_LAUNCH_FEW, 0, 4, 4, 16, 16);
         else if (a.x_dtype == HCSPMM_BF16) HC_CSR_ONE(HC_LAUNCH_FEW, 1, 8, 2, 16, 16);
         else HC_CSR_ONE(HC_LAUNCH_FEW, 2, 8, 2, 16, 16);
-#undef HC_LAUNCH_FEW
         return hipGetLastError();
     }
     HC_CSR_DISPATCH(HC_LAUNCH_CSR)
+#undef HC_LAUNCH_FEW_PANEL
+#undef HC_LAUNCH_FEW
 #undef HC_LAUNCH_PANEL
 #undef HC_LAUNCH_CSR
     return hipGetLastError();

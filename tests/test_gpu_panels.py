@@ -69,6 +69,22 @@ def test_16bit_panels(d, pad):
     assert_close(Y, ref, bound, 1e-5, "bf16 panels d=%d" % d)
 
 
+# on either side of the widths that are held to three and to two waves per SIMD, and two slices of more than a slice's limit
+@pytest.mark.parametrize("n_rows,times", [(300, 3), (9001, 1)])
+@pytest.mark.parametrize("kind", ["bf16", "f16"])
+@pytest.mark.parametrize("d", [160, 168, 216, 224, 400])
+def test_wide_16bit_panels(n_rows, times, kind, d):
+    from workloads import to_f16_bits
+    g = graph(n_rows, times=times)
+    to_bits, code = (to_bf16_bits, oracle.DT_BF16) if kind == "bf16" else (to_f16_bits, oracle.DT_F16)
+    assert has_panels(g, d, 1 if kind == "bf16" else 2)
+    bits = to_bits(np.random.default_rng(d).standard_normal((N_COLS, d)).astype(np.float32))
+    Y, _ = gpu_spmm(g, bits, 1, x_bits=kind, mfma_dtype=1 if kind == "bf16" else 2)
+    rows = np.unique(np.concatenate([np.arange(0, n_rows, 1 + n_rows // 300), np.flatnonzero(np.diff(g.rowptr) > 1000), [n_rows - 1]]))
+    ref, bound = oracle_pair(g, bits, rows=rows, x_dtype=code)
+    assert_close(Y[rows], ref, bound, 1e-5, "%s panels n=%d d=%d" % (kind, n_rows, d))
+
+
 def test_rows_that_do_not_ascend_take_no_panels():
     g = graph(300, ascending=False)
     assert not has_panels(g, 64)
