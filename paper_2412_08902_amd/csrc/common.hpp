@@ -304,6 +304,7 @@ int64_t probe_gather_blocks(int64_t n, int32_t d);
 hipError_t launch_probe_gather(const int32_t* index, int64_t n, const float* X, int64_t ldx, int32_t d, int32_t n_rows_x,
                                float* out, hipStream_t s);
 bool mfma_shape_supported(const SpmmArgs& a);
+int mfma_walks(const void* base, int64_t ld, int32_t d);     // launches over the windows for fp32 rows of d columns
 bool mfma_run_shape_supported(const SpmmArgs& a);
 hipError_t launch_mfma_run(const SpmmArgs& a, int32_t n_slices, const RunSlice* slices, const RunWin* wins,
                            const int32_t* ucols, const int32_t* wslot, const int32_t* erc, float* tile_partial, hipStream_t s);

@@ -1543,7 +1543,7 @@ static double row_lines(const void* base, int64_t ld, int32_t w, int es)
 
 // The form that a lane group reads a row of so many bytes in: up to 128, 256, 512 bytes, or more of them.
 static int row_form(int64_t bytes) { return bytes <= 128 ? 0 : bytes <= 256 ? 1 : bytes <= 512 ? 2 : 3; }
-// Values per load of the matrix path's kernels, by what rows and base are multiples of.
+// Values per load, by what rows and base are multiples of.
 static int row_vector(const void* base, int64_t ld, int32_t w)
 {
     const uint64_t all = (uint64_t)(uintptr_t)base / 4 | (uint64_t)ld | (uint64_t)w;
@@ -1559,18 +1559,25 @@ static int row_vector(const void* base, int64_t ld, int32_t w)
 // What counts is the share of the lines that a gathered row still touches, and where X stays in the L2s also whether the row takes
 // fewer loads of a lane group (row_form).  Power laws, fp32: 24,000 rows of 15, 160 -> 128 (.80, fewer loads) 39 / 35, 144 -> 115
 // (.91, fewer) 47 / 45, but 128 -> 96 (.75, as many) 27 / 31, 192 -> 160 (.83, as many) 47 / 48; 41,000 of 15: 176 -> 140 (.88, as
-// many) 79 / 83; 60,000 of 15: 192 -> 160 108 / 99.  So: up to .6 always, up to .92 with fewer loads or from 48 MB of X on; and
-// with some work to save (16,934 of 6, 224 -> 80: 26.6 / 27.4; 3,780 of 32, bf16, 224 -> 80: 18 / 20).  The matrix path reads rows off
-// the 16-byte pieces value by value: 11,008 in communities, 80 -> 33 (.67): 25 / 32, 69,144 of 31, 256 -> 129 (.62): 166 / 199.
+// many) 79 / 83; 60,000 of 15: 192 -> 160 108 / 99.  So: up to .6 always, up to .92 with fewer loads or from 24 MB of X on (57,140 of
+// 74, 118 -> 96, .65: 222 / 126; 48 MB where X W is off the 16-byte pieces and X on them), up to .7 where there is much to gather
+// (34,396 of 85, 18 -> 16: 30.7 / 25.2); and with some work to save (16,934 of 6, 224 -> 80: 26.6 / 27.4; 3,780 of 32, bf16, 224 ->
+// 80: 18 / 20).
+// On the matrix path the walks over the windows count as well, each of which takes up to four groups of 16 loads, of one, two or
+// four values by what rows are multiples of (mfma_walks).  More walks than for X and half of the lines are too many (in communities:
+// 11,008, 80 -> 33, .67: 25 / 32, 14,336, 80 -> 43, .77: 26 / 33); fewer walks, or as many with fewer loads, are ahead whatever the
+// lines (671,825 of 18, 160 -> 93, .78: 835 / 685; 134,400 of 53, 74 -> 55, .83: 174 / 108), and so are larger pieces (76,352 of 57,
+// 117 -> 112, .86: 135 / 96); as many walks and loads up to .8 where most windows are there (level to 1.2 times as fast).
 //
 // X W is held in fp32, so that 16-bit rows have to become half as long for the same bytes: 169,343 of 14, bf16, 128 -> 64: 98 / 80,
 // 128 -> 48: 95 / 75 (but 128 -> 72: 104 / 119); 400,000 of 40, f16, 256 -> 96: 974 / 693.  Up to .83 of the lines, and as many
 // lines for rows of a line and more that come from behind L2 and go through the workspace (bf16: 169,343 of 14, 128 -> 64 above,
 // 156,832 of 32, 64 -> 32: 53 / 49; but 46,367 of 7, 64 -> 32: 15.9 / 17.8, 102,206 of 16, 48 -> 13 (.92): 33 / 34, 81,692 of 35, 52
-// -> 11, off the 16-byte pieces: 36 / 41), if no window runs on the matrix path (1 M of 60, bf16, 128 -> 64, 3,145 windows there:
-// 1885 / 2075).  Matrix-path windows fetch a 16-bit row once per window and multiply on chip: 67,520 in communities, bf16, 80 -> 32:
+// -> 11, off the 16-byte pieces: 36 / 41), if no window runs on the matrix path or the loads are fewer (1 M of 60, bf16, 128 -> 64,
+// 3,145 windows there: 1885 / 2075; 2 M of 20, 160 -> 57: 2712 / 2201).  Matrix-path windows fetch a 16-bit row once per window and multiply on chip: 67,520 in communities, bf16, 80 -> 32:
 // 41 / 52, 32,128, f16, 128 -> 32: 25 / 29; rows of more than 256 bytes still gain where they are many (88,576, f16, 232 -> 14: 70 /
-// 47; but 11,008, 176 -> 32: 17.6 / 18.3).
+// 47; but 11,008, 176 -> 32: 17.6 / 18.3), and so do windows of few non-zeros with 48 MB of X (299,968 rows of 21, bf16, 112 -> 16:
+// 109 / 96, but of 37, 68 -> 16: 106 / 115).
 // What the other order refuses stays refused, and nothing is allocated that it would not have allocated.
 static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_out, int32_t y_dtype, size_t workspace)
 {
@@ -1589,13 +1596,24 @@ static bool update_before(const hcspmm_plan* plan, const SpmmArgs& a, int32_t d_
     const bool apart = update_place(plan, a.d, d_out, a.x_dtype, false) == kUpdateApart, many = plan->n_rows >= 40000;
     if ((!many && plan->nnz < (share <= 0.5 ? 100000 : 150000)) || (plan->n_rows <= 8192 && !apart)) return false;
     if (f32) {
-        if (matrix && share > 0.5 && row_vector(nullptr, d_out, d_out) < row_vector(a.X, a.ldx, a.d)) return false;
-        if (share <= 0.6) return 4 * (int64_t)d_out <= 3 * (int64_t)a.d;    // (not for a better place of rows alone)
-        return share <= 0.92 && (row_form(4 * (int64_t)d_out) < row_form(4 * (int64_t)a.d) || (x_mb >= 48.0 && plan->n_panels < 2));
+        const bool fewer = row_form(4 * (int64_t)d_out) < row_form(4 * (int64_t)a.d);
+        const int before = row_vector(a.X, a.ldx, a.d), after = row_vector(nullptr, d_out, d_out);
+        if (matrix) {
+            const int walks = mfma_walks(nullptr, d_out, d_out) - mfma_walks(a.X, a.ldx, a.d);
+            if (walks > 0 && share > 0.5) return false;
+            if (share <= (walks < 0 || fewer ? 1.0 : after > before ? 0.92 : windows ? 0.8 : 0.0)) return true;
+        }
+        if (share <= 0.6) return d_out < a.d || plan->nnz >= 40 * (int64_t)plan->n_rows;    // (seldom for a better place of rows alone)
+        if (share > 0.92) return false;
+        if (!matrix && (fewer || (share <= 0.7 && after >= before && plan->nnz >= 80 * (int64_t)plan->n_rows))) return true;
+        return plan->n_panels < 2 && x_mb >= (matrix || after < before ? 48.0 : 24.0);
     }
-    if (matrix && (windows || !many)) return 2 * a.d > 256 && share <= 0.5 && (many || !windows);
-    const bool pieces = d_out % 4 == 0 || row_form(4 * (int64_t)d_out) < row_form(2 * (int64_t)a.d);
-    return share <= (pieces ? 0.83 : 0.6) || (share <= 1.0 && pieces && !matrix && 2 * a.d >= 128 && x_mb >= 16.0 && plan->n_panels < 2 && apart);
+    if (matrix && (windows || !many)) {
+        if (windows && x_mb >= 48.0 && plan->nnz < 24 * (int64_t)plan->n_rows) return share <= 0.6;
+        return 2 * a.d > 256 && share <= 0.5 && (many || !windows);
+    }
+    const bool fewer = row_form(4 * (int64_t)d_out) < row_form(2 * (int64_t)a.d), pieces = d_out % 4 == 0 || fewer;
+    return share <= (pieces ? 0.83 : 0.6) || (share <= 1.0 && pieces && (!matrix || fewer) && 2 * a.d >= 128 && x_mb >= 16.0 && plan->n_panels < 2 && apart);
 }
 
 // Y = act((A X) W) in that order, A X (a.Y, where it reaches memory) in the caller's workspace.
@@ -1622,14 +1640,17 @@ static hcspmm_status aggregate_then_update(const hcspmm_plan* plan, const SpmmAr
 // 371,268 of 6, 56 -> 112: 227 / 163; communities, 114,816 of 58, 112 -> 160: 223 / 140.
 //
 // The lines of a gathered row and its loads decide, as there: up to .7 of the lines (.6 where rows of X are off the 16-byte pieces
-// and take as many loads: 72,512 in communities, 9 -> 27, .69: 34 / 37); up to .92 with fewer loads of a lane group, or from 48 MB of
-// X W on where both go through memory in one walk and alike (58,368 in communities, 14 -> 24, .92, as many loads: 28 / 35; 30,214
-// of 36, 143 -> 176, .91: 87 / 94; 22,423 of 18, 136 -> 192, .83: 50 / 52; 56,233 of 79, 156 -> 224, .82, slices of a line against
-// rows off the lines: 347 / 403); as many lines where one holds the row of either and it is clearly shorter and read in whole
+// and take as many loads: 72,512 in communities, 9 -> 27, .69: 34 / 37); up to .92 with fewer loads of a lane group, for rows of X W
+// of more than a line that are read in no larger pieces or have up to 128 columns (133,729 of 56, 33 -> 50, .80: 218 / 163; 112,597
+// of 359, 80 -> 112, .75: 1643 / 1097; 12,942 of 23, 160 -> 224, .71: 41 / 36; but 58,368 in communities, 14 -> 24, .92: 28 / 35;
+// 30,214 of 36, 143 -> 176, .91: 87 / 94; 20,680 of 137, 191 -> 240, .87: 202 / 218), or from 48 MB of X W on, where no slices of a
+// line stand against rows off the lines (56,233 of 79, 156 -> 224, .82: 347 / 403); as many lines where one holds the row of either and it is clearly shorter and read in whole
 // vectors (142,285 of 16, 8 -> 16: 35.0 / 27.0; but 85,184 of 39, 40 -> 64, two lines: 50 / 52; 75,504 of 63, 48 -> 64: 96 / 98).
-// Windows on the matrix path share their rows and leave less to save: up to .4, beyond it only rows read in as large pieces, and
-// where most windows are there up to .6, .67 with the product in them (in communities: 3,008 rows, 37 -> 128, .53, value by value: 21
-// / 26; 54,400, 144 -> 256, .62: 135 / 140; 174,848, in the windows, 96 -> 112, .75: 169 / 178, 121,344, 64 -> 80, .67: 111 / 92).
+// Rows of X that are read in larger pieces than those of X W are ahead up to .92 (150,939 of 133, 24 -> 30, .91: 386 / 290).
+// On the matrix path the walks over the windows decide as there (299,968 in communities, 160 -> 223, .63: 876 / 676; 16,192, 51 -> 69,
+// .82: 36.5 / 21.2; 1.7 M of 14, few windows, 63 -> 170: 3880 / 2111; but more walks: 3,008 in communities, 37 -> 128, .53: 21 / 26,
+// 70,144, 41 -> 80, .75: 80 / 108).  As many walks and loads pay up to .8, where most windows are there up to .6, .67 with the product
+// in them (larger pieces up to .92: 11,264, 160 -> 218, .65: 58 / 50; 54,400, 144 -> 256, .62: 135 / 140; 174,848, in the windows, 96 -> 112, .75: 169 / 178, 121,344, 64 -> 80, .67: 111 / 92).
 // The one pass over a few thousand rows walks a hub's non-zeros in one lane group: where more than one row in 48 is no short one it
 // takes 128 MB less to gather to be ahead (2,170 rows of 60, 32 -> 96: 12.2 / 19.9, 3,376 of 80, 32 -> 96: 15.7 / 20.0, 3,862 of
 // 163, 48 -> 96: 23.9 / 29.1; 6,850 of 58, 16 -> 113: 24.8 / 18.6).
@@ -1643,17 +1664,21 @@ static bool aggregate_first(const hcspmm_plan* plan, const SpmmArgs& a, int32_t 
     const double share = row_lines(a.X, a.ldx, a.d, 4) / row_lines(nullptr, d_out, d_out, 4);
     const bool hubs = 48 * ((int64_t)plan->n_mid + plan->n_segs) > plan->n_rows;
     if (place == kUpdateEverywhere && plan->n_rows <= 8192 && hubs && plan->nnz * (d_out - a.d) * 4 < ((int64_t)128 << 20)) return false;
+    const bool fewer = row_form(4 * (int64_t)a.d) < row_form(4 * (int64_t)d_out), on_lines = a.ldx % 32 == 0 && (uintptr_t)a.X % 128 == 0;
+    const bool sliced = a.d > 128 && !on_lines && d_out % 32 == 0 && plan->nnz >= 40 * (int64_t)plan->n_rows;
+    const int before = row_vector(nullptr, d_out, d_out), after = row_vector(a.X, a.ldx, a.d);
+    const bool pieces = after == 4, long_rows = plan->n_rows > 8192 && 4 * (int64_t)d_out > 128;
     if (matrix) {
-        if (share <= 0.4) return true;
-        if (row_vector(a.X, a.ldx, a.d) < row_vector(nullptr, d_out, d_out)) return false;
+        const int walks = mfma_walks(a.X, a.ldx, a.d) - mfma_walks(nullptr, d_out, d_out);
+        if (share <= (walks < 0 || (walks == 0 && fewer) ? 1.0 : 0.4)) return true;
+        if (walks > 0) return false;
+        if (share <= 0.92 && after > before) return true;
         if (windows) return share <= (place == kUpdateInWindows ? 0.67 : 0.6);
-    }
-    const bool fewer = row_form(4 * (int64_t)a.d) < row_form(4 * (int64_t)d_out), pieces = row_vector(a.X, a.ldx, a.d) == 4;
+        if (share <= 0.8) return true;
+    } else if (share <= 0.92 && (after > before || (long_rows && !sliced && (after == before || d_out <= 128)))) return true;
     if (share <= (fewer || pieces ? 0.7 : 0.6)) return true;
     if (share <= 0.92) {
         if (fewer) return true;
-        const bool on_lines = a.ldx % 32 == 0 && (uintptr_t)a.X % 128 == 0;
-        const bool sliced = a.d > 128 && !on_lines && d_out % 32 == 0 && plan->nnz >= 40 * (int64_t)plan->n_rows;
         return !sliced && plan->n_panels < 2 && (double)plan->n_cols * d_out * 4 >= 48.0 * (1 << 20);
     }
     return share <= 1.0 && pieces && 3 * (int64_t)a.d <= 2 * (int64_t)d_out && 4 * (int64_t)d_out <= 128;

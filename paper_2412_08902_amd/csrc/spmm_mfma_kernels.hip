@@ -896,6 +896,15 @@ bool mfma_shape_supported(const SpmmArgs& a)
     return pick_mfma_shape(a, sh);
 }
 
+int mfma_walks(const void* base, int64_t ld, int32_t d)
+{
+    SpmmArgs a{};
+    a.X = base; a.ldx = a.ldy = ld; a.d = d; a.x_dtype = HCSPMM_F32;
+    MfmaShape sh;
+    pick_mfma_shape(a, sh);
+    return (d + sh.ng * 16 * sh.vw - 1) / (sh.ng * 16 * sh.vw);
+}
+
 // the fused update needs the whole aggregated width in one launch of the wave-per-window kernel
 bool mfma_update_fusable(const SpmmArgs& a)
 {

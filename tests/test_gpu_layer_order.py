@@ -41,9 +41,14 @@ CASES = [(300, 5, 8, 16, False), (300, 5, 32, 144, False), (300, 5, 1, 32, True)
          (20_001, 12, 16, 32, False), (20_001, 12, 40, 188, False), (20_001, 12, 33, 70, False), (20_001, 12, 150, 300, False),
          (20_001, 12, 128, 160, False), (20_001, 12, 300, 602, False),
          # as many loads of a row, and nearly as many lines: X W of 48 MB
-         (20_001, 12, 256, 300, True), (50_001, 3, 256, 300, False), (20_001, 12, 96, 128, True),
+         (8_000, 12, 256, 300, True), (20_001, 12, 256, 300, False), (20_001, 12, 163, 200, True), (70_001, 3, 163, 200, False),
+         (8_000, 12, 96, 128, True), (20_001, 12, 96, 128, False),
          # ... off the 16-byte pieces
          (20_001, 12, 11, 21, True), (20_001, 12, 9, 27, True), (20_001, 12, 9, 64, False), (20_001, 12, 11, 40, False),
+         # ... on the pieces where X W is off them
+         (20_001, 12, 200, 223, False), (20_001, 12, 212, 223, True),
+         # ... of several lines and more than a few thousand, in no larger pieces or short
+         (20_001, 12, 160, 224, False), (20_001, 12, 161, 224, True), (8_192, 12, 160, 224, True), (20_001, 12, 33, 50, False),
          # as many lines, or more
          (20_001, 12, 32, 32, True), (20_001, 12, 48, 64, True), (20_001, 12, 15, 16, True), (20_001, 12, 167, 176, True),
          (20_001, 12, 64, 32, True), (20_001, 12, 9, 16, True)]
@@ -54,6 +59,16 @@ CASES = [(300, 5, 8, 16, False), (300, 5, 32, 144, False), (300, 5, 1, 32, True)
 def test_both_sides_of_the_rule(n, degree, d_in, d_out, first, mode):
     options = {"sel_coef": [1, 300, -280]} if mode == 3 else {}   # (mode 3: some windows on the matrix path)
     Y, got, ref, bound = run(graph(n, n, degree, seed=d_in + d_out), d_in, d_out, relu=d_out % 2 == 0, route_mode=mode, **options)
+    assert got == first
+    assert_close(Y, ref, bound, 1e-5)
+
+
+@pytest.mark.parametrize("d_in,d_out,mode,first", [
+    (41, 80, 1, False), (41, 80, 2, True),                      # 41 columns value by value take two walks over the windows, 80 in fours one
+    (51, 69, 2, False), (160, 223, 2, False),                   # ... one against two; two against four
+    (112, 128, 2, True), (64, 192, 2, False)])                  # as many walks
+def test_walks_over_matrix_path_windows(d_in, d_out, mode, first):
+    Y, got, ref, bound = run(graph(9000, 9000, 12, seed=d_in + d_out), d_in, d_out, route_mode=mode)
     assert got == first
     assert_close(Y, ref, bound, 1e-5)
 

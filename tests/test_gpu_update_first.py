@@ -52,9 +52,11 @@ def run(g, X, W, kind, x_pad=0, x_off=0, relu=True, **options):
 
 # n_rows, degree, d_in, d_out, kind, taken
 CASES = [(9000, 12, 32, 16, "f32", False),                      # one line either way
+         (9000, 18, 38, 32, "f32", True), (9000, 30, 32, 32, "f32", False),         # ... and two, of narrower rows and of as wide ones
          (9000, 12, 64, 32, "f32", True), (9000, 18, 160, 128, "f32", True), (9000, 18, 144, 115, "f32", True),     # fewer loads of a row
          (9000, 18, 128, 96, "f32", False), (9000, 12, 128, 112, "f32", False), (9000, 18, 192, 160, "f32", False),    # as many
-         (65537, 2, 192, 160, "f32", True), (65000, 2, 192, 166, "f32", False),      # ... X of 48 MB; lines
+         (35_000, 5, 192, 160, "f32", True), (65000, 2, 192, 166, "f32", False),     # ... X of 24 MB; lines
+         (65537, 2, 192, 146, "f32", True), (40_001, 4, 192, 146, "f32", False),     # ... of 48 MB for rows off the 16-byte pieces
          (8192, 30, 33, 7, "f32", True), (9000, 12, 160, 128, "f32", False), (9000, 5, 64, 32, "f32", False),   # too little to save
          (40001, 3, 64, 28, "f32", True), (40001, 3, 64, 33, "f32", False), (40001, 3, 144, 115, "f32", True), (40001, 3, 64, 64, "f32", False),
          (65537, 2, 128, 64, "bf16", True), (40001, 3, 128, 64, "bf16", False),      # as many lines: X of 16 MB
@@ -78,6 +80,18 @@ def test_both_sides_of_the_rule(n_rows, degree, d_in, d_out, kind, taken):
     X, W = dense_normal(n_rows, d_in, seed=1), glorot_uniform(d_in, d_out, seed=2)
     pad = d_in % 2                                              # rows of 16-bit X on whole words
     Y, first, ref, bound = run(g, X, W, kind, x_pad=pad, relu=d_out % 2 == 0, route_mode=1)
+    assert first == taken
+    assert_close(Y, ref, bound, 1e-5)
+
+
+@pytest.mark.parametrize("d_in,d_out,mode,taken", [
+    (80, 45, 1, True), (80, 45, 2, False),                      # 45 columns value by value take two walks over the windows
+    (128, 112, 1, False), (132, 128, 2, True),                  # ... and so do 132 in pieces of four
+    (63, 48, 1, False), (63, 48, 2, True), (64, 48, 2, False)])  # as many walks and loads
+def test_walks_over_matrix_path_windows(d_in, d_out, mode, taken):
+    g = graph(9000, 9000, 18, seed=d_in)
+    X, W = dense_normal(9000, d_in, seed=1), glorot_uniform(d_in, d_out, seed=2)
+    Y, first, ref, bound = run(g, X, W, "f32", route_mode=mode)
     assert first == taken
     assert_close(Y, ref, bound, 1e-5)
 
