@@ -1510,7 +1510,9 @@ hcspmm_status hcspmm_gcn_layer_ex(const hcspmm_plan* plan, const void* d_X, int6
 //  * The wave-per-window matrix kernel multiplies its tile while other waves gather, unless the multiplication outweighs the
 //    gather it hides behind (apart / in the windows; communities of degree 51, 131,072 rows: 64 -> 256: 124 / 108 us, 128 ->
 //    128: 153 / 153 us, 128 -> 160: 170 / 181 us, 256 -> 80: 308 / 349 us; of degree 20: 128 -> 64 74 / 68 us, 192 -> 128 133 /
-//    153 us); few windows do not hide it (16,384 rows, 96 -> 256: 32 / 40 us).
+//    153 us); few windows do not hide it (16,384 rows, 96 -> 256: 32 / 40 us).  W of an odd width is read value by value there and
+//    hides behind no gather of rows of 96 columns and more (bf16, 299,968 of 37: 144 -> 97 278 / 498 us, 96 -> 33 130 / 154; 70,016
+//    of 42: 128 -> 47 50 / 52; fp32, 131,072 of 17: 96 -> 67 85 / 115).
 enum UpdatePlace { kUpdateApart, kUpdateInWindows, kUpdateEverywhere };
 static UpdatePlace update_place(const hcspmm_plan* plan, int32_t agg_width, int32_t out_width, int32_t x_dtype, bool keep_z)
 {
@@ -1529,6 +1531,7 @@ static UpdatePlace update_place(const hcspmm_plan* plan, int32_t agg_width, int3
                 return kUpdateEverywhere;
         }
     }
+    if (agg_width >= 96 && out_width % 2 != 0) return kUpdateApart;
     return windows && product <= (plan->n_mfma_small >= 4096 ? 16384 : 12288) ? kUpdateInWindows : kUpdateApart;
 }
 

@@ -96,6 +96,27 @@ def test_walks_over_matrix_path_windows(d_in, d_out, mode, taken):
     assert_close(Y, ref, bound, 1e-5)
 
 
+@pytest.mark.parametrize("d_in,d_out,apart", [(80, 97, False), (96, 97, True), (96, 98, False)])
+def test_odd_widths_of_w_and_the_product_in_the_windows(d_in, d_out, apart):
+    """A X reaches the workspace only where the product is a launch of its own."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    g = graph(9000, 9000, 8, seed=d_in)
+    X, W = dense_normal(9000, d_in, seed=1), glorot_uniform(d_in, d_out, seed=2)
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, *device_graph(g), d_hint=d_in, route_mode=2)
+    assert 2 * hc.hcspmm_plan_info(plan)["n_mfma_small"] > hc.hcspmm_plan_info(plan)["n_windows"]
+    ws = torch.zeros(hc.hcspmm_aggregate_update_workspace_bytes(plan, d_in, d_out), dtype=torch.uint8, device="cuda")
+    Y = torch.empty((9000, d_out), device="cuda")
+    hc.hcspmm_aggregate_update(plan, torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), Y, ws, apply_relu=True)
+    torch.cuda.synchronize()
+    plan.destroy()
+    Z = ws.view(torch.float32)[:9000 * d_in].cpu().numpy().reshape(9000, d_in)
+    AX = oracle.spmm(g.rowptr, g.colind, g.vals, X)
+    assert np.allclose(Z, AX, rtol=0, atol=1e-4 * np.abs(AX).max()) == apart
+    args = (g.rowptr, g.colind, g.vals, X, W)
+    assert_close(Y.cpu().numpy().astype(np.float64), oracle.aggregate_update(*args, relu=True), oracle.aggregate_update(*args, relu=True, use_abs=True), 1e-5)
+
+
 @pytest.mark.parametrize("kind,n_rows,n_cols,x_pad,x_off,options", [
     ("f32", 9000, 9001, 0, 0, {}),                              # X W would be larger than the other order's rows
     ("bf16", 9000, 9000, 1, 0, {}), ("f16", 9000, 9000, 0, 1, {}),      # X off the 4-byte words
