@@ -536,7 +536,7 @@ __global__ __launch_bounds__(256) void k_pre_validate(Prep p)
     if (!p.features) return;
     if (n > kCountMidCap) p.huge_list[atomicAdd(p.ctl + 2, 1)] = w;
     else if (n > kUniqueSmallCap) p.big_list[atomicAdd(p.ctl + 1, 1)] = w;
-    else if (n > kCountTinyCap && !p.touched) p.count_1k[atomicAdd(p.ctl + 3, 1)] = w;
+    else if (n > kCountTinyCap && !p.touched && p.count_1k) p.count_1k[atomicAdd(p.ctl + 3, 1)] = w;
 }
 
 // Distinct columns of kSamples stretches of p.sample_len consecutive non-zeros, spread over the matrix, added up in ctl[8]: how
@@ -1073,11 +1073,13 @@ __global__ __launch_bounds__(256) void k_pre_windows(Prep p, int32_t* __restrict
 hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
 {
     Prep p = p_;
-    p.big_takes_1k = (p.touched ? n_touched : p.W) <= kBigTakes1kWindows ? 1 : 0;
+    const int64_t n_count = p.touched ? n_touched : p.W;
+    const bool few = n_count <= kFewWindows && p.n_cols <= kFewCols;
+    p.big_takes_1k = n_count <= kBigTakes1kWindows ? 1 : 0;
+    if (few) p.count_1k = nullptr;                              // k_pre_count_few reads no lists
     hipLaunchKernelGGL(k_pre_validate, dim3((unsigned)(((int64_t)p.n_rows + 1 + 255) / 256)), dim3(256), 0, s, p);
     if (p.features && p.W > 0) {
-        const int64_t n_count = p.touched ? n_touched : p.W;
-        if (n_count <= kFewWindows && p.n_cols <= kFewCols) {
+        if (few) {
             if (n_count > 0)
                 hipLaunchKernelGGL(k_pre_count_few, dim3((unsigned)std::min<int64_t>(n_count, kFewWindows / 4)), dim3(1024), 0, s, p, (int32_t)n_count);
         } else {
