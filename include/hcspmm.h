@@ -352,12 +352,16 @@ hcspmm_status hcspmm_spmm_timed(const hcspmm_plan* plan, const void* d_X, int64_
  * says the same of update-before-aggregate), and at the benchmark's layer size
  * the call costs what the two stages cost separately (hcspmm_gcn_layer_ex can
  * store the intermediate in 16 bits, which halves the gather bytes).
- * Where rows of X touch fewer memory lines than rows of X W would (d_out > d_in),
- * update_fusion is HCSPMM_UPDATE_AUTO and n_rows * d_in <= n_cols * d_out, the same
- * sums are associated as act((A X) W), in one of hcspmm_aggregate_update's forms;
- * the workspace then holds A X or nothing of use.  X, W and the values have to be
- * finite for the two orders to agree.  Y may lie over X or W: X W, which is complete
- * before Y is written, then always comes first.
+ * Where d_in <= d_out, update_fusion is HCSPMM_UPDATE_AUTO, T is fp32 and
+ * n_rows * d_in <= n_cols * d_out, the library may associate the same sums as
+ * act((A X) W), in one of hcspmm_aggregate_update's forms, where it expects that to be
+ * faster (rows of X that touch fewer memory lines, take fewer loads or, on the matrix
+ * path, fewer walks over the windows than rows of X W); the workspace then holds A X or
+ * nothing of use.  The choice follows from the plan, the widths and X's base and pitch.
+ * X, W and the values have to be finite for the two orders to agree; a caller that
+ * needs one order whatever they are sets update_fusion to FUSED or SPLIT, which keep
+ * X W first here.  Y may lie over X or W: X W, which is complete before Y is written,
+ * then always comes first.
  *
  *   d_X   device, n_cols x d_in fp32 (ldx >= d_in);  d_W  device, d_in x d_out fp32 (ldw >= d_out)
  *   d_Y   device, n_rows x d_out fp32 (ldy >= d_out)
@@ -398,15 +402,18 @@ size_t hcspmm_gcn_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t
  *           on degree and widths), whose gathers hide the product.
  *   windows the same in the matrix path's wave-per-window kernel only; the scalar path's rows go through the
  *           workspace.  Taken where at least half of the windows are such windows and d_in * d_out is at most
- *           16384 (12288 below 4,096 windows).
+ *           16384 (12288 below 4,096 windows), d_in being below 96 if d_out is odd.
  *   apart   Z = A X is written to the workspace and one fp32 MFMA kernel applies W and the activation.  Taken
  *           otherwise, and always when d_in is no multiple of 16 or above 256, X is not aligned for vector
  *           loads, or the graph is walked in column panels.
  *   before  X W goes to the workspace in fp32 and is aggregated from there, with the activation in the aggregation's
- *           epilogue.  Taken, before any of the above, where rows of X W touch fewer memory lines than rows of X (on
- *           graphs of some ten thousand rows and more, n_cols <= n_rows).  X and W have to be finite for the forms to agree:
- *           an infinity in W is one in the rows that are gathered here.
- * HCSPMM_UPDATE_FUSED takes the first form whenever widths and alignment allow it, HCSPMM_UPDATE_SPLIT the third.
+ *           epilogue.  Under HCSPMM_UPDATE_AUTO, with d_out <= d_in, n_cols <= n_rows and room for X W in the workspace,
+ *           the library may take it before any of the above where it expects that to be faster: rows of X W that touch
+ *           fewer memory lines than rows of X, or take fewer loads or walks over the windows; for 16-bit X from behind
+ *           the L2s also as many lines; from 100,000 non-zeros or 40,000 rows on.  X and W have to be finite for the
+ *           forms to agree: an infinity in W is one in the rows that are gathered here.
+ * HCSPMM_UPDATE_FUSED takes the first form whenever widths and alignment allow it, HCSPMM_UPDATE_SPLIT the third;
+ * neither takes the last.
  *
  *   d_X   device, n_cols x d_in, element type x_dtype (ldx >= d_in)
  *   d_W   device, d_in x d_out fp32 (ldw >= d_out)
@@ -435,11 +442,12 @@ size_t hcspmm_aggregate_update_workspace_bytes(const hcspmm_plan* plan, int32_t 
  *     dW = X^T S                            (d_in x d_out)
  * This is the stage of training where the update follows the aggregation (Section V-A): dX is
  * computed like hcspmm_aggregate_update computes its Y, the aggregated tile multiplied by W^T on the
- * matrix cores without a round trip (in the same three forms, chosen by the same rules with d_out for the
+ * matrix cores without a round trip (in the first three of its forms, chosen by the same rules with d_out for the
  * aggregated width; with d_dW given, which makes the kernels store the tile as well, medium-sized graphs take
- * it apart more often), or by a product of its own, which applies the mask of dX as it stores.  dW is a reduction over all rows of the graph: S is also written
- * to the workspace, and one streaming fp32 MFMA kernel forms X^T S from contiguous row spans whose
- * partial products are added in span order (the result does not depend on scheduling).
+ * it apart more often), or by a product of its own, which applies the mask of dX as it stores.  dW is a reduction
+ * over all rows of the graph: S is also written to the workspace, and one streaming fp32 MFMA kernel forms X^T S
+ * from contiguous row spans whose partial products are added in span order (the result does not depend on
+ * scheduling).  For widths of 65 to 128 on both sides one kernel may make both products from one read of S.
  * Eq. 3 as printed, W' = Z^T X' with the aggregated Z = A X_k, is the same call with the dense
  * operands exchanged (d_G = X_k, d_X = X'): d_dW then holds W' transposed.
  *

@@ -567,8 +567,10 @@ static hipError_t launch_gemm_of(int64_t m, int32_t k, int32_t n, const XElem<XK
                       n % 4 == 0 && ldt % 4 == 0 && (uintptr_t)T % (4 * (t_dtype == HCSPMM_F32 ? 4 : 2)) == 0};
     // bf16 X on the bf16 units: groups of up to 64 columns, equally wide, 32 rows to a wave where they leave it the registers.
     // Fp32 units / bf16 units, us, with an aggregation of one non-zero per row behind it: 169,343 x 128 x 64: 51 / 43, x 256 x 96:
-    // 102 / 85, x 256 x 16: 42 / 38, x 512 x 128: 228 / 180; 1 M x 128 x 64: 292 / 275, x 64 x 16: 95 / 86; but 40,000 x 256 x 16: 15.4 /
+    // 102 / 85, x 256 x 16: 42 / 38, x 512 x 128: 228 / 180; 1 M x 128 x 64: 292 / 275, x 64 x 16: 95 / 86; but 40,000 x 256 x 16: 15.0 /
     // 17.0, 9,000 x 256 x 96: 17.6 / 19.7 (too few rows for the splitting of W), and 1 M x 200 x 70: 568 / 622 (columns of padding).
+    // The line at 65,536 rows: above it everything measured gains or is level (66,000 x 128 x 64: 29.5 / 25.9); below it narrow
+    // products lose (65,000 x 256 x 16: 18.3 / 18.6).
     if constexpr (XK == 1) {
         const int64_t tiles = ((int64_t)n + 15) / 16, groups = (tiles + 3) / 4, nt = (tiles + groups - 1) / groups;
         if (m >= 65536 && k >= 64 && 8 * (int64_t)n >= 7 * groups * nt * 16) {
