@@ -105,6 +105,25 @@ def test_split_product_of_values_without_a_remainder():
     assert ok.mean() > 0.95 and np.all(np.abs(got[ok] - ref[ok]) <= 1e-5 * bound[ok])
 
 
+# Small values keep all their bits, those below the normal range too, and large ones whose products come back into it: 2-norms against 64 bits of
+# at most 2^-24 of the result for what each slab of 32 terms leaves out and rounds, and 2^-24 for each of the additions, which add up as a random walk.
+# Values of 2^105 and more and results of 2^82 and more come from the fp32 units: half of 2^-24 for each term, as a random walk.
+@pytest.mark.parametrize("m,k,n", [(16640, 128, 100), (300, 100, 160), (33000, 96, 40)])
+@pytest.mark.parametrize("x_exp,w_exp", [(-105, 0), (-112, 0), (-120, 0), (-120, 100), (0, -115), (-140, 30), (20, -140), (-60, -60), (60, 0), (110, -100), (100, 20)])
+def test_split_product_of_small_and_large_values(m, k, n, x_exp, w_exp):
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    X, W = np.ldexp(dense_normal(m, k, seed=1), x_exp), np.ldexp(dense_normal(k, n, seed=2), w_exp)
+    assert X.dtype == np.float32 and W.dtype == np.float32
+    T = torch.empty((m, n), device="cuda")
+    hc.hcspmm_gemm_f32(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), T)
+    rows = np.unique(np.concatenate([np.arange(0, m, 1 + m // 1000), np.arange(m - 70, m)]))
+    ref = np.ldexp(X[rows].astype(np.float64), -x_exp) @ np.ldexp(W.astype(np.float64), -w_exp)
+    got = np.ldexp(T.cpu().numpy()[rows].astype(np.float64), -x_exp - w_exp)
+    roundings = 0.5 * np.sqrt(k) if max(x_exp, w_exp) >= 100 and x_exp >= 0 else 1 + np.sqrt(k / 32)
+    assert np.linalg.norm(got - ref) <= roundings * 2.0 ** -24 * np.linalg.norm(ref)
+
+
 def test_split_product_is_no_less_exact():
     """Against 64 bits the products in three parts are no further off than a fp32 sum of as many terms: half the square root of
     the terms in units of 2^-24 (their roundings' random walk) as a 2-norm, relative to the result."""

@@ -95,6 +95,20 @@ def test_products_are_no_less_exact(d_in, d):
     assert np.linalg.norm(dX[rows] - ref) <= 0.5 * np.sqrt(d) * 2.0 ** -24 * np.linalg.norm(ref)
 
 
+# Small values keep all their bits, and large ones whose products come back into the range: 2-norms of at most 2^-24 for what a batch leaves
+# out and rounds, and 2^-24 for each addition (dX: d / 32 of them; dW: a workgroup's batches, then 16 and 16 partial sums).
+@pytest.mark.parametrize("n,d_in,d", [(5003, 128, 100), (20481, 70, 30), (5003, 60, 90), (9000, 17, 64)])
+@pytest.mark.parametrize("g_exp,x_exp,w_exp", [(-105, 0, 0), (-112, 0, 0), (-120, 0, 0), (0, -112, -118), (-120, 100, 100), (100, -112, -105), (-140, 40, 30)])
+def test_products_of_small_and_large_values(n, d_in, d, g_exp, x_exp, w_exp):
+    def change(G, X, W):
+        for a, e in ((G, g_exp), (X, x_exp), (W, w_exp)):
+            a[...] = np.ldexp(a, e)
+    S, X, W, dX, dW = whole(n, d_in, d, change)
+    S, X, W = (np.ldexp(a.astype(np.float64), -e) for a, e in ((S, g_exp), (X, x_exp), (W, w_exp)))
+    for got, ref, sums in ((np.ldexp(dX, -g_exp - w_exp), S @ W.T, d / 32), (np.ldexp(dW, -g_exp - x_exp), X.T @ S, 35)):
+        assert np.linalg.norm(got - ref) <= (1 + np.sqrt(sums)) * 2.0 ** -24 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("d_in,d", [(128, 100), (70, 47), (60, 90), (17, 64)])
 def test_products_of_values_without_a_remainder(d_in, d):
     """Infinities, NaN and values that round to infinity in bf16 come out as the fp32 units give them, where they belong alone."""
