@@ -124,6 +124,38 @@ def test_split_product_of_small_and_large_values(m, k, n, x_exp, w_exp):
     assert np.linalg.norm(got - ref) <= roundings * 2.0 ** -24 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("m,k,n", [(16640, 32, 128), (16640, 128, 100), (4000, 602, 160), (33000, 96, 40)])
+@pytest.mark.parametrize("positive_x", [0, 1])
+def test_split_product_has_no_one_sided_error(m, k, n, positive_x):
+    """Results are rounded up as often as down: a bias would add up where rows of them are summed over neighbours.  The mean error, relative to the mean
+    sum of magnitudes, is that of at most 2^-24 each over all results, by six standard deviations."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    X, W = dense_normal(m, k, seed=1), dense_normal(k, n, seed=2)
+    if positive_x:
+        X = np.maximum(X, 0)
+    T = torch.empty((m, n), device="cuda")
+    hc.hcspmm_gemm_f32(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), T)
+    rows = slice(0, 4000)
+    off = T.cpu().numpy()[rows].astype(np.float64) - X[rows].astype(np.float64) @ W.astype(np.float64)
+    assert abs(off.mean()) <= 6 / np.sqrt(off.size) * 2.0 ** -24 * (np.abs(X[rows]) @ np.abs(W)).mean()
+
+
+@pytest.mark.parametrize("m,k,n", [(16640, 128, 100), (300, 602, 160), (33000, 96, 40)])
+def test_split_product_of_single_terms(m, k, n):
+    """One non-zero to a row of X: results are rounded once.  To nearest that is 0.42 units of 2^-24 as a 2-norm (uniform by 0.58 of half a unit in the
+    last place, over mantissas from 1 to 2 spread by their logarithm)."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    X, W = np.zeros((m, k), np.float32), dense_normal(k, n, seed=2)
+    X[np.arange(m), np.random.default_rng(3).integers(0, k, m)] = dense_normal(m, 1, seed=1)[:, 0]
+    T = torch.empty((m, n), device="cuda")
+    hc.hcspmm_gemm_f32(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), T)
+    rows = slice(0, 4000)
+    ref = X[rows].astype(np.float64) @ W.astype(np.float64)
+    assert np.linalg.norm(T.cpu().numpy()[rows].astype(np.float64) - ref) <= 0.45 * 2.0 ** -24 * np.linalg.norm(ref)
+
+
 def test_split_product_is_no_less_exact():
     """Against 64 bits the products in three parts are no further off than a fp32 sum of as many terms: half the square root of
     the terms in units of 2^-24 (their roundings' random walk) as a 2-norm, relative to the result."""

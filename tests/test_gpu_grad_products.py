@@ -95,6 +95,27 @@ def test_products_are_no_less_exact(d_in, d):
     assert np.linalg.norm(dX[rows] - ref) <= 0.5 * np.sqrt(d) * 2.0 ** -24 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("n,d_in,d", [(8000, 128, 100), (8000, 100, 30), (24000, 128, 128), (40007, 60, 90), (9000, 48, 64)])
+def test_products_have_no_one_sided_error(n, d_in, d):
+    """Results are rounded up as often as down, whatever the number of batches to a workgroup: the mean error, relative to the mean sum of
+    magnitudes, is that of at most 2^-24 each over all results, by six standard deviations."""
+    S, X, W, dX, dW = whole(n, d_in, d)
+    for got, a, b in ((dX[:4000], S[:4000].astype(np.float64), W.astype(np.float64).T), (dW, X.astype(np.float64).T, S.astype(np.float64))):
+        off = got - a @ b
+        assert abs(off.mean()) <= 6 / np.sqrt(off.size) * 2.0 ** -24 * (np.abs(a) @ np.abs(b)).mean()
+
+
+@pytest.mark.parametrize("n,d_in,d", [(5003, 128, 100), (5003, 60, 90), (9000, 17, 64)])
+def test_products_of_single_terms(n, d_in, d):
+    """One non-zero to a row of S: dX is rounded once, which is 0.42 units of 2^-24 as a 2-norm."""
+    def change(G, X, W):
+        keep = np.random.default_rng(3).integers(0, d, n)
+        G[np.arange(d) != keep[:, None]] = 0
+    S, X, W, dX, dW = whole(n, d_in, d, change)
+    ref = S.astype(np.float64) @ W.astype(np.float64).T
+    assert np.linalg.norm(dX - ref) <= 0.45 * 2.0 ** -24 * np.linalg.norm(ref)
+
+
 # Small values keep all their bits, and large ones whose products come back into the range: 2-norms of at most 2^-24 for what a batch leaves
 # out and rounds, and 2^-24 for each addition (dX: d / 32 of them; dW: a workgroup's batches, then 16 and 16 partial sums).
 @pytest.mark.parametrize("n,d_in,d", [(5003, 128, 100), (20481, 70, 30), (5003, 60, 90), (9000, 17, 64)])
