@@ -50,9 +50,11 @@ def test_register_product(m, k, n, extra):
 
 # fp32 X on the bf16 units: three to eight tiles of columns and their remainders, several groups; depths around the slabs of 32; rows around
 # the workgroups' 128 and on both sides of the row counts from which each width is taken
-@pytest.mark.parametrize("m,k,n", [(16384, 32, 65), (16385, 33, 80), (16383, 64, 96), (16384 + 127, 63, 97), (16512, 96, 112), (17001, 65, 127),
+@pytest.mark.parametrize("m,k,n", [(16384, 32, 65), (16385, 40, 80), (16383, 64, 96), (16384 + 127, 63, 97), (16512, 96, 112), (17001, 65, 127),
                                    (16640, 602, 128), (16384, 31, 128), (129, 32, 129), (127, 100, 250), (1, 64, 256), (128, 47, 384),
-                                   (32768, 64, 33), (32767, 64, 48), (32900, 67, 47), (32769, 90, 64), (32768, 63, 64), (70001, 70, 52)])
+                                   (32768, 64, 33), (32767, 64, 48), (32900, 67, 47), (32769, 90, 64), (32768, 63, 64), (70001, 70, 52),
+                                   (32768, 72, 52), (49152, 96, 96), (49153, 32, 70), (49152, 64, 112), (49152, 128, 101), (65536, 32, 96), (65536, 48, 100), (65536, 64, 90),
+                                   (65537, 40, 72), (4095, 70, 272), (5505, 33, 300), (12288, 32, 150), (100000, 72, 45), (99999, 72, 45)])
 @pytest.mark.parametrize("extra", [0, 1])
 def test_split_product(m, k, n, extra):
     gemm(m, k, n, ldx=k + extra, pad=extra)
