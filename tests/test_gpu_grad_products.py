@@ -18,7 +18,7 @@ def padded(a, pad):
     return t[:, :a.shape[1]]
 
 
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 100, 1023, 4112, 9000])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 100, 1023, 3500, 3501, 4112, 9000])
 @pytest.mark.parametrize("d_in,d,pad", [(128, 128, 0), (128, 128, 3), (112, 72, 0), (66, 96, 1), (69, 100, 0), (100, 84, 2),
                                         (120, 124, 5), (96, 68, 0), (127, 80, 0)])       # whole tiles of columns and parts of them
 def test_products(n, d_in, d, pad):
