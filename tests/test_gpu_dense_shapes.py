@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import assert_close
+from gpu_util import assert_close, device_graph
 from test_gpu_backward import check, run_backward
 from workloads import dense_normal, glorot_uniform, tiny_random_csr
 
@@ -172,6 +172,27 @@ def test_split_product_is_no_less_exact():
         ref = X[rows].astype(np.float64) @ W.astype(np.float64)
         off = np.linalg.norm(T.cpu().numpy()[rows].astype(np.float64) - ref) / np.linalg.norm(ref)
         assert off <= 0.5 * np.sqrt(k) * 2.0 ** -24, (m, k, n, off)
+
+
+def test_layer_of_split_products_over_many_neighbours():
+    """Y = A (X W) against 64 bits: about 300 rows of T to a row of Y, in units of 2^-24 as a 2-norm.  An addition is rounded by 0.42 and the sums grow as a random
+    walk, over 300 neighbours and, for each T, 19 slabs: 5.3 at most.  An error of T of one sign, 1.7e-9 of its terms' magnitudes, comes to 10 by itself."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    n, k, d = 2000, 602, 160
+    g = tiny_random_csr(n, n, 0.15, seed=5)
+    g.vals[:] = 1
+    X, W = dense_normal(n, k, seed=1), glorot_uniform(k, d, seed=2)
+    plan = hc.hcspmm_prepare(n, n, *device_graph(g), route_mode=1, d_hint=d)
+    ws = torch.empty(hc.hcspmm_gcn_workspace_bytes(plan, k, d), dtype=torch.uint8, device="cuda")
+    Y = torch.empty((n, d), device="cuda")
+    hc.hcspmm_gcn_layer(plan, torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), Y, ws, apply_relu=False)
+    torch.cuda.synchronize()
+    plan.destroy()
+    A = np.zeros((n, n))
+    A[np.repeat(np.arange(n), np.diff(g.rowptr)), g.colind] = 1
+    ref = A @ (X.astype(np.float64) @ W.astype(np.float64))
+    assert np.linalg.norm(Y.cpu().numpy().astype(np.float64) - ref) <= 0.42 * np.sqrt((300 + 1) / 2 + (19 + 1) / 2) * 2.0 ** -24 * np.linalg.norm(ref)
 
 
 # X^T S: blocks of one to four tiles each way, widths that vectors divide and widths they do not, several row groups and
