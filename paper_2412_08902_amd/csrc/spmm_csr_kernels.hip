@@ -549,7 +549,7 @@ __global__ __launch_bounds__(256) void k_update_rest(int32_t n_rest, const int32
 
 // ---- rows cut into several segments: add the partial rows in segment order ------------------
 // A launch of little else than three trips to memory: the record, the partial rows, eight of them requested together whatever their
-// number (one after the other a row of seven segments makes nine trips), the sums of earlier panels beside them.
+// number (one after the other a row of seven segments makes nine trips), the sums of earlier panels beside them.  (Whole calls are level.)
 __global__ __launch_bounds__(256) void k_reduce_partials(int32_t n_multi, const MultiRow* __restrict__ multi,
                                                          const float* __restrict__ partial, SpmmArgs a)
 {
