@@ -111,6 +111,7 @@ struct Prep {
                                           // [4] [5] of count_mid, count_huge, [6] unsorted rows, [7] all scalar, [8] sample
     int32_t *big_list, *huge_list;        // every window of the two classes
     int32_t *count_1k, *count_mid, *count_huge, *n_count_mid, *n_count_huge;   // windows whose columns are still to be counted
+    int32_t* on_matrix;                   // set by launch_prep: non-zeros that the selector sends to the matrix path, per window
     const int32_t* touched;               // windows to count (null: all)
     const int32_t* old_ncols;             // counts carried over for the others
     int32_t features;                     // distinct columns are wanted
@@ -153,6 +154,7 @@ size_t prep_tile_words(int32_t W);        // 64-bit words of all sums of a prepa
 void prep_bind_sums(Prep& p, unsigned long long* words);       // sets n_tiles, wt, rt, wg and rg (from W)
 size_t panel_sum_words(int32_t n_panels, int32_t n_tiles);
 double sample_share(const Prep& p, int32_t distinct);          // distinct columns per non-zero of the sampled stretches (1: no sample)
+size_t prep_zeros(const Prep& p, int32_t n_touched);            // bytes of p.wt that launch_prep expects to be zeros
 hipError_t launch_prep(const Prep& p, int32_t n_touched, hipStream_t s);
 hipError_t launch_prep_fill(const Prep& p, hipStream_t s);      // another pass over the row tables
 hipError_t launch_prep_windows(const Prep& p, int32_t* mfma, int32_t* small, int32_t* mid, int32_t* big, hipStream_t s);

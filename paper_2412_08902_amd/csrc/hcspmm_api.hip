@@ -497,8 +497,8 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     HC_ALLOC(keep, p->segs, most_segs);
     HC_ALLOC(keep, p->multi, most_multi);
     HC_ALLOC(keep, p->rest_rows, most_rest);
-    HC_ALLOC(tmp, err, kPrepCtl);
-    HC_TRY(hipMemsetAsync(err, 0, kPrepCtl * sizeof(int32_t), stream));
+    HC_ALLOC(tmp, err, kPrepCtl + 2 * prep_tile_words(W));      // flags, and behind them the sums, which start at zero on some matrices
+    sums = reinterpret_cast<unsigned long long*>(err + kPrepCtl);
     if (carry && n_touched > 0) {
         if (zero_copy) {
             memcpy(pinned.ptr() + PinnedPage::kList, carry->touched, (size_t)n_touched * sizeof(int32_t));
@@ -537,11 +537,11 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
     pr.c0 = p->coef[0]; pr.c1 = p->coef[1]; pr.c2 = p->coef[2];
     pr.mid_row = p->mid_row; pr.long_row = p->long_row; pr.fused_mid_row = p->fused_mid_row;
     pr.ncols = p->ncols; pr.nnzw = p->nnzw; pr.route = p->route; pr.wptr = p->wptr;
-    HC_ALLOC(tmp, sums, prep_tile_words(W));
     prep_bind_sums(pr, sums);
     pr.mid_rows = p->mid_rows; pr.rest_rows = p->rest_rows; pr.segs = p->segs; pr.multi = p->multi;
     HC_ALLOC(tmp, tot_dev, 1);
     pr.out = pinned.ptr() ? reinterpret_cast<PrepTotals*>(pinned.device_ptr()) : tot_dev;
+    HC_TRY(hipMemsetAsync(err, 0, kPrepCtl * sizeof(int32_t) + prep_zeros(pr, n_touched), stream));
     HC_TRY(launch_prep(pr, n_touched, stream));
     if (pinned.ptr()) {
         HC_TRY(hipStreamSynchronize(stream));
@@ -550,6 +550,7 @@ static hcspmm_status build_plan(hcspmm_plan* p, hipStream_t stream, const PlanCa
         HC_TRY(hipMemcpyAsync(&tot, tot_dev, sizeof tot, hipMemcpyDeviceToHost, stream));
         HC_TRY(hipStreamSynchronize(stream));
     }
+    if (tot.err & 7) tot.err &= 7;                               // (columns are only asked about where the row offsets are sound)
     if (tot.err) {
         set_error("invalid CSR: %s%s%s%s", (tot.err & 1) ? "rowptr[0] != 0; " : "",
                   (tot.err & 2) ? "rowptr[n_rows] != nnz; " : "", (tot.err & 4) ? "rowptr not non-decreasing; " : "",

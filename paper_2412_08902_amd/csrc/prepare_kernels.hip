@@ -410,7 +410,7 @@ hipError_t launch_unique_big(int32_t n_big, const int32_t* big_list, int32_t n_r
 // page of host memory.
 //   k_pre_validate   row offsets; non-zeros per window; windows by size class
 //   k_pre_count*     distinct columns per window by LDS hash sets (bitmap passes beyond their capacity), range of the columns;
-//                    one launch for few windows, one per size class for many
+//                    one launch for few windows (and no k_pre_validate, if they are all, nor k_pre_select), one per size class for many
 //   k_pre_sorted, k_pre_sample   where they decide something: whether rows ascend, how much neighbouring rows share
 //   k_pre_select     selection per window, sums per tile
 //   k_pre_rows       launch guard, route and list offset per window, row classes, sums per tile
@@ -442,21 +442,34 @@ template <class T> __device__ inline T wave_sum(T v)
     return v;
 }
 
-// sum over the workgroup's 256 threads, in every thread
-__device__ inline unsigned long long block_sum_u64(unsigned long long v, unsigned long long* smem /* 4 */)
+// Inclusive prefixes over a wave by DPP moves (a 64-bit shuffle is two trips through LDS, six in a row for a sum).
+template <int CTRL, int ROWS> __device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v)
 {
-    v = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return smem[0] + smem[1] + smem[2] + smem[3];
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, false);
+    return (unsigned long long)hi << 32 | lo;
 }
+__device__ __forceinline__ unsigned long long wave_scan_u64(unsigned long long v)
+{
+    v += dpp_u64<0x111, 0xf>(v);                                // row_shr 1, 2, 4, 8
+    v += dpp_u64<0x112, 0xf>(v);
+    v += dpp_u64<0x114, 0xf>(v);
+    v += dpp_u64<0x118, 0xf>(v);
+    v += dpp_u64<0x142, 0xa>(v);                                // row_bcast 15, 31
+    v += dpp_u64<0x143, 0xc>(v);
+    return v;
+}
+__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int lane)
+{
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+}
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) { return lane_u64(wave_scan_u64(v), 63); }
 
-// the same for several values at once: two barriers for all of them
+// sums of several values over the workgroup's 256 threads, in every thread: two barriers for all of them
 template <int N> __device__ inline void block_sums_u64(unsigned long long (&v)[N], unsigned long long* smem /* 4 * N */)
 {
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
+    for (int i = 0; i < N; ++i) v[i] = wave_sum_u64(v[i]);
     __syncthreads();
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
@@ -465,23 +478,34 @@ template <int N> __device__ inline void block_sums_u64(unsigned long long (&v)[N
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = smem[i] + smem[N + i] + smem[2 * N + i] + smem[3 * N + i];
 }
+__device__ inline unsigned long long block_sum_u64(unsigned long long v, unsigned long long* smem /* 4 */)
+{
+    unsigned long long one[1] = {v};
+    block_sums_u64<1>(one, smem);
+    return one[0];
+}
 
-// exclusive prefix over the workgroup's 256 threads
+// exclusive prefixes of several values over the workgroup's 256 threads
+template <int N> __device__ inline void block_scans_u64(unsigned long long (&v)[N], unsigned long long* smem /* 4 * N */)
+{
+    const int wave = threadIdx.x >> 6;
+    unsigned long long inc[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) inc[i] = wave_scan_u64(v[i]);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 63)
+#pragma unroll
+        for (int i = 0; i < N; ++i) smem[wave * N + i] = inc[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        v[i] = (wave > 0 ? smem[i] : 0ull) + (wave > 1 ? smem[N + i] : 0ull) + (wave > 2 ? smem[2 * N + i] : 0ull) + inc[i] - v[i];
+}
 __device__ inline unsigned long long block_scan_u64(unsigned long long v, unsigned long long* smem /* 4 */)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned long long inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long t = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += t;
-    }
-    __syncthreads();
-    if (lane == 63) smem[wave] = inc;
-    __syncthreads();
-    unsigned long long base = 0;
-    for (int i = 0; i < wave; ++i) base += smem[i];
-    return base + inc - v;
+    unsigned long long one[1] = {v};
+    block_scans_u64<1>(one, smem);
+    return one[0];
 }
 
 // sums of 256 tiles each (K values per tile); blockIdx.y: one array of tiles after the other
@@ -517,6 +541,59 @@ __device__ __forceinline__ void for_sums(const unsigned long long* __restrict__ 
     for (int t = first + thread; t < last; t += threads) f(tiles + (int64_t)t * K, t < at);
 }
 
+// selection (Section IV-C): z' = c0*H*ncols^2 + c1*(H*ncols - nnzw) + c2*H*ncols ; matrix path iff z' < 0
+__device__ inline int window_route(const Prep& p, int mode, long long nc, long long nz)
+{
+    if (nc <= 0 || mode == HCSPMM_ROUTE_ALL_CSR) return 0;
+    if (mode == HCSPMM_ROUTE_ALL_MFMA) return 1;
+    // |c*| < 2^40 and H*ncols^2 < 2^58: every factor fits 64 bits, and 128-bit sums of their products keep the sign exact
+    const long long hn = (long long)kH * nc;
+    const __int128 z = (__int128)p.c0 * (hn * nc) + (__int128)p.c1 * (hn - nz) + (__int128)p.c2 * hn;
+    return z < 0 ? 1 : 0;
+}
+
+// windows on the matrix path | ... of the wave-per-window kernel | medium | wide, 16 bits each (a tile has 64 windows, a
+// group of tiles 16,384)
+__device__ inline unsigned long long window_counts(int r, long long nc)
+{
+    if (!r) return 0ull;
+    return 1ull | (nc <= kMfmaSmallMaxCols ? 1ull << 16 : nc <= kMfmaMidMaxCols ? 1ull << 32 : 1ull << 48);
+}
+
+// What a window adds to its tile's sums: [0] distinct columns; [1] non-zeros, [2] window counts, [3] columns of wide windows on the matrix path under
+// the plan's own mode, [7] columns there; [4..6] as [1..3] with every window there (what the launch guard may decide for)
+__device__ inline void window_sums(int route /* under the plan's own mode */, long long nc, long long nz, unsigned long long (&v)[kWt])
+{
+    v[0] = (unsigned long long)nc;
+    v[7] = 0ull;
+#pragma unroll
+    for (int set = 0; set < 2; ++set) {
+        const int r = set == 0 ? route : nc > 0;
+        v[1 + 3 * set] = r ? (unsigned long long)nz : 0ull;
+        v[2 + 3 * set] = window_counts(r, nc);
+        v[3 + 3 * set] = r && nc > kMfmaMidMaxCols ? (unsigned long long)nc : 0ull;
+        if (set == 0 && r) v[7] = (unsigned long long)nc;
+    }
+}
+// ... added by one thread (whole numbers: in any order, and what is taken off again leaves no trace)
+__device__ inline void add_to_tile(const Prep& p, int32_t w, const unsigned long long (&v)[kWt], bool off = false)
+{
+    unsigned long long* __restrict__ to = p.wt + (int64_t)(w / kTileWindows) * kWt;
+#pragma unroll
+    for (int i = 0; i < kWt; ++i)
+        if (v[i]) atomicAdd(to + i, off ? 0ull - v[i] : v[i]);
+}
+
+// The size class of a window of n non-zeros: on the lists of the larger ones, and of those that k_pre_count_1k counts.
+__device__ inline void list_window(const Prep& p, int32_t w, int32_t n, bool count_1k)
+{
+    if (n > kCountMidCap) p.huge_list[atomicAdd(p.ctl + 2, 1)] = w;
+    else if (n > kUniqueSmallCap) p.big_list[atomicAdd(p.ctl + 1, 1)] = w;
+    else if (n > kCountTinyCap && count_1k) p.count_1k[atomicAdd(p.ctl + 3, 1)] = w;
+}
+
+// SUMS: the tiles' sums of windows are added up here, with the counts carried over, and k_pre_count_few puts the touched windows right
+template <bool SUMS>
 __global__ __launch_bounds__(256) void k_pre_validate(Prep p)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -524,19 +601,30 @@ __global__ __launch_bounds__(256) void k_pre_validate(Prep p)
         if (p.rowptr[0] != 0) atomicOr(p.ctl, 1);
         if ((int64_t)p.rowptr[p.n_rows] != p.nnz) atomicOr(p.ctl, 2);
     }
-    if (i >= p.n_rows) return;
-    const int32_t a = p.rowptr[i], b = p.rowptr[i + 1];
+    if (!SUMS && i >= p.n_rows) return;
+    const int64_t r = min(i, (int64_t)p.n_rows - 1);
+    const int32_t a = p.rowptr[r], b = p.rowptr[r + 1];
     if (a < 0 || b < a) atomicOr(p.ctl, 4);
-    if (i % kH != 0) return;
+    const bool first = i % kH == 0 && i < p.n_rows;             // of a window
+    if (!SUMS && !first) return;
     // (differences of unsound offsets are only ever compared; nothing indexes with them)
-    const int32_t w = (int32_t)(i / kH), n = p.rowptr[min(i + kH, (int64_t)p.n_rows)] - a;
-    p.nnzw[w] = n;
-    if (p.old_ncols) p.ncols[w] = p.old_ncols[w];               // counts of untouched windows are carried over
-    else if (!p.features) p.ncols[w] = 0;                       // a scalar-only plan counts on first request
-    if (!p.features) return;
-    if (n > kCountMidCap) p.huge_list[atomicAdd(p.ctl + 2, 1)] = w;
-    else if (n > kUniqueSmallCap) p.big_list[atomicAdd(p.ctl + 1, 1)] = w;
-    else if (n > kCountTinyCap && !p.touched && p.count_1k) p.count_1k[atomicAdd(p.ctl + 3, 1)] = w;
+    const int32_t w = (int32_t)(r / kH);
+    unsigned long long v[kWt] = {};
+    if (first) {
+        const int32_t n = p.rowptr[min(i + kH, (int64_t)p.n_rows)] - a, nc = p.old_ncols ? p.old_ncols[w] : 0;
+        p.nnzw[w] = n;
+        if (p.old_ncols || !p.features) p.ncols[w] = nc;        // counts of untouched windows are carried over; a scalar-only plan counts on first request
+        if (p.features) list_window(p, w, n, !p.touched);
+        if constexpr (SUMS) window_sums(window_route(p, p.mode, nc, n), nc, n, v);
+    }
+    if constexpr (SUMS) {                                       // (a wave's four windows are of one tile)
+#pragma unroll
+        for (int j = 0; j < kWt; ++j) {
+            v[j] += __shfl_xor(v[j], 16, 64);
+            v[j] += __shfl_xor(v[j], 32, 64);
+        }
+        if ((threadIdx.x & 63) == 0) add_to_tile(p, w, v);
+    }
 }
 
 // Distinct columns of kSamples stretches of p.sample_len consecutive non-zeros, spread over the matrix, added up in ctl[8]: how
@@ -608,32 +696,30 @@ __global__ __launch_bounds__(256) void k_pre_sorted(Prep p)
     if (bad) atomicOr(p.ctl + 6, 1);
 }
 
-// Inserts the window's column ids into an open-addressing set of at least 2n entries (linear probing, empty = -1; an id
-// outside the matrix is reported and left out) and counts the insertions that found an empty slot.  The set is never more
-// than half full, so every probe sequence ends.  NT threads count one window (tid: the caller's place among them); several
-// such groups of a workgroup may each count their own, one that has none calls with take = false (the barriers are the
+// Inserts the column ids of non-zeros s .. e-1 into an open-addressing set of at least twice as many entries (linear probing, empty = -1; an id
+// outside the matrix is reported and left out) and returns how many insertions found an empty slot.  The set is never more
+// than half full, so every probe sequence ends.  nt threads count one window (tid: the caller's place among them); several
+// such groups of a workgroup may each count their own, one that has none calls with s = e (the barriers are the
 // workgroup's).
-template <int NT>
-__device__ inline void count_distinct(int32_t w, const Prep& p, int32_t* table, int* smem /* NT / 64 */, int tid, bool take = true)
+__device__ inline int count_distinct(int32_t s, int32_t e, const Prep& p, int32_t* table, int* smem /* nt / 64 */, int tid, int nt)
 {
-    int32_t s = 0, e = 0;
-    if (take) window_span(w, p.n_rows, p.rowptr, s, e);
     const int32_t n = e - s;
-    int T = NT;                                   // power of two, at least twice the entries
+    int T = nt;                                   // power of two, at least twice the entries
     while (T < 2 * n) T <<= 1;
     const uint32_t mask = (uint32_t)T - 1;
     if (n > 0)
-        for (int i = tid; i < T; i += NT) table[i] = -1;
+#pragma unroll 1
+        for (int i = tid; i < T; i += nt) table[i] = -1;
     __syncthreads();
     int cnt = 0;
     bool bad = false;
-    for (int32_t k0 = s + tid; k0 < e; k0 += 4 * NT) {          // (four loads in flight: a window is little else than their latency)
+    for (int32_t k0 = s + tid; k0 < e; k0 += 4 * nt) {          // (four loads in flight: a window is little else than their latency)
         int32_t col[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) col[j] = p.colind[min(k0 + j * NT, e - 1)];
+        for (int j = 0; j < 4; ++j) col[j] = p.colind[min(k0 + j * nt, e - 1)];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if (k0 + j * NT >= e) break;
+            if (k0 + j * nt >= e) break;
             const int32_t c = col[j];
             if (c < 0 || c >= p.n_cols) { bad = true; continue; }
             uint32_t h = ((uint32_t)c * 0x9E3779B1u >> 12) & mask;
@@ -649,50 +735,65 @@ __device__ inline void count_distinct(int32_t w, const Prep& p, int32_t* table, 
     cnt = wave_sum(cnt);
     if ((tid & 63) == 0) smem[tid >> 6] = cnt;
     __syncthreads();
-    if (tid != 0 || !take) return;
     int total = 0;
-#pragma unroll
-    for (int i = 0; i < NT / 64; ++i) total += smem[i];
-    p.ncols[w] = total;
+#pragma unroll 1
+    for (int i = 0; i < nt / 64; ++i) total += smem[i];
+    return total;
 }
 
-// A window of any size, counted by the workgroup's 1024 threads: with a hash set, and beyond half of the table's entries with
-// a bitmap of 32 * WORDS columns a pass.
-template <int WORDS>
-__device__ inline void count_window(int32_t w, const Prep& p, int32_t* table /* WORDS */, int* smem /* 16 */)
+// The same for a window of any size by the NT threads of the workgroup, with a bitmap of 32 * `words` columns a pass.  A thread takes four entries in a
+// row, eight times that requested together (one after the other a window of 21,000 non-zeros is 21 trips to memory for 1024 threads), and
+// sets the bits of one word at once: neighbouring entries of a row mostly share words, and lanes that add to the same word take turns.
+// (Hubs of 154,000 non-zeros to a window: the launch 44 -> 20 us.)
+typedef int32_t i4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <int NT>
+__device__ inline int count_bits(int32_t s, int32_t e /* at least s + 4 */, const Prep& p, uint32_t* __restrict__ bm, int words, int* smem /* NT / 64 */)
 {
-    int32_t s, e;
-    window_span(w, p.n_rows, p.rowptr, s, e);
-    if (e - s <= WORDS / 2) {
-        count_distinct<1024>(w, p, table, smem, threadIdx.x);
-        return;
-    }
-    uint32_t* __restrict__ bm = reinterpret_cast<uint32_t*>(table);
-    constexpr int kBits = WORDS * 32;
+    constexpr uint32_t U = 8;
+    const uint32_t bits_a_pass = (uint32_t)words * 32u;
     int cnt = 0;
     bool bad = false;
-    for (int64_t base = 0; base < p.n_cols; base += kBits) {
-        for (int j = threadIdx.x; j < WORDS; j += 1024) bm[j] = 0u;
+    for (int64_t base = 0; base < p.n_cols; base += bits_a_pass) {
+#pragma unroll 1
+        for (int j = threadIdx.x; j < words; j += NT) bm[j] = 0u;
         __syncthreads();
-        for (int32_t k = s + threadIdx.x; k < e; k += 1024) {
-            const int32_t col = p.colind[k];
-            bad |= col < 0 || col >= p.n_cols;
-            const int64_t c = (int64_t)col - base;
-            if (c >= 0 && c < kBits) atomicOr(&bm[c >> 5], 1u << (c & 31));
+        for (uint32_t k0 = (uint32_t)s + 4 * threadIdx.x; k0 < (uint32_t)e; k0 += 4 * NT * U) {
+            i4_any col[U];
+#pragma unroll
+            for (uint32_t j = 0; j < U; ++j)                    // (the last four entries instead of what lies behind them)
+                col[j] = *reinterpret_cast<const i4_any*>(p.colind + min(k0 + j * 4 * NT, (uint32_t)e - 4u));
+#pragma unroll
+            for (uint32_t j = 0; j < U; ++j) {
+                if (k0 + j * 4 * NT >= (uint32_t)e) break;
+                uint32_t at = ~0u, bits = 0u;                   // word, and bits to set in it
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if ((uint32_t)col[j][i] >= (uint32_t)p.n_cols) { bad = true; continue; }
+                    const uint32_t c = (uint32_t)col[j][i] - (uint32_t)base;
+                    if (c >= bits_a_pass) continue;
+                    if (c >> 5 != at) {
+                        if (bits) atomicOr(&bm[at], bits);
+                        at = c >> 5;
+                        bits = 0u;
+                    }
+                    bits |= 1u << (c & 31u);
+                }
+                if (bits) atomicOr(&bm[at], bits);
+            }
         }
         __syncthreads();
-        for (int j = threadIdx.x; j < WORDS; j += 1024) cnt += __popc(bm[j]);
+#pragma unroll 1
+        for (int j = threadIdx.x; j < words; j += NT) cnt += __popc(bm[j]);
         __syncthreads();
     }
     if (bad) atomicOr(p.ctl, 8);
     cnt = wave_sum(cnt);
     if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = cnt;
     __syncthreads();
-    if (threadIdx.x != 0) return;
     int total = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) total += smem[i];
-    p.ncols[w] = total;
+#pragma unroll 1
+    for (int i = 0; i < NT / 64; ++i) total += smem[i];
+    return total;
 }
 
 // windows of up to kCountTinyCap non-zeros, one workgroup each: all windows, or -- after a structural change -- the
@@ -712,7 +813,10 @@ __global__ __launch_bounds__(256) void k_pre_count(Prep p)
         }
         return;
     }
-    count_distinct<256>(w, p, table, smem, threadIdx.x);
+    int32_t s, e;
+    window_span(w, p.n_rows, p.rowptr, s, e);
+    const int nc = count_distinct(s, e, p, table, smem, threadIdx.x, 256);
+    if (threadIdx.x == 0) p.ncols[w] = nc;
 }
 
 __global__ __launch_bounds__(256) void k_pre_count_1k(Prep p)
@@ -722,7 +826,11 @@ __global__ __launch_bounds__(256) void k_pre_count_1k(Prep p)
     if (*p.ctl & 7) return;
     const int32_t n = p.ctl[3];
     for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
-        count_distinct<256>(p.count_1k[i], p, table, smem, threadIdx.x);
+        const int32_t w = p.count_1k[i];
+        int32_t s, e;
+        window_span(w, p.n_rows, p.rowptr, s, e);
+        const int nc = count_distinct(s, e, p, table, smem, threadIdx.x, 256);
+        if (threadIdx.x == 0) p.ncols[w] = nc;
         __syncthreads();
     }
 }
@@ -734,89 +842,108 @@ __global__ __launch_bounds__(1024) void k_pre_count_big(Prep p)
     if (*p.ctl & 7) return;
     const int32_t n_huge = *p.n_count_huge, n_mid = *p.n_count_mid, n_1k = p.big_takes_1k ? p.ctl[3] : 0;
     for (int32_t i = blockIdx.x; i < n_huge + n_mid + n_1k; i += gridDim.x) {
-        count_window<2 * kCountMidCap>(i < n_huge ? p.count_huge[i] : i < n_huge + n_mid ? p.count_mid[i - n_huge] : p.count_1k[i - n_huge - n_mid], p, table, smem);
+        const int32_t w = i < n_huge ? p.count_huge[i] : i < n_huge + n_mid ? p.count_mid[i - n_huge] : p.count_1k[i - n_huge - n_mid];
+        int32_t s, e;
+        window_span(w, p.n_rows, p.rowptr, s, e);
+        const int nc = e - s <= kCountMidCap ? count_distinct(s, e, p, table, smem, threadIdx.x, 1024)
+                                             : count_bits<1024>(s, e, p, reinterpret_cast<uint32_t*>(table), min((p.n_cols - 1) / 32 + 1, 2 * kCountMidCap), smem);
+        if (threadIdx.x == 0) p.ncols[w] = nc;
         __syncthreads();
     }
 }
 
 // Few windows to count (all of a small matrix, or the touched ones): one launch for all sizes, where by class the larger
-// windows wait for the small ones' launch and a few workgroups walk their list.  512 workgroups take every 512th window, four
-// at most (neighbouring windows, often alike in size, go to different ones): those of up to kCountTinyCap non-zeros side by
-// side on 256 threads each, the others after them, one by one, on all 1024.  Bound by its longest chain of reads and by
-// launches.  The table is half of k_pre_count_big's, so that two workgroups fit a CU and 2,048 windows run at once (one to a
-// CU: uniform rows lose, 48.4 us by class, 52.4 us here for 32,000 of 60); the bitmap of larger windows then takes two passes
-// for a matrix of 2^20 columns, and wider ones stay with the classes.  Whole preparations, by class / here: power laws of
-// 8,000 rows of 60, 32,000 of 15 and 32,000 of 60: 51.4 / 45.8, 52.0 / 47.4 and 73.0 / 62.5 us, 16,934 of 14 with their
-// product 71.7 / 68.1 us; uniform rows level up to 2,048 windows.  4,000 windows of 64 or 960 non-zeros lose (43.6 / 45.1 and
-// 53.7 / 56.0 us), so the line is at the windows that run at once.
-constexpr int kFewWords = 16384, kFewWindows = 2048, kFewCols = 2 * 32 * kFewWords;
-static_assert(4 * 2 * kCountTinyCap <= kFewWords, "four sets share the table");
-__global__ __launch_bounds__(1024) void k_pre_count_few(Prep p, int32_t n_count)
+// windows wait for the small ones' launch and a few workgroups walk their list.  Windows of up to kCountTinyCap non-zeros take 256 threads each, two to a
+// workgroup.  The larger ones, often neighbours, belong to the first kFewBig workgroups, every kFewBig-th window to each, which look for
+// theirs among up to 32 and take them one by one with a bitmap.  LDS for that grows with the columns up to 32 KB (matrices of up to 2^20 columns: four passes).
+// Bound by its longest chain of reads and by launches, so everything that does not depend on an answer from memory is asked for at once, and neither
+// k_pre_validate (ALL) nor k_pre_select is launched.
+// ALL: every window of the matrix, whose row offsets are checked here as well (k_pre_rows sums the windows itself); else the touched ones, whose sums go to
+// their tiles from here.
+// 16,934 rows: 9.3 us, and 3.0 and 3.8 for the two launches that are gone, -> 6.8 us; 1,000 touched windows of 169,343 rows: 27 -> 15 us, by the largest of
+// them.  (Workgroups of 1024 threads and 64 KB, four windows each and the larger ones after the small: a CU's second workgroup starts 5 us late, and a hash set takes
+// 6 us for 7,700 non-zeros.)  By class the same matrices took 3 to 10 us more, and 4,000 windows lose here: the line is at the windows that run at once.
+constexpr int kFewWindows = 2048, kFewCols = 1 << 20, kFewThreads = 512, kFewBig = 64, kFewMostWords = 8192;
+static_assert(kFewWindows <= 32 * kFewBig && kFewCols <= 4 * 32 * kFewMostWords, "windows to a workgroup, passes");
+template <bool ALL>
+__global__ __launch_bounds__(kFewThreads) void k_pre_count_few(Prep p, int32_t n_count, int words)
 {
-    __shared__ int32_t table[kFewWords];
-    __shared__ int smem[1024 / 64];
-    if (*p.ctl & 7) return;
-    int32_t w[4], n[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int32_t i = (int32_t)(blockIdx.x + j * gridDim.x);
-        w[j] = i >= n_count ? -1 : p.touched ? p.touched[i] : i;
-        n[j] = w[j] < 0 ? 0 : p.nnzw[w[j]];
+    constexpr int SMALL = kFewThreads / 256;
+    extern __shared__ int32_t few_lds[];                        // SMALL * 2 * kCountTinyCap or `words`, whichever is more
+    __shared__ int smem[kFewThreads / 64];
+    const int32_t n_big = min(n_count, kFewBig);
+    const bool big = (int32_t)blockIdx.x < n_big;
+    const int tid = threadIdx.x & 255, group = threadIdx.x >> 8;
+    const int32_t i = big ? (int32_t)blockIdx.x + (int32_t)(threadIdx.x & 31) * n_big : ((int32_t)blockIdx.x - n_big) * SMALL + group;
+    int32_t w = i >= n_count ? -1 : ALL ? i : p.touched[i], s, e;
+    window_span(max(w, 0), p.n_rows, p.rowptr, s, e);
+    if constexpr (ALL) {
+        if (!big && w >= 0) {
+            if (tid < kH) {
+                const int64_t r = min((int64_t)w * kH + tid, (int64_t)p.n_rows - 1);
+                const int32_t a = p.rowptr[r], b = p.rowptr[r + 1];
+                if (a < 0 || b < a) atomicOr(p.ctl, 4);
+            }
+            if (tid == 0) {
+                p.nnzw[w] = e - s;
+                list_window(p, w, e - s, false);
+            }
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if (p.rowptr[0] != 0) atomicOr(p.ctl, 1);
+            if ((int64_t)p.rowptr[p.n_rows] != p.nnz) atomicOr(p.ctl, 2);
+        }
+        // offsets that lead outside the arrays are an error by now, here or at the window that they belong to: nothing is read from there
+        if (s < 0 || e < s || e > p.nnz) s = e = 0;
+    } else if (*p.ctl & 7) {
+        return;
     }
-    const int group = threadIdx.x >> 8;
-    const int32_t own = group == 0 ? w[0] : group == 1 ? w[1] : group == 2 ? w[2] : w[3];
-    const int32_t len = group == 0 ? n[0] : group == 1 ? n[1] : group == 2 ? n[2] : n[3];
-    count_distinct<256>(own, p, table + group * 2 * kCountTinyCap, smem + group * 4, threadIdx.x & 255, own >= 0 && len <= kCountTinyCap);
+    if (w < 0) s = e = 0;
+    auto counted = [&](int32_t window, int32_t n, int nc) {     // by one thread
+        p.ncols[window] = nc;
+        if constexpr (ALL) p.on_matrix[window] = window_route(p, p.mode, nc, n) ? n : 0;
+        else
 #pragma unroll 1
-    for (int j = 0; j < 4; ++j) {
-        if ((j == 0 ? n[0] : j == 1 ? n[1] : j == 2 ? n[2] : n[3]) <= kCountTinyCap) continue;
+            for (int k = 0; k < 2; ++k) {                       // what the old count has added is taken off again
+                unsigned long long v[kWt];
+                const int32_t c = k == 0 ? p.old_ncols[window] : nc;
+                window_sums(window_route(p, p.mode, c, n), c, n, v);
+                add_to_tile(p, window, v, k == 0);
+            }
+    };
+    if (!big) {
+        const bool take = w >= 0 && e - s <= kCountTinyCap;
+        if (!take) s = e = 0;
+        const int nc = count_distinct(s, e, p, few_lds + group * 2 * kCountTinyCap, smem + group * 4, tid, 256);
+        if (take && tid == 0) counted(w, e - s, nc);
+        return;
+    }
+    // (every wave has all of the workgroup's windows in its lanes)
+    uint32_t left = (uint32_t)__ballot(e - s > kCountTinyCap);
+    while (left != 0) {
+        const int q = __builtin_ctz(left);
+        left &= left - 1;
+        const int32_t cs = __builtin_amdgcn_readlane(s, q), ce = __builtin_amdgcn_readlane(e, q), cw = __builtin_amdgcn_readlane(w, q);
         __syncthreads();
-        count_window<kFewWords>(j == 0 ? w[0] : j == 1 ? w[1] : j == 2 ? w[2] : w[3], p, table, smem);
+        const int nc = count_bits<kFewThreads>(cs, ce, p, reinterpret_cast<uint32_t*>(few_lds), words, smem);
+        if (threadIdx.x == 0) counted(cw, ce - cs, nc);
     }
 }
 
-// selection (Section IV-C): z' = c0*H*ncols^2 + c1*(H*ncols - nnzw) + c2*H*ncols ; matrix path iff z' < 0
-__device__ inline int window_route(const Prep& p, int mode, long long nc, long long nz)
-{
-    if (nc <= 0 || mode == HCSPMM_ROUTE_ALL_CSR) return 0;
-    if (mode == HCSPMM_ROUTE_ALL_MFMA) return 1;
-    // |c*| < 2^40 and H*ncols^2 < 2^58: 128-bit integers keep the sign exact
-    const __int128 hn = (__int128)kH * nc;
-    const __int128 z = (__int128)p.c0 * hn * nc + (__int128)p.c1 * (hn - nz) + (__int128)p.c2 * hn;
-    return z < 0 ? 1 : 0;
-}
-
-// windows on the matrix path | ... of the wave-per-window kernel | medium | wide, 16 bits each (a tile has 64 windows, a
-// group of tiles 16,384)
-__device__ inline unsigned long long window_counts(int r, long long nc)
-{
-    if (!r) return 0ull;
-    return 1ull | (nc <= kMfmaSmallMaxCols ? 1ull << 16 : nc <= kMfmaMidMaxCols ? 1ull << 32 : 1ull << 48);
-}
-
-// Per tile: [0] distinct columns; [1] non-zeros, [2] window counts, [3] columns of wide windows on the matrix path under
-// the plan's own mode; [4..6] the same with every window there (what the launch guard may decide for)
 __global__ __launch_bounds__(256) void k_pre_select(Prep p)
 {
-    if (*p.ctl) return;
     const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (tile >= p.n_tiles) return;
     const int32_t w = tile * kTileWindows + (threadIdx.x & 63);
+    unsigned long long v[kWt];
     const long long nc = w < p.W ? p.ncols[w] : 0, nz = w < p.W ? p.nnzw[w] : 0;
-    unsigned long long v[8] = {(unsigned long long)nc, 0, 0, 0, 0, 0, 0, 0};
+    window_sums(window_route(p, p.mode, nc, nz), nc, nz, v);
+    if (*p.ctl) return;
 #pragma unroll
-    for (int set = 0; set < 2; ++set) {
-        const int r = window_route(p, set == 0 ? p.mode : HCSPMM_ROUTE_ALL_MFMA, nc, nz);
-        v[1 + 3 * set] = r ? (unsigned long long)nz : 0ull;
-        v[2 + 3 * set] = window_counts(r, nc);
-        v[3 + 3 * set] = r && nc > kMfmaMidMaxCols ? (unsigned long long)nc : 0ull;
-        if (set == 0 && r) v[7] = (unsigned long long)nc;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = wave_sum(v[i]);
+    for (int i = 0; i < kWt; ++i) v[i] = wave_sum_u64(v[i]);
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) p.wt[(int64_t)tile * kWt + i] = v[i];
+        for (int i = 0; i < kWt; ++i) p.wt[(int64_t)tile * kWt + i] = v[i];
 }
 
 // Launch guard: a path whose share cannot repay a kernel launch of its own joins the other path.
@@ -886,56 +1013,85 @@ __device__ inline unsigned long long seg_counts(const RowClass& c)
     return (unsigned long long)c.n_seg | (unsigned long long)(c.n_seg > 1 ? c.n_seg : 0) << 32;
 }
 
+// Both kernels of the rows are a few trips to memory and sums over the workgroup: what does not depend on an answer is asked for first, and sums are DPP moves
+// (169,343 rows: 6.3 and 7.5 us with shuffles and one trip after the other, 4.9 and 5.7 so; with a thread per row, 16 waves to a CU that wait for each other at every
+// sum, 6.7 and 11).
+// DIRECT: up to kFewWindows windows, whose sums every workgroup forms itself, and those of its own tile for the kernels behind it.
+template <bool DIRECT>
 __global__ __launch_bounds__(256) void k_pre_rows(Prep p)
 {
-    __shared__ unsigned long long smem[16];
+    __shared__ unsigned long long smem[4 * 4];
     __shared__ uint8_t s_route[kTileWindows], s_wide[kTileWindows];
-    if (*p.ctl) return;
-    const int tile = blockIdx.x;
-    unsigned long long all[3] = {0, 0, 0};                      // columns in front of the tile, from it on; non-zeros on the matrix path
-    for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, tile, threadIdx.x, 256, [&](const unsigned long long* v, bool in_front) {
-        all[2] += v[1];
-        all[in_front ? 0 : 1] += v[0];
-    });
-    block_sums_u64<3>(all, smem);
-    const unsigned long long before = all[0];
-    const int mode = effective_mode(p, all[2]);
-    if (threadIdx.x < kTileWindows) {
-        const int32_t w = tile * kTileWindows + threadIdx.x;
-        const long long nc = w < p.W ? p.ncols[w] : 0, nz = w < p.W ? p.nnzw[w] : 0;
-        const int r = window_route(p, mode, nc, nz);
-        s_route[threadIdx.x] = (uint8_t)r;
-        s_wide[threadIdx.x] = nc > kMfmaSmallMaxCols ? 1 : 0;
-        unsigned long long inc = (unsigned long long)nc;
+    const int tile = blockIdx.x, t = threadIdx.x;
+    const int64_t i0 = min((int64_t)tile * kTileRows + 4 * t, (int64_t)p.n_rows);
+    int32_t start[5];
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const unsigned long long t = __shfl_up(inc, off, 64);
-            if ((int)threadIdx.x >= off) inc += t;
+    for (int j = 0; j < 5; ++j) start[j] = p.rowptr[min(i0 + j, (int64_t)p.n_rows)];
+    const int32_t w = tile * kTileWindows + (t & 63);
+    const long long nc = w < p.W ? p.ncols[w] : 0, nz = w < p.W ? p.nnzw[w] : 0;
+    const int own = window_route(p, p.mode, nc, nz);            // under the plan's own mode
+    unsigned long long all[3] = {0, 0, 0};                      // columns in front of the tile, from it on; non-zeros on the matrix path
+    if constexpr (DIRECT) {
+        int32_t c[kFewWindows / 256], on[kFewWindows / 256];
+#pragma unroll
+        for (int j = 0; j < kFewWindows / 256; ++j) {
+            const int32_t i = min(t + 256 * j, p.W - 1);
+            c[j] = p.ncols[i];
+            on[j] = p.on_matrix[i];
         }
+        if (*p.ctl) return;
+#pragma unroll
+        for (int j = 0; j < kFewWindows / 256; ++j) {
+            const int32_t i = t + 256 * j;
+            if (i >= p.W) break;
+            all[2] += (unsigned long long)on[j];
+            all[i < tile * kTileWindows ? 0 : 1] += (unsigned long long)c[j];
+        }
+        unsigned long long v[kWt];                              // two of the tile's sums to a wave
+        window_sums(own, nc, nz, v);
+        const int wave = t >> 6;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const unsigned long long sum = wave_sum_u64(wave == 0 ? v[i] : wave == 1 ? v[2 + i] : wave == 2 ? v[4 + i] : v[6 + i]);
+            if ((t & 63) == 0) p.wt[(int64_t)tile * kWt + 2 * wave + i] = sum;
+        }
+    } else {
+        for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, tile, t, 256, [&](const unsigned long long* v, bool in_front) {
+            all[2] += v[1];
+            all[in_front ? 0 : 1] += v[0];
+        });
+        if (*p.ctl) return;
+    }
+    block_sums_u64<3>(all, smem);
+    const int mode = effective_mode(p, all[2]);
+    if (t < kTileWindows) {
+        const int r = mode == p.mode ? own : mode == HCSPMM_ROUTE_ALL_MFMA && nc > 0;
+        s_route[t] = (uint8_t)r;
+        s_wide[t] = nc > kMfmaSmallMaxCols ? 1 : 0;
+        const unsigned long long inc = wave_scan_u64((unsigned long long)nc);
         if (w < p.W) {
             p.route[w] = (uint8_t)r;
-            p.wptr[w] = (int64_t)(before + inc - (unsigned long long)nc);
-            if (w == p.W - 1) p.wptr[p.W] = (int64_t)(before + inc);
+            p.wptr[w] = (int64_t)(all[0] + inc - (unsigned long long)nc);
+            if (w == p.W - 1) p.wptr[p.W] = (int64_t)(all[0] + inc);
         }
-        if (p.W == 0 && threadIdx.x == 0) p.wptr[0] = 0;
+        if (p.W == 0 && t == 0) p.wptr[0] = 0;
     }
     __syncthreads();
     const int all_scalar = scalar_form(p, (int64_t)(all[0] + all[1]));
-    if (tile == 0 && threadIdx.x == 0) p.ctl[7] = all_scalar;
+    if (tile == 0 && t == 0) p.ctl[7] = all_scalar;
+    const int route = all_scalar != 0 ? 0 : s_route[t / (kH / 4)], wide = s_wide[t / (kH / 4)];
     unsigned long long sum[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int rl = threadIdx.x * 4 + j;
-        const int64_t i = (int64_t)tile * kTileRows + rl;
-        if (i >= p.n_rows) break;
-        const RowClass c = row_class(p, p.rowptr[i + 1] - p.rowptr[i], all_scalar != 0 ? 0 : s_route[rl / kH], s_wide[rl / kH]);
+        if (i0 + j >= p.n_rows) break;
+        const RowClass c = row_class(p, start[j + 1] - start[j], route, wide);
         sum[0] += (unsigned long long)c.is_short | (unsigned long long)c.is_mid << 32;
         sum[1] += (unsigned long long)c.rest | (unsigned long long)(c.n_seg > 1) << 32;
         sum[2] += seg_counts(c);
         sum[3] += (unsigned long long)c.len_long;
     }
     block_sums_u64<4>(sum, smem);
-    if (threadIdx.x == 0)
+    if (t == 0)
 #pragma unroll
         for (int i = 0; i < 4; ++i) p.rt[(int64_t)tile * kRt + i] = sum[i];
 }
@@ -943,37 +1099,54 @@ __global__ __launch_bounds__(256) void k_pre_rows(Prep p)
 // Fills the row tables whose pointers are set; one workgroup behind the last tile's writes the totals (when p.out is set).
 __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
 {
-    __shared__ unsigned long long smem[4 * 7];
-    const int tile = blockIdx.x;
+    __shared__ unsigned long long smem[4 * 11];
+    const int tile = blockIdx.x, t = threadIdx.x;
     const bool last = tile == p.n_tiles;
-    if (*p.ctl) {
-        if (last && threadIdx.x == 0 && p.out) p.out->err = *p.ctl;
-        return;
-    }
-    unsigned long long front[3] = {0, 0, 0};                    // short | mid, rest | multi, segments | partial rows in front of the tile
-    for_sums<kRt, false>(p.rt, p.rg, p.n_tiles, tile, threadIdx.x, 256, [&](const unsigned long long* v, bool) { front[0] += v[0]; front[1] += v[1]; front[2] += v[2]; });
-    block_sums_u64<3>(front, smem);
-    const unsigned long long sm = front[0], rm = front[1], seg = front[2];
-    RowClass c[4];
-    int32_t start[5];
-    unsigned long long a = 0, b = 0;
-    const int64_t i0 = min((int64_t)tile * kTileRows + threadIdx.x * 4, (int64_t)p.n_rows);
+    const int64_t i0 = min((int64_t)tile * kTileRows + 4 * t, (int64_t)p.n_rows);
     const int32_t w = (int32_t)(i0 / kH);
-    const int route = w < p.W && p.ctl[7] == 0 ? p.route[w] : 0, wide = w < p.W ? (p.ncols[w] > kMfmaSmallMaxCols ? 1 : 0) : 0;
+    int32_t start[5];
 #pragma unroll
     for (int j = 0; j < 5; ++j) start[j] = p.rowptr[min(i0 + j, (int64_t)p.n_rows)];
+    const int32_t own_route = w < p.W ? p.route[w] : 0, own_cols = w < p.W ? p.ncols[w] : 0;
+    unsigned long long front[3] = {0, 0, 0};                    // short | mid, rest | multi, segments | partial rows in front of the tile
+    for_sums<kRt, false>(p.rt, p.rg, p.n_tiles, tile, t, 256, [&](const unsigned long long* v, bool) { front[0] += v[0]; front[1] += v[1]; front[2] += v[2]; });
+    unsigned long long v[11] = {};                              // the last workgroup's: distinct columns, long rows' non-zeros; the tiles' sums of windows in both sets
+    if (last && p.out) {
+        for_sums<kRt, true>(p.rt, p.rg, p.n_tiles, p.n_tiles, t, 256, [&](const unsigned long long* u, bool) { v[1] += u[3]; });
+        for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, p.n_tiles, t, 256, [&](const unsigned long long* u, bool) {
+            v[0] += u[0];
+            v[6] += u[7];
+#pragma unroll
+            for (int set = 0; set < 2; ++set) {
+                const unsigned long long n = u[2 + 3 * set];
+                v[2 + 5 * set] += u[1 + 3 * set];
+                v[3 + 5 * set] += (n & 0xffffull) | (n >> 16 & 0xffffull) << 32;
+                v[4 + 5 * set] += (n >> 32 & 0xffffull) | (n >> 48) << 32;
+                v[5 + 5 * set] += u[3 + 3 * set];
+            }
+        });
+    }
+    const int32_t all_scalar = p.ctl[7];
+    if (*p.ctl) {
+        if (last && t == 0 && p.out) p.out->err = *p.ctl;
+        return;
+    }
+    block_sums_u64<3>(front, smem);
+    const unsigned long long sm = front[0], rm = front[1], seg = front[2];
+    const int route = all_scalar == 0 ? own_route : 0, wide = own_cols > kMfmaSmallMaxCols ? 1 : 0;
+    RowClass c[4];
+    unsigned long long at[2] = {0, 0};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         c[j] = RowClass{0, 0, 0, 0, 0};
         if (i0 + j < p.n_rows) c[j] = row_class(p, start[j + 1] - start[j], route, wide);
-        a += row_counts(c[j]);
-        b += seg_counts(c[j]);
+        at[0] += row_counts(c[j]);
+        at[1] += seg_counts(c[j]);
     }
-    const unsigned long long ea = block_scan_u64(a, smem);
-    const unsigned long long eb = block_scan_u64(b, smem);
-    uint32_t n_short = (uint32_t)sm + (uint32_t)(ea & 0xffffull), n_mid = (uint32_t)(sm >> 32) + (uint32_t)(ea >> 16 & 0xffffull);
-    uint32_t n_rest = (uint32_t)rm + (uint32_t)(ea >> 32 & 0xffffull), n_multi = (uint32_t)(rm >> 32) + (uint32_t)(ea >> 48);
-    uint32_t n_seg = (uint32_t)seg + (uint32_t)eb, n_slot = (uint32_t)(seg >> 32) + (uint32_t)(eb >> 32);
+    block_scans_u64<2>(at, smem);
+    uint32_t n_short = (uint32_t)sm + (uint32_t)(at[0] & 0xffffull), n_mid = (uint32_t)(sm >> 32) + (uint32_t)(at[0] >> 16 & 0xffffull);
+    uint32_t n_rest = (uint32_t)rm + (uint32_t)(at[0] >> 32 & 0xffffull), n_multi = (uint32_t)(rm >> 32) + (uint32_t)(at[0] >> 48);
+    uint32_t n_seg = (uint32_t)seg + (uint32_t)at[1], n_slot = (uint32_t)(seg >> 32) + (uint32_t)(at[1] >> 32);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int32_t i = (int32_t)(i0 + j);
@@ -983,6 +1156,7 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
         const int ns = c[j].n_seg;
         if (ns == 0) continue;
         if (p.segs)
+#pragma unroll 1
             for (int q = 0; q < ns; ++q) {
                 Segment sg;
                 sg.row = i;
@@ -1003,34 +1177,25 @@ __global__ __launch_bounds__(256) void k_pre_fill(Prep p)
         }
     }
     if (!last || !p.out) return;
-    // what is in front of the place behind the last tile are the row totals; the window totals come from the tile sums too
-    unsigned long long v[7] = {0, 0, 0, 0, 0, 0, 0}, on_matrix = 0;
-    for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, p.n_tiles, threadIdx.x, 256, [&](const unsigned long long* u, bool) { on_matrix += u[1]; });
-    const int set = counts_set(p, effective_mode(p, block_sum_u64(on_matrix, smem)));
-    for_sums<kRt, true>(p.rt, p.rg, p.n_tiles, p.n_tiles, threadIdx.x, 256, [&](const unsigned long long* u, bool) { v[1] += u[3]; });
-    for_sums<kWt, true>(p.wt, p.wg, p.n_tiles, p.n_tiles, threadIdx.x, 256, [&](const unsigned long long* u, bool) {
-        v[0] += u[0];
-        if (set < 0) return;
-        const unsigned long long n = u[2 + 3 * set];
-        v[2] += u[1 + 3 * set];
-        v[3] += (n & 0xffffull) | (n >> 16 & 0xffffull) << 32;
-        v[4] += (n >> 32 & 0xffffull) | (n >> 48) << 32;
-        v[5] += u[3 + 3 * set];
-        v[6] += u[set == 0 ? 7 : 0];
-    });
-    block_sums_u64<7>(v, smem);
-    if (threadIdx.x == 0) {
-        PrepTotals t{};
-        t.total_ncols = (int64_t)v[0]; t.nnz_long = (int64_t)v[1]; t.nnz_mfma = (int64_t)v[2]; t.wide_cols = (int64_t)v[5]; t.mfma_cols = (int64_t)v[6];
-        t.n_mfma = (int32_t)v[3]; t.n_mfma_small = (int32_t)(v[3] >> 32);
-        t.n_mfma_mid = (int32_t)v[4]; t.n_mfma_big = (int32_t)(v[4] >> 32);
-        t.n_short = (int32_t)n_short; t.n_mid = (int32_t)n_mid; t.n_rest = (int32_t)n_rest; t.n_multi = (int32_t)n_multi;
-        t.n_segs = (int32_t)n_seg; t.n_slots = (int64_t)n_slot;
-        t.n_big_list = p.ctl[1]; t.n_huge_list = p.ctl[2];
-        t.all_scalar = p.ctl[7];
-        t.sample_distinct = p.ctl[8];
-        t.err = 0;
-        *p.out = t;
+    // what is in front of the place behind the last tile are the row totals
+    block_sums_u64<11>(v, smem);
+    const int set = counts_set(p, effective_mode(p, v[2]));
+    if (t == 0) {
+        PrepTotals o{};
+        o.total_ncols = (int64_t)v[0]; o.nnz_long = (int64_t)v[1];
+        if (set >= 0) {
+            const unsigned long long lo = set == 0 ? v[3] : v[8], hi = set == 0 ? v[4] : v[9];
+            o.nnz_mfma = (int64_t)(set == 0 ? v[2] : v[7]); o.wide_cols = (int64_t)(set == 0 ? v[5] : v[10]); o.mfma_cols = (int64_t)(set == 0 ? v[6] : v[0]);
+            o.n_mfma = (int32_t)lo; o.n_mfma_small = (int32_t)(lo >> 32);
+            o.n_mfma_mid = (int32_t)hi; o.n_mfma_big = (int32_t)(hi >> 32);
+        }
+        o.n_short = (int32_t)n_short; o.n_mid = (int32_t)n_mid; o.n_rest = (int32_t)n_rest; o.n_multi = (int32_t)n_multi;
+        o.n_segs = (int32_t)n_seg; o.n_slots = (int64_t)n_slot;
+        o.n_big_list = p.ctl[1]; o.n_huge_list = p.ctl[2];
+        o.all_scalar = p.ctl[7];
+        o.sample_distinct = p.ctl[8];
+        o.err = 0;
+        *p.out = o;
     }
 }
 
@@ -1070,18 +1235,32 @@ __global__ __launch_bounds__(256) void k_pre_windows(Prep p, int32_t* __restrict
     else big[(uint32_t)(hi >> 32) + (uint32_t)(ex >> 48)] = w;
 }
 
+// Whether k_pre_count_few counts the windows.
+static bool prep_counts_few(const Prep& p, int32_t n_touched)
+{
+    const int64_t n_count = p.touched ? n_touched : p.W;
+    return p.features && n_count > 0 && n_count <= kFewWindows && p.n_cols <= kFewCols;
+}
+size_t prep_zeros(const Prep& p, int32_t n_touched) { return p.touched && prep_counts_few(p, n_touched) ? (size_t)kWt * p.n_tiles * sizeof(unsigned long long) : 0; }
+
 hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
 {
     Prep p = p_;
     const int64_t n_count = p.touched ? n_touched : p.W;
-    const bool few = n_count <= kFewWindows && p.n_cols <= kFewCols;
+    const bool few = prep_counts_few(p, n_touched);
     p.big_takes_1k = n_count <= kBigTakes1kWindows ? 1 : 0;
-    if (few) p.count_1k = nullptr;                              // k_pre_count_few reads no lists
-    hipLaunchKernelGGL(k_pre_validate, dim3((unsigned)(((int64_t)p.n_rows + 1 + 255) / 256)), dim3(256), 0, s, p);
+    if (few) p.on_matrix = p.count_1k;                          // k_pre_count_few has no lists
+    const dim3 grid_rows((unsigned)(((int64_t)p.n_rows + 1 + 255) / 256));
+    if (few && p.touched) hipLaunchKernelGGL(k_pre_validate<true>, grid_rows, dim3(256), 0, s, p);
+    else if (!few) hipLaunchKernelGGL(k_pre_validate<false>, grid_rows, dim3(256), 0, s, p);
     if (p.features && p.W > 0) {
         if (few) {
-            if (n_count > 0)
-                hipLaunchKernelGGL(k_pre_count_few, dim3((unsigned)std::min<int64_t>(n_count, kFewWindows / 4)), dim3(1024), 0, s, p, (int32_t)n_count);
+            constexpr int per = kFewThreads / 256;
+            const int words = std::min((p.n_cols - 1) / 32 + 1, kFewMostWords);
+            const size_t lds = (size_t)std::max(words, per * 2 * kCountTinyCap) * sizeof(int32_t);
+            const dim3 grid((unsigned)(std::min<int64_t>(n_count, kFewBig) + (n_count + per - 1) / per));
+            if (p.touched) hipLaunchKernelGGL(k_pre_count_few<false>, grid, dim3(kFewThreads), lds, s, p, (int32_t)n_count, words);
+            else hipLaunchKernelGGL(k_pre_count_few<true>, grid, dim3(kFewThreads), lds, s, p, (int32_t)n_count, words);
         } else {
             if (n_count > 0) hipLaunchKernelGGL(k_pre_count, dim3((unsigned)n_count), dim3(256), 0, s, p);
             // windows beyond the small set's capacity; how many there are only the device knows, so the grids are bounded by
@@ -1105,10 +1284,11 @@ hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
         if (blocks > 65536) blocks = 65536;
         hipLaunchKernelGGL(k_pre_sorted, dim3((unsigned)blocks), dim3(256), 0, s, p);
     }
-    hipLaunchKernelGGL(k_pre_select, dim3((unsigned)(p.n_tiles + 3) / 4), dim3(256), 0, s, p);
+    if (!few) hipLaunchKernelGGL(k_pre_select, dim3((unsigned)(p.n_tiles + 3) / 4), dim3(256), 0, s, p);
     const int32_t groups = group_count(p.n_tiles);
     if (groups) hipLaunchKernelGGL(k_group_sums<kWt>, dim3((unsigned)groups), dim3(256), 0, s, p.n_tiles, p.wt, p.wg);
-    hipLaunchKernelGGL(k_pre_rows, dim3((unsigned)p.n_tiles), dim3(256), 0, s, p);
+    if (few && !p.touched) hipLaunchKernelGGL(k_pre_rows<true>, dim3((unsigned)p.n_tiles), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(k_pre_rows<false>, dim3((unsigned)p.n_tiles), dim3(256), 0, s, p);
     if (groups) hipLaunchKernelGGL(k_group_sums<kRt>, dim3((unsigned)groups), dim3(256), 0, s, p.n_tiles, p.rt, p.rg);
     hipLaunchKernelGGL(k_pre_fill, dim3((unsigned)p.n_tiles + 1), dim3(256), 0, s, p);
     return hipGetLastError();

@@ -240,3 +240,26 @@ def test_updates_that_touch_every_size_class(n, every):
     a, b = hc.hcspmm_plan_export(plan), hc.hcspmm_plan_export(hc.hcspmm_prepare(n, 3005, rp, c2, va))
     for k in KEYS:
         assert np.array_equal(a[k], b[k]), k
+
+
+# the launch for few windows: fewer of them than the workgroups for the larger ones, as many, and up to 32 to each of these; columns around one, two and
+# four passes of their bitmap
+@pytest.mark.parametrize("n,n_cols", [(16 * 63, 1 << 18), (16 * 64, (1 << 18) + 1), (16 * 65, 65_537), (2047 * 16 + 3, 1 << 18), (3000, 3 << 18), (3000, (3 << 18) + 1)])
+def test_larger_windows_of_few(n, n_cols):
+    check_plan(mixed_sizes(n, n, n_cols=n_cols), 3, sel_coef=[1, 300, -328])
+
+
+@pytest.mark.parametrize("row", [0, 1, 700, 1599, 1600])
+@pytest.mark.parametrize("value", [-5, 1 << 30])
+def test_unsound_offsets_of_few_windows(row, value):
+    """No offset leads a window's reads outside the arrays, and the error is the offsets', whatever the columns hold."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    g = ragged(np.full(1600, 90), 300, row)
+    col = g.colind.copy()
+    col[::997] = 300
+    rp, ci, va = device_graph(CSRGraph(1600, 300, g.rowptr, col, g.vals))
+    rp[row] = value
+    with pytest.raises(hc.HcspmmError) as e:
+        hc.hcspmm_prepare(1600, 300, rp, ci, va)
+    assert e.value.status == hc.HCSPMM_EBADCSR and "rowptr" in str(e.value) and "column" not in str(e.value)
