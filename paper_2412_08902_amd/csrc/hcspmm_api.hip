@@ -1214,7 +1214,6 @@ hcspmm_status hcspmm_plan_update(hcspmm_plan* plan, int64_t nnz, const int32_t* 
         for (int32_t w = 0; w < plan->W; ++w)
             if (mark[(size_t)w]) touched.push_back(w);
     }
-    HC_HIP(hipStreamSynchronize(s));                             // calls that still use the old arrays are done
     hcspmm_plan fresh;
     hcspmm_status st = init_plan_header(&fresh, plan->n_rows, plan->n_cols, nnz, d_rowptr, d_colind, d_vals, plan->opt);
     if (st != HCSPMM_OK) return st;
@@ -1236,10 +1235,13 @@ hcspmm_status hcspmm_plan_update(hcspmm_plan* plan, int64_t nnz, const int32_t* 
     }
     const bool nothing_changed = touched.empty() && nnz == plan->nnz && plan->features_complete;
     if (nothing_changed) {
+        HC_HIP(hipStreamSynchronize(s));                         // calls that still use the old arrays are done
         // same structure: only the borrowed pointers move
         plan->rowptr = d_rowptr; plan->colind = d_colind; plan->vals = d_vals;
         return HCSPMM_OK;
     }
+    // (build_plan waits for the stream before it returns a plan, so calls that use the old arrays are done by then.  Waiting for them here as
+    // well left the GPU idle while this call allocates and launches: 1,000 rows of 169,343 changed behind a product, twice: 328 -> 297 us.)
     st = build_plan(&fresh, s, incremental ? &carry : nullptr);
     if (st != HCSPMM_OK) return st;                              // the old plan is untouched and still valid for the old arrays
     if ((st = reserve_row_sums(&fresh, plan->acc_rows_elems)) != HCSPMM_OK) { free_plan_arrays(&fresh); return st; }
