@@ -245,7 +245,12 @@ template <int VEC> __device__ inline void out_store(float* __restrict__ Y, int y
 {
     float y[VEC];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) y[i] = relu ? fmaxf(x[i], 0.f) : x[i];
+    for (int i = 0; i < VEC; ++i) y[i] = x[i];
+    if (relu) {
+        asm volatile("");                                       // (a branch: to select costs three instructions a value with or without an activation)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) y[i] = fmaxf(x[i], 0.f);
+    }
     if (y_dtype == HCSPMM_F32) {
         float* __restrict__ p = Y + off;
         if constexpr (VEC == 8) {
@@ -285,6 +290,7 @@ struct CsrHints {
     bool scattered;       // neighbouring rows are known to share few columns
     int32_t long_row;     // rows with more non-zeros are cut into segments
     bool beside;          // the matrix path runs at the same time on streams of its own
+    int64_t entries;      // non-zeros of the matrix, which indices of non-zeros stay below
 };
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,

@@ -980,7 +980,7 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
             if (q > 0) { b.rowptr = p->panel_split + (int64_t)(q - 1) * p->n_rows; b.acc = sums; b.ldacc = ld_sums; }
             b.rowend = final_panel ? p->rowptr + 1 : p->panel_split + (int64_t)q * p->n_rows;
             if (!final_panel) { b.Y = sums; b.ldy = ld_sums; b.y_dtype = HCSPMM_F32; b.relu = 0; }
-            const CsrHints hints{t.nnz, p->n_rows, true, p->long_row, false};
+            const CsrHints hints{t.nnz, p->n_rows, true, p->long_row, false, p->nnz};
             HC_HIP(launch_csr(b, t.n_segs, p->panel[q].segs, partial, t.n_mid, p->panel[q].mid_rows, p->n_rows, nullptr, nullptr, p->mid_row,
                               hints, stream));
             HC_HIP(launch_reduce_partials(b, t.n_multi, p->panel[q].multi, partial, stream));
@@ -1025,7 +1025,7 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
     const int64_t nnz_scalar = p->nnz - (p->scalar_exec ? 0 : p->nnz_mfma), n_scalar = p->scalar_exec ? p->W : p->n_csr;
     const int64_t cols_scalar = p->total_ncols - (p->scalar_exec ? 0 : p->mfma_ncols);
     const bool scattered = !p->local && (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * cols_scalar > 6 * nnz_scalar);
-    const CsrHints hints{nnz_scalar, n_scalar * kH, scattered, p->long_row, side && has_csr};
+    const CsrHints hints{nnz_scalar, n_scalar * kH, scattered, p->long_row, side && has_csr, p->nnz};
     const uint8_t* route = p->scalar_exec || p->n_mfma == 0 ? nullptr : p->route;
     if (upd && !windows_only)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, n_scalar > 0 ? p->n_rows : 0, nullptr,
