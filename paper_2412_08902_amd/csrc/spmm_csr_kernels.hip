@@ -478,6 +478,45 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, 256), amdgpu_waves_per_
     csr_body<G>(wk, a, red);
 }
 
+// The launch of a matrix of few rows, all of them mid or long rows (see launch_csr): what a call passes is held to 112 bytes.  Beyond that a
+// launch costs the host 0.9 us more (2.7 us up to 112 bytes of arguments, 3.6 from 120 on, kernels of nothing), and these calls are little else: 2,708 rows of 5, 32
+// columns, calls in a row 4.0 -> 3.5 us (4.8 -> 4.6 through the Python binding).
+struct CsrFewRows {
+    const int32_t *rowptr, *colind;
+    const float* vals;
+    const void* X;
+    float* Y;
+    const Segment* segs;
+    float* partial;
+    int32_t ldx, ldy, n_rows, d, long_row, n_segs;
+    uint32_t seg_blocks, mid_blocks;
+    int32_t run_mid, slice_w;
+    uint8_t n_slices, y_dtype, relu, y_vec;
+};
+static_assert(sizeof(CsrFewRows) <= 112, "arguments of a cheap launch");
+template <class G>
+__global__ __launch_bounds__(256, G::WAVES) void k_csr_few_rows(CsrFewRows r)
+{
+    __shared__ float red[256 * G::N];
+    SpmmArgs a{};
+    a.n_rows = r.n_rows; a.rowptr = r.rowptr; a.colind = r.colind; a.vals = r.vals; a.X = r.X; a.ldx = r.ldx; a.d = r.d;
+    a.Y = r.Y; a.ldy = r.ldy; a.relu = r.relu; a.y_dtype = r.y_dtype;
+    CsrWork wk{};
+    wk.n_segs = r.n_segs; wk.segs = r.segs; wk.partial = r.partial; wk.n_mid = r.n_rows; wk.mid_row = r.long_row; wk.y_vec = r.y_vec;
+    uint32_t b = blockIdx.x;
+    int slice;
+    if (b < r.seg_blocks * r.n_slices) {
+        b = csr_block(blockIdx.x, b, r.seg_blocks, -1, r.n_slices, slice);
+        const int c0 = slice * r.slice_w;
+        csr_long_body<G>(b, c0, min(a.d, c0 + r.slice_w), wk, red, a);
+        return;
+    }
+    b -= r.seg_blocks * r.n_slices;
+    b = csr_block(blockIdx.x, b, r.mid_blocks, r.run_mid, r.n_slices, slice);
+    const int c0 = slice * r.slice_w;
+    csr_mid_body<G>(b, c0, min(a.d, c0 + r.slice_w), wk, a);
+}
+
 // The same launch with the update stage fused into the short rows; long and mid rows write their
 // aggregated rows to a.Y (the workspace Z) and are finished by k_update_rest.
 // (Four waves per SIMD for 16-bit rows of 129 to 256 bytes, whose form the compiler else gives a few registers too many: 1.2 M rows of
@@ -814,7 +853,8 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     // costs more than the shorter chains save (a group / a wave per row, us, fp32: 2,000 rows of 11, 96 columns: 6.7 / 5.1;
     // 3,000 of 21, 160 columns in two slices: 7.8 / 10.3; communities of 20, 7,936 rows, 128 columns: 7.4 / 11.1; bf16, 128
     // columns: 4,000 of 11: 6.6 / 5.9; 6,000 of 13: 7.1 / 6.7; 8,000 of 31: 8.1 / 8.9).
-    if (n_items > 0 && (int64_t)a.n_rows * n_slices <= (a.x_dtype == HCSPMM_F32 ? 4096 : 6144)) {
+    const bool few_rows = n_items > 0 && (int64_t)a.n_rows * n_slices <= (a.x_dtype == HCSPMM_F32 ? 4096 : 6144);
+    if (few_rows) {
         wk.n_mid = a.n_rows;
         wk.mid_rows = nullptr;
         wk.mid_row = hints.long_row;
@@ -848,6 +888,15 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
         } else if (a.x_dtype == HCSPMM_F32) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 0, 4) }
         else if (a.x_dtype == HCSPMM_BF16) { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 1, 8) }
         else { HC_CSR_PANEL_DISPATCH(HC_LAUNCH_PANEL, 2, 8) }
+        return hipGetLastError();
+    }
+    if (few_rows && most == 0 && !sh.wide && !route && !a.acc && a.ldx <= INT32_MAX && a.ldy <= INT32_MAX && wk.grid.n_slices <= 255) {
+        const CsrFewRows r{a.rowptr, a.colind, a.vals, a.X, a.Y, segs, partial, (int32_t)a.ldx, (int32_t)a.ldy, a.n_rows, a.d, wk.mid_row, n_segs,
+                           wk.grid.seg_blocks, wk.grid.mid_blocks, wk.grid.run_mid, wk.grid.slice_w, (uint8_t)wk.grid.n_slices, (uint8_t)a.y_dtype,
+                           (uint8_t)(a.relu != 0), (uint8_t)wk.y_vec};
+#define HC_LAUNCH_FEW_ROWS(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_csr_few_rows<Gather<XK, V, NVV, L, GR, false>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, r)
+        HC_CSR_DISPATCH(HC_LAUNCH_FEW_ROWS)
+#undef HC_LAUNCH_FEW_ROWS
         return hipGetLastError();
     }
     if (most > 0) {

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import assert_close, gpu_spmm, oracle_pair
+from gpu_util import assert_close, device_graph, gpu_spmm, oracle_pair
 from workloads import tiny_random_csr, to_bf16_bits, to_f16_bits
 from workloads.graphs import CSRGraph
 
@@ -169,3 +169,26 @@ def test_whole_rows_of_several_vectors(kind, degree, d, pad):
         Y, _ = gpu_spmm(g, X, 1, pad_x=pad, pad_y=1, x_bits=kind)
         ref, bound = oracle_pair(g, X, x_dtype=code)
     assert_close(Y, ref, bound, 1e-5, "%s d=%d degree=%d" % (kind, d, degree))
+
+
+# both sides of the line up to which every row takes a wave (rows times slices), with rows of several segments, a relu and a pitched Y
+@pytest.mark.parametrize("kind,n,d", [(None, 4096, 32), (None, 4097, 32), (None, 2048, 256), (None, 2049, 256), ("bf16", 6144, 64), ("bf16", 6145, 64), (None, 600, 1030)])
+def test_few_rows_with_long_ones(kind, n, d):
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    lengths = np.full(n, 3, np.int64)
+    lengths[[1, n // 2, n - 1]] = [5000, 300, 2049]
+    rng = np.random.default_rng(n + d)
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    g = CSRGraph(n, 3000, rowptr, rng.integers(0, 3000, rowptr[-1]).astype(np.int32), rng.standard_normal(rowptr[-1]).astype(np.float32))
+    X = rng.standard_normal((g.n_cols, d)).astype(np.float32)
+    bits = X if kind is None else to_bf16_bits(X)
+    Xd = torch.from_numpy(bits).cuda() if kind is None else torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16)
+    plan = hc.hcspmm_prepare(n, g.n_cols, *device_graph(g), route_mode=1, d_hint=d, mfma_dtype=0 if kind is None else 1)
+    Y = torch.full((n, d + 3), -7.0, device="cuda")
+    hc.hcspmm_spmm(plan, Xd, Y[:, :d])
+    torch.cuda.synchronize()
+    plan.destroy()
+    ref, bound = oracle_pair(g, bits, **({} if kind is None else {"x_dtype": oracle.DT_BF16}))
+    assert_close(Y[:, :d].cpu().numpy().astype(np.float64), ref, bound, 1e-5, "n=%d d=%d" % (n, d))
+    assert bool((Y[:, d:] == -7.0).all())
