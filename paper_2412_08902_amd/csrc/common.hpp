@@ -209,6 +209,7 @@ struct SpmmArgs {
     int32_t y_dtype;
     const float* acc;     // scalar path: fp32 rows (pitch ldacc) added to the result before the activation and the store; may be Y
     int64_t ldacc;
+    const uint2* x_mask;  // scalar path, where csr_mask_usable says so: which elements of X count (launch_relu_bits), the others are 0
 };
 
 // Update stage of the aggregate-then-update layer: Y = act(Z W) for aggregated rows Z (Section V-A).
@@ -295,6 +296,7 @@ struct CsrHints {
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
                       int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd = nullptr);
+bool csr_mask_usable(const SpmmArgs& a, const CsrHints& hints);     // launch_csr may be given a.x_mask
 bool csr_panels_usable(const SpmmArgs& a);   // the launch has kernels that add to rows of sums for this shape
 hipError_t launch_update_rest(const SpmmArgs& a, int32_t n_rest, const int32_t* rest_rows, const UpdateArgs& upd,
                               hipStream_t s);
@@ -341,6 +343,8 @@ hipError_t launch_gemm_tn(int64_t n_rows, const float* X, int64_t ldx, int32_t d
 bool gemm_grad_usable(int64_t n_rows, int64_t ldx, int32_t d_in, int32_t d);
 hipError_t launch_gemm_grad(int64_t n_rows, const float* X, int64_t ldx, int32_t d_in, const float* S, int64_t lds_, int32_t d,
                             const float* W, int64_t ldw, float* dX, int64_t lddx, float* dW, int64_t lddw, float* partial, hipStream_t s);
+bool relu_bits_usable(int32_t d, const float* Yf, int64_t ldy);
+hipError_t launch_relu_bits(int64_t n, int32_t d, const float* Yf, int64_t ldy, uint2* bits, hipStream_t s);   // bits: [ceil(d / 64)][n]
 hipError_t launch_relu_mask(int64_t n, int32_t d, const float* G, int64_t ldg, const float* Yf, int64_t ldy, float* Gm,
                             int64_t ldo, hipStream_t s);
 hipError_t launch_transpose(int32_t rows, int32_t cols, const float* W, int64_t ldw, float* Wt, hipStream_t s);

@@ -941,6 +941,16 @@ static hcspmm_status reserve_panel_sums(hcspmm_plan* p, int32_t d, hipStream_t s
     return HCSPMM_OK;
 }
 
+// (the windows' distinct columns against their non-zeros say how much the rows of a window share; a scalar-only plan does
+// not count them and goes by its sample)
+static CsrHints csr_hints(const hcspmm_plan* p, bool beside)
+{
+    const int64_t nnz_scalar = p->nnz - (p->scalar_exec ? 0 : p->nnz_mfma), n_scalar = p->scalar_exec ? p->W : p->n_csr;
+    const int64_t cols_scalar = p->total_ncols - (p->scalar_exec ? 0 : p->mfma_ncols);
+    const bool scattered = !p->local && (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * cols_scalar > 6 * nnz_scalar);
+    return CsrHints{nnz_scalar, n_scalar * kH, scattered, p->long_row, beside, p->nnz};
+}
+
 static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStream_t stream,
                               hipEvent_t* ev = nullptr /* 5 events when timing stages */,
                               const UpdateArgs* upd = nullptr /* fuse the update stage where a tile stays on chip */,
@@ -1020,12 +1030,8 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
         HC_HIP(launch_mfma_small(a, p->n_mfma_small, p->mfma_small_desc, p->wcols, p->erc, s_small, upd));
         if (ev) HC_HIP(hipEventRecord(ev[2], stream));
     }
-    // (the windows' distinct columns against their non-zeros say how much the rows of a window share; a scalar-only plan does
-    // not count them and goes by its sample)
-    const int64_t nnz_scalar = p->nnz - (p->scalar_exec ? 0 : p->nnz_mfma), n_scalar = p->scalar_exec ? p->W : p->n_csr;
-    const int64_t cols_scalar = p->total_ncols - (p->scalar_exec ? 0 : p->mfma_ncols);
-    const bool scattered = !p->local && (p->opt.route_mode == HCSPMM_ROUTE_ALL_CSR || 10 * cols_scalar > 6 * nnz_scalar);
-    const CsrHints hints{nnz_scalar, n_scalar * kH, scattered, p->long_row, side && has_csr, p->nnz};
+    const int64_t n_scalar = p->scalar_exec ? p->W : p->n_csr;
+    const CsrHints hints = csr_hints(p, side && has_csr);
     const uint8_t* route = p->scalar_exec || p->n_mfma == 0 ? nullptr : p->route;
     if (upd && !windows_only)        // the fused launch walks every row: its tile tier also takes the shorter mid rows
         HC_HIP(launch_csr(a, p->n_segs, p->segs, partial, p->n_mid, p->mid_rows, n_scalar > 0 ? p->n_rows : 0, nullptr,
@@ -1733,7 +1739,7 @@ hcspmm_status hcspmm_aggregate_update(const hcspmm_plan* plan, const void* d_X, 
 
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// workspace of the backward pass: S | masked G | W^T | partial products of dW
+// workspace of the backward pass: S | masked G, or the mask in bits | W^T | partial products of dW
 struct BackwardLayout { size_t s_off, gm_off, wt_off, part_off, total; };
 
 static BackwardLayout backward_layout(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)
@@ -1745,6 +1751,27 @@ static BackwardLayout backward_layout(const hcspmm_plan* plan, int32_t d_in, int
     l.part_off = l.wt_off + align256((size_t)d_in * d_out * sizeof(float));
     l.total = l.part_off + align256((size_t)gemm_tn_spans(plan->n_rows, d_in, d_out) * d_in * d_out * sizeof(float));
     return l;
+}
+
+// Whether the backward pass's activation mask rides in the gather, as a bit per element that it looks up beside the rows of G, instead of
+// in a masked copy of G, which reads and writes G once more.  Each gathered row costs a request of its own for every 64 columns; rows of a
+// window that share columns find their bits in the same lines, scattered ones hardly, so the lines lie by degree and by the windows' distinct
+// columns (.70 of the non-zeros and less in communities, .77 and more in power laws).  Whole call, W of 32 columns, copy / bits, us:
+//   scattered     169,343 rows of 5, 64 columns: 79 / 71; 1 M of 5, 256: 1780 / 1613, of 8, 128: 1033 / 1021; but of 10: 1146 / 1174,
+//                 400,000 of 15, 128: 519 / 544; G of up to 64 MB in whole 128 columns: 100,000 of 10, 128: 104.6 / 98.5, of 21: level;
+//                 with columns of padding in the last 64 bits they lose (1 M of 8, 96: 788 / 817)
+//   communities   131,072 of 10, 128 columns: 122 / 107, of 23: 145 / 131, 64: 75.2 / 71.8, of 17, 256: 281 / 258; 8,192 of 10, 128: 26.1 / 24.0;
+//                 up to 64 columns, where one load asks for a row, not between the L2s of an XCD and of the chip (32,768 of 23, 64:
+//                 31.2 / 32.4); 36 and 68 columns lose (131,072 of 35, 36: 85 / 87; 250,048 of 20, 68: 211 / 218, but 132: 442 / 431, 200: 610 / 587)
+static bool mask_rides(const hcspmm_plan* plan, const SpmmArgs& a /* with the masked copy for X */, const float* G, int64_t ldg, const float* Yf, int64_t ldyf)
+{
+    if (plan->n_rows == 0 || plan->n_panels > 1 || !(plan->scalar_exec || plan->n_mfma == 0)) return false;
+    if (ldg != a.d || (uintptr_t)G % 128 != 0 || !relu_bits_usable(a.d, Yf, ldyf)) return false;     // (rows lie as those of the copy would)
+    const bool shared = plan->local || (plan->opt.route_mode != HCSPMM_ROUTE_ALL_CSR && 4 * plan->total_ncols <= 3 * plan->nnz);
+    if (a.d % 64 != 0 && (a.d < 96 || !shared)) return false;
+    const double mb = (double)plan->n_cols * a.d * 4 / (1 << 20);
+    const int64_t most = shared ? (a.d > 64 || mb >= 24.0 ? 30 : 12) : a.d % 128 == 0 && mb <= 64.0 ? 11 : 8;
+    return plan->nnz <= most * plan->n_rows && csr_mask_usable(a, csr_hints(plan, false));
 }
 
 size_t hcspmm_layer_backward_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)
@@ -1779,24 +1806,29 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
     float* Gm = reinterpret_cast<float*>(ws + l.gm_off);
     float* Wt = reinterpret_cast<float*>(ws + l.wt_off);
     float* part = reinterpret_cast<float*>(ws + l.part_off);
-    const float* G = static_cast<const float*>(d_G);
-    int64_t g_ld = ldg;
-    if (d_Yfwd && plan->n_cols > 0) {
-        HC_HIP(launch_relu_mask(plan->n_cols, d_out, G, ldg, static_cast<const float*>(d_Yfwd), ldyf, Gm, d_out, s));
-        G = Gm;
-        g_ld = d_out;
+    const float *G = static_cast<const float*>(d_G), *Yf = static_cast<const float*>(d_Yfwd);
+    const bool masked = d_Yfwd && plan->n_cols > 0;
+    SpmmArgs a{};
+    a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
+    a.X = masked ? Gm : G; a.ldx = masked ? d_out : ldg; a.d = d_out; a.x_dtype = HCSPMM_F32; a.Y = S; a.ldy = d_out; a.relu = 0;
+    // as in hcspmm_aggregate_update; the wave-per-window kernel neither stores S for dW nor applies the mask
+    UpdatePlace place = kUpdateApart;
+    if (plan->n_rows > 0 && d_dX) {
+        place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
+                : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
+                                                                 : update_place(plan, d_out, d_in, HCSPMM_F32, d_dW != nullptr);
+        if (place == kUpdateInWindows && (d_dW || mask_dx_by_x)) place = kUpdateApart;
+        if (place != kUpdateApart && !update_fusable(a)) place = kUpdateApart;
+    }
+    if (masked && place == kUpdateApart && mask_rides(plan, a, G, ldg, Yf, ldyf)) {
+        uint2* bits = reinterpret_cast<uint2*>(Gm);             // (8 bytes per row and 64 columns, of 36 columns and more)
+        HC_HIP(launch_relu_bits(plan->n_cols, d_out, Yf, ldyf, bits, s));
+        a.X = G; a.x_mask = bits;
+    } else if (masked) {
+        HC_HIP(launch_relu_mask(plan->n_cols, d_out, G, ldg, Yf, ldyf, Gm, d_out, s));
     }
     if (plan->n_rows > 0) {
-        SpmmArgs a{};
-        a.n_rows = plan->n_rows; a.n_cols = plan->n_cols; a.rowptr = plan->rowptr; a.colind = plan->colind; a.vals = plan->vals;
-        a.X = G; a.ldx = g_ld; a.d = d_out; a.x_dtype = HCSPMM_F32; a.Y = S; a.ldy = d_out; a.relu = 0;
         if (d_dX) {
-            // as in hcspmm_aggregate_update; the wave-per-window kernel neither stores S for dW nor applies the mask
-            UpdatePlace place = plan->opt.update_fusion == HCSPMM_UPDATE_FUSED   ? kUpdateEverywhere
-                                : plan->opt.update_fusion == HCSPMM_UPDATE_SPLIT ? kUpdateApart
-                                                                                 : update_place(plan, d_out, d_in, HCSPMM_F32, d_dW != nullptr);
-            if (place == kUpdateInWindows && (d_dW || mask_dx_by_x)) place = kUpdateApart;
-            if (place != kUpdateApart && !update_fusable(a)) place = kUpdateApart;
             if (place == kUpdateApart && d_dW && !mask_dx_by_x && gemm_grad_usable(plan->n_rows, ldx, d_in, d_out)) {
                 if ((st = run_spmm(plan, a, s)) != HCSPMM_OK) return st;
                 HC_HIP(launch_gemm_grad(plan->n_rows, static_cast<const float*>(d_X), ldx, d_in, S, d_out, d_out, static_cast<const float*>(d_W), ldw,

@@ -106,7 +106,10 @@ template <int XK> __device__ __forceinline__ float widened(const uint32_t* w, in
 // PANEL: a column panel's share of the rows -- each row's end is read from a.rowend, and results may be added to rows of fp32
 // sums.  (Kept out of the plain kernels, which have no scalar register to spare in 128-byte rows: power law, fp32, 32
 // columns, 39.7 -> 35.1 us.)
-template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL = false> struct Gather {
+// MASK: elements of X count where a.x_mask has their bit.  A lane of the group asks for the 64 bits of its non-zero's row and 64 columns,
+// once per 16 non-zeros and ahead of their X rows; the words are handed round like indices and values.
+template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL = false, bool MASK = false> struct Gather {
+    static_assert(!MASK || (XK == 0 && VEC == 4 && LANES_ == 16 && GROUP_ == 16 && !WIDE && !PANEL), "forms with a mask");
     static constexpr bool MANY = WIDE;                          // several rows to a group
     static constexpr int LANES = LANES_, GROUP = GROUP_, SPLIT = GROUP / LANES, STEPS = GROUP / SPLIT;
     static_assert((GROUP == 16 && (LANES == 16 || LANES == 8)) || (GROUP == 8 && LANES == 8), "forms");
@@ -129,6 +132,9 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
     uint32_t lane_off[NV];      // byte offset of this lane's vectors inside the slice
     int shift[NV];              // leading elements of a vector that belong to the lane to the left
     bool ok[NV];                // the vector has columns of the slice
+    const char* bits;           // MASK: the slice's first 64 columns of the mask (uniform), bytes to the next 64, this lane's first bit
+    size_t next_bits;
+    int bit;
 
     // columns [c0, c0 + w) of X, w <= COLS; a vector that would stick out of the row is moved left so that it ends at the
     // row's last column of the slice (the elements it then shares with its left neighbour are not stored)
@@ -137,6 +143,12 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
         const int lig = lig_ % LANES;
         X = static_cast<const char*>(a.X);
         ldxb = (uint64_t)a.ldx * ES;
+        if constexpr (MASK) {
+            const size_t block = (size_t)a.n_cols * sizeof(uint2);
+            bits = reinterpret_cast<const char*>(a.x_mask) + (size_t)(c0 / 64) * block;
+            next_bits = c0 + 64 < a.d ? block : 0;
+            bit = lig;
+        }
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int col = (v * LANES + lig) * VEC;
@@ -147,8 +159,8 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
             lane_off[v] = (uint32_t)(max(c0 + at, 0) * ES);
         }
     }
-    // what a lane keeps of a non-zero: byte offset of its X row (the column itself in the WIDE form)
-    __device__ __forceinline__ uint32_t key(int32_t c) const { return WIDE ? (uint32_t)c : (uint32_t)c * (uint32_t)ldxb; }
+    // what a lane keeps of a non-zero: byte offset of its X row (the column itself in the WIDE and MASK forms)
+    __device__ __forceinline__ uint32_t key(int32_t c) const { return WIDE || MASK ? (uint32_t)c : (uint32_t)c * (uint32_t)ldxb; }
 
     // step T's entry: slot T of the group, or slots 2T and 2T+1 for its two halves
     template <int T> static __device__ __forceinline__ uint32_t slot(uint32_t x)
@@ -166,9 +178,21 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
             else raw_load<BYTES>(X + (size_t)(b + lane_off[v]), x[v]);
         }
     }
-    template <int T> __device__ __forceinline__ void add(float val, const Raw<RAW> (&x)[NV], float (&acc)[N]) const
+    template <int T> __device__ __forceinline__ void add(float val, const Raw<RAW> (&x)[NV], float (&acc)[N], const uint2 (&m)[NV]) const
     {
         const float w = __uint_as_float(slot<T>(__float_as_uint(val)));
+        if constexpr (MASK) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const uint32_t lo = row_bcast<T>(m[v].x), hi = row_bcast<T>(m[v].y);
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    const uint32_t on = (uint32_t)__builtin_amdgcn_sbfe((int)(i < 2 ? lo : hi), bit + (i & 1) * 16, 1);     // all ones or zero
+                    acc[v * VEC + i] = fmaf(w, __uint_as_float(x[v].w[i] & on), acc[v * VEC + i]);
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
@@ -180,7 +204,7 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
     // 16-bit rows of a word per lane and less that take a wave or more each have little to widen and lose by it (bf16, order
     // fixed / left alone: 4,875 rows of 196, 32 columns 9.05 / 8.35 us, 6,627 of 137, 16 columns 8.27 / 7.90).
     static constexpr bool FIXED_WAVE = XK == 0 || BYTES > 4;
-    template <bool FIXED, int T0, int COUNT, class Next> __device__ __forceinline__ void steps(uint32_t key_, float val, float (&acc)[N], Next&& next) const
+    template <bool FIXED, int T0, int COUNT, class Next> __device__ __forceinline__ void steps(uint32_t key_, float val, float (&acc)[N], const uint2 (&m)[NV], Next&& next) const
     {
         Raw<RAW> x[COUNT][NV];
         unrolled<COUNT>([&](auto u) { this->template load<T0 + decltype(u)::value>(key_, x[decltype(u)::value]); });
@@ -189,7 +213,7 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
             next();
             if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
         }
-        unrolled<COUNT>([&](auto u) { this->template add<T0 + decltype(u)::value>(val, x[decltype(u)::value], acc); });
+        unrolled<COUNT>([&](auto u) { this->template add<T0 + decltype(u)::value>(val, x[decltype(u)::value], acc, m); });
     }
     // Up to GROUP non-zeros (cnt of them, uniform within the group), U steps at a time.  Slots past the row's end carry the
     // row's last column with value 0, so the loads carry no branches.
@@ -197,14 +221,21 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
     // mostly come from behind L2, would hold up X rows that hit it.
     template <bool FIXED = true, class Next> __device__ __forceinline__ void batch(uint32_t key_, float val, int cnt, float (&acc)[N], Next&& next) const
     {
+        uint2 m[NV] = {};
+        if constexpr (MASK) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) m[v] = *reinterpret_cast<const uint2*>(bits + v * next_bits + (size_t)(key_ * (uint32_t)sizeof(uint2)));
+            key_ *= (uint32_t)ldxb;
+            if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
+        }
         if constexpr (SPLIT == 2 && XK == 0) {
             // a wave whose groups all have more than half a batch left keeps the whole batch in flight (16-bit rows have twice
             // the accumulators and would spill)
-            if (__all(cnt > GROUP / 2)) { steps<FIXED, 0, STEPS>(key_, val, acc, next); return; }
+            if (__all(cnt > GROUP / 2)) { steps<FIXED, 0, STEPS>(key_, val, acc, m, next); return; }
         }
         unrolled<STEPS / U>([&](auto blk) {
             constexpr int T0 = decltype(blk)::value * U;
-            if (T0 == 0 || cnt > T0 * SPLIT) this->template steps<FIXED, T0, U>(key_, val, acc, next);
+            if (T0 == 0 || cnt > T0 * SPLIT) this->template steps<FIXED, T0, U>(key_, val, acc, m, next);
         });
     }
     // (key, value) of non-zero k of a row ending at e (k may run past the end: value 0, last column)
@@ -817,6 +848,21 @@ static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh, i
     return degree >= 40.0 && a.d >= 168 ? 2 : degree >= (f32 ? 15.0 : 28.0) ? 3 : 0;
 }
 
+static bool few_rows_form(const SpmmArgs& a, int n_slices) { return (int64_t)a.n_rows * n_slices <= (a.x_dtype == HCSPMM_F32 ? 4096 : 6144); }
+
+bool csr_mask_usable(const SpmmArgs& a, const CsrHints& hints)
+{
+    if (a.x_dtype != HCSPMM_F32 || a.d % 4 != 0 || a.d <= 32 || a.rowend || a.acc || hints.beside || hints.entries > ((int64_t)1 << 30) || tune().rpg >= 1) return false;
+    if ((int64_t)a.n_cols * (int64_t)sizeof(uint2) > INT32_MAX) return false;
+    SpmmArgs t = a;
+    int32_t slice_w;
+    const int n_slices = pick_slices(a, hints, slice_w);
+    if (n_slices > 1) t.d = slice_w;
+    const CsrShape sh = pick_shape(t, false);
+    if (pick_shape(a, false).wide || sh.vec != 4 || sh.lanes != 16 || sh.nv > 2 || (n_slices > 1 && slice_w % 64 != 0)) return false;
+    return !few_rows_form(a, n_slices) && (int64_t)a.n_rows * n_slices <= ((int64_t)1 << 26) && few_waves(a, hints, sh, t.d) == 0;
+}
+
 hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, float* partial, int32_t n_mid,
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
                       int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd)
@@ -853,7 +899,7 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
     // costs more than the shorter chains save (a group / a wave per row, us, fp32: 2,000 rows of 11, 96 columns: 6.7 / 5.1;
     // 3,000 of 21, 160 columns in two slices: 7.8 / 10.3; communities of 20, 7,936 rows, 128 columns: 7.4 / 11.1; bf16, 128
     // columns: 4,000 of 11: 6.6 / 5.9; 6,000 of 13: 7.1 / 6.7; 8,000 of 31: 8.1 / 8.9).
-    const bool few_rows = n_items > 0 && (int64_t)a.n_rows * n_slices <= (a.x_dtype == HCSPMM_F32 ? 4096 : 6144);
+    const bool few_rows = n_items > 0 && few_rows_form(a, n_slices);
     if (few_rows) {
         wk.n_mid = a.n_rows;
         wk.mid_rows = nullptr;
@@ -897,6 +943,12 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
 #define HC_LAUNCH_FEW_ROWS(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_csr_few_rows<Gather<XK, V, NVV, L, GR, false>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, r)
         HC_CSR_DISPATCH(HC_LAUNCH_FEW_ROWS)
 #undef HC_LAUNCH_FEW_ROWS
+        return hipGetLastError();
+    }
+    if (a.x_mask) {
+        if (most != 0 || sh.wide || sh.vec != 4 || sh.lanes != 16 || sh.group != 16 || sh.nv > 2 || few_rows) return hipErrorInvalidValue;   // see csr_mask_usable
+        if (sh.nv == 1) hipLaunchKernelGGL((k_csr<Gather<0, 4, 1, 16, 16, false, false, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a);
+        else hipLaunchKernelGGL((k_csr<Gather<0, 4, 2, 16, 16, false, false, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a);
         return hipGetLastError();
     }
     if (most > 0) {

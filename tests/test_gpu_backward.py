@@ -364,3 +364,46 @@ def test_fused_update_of_many_rows(din, dout, mode):
     assert_close(S[rows], S_ref, S_abs, TOL_F32, "S")
     ref = np.where(X[rows] > 0, S_ref @ W.astype(np.float64).T, 0.0)
     assert_close(dX[rows], ref, S_abs @ np.abs(W).astype(np.float64).T, TOL_F32, "masked dX")
+
+
+@pytest.mark.parametrize("kind,n,d", [("power", 4100, 64), ("power", 20011, 128), ("power", 5003, 256), ("blocks", 6016, 64), ("blocks", 6016, 96),
+                                      ("blocks", 8256, 100), ("blocks", 8256, 128), ("blocks", 5056, 132), ("blocks", 6016, 256)])
+def test_backward_mask_by_bits_equals_the_masked_copy(kind, n, d):
+    """Where the mask is looked up bit by bit beside the gathered rows, the products are those of the masked copy, which rows of G
+    of another pitch still take: the same terms in the same order, so bit for bit; hubs of a wave and of a segment each and more,
+    columns left over past the last 64, and masked elements of G that are not finite."""
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    if kind == "power":
+        g = gcn_normalise(chung_lu_graph(n, 6 * n, 2.0, seed=81, max_degree=n // 3))     # the longest row of 20,011 has several segments
+    else:
+        g = gcn_normalise(sbm_graph(n // 64, 64, 0.1, 4, seed=82))
+    assert g.nnz <= (8 if kind == "power" else 12) * n
+    X, W, G, Y = dense_normal(n, 48, seed=83), glorot_uniform(48, d, seed=84), dense_normal(n, d, seed=85), dense_normal(n, d, seed=86)
+    Y[::5] = 0.0
+    Y[3, :] = np.nan
+    dX, dW, S = run_backward(g, G, X, W, Y_fwd=Y, update_fusion=2)
+    check(g, G, X, W, dX, dW, S, Y_fwd=Y)
+    wild = G.copy()
+    wild[Y < -1.0] = np.inf
+    wild[~(Y > 0)] *= np.where(np.arange((~(Y > 0)).sum()) % 3 == 0, np.float32(np.nan), np.float32(1.0))
+    rp, ci, va = device_graph(g)
+    plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, rp, ci, va, d_hint=d, update_fusion=2)
+    ws = torch.empty(hc.hcspmm_layer_backward_workspace_bytes(plan, 48, d), dtype=torch.uint8, device="cuda")
+    out = []
+    for pad in (0, 4):
+        Gd = torch.full((n, d + pad), float("nan"), device="cuda")
+        Gd[:, :d] = torch.from_numpy(wild).cuda()
+        dx, dw = torch.empty((n, 48), device="cuda"), torch.empty((48, d), device="cuda")
+        hc.hcspmm_layer_backward(plan, Gd[:, :d], torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), dx, dw, ws, Y_fwd=torch.from_numpy(Y).cuda())
+        torch.cuda.synchronize()
+        out.append((dx, dw, ws[:n * d * 4].clone()))
+        if pad == 0:        # the route was taken: the bits of the first 64 columns lie behind S
+            at = (n * d * 4 + 255) // 256 * 256
+            halves = ws[at:at + 8 * n].view(torch.int16).cpu().numpy().reshape(n, 4).astype(np.int64)
+            bits = (halves[:, None, :] >> np.arange(16)[None, :, None]) & 1
+            assert np.array_equal(bits.reshape(n, 64) == 1, Y[:, :64] > 0)
+    plan.destroy()
+    assert torch.isfinite(out[0][0]).all()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
