@@ -823,7 +823,7 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
     return degree <= 16.0 && h.rows >= (row <= 64 ? 200000 : 1000000);
 }
 
-// Waves per SIMD that whole rows of more than 512 bytes of fp32, 256 of 16 bits, are held to on scattered matrices (0: what the
+// Waves per SIMD that whole rows of more than 512 bytes of fp32, 256 of 16 bits, are held to on scattered matrices, and others below (0: what the
 // registers allow, five to six).  The forms that read them ask for eight vectors per lane at once, and all those waves for more than the
 // L2s keep for each other.  Where rows have many non-zeros, which is where X rows are read again, fewer waves are ahead, and
 // where they have very many and are wide, two (all / three / two, us, power laws; fp32: 1 M rows of 20, 150 columns: 2428 / 2225 /
@@ -837,9 +837,21 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
 // In column panels, whose X rows are meant to stay in the L2s, 16-bit rows are held to three from 168 columns on and to two from 224
 // (all / three / two, us, bf16: 104,000 rows of 193, 136 columns: 533 / 559 / 675, 184: 713 / 690 / 753, 252: 1040 / 998 / 985; 66,576
 // of 180, 184: 415 / 395 / 409, 252: 603 / 577 / 551; f16 the same).
+// Scattered rows of one 16-byte vector per lane, whole or in slices: what all eight waves ask for at once is more than an XCD's L2, and from
+// 40 non-zeros per row and 36 MB of X on, where rows come back often enough, five waves find more of it there, from 60 on four (all / five /
+// four, us, fp32: 2.4 M rows of 51, 32 columns: 2116 / 2096 / 2089, 1 M of 43, 32: 649 / 639 / 635, of 51, 64: 1528 / 1525 / 1536, 300,000 of 43, 128: 698 / 688 /
+// 693, of 111, 64: 867 / 850 / 840, 400,000 of 76, 64: 838 / 817 / 807, 128: 1744 / 1710 / 1695; but 300,000 of 36, 32: 138 / 139 / 142, 1 M of 21, 32:
+// 312 / 326 / 347, 100,000 of 51, 64: 95 / 98 / 104; bf16: 1 M of 51, 64 columns: 816 / 795 / 786, 300,000 of 51, 64: 200 / 195 / 200, of 111, 128:
+// 895 / 862 / 841, 700,000 of 101, 64: 1058 / 1024 / 1003; but 1 M of 21, 64: 363 / 369 / 388).  Whole rows of up to 128 bytes of fp32 from 96 MB or
+// 70 non-zeros on (600,000 of 65, 24 columns: 610 / -- / 615, 300,000 of 42, 32: 163.0 / 163.7 / --).
 static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh, int32_t width)
 {
     const bool f32 = a.x_dtype == HCSPMM_F32;
+    if (sh.vec == (f32 ? 4 : 8) && sh.nv == 1 && sh.group == 16 && !sh.wide && !a.rowend && !h.beside && h.scattered) {
+        const double x_mb = (double)a.n_cols * a.d * (f32 ? 4 : 2) / (1 << 20);
+        if (h.nnz < 40 * h.rows || x_mb < 36.0 || (f32 && a.d <= 32 && x_mb < 96.0 && h.nnz < 70 * h.rows)) return 0;
+        return h.nnz < 60 * h.rows ? 5 : 4;
+    }
     if (sh.lanes != 16 || sh.vec * sh.nv != 16 || !(f32 || sh.vec == 8) || h.rows <= 0) return 0;
     if (a.rowend) return f32 || width < 168 ? 0 : width < 224 ? 3 : 2;
     const double degree = (double)h.nnz / (double)h.rows;
@@ -949,6 +961,19 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
         if (most != 0 || sh.wide || sh.vec != 4 || sh.lanes != 16 || sh.group != 16 || sh.nv > 2 || few_rows) return hipErrorInvalidValue;   // see csr_mask_usable
         if (sh.nv == 1) hipLaunchKernelGGL((k_csr<Gather<0, 4, 1, 16, 16, false, false, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a);
         else hipLaunchKernelGGL((k_csr<Gather<0, 4, 2, 16, 16, false, false, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a);
+        return hipGetLastError();
+    }
+    if (most > 3) {
+#define HC_LAUNCH_SOME(XK, V, L, MOST) hipLaunchKernelGGL((k_csr_few<Gather<XK, V, 1, L, 16, false>, MOST>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
+#define HC_LAUNCH_SOME_OF(XK, V)                                                                          \
+    if (sh.lanes == 8) { if (most == 4) HC_LAUNCH_SOME(XK, V, 8, 4); else HC_LAUNCH_SOME(XK, V, 8, 5); } \
+    else if (most == 4) HC_LAUNCH_SOME(XK, V, 16, 4);                                                    \
+    else HC_LAUNCH_SOME(XK, V, 16, 5)
+        if (a.x_dtype == HCSPMM_F32) { HC_LAUNCH_SOME_OF(0, 4); }
+        else if (a.x_dtype == HCSPMM_BF16) { HC_LAUNCH_SOME_OF(1, 8); }
+        else { HC_LAUNCH_SOME_OF(2, 8); }
+#undef HC_LAUNCH_SOME_OF
+#undef HC_LAUNCH_SOME
         return hipGetLastError();
     }
     if (most > 0) {

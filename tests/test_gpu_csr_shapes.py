@@ -192,3 +192,24 @@ def test_few_rows_with_long_ones(kind, n, d):
     ref, bound = oracle_pair(g, bits, **({} if kind is None else {"x_dtype": oracle.DT_BF16}))
     assert_close(Y[:, :d].cpu().numpy().astype(np.float64), ref, bound, 1e-5, "n=%d d=%d" % (n, d))
     assert bool((Y[:, d:] == -7.0).all())
+
+
+# long scattered rows of one 16-byte vector per lane on 36 MB of X and more: five waves per SIMD from 40 non-zeros per row on, four from 60
+# (up to 32 columns of fp32 from 70)
+@pytest.mark.parametrize("kind,d", [("f32", 20), ("f32", 32), ("f32", 47), ("f32", 128), ("bf16", 64), ("bf16", 100), ("f16", 62), ("f16", 128)])
+@pytest.mark.parametrize("degree", [40, 60, 70])
+def test_fewer_waves_for_long_scattered_rows(kind, d, degree):
+    es = 4 if kind == "f32" else 2
+    n_cols = (37 << 20) // (d * es)
+    lengths = np.full(5000, degree)
+    lengths[[0, 1, 2, 3, 4]] = [0, 1, 300, 1100, 5000]
+    g = short_rows(lengths, n_cols, d)
+    assert degree <= g.nnz / g.n_rows < degree + 20
+    X = np.random.default_rng(d).standard_normal((n_cols, d)).astype(np.float32)
+    code, bits = {"f32": (None, None), "bf16": (oracle.DT_BF16, to_bf16_bits), "f16": (oracle.DT_F16, to_f16_bits)}[kind]
+    if bits:
+        X = bits(X)
+    rows = np.unique(np.concatenate([np.arange(8), np.arange(8, 5000, 7), np.arange(4980, 5000)]))
+    Y, _ = gpu_spmm(g, X, 1, pad_y=d % 3, x_bits=kind if bits else None)
+    ref, bound = oracle_pair(g, X, rows=rows, x_dtype=code)
+    assert_close(Y[rows], ref, bound, 1e-5, "%s d=%d" % (kind, d))
