@@ -260,7 +260,7 @@ __device__ inline void store_tile(const v4f (&acc)[NG][VW], int lane, int32_t r0
             float y[VW];
 #pragma unroll
             for (int t = 0; t < VW; ++t) y[t] = acc[g][t][r];
-            out_store<VW>(Y, y_dtype, (int64_t)row * ldy + col0 + col, y, relu);
+            out_store<VW, false>(Y, y_dtype, (int64_t)row * ldy + col0 + col, y, relu);
         }
     }
 }
