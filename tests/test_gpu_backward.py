@@ -367,19 +367,23 @@ def test_fused_update_of_many_rows(din, dout, mode):
 
 
 @pytest.mark.parametrize("kind,n,d", [("power", 4100, 64), ("power", 20011, 128), ("power", 5003, 256), ("blocks", 6016, 64), ("blocks", 6016, 96),
-                                      ("blocks", 8256, 100), ("blocks", 8256, 128), ("blocks", 5056, 132), ("blocks", 6016, 256)])
+                                      ("blocks", 8256, 100), ("blocks", 8256, 128), ("blocks", 5056, 132), ("blocks", 6016, 256), ("oblong", 4500, 64), ("oblong", 9100, 128)])
 def test_backward_mask_by_bits_equals_the_masked_copy(kind, n, d):
     """Where the mask is looked up bit by bit beside the gathered rows, the products are those of the masked copy, which rows of G
     of another pitch still take: the same terms in the same order, so bit for bit; hubs of a wave and of a segment each and more,
     columns left over past the last 64, and masked elements of G that are not finite."""
     import torch
     import paper_2412_08902_amd.binding as hc
-    if kind == "power":
+    if kind == "oblong":        # as many rows again as columns, and a few; columns in no order, some twice in a row
+        rng = np.random.default_rng(80)
+        rowptr = np.concatenate([[0], np.cumsum(rng.integers(0, 13, 2 * n + 3))]).astype(np.int32)
+        g = CSRGraph(2 * n + 3, n, rowptr, rng.integers(0, n, rowptr[-1]).astype(np.int32), rng.standard_normal(rowptr[-1]).astype(np.float32))
+    elif kind == "power":
         g = gcn_normalise(chung_lu_graph(n, 6 * n, 2.0, seed=81, max_degree=n // 3))     # the longest row of 20,011 has several segments
     else:
         g = gcn_normalise(sbm_graph(n // 64, 64, 0.1, 4, seed=82))
-    assert g.nnz <= (8 if kind == "power" else 12) * n
-    X, W, G, Y = dense_normal(n, 48, seed=83), glorot_uniform(48, d, seed=84), dense_normal(n, d, seed=85), dense_normal(n, d, seed=86)
+    assert g.nnz <= (12 if kind == "blocks" else 8) * g.n_rows
+    X, W, G, Y = dense_normal(g.n_rows, 48, seed=83), glorot_uniform(48, d, seed=84), dense_normal(n, d, seed=85), dense_normal(n, d, seed=86)
     Y[::5] = 0.0
     Y[3, :] = np.nan
     dX, dW, S = run_backward(g, G, X, W, Y_fwd=Y, update_fusion=2)
@@ -391,15 +395,17 @@ def test_backward_mask_by_bits_equals_the_masked_copy(kind, n, d):
     plan = hc.hcspmm_prepare(g.n_rows, g.n_cols, rp, ci, va, d_hint=d, update_fusion=2)
     ws = torch.empty(hc.hcspmm_layer_backward_workspace_bytes(plan, 48, d), dtype=torch.uint8, device="cuda")
     out = []
+    Yd = torch.full((n, d + 8), float("nan"), device="cuda")
+    Yd[:, :d] = torch.from_numpy(Y).cuda()
     for pad in (0, 4):
         Gd = torch.full((n, d + pad), float("nan"), device="cuda")
         Gd[:, :d] = torch.from_numpy(wild).cuda()
-        dx, dw = torch.empty((n, 48), device="cuda"), torch.empty((48, d), device="cuda")
-        hc.hcspmm_layer_backward(plan, Gd[:, :d], torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), dx, dw, ws, Y_fwd=torch.from_numpy(Y).cuda())
+        dx, dw = torch.empty((g.n_rows, 48), device="cuda"), torch.empty((48, d), device="cuda")
+        hc.hcspmm_layer_backward(plan, Gd[:, :d], torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), dx, dw, ws, Y_fwd=Yd[:, :d])
         torch.cuda.synchronize()
-        out.append((dx, dw, ws[:n * d * 4].clone()))
+        out.append((dx, dw, ws[:g.n_rows * d * 4].clone()))
         if pad == 0:        # the route was taken: the bits of the first 64 columns lie behind S
-            at = (n * d * 4 + 255) // 256 * 256
+            at = (g.n_rows * d * 4 + 255) // 256 * 256
             halves = ws[at:at + 8 * n].view(torch.int16).cpu().numpy().reshape(n, 4).astype(np.int64)
             bits = (halves[:, None, :] >> np.arange(16)[None, :, None]) & 1
             assert np.array_equal(bits.reshape(n, 64) == 1, Y[:, :64] > 0)
