@@ -959,6 +959,7 @@ static hcspmm_status run_spmm(const hcspmm_plan* plan, const SpmmArgs& a, hipStr
                               bool acc_rows = false /* column panels may keep fp32 sums of a 16-bit output in a buffer of the plan */)
 {
     hcspmm_plan* p = const_cast<hcspmm_plan*>(plan);
+    if (a.x_mask && p->n_mfma > 0 && !p->scalar_exec) HC_HIP(hipErrorInvalidValue);      // (the matrix path looks at no mask; launch_csr refuses the other cases)
     if (!scratch_mem) {
         const hcspmm_status st = reserve_scratch(p, a.d, stream);
         if (st != HCSPMM_OK) return st;

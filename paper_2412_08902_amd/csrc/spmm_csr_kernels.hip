@@ -879,6 +879,8 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
                       const int32_t* mid_rows, int32_t n_items, const int32_t* row_list, const uint8_t* route,
                       int32_t mid_row, const CsrHints& hints, hipStream_t s, const UpdateArgs* upd)
 {
+    // a mask that no kernel of the launch looks at must not pass for one that was applied
+    if (a.x_mask && (upd || !csr_mask_usable(a, hints))) return hipErrorInvalidValue;
     const bool narrow = upd ? fused_narrow(a) : !a.rowend && narrow_rows(a, hints);
     CsrShape sh = pick_shape(a, narrow);
     // the other forms address indices and values, too, with 32-bit offsets from a uniform base: short rows are bound by the vector units as much as by
@@ -937,6 +939,14 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
 #define HC_LAUNCH_FEW_PANEL(XK, V, NVV, L, GR, W)                                                                                                     \
     if (most == 2) hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W, true>, 2>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a); \
     else hipLaunchKernelGGL((k_csr_few<Gather<XK, V, NVV, L, GR, W, true>, 3>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a)
+    if (a.x_mask) {
+        // (what csr_mask_usable has found, once more where the launch is chosen)
+        if (most != 0 || sh.wide || sh.vec != 4 || sh.lanes != 16 || sh.group != 16 || sh.nv > 2 || few_rows ||
+            (wk.grid.n_slices > 1 && wk.grid.slice_w % 64 != 0)) return hipErrorInvalidValue;
+        if (sh.nv == 1) hipLaunchKernelGGL((k_csr<Gather<0, 4, 1, 16, 16, false, false, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a);
+        else hipLaunchKernelGGL((k_csr<Gather<0, 4, 2, 16, 16, false, false, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a);
+        return hipGetLastError();
+    }
     if (a.rowend) {
         // panels are taken for rows of kPanelRowBytes and more: 16-byte vectors, two per lane at most (wider slices take turns)
         if (sh.vec != (a.x_dtype == HCSPMM_F32 ? 4 : 8)) return hipErrorInvalidValue;
@@ -955,12 +965,6 @@ hipError_t launch_csr(const SpmmArgs& a, int32_t n_segs, const Segment* segs, fl
 #define HC_LAUNCH_FEW_ROWS(XK, V, NVV, L, GR, W) hipLaunchKernelGGL((k_csr_few_rows<Gather<XK, V, NVV, L, GR, false>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, r)
         HC_CSR_DISPATCH(HC_LAUNCH_FEW_ROWS)
 #undef HC_LAUNCH_FEW_ROWS
-        return hipGetLastError();
-    }
-    if (a.x_mask) {
-        if (most != 0 || sh.wide || sh.vec != 4 || sh.lanes != 16 || sh.group != 16 || sh.nv > 2 || few_rows) return hipErrorInvalidValue;   // see csr_mask_usable
-        if (sh.nv == 1) hipLaunchKernelGGL((k_csr<Gather<0, 4, 1, 16, 16, false, false, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a);
-        else hipLaunchKernelGGL((k_csr<Gather<0, 4, 2, 16, 16, false, false, true>>), dim3((unsigned)wk.grid.blocks()), dim3(256), 0, s, wk, a);
         return hipGetLastError();
     }
     if (most > 3) {
