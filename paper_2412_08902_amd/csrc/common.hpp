@@ -243,7 +243,9 @@ __device__ inline uint32_t out16_pack(float lo, float hi, int y_dtype)
 // optional max(0, .).  The address is aligned for VEC fp32 elements when y_dtype is fp32 and for min(VEC, 4) 16-bit
 // elements otherwise (no 16-bit store is wider than 8 bytes).
 // BRANCH: without an activation nothing is spent on one (to select costs three instructions a value with or without; short rows of the scalar path
-// are bound by such, matrix tiles are not, and lose by the branch: 299,968 rows of 58, 208 -> 48 with an activation: 222.7 -> 224.3 us).
+// are bound by such).  Matrix tiles and the dense products' are not, and lose by the branch, behind which all their results wait: 299,968 rows of 58, 208 -> 48 with
+// an activation, select / branch: 222.7 / 224.3 us; products without one, by the kernel trace: 2,197 x 235 x 224 (k_gemm_split) 13.16 / 13.36 us, 3,559 x 128 x 112
+// (k_gemm_f32, the shortest of 600) 7.71 / 7.85, 5,625 x 103 x 48 6.50 / 6.62; large ones level.
 template <int VEC, bool BRANCH = true> __device__ inline void out_store(float* __restrict__ Y, int y_dtype, int64_t off, const float (&x)[VEC], int relu)
 {
     float y[VEC];
