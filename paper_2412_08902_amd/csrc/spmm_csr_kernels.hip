@@ -304,12 +304,12 @@ template <int XK, int VEC, int NV, int LANES_, int GROUP_, bool WIDE, bool PANEL
                 for (int i = 0; i < VEC; ++i) y[i] += t.v[i];
             }
             if (y_vec && shift[v] == 0) {
-                out_store<VEC>(a.Y, a.y_dtype, off, y, a.relu);
+                out_store<VEC, XK != 0>(a.Y, a.y_dtype, off, y, a.relu);
             } else {
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) {
                     const float one[1] = {y[i]};
-                    if (i >= shift[v]) out_store<1>(a.Y, a.y_dtype, off + i, one, a.relu);
+                    if (i >= shift[v]) out_store<1, XK != 0>(a.Y, a.y_dtype, off + i, one, a.relu);
                 }
             }
         }

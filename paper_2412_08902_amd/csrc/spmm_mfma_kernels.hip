@@ -260,7 +260,7 @@ __device__ inline void store_tile(const v4f (&acc)[NG][VW], int lane, int32_t r0
             float y[VW];
 #pragma unroll
             for (int t = 0; t < VW; ++t) y[t] = acc[g][t][r];
-            out_store<VW, false>(Y, y_dtype, (int64_t)row * ldy + col0 + col, y, relu);
+            out_store<VW>(Y, y_dtype, (int64_t)row * ldy + col0 + col, y, relu);
         }
     }
 }
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(256) void k_reduce_tiles(const MultiRow* __restrict
         float acc = 0.f;
         for (int q = 0; q < m.n_slots; ++q) acc += tile_partial[((int64_t)(m.first_slot + q) * kH + r) * a.d + c];
         const float one[1] = {acc};
-        out_store<1, false>(a.Y, a.y_dtype, row * a.ldy + c, one, a.relu);
+        out_store<1>(a.Y, a.y_dtype, row * a.ldy + c, one, a.relu);
     }
 }
 
