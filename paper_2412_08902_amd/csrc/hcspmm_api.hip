@@ -1764,7 +1764,21 @@ static BackwardLayout backward_layout(const hcspmm_plan* plan, int32_t d_in, int
 //   communities   131,072 of 10, 128 columns: 122 / 107, of 23: 145 / 131, 64: 75.2 / 71.8, of 17, 256: 281 / 258; 8,192 of 10, 128: 26.1 / 24.0;
 //                 up to 64 columns, where one load asks for a row, not between the L2s of an XCD and of the chip (32,768 of 23, 64:
 //                 31.2 / 32.4); 36 and 68 columns lose (131,072 of 35, 36: 85 / 87; 250,048 of 20, 68: 211 / 218, but 132: 442 / 431, 200: 610 / 587)
-static bool mask_rides(const hcspmm_plan* plan, const SpmmArgs& a /* with the masked copy for X */, const float* G, int64_t ldg, const float* Yf, int64_t ldyf)
+// What the copy costs falls with G, and a G of a few MB that has just been copied is in the L2s when it is gathered, as the caller's is not; how much then stays of what else
+// the call reads goes by X.  From 12 MB of G on (8 where rows are scattered) the bits are ahead whatever X (copy / bits, X of 144 columns: 24,064 rows of 5, 128 columns: 49.9 /
+// 48.2, 49,152 in communities of 11, 64: 53.3 / 51.9; but 16,384 of 22, 128: 42.9 / 43.2).  Below they lose behind wide X (4,480 of 10, 128, X of 144: 33.2 / 33.5, of 256: 35.9 /
+// 37.4; 8,192 of 8, 128, X of 96: 28.3 / 29.2) and win behind narrow ones from 2 MB on (of 48: 6,016 of 8, 128: 24.4 / 23.1; of up to 128 columns only up to 3 MB: 12,032 in communities
+// of 7, 64, X of 128: 24.7 / 23.2, 16,384 of 8: 27.3 / 27.9), at columns of padding not past 6 (16,384 in communities of 16, 132, X of 32: 37.7 / 38.5).  Smaller ones are level or a little
+// ahead with some thousand rows and six non-zeros to a row of G (6,016 in communities of 11, 64, X of 48: 18.9 / 18.6, 6,016 of 8: 20.0 / 19.9; but of 5: 19.5 / 20.1,
+// 2,112 of 10, 128: 20.4 / 20.7, 4,480 in communities of 11, 96: 19.8 / 20.0).
+static bool mask_rides_size(const hcspmm_plan* plan, int32_t d, int32_t d_in, bool shared, double mb)
+{
+    if (mb >= (shared ? 11.5 : 8.0)) return true;
+    if (d_in > 128 || (d % 64 != 0 && mb > 6.0)) return false;
+    if (mb >= 2.0) return d_in <= 64 || mb <= 3.0;
+    return d_in <= 64 && d % 64 == 0 && plan->n_cols >= 4000 && (shared || plan->nnz >= 6 * (int64_t)plan->n_cols);
+}
+static bool mask_rides(const hcspmm_plan* plan, const SpmmArgs& a /* with the masked copy for X */, int32_t d_in, const float* G, int64_t ldg, const float* Yf, int64_t ldyf)
 {
     if (plan->n_rows == 0 || plan->n_panels > 1 || !(plan->scalar_exec || plan->n_mfma == 0)) return false;
     if (ldg != a.d || (uintptr_t)G % 128 != 0 || !relu_bits_usable(a.d, Yf, ldyf)) return false;     // (rows lie as those of the copy would)
@@ -1772,7 +1786,7 @@ static bool mask_rides(const hcspmm_plan* plan, const SpmmArgs& a /* with the ma
     if (a.d % 64 != 0 && (a.d < 96 || !shared)) return false;
     const double mb = (double)plan->n_cols * a.d * 4 / (1 << 20);
     const int64_t most = shared ? (a.d > 64 || mb >= 24.0 ? 30 : 12) : a.d % 128 == 0 && mb <= 64.0 ? 11 : 8;
-    return plan->nnz <= most * plan->n_rows && csr_mask_usable(a, csr_hints(plan, false));
+    return plan->nnz <= most * plan->n_rows && mask_rides_size(plan, a.d, d_in, shared, mb) && csr_mask_usable(a, csr_hints(plan, false));
 }
 
 size_t hcspmm_layer_backward_workspace_bytes(const hcspmm_plan* plan, int32_t d_in, int32_t d_out)
@@ -1821,7 +1835,7 @@ hcspmm_status hcspmm_layer_backward(const hcspmm_plan* plan, const void* d_G, in
         if (place == kUpdateInWindows && (d_dW || mask_dx_by_x)) place = kUpdateApart;
         if (place != kUpdateApart && !update_fusable(a)) place = kUpdateApart;
     }
-    if (masked && place == kUpdateApart && mask_rides(plan, a, G, ldg, Yf, ldyf)) {
+    if (masked && place == kUpdateApart && mask_rides(plan, a, d_in, G, ldg, Yf, ldyf)) {
         uint2* bits = reinterpret_cast<uint2*>(Gm);             // (8 bytes per row and 64 columns, of 36 columns and more)
         HC_HIP(launch_relu_bits(plan->n_cols, d_out, Yf, ldyf, bits, s));
         a.X = G; a.x_mask = bits;

@@ -413,3 +413,25 @@ def test_backward_mask_by_bits_equals_the_masked_copy(kind, n, d):
     assert torch.isfinite(out[0][0]).all()
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# (rows and columns of G, columns of X) on both sides of the lines of mask_rides_size: the workspace holds the mask's bits behind S, or the masked copy
+@pytest.mark.parametrize("kind,n,d,d_in,bits", [("power", 4452, 128, 144, False), ("power", 4452, 128, 128, True), ("power", 8192, 128, 96, False), ("power", 8192, 128, 64, True),
+                                                ("power", 16384, 128, 144, True), ("power", 16383, 128, 144, False), ("power", 2999, 128, 48, False),
+                                                ("blocks", 12032, 64, 128, True), ("blocks", 12032, 64, 129, False), ("blocks", 12032, 132, 32, False), ("blocks", 11904, 132, 32, True),
+                                                ("blocks", 23616, 128, 160, True), ("blocks", 23488, 128, 160, False)])
+def test_backward_mask_by_bits_or_copy(kind, n, d, d_in, bits):
+    import torch
+    import paper_2412_08902_amd.binding as hc
+    g = gcn_normalise(chung_lu_graph(n, 5 * n // 2 * 2, 2.1, seed=91)) if kind == "power" else gcn_normalise(sbm_graph(n // 64, 64, 0.1, 4, seed=92))
+    X, W, G, Y = dense_normal(n, d_in, seed=93), glorot_uniform(d_in, d, seed=94), dense_normal(n, d, seed=95), dense_normal(n, d, seed=96)
+    plan = hc.hcspmm_prepare(n, n, *device_graph(g), d_hint=d, update_fusion=2)
+    ws = torch.empty(hc.hcspmm_layer_backward_workspace_bytes(plan, d_in, d), dtype=torch.uint8, device="cuda")
+    dX, dW = torch.empty((n, d_in), device="cuda"), torch.empty((d_in, d), device="cuda")
+    hc.hcspmm_layer_backward(plan, *(torch.from_numpy(a).cuda() for a in (G, X, W)), dX, dW, ws, Y_fwd=torch.from_numpy(Y).cuda())
+    torch.cuda.synchronize()
+    plan.destroy()
+    at = (n * d * 4 + 255) // 256 * 256
+    masked = np.where(Y > 0, G, np.float32(0))
+    assert np.array_equal(ws[at:at + 4 * n * d].view(torch.float32).cpu().numpy().reshape(n, d), masked) != bits
+    check(g, masked, X, W, dX.cpu().numpy().astype(np.float64), dW.cpu().numpy().astype(np.float64), ws[:n * d * 4].view(torch.float32).reshape(n, d).cpu().numpy().astype(np.float64))
