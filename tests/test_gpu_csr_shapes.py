@@ -213,3 +213,21 @@ def test_fewer_waves_for_long_scattered_rows(kind, d, degree):
     Y, _ = gpu_spmm(g, X, 1, pad_y=d % 3, x_bits=kind if bits else None)
     ref, bound = oracle_pair(g, X, rows=rows, x_dtype=code)
     assert_close(Y[rows], ref, bound, 1e-5, "%s d=%d" % (kind, d))
+
+
+# the same for 16-bit X with more rows than those that all take a wave (6,144 times the slices), so that rows of up to 64 non-zeros take a lane group each
+@pytest.mark.parametrize("kind,d", [("bf16", 64), ("bf16", 100), ("f16", 62), ("f16", 128)])
+@pytest.mark.parametrize("degree", [40, 60])
+def test_fewer_waves_for_short_rows_of_16_bit(kind, d, degree):
+    n, n_cols = 14000, (37 << 20) // (2 * d)
+    lengths = np.where(np.arange(n) % 2 == 0, degree, degree + 3)          # on both sides of 64 where degree is 60: 60 and 63, beside rows of a wave
+    lengths[:5] = [0, 1, 300, 1100, 5000]
+    lengths[5::16] = 66
+    g = short_rows(lengths, n_cols, d)
+    assert degree <= g.nnz / g.n_rows < degree + 20 and g.n_rows > 2 * 6144
+    code, bits = (oracle.DT_BF16, to_bf16_bits) if kind == "bf16" else (oracle.DT_F16, to_f16_bits)
+    X = bits(np.random.default_rng(d).standard_normal((n_cols, d)).astype(np.float32))
+    rows = np.unique(np.concatenate([np.arange(40), np.arange(40, n, 13), np.arange(n - 40, n)]))
+    Y, _ = gpu_spmm(g, X, 1, pad_y=d % 3, x_bits=kind)
+    ref, bound = oracle_pair(g, X, rows=rows, x_dtype=code)
+    assert_close(Y[rows], ref, bound, 1e-5, "%s d=%d" % (kind, d))
