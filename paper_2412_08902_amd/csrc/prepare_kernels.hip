@@ -854,7 +854,7 @@ __global__ __launch_bounds__(1024) void k_pre_count_big(Prep p)
 
 // Few windows to count (all of a small matrix, or the touched ones): one launch for all sizes, where by class the larger
 // windows wait for the small ones' launch and a few workgroups walk their list.  Windows of up to kCountTinyCap non-zeros take 256 threads each, two to a
-// workgroup.  The larger ones, often neighbours, belong to the first kFewBig workgroups, every kFewBig-th window to each, which look for
+// workgroup.  The larger ones, often neighbours, belong to the first n_big workgroups (few_big), every n_big-th window to each, which look for
 // theirs among up to 32 and take them one by one with a bitmap.  LDS for that grows with the columns up to 32 KB (matrices of up to 2^20 columns: four passes).
 // Bound by its longest chain of reads and by launches, so everything that does not depend on an answer from memory is asked for at once, and neither
 // k_pre_validate (ALL) nor k_pre_select is launched.
@@ -866,12 +866,11 @@ __global__ __launch_bounds__(1024) void k_pre_count_big(Prep p)
 constexpr int kFewWindows = 2048, kFewCols = 1 << 20, kFewThreads = 512, kFewBig = 64, kFewMostWords = 8192;
 static_assert(kFewWindows <= 32 * kFewBig && kFewCols <= 4 * 32 * kFewMostWords, "windows to a workgroup, passes");
 template <bool ALL>
-__global__ __launch_bounds__(kFewThreads) void k_pre_count_few(Prep p, int32_t n_count, int words)
+__global__ __launch_bounds__(kFewThreads) void k_pre_count_few(Prep p, int32_t n_count, int32_t n_big, int words)
 {
     constexpr int SMALL = kFewThreads / 256;
     extern __shared__ int32_t few_lds[];                        // SMALL * 2 * kCountTinyCap or `words`, whichever is more
     __shared__ int smem[kFewThreads / 64];
-    const int32_t n_big = min(n_count, kFewBig);
     const bool big = (int32_t)blockIdx.x < n_big;
     const int tid = threadIdx.x & 255, group = threadIdx.x >> 8;
     const int32_t i = big ? (int32_t)blockIdx.x + (int32_t)(threadIdx.x & 31) * n_big : ((int32_t)blockIdx.x - n_big) * SMALL + group;
@@ -1235,6 +1234,15 @@ __global__ __launch_bounds__(256) void k_pre_windows(Prep p, int32_t* __restrict
     else big[(uint32_t)(hi >> 32) + (uint32_t)(ex >> 48)] = w;
 }
 
+// How many of k_pre_count_few's workgroups are for the larger windows, by the matrix's non-zeros per window.  Each counts its own one by one, so graphs whose windows are
+// mostly large want many (64 / 256 / 512 of them, whole calls, us, power laws: 9,913 rows of 210: 100.9 / 85.3 / 82.7, 20,000 of 120: 84.0 / 68.5 / 66.1, 100,000
+// of 100 with 700 rows changed: 248 / 226 / 226; 32,000 of 60: 74.4 / 64.1 / 64.3, 8,000 of 60: 52.8 / 52.0 / 52.8), others few, since every one looks for its own before
+// it may leave (16,934 of 14: 57.2 / 57.5 / 57.7).
+static int32_t few_big(const Prep& p)
+{
+    return p.nnz <= 256 * (int64_t)p.W ? kFewBig : p.nnz <= 1024 * (int64_t)p.W ? 4 * kFewBig : 8 * kFewBig;
+}
+
 // Whether k_pre_count_few counts the windows.
 static bool prep_counts_few(const Prep& p, int32_t n_touched)
 {
@@ -1258,9 +1266,10 @@ hipError_t launch_prep(const Prep& p_, int32_t n_touched, hipStream_t s)
             constexpr int per = kFewThreads / 256;
             const int words = std::min((p.n_cols - 1) / 32 + 1, kFewMostWords);
             const size_t lds = (size_t)std::max(words, per * 2 * kCountTinyCap) * sizeof(int32_t);
-            const dim3 grid((unsigned)(std::min<int64_t>(n_count, kFewBig) + (n_count + per - 1) / per));
-            if (p.touched) hipLaunchKernelGGL(k_pre_count_few<false>, grid, dim3(kFewThreads), lds, s, p, (int32_t)n_count, words);
-            else hipLaunchKernelGGL(k_pre_count_few<true>, grid, dim3(kFewThreads), lds, s, p, (int32_t)n_count, words);
+            const int32_t n_big = (int32_t)std::min<int64_t>(n_count, few_big(p));
+            const dim3 grid((unsigned)(n_big + (n_count + per - 1) / per));
+            if (p.touched) hipLaunchKernelGGL(k_pre_count_few<false>, grid, dim3(kFewThreads), lds, s, p, (int32_t)n_count, n_big, words);
+            else hipLaunchKernelGGL(k_pre_count_few<true>, grid, dim3(kFewThreads), lds, s, p, (int32_t)n_count, n_big, words);
         } else {
             if (n_count > 0) hipLaunchKernelGGL(k_pre_count, dim3((unsigned)n_count), dim3(256), 0, s, p);
             // windows beyond the small set's capacity; how many there are only the device knows, so the grids are bounded by

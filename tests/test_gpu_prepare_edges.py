@@ -263,3 +263,20 @@ def test_unsound_offsets_of_few_windows(row, value):
     with pytest.raises(hc.HcspmmError) as e:
         hc.hcspmm_prepare(1600, 300, rp, ci, va)
     assert e.value.status == hc.HCSPMM_EBADCSR and "rowptr" in str(e.value) and "column" not in str(e.value)
+
+
+# more workgroups for the larger windows where a matrix has many of them: 256 from 257 non-zeros per window on, 512 from 1,025 on; fewer windows than those,
+# as many, and several to a workgroup, with small and empty ones between
+@pytest.mark.parametrize("per_window", [256, 257, 1024, 1025, 2500])
+@pytest.mark.parametrize("windows", [63, 256, 257, 513, 1100])
+def test_many_larger_windows(per_window, windows):
+    rng = np.random.default_rng(windows + per_window)
+    share = rng.choice([0.0, 0.3, 1.0, 1.7], windows)
+    sizes = np.floor(share * per_window).astype(np.int64)
+    sizes[-1] = max(0, per_window * windows - sizes[:-1].sum())   # exactly the average
+    while sizes.sum() > per_window * windows:
+        big = sizes.argmax()
+        sizes[big] -= min(sizes[big], sizes.sum() - per_window * windows)
+    lengths = np.repeat(sizes // 16, 16)
+    lengths[::16] += sizes % 16
+    check_plan(ragged(lengths, 5000, windows), 3, sel_coef=[1, 300, -328])
