@@ -243,8 +243,8 @@ __device__ inline uint32_t out16_pack(float lo, float hi, int y_dtype)
 // optional max(0, .).  The address is aligned for VEC fp32 elements when y_dtype is fp32 and for min(VEC, 4) 16-bit
 // elements otherwise (no 16-bit store is wider than 8 bytes).
 // BRANCH: without an activation nothing is spent on one.  To select costs three instructions a value with or without, which rows of 16-bit X on the scalar
-// path are bound by (select / branch, us: communities, 131,072 rows of 20, bf16, 64 columns: 22.5 / 21.8, 65,536 of 13 behind a product: 24.5 / 24.4; power law, 100,000 of
-// 7: 14.0 / 13.7).  fp32 rows, which need nothing widened, are level or lose (communities, 32 columns: 20.16 / 20.14; power law, 300,000 of 6, 8 columns: 18.97 / 19.10,
+// path are bound by, one vector to a lane (select / branch, us: communities, 131,072 rows of 20, bf16, 64 columns: 22.5 / 21.8, 65,536 of 13 behind a product: 24.5 / 24.4; power law, 100,000 of
+// 7: 14.0 / 13.7; but two vectors, 662,778 of 10, 144: 315.5 / 320.4).  fp32 rows, which need nothing widened, are level or lose (communities, 32 columns: 20.16 / 20.14; power law, 300,000 of 6, 8 columns: 18.97 / 19.10,
 // 20,641 of 6, 32 columns and a product: 18.5 / 18.6).  Matrix tiles and the dense products lose too, whose results all wait behind the branch: 299,968 rows of 58, 208 -> 48
 // with an activation: 222.7 / 224.3; without one, by the kernel trace, 2,197 x 235 x 224 (k_gemm_split): 13.16 / 13.36, 3,559 x 128 x 112 (k_gemm_f32, the
 // shortest of 600): 7.71 / 7.85, 5,625 x 103 x 48: 6.50 / 6.62; large ones level.
