@@ -838,11 +838,12 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
 // (all / three / two, us, bf16: 104,000 rows of 193, 136 columns: 533 / 559 / 675, 184: 713 / 690 / 753, 252: 1040 / 998 / 985; 66,576
 // of 180, 184: 415 / 395 / 409, 252: 603 / 577 / 551; f16 the same).
 // Scattered rows of one 16-byte vector per lane, whole or in slices: what all eight waves ask for at once is more than an XCD's L2, and from
-// 40 non-zeros per row and 36 MB of X on, where rows come back often enough, five waves find more of it there, from 60 on four (all / five /
-// four, us, fp32: 2.4 M rows of 51, 32 columns: 2116 / 2096 / 2089, 1 M of 43, 32: 649 / 639 / 635, of 51, 64: 1528 / 1525 / 1536, 300,000 of 43, 128: 698 / 688 /
+// 40 non-zeros per row and 36 MB of X on, where rows come back often enough, five waves find more of it there, from 60 on four, rows of up to 64 columns of 16 bits from 85 on
+// (all / five / four, us, fp32: 2.4 M rows of 51, 32 columns: 2116 / 2096 / 2089, 1 M of 43, 32: 649 / 639 / 635, of 51, 64: 1528 / 1525 / 1536, 300,000 of 43, 128: 698 / 688 /
 // 693, of 111, 64: 867 / 850 / 840, 400,000 of 76, 64: 838 / 817 / 807, 128: 1744 / 1710 / 1695; but 300,000 of 36, 32: 138 / 139 / 142, 1 M of 21, 32:
-// 312 / 326 / 347, 100,000 of 51, 64: 95 / 98 / 104; bf16: 1 M of 51, 64 columns: 816 / 795 / 786, 300,000 of 51, 64: 200 / 195 / 200, of 111, 128:
-// 895 / 862 / 841, 700,000 of 101, 64: 1058 / 1024 / 1003; but 1 M of 21, 64: 363 / 369 / 388).  Whole rows of up to 128 bytes of fp32 from 96 MB or
+// 312 / 326 / 347, 100,000 of 51, 64: 95 / 98 / 104; bf16: 1 M of 51, 64 columns: 816 / 795 / 786, 300,000 of 51, 64: 200 / 195 / 200, 400,000 of 61, 64: 306 / 300 / 308, of 76: 386 / 376 / 379, 700,000 of 90, 64: 873 / 846 /
+// 844, 300,000 of 111, 128: 895 / 862 / 841,
+// 700,000 of 101, 64: 1058 / 1024 / 1003; but 1 M of 21, 64: 363 / 369 / 388).  Whole rows of up to 128 bytes of fp32 from 96 MB or
 // 70 non-zeros on (600,000 of 65, 24 columns: 610 / -- / 615, 300,000 of 42, 32: 163.0 / 163.7 / --).
 static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh, int32_t width)
 {
@@ -850,7 +851,7 @@ static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh, i
     if (sh.vec == (f32 ? 4 : 8) && sh.nv == 1 && sh.group == 16 && !sh.wide && !a.rowend && !h.beside && h.scattered) {
         const double x_mb = (double)a.n_cols * a.d * (f32 ? 4 : 2) / (1 << 20);
         if (h.nnz < 40 * h.rows || x_mb < 36.0 || (f32 && a.d <= 32 && x_mb < 96.0 && h.nnz < 70 * h.rows)) return 0;
-        return h.nnz < 60 * h.rows ? 5 : 4;
+        return h.nnz < (f32 || sh.lanes == 16 ? 60 : 85) * h.rows ? 5 : 4;
     }
     if (sh.lanes != 16 || sh.vec * sh.nv != 16 || !(f32 || sh.vec == 8) || h.rows <= 0) return 0;
     if (a.rowend) return f32 || width < 168 ? 0 : width < 224 ? 3 : 2;
