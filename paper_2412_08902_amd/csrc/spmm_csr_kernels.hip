@@ -844,13 +844,15 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
 // 312 / 326 / 347, 100,000 of 51, 64: 95 / 98 / 104; bf16: 1 M of 51, 64 columns: 816 / 795 / 786, 300,000 of 51, 64: 200 / 195 / 200, 400,000 of 61, 64: 306 / 300 / 308, of 76: 386 / 376 / 379, 700,000 of 90, 64: 873 / 846 /
 // 844, 300,000 of 111, 128: 895 / 862 / 841,
 // 700,000 of 101, 64: 1058 / 1024 / 1003; but 1 M of 21, 64: 363 / 369 / 388).  Whole rows of up to 128 bytes of fp32 from 96 MB or
-// 70 non-zeros on (600,000 of 65, 24 columns: 610 / -- / 615, 300,000 of 42, 32: 163.0 / 163.7 / --).
+// 70 non-zeros on (600,000 of 65, 24 columns: 610 / -- / 615, 300,000 of 42, 32: 163.0 / 163.7 / --), fp32 rows of more than 64 from 60 non-zeros on only (beside
+// communities of half the rows, 431,072 of 42, 128: 799 / 809 / --, 300,000 of 42, 128, another graph than above: 634 / 637 / --).
 static int few_waves(const SpmmArgs& a, const CsrHints& h, const CsrShape& sh, int32_t width)
 {
     const bool f32 = a.x_dtype == HCSPMM_F32;
     if (sh.vec == (f32 ? 4 : 8) && sh.nv == 1 && sh.group == 16 && !sh.wide && !a.rowend && !h.beside && h.scattered) {
         const double x_mb = (double)a.n_cols * a.d * (f32 ? 4 : 2) / (1 << 20);
         if (h.nnz < 40 * h.rows || x_mb < 36.0 || (f32 && a.d <= 32 && x_mb < 96.0 && h.nnz < 70 * h.rows)) return 0;
+        if (f32 && a.d > 64 && h.nnz < 60 * h.rows) return 0;
         return h.nnz < (f32 || sh.lanes == 16 ? 60 : 85) * h.rows ? 5 : 4;
     }
     if (sh.lanes != 16 || sh.vec * sh.nv != 16 || !(f32 || sh.vec == 8) || h.rows <= 0) return 0;
