@@ -396,7 +396,7 @@ hipError_t launch_unique_big(int32_t n_big, const int32_t* big_list, int32_t n_r
 }
 
 // ------------------------------------------------------------------------------------------------
-// From the CSR arrays to a plan's launch tables in five to seven launches and one read-back.
+// From the CSR arrays to a plan's launch tables in three to seven launches and one read-back.
 //
 // A preparation's work is small (a medium graph: ~40 us of kernels), so launches and synchronisations are what it costs.
 // (27 launches, three-kernel scans over arrays of flags and six read-backs took 240 us on 17,000 rows and 490 us on

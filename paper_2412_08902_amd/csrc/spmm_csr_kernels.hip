@@ -839,7 +839,7 @@ static bool narrow_rows(const SpmmArgs& a, const CsrHints& h)
 // of 180, 184: 415 / 395 / 409, 252: 603 / 577 / 551; f16 the same).
 // Scattered rows of one 16-byte vector per lane, whole or in slices: what all eight waves ask for at once is more than an XCD's L2, and from
 // 40 non-zeros per row and 36 MB of X on, where rows come back often enough, five waves find more of it there, from 60 on four, rows of up to 64 columns of 16 bits from 85 on
-// (all / five / four, us, fp32: 2.4 M rows of 51, 32 columns: 2116 / 2096 / 2089, 1 M of 43, 32: 649 / 639 / 635, of 51, 64: 1528 / 1525 / 1536, 300,000 of 43, 128: 698 / 688 /
+// (all / five / four, us, fp32: 2.4 M rows of 51, 32 columns: 2116 / 2096 / 2089 (five: 1.1 % fewer bytes behind L2, hits 19.7 -> 20.0 %), 1 M of 43, 32: 649 / 639 / 635, of 51, 64: 1528 / 1525 / 1536, 300,000 of 43, 128: 698 / 688 /
 // 693, of 111, 64: 867 / 850 / 840, 400,000 of 76, 64: 838 / 817 / 807, 128: 1744 / 1710 / 1695; but 300,000 of 36, 32: 138 / 139 / 142, 1 M of 21, 32:
 // 312 / 326 / 347, 100,000 of 51, 64: 95 / 98 / 104; bf16: 1 M of 51, 64 columns: 816 / 795 / 786, 300,000 of 51, 64: 200 / 195 / 200, 400,000 of 61, 64: 306 / 300 / 308, of 76: 386 / 376 / 379, 700,000 of 90, 64: 873 / 846 /
 // 844, 300,000 of 111, 128: 895 / 862 / 841,

@@ -72,7 +72,7 @@ CASES = [(9000, 12, 32, 16, "f32", False),                      # one line eithe
          # bf16 X on the bf16 units, W in LDS (up to 256 of depth): from 16,384 rows on, one column tile from 49,152; K around its slabs, ends of tiles
          (16383, 18, 256, 64, "bf16", True), (16384, 18, 256, 64, "bf16", True), (16385, 18, 250, 64, "bf16", True), (16399, 18, 191, 33, "bf16", True),
          (49151, 12, 128, 16, "bf16", True), (49153, 12, 128, 15, "bf16", True), (16400, 18, 222, 80, "bf16", True), (49185, 3, 96, 1, "bf16", True),
-         # ... (before that, and beyond 256 of depth, from 65,536 rows on): K around its slabs of 32, one to four column tiles, two groups of them
+         # ... the same from 65,536 rows on, and the last two beyond 256 of depth: K around the slabs of 32, one to four column tiles, two groups of them
          (65600, 2, 130, 47, "bf16", True), (65536, 2, 65, 16, "bf16", True),
          (65541, 2, 159, 31, "bf16", True), (65536, 2, 288, 95, "bf16", True), (65537, 2, 322, 128, "bf16", True)]
 
